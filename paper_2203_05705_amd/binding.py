@@ -1,9 +1,11 @@
-"""ctypes binding of libard.so: argument marshalling only.
+"""Binding of libard.so: argument marshalling only.
 
 Function names follow the C ABI (``include/ard.h``) without the ``ard_`` prefix.
 Tensors are torch CUDA tensors used purely as device memory; every computation
-runs in the library's HIP kernels.  If the library has not been built the first
-call raises -- there is no fallback path.
+runs in the library's HIP kernels.  The calls a training step issues come from the
+extension ``_ardcall`` (``csrc/pyhost.cpp``), the others go through ctypes.  If the
+library or the extension has not been built the first call raises -- there is no
+fallback path.
 """
 from __future__ import annotations
 
@@ -37,41 +39,47 @@ class CPattern(C.Structure):
                 ("d_colptr", C.c_void_p), ("d_csc_rows", C.c_void_p)]
 
 
-class Pattern:
-    """Host description of a dropout pattern (keeps the tensors it points to alive)."""
+try:
+    from . import _ardcall
+except ImportError as e:   # not built: the names below are looked up in __getattr__, which says so
+    _ardcall, _missing = None, e
 
-    def __init__(self, kind=PAT_NONE, dp=1, b=1, tile_r=0, tile_c=0, keep: Optional[torch.Tensor] = None,
-                 count: Optional[int] = None, lists: Optional[dict] = None):
-        self.kind, self.dp, self.b, self.tile_r, self.tile_c = kind, dp, b, tile_r, tile_c
-        self.keep = keep
-        self.count = (0 if keep is None else int(keep.numel())) if count is None else count
-        self.lists = lists
+if _ardcall is not None:
+    _ardcall.configure(LIB_PATH, ArdError, torch._C._cuda_getCurrentRawStream)
+    from ._ardcall import (batch, compact_weight, conv_bwd_blocks, conv_bwd_data, conv_bwd_rows, conv_bwd_weight,  # noqa: F401
+                           conv_fwd, conv_fwd_blocks, conv_fwd_rows, conv_select, drop_gemm_bwd_data,
+                           drop_gemm_bwd_weight, drop_gemm_bwd_weight_static, drop_gemm_fwd, lstm_bwd, lstm_fwd,
+                           sens_block_pattern, sens_predict, sens_row_pattern)
 
-    @staticmethod
-    def row(dp, b):
-        return Pattern(PAT_ROW, dp, b)
+    class Pattern(_ardcall.PatternBase):
+        """Host description of a dropout pattern (keeps the tensors it points to alive):
+        Pattern(kind, dp, b, tile_r, tile_c, keep, count, lists), or Pattern.row(dp, b),
+        Pattern.tile(dp, b, tile_r, tile_c, lists=None), Pattern.list(keep, count=None)."""
 
-    @staticmethod
-    def tile(dp, b, tile_r, tile_c, lists=None):
-        return Pattern(PAT_TILE, dp, b, tile_r, tile_c, lists=lists)
+        @staticmethod
+        def list(keep: torch.Tensor, count=None):
+            assert keep.dtype == torch.int32 and keep.is_cuda
+            return Pattern(PAT_LIST, keep=keep, count=count)
 
-    @staticmethod
-    def list(keep: torch.Tensor, count=None):
-        assert keep.dtype == torch.int32 and keep.is_cuda
-        return Pattern(PAT_LIST, keep=keep, count=count)
+        def c(self) -> CPattern:
+            p = CPattern(self.kind, self.dp, self.b, self.tile_r, self.tile_c, self.count,
+                         None, None, None, None, None)
+            if self.kind == PAT_LIST and self.keep is not None:
+                p.d_keep = self.keep.data_ptr()
+            if self.kind == PAT_TILE and self.lists:
+                p.d_keep = self.lists["keep"].data_ptr()
+                p.d_mask = self.lists["mask"].data_ptr()
+                p.d_rowptr = self.lists["rowptr"].data_ptr()
+                p.d_colptr = self.lists["colptr"].data_ptr()
+                p.d_csc_rows = self.lists["csc_rows"].data_ptr()
+            return p
 
-    def c(self) -> CPattern:
-        p = CPattern(self.kind, self.dp, self.b, self.tile_r, self.tile_c, self.count,
-                     None, None, None, None, None)
-        if self.kind == PAT_LIST and self.keep is not None:
-            p.d_keep = self.keep.data_ptr()
-        if self.kind == PAT_TILE and self.lists:
-            p.d_keep = self.lists["keep"].data_ptr()
-            p.d_mask = self.lists["mask"].data_ptr()
-            p.d_rowptr = self.lists["rowptr"].data_ptr()
-            p.d_colptr = self.lists["colptr"].data_ptr()
-            p.d_csc_rows = self.lists["csc_rows"].data_ptr()
-        return p
+
+def __getattr__(name):
+    if _ardcall is None and not name.startswith("_"):
+        raise RuntimeError(f"the extension _ardcall is missing ({_missing}): build it with "
+                           "`python -m paper_2203_05705_amd.build` (or __graft_entry__.build()); there is no fallback path")
+    raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
 
 
 _lib = None
@@ -156,7 +164,7 @@ def _stream(stream):
     return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
-def _pref(p: Optional[Pattern]):
+def _pref(p: "Optional[Pattern]"):
     if p is None:
         return None, None
     cp = p.c()
@@ -176,6 +184,7 @@ def set_output_allocator(fn=None):
     guard bands; returns the previous allocator."""
     global _ALLOC
     prev, _ALLOC = _ALLOC, (torch.empty if fn is None else fn)
+    _ardcall.set_allocator(None if _ALLOC is torch.empty else _ALLOC)
     return prev
 
 
@@ -224,7 +233,7 @@ def prune_schedule(n_epochs: int, total: float, mean: float, var: float, lam: fl
 
 # ---- device entry points ---------------------------------------------------------
 
-def pattern_gen(pat: Pattern, rows: int, cols: int = 0, device="cuda", stream=None) -> dict:
+def pattern_gen(pat: "Pattern", rows: int, cols: int = 0, device="cuda", stream=None) -> dict:
     """Mask, kept list, count (and tile offsets) as device tensors."""
     cp, ref = _pref(pat)
     if pat.kind == PAT_TILE:
@@ -263,7 +272,7 @@ def _workspace(nbytes: int, device, ws: Optional[torch.Tensor]):
     return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
 
 
-def kept_count(pat: Optional[Pattern], units: int) -> int:
+def kept_count(pat: "Optional[Pattern]", units: int) -> int:
     """Number of kept units of a ROW / LIST / NONE pattern over `units` (asked of the library)."""
     _, r = _pref(pat)
     n = lib().ard_kept_count(r, units)
@@ -283,120 +292,6 @@ def pad_compact(t: torch.Tensor) -> torch.Tensor:
     out = torch.zeros((B, pad8(n)), dtype=t.dtype, device=t.device)
     out[:, :n] = t
     return out
-
-
-def _check_compact(t, count, what):
-    if t.shape[1] != pad8(count) or not t.is_contiguous():
-        raise ValueError(f"{what}: a compact activation has pad8(kept)={pad8(count)} contiguous columns, got {tuple(t.shape)}")
-
-
-def compact_weight(W, pat_out=None, pat_in=None, out=None, stream=None):
-    """Wc[pad8(O') x pad8(I')]: W[kept o, kept i] in the top-left corner, zeros elsewhere."""
-    _dev(W)
-    O, I = W.shape
-    Ok, Ik = kept_count(pat_out, O), kept_count(pat_in, I)
-    Wc = _out((pad8(Ok), pad8(Ik)), W.dtype, W.device) if out is None else out
-    co, ro = _pref(pat_out)
-    ci, ri = _pref(pat_in)
-    _check(lib().ard_compact_weight(_dtype_code(W), I, O, W.data_ptr(), Wc.data_ptr(), ro, ri, _stream(stream)))
-    return Wc
-
-
-def drop_gemm_fwd(X, W, pat_out=None, pat_in=None, alpha=1.0, relu=False, flags=0, out=None, ws=None, stream=None,
-                  I=None, O=None):
-    """Y = X . W^T under the patterns.  With layout flags pass the full sizes I / O explicitly."""
-    _dev(X), _dev(W)
-    B = X.shape[0]
-    I = (W.shape[1] if not flags & W_COMPACT else None) if I is None else I
-    O = (W.shape[0] if not flags & W_COMPACT else None) if O is None else O
-    assert I is not None and O is not None, "pass I and O with ARD_W_COMPACT"
-    dt = _dtype_code(X)
-    Oc = pad8(kept_count(pat_out, O)) if flags & OUT_COMPACT else O
-    if flags & IN_COMPACT:
-        _check_compact(X, kept_count(pat_in, I), "X")
-    Y = _out((B, Oc), X.dtype, X.device) if out is None else out
-    co, ro = _pref(pat_out)
-    ci, ri = _pref(pat_in)
-    ws = _workspace(gemm_workspace_bytes(dt, B, I, O, pat_out, pat_in), X.device, ws)
-    _check(lib().ard_drop_gemm_fwd(dt, B, I, O, X.data_ptr(), W.data_ptr(), Y.data_ptr(), ro, ri,
-                                   float(alpha), int(bool(relu)), int(flags), ws.data_ptr(), ws.numel(), _stream(stream)))
-    return Y
-
-
-def drop_gemm_bwd_data(dY, W, pat_out=None, pat_in=None, alpha=1.0, relu_src=None, flags=0, out=None, ws=None,
-                       stream=None, I=None, O=None):
-    _dev(dY), _dev(W)
-    B = dY.shape[0]
-    I = (W.shape[1] if not flags & W_COMPACT else None) if I is None else I
-    O = (W.shape[0] if not flags & W_COMPACT else None) if O is None else O
-    assert I is not None and O is not None, "pass I and O with ARD_W_COMPACT"
-    dt = _dtype_code(dY)
-    Ic = pad8(kept_count(pat_in, I)) if flags & IN_COMPACT else I
-    if flags & OUT_COMPACT:
-        _check_compact(dY, kept_count(pat_out, O), "dY")
-    dX = _out((B, Ic), dY.dtype, dY.device) if out is None else out
-    co, ro = _pref(pat_out)
-    ci, ri = _pref(pat_in)
-    ws = _workspace(gemm_workspace_bytes(dt, B, I, O, pat_out, pat_in), dY.device, ws)
-    _check(lib().ard_drop_gemm_bwd_data(dt, B, I, O, dY.data_ptr(), W.data_ptr(), dX.data_ptr(), ro, ri,
-                                        float(alpha), _ptr(relu_src), int(flags), ws.data_ptr(), ws.numel(),
-                                        _stream(stream)))
-    return dX
-
-
-def drop_gemm_bwd_weight(dY, X, pat_out=None, pat_in=None, alpha=1.0, beta=0.0, flags=0, out=None, ws=None,
-                         stream=None, I=None, O=None):
-    _dev(dY), _dev(X)
-    B = dY.shape[0]
-    O = dY.shape[1] if O is None else O
-    I = X.shape[1] if I is None else I
-    dt = _dtype_code(dY)
-    if flags & OUT_COMPACT:
-        _check_compact(dY, kept_count(pat_out, O), "dY")
-    if flags & IN_COMPACT:
-        _check_compact(X, kept_count(pat_in, I), "X")
-    shape = (pad8(kept_count(pat_out, O)), pad8(kept_count(pat_in, I))) if flags & DW_COMPACT else (O, I)
-    dW = _out(shape, dY.dtype, dY.device) if out is None else out
-    co, ro = _pref(pat_out)
-    ci, ri = _pref(pat_in)
-    ws = _workspace(gemm_workspace_bytes(dt, B, I, O, pat_out, pat_in), dY.device, ws)
-    _check(lib().ard_drop_gemm_bwd_weight(dt, B, I, O, dY.data_ptr(), X.data_ptr(), dW.data_ptr(), ro, ri,
-                                          float(alpha), float(beta), int(flags), ws.data_ptr(), ws.numel(),
-                                          _stream(stream)))
-    return dW
-
-
-def drop_gemm_bwd_weight_static(dY, X, pat_out, pat_in, out, alpha=1.0, beta=0.0, flags=0, stream=None, I=None, O=None):
-    """The weight gradient on the library's own scratch: the caller passes every tensor, output included,
-    and nothing is allocated here or in the library."""
-    _dev(dY), _dev(X), _dev(out)
-    O = dY.shape[1] if O is None else O
-    I = X.shape[1] if I is None else I
-    co, ro = _pref(pat_out)
-    ci, ri = _pref(pat_in)
-    _check(lib().ard_drop_gemm_bwd_weight_static(_dtype_code(dY), dY.shape[0], I, O, dY.data_ptr(), X.data_ptr(),
-                                                 out.data_ptr(), ro, ri, float(alpha), float(beta), int(flags),
-                                                 _stream(stream)))
-    return out
-
-
-class batch:
-    """Context manager: the library calls made inside are recorded and issued as one grouped launch on
-    leaving it (they must be independent of each other and use separate workspaces)."""
-
-    def __init__(self, stream=None):
-        self.stream = stream
-
-    def __enter__(self):
-        _check(lib().ard_batch_begin())
-        return self
-
-    def __exit__(self, exc_type, exc, tb):
-        if exc_type is not None:
-            lib().ard_batch_abort()
-            return False
-        _check(lib().ard_batch_launch(_stream(self.stream)))
-        return False
 
 
 def relu_bwd(dY, Y, out=None, stream=None):
@@ -420,42 +315,6 @@ def lstm_status_offset(dtype_code, T, B, I, H, pat=None):
     return None if off == (1 << 64) - 1 else off
 
 
-def lstm_fwd(x, W, pat=None, ws=None, stream=None, out=None):
-    """x[T,B,I], W[4H, I+H] -> (h[T,B,H] dtype, c[T,B,H] fp32, gates[T,B,4H] fp32); out: reuse such a triple."""
-    _dev(x), _dev(W)
-    T, B, I = x.shape
-    H = W.shape[0] // 4
-    assert W.shape == (4 * H, I + H)
-    dt = _dtype_code(x)
-    if out is not None:
-        h, c, gates = out
-    else:
-        h = _out((T, B, H), x.dtype, x.device)
-        c = _out((T, B, H), torch.float32, x.device)
-        gates = _out((T, B, 4 * H), torch.float32, x.device)
-    cp, r = _pref(pat)
-    ws = _workspace(lstm_workspace_bytes(dt, T, B, I, H, pat), x.device, ws)
-    _check(lib().ard_lstm_fwd(dt, T, B, I, H, x.data_ptr(), W.data_ptr(), r, h.data_ptr(), c.data_ptr(),
-                              gates.data_ptr(), ws.data_ptr(), ws.numel(), _stream(stream)))
-    return h, c, gates
-
-
-def lstm_bwd(x, W, pat, h, c, gates, dh, ws=None, stream=None, out=None):
-    """Returns (dx[T,B,I], dW[4H, I+H]) in the storage dtype; out: reuse such a pair."""
-    for t in (x, W, h, c, gates, dh):
-        _dev(t)
-    T, B, I = x.shape
-    H = W.shape[0] // 4
-    dt = _dtype_code(x)
-    dx, dW = out if out is not None else (_out(x.shape, x.dtype, x.device), _out(W.shape, W.dtype, W.device))
-    cp, r = _pref(pat)
-    ws = _workspace(lstm_workspace_bytes(dt, T, B, I, H, pat), x.device, ws)
-    _check(lib().ard_lstm_bwd(dt, T, B, I, H, x.data_ptr(), W.data_ptr(), r, h.data_ptr(), c.data_ptr(),
-                              gates.data_ptr(), dh.data_ptr(), dx.data_ptr(), dW.data_ptr(), ws.data_ptr(),
-                              ws.numel(), _stream(stream)))
-    return dx, dW
-
-
 # ---- convolution with dropped input feature maps ---------------------------------------------
 
 def conv_workspace_bytes(dtype_code, N, C, H, W, Cout, kh, kw, stride, pad) -> int:
@@ -474,152 +333,9 @@ def fmap_drop_conv(mode, shape, dtype_code, Cout, ksize, stride, pad, rate=0.0, 
                                     _ptr(score), ws.data_ptr(), ws.numel(), _stream(stream)))
 
 
-def conv_select(A, rate, Cout=1, ksize=(3, 3), stride=1, pad=1, ws=None, stream=None, out=None):
-    """Sensitivity scores and channel selection: dict(mask, keep, count, score) (out: reuse such a dict)."""
-    _dev(A)
-    N, Cc, H, W = A.shape
-    if out is None:
-        out = dict(mask=_out((Cc,), torch.uint8, A.device),
-                   keep=torch.full((Cc,), -1, dtype=torch.int32, device=A.device),
-                   count=torch.zeros(1, dtype=torch.int32, device=A.device),
-                   score=_out((Cc,), torch.int64, A.device))
-    fmap_drop_conv(CONV_SELECT, A.shape, _dtype_code(A), Cout, ksize, stride, pad, rate=rate, A=A, mask=out["mask"],
-                   keep=out["keep"], count=out["count"], score=out["score"], ws=ws, stream=stream)
-    return out
-
-
 def sens_regions(shape, ksize, stride, pad, x, y=0):
     """(rows, row_bands, col_blocks) of the input matrix of one image under x-by-y regions."""
     N, Cc, H, W = shape
     r, rb, cb = C.c_int32(), C.c_int32(), C.c_int32()
     _check(lib().ard_sens_regions(N, Cc, H, W, ksize[0], ksize[1], stride, pad, x, y, C.byref(r), C.byref(rb), C.byref(cb)))
     return r.value, rb.value, cb.value
-
-
-def sens_predict(A, ksize, stride, pad, x, y, k_permille, t_permille, threshold, seed, iteration, stream=None):
-    """Region-level sensitivity prediction: dict(count, samples, sens), each [N, RB, CB] on the device."""
-    _dev(A)
-    N = A.shape[0]
-    _, RB, CB = sens_regions(A.shape, ksize, stride, pad, x, y)
-    out = dict(count=_out((N, RB, CB), torch.int32, A.device), samples=_out((N, RB, CB), torch.int32, A.device),
-               sens=_out((N, RB, CB), torch.uint8, A.device))
-    _check(lib().ard_sens_predict(_dtype_code(A), N, A.shape[1], A.shape[2], A.shape[3], ksize[0], ksize[1], stride, pad, x, y,
-                                  k_permille, t_permille, float(threshold), seed, iteration, A.data_ptr(),
-                                  out["count"].data_ptr(), out["samples"].data_ptr(), out["sens"].data_ptr(), _stream(stream)))
-    return out
-
-
-def sens_row_pattern(sens, rows, x, m, n, seed, iteration, stream=None):
-    """Row-based pattern from the per-band sensitivity sens[N, RB, 1]: dict(mask[N*rows], keep, count)."""
-    _dev(sens)
-    N = sens.shape[0]
-    out = dict(mask=_out((N * rows,), torch.uint8, sens.device),
-               keep=torch.full((N * rows,), -1, dtype=torch.int32, device=sens.device),
-               count=torch.zeros(1, dtype=torch.int32, device=sens.device))
-    _check(lib().ard_sens_row_pattern(N, rows, x, sens.data_ptr(), float(m), float(n), seed, iteration, out["mask"].data_ptr(),
-                                      out["keep"].data_ptr(), out["count"].data_ptr(), _stream(stream)))
-    return out
-
-
-def sens_block_pattern(pred, balance, m, n, seed, iteration, stream=None):
-    """Block-based pattern from ard_sens_predict's outputs: dict(sens (balanced), keep), each [N, RB, CB]."""
-    N, RB, CB = pred["sens"].shape
-    dev = pred["sens"].device
-    out = dict(sens=_out((N, RB, CB), torch.uint8, dev), keep=_out((N, RB, CB), torch.uint8, dev))
-    _check(lib().ard_sens_block_pattern(N, RB, CB, pred["count"].data_ptr(), pred["samples"].data_ptr(), pred["sens"].data_ptr(),
-                                        int(bool(balance)), float(m), float(n), seed, iteration, out["sens"].data_ptr(),
-                                        out["keep"].data_ptr(), _stream(stream)))
-    return out
-
-
-def conv_fwd_rows(A, Wt, row_pat, n_keep, stride=1, pad=1, ws=None, stream=None, out=None):
-    """Forward convolution over the kept output positions of a row pattern (dict from sens_row_pattern)."""
-    _dev(A), _dev(Wt)
-    N, Cc, H, W = A.shape
-    Cout, _, kh, kw = Wt.shape
-    Ho, Wo = _out_hw(H, W, (kh, kw), stride, pad)
-    Y = _out((N, Cout, Ho, Wo), A.dtype, A.device) if out is None else out
-    fmap_drop_conv(CONV_FWD_ROWS, A.shape, _dtype_code(A), Cout, (kh, kw), stride, pad, n_keep=n_keep, A=A, Wt=Wt, out=Y,
-                   keep=row_pat["keep"], mask=row_pat["mask"], ws=ws, stream=stream)
-    return Y
-
-
-def conv_fwd_blocks(A, Wt, block_keep, x, y, stride=1, pad=1, ws=None, stream=None, out=None):
-    """Forward convolution under a block pattern (block_keep from sens_block_pattern, uint8 [N*RB*CB])."""
-    _dev(A), _dev(Wt), _dev(block_keep)
-    N, Cc, H, W = A.shape
-    Cout, _, kh, kw = Wt.shape
-    Ho, Wo = _out_hw(H, W, (kh, kw), stride, pad)
-    Y = _out((N, Cout, Ho, Wo), A.dtype, A.device) if out is None else out
-    dt = _dtype_code(A)
-    ws = _workspace(conv_workspace_bytes(dt, N, Cc, H, W, Cout, kh, kw, stride, pad), A.device, ws)
-    _check(lib().ard_conv_fwd_blocks(dt, N, Cc, H, W, Cout, kh, kw, stride, pad, int(x), int(y), A.data_ptr(), Wt.data_ptr(),
-                                     block_keep.data_ptr(), Y.data_ptr(), ws.data_ptr(), ws.numel(), _stream(stream)))
-    return Y
-
-
-def conv_bwd_blocks(dY, A, Wt, block_keep, x, y, stride=1, pad=1, ws=None, stream=None, out=None):
-    """Gradients (dA, dWt) of conv_fwd_blocks."""
-    _dev(dY), _dev(A), _dev(Wt), _dev(block_keep)
-    N, Cc, H, W = A.shape
-    Cout, _, kh, kw = Wt.shape
-    dA, dWt = out if out is not None else (_out(A.shape, A.dtype, A.device), _out(Wt.shape, Wt.dtype, Wt.device))
-    dt = _dtype_code(A)
-    ws = _workspace(conv_workspace_bytes(dt, N, Cc, H, W, Cout, kh, kw, stride, pad), A.device, ws)
-    for mode, o in ((CONV_BWD_DATA, dA), (CONV_BWD_WEIGHT, dWt)):
-        _check(lib().ard_conv_bwd_blocks(mode, dt, N, Cc, H, W, Cout, kh, kw, stride, pad, int(x), int(y), A.data_ptr(),
-                                         Wt.data_ptr(), dY.data_ptr(), block_keep.data_ptr(), o.data_ptr(), ws.data_ptr(),
-                                         ws.numel(), _stream(stream)))
-    return dA, dWt
-
-
-def conv_bwd_rows(dY, A, Wt, row_pat, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0):
-    """Gradients (dA, dWt) of conv_fwd_rows: gradient arriving on dropped output positions counts as zero.
-    reuse: CONV_REUSE_* flags for the weight gradient (grids that conv_fwd_rows and the data gradient left in ws)."""
-    _dev(dY), _dev(A), _dev(Wt)
-    Cout, _, kh, kw = Wt.shape
-    dA, dWt = out if out is not None else (_out(A.shape, A.dtype, A.device), _out(Wt.shape, Wt.dtype, Wt.device))
-    dt = _dtype_code(A)
-    fmap_drop_conv(CONV_BWD_DATA_ROWS, A.shape, dt, Cout, (kh, kw), stride, pad, Wt=Wt, dY=dY, out=dA, mask=row_pat["mask"],
-                   ws=ws, stream=stream)
-    fmap_drop_conv(CONV_BWD_WEIGHT_ROWS | reuse, A.shape, dt, Cout, (kh, kw), stride, pad, A=A, dY=dY, out=dWt, mask=row_pat["mask"],
-                   ws=ws, stream=stream)
-    return dA, dWt
-
-
-def _out_hw(H, W, ksize, stride, pad):
-    ho, wo = lib().ard_conv_out_size(H, ksize[0], stride, pad), lib().ard_conv_out_size(W, ksize[1], stride, pad)
-    if ho < 0 or wo < 0:
-        _check(min(ho, wo))
-    return ho, wo
-
-
-def conv_fwd(A, Wt, keep, n_keep, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0):
-    _dev(A), _dev(Wt)
-    N, Cc, H, W = A.shape
-    Cout, _, kh, kw = Wt.shape
-    Ho, Wo = _out_hw(H, W, (kh, kw), stride, pad)
-    Y = _out((N, Cout, Ho, Wo), A.dtype, A.device) if out is None else out
-    fmap_drop_conv(CONV_FWD | reuse, A.shape, _dtype_code(A), Cout, (kh, kw), stride, pad, n_keep=n_keep, A=A, Wt=Wt, out=Y,
-                   keep=keep, ws=ws, stream=stream)
-    return Y
-
-
-def conv_bwd_data(dY, Wt, keep, n_keep, in_hw, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0):
-    _dev(dY), _dev(Wt)
-    N = dY.shape[0]
-    Cout, Cc, kh, kw = Wt.shape
-    dA = _out((N, Cc, in_hw[0], in_hw[1]), dY.dtype, dY.device) if out is None else out
-    fmap_drop_conv(CONV_BWD_DATA | reuse, dA.shape, _dtype_code(dY), Cout, (kh, kw), stride, pad, n_keep=n_keep, Wt=Wt, dY=dY,
-                   out=dA, keep=keep, ws=ws, stream=stream)
-    return dA
-
-
-def conv_bwd_weight(dY, A, keep, n_keep, ksize=(3, 3), stride=1, pad=1, ws=None, stream=None, out=None, reuse=0):
-    _dev(dY), _dev(A)
-    N, Cc, H, W = A.shape
-    Cout = dY.shape[1]
-    dW = _out((Cout, Cc, ksize[0], ksize[1]), A.dtype, A.device) if out is None else out
-    fmap_drop_conv(CONV_BWD_WEIGHT | reuse, A.shape, _dtype_code(A), Cout, ksize, stride, pad, n_keep=n_keep, A=A, dY=dY,
-                   out=dW, keep=keep, ws=ws, stream=stream)
-    return dW

@@ -1,15 +1,18 @@
-"""Builds libard.so (the C-ABI HIP library) in-tree with hipcc for gfx950."""
+"""Builds libard.so (the C-ABI HIP library) in-tree with hipcc for gfx950, and the CPython extension
+_ardcall.so (argument marshalling for binding.py) with g++."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libard.so")
+EXT = os.path.join(HERE, "_ardcall.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
 HIPCC_FLAGS = [
@@ -75,6 +78,26 @@ def build_library(verbose: bool = True, jobs: int = 8, host_sanitizers: bool = F
     return lib
 
 
+def build_extension(verbose: bool = True) -> str:
+    """Compile csrc/pyhost.cpp to _ardcall.so next to this file (host code: torch's own headers and libraries,
+    no HIP).  Always recompiles."""
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    tmp = EXT + ".tmp"
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(tdir, "include"), "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "pyhost.cpp"), "-o", tmp,
+           "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on pyhost.cpp:\n{r.stderr}")
+    os.replace(tmp, EXT)
+    if verbose:
+        print(f"[build] linked {EXT}", flush=True)
+    return EXT
+
+
 if __name__ == "__main__":
+    build_extension()
     build_library(host_sanitizers="--host-sanitizers" in sys.argv[1:])
     sys.exit(0)
