@@ -173,9 +173,9 @@ static FastDiv fast_div(uint32_t d) {
   const uint64_t m = ((1ull << 32) * ((1ull << l) - d)) / d + 1;
   return FastDiv{(uint32_t)m, l - 1};
 }
-static __device__ __forceinline__ uint32_t fdiv(uint32_t a, const FastDiv& f) {
+__host__ __device__ static __forceinline__ uint32_t fdiv(uint32_t a, const FastDiv& f) {
   if (f.shift < 0) return a;
-  const uint32_t t = __umulhi(a, f.mul);
+  const uint32_t t = (uint32_t)(((uint64_t)a * f.mul) >> 32);
   return (t + ((a - t) >> 1)) >> f.shift;
 }
 

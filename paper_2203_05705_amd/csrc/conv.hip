@@ -1195,7 +1195,7 @@ static int32_t conv_grid_gemm(const uint16_t* Wp, int rows, int K, const uint16_
   const long tiles = (long)F.tiles_m * F.tiles_n;
   if (tiles >= (1L << 24)) return fail(ARD_ESHAPE, "convolution too large for one launch");
   F.total_tiles = (int)tiles;
-  F.group_m = direct_group_m(F.total_tiles);
+  set_bands(F, direct_group_m(F.total_tiles));
   const int grid = direct_plain_grid(F.total_tiles);
   if (bm == 256 && bn == 256) return launch_direct_kernel<true, true, 256, 256, 8, 1>(F, grid, stream);
   if (bm == 256) return launch_direct_kernel<true, true, 256, 128, 8, 1>(F, grid, stream);
@@ -1363,7 +1363,7 @@ static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, c
   F.M = a.Cout;
   F.N = Nn;
   F.cv = ConvMap{0, 0, Hg * Wg, Wg, Cpa, a.kw, 0, 0, nullptr, 0, nullptr, 0, -1};
-  F.group_m = direct_group_m(F.total_tiles);
+  set_bands(F, direct_group_m(F.total_tiles));
   st = big ? launch_direct_kernel<false, false, 256, 128, 8, 2>(F, direct_plain_grid(F.total_tiles), stream)
            : launch_direct_kernel<false, false, 128, 128, 4, 2>(F, direct_plain_grid(F.total_tiles), stream);
   if (st) return st;

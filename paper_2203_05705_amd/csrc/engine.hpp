@@ -529,4 +529,11 @@ int32_t run_gemm(int32_t dtype, bool a_kc, bool b_kc, GemmParams P, int max_bn, 
 bool run_gemm_partials(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P, hipStream_t stream, void* part,
                        size_t part_bytes, int* splits, int32_t* status);
 
+// fp32 products on the register-direct kernels (fast32.hip); false: not taken, nothing launched
+bool try_f32(bool a_kc, bool b_kc, const GemmParams& P, void* ws, size_t ws_bytes, hipStream_t stream, int32_t& st);
+bool try_f32_tile(int op, int B, int I, int O, int TR, int TC, const ard_pattern& pat, const void* Ap, const void* Bp, void* Cp,
+                  float alpha, int relu, const void* relu_src, hipStream_t stream, int32_t& st);
+// whether those kernels read a weight through these maps themselves (no gathered copy wanted)
+bool f32_takes_maps(const Axis& out, const Axis& in);
+
 }  // namespace ard

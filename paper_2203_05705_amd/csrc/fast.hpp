@@ -35,6 +35,7 @@
 // contraction map = identity or a block progression with block size a multiple of 64.
 #pragma once
 #include <type_traits>
+#include <utility>
 
 #include "engine.hpp"
 
@@ -75,34 +76,49 @@ struct ConvMap {
   int pix_pairs;  // list entries 2i, 2i+1 are pixels 2m, 2m+1 of one image (or both padding): stored as one word
 };
 
+// (What every launch reads comes first and is fetched in one go, see touch_args; the class tables come last.)
 struct FastParams {
   const uint16_t* A;
   const uint16_t* B;
   uint16_t* C;
   int lda, ldb, ldc;
-  long a_elems, b_elems;  // elements the caller owns behind A / B: what the loaders may touch (host-side proof)
-  Axis am, bn, k;  // plain mode: compact -> physical rows of A (M), rows of B (N), contraction
-  ClassTab tab;
-  int c_rows_mapped, c_cols_mapped;  // output rows / columns go through the M / N map (else identity)
-  float alpha, beta;
-  int relu, out_f32;
-  const uint16_t* relu_src;  // optional, same layout as C
-  float* part;               // != NULL: write fp32 partial sums part[split][M][N] instead of C
-  int splits;
+  int ncls;               // tab.ncls (set_bands)
   int M, N, tiles_m, tiles_n, group_m, total_tiles;
-  ConvMap cv;  // MODE 1 / 2 of the kernel only
+  int splits;
+  FastDiv tiles_div, band_div;  // total_tiles, group_m * tiles_n (set_bands)
+  float alpha, beta;
+  Axis am, bn, k;  // plain mode: compact -> physical rows of A (M), rows of B (N), contraction
+  float* part;               // != NULL: write fp32 partial sums part[split][M][N] instead of C
+  const uint16_t* relu_src;  // optional, same layout as C
+  int relu, out_f32;
+  int c_rows_mapped, c_cols_mapped;  // output rows / columns go through the M / N map (else identity)
+  // Scattering epilogue (row patterns without compact outputs): the tile's results go through
+  // LDS and are written, with the dropped positions it owns as +0.0, through these affine maps.
+  int scatter;
+  int scatter_rows_only;  // the tile writes its kept rows only (a separate pass zeroes the dropped rows)
+  Axis srm, scn;
   // MODE 1, optional (block-based sensitivity-aware pattern, Section 5.2.2): the column tile t of the
   // product contracts over the kb_cnt[t] 64-wide blocks kb_list[t * kb_stride ...] of the contraction only
   // (at most 128 of them); entries of cv.pix may then be -1 (padding of a tile: nothing is stored).
   const int* kb_list;
   const int* kb_cnt;
   int kb_stride;
-  // Scattering epilogue (row patterns without compact outputs): the tile's results go through
-  // LDS and are written, with the dropped positions it owns as +0.0, through these affine maps.
-  int scatter, scatter_vec;
-  int scatter_rows_only;  // the tile writes its kept rows only (a separate pass zeroes the dropped rows)
-  Axis srm, scn;
+  ConvMap cv;  // MODE 1 / 2 of the kernel only
+  long a_elems, b_elems;  // elements the caller owns behind A / B: what the loaders may touch (host-side proof)
+  ClassTab tab;
 };
+
+// Brings the first LINES 64-byte lines of a kernel's arguments into the scalar cache with one round trip.  Left
+// to themselves the loads come in small groups behind branches, each a trip of about 1000 clocks to memory the
+// host has just written: 5 of the 17 thousand clocks of a 1024 x 1024 x 1024 product on 64 x 64 tiles.
+template <int LINES, class Params>
+__device__ __forceinline__ void touch_args(const Params& P) {
+  const int* w = reinterpret_cast<const int*>(&P);
+  int x = 0;
+#pragma unroll
+  for (int i = 0; i < LINES; ++i) x |= w[16 * i];
+  asm volatile("" ::"s"(x));
+}
 
 // Two fp32 values to packed bf16 (low half = first) with the conversion instruction of gfx950
 // (round to nearest even, the same rounding as f32_to_bf16_bits for finite values).
@@ -342,6 +358,14 @@ __device__ __forceinline__ bf16x8_t frag_value(const Frag& f) {
 #endif
 constexpr int direct_stages(int bm, int bn) { return bm + bn <= 128 ? ARD_NST_SMALL : 2; }
 
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(const F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_for(const F& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
@@ -353,82 +377,81 @@ __device__ __forceinline__ void wait_vmcnt() {
 // would also wait for the younger stages still in flight.
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-// Scattering store of one workgroup tile.  `tile` holds the final bf16 values of compact rows
-// [m0, m1) x columns [n0, n1) ([.][ldt] in LDS).  Output maps are affine with off < step: compact
-// index i owns the physical group [i*step, (i+1)*step) that contains its kept position, the last
-// index also the tail up to nphys; everything in the owned region that is not a kept position is
-// written as +0.0.  VEC: 16-byte pieces (host checks extents, leading dimension and alignment).
-template <bool VEC>
-__device__ __forceinline__ void direct_scatter_tile(const uint16_t* tile, int ldt, const FastParams& P, int m0, int m1,
-                                                    int n0, int n1, int tid, int nthreads) {
-  const Axis& rm = P.srm;
-  const Axis& cn = P.scn;
-  const int sr = rm.step, sc = cn.step;
-  const int c_lo = n0 * sc, c_hi = n1 == P.N ? cn.nphys : n1 * sc;
-  constexpr int W = VEC ? 8 : 1;
-  const int CW = (c_hi - c_lo + W - 1) / W;
-  // threads = (row slot, piece slot): a power-of-two number of lanes walks the pieces of a row
-  int sh = 0;
-  while ((1 << sh) < CW && sh < 6) ++sh;
-  const int LPR = 1 << sh, RPP = nthreads >> sh;
-  const int rsub = tid >> sh, cl = tid & (LPR - 1);
-  auto write_row = [&](int r, int li) {
-    uint16_t* rowp = P.C + (long)r * P.ldc;
-    if (li < 0) {
-      for (int cq = cl; cq < CW; cq += LPR) {
-        if (VEC) *reinterpret_cast<uint4*>(rowp + c_lo + cq * W) = make_uint4(0, 0, 0, 0);
-        else rowp[c_lo + cq] = 0;
-      }
-      return;
-    }
-    const uint16_t* trow = tile + li * ldt - n0;
-    for (int cq = cl; cq < CW; cq += LPR) {
-      const int c0 = c_lo + cq * W;
-      int j = 0;
-      const int d = c0 - cn.off + sc - 1;
-      if (d >= sc) {
-        j = (int)((float)d / (float)sc);
-        j += ((j + 1) * sc <= d) - (j * sc > d);
-      }
-      uint4 gate = make_uint4(0, 0, 0, 0);
-      if (P.relu_src) {
-        const uint16_t* g = P.relu_src + (long)r * P.ldc + c0;
-        if (VEC) gate = *reinterpret_cast<const uint4*>(g);
-        else gate.x = *g;
-      }
-      const uint32_t* gw = reinterpret_cast<const uint32_t*>(&gate);
-      uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int t = 0; t < W; ++t) {
-        if (!(j < n1 && cn.off + j * sc == c0 + t)) continue;
-        uint32_t v = trow[j];
-        ++j;
-        if (P.relu_src) {
-          const uint32_t g = (gw[t >> 1] >> (16 * (t & 1))) & 0xffffu;
-          if (!(bf16_bits_to_f32((uint16_t)g) > 0.0f)) v = 0;
-        }
-        w[t >> 1] |= v << (16 * (t & 1));
-      }
-      if (VEC) *reinterpret_cast<uint4*>(rowp + c0) = make_uint4(w[0], w[1], w[2], w[3]);
-      else rowp[c0] = (uint16_t)w[0];
-    }
-  };
-  if (P.scatter_rows_only) {
-    // kept rows only, whole rows (kept columns and the zeros between them)
-    for (int i = m0 + rsub; i < m1; i += RPP) write_row(i * sr + rm.off, i - m0);
-    return;
-  }
-  // the groups of this tile's compact rows: one kept row and step - 1 dropped ones each
-  for (int i = m0 + rsub; i < m1; i += RPP)
-    for (int g = 0; g < sr; ++g) {
-      const int r = i * sr + g;
-      if (r >= rm.nphys) break;
-      write_row(r, g == rm.off ? i - m0 : -1);
-    }
-  // the last tile also owns the rows behind the last group
-  if (m1 == P.M)
-    for (int r = P.M * sr + rsub; r < rm.nphys; r += RPP) write_row(r, -1);
+// Scattering store of one workgroup tile.  Output maps are affine with off < step: compact index i owns the
+// physical group [i*step, (i+1)*step) that contains its kept position, the last index also the tail up to nphys;
+// everything in the owned region that is not a kept position is written as +0.0.
+// `img` holds the image of compact rows [m0, m1) in LDS exactly as it leaves: physical columns with their zeros,
+// `pitch` elements per row, shifted so that the 16-byte pieces of a row in LDS are the 16-byte pieces of its
+// place in memory (rows may have any length and alignment).  A row leaves piece by piece, only those its region
+// cuts at either end element by element.
+__device__ __forceinline__ int scatter_shift(const FastParams& P, int r, int c_lo) {
+  return (int)(((reinterpret_cast<uintptr_t>(P.C) >> 1) + (uintptr_t)((long)r * P.ldc + c_lo)) & 7);
 }
+__device__ __forceinline__ void direct_scatter_rows(const uint4* img, int pitch, const FastParams& P, int m0, int m1, int c_lo,
+                                                    int c_hi, int tid, int nthreads) {
+  const Axis& rm = P.srm;
+  const int CW = (c_hi - c_lo + 14) >> 3;  // (most pieces a row can have)
+  // rows to write: the kept ones alone, or with the dropped ones of their groups, and after the last group the rest
+  const bool all = !P.scatter_rows_only;
+  const int sr = all ? rm.step : 1;
+  const int r_first = all ? m0 * sr : m0 * rm.step + rm.off, r_inc = all ? 1 : rm.step;
+  const int nrows = all ? (m1 == P.M ? rm.nphys : m1 * sr) - r_first : m1 - m0;
+  const int total = nrows * CW;
+  const float inv_cw = 1.0f / (float)CW, inv_sr = 1.0f / (float)sr;  // (indices below 2^20: (i + 1/2) / n truncates exactly)
+  constexpr int U = 4;  // pieces in flight per thread
+  for (int e0 = tid; e0 < total; e0 += U * nthreads) {
+    uint4 v[U];
+    long at[U];   // element index of the piece in C
+    int c0[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = imin(e0 + u * nthreads, total - 1);
+      const int q = (int)(((float)e + 0.5f) * inv_cw), cq = e - q * CW;
+      const int i = (int)(((float)q + 0.5f) * inv_sr), g = q - i * sr;
+      const int r = r_first + q * r_inc;
+      uint32_t m = (!all || g == rm.off) && i < m1 - m0 ? ~0u : 0u;
+      asm("" : "+v"(m));  // (kept as a mask: behind a branch every LDS read would be waited for by itself)
+      v[u] = img[imin(i, m1 - m0 - 1) * (pitch >> 3) + cq];
+      v[u].x &= m, v[u].y &= m, v[u].z &= m, v[u].w &= m;
+      c0[u] = c_lo - scatter_shift(P, r, c_lo) + cq * 8;
+      at[u] = (long)r * P.ldc + c0[u];
+      if (e0 + u * nthreads >= total) c0[u] = c_hi;  // nothing to store
+    }
+    if (P.relu_src) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (c0[u] >= c_hi) continue;
+        const uint16_t* g = P.relu_src + at[u];
+        uint16_t q[8];
+        if (c0[u] >= c_lo && c0[u] + 8 <= c_hi && (reinterpret_cast<uintptr_t>(g) & 15) == 0) {
+          *reinterpret_cast<uint4*>(q) = *reinterpret_cast<const uint4*>(g);
+        } else {
+#pragma unroll
+          for (int t = 0; t < 8; ++t) q[t] = g[imin(imax(t, c_lo - c0[u]), c_hi - 1 - c0[u])];
+        }
+        uint32_t* w = reinterpret_cast<uint32_t*>(&v[u]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          w[t] &= (bf16_bits_to_f32(q[2 * t]) > 0.0f ? 0xffffu : 0u) | (bf16_bits_to_f32(q[2 * t + 1]) > 0.0f ? 0xffff0000u : 0u);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (c0[u] >= c_hi) continue;
+      uint16_t* o = P.C + at[u];
+      if (c0[u] >= c_lo && c0[u] + 8 <= c_hi) {
+        *reinterpret_cast<uint4*>(o) = v[u];
+      } else {
+        const uint32_t* w = reinterpret_cast<const uint32_t*>(&v[u]);
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          if (c0[u] + t >= c_lo && c0[u] + t < c_hi) o[t] = (uint16_t)(w[t >> 1] >> (16 * (t & 1)));
+      }
+    }
+  }
+}
+// widest column step the LDS image is made for (16 rows of 128 columns fit the smallest stage memory)
+constexpr int kScatterMaxStep = 8;
 
 // What one workgroup computes: its row / column / contraction maps (class-based launches build them
 // from the class tables), the first compact row and column of its tile and its share of the
@@ -437,8 +460,21 @@ struct DirectWork {
   Axis am, bn, kax;
   int m0, n0, split;
 };
-template <int F_BM, int BN>
-__host__ __device__ __forceinline__ bool direct_assign(const FastParams& P, int block_id, DirectWork& w) {
+// The `i`-th run of W rows (columns) of a class: whole blocks of the progression, or, where a block is wider
+// than the tile, the i-th part of a block.  false: the run lies beyond the matrix.
+template <int W>
+__host__ __device__ __forceinline__ bool class_rows(int off, int cnt, int step, int bs, int phys, int i, Axis& r) {
+  if (bs <= W) {
+    const int g = W / bs, left = cnt - i * g;
+    r = axis_baff(off + i * g * step, step, bs, left < g ? left : g, phys);
+    return true;
+  }
+  const int parts = bs / W, m = i / parts, first = (off + m * step) * bs + (i - m * parts) * W;
+  r = Axis{nullptr, AX_AFFINE, first, 1, 1, imin(W, phys - first), phys};
+  return r.n > 0;
+}
+template <int F_BM, int BN, class Params>
+__host__ __device__ __forceinline__ bool direct_assign(const Params& P, int block_id, DirectWork& w) {
   // Workgroup ids go round-robin over the 8 XCDs.  XCD x = id % 8 takes, of every class, the
   // contiguous share [x*n/8, (x+1)*n/8) of its n workgroups: the shares are compact rectangles
   // (operand panels stay in that XCD's L2) and heavy and light classes are spread evenly.
@@ -447,21 +483,23 @@ __host__ __device__ __forceinline__ bool direct_assign(const FastParams& P, int 
   Axis am = P.am, bn = P.bn, kax = P.k;
   int m0 = 0, n0 = 0;
   int split = 0;  // share of the contraction this workgroup takes
-  if (P.tab.ncls == 0) {
+  if (P.ncls == 0) {
     // work items = (split, tile), split-major: an XCD's contiguous share holds whole splits (or long
     // runs of one), so the workgroups in flight on it read the same slab of the contraction
     const int total = P.total_tiles * P.splits;
     const int lo = (int)((long)xcd * total / 8), hi = (int)((long)(xcd + 1) * total / 8);
     if (local >= hi - lo) return false;
     int L = lo + local;
-    split = L / P.total_tiles;
+    split = (int)fdiv((uint32_t)L, P.tiles_div);
     L -= split * P.total_tiles;
-    // bands of group_m tile rows, walked column by column
-    const int band_sz = P.group_m * P.tiles_n;
-    const int band = L / band_sz, inb = L - band * band_sz;
+    // bands of group_m (a power of two) tile rows, walked column by column
+    const int band = (int)fdiv((uint32_t)L, P.band_div), inb = L - band * P.group_m * P.tiles_n;
     const int rows_in_band = imin(P.group_m, P.tiles_m - band * P.group_m);
-    m0 = (band * P.group_m + inb % rows_in_band) * F_BM;
-    n0 = (inb / rows_in_band) * BN;
+    int col;
+    if (rows_in_band == P.group_m) col = inb >> (31 - __builtin_clz((unsigned)P.group_m));
+    else col = inb / rows_in_band;
+    m0 = (band * P.group_m + inb - col * rows_in_band) * F_BM;
+    n0 = col * BN;
     // per-tile contraction lists: the length comes from the tile's count, the blocks are looked up step
     // by step (the host-side proof clears kb_cnt and walks the whole contraction, which bounds every list)
     if (P.kb_cnt) kax.n = imin(imax(P.kb_cnt[n0 / BN], 0), imin(kax.nphys / 64, 128)) * 64;
@@ -485,17 +523,11 @@ __host__ __device__ __forceinline__ bool direct_assign(const FastParams& P, int 
     const int rows_in_band = imin(P.group_m, t.mblk[c] - band * P.group_m);
     const int mi = band * P.group_m + inb % rows_in_band, ni = inb / rows_in_band;
     if (t.m_bs) {
-      const int g = F_BM / t.m_bs;
-      const int left = t.m_cnt[c] - mi * g;
-      am = axis_baff(t.m_off[c] + mi * g * t.m_step, t.m_step, t.m_bs, left < g ? left : g, t.m_phys);
+      if (!class_rows<F_BM>(t.m_off[c], t.m_cnt[c], t.m_step, t.m_bs, t.m_phys, mi, am)) return false;
     } else {
       m0 = mi * F_BM;
     }
-    {
-      const int g = BN / t.n_bs;
-      const int left = t.n_cnt[c] - ni * g;
-      bn = axis_baff(t.n_off[c] + ni * g * t.n_step, t.n_step, t.n_bs, left < g ? left : g, t.n_phys);
-    }
+    if (!class_rows<BN>(t.n_off[c], t.n_cnt[c], t.n_step, t.n_bs, t.n_phys, ni, bn)) return false;
     if (t.k_bs) kax = axis_baff(t.k_off[c], t.k_step, t.k_bs, t.k_cnt[c], t.k_phys);
   }
   w.am = am, w.bn = bn, w.kax = kax;
@@ -537,6 +569,8 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
 
+  touch_args<(MODE == 0 ? 6 : 8)>(P);
+  if (MODE == 0 && P.ncls) touch_args<(int)(sizeof(ClassTab) / 64)>(P.tab);
   DirectWork wk;
   if (!direct_assign<F_BM, BN>(P, block_id, wk)) return;
   const Axis am = wk.am, bn = wk.bn, kax = wk.kax;
@@ -769,20 +803,12 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       int it0 = 0;
       if (kax.kind == AX_AFFINE || (kax.kind == AX_BAFF && (kax.bs % 64 == 0 || kax.bs == 32) && kax.nphys % kax.bs == 0)) {
         // steps whose stage it+NST is not the last one (only the last can be partial)
-        for (; it0 + 2 * NST < S; it0 += NST) {
-          steady_step(I0{}, it0);
-          steady_step(I1{}, it0 + 1);
-          if (NST > 2) steady_step(std::integral_constant<int, 2 % NST>{}, it0 + 2);
-          if (NST > 3) steady_step(std::integral_constant<int, 3 % NST>{}, it0 + 3);
-        }
+        for (; it0 + 2 * NST < S; it0 += NST) static_for<NST>([&](auto b) { steady_step(b, it0 + decltype(b)::value); });
       }
-      for (int it = it0; it < S; it += NST) {
-        step(I0{}, it);
-        if (NST > 1 && it + 1 < S) step(std::integral_constant<int, 1 % NST>{}, it + 1);
-        if (NST > 2 && it + 2 < S) step(std::integral_constant<int, 2 % NST>{}, it + 2);
-        if (NST > 3 && it + 3 < S) step(std::integral_constant<int, 3 % NST>{}, it + 3);
-        static_assert(NST >= 2 && NST <= 4, "pipeline depth");
-      }
+      for (int it = it0; it < S; it += NST)
+        static_for<NST>([&](auto b) {
+          if (it + decltype(b)::value < S) step(b, it + decltype(b)::value);
+        });
     }
   }
 
@@ -793,7 +819,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   const int nphys = P.c_cols_mapped ? bn.nphys : P.N, mphys = P.c_rows_mapped ? am.nphys : P.M;
   // Columns at or beyond the B operand's extent (padding of a compact output) are stored as zeros:
   // the loaders fed them clamped, i.e. arbitrary, rows.
-  const int n_valid = (MODE == 0 && P.tab.ncls == 0) ? bn.n : 0x7fffffff;
+  const int n_valid = (MODE == 0 && P.ncls == 0) ? bn.n : 0x7fffffff;
   // (the 256 x 256 tile has no registers to spare: it only stores plain bf16 results)
   constexpr bool GENERAL_OUT = !(F_BM == 256 && BN == 256);
   if (GENERAL_OUT && P.part) {
@@ -914,27 +940,52 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     return;
   }
   if (GENERAL_OUT && MODE == 0 && P.scatter) {
-    // final bf16 values -> LDS (the operand stages are dead once every wave is past its last read)
-    constexpr int LDT = BN + 2;
-    uint16_t* tile = reinterpret_cast<uint16_t*>(lds);
-    __syncthreads();
+    // The physical image of as many rows as fit at a time is made in LDS (the operand stages are dead once every
+    // wave is past its last read): zeros, then the values at their places, then whole pieces to memory.  (Gathering
+    // each piece's elements from a compact tile took 20 thousand clocks of a 64 x 64 tile at dp = 2 x 2, eight
+    // dependent LDS reads and their index arithmetic per piece.)
+    const int sc = P.scn.step, m1 = imin(m0 + F_BM, P.M), n1 = imin(n0 + BN, P.N);
+    const int c_lo = n0 * sc, c_hi = n1 == P.N ? P.scn.nphys : n1 * sc;
+    const int pitch = (BN * sc + sc + 15) & ~7;
+    constexpr int LDS_BYTES = NST * (F_BM + BN) * LDS_ROW_U4 * 16;
+    static_assert(LDS_BYTES / (2 * ((BN * kScatterMaxStep + kScatterMaxStep + 15) & ~7)) >= 16, "16 rows of the image fit");
+    const int rows_fit = imin(F_BM, LDS_BYTES / (pitch * 2) & ~15);
+    for (int r0 = 0; r0 < F_BM && m0 + r0 < m1; r0 += rows_fit) {
+      __syncthreads();
+      for (int i = tid; i < rows_fit * (pitch >> 3); i += 64 * NW) lds[i] = make_uint4(0, 0, 0, 0);
+      __syncthreads();
+      uint16_t* img = reinterpret_cast<uint16_t*>(lds);
+      int rr = r0, ppitch = pitch;
 #pragma unroll
-    for (int im = 0; im < TM; ++im)
+      for (int im = 0; im < TM; ++im)
 #pragma unroll
-      for (int in = 0; in < TN; ++in) {
-        const int lj = wn * WTN + in * 32 + (lane & 31);
-        const int li0 = wm * WTM + im * 32 + 4 * (lane >> 5);
+        for (int half = 0; half < 2; ++half) {
+          // (opaque: the addresses of all rows computed ahead of the loop would take 100 registers)
+          asm volatile("" : "+s"(rr), "+s"(ppitch));
+          const int lrow = wm * WTM + im * 32 + 16 * half - rr;  // 16 rows of this wave, relative to the image
+          if (lrow < 0 || lrow >= rows_fit) continue;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float x = n0 + lj < n_valid ? P.alpha * acc[im][in][v] : 0.0f;
-          if (P.relu) x = fmaxf(x, 0.0f);
-          tile[(li0 + 8 * (v >> 2) + (v & 3)) * LDT + lj] = f32_to_bf16_bits(x);
+          for (int v = 8 * half; v < 8 * half + 8; v += 2) {
+            const int li = lrow - 16 * half + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+            const int i = m0 + rr + li, r = i * P.srm.step + P.srm.off;
+            const int sh0 = scatter_shift(P, r, c_lo) + P.scn.off, sh1 = scatter_shift(P, r + P.srm.step, c_lo) + P.scn.off;
+#pragma unroll
+            for (int in = 0; in < TN; ++in) {
+              const int lj = wn * WTN + in * 32 + (lane & 31);
+              float x0 = P.alpha * acc[im][in][v], x1 = P.alpha * acc[im][in][v + 1];
+              if (P.relu) x0 = fmaxf(x0, 0.0f), x1 = fmaxf(x1, 0.0f);
+              const uint32_t b01 = pack_bf16x2(x0, x1);
+              // (columns beyond the operand are padding zeros, rows and columns beyond the output stay out of the image)
+              if (n0 + lj < n1 && n0 + lj < n_valid) {
+                if (i < m1) img[li * ppitch + sh0 + lj * sc] = (uint16_t)b01;
+                if (i + 1 < m1) img[(li + 1) * ppitch + sh1 + lj * sc] = (uint16_t)(b01 >> 16);
+              }
+            }
+          }
         }
-      }
-    __syncthreads();
-    const int m1 = min(m0 + F_BM, P.M), n1 = min(n0 + BN, P.N);
-    if (P.scatter_vec) direct_scatter_tile<true>(tile, LDT, P, m0, m1, n0, n1, tid, 64 * NW);
-    else direct_scatter_tile<false>(tile, LDT, P, m0, m1, n0, n1, tid, 64 * NW);
+      __syncthreads();
+      direct_scatter_rows(lds, pitch, P, m0 + r0, imin(m0 + r0 + rows_fit, m1), c_lo, c_hi, tid, 64 * NW);
+    }
     return;
   }
   int prow[TM];
@@ -1125,26 +1176,33 @@ static __device__ __forceinline__ void finish_vec_body(const FinishArgs& a, cons
         else if (C.cn.kind == AX_AFFINE) jj[t] = (j < C.cn.n && C.cn.off + j * C.cn.step == c0 + t) ? j++ : -1;
         else jj[t] = ax_inverse(C.cn, c0 + t);
       }
-      // the 8 loads of one split are independent; splits are summed in order
+      // The 8 loads of one split are independent and unconditional (positions that are not kept read some kept one
+      // and are masked out: behind branches every load would be waited for by itself); splits are summed in order.
       float x[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
       const float* prow = part + (long)i * N;
+      uint32_t keep[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        keep[t] = jj[t] >= 0 ? ~0u : 0u;
+        asm("" : "+v"(keep[t]));
+        jj[t] = imax(jj[t], 0);
+      }
       for (int sp = 0; sp < splits; ++sp) {
         float v[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = jj[t] >= 0 ? prow[sp * MN + jj[t]] : 0.0f;
+        for (int t = 0; t < 8; ++t) v[t] = prow[sp * MN + jj[t]];
 #pragma unroll
         for (int t = 0; t < 8; ++t) x[t] += v[t];
       }
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
-        if (jj[t] < 0) continue;
         float v = x[t] * C.alpha;
         if (C.relu) v = fmaxf(v, 0.0f);
         if (C.relu_src) {
           const uint32_t g = (gw[t >> 1] >> (16 * (t & 1))) & 0xffffu;
           v = bf16_bits_to_f32((uint16_t)g) > 0.0f ? v : 0.0f;
         }
-        w[t >> 1] |= (uint32_t)f32_to_bf16_bits(v) << (16 * (t & 1));
+        w[t >> 1] |= ((uint32_t)f32_to_bf16_bits(v) & keep[t]) << (16 * (t & 1));
       }
     }
     *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(C.p) + idx) = make_uint4(w[0], w[1], w[2], w[3]);
@@ -1163,7 +1221,8 @@ struct ZeroRowsArgs {
 };
 static __device__ __forceinline__ void zero_rows_body(const ZeroRowsArgs& a, const int bx, const int nblocks) {
   const int dropped = a.rows - a.n_kept;
-  const int per_row = a.vec ? a.cols >> 3 : a.cols;
+  // pieces of 16 bytes, of every row's own alignment where rows are no whole number of them
+  const int per_row = a.vec ? a.cols >> 3 : (a.cols + 14) >> 3;
   const long total = (long)dropped * per_row;
   for (long e = (long)bx * 256 + threadIdx.x; e < total; e += (long)nblocks * 256) {
     // (a 64-bit division costs several times a 32-bit one, and nearly every matrix stays below 2^32 pieces)
@@ -1177,8 +1236,13 @@ static __device__ __forceinline__ void zero_rows_body(const ZeroRowsArgs& a, con
       const int q = (d - a.off) / (a.step - 1), t = (d - a.off) - q * (a.step - 1);
       r = q < a.n_kept ? a.off + q * a.step + 1 + t : a.off + a.n_kept * a.step + (d - a.off - a.n_kept * (a.step - 1)) - (a.step - 1);
     }
-    if (a.vec) *reinterpret_cast<uint4*>(a.C + (long)r * a.ld + c * 8) = make_uint4(0, 0, 0, 0);
-    else a.C[(long)r * a.ld + c] = 0;
+    uint16_t* rowp = a.C + (long)r * a.ld;
+    const int c0 = c * 8 - (a.vec ? 0 : (int)((reinterpret_cast<uintptr_t>(rowp) & 15) >> 1));
+    if (c0 >= 0 && c0 + 8 <= a.cols) {
+      *reinterpret_cast<uint4*>(rowp + c0) = make_uint4(0, 0, 0, 0);
+    } else {
+      for (int q = imax(c0, 0); q < c0 + 8 && q < a.cols; ++q) rowp[q] = 0;
+    }
   }
 }
 static __global__ __launch_bounds__(256) void zero_rows_kernel(const ZeroRowsArgs a) {
@@ -1186,16 +1250,18 @@ static __global__ __launch_bounds__(256) void zero_rows_kernel(const ZeroRowsArg
 }
 
 // Zero the dropped tiles of a tile-masked matrix (weight gradient): one workgroup per tile.
-static __global__ __launch_bounds__(256) void zero_dropped_tiles_kernel(uint16_t* C, int ld, int rows, int cols, int tr, int tc,
+template <typename T>
+static __global__ __launch_bounds__(256) void zero_dropped_tiles_kernel(T* C, int ld, int rows, int cols, int tr, int tc,
                                                                  int TC, int dp, int o) {
   const int t = blockIdx.x;
   if (((t + dp - o) % dp) == 0) return;  // kept tile: written by the GEMM
   const int r0 = (t / TC) * tr, c0 = (t % TC) * tc;
   const int h = min(tr, rows - r0), w = min(tc, cols - c0);
-  if (((w | c0 | ld) & 7) == 0) {
-    const int w8 = w >> 3;
+  constexpr int CE = ElemTraits<T>::CE;
+  if (((w | c0 | ld) & (CE - 1)) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
+    const int w8 = w / CE;
     for (int i = threadIdx.x; i < h * w8; i += 256) {
-      const int r = i / w8, c = (i - r * w8) * 8;
+      const int r = i / w8, c = (i - r * w8) * CE;
       *reinterpret_cast<uint4*>(C + (long)(r0 + r) * ld + c0 + c) = make_uint4(0, 0, 0, 0);
     }
   } else {
@@ -1206,11 +1272,103 @@ static __global__ __launch_bounds__(256) void zero_dropped_tiles_kernel(uint16_t
   }
 }
 
+// an XCD's share should be about square in tiles: bands of group_m tile rows
+static inline int direct_group_m(int total_tiles) {
+  const int per_xcd = ceil_div(total_tiles, 8);
+  int gm = 1;
+  while (gm * gm * 2 <= per_xcd && gm < 8) gm *= 2;
+  return gm;
+}
+template <class Params> static inline void set_bands(Params& P, int group_m) {
+  P.ncls = P.tab.ncls;
+  P.group_m = group_m;
+  P.tiles_div = fast_div((uint32_t)imax(P.total_tiles, 1)), P.band_div = fast_div((uint32_t)imax(group_m * P.tiles_n, 1));
+}
+
+// Classes of a tile pattern (tiles of x by y, every dp-th from tile o on, over a TR x TC grid of W[O x I]) for
+// op 0: Y = X . W^T, 1: dX = dY . W, 2: dW = dY^T . X.  Fills everything but the workgroup counts; false: more
+// classes than the table holds.
+static inline bool tile_classes(int op, int O, int I, int TR, int TC, int x, int y, int dp, int o, ClassTab& t) {
+  int a = TC, b = dp;
+  while (b) {
+    const int r = a % b;
+    a = b;
+    b = r;
+  }
+  const int Pp = dp / a;  // a = gcd(TC, dp)
+  if (Pp > F_MAXCLS || (op == 1 && dp > F_MAXCLS)) return false;
+  auto cnt = [](int total, int first, int step) { return first < total ? (total - first + step - 1) / step : 0; };
+  auto first_col = [&](int c) { return (int)((((long)o - (long)c * TC) % dp + dp) % dp); };
+  if (op == 1) {
+    t.ncls = dp;
+    t.n_step = dp, t.n_bs = y, t.n_phys = I;
+    t.k_step = Pp, t.k_bs = x, t.k_phys = O;
+    for (int c = 0; c < dp; ++c) {
+      t.n_off[c] = c;
+      t.n_cnt[c] = cnt(TC, c, dp);
+      int J0 = -1;
+      for (int J = 0; J < Pp && J0 < 0; ++J)
+        if ((((long)J * TC + c - o) % dp + dp) % dp == 0) J0 = J;
+      t.k_off[c] = J0 < 0 ? 0 : J0;
+      t.k_cnt[c] = J0 < 0 ? 0 : cnt(TR, J0, Pp);
+    }
+    return true;
+  }
+  t.ncls = Pp;
+  if (op == 0) {
+    t.n_step = Pp, t.n_bs = x, t.n_phys = O;
+    t.k_step = dp, t.k_bs = y, t.k_phys = I;
+    for (int c = 0; c < Pp; ++c) {
+      t.n_off[c] = c;
+      t.n_cnt[c] = cnt(TR, c, Pp);
+      t.k_off[c] = first_col(c);
+      t.k_cnt[c] = cnt(TC, t.k_off[c], dp);
+    }
+  } else {
+    t.m_step = Pp, t.m_bs = x, t.m_phys = O;
+    t.n_step = dp, t.n_bs = y, t.n_phys = I;
+    for (int c = 0; c < Pp; ++c) {
+      t.m_off[c] = c;
+      t.m_cnt[c] = cnt(TR, c, Pp);
+      t.n_off[c] = first_col(c);
+      t.n_cnt[c] = cnt(TC, t.n_off[c], dp);
+    }
+  }
+  return true;
+}
+// Workgroups per class for BM x BN tiles over B rows (op 2: over the class's own rows); `heavy` ones have
+// something to contract.  Returns their total.
+static inline int count_classes(int op, ClassTab& t, int B, int bm, int bn, int& heavy) {
+  auto runs = [](int cnt, int bs, int w) { return bs <= w ? ceil_div(cnt, w / bs) : cnt * (bs / w); };
+  int total = 0;
+  heavy = 0;
+  for (int c = 0; c < t.ncls; ++c) {
+    const int mb = op == 2 ? runs(t.m_cnt[c], t.m_bs, bm) : ceil_div(B, bm), nb = runs(t.n_cnt[c], t.n_bs, bn);
+    t.mblk[c] = mb > 0 ? mb : 1;
+    t.nblk[c] = mb > 0 ? mb * nb : 0;
+    total += t.nblk[c];
+    if (op == 2 || t.k_cnt[c] > 0) heavy += t.nblk[c];
+  }
+  return total;
+}
+static inline bool tile_run_fits(int bs, int w) { return bs <= w ? w % bs == 0 : bs % w == 0; }
+
 // Grid of a plain (class-free) launch: every XCD takes the share [x*n/8, (x+1)*n/8) of the tiles.
 static inline int direct_plain_grid(int total_tiles) {
   int worst = 0;
   for (int x = 0; x < 8; ++x) {
     const int sum = (int)((long)(x + 1) * total_tiles / 8) - (int)((long)x * total_tiles / 8);
+    worst = sum > worst ? sum : worst;
+  }
+  return worst * 8;
+}
+
+// Grid of a class launch: every XCD takes the share [x*n/8, (x+1)*n/8) of each class.
+static inline int class_grid(const ClassTab& t) {
+  int worst = 0;
+  for (int x = 0; x < 8; ++x) {
+    int sum = 0;
+    for (int c = 0; c < t.ncls; ++c) sum += (int)((long)(x + 1) * t.nblk[c] / 8) - (int)((long)x * t.nblk[c] / 8);
     worst = sum > worst ? sum : worst;
   }
   return worst * 8;
@@ -1399,9 +1557,7 @@ bool batch_push_zero_rows(const ZeroRowsArgs& a, int gx);
 // Host side: launch one instantiation with its dynamic LDS (stages x (BM + BN) rows of 128 bytes);
 // kernels above the 64 KiB default get their limit raised once.
 template <bool A_KC, bool B_KC, int BM, int BN, int NW, int MODE>
-static int32_t launch_direct_kernel(const FastParams& F_in, int grid_x, hipStream_t stream) {
-  FastParams F = F_in;
-  if (F.splits < 1) F.splits = 1;
+static int32_t launch_direct_alone(const FastParams& F, int grid_x, hipStream_t stream) {
   auto kernel = gemm_direct_kernel<A_KC, B_KC, BM, BN, NW, MODE>;
   const size_t lds_bytes = (size_t)direct_stages(BM, BN) * (BM + BN) * LDS_ROW_U4 * sizeof(uint4);
   static thread_local bool raised = false;
@@ -1409,6 +1565,15 @@ static int32_t launch_direct_kernel(const FastParams& F_in, int grid_x, hipStrea
     ARD_HIP_CHECK(ard::raise_lds_limit((const void*)kernel, (int)lds_bytes));
     raised = !dry_run();
   }
+  ARD_LAUNCH_NAMED("gemm_direct_kernel", kernel, dim3((unsigned)grid_x), dim3(64 * NW), lds_bytes, stream, F);
+  ARD_LAUNCH_CHECK("gemm_direct_kernel");
+  return ARD_OK;
+}
+template <bool A_KC, bool B_KC, int BM, int BN, int NW, int MODE>
+static int32_t launch_direct_kernel(const FastParams& F_in, int grid_x, hipStream_t stream) {
+  FastParams F = F_in;
+  if (F.splits < 1) F.splits = 1;
+  const size_t lds_bytes = (size_t)direct_stages(BM, BN) * (BM + BN) * LDS_ROW_U4 * sizeof(uint4);
   // class-free launches: the (split, tile) items are dealt to the XCDs inside the kernel
   if (F.tab.ncls == 0) grid_x = direct_plain_grid(F.total_tiles * (F.splits < 1 ? 1 : F.splits));
   // no lane may leave its operand: cheap envelope always, the exhaustive walk on request
@@ -1420,17 +1585,7 @@ static int32_t launch_direct_kernel(const FastParams& F_in, int grid_x, hipStrea
   }
   constexpr int gk = direct_group_kind<A_KC, B_KC, BM, BN, NW, MODE>();
   if (gk >= 0 && batch_open() && batch_push_direct(gk, F, grid_x, lds_bytes)) return ARD_OK;
-  ARD_LAUNCH_NAMED("gemm_direct_kernel", kernel, dim3((unsigned)grid_x), dim3(64 * NW), lds_bytes, stream, F);
-  ARD_LAUNCH_CHECK("gemm_direct_kernel");
-  return ARD_OK;
-}
-
-// an XCD's share should be about square in tiles: bands of group_m tile rows
-static inline int direct_group_m(int total_tiles) {
-  const int per_xcd = ceil_div(total_tiles, 8);
-  int gm = 1;
-  while (gm * gm * 2 <= per_xcd && gm < 8) gm *= 2;
-  return gm;
+  return launch_direct_alone<A_KC, B_KC, BM, BN, NW, MODE>(F, grid_x, stream);
 }
 
 }  // namespace ard

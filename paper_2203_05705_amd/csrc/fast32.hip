@@ -1,0 +1,228 @@
+// Host side of the fp32 kernels: which products they take, tile choice, launches.
+#include "fast32.hpp"
+
+namespace ard {
+
+// Sums the partial sums of a contraction split over the grid and writes the output through its (affine) maps:
+// one thread per physical column, dropped positions included.
+static __global__ void gemm_finish_f32_kernel(const float* part, int splits, int M, int N, OutMat C, FastDiv row_div, FastDiv col_div) {
+  const int cols = C.fill ? C.cn.nphys : N, rows = C.fill ? C.rm.nphys : M;
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= cols) return;
+  int j = c;
+  bool col_kept = true;
+  if (C.fill) {
+    const int d = c - C.cn.off;
+    j = d >= 0 ? (int)fdiv((uint32_t)d, col_div) : 0;
+    col_kept = d >= 0 && j * C.cn.step == d && j < N;
+  }
+  for (int r = blockIdx.y; r < rows; r += gridDim.y) {
+    int i = r;
+    bool kept = col_kept;
+    if (C.fill) {
+      const int d = r - C.rm.off;
+      i = d >= 0 ? (int)fdiv((uint32_t)d, row_div) : 0;
+      kept = kept && d >= 0 && i * C.rm.step == d && i < M;
+    }
+    float x = 0.0f;
+    if (kept)
+      for (int s = 0; s < splits; ++s) x += part[((long)s * M + i) * N + j];
+    const long idx = (long)(C.fill ? r : ax_phys(C.rm, r)) * C.ld + (C.fill ? c : ax_phys(C.cn, c));
+    store_out<float>(C, idx, C.alpha * x, kept);
+  }
+}
+
+// Workgroup tiles: how the four wavefronts share it, contraction steps in flight, and the share of the
+// matrix-core rate a full chip of them reaches (128 x 128 on 2048^3, the small ones on products they fill).
+struct F32Cfg {
+  int bm, bn, wk, d;
+  float eff;
+};
+static const F32Cfg kF32Cfgs[4] = {{128, 128, 1, 3, 0.85f}, {64, 64, 4, 3, 0.8f}, {32, 32, 4, 4, 0.6f}, {16, 16, 4, 8, 0.4f}};
+
+template <int AK, int BK, int MODE>
+static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
+  const F32Cfg& c = kF32Cfgs[cfg];
+  const size_t lds = (size_t)c.wk * c.bm * (c.bn + 1) * 4 + (size_t)(c.bm * 3 > c.bm + c.bn ? c.bm * 3 : c.bm + c.bn) * 4;  // accumulators, tables
+  const dim3 g((unsigned)grid), b(256);
+#define ARD_F32_CASE(I, ...)                                                                             \
+  case I: {                                                                                              \
+    auto kernel = gemm_f32_kernel<AK, BK, __VA_ARGS__, MODE>;                                            \
+    static thread_local bool raised = false;                                                             \
+    if (!raised && lds >= 65536) {                                                                       \
+      ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));                                     \
+      raised = !dry_run();                                                                               \
+    }                                                                                                    \
+    ARD_LAUNCH_NAMED("gemm_f32_kernel", kernel, g, b, lds, stream, F);                                   \
+    break;                                                                                               \
+  }
+  switch (cfg) {
+    ARD_F32_CASE(0, 4, 4, 2, 2, 1, 3)
+    ARD_F32_CASE(1, 4, 4, 1, 1, 4, 3)
+    ARD_F32_CASE(2, 2, 2, 1, 1, 4, 4)
+    ARD_F32_CASE(3, 1, 1, 1, 1, 4, 8)
+    default: return fail(ARD_EUNSUPPORTED, "no such fp32 tile");
+  }
+#undef ARD_F32_CASE
+  ARD_LAUNCH_CHECK("gemm_f32_kernel");
+  return ARD_OK;
+}
+
+static int32_t launch_f32_kinds(int ak, int bk, F32Params& F, int cfg, int grid, hipStream_t stream) {
+#define ARD_F32_KINDS(A, B) \
+  if (ak == A && bk == B) return launch_f32<A, B, 0>(F, cfg, grid, stream);
+  ARD_F32_KINDS(F32_KC_VEC, F32_KC_VEC)
+  ARD_F32_KINDS(F32_KC_VEC, F32_KC)
+  ARD_F32_KINDS(F32_KC, F32_KC_VEC)
+  ARD_F32_KINDS(F32_KC, F32_KC)
+  ARD_F32_KINDS(F32_KC_VEC, F32_MC_VEC)
+  ARD_F32_KINDS(F32_KC_VEC, F32_MC)
+  ARD_F32_KINDS(F32_KC, F32_MC_VEC)
+  ARD_F32_KINDS(F32_KC, F32_MC)
+  ARD_F32_KINDS(F32_MC_VEC, F32_MC_VEC)
+  ARD_F32_KINDS(F32_MC_VEC, F32_MC)
+  ARD_F32_KINDS(F32_MC, F32_MC_VEC)
+  ARD_F32_KINDS(F32_MC, F32_MC)
+#undef ARD_F32_KINDS
+  return fail(ARD_EUNSUPPORTED, "operand layout combination not built");
+}
+
+// Time of a product with this tile, in clocks: rounds of workgroups over 256 CUs (the wavefronts of several
+// workgroups on a CU share its matrix cores, 256 FLOP per clock) against the chain of memory round trips of
+// one wavefront (about 1500 clocks per D steps), and what it takes to store the `spread` physical positions
+// per result (zeros of dropped rows and columns included): about 4 per clock and CU, and 600 clocks for a
+// workgroup to come and go.
+static float f32_clocks(const F32Cfg& c, long tiles, int K, int splits, float spread) {
+  const float rounds = (float)((tiles * splits + 255) / 256);
+  const float k = (float)K / splits;
+  const float mfma = rounds * c.bm * c.bn * k * (2.0f / 256.0f) / c.eff;
+  const int steps = imax(1, (int)(k / 16.0f / c.wk));
+  const float chain = 1500.0f * ((steps + c.d - 1) / c.d);
+  return (mfma > chain ? mfma : chain) + rounds * (600.0f + 0.25f * c.bm * c.bn * (splits > 1 ? 1.0f : spread));
+}
+
+static bool affine(const Axis& a) { return a.kind == AX_AFFINE && a.step >= 1 && a.off >= 0; }
+bool f32_takes_maps(const Axis& out, const Axis& in) {
+  return !dev_knobs().no_fast && affine(in) && affine(out);
+}
+
+bool try_f32(bool a_kc, bool b_kc, const GemmParams& P, void* ws, size_t ws_bytes, hipStream_t stream, int32_t& st) {
+  if (dev_knobs().no_fast || P.kb_ptr || P.tmask || P.C.plane || (!a_kc && b_kc)) return false;
+  if (P.M < 1 || P.N < 1 || (long)P.M * P.N >= (1L << 31) || P.k.n < 0) return false;
+  const Axis ka = P.A.kdense ? axis_identity(P.k.n) : P.k, kb = P.B.kdense ? axis_identity(P.k.n) : P.k;
+  if (!affine(ka) || !affine(kb)) return false;
+  for (const Operand* op : {&P.A, &P.B}) {
+    const bool kc = op == &P.A ? a_kc : b_kc;
+    const Axis& k = op == &P.A ? ka : kb;
+    if (!(affine(op->r) || op->r.kind == AX_LIST) || op->r.n < 1) return false;
+    if (k.n > 0 && k.off + (long)(k.n - 1) * k.step >= k.nphys) return false;
+    if (affine(op->r) && op->r.off + (long)(op->r.n - 1) * op->r.step >= op->r.nphys) return false;
+    if (((uintptr_t)op->p & 3) || (long)imax(kc ? op->r.nphys : k.nphys, 1) * op->ld * 4 >= (1L << 31)) return false;
+  }
+  auto kind = [](bool kc, const Axis& r, const Axis& k) {
+    if (kc) return k.step == 1 ? (int)F32_KC_VEC : (int)F32_KC;
+    return r.kind == AX_AFFINE && r.step == 1 && r.n >= 4 ? (int)F32_MC_VEC : (int)F32_MC;
+  };
+  const OutMat& C = P.C;
+  auto owned = [](const Axis& a) { return a.kind == AX_AFFINE && a.off < a.step; };
+  auto map_ok = [&](const Axis& a) { return a.kind == AX_LIST || (C.fill ? owned(a) : a.kind == AX_AFFINE); };
+  if (!map_ok(C.rm) || !map_ok(C.cn)) return false;
+  F32Params F{};
+  F.A = (const float*)P.A.p, F.B = (const float*)P.B.p;
+  F.lda = (int)P.A.ld, F.ldb = (int)P.B.ld;
+  F.am = P.A.r, F.bn = P.B.r, F.k = axis_identity(P.k.n);
+  F.ka_off = ka.off, F.ka_step = ka.step, F.kb_off = kb.off, F.kb_step = kb.step;
+  F.C = C;
+  F.row_div = fast_div((uint32_t)C.rm.step), F.col_div = fast_div((uint32_t)C.cn.step);
+  F.M = P.M, F.N = P.N;
+  // Tile, and whether the contraction is split over the grid as well: a finishing pass costs about 12000
+  // clocks (a dependent launch that reads what other XCDs wrote).
+  const bool can_split = ws && C.rm.kind == AX_AFFINE && C.cn.kind == AX_AFFINE;
+  const float spread = C.fill ? (float)((double)C.rm.nphys * C.cn.nphys / ((double)P.M * P.N)) : 1.0f;
+  int cfg = 0, splits = 1;
+  float best = 0.0f;
+  for (int i = 0; i < 4; ++i) {
+    const F32Cfg& c = kF32Cfgs[i];
+    const long tiles = (long)ceil_div(P.M, c.bm) * ceil_div(P.N, c.bn);
+    if (tiles >= (1L << 24)) continue;
+    for (int sp = 1; sp <= 16; sp *= 2) {
+      if (sp > 1 && (!can_split || P.k.n < 16 * c.wk * c.d * sp || (size_t)sp * P.M * P.N * 4 > ws_bytes)) break;
+      const float t = f32_clocks(c, tiles, P.k.n, sp, spread) + (sp > 1 ? 12000.0f : 0.0f);
+      if (best == 0.0f || t < best) best = t, cfg = i, splits = sp;
+    }
+  }
+  if (best == 0.0f) return false;
+  const F32Cfg& c = kF32Cfgs[cfg];
+  F.tiles_m = ceil_div(P.M, c.bm), F.tiles_n = ceil_div(P.N, c.bn);
+  F.total_tiles = F.tiles_m * F.tiles_n;
+  set_bands(F, direct_group_m(F.total_tiles));
+  F.splits = splits;
+  if (splits > 1) F.part = (float*)ws;
+  st = launch_f32_kinds(kind(a_kc, F.am, ka), kind(b_kc, F.bn, kb), F, cfg, direct_plain_grid(F.total_tiles * splits), stream);
+  if (st || splits == 1) return true;
+  const int cols = C.fill ? C.cn.nphys : P.N, rows = C.fill ? C.rm.nphys : P.M;
+  ARD_LAUNCH(gemm_finish_f32_kernel, dim3((unsigned)ceil_div(cols, 256), (unsigned)imin(rows, 4096)), dim3(256), 0, stream,
+             (const float*)F.part, splits, P.M, P.N, C, F.row_div, F.col_div);
+  const hipError_t e = launch_status();
+  if (e != hipSuccess) st = fail(ARD_EHIP, "launch of gemm_finish_f32_kernel failed: %s", hipGetErrorString(e));
+  return true;
+}
+
+// Tile pattern (Section 3.2): classes of tile rows or columns as in the bf16 kernels (tile_classes); any tile
+// size works, a tile wider than the workgroup's tile is taken in parts.
+bool try_f32_tile(int op, int B, int I, int O, int TR, int TC, const ard_pattern& pat, const void* Ap, const void* Bp, void* Cp,
+                  float alpha, int relu, const void* relu_src, hipStream_t stream, int32_t& st) {
+  if (dev_knobs().no_fast) return false;
+  if ((long)B * O * 4 >= (1L << 31) || (long)B * I * 4 >= (1L << 31) || (long)O * I * 4 >= (1L << 31)) return false;
+  if (((uintptr_t)Ap & 3) || ((uintptr_t)Bp & 3)) return false;
+  const int x = pat.tile_r, y = pat.tile_c, dp = pat.dp, o = pat.b - 1;
+  F32Params F{};
+  ClassTab& t = F.tab;
+  if (!tile_classes(op, O, I, TR, TC, x, y, dp, o, t)) return false;
+  F.A = (const float*)Ap, F.B = (const float*)Bp;
+  F.ldb = I;
+  F.ka_step = F.kb_step = 1;
+  F.c_cols_mapped = 1;
+  F.C.p = Cp, F.C.alpha = alpha, F.C.relu = relu, F.C.relu_src = relu_src;
+  int ak = F32_KC_VEC, bk = F32_KC_VEC;
+  if (op == 0) {
+    F.lda = I, F.am = axis_identity(B), F.C.ld = O, F.M = B, F.N = O;
+  } else {
+    // (groups of four columns must not straddle the end of the matrix: a block progression is not moved back)
+    bk = I % 4 == 0 ? F32_MC_VEC : F32_MC;
+    F.lda = O, F.C.ld = I, F.N = I;
+    if (op == 1) {
+      F.am = axis_identity(B), F.M = B;
+    } else {
+      ak = O % 4 == 0 ? F32_MC_VEC : F32_MC;
+      F.k = axis_identity(B), F.c_rows_mapped = 1, F.M = O;
+    }
+  }
+  int K = op == 2 ? B : 0, heavy = 0, cfg = -1;
+  if (op != 2)
+    for (int c = 0; c < t.ncls; ++c) K = imax(K, t.k_cnt[c] * t.k_bs);
+  float best = 0.0f;
+  for (int i = 0; i < 4; ++i) {
+    const F32Cfg& c = kF32Cfgs[i];
+    if (!tile_run_fits(t.n_bs, c.bn) || (op == 2 && !tile_run_fits(t.m_bs, c.bm))) continue;
+    if (count_classes(op, t, B, c.bm, c.bn, heavy) == 0) continue;
+    const float est = f32_clocks(c, imax(heavy, 1), K, 1, 1.0f);
+    if (cfg < 0 || est < best) best = est, cfg = i;
+  }
+  if (cfg < 0) return false;
+  F.total_tiles = count_classes(op, t, B, kF32Cfgs[cfg].bm, kF32Cfgs[cfg].bn, heavy);
+  set_bands(F, direct_group_m(F.total_tiles));
+  F.splits = 1;
+  if (op == 2) {
+    ARD_LAUNCH(zero_dropped_tiles_kernel<float>, dim3((unsigned)(TR * TC)), dim3(256), 0, stream, (float*)Cp, I, O, I, x, y, TC, dp, o);
+    const hipError_t e = launch_status();
+    if (e != hipSuccess) {
+      st = fail(ARD_EHIP, "launch of zero_dropped_tiles_kernel failed: %s", hipGetErrorString(e));
+      return true;
+    }
+  }
+  st = launch_f32_kinds(ak, bk, F, cfg, class_grid(F.tab), stream);
+  return true;
+}
+
+}  // namespace ard

@@ -81,6 +81,7 @@ bool run_gemm_partials(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P,
 int32_t run_gemm(int32_t dtype, bool a_kc, bool b_kc, GemmParams P, int max_bn, int /*max_bm*/, hipStream_t stream,
                  void* ws, size_t ws_bytes) {
   int32_t st_fast = ARD_OK;
+  if (dtype == ARD_F32 && try_f32(a_kc, b_kc, P, ws, ws_bytes, stream, st_fast)) return st_fast;
   if (try_direct(dtype, a_kc, b_kc, P, ws, ws_bytes, stream, st_fast)) return st_fast;
   if (dtype != ARD_BF16 && dtype != ARD_F32) return fail(ARD_EDTYPE, "unknown dtype %d", dtype);
   // A product with too few tiles for the chip splits its contraction over blockIdx.y into fp32
@@ -118,15 +119,6 @@ int32_t run_gemm(int32_t dtype, bool a_kc, bool b_kc, GemmParams P, int max_bn, 
 
 // ---- large-tile path -------------------------------------------------------------------
 
-static int gcd_int(int a, int b) {
-  while (b) {
-    int t = a % b;
-    a = b;
-    b = t;
-  }
-  return a;
-}
-
 template <int BM, int BN, int NW>
 static int32_t launch_direct_cfg(bool a_kc, bool b_kc, FastParams& F, int grid_x, hipStream_t stream) {
   if (a_kc && b_kc) return launch_direct_kernel<true, true, BM, BN, NW, 0>(F, grid_x, stream);
@@ -135,21 +127,7 @@ static int32_t launch_direct_cfg(bool a_kc, bool b_kc, FastParams& F, int grid_x
   return fail(ARD_EUNSUPPORTED, "operand layout combination not built");
 }
 
-// Grid of the large-tile kernel: every XCD takes the share [x*n/8, (x+1)*n/8) of each class.
-static int fast_grid(const FastParams& F) {
-  int worst = 0;
-  for (int x = 0; x < 8; ++x) {
-    int sum = 0;
-    if (F.tab.ncls == 0) {
-      sum = (int)((long)(x + 1) * F.total_tiles / 8) - (int)((long)x * F.total_tiles / 8);
-    } else {
-      for (int c = 0; c < F.tab.ncls; ++c)
-        sum += (int)((long)(x + 1) * F.tab.nblk[c] / 8) - (int)((long)x * F.tab.nblk[c] / 8);
-    }
-    worst = sum > worst ? sum : worst;
-  }
-  return worst * 8;
-}
+static int fast_grid(const FastParams& F) { return F.tab.ncls == 0 ? direct_plain_grid(F.total_tiles) : class_grid(F.tab); }
 
 struct TileCfg {
   int bm, bn;
@@ -159,11 +137,7 @@ static const TileCfg kTileCfgs[] = {{256, 256}, {256, 128}, {128, 128}, {128, 64
 static int32_t launch_direct(bool a_kc, bool b_kc, FastParams& F, int bm, int bn, hipStream_t stream) {
   if (F.total_tiles <= 0) return ARD_OK;
   if (F.splits < 1) F.splits = 1;
-  // an XCD's share should be about square in tiles: bands of group_m tile rows
-  const int per_xcd = ceil_div(F.total_tiles, 8);
-  int gm = 1;
-  while (gm * gm * 2 <= per_xcd && gm < 8) gm *= 2;
-  F.group_m = gm;
+  set_bands(F, direct_group_m(F.total_tiles));
   const int grid = fast_grid(F);
   if (bm == 256 && bn == 256) return launch_direct_cfg<256, 256, 8>(a_kc, b_kc, F, grid, stream);
   if (bm == 256 && bn == 128) return launch_direct_cfg<256, 128, 8>(a_kc, b_kc, F, grid, stream);
@@ -235,8 +209,11 @@ static bool try_direct(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P,
   // epilogue (no partial sums, no finishing pass) unless the product is so small that it has to
   // be split to occupy the chip at all.
   auto owns_groups = [](const Axis& a) { return a.kind == AX_AFFINE && a.step >= 1 && a.off < a.step; };
-  bool scatter = !raw_splits && !direct_out && C.fill && !C.out_f32 && C.beta == 0.0f && owns_groups(C.rm) && owns_groups(C.cn) &&
-                 (long)C.rm.nphys * C.ld < (1L << 31) && !dev_knobs().no_scatter;
+  // (so is a plain output whose rows are an odd number of elements: the plain epilogue would store it one
+  // element at a time)
+  const bool odd_rows = direct_out && (C.ld & 1) && C.rm.nphys == P.M && C.cn.nphys == P.N;
+  bool scatter = !raw_splits && ((!direct_out && C.fill) || odd_rows) && !C.out_f32 && C.beta == 0.0f && owns_groups(C.rm) && owns_groups(C.cn) && C.cn.step <= kScatterMaxStep &&
+                 (long)C.rm.nphys * C.ld < (1L << 31) && C.cn.nphys < (1 << 23) && !dev_knobs().no_scatter;
   if (scatter) {
     // tile: as large as still gives every CU a workgroup; at least 64 workgroups or no scatter
     bm = bn = 64;
@@ -326,16 +303,15 @@ static bool try_direct(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P,
     F.scatter = 1;
     F.srm = C.rm;
     F.scn = C.cn;
-    F.scatter_vec = (C.cn.nphys % 8) == 0 && (C.ld % 8) == 0 && ((uintptr_t)C.p & 15) == 0 &&
-                    (!C.relu_src || ((uintptr_t)C.relu_src & 15) == 0) && C.cn.nphys < (1 << 23);
+    const int vec = (C.cn.nphys % 8) == 0 && (C.ld % 8) == 0 && ((uintptr_t)C.p & 15) == 0;
     const int dropped_rows = C.rm.nphys - C.rm.n;
     if (C.rm.step > 1 && dropped_rows > 0) {
       // dropped rows: their own pass over all CUs (recorded with the product in a grouped launch; a call that
       // is not part of a caller's batch makes one of its own for the two)
       F.scatter_rows_only = 1;
       self_batch = batch_self_begin();
-      zero_args = ZeroRowsArgs{(uint16_t*)C.p, (int)C.ld, C.rm.nphys, C.cn.nphys, C.rm.off, C.rm.step, C.rm.n, F.scatter_vec};
-      const long pieces = (long)dropped_rows * (F.scatter_vec ? C.cn.nphys / 8 : C.cn.nphys);
+      zero_args = ZeroRowsArgs{(uint16_t*)C.p, (int)C.ld, C.rm.nphys, C.cn.nphys, C.rm.off, C.rm.step, C.rm.n, vec};
+      const long pieces = (long)dropped_rows * (vec ? C.cn.nphys / 8 : (C.cn.nphys + 14) / 8);
       zero_gx = (pieces + 1023) / 1024;  // four stores per thread
       zero_gx = zero_gx < 1 ? 1 : (zero_gx > 2048 ? 2048 : zero_gx);
       // (recorded behind the product: the product's workgroups have the longer way to go and start first)
@@ -470,99 +446,52 @@ static int32_t tile_lists(const LayerArgs& a, void* ws, size_t ws_bytes, hipStre
   return ARD_OK;
 }
 
+static bool has_tile_lists(const LayerArgs& a, const void* ws, size_t ws_bytes) {
+  const ard_pattern* p = a.po;
+  return (p->d_keep && p->d_mask && p->d_rowptr && p->d_colptr && p->d_csc_rows) || (ws && ws_bytes >= tile_ws_bytes(a.TR, a.TC));
+}
+
 // Tile pattern on the large-tile path: classes of tile rows / columns (see fast.hpp).
 // op 0: Y = X . W^T   1: dX = dY . W   2: dW = dY^T . X
 static bool try_fast_tile(int op, const LayerArgs& a, const void* Ap, const void* Bp, void* Cp, float alpha, int relu,
-                          hipStream_t stream, int32_t& st, const void* relu_src = nullptr) {
+                          const void* ws, size_t ws_bytes, hipStream_t stream, int32_t& st, const void* relu_src = nullptr) {
+  // (fp32 calls without room for the tile lists of the general engine are refused there, as documented)
+  if (a.dtype == ARD_F32)
+    return has_tile_lists(a, ws, ws_bytes) && try_f32_tile(op, a.B, a.I, a.O, a.TR, a.TC, *a.po, Ap, Bp, Cp, alpha, relu, relu_src, stream, st);
   if (a.dtype != ARD_BF16 || dev_knobs().no_fast) return false;
   const int x = a.po->tile_r, y = a.po->tile_c, dp = a.po->dp, o = a.po->b - 1, TR = a.TR, TC = a.TC;
   const int B = a.B, I = a.I, O = a.O;
   if ((I % 8) || (O % 8) || (long)B * O >= (1L << 31) || (long)B * I >= (1L << 31) || (long)O * I >= (1L << 31)) return false;
   if (((uintptr_t)Ap & 15) || ((uintptr_t)Bp & 15)) return false;
-  const int g = gcd_int(TC, dp), Pp = dp / g;
   FastParams F{};
   ClassTab& t = F.tab;
-  auto cnt = [](int total, int first, int step) { return first < total ? (total - first + step - 1) / step : 0; };
+  if (!tile_classes(op, O, I, TR, TC, x, y, dp, o, t)) return false;
+  F.A = (const uint16_t*)Ap, F.B = (const uint16_t*)Bp, F.C = (uint16_t*)Cp;
+  F.ldb = I;
+  F.c_cols_mapped = 1;
   if (op == 0) {
     // contraction blocks: whole 64-deep steps, or the 32-wide tiles of Section 3.2 taken two per step
-    if ((256 % x) || ((y % 64) && y != 32) || Pp > F_MAXCLS) return false;
-    t.ncls = Pp;
-    t.n_step = Pp, t.n_bs = x, t.n_phys = O;
-    t.k_step = dp, t.k_bs = y, t.k_phys = I;
-    for (int c = 0; c < Pp; ++c) {
-      t.n_off[c] = c;
-      t.n_cnt[c] = cnt(TR, c, Pp);
-      const int t0 = (int)((((long)o - (long)c * TC) % dp + dp) % dp);
-      t.k_off[c] = t0;
-      t.k_cnt[c] = cnt(TC, t0, dp);
-      t.mblk[c] = 1;
-    }
-    F.A = (const uint16_t*)Ap, F.lda = I, F.am = axis_identity(B);
-    F.B = (const uint16_t*)Bp, F.ldb = I;
+    if ((256 % x) || ((y % 64) && y != 32)) return false;
+    F.lda = I, F.am = axis_identity(B);
     F.a_elems = (long)B * I, F.b_elems = (long)O * I;
-    F.C = (uint16_t*)Cp, F.ldc = O;
-    F.c_cols_mapped = 1;
+    F.ldc = O;
     F.M = B, F.N = O;
   } else if (op == 1) {
-    if ((256 % y) || ((x % 64) && x != 32) || dp > F_MAXCLS) return false;
-    t.ncls = dp;
-    t.n_step = dp, t.n_bs = y, t.n_phys = I;
-    t.k_step = Pp, t.k_bs = x, t.k_phys = O;
-    for (int c = 0; c < dp; ++c) {
-      t.n_off[c] = c;
-      t.n_cnt[c] = cnt(TC, c, dp);
-      int J0 = -1;
-      for (int J = 0; J < Pp; ++J)
-        if ((((long)J * TC + c - o) % dp + dp) % dp == 0) {
-          J0 = J;
-          break;
-        }
-      t.k_off[c] = J0 < 0 ? 0 : J0;
-      t.k_cnt[c] = J0 < 0 ? 0 : cnt(TR, J0, Pp);
-      t.mblk[c] = 1;
-    }
-    F.A = (const uint16_t*)Ap, F.lda = O, F.am = axis_identity(B);
-    F.B = (const uint16_t*)Bp, F.ldb = I;
+    if ((256 % y) || ((x % 64) && x != 32)) return false;
+    F.lda = O, F.am = axis_identity(B);
     F.a_elems = (long)B * O, F.b_elems = (long)O * I;
-    F.C = (uint16_t*)Cp, F.ldc = I;
-    F.c_cols_mapped = 1;
+    F.ldc = I;
     F.M = B, F.N = I;
   } else {
-    if ((256 % x) || (256 % y) || (x % 8) || (y % 8) || Pp > F_MAXCLS) return false;
-    t.ncls = Pp;
-    t.m_step = Pp, t.m_bs = x, t.m_phys = O;
-    t.n_step = dp, t.n_bs = y, t.n_phys = I;
-    t.k_bs = 0;
-    for (int c = 0; c < Pp; ++c) {
-      t.m_off[c] = c;
-      t.m_cnt[c] = cnt(TR, c, Pp);
-      const int t0 = (int)((((long)o - (long)c * TC) % dp + dp) % dp);
-      t.n_off[c] = t0;
-      t.n_cnt[c] = cnt(TC, t0, dp);
-      t.mblk[c] = ceil_div(t.m_cnt[c], 256 / x);
-    }
-    F.A = (const uint16_t*)Ap, F.lda = O;
-    F.B = (const uint16_t*)Bp, F.ldb = I;
+    if ((256 % x) || (256 % y) || (x % 8) || (y % 8)) return false;
+    F.lda = O;
     F.a_elems = (long)B * O, F.b_elems = (long)B * I;
     F.k = axis_identity(B);
-    F.C = (uint16_t*)Cp, F.ldc = I;
-    F.c_rows_mapped = F.c_cols_mapped = 1;
+    F.ldc = I;
+    F.c_rows_mapped = 1;
     F.M = O, F.N = I;
   }
-  // workgroups per class for a BM x BN tile; "heavy" ones have something to contract
-  auto count = [&](int bm, int bn, int& heavy) {
-    int total = 0;
-    heavy = 0;
-    for (int c = 0; c < t.ncls; ++c) {
-      const int mb = op == 2 ? ceil_div(t.m_cnt[c], bm / x) : ceil_div(B, bm);
-      const int nb = ceil_div(t.n_cnt[c], bn / t.n_bs);
-      t.mblk[c] = mb > 0 ? mb : 1;
-      t.nblk[c] = (t.n_cnt[c] > 0 && mb > 0) ? mb * nb : 0;
-      total += t.nblk[c];
-      if (op == 2 || t.k_cnt[c] > 0) heavy += t.nblk[c];
-    }
-    return total;
-  };
+  auto count = [&](int bm, int bn, int& heavy) { return count_classes(op, t, B, bm, bn, heavy); };
   // Tile choice by estimated time: rounds of workgroups over the chip x contraction steps x the time one
   // round of one step takes with that tile.  A period that does not divide the tile grid leaves classes of
   // 21 or 13 tile rows: wide tiles then end in a mostly empty block and the workgroup count lands just above
@@ -599,7 +528,7 @@ static bool try_fast_tile(int op, const LayerArgs& a, const void* Ap, const void
   F.relu_src = (const uint16_t*)relu_src;
   F.total_tiles = total;
   if (op == 2) {
-    ARD_LAUNCH(zero_dropped_tiles_kernel, dim3((unsigned)(TR * TC)), dim3(256), 0, stream, (uint16_t*)Cp, I, O, I,
+    ARD_LAUNCH(zero_dropped_tiles_kernel<uint16_t>, dim3((unsigned)(TR * TC)), dim3(256), 0, stream, (uint16_t*)Cp, I, O, I,
                        x, y, TC, dp, o);
     hipError_t e = ard::launch_status();
     if (e != hipSuccess) {
@@ -659,14 +588,20 @@ __global__ __launch_bounds__(256) void compact_weight_kernel(const CompactWArgs 
 }
 static bool batch_push_compact_w(const CompactWArgs& a, int gx, int gy);
 
-// out[r][c] = c < cols ? in[r*cols + c] : 0 for c < pad8(cols): aligned copy of a narrow activation
+// Compact copies of up to two operands of one product in one launch: dst[r][c] = src[rows(r)][cols(c)], rows and
+// columns up to the next multiple of 8 zero.  The matrix kernels want 16-byte pieces along the contiguous axis;
+// an operand whose kept columns are strided, whose rows are no multiple of 16 bytes or whose pointer is not
+// aligned is copied once (a few microseconds, its kept part only) instead of being gathered element by element
+// inside the product (layer 1027 x 1501 -> 1203 in bf16, dp = 3 / 2: 35-79 us per product on the general engine).
+struct PackArgs {
+  CompactWArgs job[2];
+  int gx[2], split;  // workgroups along a row; job 1 starts at workgroup `split`
+};
 template <typename T>
-__global__ void pad_cols_kernel(const T* in, int rows, int cols, T* out) {
-  const int pc = pad8(cols);
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long)rows * pc) return;
-  const int r = (int)(idx / pc), c = (int)(idx - (long)r * pc);
-  out[idx] = c < cols ? in[(long)r * cols + c] : (T)0;
+__global__ __launch_bounds__(256) void pack_operands_kernel(const PackArgs a) {
+  const int second = (int)blockIdx.x >= a.split;
+  const int b = (int)blockIdx.x - (second ? a.split : 0), gx = second ? a.gx[1] : a.gx[0];
+  compact_weight_body<T>(second ? a.job[1] : a.job[0], b % gx, b / gx);
 }
 
 static int32_t compact_weight(int32_t dtype, int I, const void* W, void* Wc, const Axis& ao, const Axis& ai,
@@ -684,72 +619,113 @@ static int32_t compact_weight(int32_t dtype, int I, const void* W, void* Wc, con
   return ARD_OK;
 }
 
-// A [rows x cols] activation whose rows are not 16-byte aligned (cols % 8 != 0, bf16) is
-// copied once into the workspace with zero-padded rows, so the product can use 16-byte loads.
-// Returns the pointer to use and its leading dimension; advances ws_off.
-static int32_t aligned_activation(int32_t dtype, const void* p, int rows, int cols, void* ws, size_t ws_bytes,
-                                  size_t& ws_off, hipStream_t stream, const void*& out, int& ld) {
-  out = p;
-  ld = cols;
-  if (dtype != ARD_BF16 || (cols % 8) == 0 || cols > 256) return ARD_OK;
-  const size_t need = align_up((size_t)rows * pad8(cols) * 2, 256);
-  if (!ws || ws_off + need > ws_bytes) return ARD_OK;  // no room: the general kernel copes with the original
-  uint16_t* dst = (uint16_t*)((char*)ws + ws_off);
-  const long total = (long)rows * pad8(cols);
-  ARD_LAUNCH(pad_cols_kernel<uint16_t>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream,
-                     (const uint16_t*)p, rows, cols, dst);
-  ARD_LAUNCH_CHECK("pad_cols_kernel");
-  ws_off += need;
-  out = dst;
-  ld = pad8(cols);
-  return ARD_OK;
-}
-
 constexpr int32_t kLayoutFlags = ARD_IN_COMPACT | ARD_OUT_COMPACT | ARD_W_COMPACT | ARD_DW_COMPACT;
 static bool is_identity(const Axis& a) { return a.kind == AX_AFFINE && a.off == 0 && a.step == 1; }
 
 // Row / list pattern layer: resolves the layout flags into operand descriptions.
 struct RowLayer {
   Axis ao, ai;      // kept output / input neurons
-  bool in_c, out_c; // activations compact on the input / output side
+  bool in_c, out_c; // activations compact on the input / output side (as passed, or packed here)
+  const void *Xp, *dYp;  // activations actually read
   const void* Wp;   // weight operand actually multiplied
   long w_ld;
   Axis w_rows, w_cols;  // maps into Wp (identity when Wp is compact)
   bool w_compact;
-  size_t ws_used;  // bytes of the workspace taken by the gathered weight
+  size_t ws_used;  // bytes of the workspace taken by packed operands
 };
 
-static int32_t resolve_row_layer(const LayerArgs& a, int32_t flags, const void* W, bool need_w, void* ws, size_t ws_bytes,
-                                 hipStream_t stream, RowLayer& L) {
+// Which operands of a product (op 0: X, W; 1: dY, W; 2: dY, X) are copied compact before it.
+struct PackPlan {
+  bool x, w, dy;
+};
+static PackPlan plan_packs(int op, int32_t dtype, int B, int I, int O, const void* X, const void* W, const void* dY, const Axis& ao,
+                           const Axis& ai, int32_t flags) {
+  PackPlan p{};
+  if (ao.n <= 0 || ai.n <= 0) return p;
+  const bool in_c = flags & ARD_IN_COMPACT, out_c = flags & ARD_OUT_COMPACT, w_c = flags & ARD_W_COMPACT;
+  const bool need_x = op != 1 && !in_c, need_dy = op != 0 && !out_c, need_w = op != 2 && !w_c;
+  if (dtype == ARD_BF16) {
+    if (dev_knobs().no_fast) {
+      p.w = need_w && !is_identity(ai);
+      return p;
+    }
+    auto ragged = [](const void* q, int ld) { return (ld % 8) != 0 || ((uintptr_t)q & 15) != 0; };
+    p.x = need_x && (!is_identity(ai) || ragged(X, I));
+    p.dy = need_dy && (!is_identity(ao) || ragged(dY, O));
+    // (the data gradient contracts over the output neurons: with a compact dY its weight has to be compact too)
+    p.w = need_w && (!is_identity(ai) || ragged(W, I) || (op == 1 && !is_identity(ao)));
+    return p;
+  }
+  // fp32 kernels take any map themselves: a copy only pays where strided loads would be repeated often enough
+  // (1024 x 2048 -> 2048, dp = 2 on both sides: 68 us per product gathering, half of that with copies; the weight
+  // gradient gathers whole runs of rows and is better off up to 333 x 1501 -> 1203, 17 us against 19)
+  const bool own = f32_takes_maps(ao, ai);
+  const bool heavy = !own || 2.0 * B * ao.n * ai.n >= (op == 2 ? 5e8 : 6e7);
+  p.x = own && need_x && heavy && !is_identity(ai);
+  p.dy = own && need_dy && heavy && !is_identity(ao);
+  p.w = need_w && heavy && !is_identity(ai);
+  return p;
+}
+
+static int32_t resolve_row_layer(const LayerArgs& a, int op, int32_t flags, const void* X, const void* W, const void* dY, void* ws,
+                                 size_t ws_bytes, hipStream_t stream, RowLayer& L) {
   if (flags & ~(ARD_IN_COMPACT | ARD_OUT_COMPACT | ARD_W_COMPACT | ARD_DW_COMPACT))
     return fail(ARD_EINVAL, "unknown flag bits 0x%x", flags);
   L.ao = axis_of_pattern(a.po, a.O);
   L.ai = axis_of_pattern(a.pi, a.I);
   L.in_c = (flags & ARD_IN_COMPACT) != 0;
   L.out_c = (flags & ARD_OUT_COMPACT) != 0;
-  L.Wp = W;
+  L.Xp = X, L.dYp = dY, L.Wp = W;
   L.w_ld = a.I;
   L.w_rows = L.ao;
   L.w_cols = L.ai;
-  L.w_compact = false;
+  L.w_compact = op != 2 && (flags & ARD_W_COMPACT) != 0;
   L.ws_used = 0;
-  if (!need_w) return ARD_OK;
-  const int es = a.dtype == ARD_BF16 ? 2 : 4;
-  if (flags & ARD_W_COMPACT) {
-    L.w_compact = true;
-  } else if (!is_identity(L.ai) && L.ai.n > 0 && L.ao.n > 0) {
-    // the kept input neurons are strided along the contiguous axis of W: gather the kept block once
+  const size_t es = a.dtype == ARD_BF16 ? 2 : 4;
+  if (op != 2 && !L.w_compact && !is_identity(L.ai) && L.ai.n > 0 && L.ao.n > 0) {
+    // (room for the gathered weight is part of the contract of a call with an input pattern)
     const size_t need = (size_t)pad8(L.ao.n) * pad8(L.ai.n) * es;
     if (!ws || ws_bytes < need) return fail(ARD_EWORKSPACE, "workspace too small: need %zu bytes, got %zu", need, ws_bytes);
-    int32_t st;
-    {
-      BatchSuspend now;  // the product of this very call reads the gathered block
-      st = compact_weight(a.dtype, a.I, W, ws, L.ao, L.ai, stream);
+  }
+  PackPlan plan = plan_packs(op, a.dtype, a.B, a.I, a.O, X, W, dY, L.ao, L.ai, flags);
+  PackArgs pa{};
+  int n = 0;
+  auto add = [&](const void* src, long ld, const Axis& r, const Axis& c) -> const void* {
+    const size_t need = align_up((size_t)pad8(r.n) * pad8(c.n) * es, 256);
+    const int gx = ceil_div(pad8(c.n), 256), gy = ceil_div(pad8(r.n), kCwRows);
+    if (!ws || L.ws_used + need > ws_bytes || (long)gx * gy >= (1L << 30)) return nullptr;  // the general engine copes with the original
+    void* dst = (char*)ws + L.ws_used;
+    L.ws_used += need;
+    pa.job[n] = CompactWArgs{src, dst, ld, r, c};
+    pa.gx[n] = gx;
+    if (n == 0) pa.split = gx * gy;
+    ++n;
+    return dst;
+  };
+  int blocks = 0;
+  if (plan.w) {
+    if (const void* q = add(W, a.I, L.ao, L.ai)) L.Wp = q, L.w_compact = true;
+    blocks = n ? pa.split : 0;
+  }
+  if (plan.x)
+    if (const void* q = add(X, a.I, axis_identity(a.B), L.ai)) {
+      L.Xp = q, L.in_c = true;
+      blocks += pa.gx[n - 1] * ceil_div(pad8(a.B), kCwRows);
     }
+  if (plan.dy)
+    if (const void* q = add(dY, a.O, axis_identity(a.B), L.ao)) {
+      L.dYp = q, L.out_c = true;
+      blocks += pa.gx[n - 1] * ceil_div(pad8(a.B), kCwRows);
+    }
+  if (n == 1 && L.Wp != W) {
+    BatchSuspend now;
+    const int32_t st = compact_weight(a.dtype, a.I, W, const_cast<void*>(L.Wp), L.ao, L.ai, stream);
     if (st) return st;
-    L.Wp = ws;
-    L.w_compact = true;
-    L.ws_used = align_up(need, 256);
+  } else if (n) {
+    BatchSuspend now;  // the product of this very call reads the copies
+    if (a.dtype == ARD_BF16) ARD_LAUNCH(pack_operands_kernel<uint16_t>, dim3((unsigned)blocks), dim3(256), 0, stream, pa);
+    else ARD_LAUNCH(pack_operands_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, stream, pa);
+    ARD_LAUNCH_CHECK("pack_operands_kernel");
   }
   if (L.w_compact) {
     L.w_ld = pad8(L.ai.n);
@@ -894,21 +870,13 @@ static int32_t launch_item_alone(const BatchItem& it, hipStream_t stream) {
   const dim3 grid((unsigned)it.gx, (unsigned)it.gy), block(256);
   switch (it.kind) {
     case GK_DIRECT_KK_64:
-      ARD_LAUNCH_NAMED("gemm_direct_kernel", (gemm_direct_kernel<true, true, 64, 64, 4, 0>), grid, block, it.lds, stream,
-                       *reinterpret_cast<const FastParams*>(it.args));
-      break;
+      return launch_direct_alone<true, true, 64, 64, 4, 0>(*reinterpret_cast<const FastParams*>(it.args), it.gx, stream);
     case GK_DIRECT_KM_64:
-      ARD_LAUNCH_NAMED("gemm_direct_kernel", (gemm_direct_kernel<true, false, 64, 64, 4, 0>), grid, block, it.lds, stream,
-                       *reinterpret_cast<const FastParams*>(it.args));
-      break;
+      return launch_direct_alone<true, false, 64, 64, 4, 0>(*reinterpret_cast<const FastParams*>(it.args), it.gx, stream);
     case GK_DIRECT_MM_64:
-      ARD_LAUNCH_NAMED("gemm_direct_kernel", (gemm_direct_kernel<false, false, 64, 64, 4, 0>), grid, block, it.lds, stream,
-                       *reinterpret_cast<const FastParams*>(it.args));
-      break;
+      return launch_direct_alone<false, false, 64, 64, 4, 0>(*reinterpret_cast<const FastParams*>(it.args), it.gx, stream);
     case GK_DIRECT_MM_128x64:
-      ARD_LAUNCH_NAMED("gemm_direct_kernel", (gemm_direct_kernel<false, false, 128, 64, 4, 0>), grid, block, it.lds, stream,
-                       *reinterpret_cast<const FastParams*>(it.args));
-      break;
+      return launch_direct_alone<false, false, 128, 64, 4, 0>(*reinterpret_cast<const FastParams*>(it.args), it.gx, stream);
     case GK_SKINNY_FWD:
       ARD_LAUNCH(skinny_fwd_kernel, grid, block, it.lds, stream, *reinterpret_cast<const SkinnyArgs*>(it.args));
       break;
@@ -1004,13 +972,15 @@ extern "C" size_t ard_gemm_workspace_bytes(int32_t dtype, int32_t B, int32_t I, 
   if (I <= 0 || O <= 0) return 0;
   if (pat_out && pat_out->kind == ARD_PAT_TILE && pat_out->tile_r > 0 && pat_out->tile_c > 0)
     return tile_ws_bytes(ceil_div(O, pat_out->tile_r), ceil_div(I, pat_out->tile_c));
-  // gathered kept block of W, then room for fp32 partial results of up to 8 contraction splits
+  // compact copies of the operands that may need one (plan_packs), then room for fp32 partial results of up to 8
+  // contraction splits
   const size_t Ok = (size_t)kept_count(pat_out, O), Ik = (size_t)kept_count(pat_in, I), Bn = B > 0 ? (size_t)B : 0;
-  size_t bytes = 0;
   const size_t es = dtype == ARD_BF16 ? 2 : 4;
-  if (pat_in && pat_in->kind != ARD_PAT_NONE) bytes += align_up((size_t)pad8((int)Ok) * pad8((int)Ik) * es, 256);
-  if (O % 8) bytes += align_up(Bn * pad8(O) * es, 256);
-  if (I % 8) bytes += align_up(Bn * pad8(I) * es, 256);
+  const bool bf = dtype == ARD_BF16, po = pat_out && pat_out->kind != ARD_PAT_NONE, pi = pat_in && pat_in->kind != ARD_PAT_NONE;
+  size_t bytes = 0;
+  if (pi || (bf && (po || I % 8))) bytes += align_up((size_t)pad8((int)Ok) * pad8((int)Ik) * es, 256);
+  if (po || (bf && O % 8)) bytes += align_up((size_t)pad8((int)Bn) * pad8((int)Ok) * es, 256);
+  if (pi || (bf && I % 8)) bytes += align_up((size_t)pad8((int)Bn) * pad8((int)Ik) * es, 256);
   const size_t Okp = pad8((int)Ok), Ikp = pad8((int)Ik);
   size_t big = Bn * Okp;
   if (Bn * Ikp > big) big = Bn * Ikp;
@@ -1042,7 +1012,7 @@ extern "C" int32_t ard_drop_gemm_fwd(int32_t dtype, int32_t B, int32_t I, int32_
   size_t ws_used = 0;
   if (a.tile) {
     if (flags) return fail(ARD_EINVAL, "tile patterns take no layout flags");
-    if (try_fast_tile(0, a, X, W, Y, alpha, fuse_relu != 0, stream, st)) return st;
+    if (try_fast_tile(0, a, X, W, Y, alpha, fuse_relu != 0, ws, ws_bytes, stream, st)) return st;
     TileLists L;
     st = tile_lists(a, ws, ws_bytes, stream, L);
     if (st) return st;
@@ -1062,13 +1032,13 @@ extern "C" int32_t ard_drop_gemm_fwd(int32_t dtype, int32_t B, int32_t I, int32_
                                                flags, alpha, 0.0f, fuse_relu != 0, nullptr, stream, &st))
       return st;
     RowLayer L;
-    st = resolve_row_layer(a, flags, W, true, ws, ws_bytes, stream, L);
+    st = resolve_row_layer(a, 0, flags, X, W, nullptr, ws, ws_bytes, stream, L);
     if (st) return st;
     // contraction over the kept input neurons; an operand that is already compact ignores the map.
     // Compact matrices have pad8(count) columns, a compact W also pad8(count) rows, zero filled.
     ws_used = L.ws_used;
     P.k = L.ai;
-    P.A = Operand{X, L.in_c ? pad8(L.ai.n) : I, axis_identity(B), 0, L.in_c, L.in_c, 0};
+    P.A = Operand{L.Xp, L.in_c ? pad8(L.ai.n) : I, axis_identity(B), 0, L.in_c, L.in_c, 0};
     P.B = Operand{L.Wp, L.w_ld, L.w_rows, 0, L.w_compact, L.w_compact, 0};
     if (L.out_c) {
       // the padding columns are written too (as zeros: W has no rows there)
@@ -1111,7 +1081,7 @@ extern "C" int32_t ard_drop_gemm_bwd_data(int32_t dtype, int32_t B, int32_t I, i
   size_t ws_used = 0;
   if (a.tile) {
     if (flags) return fail(ARD_EINVAL, "tile patterns take no layout flags");
-    if ((!relu_src || ((uintptr_t)relu_src & 3) == 0) && try_fast_tile(1, a, dY, W, dX, alpha, 0, stream, st, relu_src)) return st;
+    if ((!relu_src || ((uintptr_t)relu_src & 3) == 0) && try_fast_tile(1, a, dY, W, dX, alpha, 0, ws, ws_bytes, stream, st, relu_src)) return st;
     TileLists L;
     st = tile_lists(a, ws, ws_bytes, stream, L);
     if (st) return st;
@@ -1131,21 +1101,13 @@ extern "C" int32_t ard_drop_gemm_bwd_data(int32_t dtype, int32_t B, int32_t I, i
                                                flags, alpha, 0.0f, 0, relu_src, stream, &st))
       return st;
     RowLayer L;
-    st = resolve_row_layer(a, flags, W, true, ws, ws_bytes, stream, L);
+    st = resolve_row_layer(a, 1, flags, nullptr, W, dY, ws, ws_bytes, stream, L);
     if (st) return st;
     // contraction over the kept output neurons
     ws_used = L.ws_used;
     P.k = L.ao;
-    P.A = Operand{dY, L.out_c ? pad8(L.ao.n) : O, axis_identity(B), 0, L.out_c, L.out_c, 0};
+    P.A = Operand{L.dYp, L.out_c ? pad8(L.ao.n) : O, axis_identity(B), 0, L.out_c, L.out_c, 0};
     P.B = Operand{L.Wp, L.w_ld, L.w_cols, 0, L.w_compact, L.w_compact, L.w_compact};
-    if (!L.out_c && L.w_compact && is_identity(L.ao)) {
-      // narrow dY (last layer): a zero-padded copy lets the contraction run over whole chunks
-      const void* dYp;
-      int dy_ld;
-      st = aligned_activation(dtype, dY, B, O, ws, ws_bytes, ws_used, stream, dYp, dy_ld);
-      if (st) return st;
-      if (dYp != dY) P.A = Operand{dYp, dy_ld, axis_identity(B), 0, 0, 1, 0};
-    }
     if (L.in_c) {
       P.N = pad8(L.ai.n);
       P.C.cn = axis_identity(P.N);
@@ -1186,7 +1148,7 @@ extern "C" int32_t ard_drop_gemm_bwd_weight(int32_t dtype, int32_t B, int32_t I,
   bool dw_compact = false;
   if (a.tile) {
     if (flags) return fail(ARD_EINVAL, "tile patterns take no layout flags");
-    if (beta == 0.0f && try_fast_tile(2, a, dY, X, dW, alpha, 0, stream, st)) return st;
+    if (beta == 0.0f && try_fast_tile(2, a, dY, X, dW, alpha, 0, ws, ws_bytes, stream, st)) return st;
     TileLists L;
     st = tile_lists(a, ws, ws_bytes, stream, L);
     if (st) return st;
@@ -1200,31 +1162,22 @@ extern "C" int32_t ard_drop_gemm_bwd_weight(int32_t dtype, int32_t B, int32_t I,
     P.tm_tc = a.TC;
   } else {
     if (flags & ARD_W_COMPACT) return fail(ARD_EINVAL, "ARD_W_COMPACT has no meaning for the weight gradient");
+    const int32_t both = ARD_IN_COMPACT | ARD_OUT_COMPACT;
+    if ((flags & ARD_DW_COMPACT) && (flags & both) != both) return fail(ARD_EINVAL, "ARD_DW_COMPACT needs ARD_IN_COMPACT and ARD_OUT_COMPACT");
+    if (!(flags & ~kLayoutFlags) && try_skinny(2, dtype, B, I, O, dY, X, dW, axis_of_pattern(pat_out, O), axis_of_pattern(pat_in, I),
+                                               flags, alpha, beta, 0, nullptr, stream, &st))
+      return st;
     RowLayer L;
-    st = resolve_row_layer(a, flags, nullptr, false, ws, ws_bytes, stream, L);
+    st = resolve_row_layer(a, 2, flags, X, nullptr, dY, ws, ws_bytes, stream, L);
     if (st) return st;
-    P.A = Operand{dY, L.out_c ? pad8(L.ao.n) : O, L.out_c ? axis_identity(L.ao.n) : L.ao, 0, 0, 0, L.out_c};
-    P.B = Operand{X, L.in_c ? pad8(L.ai.n) : I, L.in_c ? axis_identity(L.ai.n) : L.ai, 0, 0, 0, L.in_c};
-    if (!L.out_c && is_identity(L.ao)) {
-      const void* q;
-      int q_ld;
-      st = aligned_activation(dtype, dY, B, O, ws, ws_bytes, ws_used, stream, q, q_ld);
-      if (st) return st;
-      if (q != dY) P.A = Operand{q, q_ld, L.ao, 0, 0, 0, 1};
-    }
-    if (!L.in_c && is_identity(L.ai)) {
-      const void* q;
-      int q_ld;
-      st = aligned_activation(dtype, X, B, I, ws, ws_bytes, ws_used, stream, q, q_ld);
-      if (st) return st;
-      if (q != X) P.B = Operand{q, q_ld, L.ai, 0, 0, 0, 1};
-    }
+    ws_used = L.ws_used;
+    P.A = Operand{L.dYp, L.out_c ? pad8(L.ao.n) : O, L.out_c ? axis_identity(L.ao.n) : L.ao, 0, 0, 0, L.out_c};
+    P.B = Operand{L.Xp, L.in_c ? pad8(L.ai.n) : I, L.in_c ? axis_identity(L.ai.n) : L.ai, 0, 0, 0, L.in_c};
     P.C.rm = L.ao;
     P.C.cn = L.ai;
     if (flags & ARD_DW_COMPACT) {
       // dW of the kept synapses only, [pad8(O') x pad8(I')] like a compact weight: both activations
       // come compact, so the padding rows and columns are products of zeros
-      if (!L.out_c || !L.in_c) return fail(ARD_EINVAL, "ARD_DW_COMPACT needs ARD_IN_COMPACT and ARD_OUT_COMPACT");
       const int Mp = pad8(L.ao.n), Np = pad8(L.ai.n);
       P.A.r = axis_identity(Mp);
       P.B.r = axis_identity(Np);
@@ -1233,9 +1186,6 @@ extern "C" int32_t ard_drop_gemm_bwd_weight(int32_t dtype, int32_t B, int32_t I,
       dw_compact = true;
     }
   }
-  if (!a.tile && try_skinny(2, dtype, B, I, O, dY, X, dW, axis_of_pattern(pat_out, O), axis_of_pattern(pat_in, I), flags, alpha,
-                            beta, 0, nullptr, stream, &st))
-    return st;
   P.A.vec = operand_vec_ok(P.A, false, P.k, ce);
   P.B.vec = operand_vec_ok(P.B, false, P.k, ce);
   P.C.p = dW;
