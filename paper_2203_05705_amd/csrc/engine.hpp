@@ -529,6 +529,21 @@ int32_t run_gemm(int32_t dtype, bool a_kc, bool b_kc, GemmParams P, int max_bn, 
 bool run_gemm_partials(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P, hipStream_t stream, void* part,
                        size_t part_bytes, int* splits, int32_t* status);
 
+// Zero-bordered channel planes of an fp32 convolution (conv.hip): planes of `plane` elements (a multiple of 16),
+// rows `Wg` elements apart, Cp channels per image (a multiple of 16, the extra ones zero).
+struct F32Conv {
+  int HoWo, Wo;        // output pixels per image / per row
+  int Wg, plane, Cp;   // of the B grid
+  int Co;              // weight gradient: channels per image of the gradient's grid
+  int kw, taps;
+  int npix;            // forward, data gradient: output pixels over the batch
+  FastDiv per_row, per_img, steps_inner;  // Wo, HoWo, 16-deep contraction steps per tap / (weight gradient) per image
+  FastDiv by_cp, by_kw;
+};
+int32_t f32_conv_product(const float* W, int rows, const float* grid, const F32Conv& cv, const OutMat& C, hipStream_t stream);
+int32_t f32_conv_wgrad(const float* grid_y, const float* grid_a, const F32Conv& cv, int N, int rows, int cap, float* part, int* splits,
+                       hipStream_t stream);
+
 // fp32 products on the register-direct kernels (fast32.hip); false: not taken, nothing launched
 bool try_f32(bool a_kc, bool b_kc, const GemmParams& P, void* ws, size_t ws_bytes, hipStream_t stream, int32_t& st);
 bool try_f32_tile(int op, int B, int I, int O, int TR, int TC, const ard_pattern& pat, const void* Ap, const void* Bp, void* Cp,

@@ -168,6 +168,64 @@ bool try_f32(bool a_kc, bool b_kc, const GemmParams& P, void* ws, size_t ws_byte
   return true;
 }
 
+// Convolution on the zero-bordered channel planes of the grid (conv.hip): C[row][pixel] = sum over (tap, channel)
+// of W[row][tap*Cp + channel] * grid, row r stored to channel plane C.rm(r).
+int32_t f32_conv_product(const float* W, int rows, const float* grid, const F32Conv& cv, const OutMat& C, hipStream_t stream) {
+  F32Params F{};
+  const int taps_cp = cv.taps * cv.Cp;
+  F.A = W, F.B = grid, F.lda = taps_cp;
+  F.am = axis_identity(rows), F.bn = axis_identity(cv.npix), F.k = axis_identity(taps_cp);
+  F.C = C, F.M = rows, F.N = cv.npix, F.splits = 1;
+  F.cv = cv;
+  int cfg = 0;
+  float best = 0.0f;
+  for (int i = 0; i < 4; ++i) {
+    const F32Cfg& c = kF32Cfgs[i];
+    const long tiles = (long)ceil_div(rows, c.bm) * ceil_div(cv.npix, c.bn);
+    const float t = f32_clocks(c, tiles, taps_cp, 1, 1.0f);
+    if (i == 0 || t < best) best = t, cfg = i;
+  }
+  F.tiles_m = ceil_div(rows, kF32Cfgs[cfg].bm), F.tiles_n = ceil_div(cv.npix, kF32Cfgs[cfg].bn);
+  if ((long)F.tiles_m * F.tiles_n >= (1L << 24)) return fail(ARD_ESHAPE, "convolution too large for one launch");
+  F.total_tiles = F.tiles_m * F.tiles_n;
+  set_bands(F, direct_group_m(F.total_tiles));
+  const int grid_x = direct_plain_grid(F.total_tiles);
+  // (groups of four pixels are contiguous where output rows are whole numbers of them)
+  return cv.Wo % 4 == 0 ? launch_f32<F32_KC_VEC, F32_MC_VEC, 1>(F, cfg, grid_x, stream) : launch_f32<F32_KC_VEC, F32_MC, 1>(F, cfg, grid_x, stream);
+}
+
+// Its weight gradient: part[split][co][tap*Cp + channel] = sum over the pixels of the grid planes of dY * A, both
+// read along their planes; the contraction is split until the chip is full, `cap` partial results at most.
+// Returns the number of splits through *splits.
+int32_t f32_conv_wgrad(const float* grid_y, const float* grid_a, const F32Conv& cv, int N, int rows, int cap, float* part, int* splits,
+                       hipStream_t stream) {
+  F32Params F{};
+  const int cols = cv.taps * cv.Cp, K = N * cv.plane, steps = K / 16;
+  F.A = grid_y, F.B = grid_a, F.lda = cv.plane;
+  F.am = axis_identity(rows), F.bn = axis_identity(cols), F.k = axis_identity(K);
+  F.M = rows, F.N = cols;
+  F.cv = cv;
+  F.part = part;
+  int cfg = 1, sp = 1;
+  float best = 0.0f;
+  for (int i = 0; i < 3; ++i) {
+    const F32Cfg& c = kF32Cfgs[i];
+    const long tiles = (long)ceil_div(rows, c.bm) * ceil_div(cols, c.bn);
+    for (int s = 1; s <= cap && s * 4 * c.wk <= imax(steps, 4 * c.wk); s = s < 8 ? s + 1 : s + s / 4) {
+      // (what the pass over the partial results costs: they come and go at about 1000 bytes a clock)
+      const float t = f32_clocks(c, tiles, K, s, 1.0f) + (float)s * rows * cols * 8.0f / 1000.0f;
+      if (best == 0.0f || t < best) best = t, cfg = i, sp = s;
+    }
+  }
+  F.tiles_m = ceil_div(rows, kF32Cfgs[cfg].bm), F.tiles_n = ceil_div(cols, kF32Cfgs[cfg].bn);
+  if ((long)F.tiles_m * F.tiles_n * sp >= (1L << 24)) return fail(ARD_ESHAPE, "convolution too large for one launch");
+  F.total_tiles = F.tiles_m * F.tiles_n;
+  F.splits = sp;
+  set_bands(F, direct_group_m(F.total_tiles));
+  *splits = sp;
+  return launch_f32<F32_KC_VEC, F32_KC_VEC, 2>(F, cfg, direct_plain_grid(F.total_tiles * sp), stream);
+}
+
 // Tile pattern (Section 3.2): classes of tile rows or columns as in the bf16 kernels (tile_classes); any tile
 // size works, a tile wider than the workgroup's tile is taken in parts.
 bool try_f32_tile(int op, int B, int I, int O, int TR, int TC, const ard_pattern& pat, const void* Ap, const void* Bp, void* Cp,

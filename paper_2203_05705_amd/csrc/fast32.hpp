@@ -20,17 +20,6 @@
 
 namespace ard {
 
-struct F32Conv {
-  int HoWo, Wo;        // output pixels per image / per row
-  int Wg, plane;       // grid: row pitch, elements per channel plane (a multiple of 16)
-  int Cp;              // channels of the B grid (MODE 1: a multiple of 16)
-  int Co;              // MODE 2: channels of the A grid
-  int kw;
-  int npix;            // MODE 1: columns of the product
-  FastDiv per_row, per_img, steps_inner;  // Wo, HoWo, contraction steps per tap (MODE 1) / per image (MODE 2)
-  FastDiv by_cp, by_kw;
-};
-
 // (What every workgroup reads first comes first: the arguments are fetched line by line.)
 struct F32Params {
   const float *A, *B;
@@ -165,14 +154,14 @@ template <int KIND, int T> struct F32LoaderMC {
   }
   // MODE 1: rows = output pixels, contraction = channels of one tap (`plane` elements apart)
   __device__ __forceinline__ void init_pixels(const float* p, const F32Conv& cv, int row0, int lane) {
-    static_assert(!VEC, "pixels are addressed one by one");
     base = reinterpret_cast<const char*>(p);
     const int i = lane & 15, g = lane >> 4;
     k4 = 4 * g;
     kunit = kst = (long)cv.plane * 4;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int row = imin(row0 + T * i + t, cv.npix - 1);
+    for (int t = 0; t < NV; ++t) {
+      // (VEC: output rows are whole groups of T pixels, so a group never straddles two)
+      const int row = VEC ? imin(row0 + T * i, cv.npix - T) : imin(row0 + T * i + t, cv.npix - 1);
       const int n = (int)fdiv((uint32_t)row, cv.per_img), rem = row - n * cv.HoWo;
       const int ho = (int)fdiv((uint32_t)rem, cv.per_row), wo = rem - ho * cv.Wo;
       voff[t] = ((uint32_t)(n * cv.Cp + 4 * g) * (uint32_t)cv.plane + (uint32_t)(ho * cv.Wg + wo)) * 4u;
@@ -400,18 +389,6 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   constexpr int CL = BN < 64 ? BN : 64;           // threads along a row of the tile
   constexpr int RP = 256 / CL;
   const int tc = tid % CL, tr = tid / CL;
-  if constexpr (MODE == 1) {
-    // row = channel (C.rm: kept-channel list or identity), column = pixel (image, position)
-    for (int lc = tc; lc < BN; lc += CL) {
-      const int j = w.n0 + lc;
-      if (j >= P.N) continue;
-      const int n = (int)fdiv((uint32_t)j, P.cv.per_img);
-      float* col = (float*)C.p + (long)n * C.img_stride + (j - n * P.cv.HoWo);
-      for (int lr = tr; lr < BM; lr += RP)
-        if (w.m0 + lr < P.M) col[(long)ax_phys(C.rm, w.m0 + lr) * C.plane] = sum(lr, lc);
-    }
-    return;
-  }
   // One loop for every kind of output: a slot of the tile's columns is a physical column, a row a compact one with
   // the physical rows it owns.  With zero fill compact index i of an affine map owns the group [i*step,
   // (i+1)*step), of a list the positions up to the next kept one.
@@ -421,7 +398,7 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   const Axis rows = raw ? axis_identity(P.M) : P.c_rows_mapped ? w.am : classes ? axis_identity(P.M) : C.rm;
   const Axis cols = raw ? axis_identity(P.N) : P.c_cols_mapped ? w.bn : classes ? axis_identity(P.N) : C.cn;
   float* const out = raw ? P.part + (long)w.split * P.M * P.N : (float*)C.p;
-  const long ld = raw ? P.N : C.ld;
+  const long ld = raw ? P.N : MODE == 1 ? C.plane : C.ld;  // (MODE 1: a row is a channel plane)
   const float alpha = raw ? 1.0f : C.alpha, beta = raw ? 0.0f : C.beta;
   const float* const src = raw ? nullptr : (const float*)C.relu_src;
   const bool relu = !raw && C.relu;
@@ -455,7 +432,11 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   const int nr = m1 - w.m0, i_ok = classes ? nr : imin(nr, w.am.n - w.m0);
   for (int c = w.n0 * sc + tc; c < c_end; c += CL) {
     int j = c, clo, chi, cp;
-    if (walk) {
+    if constexpr (MODE == 1) {
+      const int n = (int)fdiv((uint32_t)j, P.cv.per_img);  // column = (image, position)
+      cp = n * (int)C.img_stride + (j - n * P.cv.HoWo);
+      clo = cp, chi = cp + 1;
+    } else if (walk) {
       const int d = c - cols.off;
       j = d >= 0 ? (int)fdiv((uint32_t)d, P.col_div) : 0;
       const bool kept = d >= 0 && j * sc == d && j < P.N;
