@@ -947,9 +947,9 @@ __global__ __launch_bounds__(256) void to_grid_src_kernel(const uint16_t* src, c
 // multiple of 16, both filled up with zeros): a tap is then a constant offset into a plane, no load needs a bounds
 // test, and the products of fast32.hpp read the planes as they are (forward and data gradient: channels of a tap
 // along the contraction, pixels along a plane; weight gradient: pixels of a plane along the contraction).  The
-// general engine computed every element's patch address and tested it against the border.  N=32, C=Cout=128, 32x32,
-// 3x3, half of the channels kept: forward 136 -> 43 us (75 TFLOP/s), data gradient 193 -> 43, weight gradient 165 -> 33
-// (where the cost model takes the 64x64 and 32x32 tiles: 256 and 512 workgroups), copies 6.5 + 8.8 + 12.9 us.
+// general engine computed every element's patch address and tested it against the border.  N=64, C=Cout=64, 32x32,
+// 3x3, half of the channels kept (2.4 GFLOP a pass): forward 136 -> 32 us, data gradient 193 -> 29, weight gradient
+// 165 -> 33, copies 6.5 + 8.8 + 12.9 us.
 struct PlaneCopy {
   const float* src;
   const int* chan;   // kept channels (NULL: all)
