@@ -331,8 +331,8 @@ size_t ard_conv_workspace_bytes(int32_t dtype, int32_t N, int32_t C, int32_t H, 
  * BWD_DATA_ROWS / BWD_WEIGHT_ROWS: the gradients of FWD_ROWS with respect to A and Wt.  Only kept rows took
  *   part in the product, so gradient arriving on a dropped position counts as zero: d_mask[N*Ho*Wo] is the
  *   row mask; BWD_DATA / BWD_WEIGHT run with every channel kept on a dY whose dropped positions are zero
- *   (zeroed while dY is copied into its grid; a masked copy for fp32 and strided layers).  No time is saved
- *   over an undropped layer; n_keep, d_keep are ignored.  Needs dYin, d_mask and Wt (data) or A (weight).
+ *   (zeroed while dY is copied into its grid; a masked copy for fp32 and strided layers).  The bf16 stride-1
+ *   weight gradient contracts over the kept positions only; n_keep, d_keep are ignored.  Needs dYin, d_mask and Wt (data) or A (weight).
  *   The reuse flags apply as for BWD_DATA / BWD_WEIGHT: ARD_CONV_REUSE_A takes the grid FWD_ROWS left,
  *   ARD_CONV_REUSE_DY the masked grid an earlier *_ROWS gradient of the same mask left.
  * FWD / BWD_DATA / BWD_WEIGHT read the kept channels from d_keep (n_keep entries,
@@ -418,7 +418,12 @@ int32_t ard_conv_fwd_blocks(int32_t dtype, int32_t N, int32_t C, int32_t H, int3
  *          pixel of sum_co dY[n,co,p] * Wt[co,q]; needs Wt and dYin (A unused, may be NULL); stride 1 and
  *          pad <= k-1 only, as for ARD_CONV_BWD_DATA of ard_fmap_drop_conv (else ARD_EUNSUPPORTED).
  * Every element of out is written.  d_block_keep, x, y, workspace and dtypes as for ard_conv_fwd_blocks.
- * No work is skipped.  Blocks of whole channels (y % (kh*kw) == 0, at most 16 column blocks): per column
+ * bf16, stride 1, blocks of whole channels (y % (8*kh*kw) == 0): the weight gradient contracts, for every
+ * group of channels, over its kept positions only; with groups of whole 64 channels, bands of whole output rows
+ * and a size-preserving filter the data gradient leaves out the filter rows that read dropped bands only.  mode may
+ * then carry ARD_CONV_REUSE_DY for the weight gradient: the same workspace still holds the copy of dY the data
+ * gradient of the same dYin and d_block_keep made (ignored where that pass left none).
+ * Other blocks of whole channels (y % (kh*kw) == 0, at most 16 column blocks), without skipping work: per column
  * block, dY is copied with the positions of that block's dropped bands zeroed and the ordinary gradient
  * pass runs on the copy with the block's channels as the kept list (the fast path where the shape allows).
  * Other block shapes run on the general convolution engine: the weight gradient masks the patches it

@@ -15,7 +15,7 @@
 #include <stdlib.h>
 
 #include "engine.hpp"
-#include "fast.hpp"
+#include "conv_blocks.hpp"
 #include "pattern.hpp"
 
 namespace ard {
@@ -786,6 +786,70 @@ __global__ __launch_bounds__(256) void block_plan_kernel(BlockPlanJob j) {
   block_plan_body(j, (int)blockIdx.x, red4);
 }
 
+// Ascending list, per column block cb, of the output positions (n * HoWo + p) whose band the pattern keeps, and
+// their number (row-based pattern: CB = 1, bands of one position).  Workgroup (cb, g) takes the g-th share of the
+// bands; where its part of the list starts is the number of kept positions before the share, which it counts
+// itself: no pass of its own, no hand-over.
+struct PosListJob {
+  const uint8_t* blk;
+  int bands, RB, CB, x, HoWo, parts, stride;  // bands = N * RB
+  int *list, *cnt;
+  int blocks;  // = CB * parts (0: no job)
+};
+__device__ __forceinline__ int band_positions(const PosListJob& j, int cb, int b) {  // kept positions of band b
+  return j.blk[(long)b * j.CB + cb] ? min(j.x, j.HoWo - b % j.RB * j.x) : 0;
+}
+__device__ __forceinline__ void pos_list_body(const PosListJob& j, int block, int* lds /* [520] */) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cb = block / j.parts, g = block - cb * j.parts;
+  const int b0 = (int)((long)g * j.bands / j.parts), b1 = (int)((long)(g + 1) * j.bands / j.parts);
+  int before = 0;
+  if (j.x == 1 && j.CB == 1 && ((uintptr_t)j.blk & 15) == 0) {
+    // bytes of a mask, 16 at a time
+    for (int b = tid * 16; b + 16 <= b0; b += 4096) {
+      const uint4 v = *reinterpret_cast<const uint4*>(j.blk + b);
+      for (uint32_t w : {v.x, v.y, v.z, v.w}) before += __popc((w | ((w & 0x7f7f7f7fu) + 0x7f7f7f7fu)) & 0x80808080u);
+    }
+    for (int b = (b0 & ~15) + tid; b < b0; b += 256) before += j.blk[b] ? 1 : 0;
+  } else {
+    for (int b = tid; b < b0; b += 256) before += band_positions(j, cb, b);
+  }
+  for (int o = 32; o > 0; o >>= 1) before += __shfl_down(before, o, 64);
+  if (lane == 0) lds[512 + wave] = before;
+  __syncthreads();
+  int at = lds[512] + lds[513] + lds[514] + lds[515];
+  int* const out = j.list + (long)cb * j.stride;
+  for (int c = b0; c < b1; c += 256) {
+    const int b = c + tid, len = b < b1 ? band_positions(j, cb, b) : 0;
+    int incl = len;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      incl += lane >= o ? v : 0;
+    }
+    if (lane == 63) lds[516 + wave] = incl;
+    __syncthreads();
+    int first = at;
+    for (int w = 0; w < 4; ++w) {
+      first += w < wave ? lds[516 + w] : 0;
+      at += lds[516 + w];
+    }
+    first += incl - len;
+    if (j.x == 1) {
+      if (len) out[first] = b / j.RB * j.HoWo + b % j.RB;
+    } else {
+      // a wavefront takes every fourth band, 64 positions at a time
+      lds[tid] = len, lds[256 + tid] = first;
+      __syncthreads();
+      for (int i = wave; i < min(256, b1 - c); i += 4) {
+        const int n = lds[i], to = lds[256 + i], bi = c + i, p0 = bi / j.RB * j.HoWo + bi % j.RB * j.x;
+        for (int e = lane; e < n; e += 64) out[to + e] = p0 + e;
+      }
+    }
+    __syncthreads();
+  }
+  if (g == j.parts - 1 && tid == 0) j.cnt[cb] = at;
+}
+
 // Wp[row][tap*Cp + q]: forward (flip = 0): row = output channel, q = kept input channel;
 // data gradient (flip = 1): row = kept input channel, q = output channel, taps reversed.
 struct PackJob {
@@ -849,7 +913,7 @@ __global__ __launch_bounds__(256) void to_grid_src_kernel(const uint16_t* src, c
                                                           int Ws, FastDiv div_ws, int Hg, int Wg, int oh, int ow, int Cp,
                                                           int N,
                                                           long n_pix_total, BandMask bm, uint16_t* dst, PackJob pj,
-                                                          ZeroPlanesJob zj, ZeroPixelsJob zp, BlockPlanJob bj, int main_x) {
+                                                          ZeroPlanesJob zj, ZeroPixelsJob zp, BlockPlanJob bj, PosListJob lj, int main_x) {
   __shared__ uint32_t tile[64 * 32];
   __shared__ int red4[4];
   // (workgroups beyond the copy's own pack the weights of the product that follows and zero the planes it will
@@ -857,7 +921,9 @@ __global__ __launch_bounds__(256) void to_grid_src_kernel(const uint16_t* src, c
   // (they come first in the launch: started last they would be a tail of their own behind the copy)
   const int extra_x = (int)gridDim.x - main_x;
   if ((int)blockIdx.x < extra_x) {
-    const int b = (int)blockIdx.x * (int)gridDim.y + (int)blockIdx.y;
+    int b = (int)blockIdx.x * (int)gridDim.y + (int)blockIdx.y;
+    if (b < lj.blocks) return pos_list_body(lj, b, reinterpret_cast<int*>(tile));
+    b -= lj.blocks;
     if (b < pj.blocks) pack_weights_body<uint16_t>(pj, (long)b * 256 + threadIdx.x);
     else if (b < pj.blocks + zj.blocks) zero_dropped_planes_body(zj, b - pj.blocks);
     else if (b < pj.blocks + zj.blocks + zp.blocks) zero_dropped_pixels_body(zp, b - pj.blocks - zj.blocks);
@@ -1044,10 +1110,12 @@ __global__ void iota_kernel(int* p, int n) {
 // A thread owns one kept synapse (co, tap, r): consecutive threads read consecutive r (coalesced), the
 // loads of the splits are independent and summed in split order.  The same launch writes the zeros of
 // the dropped channels (its first gridDim.x - zero_blocks workgroups sum, the rest zero).
+// (column blocks of a pattern: channels lie in groups of `group`, part[sp][co][(r / group) * taps * Cp + tap*Cp +
+// r % group] with Cp channels reserved per group; one group else.  keep NULL: every channel.)
 template <typename T>
 __global__ __launch_bounds__(256) void wgrad_grid_reduce_kernel(const float* part, const int* keep, int n_keep, int splits,
-                                                                int Cout, int C, int taps, int Cp, int sum_blocks, T* dWt) {
-  const int Nn = taps * Cp;
+                                                                int Cout, int C, int taps, int Cp, int sum_blocks, int group, int pitch, T* dWt) {
+  const int Nn = pitch;
   if ((int)blockIdx.x < sum_blocks) {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (long)Cout * taps * n_keep) return;
@@ -1055,7 +1123,8 @@ __global__ __launch_bounds__(256) void wgrad_grid_reduce_kernel(const float* par
     const uint32_t i32 = (uint32_t)idx, q1 = i32 / (uint32_t)n_keep;
     const int r = (int)(i32 - q1 * (uint32_t)n_keep);
     const int co = (int)(q1 / (uint32_t)taps), tap = (int)(q1 - (uint32_t)co * (uint32_t)taps);
-    const float* p = part + (long)co * Nn + tap * Cp + r;
+    const int cb = r / group;
+    const float* p = part + (long)co * Nn + (cb * taps + tap) * Cp + r - cb * group;
     const long stride = (long)Cout * Nn;
     float s = 0.0f;
     int sp = 0;
@@ -1067,7 +1136,7 @@ __global__ __launch_bounds__(256) void wgrad_grid_reduce_kernel(const float* par
       s += v3;
     }
     for (; sp < splits; ++sp) s += p[sp * stride];
-    dWt[((long)co * C + keep[r]) * taps + tap] = ElemTraits<T>::from_f32(s);
+    dWt[((long)co * C + (keep ? keep[r] : r)) * taps + tap] = ElemTraits<T>::from_f32(s);
     return;
   }
   // zeros of the dropped channels: one thread per (co, c)
@@ -1087,6 +1156,10 @@ struct ConvArgs {
   int32_t bx, by;
   int32_t kept_only;  // gradients: write the kept channels' part of the output only (the caller covers the rest)
   BandMask dy_mask;   // gradients on the channels-last grids: positions of dY that count (blk == NULL: all)
+  // weight gradient on the channels-last grids: contract over the kept positions only (blk == NULL: over all), for each
+  // group of `cpb` channels over its own (0: one group)
+  PosListJob lists;
+  int32_t cpb;
 };
 
 struct ConvWs {
@@ -1105,6 +1178,8 @@ struct ConvWs {
   size_t plane_part_bytes;
   int *blk_pix, *blk_kb, *blk_cnt;  // block pattern on the fast path: padded pixel list, per-tile block lists and counts
   size_t blk_ints;                  // ints reserved for blk_pix and for blk_kb
+  int *pos_list, *pos_cnt;          // kept output positions of every column block of a pattern (pos_blocks at most)
+  int pos_blocks;
   size_t total;
   int splits;
   int gsplits;  // contraction splits of the fast weight-gradient product
@@ -1173,6 +1248,8 @@ static ConvWs conv_ws_layout(char* base, const ConvArgs& a) {
   w.gpart = nullptr;
   w.blk_pix = w.blk_kb = w.blk_cnt = nullptr;
   w.blk_ints = 0;
+  w.pos_list = w.pos_cnt = nullptr;
+  w.pos_blocks = 0;
   w.gsplits = 1;
   w.plane_a = w.plane_y = w.plane_wp = w.plane_part = nullptr;
   w.plane_part_bytes = 0;
@@ -1202,6 +1279,9 @@ static ConvWs conv_ws_layout(char* base, const ConvArgs& a) {
     w.blk_pix = (int*)take(w.blk_ints * 4);
     w.blk_kb = (int*)take(w.blk_ints * 4);
     w.blk_cnt = (int*)take((w.blk_ints / 128 + 1) * 4 * 2);  // counts, then the tiles' places in the launch
+    w.pos_blocks = imin(pad64(a.C) / 64, 16);
+    w.pos_list = (int*)take((size_t)w.pos_blocks * a.N * a.Ho * a.Wo * 4);
+    w.pos_cnt = (int*)take((size_t)w.pos_blocks * 4);
   }
   w.total = off;
   return w;
@@ -1241,14 +1321,14 @@ static bool al16c(const void* p) { return ((uintptr_t)p & 15) == 0; }
 static int32_t to_grid(const void* src, const int* chan, int n_chan, int Cs, int Hs, int Ws, int N, int Hg, int Wg, int oh,
                        int ow, int Cp, long margin, uint16_t* dst, hipStream_t stream, BandMask bm = BandMask{},
                        PackJob pj = PackJob{}, ZeroPlanesJob zj = ZeroPlanesJob{}, ZeroPixelsJob zp = ZeroPixelsJob{},
-                       BlockPlanJob bj = BlockPlanJob{}) {
+                       BlockPlanJob bj = BlockPlanJob{}, PosListJob lj = PosListJob{}) {
   const long total = (long)N * Hg * Wg + margin;
   if (oh < 0 || ow < 0 || Hg < oh + Hs || Wg < ow + Ws) return fail(ARD_EINVAL, "grid copy: the image does not fit the grid");
   const int main_x = N * ceil_div(Hs * Ws, 64);
   const int gy = Cp / 64;
-  dim3 grid((unsigned)(main_x + ceil_div(pj.blocks + zj.blocks + zp.blocks + bj.blocks, gy)), (unsigned)gy);
+  dim3 grid((unsigned)(main_x + ceil_div(pj.blocks + zj.blocks + zp.blocks + bj.blocks + lj.blocks, gy)), (unsigned)gy);
   ARD_LAUNCH(to_grid_src_kernel, grid, dim3(256), 0, stream, (const uint16_t*)src, chan, n_chan, Cs, Hs, Ws,
-             fast_div((uint32_t)Ws), Hg, Wg, oh, ow, Cp, N, total, bm, dst, pj, zj, zp, bj, main_x);
+             fast_div((uint32_t)Ws), Hg, Wg, oh, ow, Cp, N, total, bm, dst, pj, zj, zp, bj, lj, main_x);
   ARD_LAUNCH_CHECK("to_grid_src_kernel");
   return ARD_OK;
 }
@@ -1308,6 +1388,16 @@ static int32_t conv_grid_gemm(const uint16_t* Wp, int rows, int K, const uint16_
   if (bm == 256) return launch_direct_kernel<true, true, 256, 128, 8, 1>(F, grid, stream);
   if (bm == 128) return launch_direct_kernel<true, true, 128, 256, 8, 1>(F, grid, stream);
   return launch_direct_kernel<true, true, 64, 64, 4, 1>(F, grid, stream);
+}
+
+// The kept positions of the column blocks of a pattern (bands of x positions, CB blocks), listed in the workspace
+static PosListJob pos_list_job(const ConvArgs& a, const uint8_t* blk, int x, int CB, const ConvWs& w) {
+  PosListJob j{};
+  j.blk = blk, j.HoWo = a.Ho * a.Wo, j.x = x, j.RB = ceil_div(j.HoWo, x), j.CB = CB, j.bands = a.N * j.RB;
+  j.parts = imin(imax(j.bands / (x == 1 ? 512 : 32), 1), 128);  // (a share is a few rounds of the workgroup)
+  j.stride = a.N * j.HoWo;
+  j.list = w.pos_list, j.cnt = w.pos_cnt, j.blocks = CB * j.parts;
+  return j;
 }
 
 // The column tile (128 or 256 positions) that wastes the least padding, or 0 when this path does not apply.
@@ -1413,7 +1503,8 @@ static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, c
                          a.C * ceil_div(a.N, ZP_IMGS)};
     }
     if (!(a.reuse & ARD_CONV_REUSE_DY)) {
-      st = to_grid(dYin, nullptr, a.Cout, a.Cout, a.Ho, a.Wo, a.N, Hg, Wg, ph, pw, Cp, margin, w.grid_y, stream, a.dy_mask, pj, zj);
+      st = to_grid(dYin, nullptr, a.Cout, a.Cout, a.Ho, a.Wo, a.N, Hg, Wg, ph, pw, Cp, margin, w.grid_y, stream, a.dy_mask, pj, zj,
+                   ZeroPixelsJob{}, BlockPlanJob{}, a.lists);
     } else {
       ARD_LAUNCH(pack_weights_grid_kernel, dim3((unsigned)pj.blocks), dim3(256), 0, stream, pj);
       ARD_LAUNCH_CHECK("pack_weights_grid_kernel");
@@ -1436,10 +1527,14 @@ static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, c
   // dY: bordered like the data gradient's grid when the filter preserves the size (then shared with it)
   const int ph = same ? a.kh - 1 - a.pad : 0, pw = same ? a.kw - 1 - a.pad : 0;
   const long y_shift = (long)ph * Wg + pw;  // pixels between the bordered grid's origin and dY(., 0, 0)
+  // (the lists of kept positions are made in the launch of dY's copy, by either gradient: who shares the copy shares them)
   if (!(a.reuse & ARD_CONV_REUSE_DY))
-    st = to_grid(dYin, nullptr, a.Cout, a.Cout, a.Ho, a.Wo, a.N, Hg, Wg, ph, pw, Cpy, margin, w.grid_y, stream, a.dy_mask);
+    st = to_grid(dYin, nullptr, a.Cout, a.Cout, a.Ho, a.Wo, a.N, Hg, Wg, ph, pw, Cpy, margin, w.grid_y, stream, a.dy_mask, PackJob{},
+                 ZeroPlanesJob{}, ZeroPixelsJob{}, BlockPlanJob{}, a.lists);
   if (st) return st;
-  const int Kq = a.N * Hg * Wg, Nn = taps * Cpa;
+  const bool listed = a.lists.blk != nullptr;
+  const int group = a.cpb ? a.cpb : Cpa, groups = a.cpb ? a.lists.CB : 1, cols = taps * group;  // columns of a group of channels
+  const int Kq = a.N * Hg * Wg, Nn = groups * cols;
   FastParams F{};
   F.A = w.grid_y + y_shift * Cpy;
   F.B = w.grid_a;
@@ -1459,7 +1554,7 @@ static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, c
   const int bm = big ? 256 : 128;
   const long cap = (long)w.gsplits * taps * pad64(a.C) / Nn;
   F.tiles_m = ceil_div(a.Cout, bm);
-  F.tiles_n = ceil_div(Nn, 128);
+  F.tiles_n = groups * ceil_div(cols, 128);
   F.total_tiles = F.tiles_m * F.tiles_n;
   int splits = (big ? 256 : 512) / F.total_tiles;
   if (splits > cap) splits = (int)cap;
@@ -1469,17 +1564,65 @@ static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, c
   F.splits = splits;
   F.M = a.Cout;
   F.N = Nn;
-  F.cv = ConvMap{0, 0, Hg * Wg, Wg, Cpa, a.kw, 0, 0, nullptr, 0, nullptr, 0, -1};
+  F.cv = ConvMap{a.Ho * a.Wo, a.Wo, Hg * Wg, Wg, Cpa, a.kw, 0, 0, nullptr, 0, nullptr, a.N * a.Ho * a.Wo, -1};
+  if (listed) F.li = ListMap{0, a.lists.stride, a.N * a.Ho * a.Wo, ceil_div(cols, 128), cols, a.cpb, group, a.N * Hg * Wg, a.lists.list, a.lists.cnt};
   set_bands(F, direct_group_m(F.total_tiles));
-  st = big ? launch_direct_kernel<false, false, 256, 128, 8, 2>(F, direct_plain_grid(F.total_tiles), stream)
+  if (listed)
+    st = big ? launch_direct_kernel<false, false, 256, 128, 8, 3>(F, direct_plain_grid(F.total_tiles), stream)
+             : launch_direct_kernel<false, false, 128, 128, 4, 3>(F, direct_plain_grid(F.total_tiles), stream);
+  else
+    st = big ? launch_direct_kernel<false, false, 256, 128, 8, 2>(F, direct_plain_grid(F.total_tiles), stream)
            : launch_direct_kernel<false, false, 128, 128, 4, 2>(F, direct_plain_grid(F.total_tiles), stream);
   if (st) return st;
   if ((long)a.Cout * taps * Ck >= (1L << 31)) return fail(ARD_ESHAPE, "weight gradient beyond 2^31 kept synapses");
   const int sum_blocks = (int)(((long)a.Cout * taps * Ck + 255) / 256);
   const int zero_blocks = Ck < a.C && !a.kept_only ? (int)(((long)a.Cout * a.C + 255) / 256) : 0;
   ARD_LAUNCH(wgrad_grid_reduce_kernel<uint16_t>, dim3((unsigned)(sum_blocks + zero_blocks)), dim3(256), 0, stream, (const float*)w.gpart,
-             (const int*)d_keep, Ck, splits, a.Cout, a.C, taps, Cpa, sum_blocks, (uint16_t*)out);
+             (const int*)d_keep, Ck, splits, a.Cout, a.C, taps, group, sum_blocks, group, Nn, (uint16_t*)out);
   ARD_LAUNCH_CHECK("wgrad_grid_reduce_kernel");
+  return ARD_OK;
+}
+
+// Data gradient under the block pattern in one launch (conv_blocks.hpp): tiles of 128 positions are whole bands or
+// parts of a band, and at least half full (else the passes per column block, whose tiles run over all positions).
+static bool block_data_tiles(const ConvArgs& a, const ConvWs& w, BlockDataParams& P) {
+  const int taps = a.kh * a.kw, hw = a.H * a.W;
+  if (!w.grid_a || dev_knobs().no_fast || a.kh - 1 != 2 * a.pad || a.kw - 1 != 2 * a.pad || a.kh > 15 || a.kw > 15) return false;
+  if (a.by % (64 * taps) || (long)a.C * taps % a.by || a.bx % a.W) return false;
+  P.RB = ceil_div(hw, a.bx), P.CB = a.C * taps / a.by;
+  P.CG = pad64(a.Cout) / 64;
+  if (P.RB > 64 || taps * P.CG > 128) return false;
+  P.x = a.bx, P.rows_per_band = a.bx / a.W;
+  P.bands_per_tile = imax(1, 128 / a.bx), P.parts = ceil_div(a.bx, 128);
+  P.tiles_img = P.parts == 1 ? ceil_div(P.RB, P.bands_per_tile) : P.RB * P.parts;
+  P.cpb = a.by / taps, P.mt = P.cpb / 64;
+  return hw * 2 >= P.tiles_img * 128 && (long)a.N * P.tiles_img * P.CB * P.mt < (1L << 24);
+}
+static int32_t conv_block_data(const ConvArgs& a, BlockDataParams P, const void* Wt, const void* dYin, void* out, const ConvWs& w,
+                               hipStream_t stream) {
+  const int taps = a.kh * a.kw, ph = a.kh - 1 - a.pad, pw = a.kw - 1 - a.pad, Cp = pad64(a.Cout), Hg = a.Ho + 2 * ph, Wg = a.Wo + 2 * pw;
+  int hgm, wgm;
+  (void)conv_grid_pixels(a, &hgm, &wgm);
+  const long margin = (long)a.kh * wgm + a.kw + 128;
+  // (the kept positions of every group, which the weight gradient of the same workspace contracts over, ride along)
+  if (int32_t st = to_grid(dYin, nullptr, a.Cout, a.Cout, a.Ho, a.Wo, a.N, Hg, Wg, ph, pw, Cp, margin, w.grid_y, stream, BandMask{},
+                           pack_job(Wt, nullptr, a.C, taps, a.C, a.Cout, Cp, 1, w.gwp), ZeroPlanesJob{}, ZeroPixelsJob{}, BlockPlanJob{}, a.lists))
+    return st;
+  P.W = w.gwp, P.grid = w.grid_y, P.dA = (uint16_t*)out, P.blk = a.blk;
+  P.ldw = taps * Cp, P.Cp = Cp, P.kh = a.kh, P.kw = a.kw, P.ph = ph;
+  P.H = a.H, P.W_ = a.W, P.C = a.C, P.HgWg = Hg * Wg, P.Wg = Wg;
+  P.total = a.N * P.tiles_img * P.CB * P.mt;
+  const int hw = a.H * a.W;
+  P.width = hw % 8 == 0 && a.bx % 8 == 0 && al16c(out) ? 16 : hw % 2 == 0 && a.bx % 2 == 0 && ((uintptr_t)out & 3) == 0 ? 4 : 2;
+  P.by_groups = fast_div((uint32_t)(P.CB * P.mt)), P.by_tiles = fast_div((uint32_t)P.tiles_img), P.by_w = fast_div((uint32_t)a.W);
+  // (a lane's last read: the last pixel of the last image through the last tap, inside the grid; rows of W: C of them)
+  static thread_local bool raised = false;
+  if (!raised) {
+    ARD_HIP_CHECK(raise_lds_limit((const void*)conv_block_data_kernel, kBdLds));
+    raised = !dry_run();
+  }
+  ARD_LAUNCH(conv_block_data_kernel, dim3((unsigned)(ceil_div(P.total, 8) * 8)), dim3(256), kBdLds, stream, P);
+  ARD_LAUNCH_CHECK("conv_block_data_kernel");
   return ARD_OK;
 }
 
@@ -1532,7 +1675,7 @@ static int32_t conv_run_planes(const ConvArgs& a, const void* A, const void* Wt,
   const int sum_blocks = (int)(((long)a.Cout * taps * Ck + 255) / 256);
   const int zero_blocks = Ck < a.C && !a.kept_only ? (int)(((long)a.Cout * a.C + 255) / 256) : 0;
   ARD_LAUNCH(wgrad_grid_reduce_kernel<float>, dim3((unsigned)(sum_blocks + zero_blocks)), dim3(256), 0, stream, (const float*)w.plane_part,
-             (const int*)d_keep, Ck, splits, a.Cout, a.C, taps, Cp, sum_blocks, (float*)out);
+             (const int*)d_keep, Ck, splits, a.Cout, a.C, taps, Cp, sum_blocks, Cp, taps * Cp, (float*)out);
   ARD_LAUNCH_CHECK("wgrad_grid_reduce_kernel");
   return ARD_OK;
 }
@@ -1606,22 +1749,26 @@ static int32_t conv_run(const ConvArgs& a, double rate, const void* A, const voi
     if (!dYin || !d_mask || !out) return fail(ARD_EINVAL, "the row-pattern gradients need dYin, d_mask and out");
     // (the reuse flags mean what they mean for the ordinary gradients: the grid of A that FWD_ROWS left, the
     // masked grid of dY that BWD_DATA_ROWS left -- same mask, same layout)
-    ARD_LAUNCH(iota_kernel, dim3(ceil_div(a.C, 256)), dim3(256), 0, stream, w.all_chan, a.C);
-    ARD_LAUNCH_CHECK("iota_kernel");
     ConvArgs full = a;
     full.mode = a.mode == ARD_CONV_BWD_DATA_ROWS ? ARD_CONV_BWD_DATA : ARD_CONV_BWD_WEIGHT;
     full.n_keep = a.C;
     const void* dy_use = w.dy_rows;
+    int32_t* every = nullptr;  // (no list: every channel)
     if ((w.grid_a || w.plane_a) && !dev_knobs().no_fast) {
       // the pass copies dY into its grid anyway: that copy drops the positions (bands of one row)
       full.dy_mask = BandMask{(const uint8_t*)d_mask, a.Ho * a.Wo, 1, 0, 1};
       dy_use = dYin;
+      // the weight gradient contracts over the kept positions only
+      if (w.grid_a) full.lists = pos_list_job(a, (const uint8_t*)d_mask, 1, 1, w);
     } else {
+      ARD_LAUNCH(iota_kernel, dim3(ceil_div(a.C, 256)), dim3(256), 0, stream, w.all_chan, a.C);
+      ARD_LAUNCH_CHECK("iota_kernel");
+      every = w.all_chan;
       ARD_LAUNCH(mask_pixels_kernel<T>, dim3(a.Cout, a.N), dim3(256), 0, stream, (const T*)dYin, (const uint8_t*)d_mask, a.Cout,
                  a.Ho * a.Wo, (T*)w.dy_rows);
       ARD_LAUNCH_CHECK("mask_pixels_kernel");
     }
-    return conv_run<T>(full, 0.0, A, Wt, dy_use, out, nullptr, w.all_chan, nullptr, nullptr, w, stream);
+    return conv_run<T>(full, 0.0, A, Wt, dy_use, out, nullptr, every, nullptr, nullptr, w, stream);
   }
   if (a.n_keep < 0 || a.n_keep > a.C) return fail(ARD_EINVAL, "n_keep=%d outside 0..%d", a.n_keep, a.C);
   if (a.n_keep > 0 && a.n_keep < a.C && !d_keep) return fail(ARD_EINVAL, "d_keep is required");
@@ -1807,7 +1954,9 @@ extern "C" int32_t ard_conv_bwd_blocks(int32_t mode, int32_t dtype, int32_t N, i
                                        const void* A, const void* Wt, const void* dYin, const uint8_t* d_block_keep, void* out,
                                        void* ws, size_t ws_bytes, void* stream) {
   BatchSuspend not_recorded;
-  if (mode != ARD_CONV_BWD_DATA && mode != ARD_CONV_BWD_WEIGHT)
+  const int32_t reuse = mode & ARD_CONV_REUSE_DY;
+  mode &= ~ARD_CONV_REUSE_DY;
+  if ((mode != ARD_CONV_BWD_DATA && mode != ARD_CONV_BWD_WEIGHT) || (reuse && mode != ARD_CONV_BWD_WEIGHT))
     return fail(ARD_EINVAL, "mode must be ARD_CONV_BWD_DATA or ARD_CONV_BWD_WEIGHT (got %d)", mode);
   ConvArgs a{mode, dtype, N, C, H, Wd, Cout, kh, kw, stride, pad, C, 0, 0, 0, 0, d_block_keep, x, y};
   int32_t st = conv_check(a);
@@ -1824,6 +1973,23 @@ extern "C" int32_t ard_conv_bwd_blocks(int32_t mode, int32_t dtype, int32_t N, i
   ConvWs w = conv_ws_layout((char*)ws, a);
   if (!ws || ws_bytes < w.total) return fail(ARD_EWORKSPACE, "workspace too small: need %zu bytes, got %zu", w.total, ws_bytes);
   hipStream_t s = (hipStream_t)stream;
+  const int taps = kh * kw;
+  const int CB = ceil_div(C * taps, a.by), RB = ceil_div(a.Ho * a.Wo, a.bx);
+  // Groups of whole channels on the channels-last grids: each contracts over its kept positions only, all of them in
+  // one launch; the data gradient likewise where its tiles fit the bands.
+  const bool by_groups = w.grid_a && !dev_knobs().no_fast && a.by % (8 * taps) == 0 && CB * (a.by / taps) <= pad64(C) && CB <= w.pos_blocks;
+  BlockDataParams bd{};
+  const bool one_launch = by_groups && block_data_tiles(a, w, bd);
+  if (by_groups) a.lists = pos_list_job(a, d_block_keep, a.bx, CB, w);
+  if (one_launch && mode == ARD_CONV_BWD_DATA) return conv_block_data(a, bd, Wt, dYin, out, w, s);
+  if (by_groups && mode == ARD_CONV_BWD_WEIGHT) {
+    ConvArgs g = a;
+    g.blk = nullptr;
+    g.cpb = a.by / taps;
+    g.reuse = one_launch ? reuse : 0;  // (else the data gradient left dY masked for its last column block)
+    return conv_run<uint16_t>(g, 0.0, A, Wt, dYin, out, nullptr, nullptr, nullptr, nullptr, w, s);
+  }
+  a.lists = PosListJob{};
   // every channel is kept: the passes take the identity list
   ARD_LAUNCH(iota_kernel, dim3(ceil_div(C, 256)), dim3(256), 0, s, w.all_chan, C);
   ARD_LAUNCH_CHECK("iota_kernel");
@@ -1832,8 +1998,6 @@ extern "C" int32_t ard_conv_bwd_blocks(int32_t mode, int32_t dtype, int32_t N, i
   // of the output position alone.  Per column block: dY copied with the positions of its dropped bands zeroed,
   // then the ordinary gradient pass (whichever engine takes the shape) with that channel range as the kept
   // list, writing its channels' part of the output only.  Work is not skipped, but the passes are the fast ones.
-  const int taps = kh * kw;
-  const int CB = ceil_div(C * taps, a.by), RB = ceil_div(a.Ho * a.Wo, a.bx);
   if (a.by % taps == 0 && CB <= 16 && !(mode == ARD_CONV_BWD_DATA && stride != 1)) {
     const int cpb = a.by / taps;
     for (int cb = 0; cb < CB; ++cb) {

@@ -76,6 +76,18 @@ struct ConvMap {
   int pix_pairs;  // list entries 2i, 2i+1 are pixels 2m, 2m+1 of one image (or both padding): stored as one word
 };
 
+// Weight gradient over listed output positions (MODE 3; row- and block-based sensitivity-aware patterns, Section 5.2):
+// column block cb (a group of `chans` input channels over all taps, `cols` columns of the product, `tiles` column
+// tiles) contracts over its own cnt[cb] output positions list[cb * stride ...], numbered n * HoWo + p.
+struct ListMap {
+  int ncls;          // 0 (shares its place with ClassTab::ncls)
+  int stride, max;   // entries reserved per block; a count beyond `max` is cut
+  int tiles, cols, chans, cols_per_tap;
+  int pad;           // grid pixel whose gradient is zero: fills up the last step
+  const int* list;
+  const int* cnt;
+};
+
 // (What every launch reads comes first and is fetched in one go, see touch_args; the class tables come last.)
 struct FastParams {
   const uint16_t* A;
@@ -103,9 +115,12 @@ struct FastParams {
   const int* kb_list;
   const int* kb_cnt;
   int kb_stride;
-  ConvMap cv;  // MODE 1 / 2 of the kernel only
+  ConvMap cv;  // MODE 1 / 2 / 3 of the kernel only
   long a_elems, b_elems;  // elements the caller owns behind A / B: what the loaders may touch (host-side proof)
-  ClassTab tab;
+  union {
+    ClassTab tab;
+    ListMap li;  // MODE 3
+  };
 };
 
 // Brings the first LINES 64-byte lines of a kernel's arguments into the scalar cache with one round trip.  Left
@@ -303,6 +318,44 @@ template <int ROWS, int NW> struct DirectLoader<false, ROWS, NW> {
     }
   }
 };
+
+// MC operand whose contraction rows are listed grid pixels (MODE 3): the list of the steps in flight lies in LDS as
+// pixel numbers, a lane looks up the rows of its chunks one step before it loads them.
+template <int ROWS, int NW> struct ListLoader {
+  using L = DirectLoader<false, ROWS, NW>;
+  static constexpr int NI = L::NI;
+  const char* base;
+  uint32_t row_bytes;
+  uint32_t coff[NI];  // this lane's chunk within a pixel (a tap's pixel offset included), in bytes
+  int kloc[NI];       // contraction row within the step
+  __host__ __device__ __forceinline__ void init(const uint16_t* p, int ld, int ncols, int col0, int lane, int wave) {
+    base = reinterpret_cast<const char*>(p);
+    row_bytes = (uint32_t)ld * 2u;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      kloc[j] = L::KPI * (wave * NI + j) + lane / L::CPR;
+      coff[j] = (uint32_t)imin(col0 + ((lane % L::CPR) ^ mc_swz<ROWS>(kloc[j])) * 8, ncols - 8) * 2u;
+    }
+  }
+  // columns = (tap, channel of the block)
+  __host__ __device__ __forceinline__ void init_taps(const uint16_t* p, const ConvMap& cv, const ListMap& li, int cb, int col0, int lane, int wave) {
+    init(p, cv.Cp, li.cols, col0, lane, wave);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int col = (int)(coff[j] >> 1), t = col / li.cols_per_tap;
+      coff[j] = (uint32_t)(((t / cv.kw) * cv.Wg + t % cv.kw) * cv.Cp + cb * li.chans + col - t * li.cols_per_tap) * 2u;
+    }
+  }
+  __device__ __forceinline__ void look(const int* step_list, uint32_t (&off)[NI]) const {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) off[j] = __umul24((uint32_t)step_list[kloc[j]], row_bytes) + coff[j];
+  }
+  __device__ __forceinline__ void issue_one(uint4* op_tile, uint32_t off, int wave, int j) const {
+    __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(base + off), ARD_LDS_PTR(op_tile + (wave * NI + j) * 64), 16, 0, 0);
+  }
+};
+// list entries a workgroup of the 256-row / 128-row tile holds in LDS at a time
+constexpr int direct_list_cap(int bm) { return bm == 256 ? 8192 : 3072; }
 
 // Byte offset, inside an MC operand tile of `ROWS` rows, of this lane's source position for the
 // transposing reads of the 32-wide MFMA tile that starts at tile row `tile_col0`.  The reads
@@ -555,6 +608,9 @@ __host__ __device__ __forceinline__ void direct_slab(const FastParams& P, const 
 // MODE 0: plain product.  MODE 1: convolution, B rows are output pixels gathered from the
 // bordered channels-last grid (contraction = (tap, channel)), output NCHW.  MODE 2: weight
 // gradient of the convolution, contraction over the grid's pixels, B columns = (tap, channel).
+// MODE 3: the same over listed pixels (ListMap): what a pattern drops is neither loaded nor multiplied.  N=128,
+// C=Cout=256, 28x28, 3x3, 30 % of the positions kept: 123 -> 42 us (row pattern), 4 x 38 -> 45 us (block pattern, four
+// groups of channels).
 // (body of the kernel as a device function: the grouped kernel of gemm.hip runs it on a range of
 // its workgroups; block_id is the workgroup's index within the product, lds its dynamic LDS)
 template <bool A_KC, bool B_KC, int F_BM, int BN, int NW, int MODE = 0>
@@ -585,6 +641,13 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[im][in][v] = 0.0f;
 
+  int li_cb = 0, li_cnt = 0, jn0 = n0, jlim = P.N;  // jn0, jlim: this tile's columns within its block
+  if constexpr (MODE == 3) {
+    const int tn = n0 / BN;
+    li_cb = tn / P.li.tiles;
+    jn0 = (tn - li_cb * P.li.tiles) * BN, jlim = P.li.cols;
+    li_cnt = imin(imax(P.li.cnt[li_cb], 0), P.li.max);
+  }
   // per-tile contraction list (MODE 1): lane l keeps the tile's l-th and (64+l)-th block, a step reads its
   // block out of the lane that holds it, so the loop touches no memory for the list
   int kbl0 = 0, kbl1 = 0;
@@ -621,12 +684,14 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     direct_slab<MODE>(P, kax, s, ks, ksb);
   };
 
-  if (Kn > 0) {
-    DirectLoader<A_KC, F_BM, NW> la;
-    DirectLoader<B_KC, BN, NW> lb;
+  if (MODE == 3 ? li_cnt > 0 : Kn > 0) {
+    std::conditional_t<MODE == 3, ListLoader<F_BM, NW>, DirectLoader<A_KC, F_BM, NW>> la;
+    std::conditional_t<MODE == 3, ListLoader<BN, NW>, DirectLoader<B_KC, BN, NW>> lb;
     const int kbump = MODE == 0 ? direct_kbump(kax) : 0;
-    la.init(P.A, P.lda, am, m0, lane, wave, kbump);
-    if constexpr (MODE == 1) lb.init_pixels(P.B, P.cv, n0, lane, wave);
+    if constexpr (MODE == 3) la.init(P.A, P.lda, am.n, m0, lane, wave);
+    else la.init(P.A, P.lda, am, m0, lane, wave, kbump);
+    if constexpr (MODE == 3) lb.init_taps(P.B, P.cv, P.li, li_cb, jn0, lane, wave);
+    else if constexpr (MODE == 1) lb.init_pixels(P.B, P.cv, n0, lane, wave);
     else if constexpr (MODE == 2) lb.init_tap_columns(P.B, P.cv, P.N, n0, lane, wave);
     else lb.init(P.B, P.ldb, bn, n0, lane, wave, kbump);
     const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)lds);
@@ -655,10 +720,20 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       }
     }
     // contraction steps of this workgroup (a share of them when the contraction is split)
-    const int S_all = (Kn + 63) >> 6;
+    const int S_all = ((MODE == 3 ? li_cnt : Kn) + 63) >> 6;
     const int s_lo = (int)((long)split * S_all / P.splits), s_hi = (int)((long)(split + 1) * S_all / P.splits);
-    const int S = s_hi - s_lo;
+    int S = s_hi - s_lo;
+    int* const list = reinterpret_cast<int*>(lds + NST * (OPA + OPB));  // MODE 3: grid pixels of the steps of a chunk
+    uint32_t ao[decltype(la)::NI], bo[decltype(lb)::NI];
     auto load_stage = [&](int it, int buf) {
+      if constexpr (MODE == 3) {
+        la.look(list + it * 64, ao), lb.look(list + it * 64, bo);
+#pragma unroll
+        for (int j = 0; j < decltype(la)::NI; ++j) la.issue_one(lds + buf * OPA, ao[j], wave, j);
+#pragma unroll
+        for (int j = 0; j < decltype(lb)::NI; ++j) lb.issue_one(lds + NST * OPA + buf * OPB, bo[j], wave, j);
+        return;
+      } else {
       const int krem = Kn - (s_lo + it) * 64;
       int ks, ksb;
       slab(s_lo + it, ks, ksb);
@@ -669,6 +744,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       } else {
         la.issue(lds + buf * OPA, ks, wave);
         lb.issue(lds + NST * OPA + buf * OPB, ksb, wave);
+      }
       }
     };
     constexpr int QA = 16 * F_BM * 2, QB = 16 * BN * 2;  // bytes per 16-wide slice of an MC tile
@@ -759,6 +835,8 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       mma(0);
       wait(1);
       issue(B{}, I2{}, 0);
+      // (looked up here, the rows of the next loads are known long before the loads are issued)
+      if constexpr (MODE == 3) la.look(list + (it + NST) * 64, ao), lb.look(list + (it + NST) * 64, bo);
       mma(1);
       wait(0);
       issue(B{}, I3{}, 1);
@@ -768,7 +846,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       wg_barrier();
       issue(NB{}, I0{}, 0);
       int ks, ksb;
-      slab(s_lo + it + NST, ks, ksb);
+      if constexpr (MODE != 3) slab(s_lo + it + NST, ks, ksb);
       // the loads of stage it+NST spread between the last slice's MFMAs (a burst of LPS load instructions
       // keeps this wavefront from issuing MFMAs for as long as it takes to issue them)
       {
@@ -784,15 +862,20 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
 #pragma unroll
             for (int r = 0; r < (LPS + MM - 1) / MM; ++r)
               if (li < LPS && li * MM < mi * LPS) {
-                if (li < NA) la.issue_one(lds + BUF * OPA, ks, wave, li);
-                else lb.issue_one(lds + NST * OPA + BUF * OPB, ksb, wave, li - NA);
+                if constexpr (MODE == 3) {
+                  if (li < NA) la.issue_one(lds + BUF * OPA, ao[li < NA ? li : 0], wave, li);
+                  else lb.issue_one(lds + NST * OPA + BUF * OPB, bo[li < NA ? 0 : li - NA], wave, li - NA);
+                } else {
+                  if (li < NA) la.issue_one(lds + BUF * OPA, ks, wave, li);
+                  else lb.issue_one(lds + NST * OPA + BUF * OPB, ksb, wave, li - NA);
+                }
                 ++li;
               }
             __builtin_amdgcn_sched_barrier(0);
           }
       }
     };
-    if (S > 0) {
+    auto contract = [&] {
 #pragma unroll
       for (int st = 0; st < NST; ++st)
         if (st < S) load_stage(st, st);
@@ -801,7 +884,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       wg_barrier();
       issue(I0{}, I0{}, 0);
       int it0 = 0;
-      if (kax.kind == AX_AFFINE || (kax.kind == AX_BAFF && (kax.bs % 64 == 0 || kax.bs == 32) && kax.nphys % kax.bs == 0)) {
+      if (MODE == 3 || kax.kind == AX_AFFINE || (kax.kind == AX_BAFF && (kax.bs % 64 == 0 || kax.bs == 32) && kax.nphys % kax.bs == 0)) {
         // steps whose stage it+NST is not the last one (only the last can be partial)
         for (; it0 + 2 * NST < S; it0 += NST) static_for<NST>([&](auto b) { steady_step(b, it0 + decltype(b)::value); });
       }
@@ -809,6 +892,26 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
         static_for<NST>([&](auto b) {
           if (it + decltype(b)::value < S) step(b, it + decltype(b)::value);
         });
+    };
+    if constexpr (MODE == 3) {
+      // as much of this share's list at a time as LDS holds, as pixels of the grid
+      constexpr int CAP = direct_list_cap(F_BM);
+      const int* src = P.li.list + (long)li_cb * P.li.stride;
+      const int top = (int)(P.cv.pix_total - 1);
+      for (int e0 = s_lo * 64; e0 < s_hi * 64; e0 += CAP) {
+        const int e1 = imin(e0 + CAP, s_hi * 64);
+        __syncthreads();
+        for (int i = e0 + tid; i < e1; i += 64 * NW) {
+          const int p = imin(imax(src[imin(i, li_cnt - 1)], 0), top);
+          const int n = p / P.cv.HoWo, rem = p - n * P.cv.HoWo, ho = rem / P.cv.Wo;
+          list[i - e0] = i < li_cnt ? n * P.cv.HgWg + ho * P.cv.Wg + rem - ho * P.cv.Wo : P.li.pad;
+        }
+        __syncthreads();
+        S = (e1 - e0) >> 6;
+        contract();
+      }
+    } else if (S > 0) {
+      contract();
     }
   }
 
@@ -827,8 +930,8 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     float* part = P.part + (long)split * P.M * P.N;
 #pragma unroll
     for (int in = 0; in < TN; ++in) {
-      const int j = n0 + wn * WTN + in * 32 + (lane & 31);
-      if (j >= P.N) continue;
+      const int jb = jn0 + wn * WTN + in * 32 + (lane & 31), j = jb + li_cb * jlim;
+      if (jb >= jlim) continue;
 #pragma unroll
       for (int im = 0; im < TM; ++im) {
         const int i0 = m0 + wm * WTM + im * 32 + 4 * (lane >> 5);
@@ -1404,6 +1507,22 @@ static int32_t direct_envelope(const FastParams& F) {
   if (F.a_elems <= 0 || F.b_elems <= 0) return fail(ARD_EINVAL, "bounds proof: operand extents not stated");
   if (F.a_elems >= (1L << 31) || F.b_elems >= (1L << 31)) return fail(ARD_ESHAPE, "bounds proof: operand beyond 32-bit offsets");
   if (F.lda < 8 || F.ldb < 8) return fail(ARD_ESHAPE, "bounds proof: leading dimension below one 16-byte run");
+  if constexpr (MODE == 3) {
+    // every list entry is clamped to a pixel of the grid, the filler included; columns are clamped to the axis
+    const ConvMap& cv = F.cv;
+    const ListMap& l = F.li;
+    if (!l.list || !l.cnt || l.tiles < 1 || l.cols < 8 || l.cols_per_tap < 8 || (l.cols_per_tap % 8) || (l.chans % 8) || l.max > l.stride || F.am.n < 8)
+      return fail(ARD_EINVAL, "bounds proof: bad position list");
+    if (cv.pix_total < 1 || cv.Cp < 64 || (cv.Cp % 64) || cv.kw < 1 || F.lda % 64) return fail(ARD_ESHAPE, "bounds proof: bad grid");
+    const int row = cv.pix_total - 1, n = row / cv.HoWo, rem = row - n * cv.HoWo;
+    const long at = (long)n * cv.HgWg + (long)(rem / cv.Wo) * cv.Wg + rem % cv.Wo, last = at > l.pad ? at : l.pad;
+    const int tl = (l.cols - 8) / l.cols_per_tap, cbs = F.tiles_n / l.tiles;
+    const long shift = (long)(tl / cv.kw) * cv.Wg + tl % cv.kw;
+    if (l.pad < 0 || last >= (1L << 24) || (last + 1) * F.lda > F.a_elems || F.am.n > F.lda || (last + shift + 1) * cv.Cp > F.b_elems ||
+        (long)(cbs - 1) * l.chans + l.cols_per_tap > cv.Cp)
+      return fail(ARD_ESHAPE, "bounds proof: listed pixels leave the grid");
+    return ARD_OK;
+  }
   const ClassTab& t = F.tab;
   const int ncls = t.ncls ? t.ncls : 1;
   for (int c = 0; c < ncls; ++c) {
@@ -1559,7 +1678,7 @@ bool batch_push_zero_rows(const ZeroRowsArgs& a, int gx);
 template <bool A_KC, bool B_KC, int BM, int BN, int NW, int MODE>
 static int32_t launch_direct_alone(const FastParams& F, int grid_x, hipStream_t stream) {
   auto kernel = gemm_direct_kernel<A_KC, B_KC, BM, BN, NW, MODE>;
-  const size_t lds_bytes = (size_t)direct_stages(BM, BN) * (BM + BN) * LDS_ROW_U4 * sizeof(uint4);
+  const size_t lds_bytes = (size_t)direct_stages(BM, BN) * (BM + BN) * LDS_ROW_U4 * sizeof(uint4) + (MODE == 3 ? direct_list_cap(BM) * 4 : 0);
   static thread_local bool raised = false;
   if (!raised && lds_bytes >= 65536) {
     ARD_HIP_CHECK(ard::raise_lds_limit((const void*)kernel, (int)lds_bytes));
@@ -1578,10 +1697,12 @@ static int32_t launch_direct_kernel(const FastParams& F_in, int grid_x, hipStrea
   if (F.tab.ncls == 0) grid_x = direct_plain_grid(F.total_tiles * (F.splits < 1 ? 1 : F.splits));
   // no lane may leave its operand: cheap envelope always, the exhaustive walk on request
   if (int32_t st = direct_envelope<A_KC, B_KC, BM, BN, MODE>(F)) return st;
-  if (dry_run() || dev_knobs().prove_bounds) {
-    DirectBounds b;
-    if (int32_t st = direct_prove<A_KC, B_KC, BM, BN, NW, MODE>(F, grid_x, b)) return st;
-    note_direct_bounds(b, F.a_elems * 2, F.b_elems * 2);
+  if constexpr (MODE != 3) {  // (MODE 3: the envelope is exact, whatever the list says)
+    if (dry_run() || dev_knobs().prove_bounds) {
+      DirectBounds b;
+      if (int32_t st = direct_prove<A_KC, B_KC, BM, BN, NW, MODE>(F, grid_x, b)) return st;
+      note_direct_bounds(b, F.a_elems * 2, F.b_elems * 2);
+    }
   }
   constexpr int gk = direct_group_kind<A_KC, B_KC, BM, BN, NW, MODE>();
   if (gk >= 0 && batch_open() && batch_push_direct(gk, F, grid_x, lds_bytes)) return ARD_OK;

@@ -742,7 +742,8 @@ PyObject* conv_bwd_blocks(const Args& a) {  // dY, A, Wt, block_keep, x, y, stri
   Workspace ws(a, 8, A.device(), [&] { return s.ws_bytes(dt); });
   const int x = as_int(a.v[4]), y = as_int(a.v[5]);
   void* st = stream_of(a.v[9]);
-  const int modes[2] = {ARD_CONV_BWD_DATA, ARD_CONV_BWD_WEIGHT};
+  // (the weight gradient takes what the data gradient just left in the workspace, where it left it)
+  const int modes[2] = {ARD_CONV_BWD_DATA, ARD_CONV_BWD_WEIGHT | ARD_CONV_REUSE_DY};
   for (int i = 0; i < 2; ++i)
     enqueue([&] {
       return lib().ard_conv_bwd_blocks(modes[i], dt, s.N, s.C, s.H, s.W, s.Co, s.kh, s.kw, s.stride, s.pad, x, y, ptr(A), ptr(Wt), ptr(dY),

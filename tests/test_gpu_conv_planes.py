@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from oracle import conv as OC
+from oracle import sensitivity as S
 from paper_2203_05705_amd import binding as ard
 from util import assert_parity, from_vals, stored
 
@@ -32,3 +33,39 @@ def test_planes(N, C, Cout, H, W, k, pad, rate):
                   np.broadcast_to((m == 0)[None, :, None, None], A.shape), "dA")
     assert_parity(ard.conv_bwd_weight(dYd, Ad, sel["keep"], cnt, (k, k), 1, pad, ws=ws), OC.conv_bwd_weight(dY, A, m, (k, k), 1, pad), "f32",
                   np.broadcast_to((m == 0)[None, :, None, None], Wt.shape), "dWt")
+
+
+# bf16, gradients under the two patterns: tiles of several bands, one band and parts of a band; planes stored 16, 4 and
+# 2 bytes at a time; fewer and more than 64 contraction steps; every band dropped, and none
+@pytest.mark.parametrize("N,C,Cout,H,W,k,rows,group,p", [
+    (3, 128, 72, 16, 16, 3, 4, 64, 0.3), (2, 192, 130, 13, 13, 3, 13, 64, 0.5), (2, 128, 40, 14, 14, 5, 7, 128, 0.4), (1, 64, 256, 28, 28, 3, 2, 64, 0.3),
+    (2, 256, 300, 12, 20, 3, 3, 128, 0.6), (2, 64, 600, 16, 16, 3, 4, 64, 0.5), (2, 64, 8, 16, 16, 1, 8, 64, 0.5), (2, 128, 24, 16, 16, 3, 8, 64, 0.0),
+    (2, 128, 24, 16, 16, 3, 8, 64, 1.0), (40, 64, 16, 24, 24, 3, 3, 64, 0.3)])
+def test_block_gradients_in_one_launch(N, C, Cout, H, W, k, rows, group, p):
+    print("block gradients", N, C, Cout, H, W, k, rows, group, p, flush=True)
+    rng = np.random.default_rng(C + H)
+    A, Wt, dY = (stored(rng.standard_normal(s) * 0.5, "bf16") for s in ((N, C, H, W), (Cout, C, k, k), (N, Cout, H, W)))
+    Ad, Wd, dYd = (from_vals(v, "bf16") for v in (A, Wt, dY))
+    x, y = rows * W, group * k * k
+    _, RB, CB = ard.sens_regions(A.shape, (k, k), 1, k // 2, x, y)
+    keep = (rng.uniform(size=(N, RB, CB)) < p).astype(np.uint8)
+    dA, dW = ard.conv_bwd_blocks(dYd, Ad, Wd, torch.from_numpy(keep.reshape(-1)).cuda(), x, y, 1, k // 2)
+    rA, rW = S.conv_bwd_blocks(dY, A, Wt, keep, x, y, 1, k // 2)
+    assert_parity(dA, rA, "bf16", None, "dA")
+    assert_parity(dW, rW, "bf16", None, "dWt")
+
+
+# the weight gradient over listed positions: none, one, a few around whole steps, more than one workgroup's list at a time
+@pytest.mark.parametrize("N,C,Cout,H,W,kept", [(2, 16, 8, 9, 9, 0), (2, 16, 8, 9, 9, 1), (3, 72, 130, 8, 8, 64), (3, 72, 40, 8, 8, 65), (3, 72, 300, 8, 8, 192),
+                                               (64, 8, 16, 56, 56, 199000)])
+def test_row_gradients_over_listed_positions(N, C, Cout, H, W, kept):
+    print("row gradients", N, C, Cout, H, W, kept, flush=True)
+    rng = np.random.default_rng(kept)
+    A, Wt, dY = (stored(rng.standard_normal(s) * 0.5, "bf16") for s in ((N, C, H, W), (Cout, C, 3, 3), (N, Cout, H, W)))
+    Ad, Wd, dYd = (from_vals(v, "bf16") for v in (A, Wt, dY))
+    mask = np.zeros(N * H * W, np.uint8)
+    mask[rng.choice(N * H * W, kept, replace=False)] = 1
+    dA, dW = ard.conv_bwd_rows(dYd, Ad, Wd, dict(mask=torch.from_numpy(mask).cuda()), 1, 1)
+    rA, rW = S.conv_bwd_rows(dY, A, Wt, mask.reshape(N, H * W), 1, 1)
+    assert_parity(dA, rA, "bf16", None, "dA")
+    assert_parity(dW, rW, "bf16", None, "dWt")
