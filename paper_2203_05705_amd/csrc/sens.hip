@@ -146,16 +146,26 @@ __global__ __launch_bounds__(256) void sens_predict_lut_kernel(const T* A, SensG
 // first: the draws of a region fall on a few input rows of its channels (config 5, a band of 8 positions:
 // 4 rows x 28 x 256 channels for 5529 draws), and a gather from memory costs a whole cache-line transaction per
 // draw (69 M of them made the pass take 460 us) where the copy is a few coalesced 16-byte loads per thread.
-// Same draws, same elements, same counts.  Needs planes that are whole numbers of 16-byte pieces (then every
-// channel's run starts at the same offset within a piece); the host checks it.
+// Same draws, same elements, same counts.
+//
+// What a draw needs of an element is one bit (above the threshold or not).  The bits lie in rows of W + 2 pad with
+// the zero border of the input matrix around them, so that a draw's bit number is a sum of one table entry for its
+// row and one for its column and nothing is tested.  The pass is bound by the vector ALUs, mostly by the mixer's
+// multiplications (a 32-bit one takes four times as long as an addition), and saves what it can of them:
+//  * the bits of (prefix ^ index) + golden above the lowest 16 take two values over a region (j < 65536; the sum
+//    carries or it does not), so the mixer's first product is one of two constants plus a 16-bit number times the
+//    multiplier; only the upper half of the second product is needed;
+//  * u * h = (row, f) and f * w = (column, .) give row and column of the drawn element without dividing.
+// N=128, 256 channels, 28x28, 3x3, 30 % sampled (69 M draws): bands of 8 positions 138 -> 97 us, 112 x 576
+// regions 120 -> 81 us.
 struct SensStage {
-  int nrow_max, chp;  // input rows a workgroup's bands can touch; elements reserved per channel (a multiple of the piece)
-  FastDiv div_taps, div_kw, div_wo;
-  int G, RBG;         // consecutive row bands (of one image and column block) per workgroup; groups per image
+  int nrow_max, ch_bits;  // input rows (border included) a workgroup's bands can touch; bits reserved per channel
+  FastDiv div_taps, div_kw, div_wo, div_w;
+  int G, RBG;             // consecutive row bands (of one image and column block) per workgroup; groups per image
 };
 template <typename T>
 __global__ __launch_bounds__(256) void sens_predict_staged_kernel(const T* A, SensGeom g, SensStage sg, int k_permille,
-                                                                  int t_permille, float thr, uint64_t prefix, FastDiv div_w,
+                                                                  int t_permille, float thr, uint64_t prefix,
                                                                   int* count, int* samples, uint8_t* sens) {
   constexpr int CE = ElemTraits<T>::CE;  // elements per 16-byte piece
   extern __shared__ uint4 sens_stage_lds[];
@@ -165,77 +175,109 @@ __global__ __launch_bounds__(256) void sens_predict_staged_kernel(const T* A, Se
   const int rb_first = rbg * sg.G, nb = min(sg.G, g.RB - rb_first);
   const int r0 = rb_first * g.x, q0 = cb * g.y;
   const int h = min(nb * g.x, g.rows - r0), w = min(g.y, g.cols - q0);  // rows of the group, columns of the block
-  const int taps = g.KH * g.KW;
-  // footprint: channels [ch_lo, ch_hi], input rows [ih_lo, ih_hi] (clipped to the image), all columns
+  const int taps = g.KH * g.KW, pitch = g.W + 2 * g.pad;
+  // footprint: channels [ch_lo, ch_hi], input rows from `top` (border included), of which [ih_lo, ih_hi] exist
   const int ch_lo = q0 / taps, ch_hi = (q0 + w - 1) / taps;
   const int oh_lo = r0 / g.Wo, oh_hi = (r0 + h - 1) / g.Wo;
-  const int ih_lo = max(0, oh_lo * g.stride - g.pad), ih_hi = min(g.H - 1, oh_hi * g.stride - g.pad + g.KH - 1);
-  const int nch = ch_hi - ch_lo + 1;
-  const int run0 = ih_lo * g.W, run = max(0, ih_hi - ih_lo + 1) * g.W;  // elements of a channel's plane that are staged
-  const int off = run0 % CE;                                           // the run's offset within its first piece
-  const int pieces = run > 0 ? (off + run + CE - 1) / CE : 0;           // 16-byte pieces per channel
-  // What a draw needs of an element is one bit (above the threshold or not): the copy keeps one byte per
-  // 16-byte piece, bit e = element e of the piece.  The footprint shrinks 16 (bf16) or 32 (fp32) times, so
-  // the CU holds as many workgroups as its wavefront slots allow and many bands can share one copy.
-  uint8_t* stage = reinterpret_cast<uint8_t*>(sens_stage_lds);
-  const int chpb = sg.chp / CE;                               // bytes per channel (chp is a multiple of the piece)
-  const int nch_max = min(g.C, (g.y + taps - 2) / taps + 1);  // channels a column block can touch
-  int* col_lut = reinterpret_cast<int*>(stage + (((size_t)chpb * nch_max + 3) & ~(size_t)3));
+  const int top = oh_lo * g.stride - g.pad;
+  const int ih_lo = max(0, top), ih_hi = min(g.H - 1, oh_hi * g.stride - g.pad + g.KH - 1);
+  const int nch = ch_hi - ch_lo + 1, run = max(0, ih_hi - ih_lo + 1) * g.W;  // elements of a channel that are staged
+  const int pieces = run > 0 ? (2 * (CE - 1) + run) / CE : 0;  // 16-byte pieces a run can touch
+  const int nch_max = min(g.C, (g.y + taps - 2) / taps + 1);   // channels a column block can touch
+  uint32_t* bits = reinterpret_cast<uint32_t*>(sens_stage_lds);
+  const int words = (sg.ch_bits * nch_max + 31) / 32 + 1;
+  int* col_lut = reinterpret_cast<int*>(bits + words);
   int* row_lut = col_lut + w;
-  const T* img = A + (long)n * g.C * g.H * g.W;
+  for (int i = threadIdx.x; i < words; i += 256) bits[i] = 0;
+  __syncthreads();
+  const int border_above = 0.0f > thr ? 1 : 0;  // the zero border: bits are kept relative to it
+  const long img = (long)n * g.C * g.H * g.W, end = (long)g.N * g.C * g.H * g.W;
   // consecutive threads take consecutive pieces, running on from one channel into the next
   for (int i = threadIdx.x; i < nch * pieces; i += 256) {
     const int c = i / pieces, pc = i - c * pieces;
-    const T* src = img + (long)(ch_lo + c) * g.H * g.W + (run0 - off) + pc * CE;
-    const uint4 v = *reinterpret_cast<const uint4*>(src);
+    const long first = img + (long)(ch_lo + c) * g.H * g.W + ih_lo * g.W;  // the run's first element
+    const long at = (first & ~(long)(CE - 1)) + pc * CE;
+    int o = (int)(at - first);                                            // element of the run, or before it
+    if (o >= run) continue;
     T el[CE];
-    *reinterpret_cast<uint4*>(el) = v;
-    unsigned bits = 0;
+    if (at + CE <= end) {
+      *reinterpret_cast<uint4*>(el) = *reinterpret_cast<const uint4*>(A + at);
+    } else {
+      for (int e = 0; e < CE; ++e) el[e] = at + e < end ? A[at + e] : (T)0;
+    }
+    uint32_t b = 0;
 #pragma unroll
-    for (int e = 0; e < CE; ++e) bits |= (ElemTraits<T>::to_f32(el[e]) > thr ? 1u : 0u) << e;
-    stage[(size_t)c * chpb + pc] = (uint8_t)bits;
+    for (int e = 0; e < CE; ++e) b |= (ElemTraits<T>::to_f32(el[e]) > thr ? 1u : 0u) << e;
+    if (border_above) b = ~b;
+    int left = CE;
+    if (o < 0) b >>= -o, left += o, o = 0;
+    left = min(left, run - o);
+    int row = (int)fdiv((uint32_t)o, sg.div_w), x = o - row * g.W;
+    row += ih_lo - top;
+    while (left > 0) {
+      const int len = min(left, g.W - x), pos = c * sg.ch_bits + row * pitch + x + g.pad, sh = pos & 31;
+      const uint32_t seg = b & ((1u << len) - 1u);
+      atomicOr(&bits[pos >> 5], seg << sh);
+      if (sh + len > 32) atomicOr(&bits[(pos >> 5) + 1], seg >> (32 - sh));
+      b >>= len, left -= len, x = 0, ++row;
+    }
   }
-  const int border_above = 0.0f > thr ? 1 : 0;  // the zero border of the input matrix
   for (int i = threadIdx.x; i < w; i += 256) {
     const int q = q0 + i;
     const int ch = (int)fdiv((uint32_t)q, sg.div_taps), tap = q - ch * taps;
     const int kh = (int)fdiv((uint32_t)tap, sg.div_kw), kw = tap - kh * g.KW;
-    col_lut[i] = ((ch - ch_lo) * sg.chp) | (kh << 24) | (kw << 28);
+    col_lut[i] = (ch - ch_lo) * sg.ch_bits + kh * pitch + kw;
   }
   for (int i = threadIdx.x; i < h; i += 256) {
     const int p = r0 + i;
     const int oh = (int)fdiv((uint32_t)p, sg.div_wo), ow = p - oh * g.Wo;
-    row_lut[i] = (oh * g.stride) | ((ow * g.stride) << 16);
+    row_lut[i] = (oh - oh_lo) * g.stride * pitch + ow * g.stride;
   }
   __syncthreads();
+  constexpr uint32_t C1L = 0x1CE4E5B9u, C1H = 0xBF58476Du, C2L = 0x133111EBu, C2H = 0x94D049BBu;
   for (int gi = 0; gi < nb; ++gi) {
     const int region = ((n * g.RB) + rb_first + gi) * g.CB + cb;
-    const int rr0 = gi * g.x;                   // first row of this band within the group
-    const int hb = min(g.x, h - rr0);
+    const int* rows = row_lut + gi * g.x;       // rows of this band within the group
+    const int hb = min(g.x, h - gi * g.x);
     const int size = hb * w;
     int s = (int)(((long)k_permille * size) / 1000);
     if (s < 1) s = 1;
-    int c = 0;
+    // z = (prefix ^ index) + golden, index = region * 65536 + j: its bits from 16 up, without and with the carry
+    const uint64_t P = prefix ^ ((uint64_t)region << 16);
+    uint32_t m[2];
+    uint32_t K[2][2];
+    for (int cy = 0; cy < 2; ++cy) {
+      const uint64_t H = ((P >> 16) + (kSensGolden >> 16) + cy) & 0xffffffffffffULL;
+      m[cy] = (uint32_t)(H >> 14) & 0xffffu;                       // what z >> 30 puts on the lowest 16 bits
+      const uint64_t k = ((H ^ (H >> 30)) << 16) * (((uint64_t)C1H << 32) | C1L);
+      K[cy][0] = (uint32_t)k, K[cy][1] = (uint32_t)(k >> 32);
+      asm("" : "+s"(m[cy]), "+s"(K[cy][0]), "+s"(K[cy][1]));  // (else every draw multiplies the constant it has chosen)
+    }
+    const uint32_t p16 = (uint32_t)P & 0xffffu, g16 = (uint32_t)(kSensGolden & 0xffffu);
+    uint32_t c = 0;
     // (four draws in flight per thread: their table and LDS reads overlap)
 #pragma unroll 4
     for (int j = threadIdx.x; j < s; j += 256) {
-      const uint32_t u = sens_draw(prefix, (uint64_t)region * 65536u + (uint64_t)j);
-      const uint32_t e = (uint32_t)(((uint64_t)u * (uint64_t)size) >> 32);
-      const uint32_t r = fdiv(e, div_w), q = e - r * (uint32_t)w;
-      const int ci = col_lut[q], ri = row_lut[rr0 + r];
-      const int ih = (ri & 0xffff) + ((ci >> 24) & 15) - g.pad, iw = (ri >> 16) + ((ci >> 28) & 15) - g.pad;
-      int above = border_above;
-      if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W) {
-        const int idx = (ci & 0xffffff) + off + (ih - ih_lo) * g.W + iw;  // element within the staged channels
-        above = (stage[idx / CE] >> (idx % CE)) & 1;
-      }
-      c += above;
+      const uint32_t a = (p16 ^ (uint32_t)j) + g16;
+      const bool cy = a > 0xffffu;
+      const uint32_t l = (a & 0xffffu) ^ (cy ? m[1] : m[0]);
+      const uint64_t y = (uint64_t)l * C1L + (((uint64_t)(cy ? K[1][1] : K[0][1]) << 32) | (cy ? K[1][0] : K[0][0]));
+      uint32_t ylo = (uint32_t)y, yhi = (uint32_t)(y >> 32);
+      yhi += __umul24(l, C1H & 0xffffffu) + (__umul24(l, C1H >> 24) << 24);
+      ylo ^= (yhi << 5) | (ylo >> 27);
+      yhi ^= yhi >> 27;
+      uint32_t u = __umulhi(ylo, C2L) + ylo * C2H + yhi * C2L;
+      u ^= u >> 31;
+      const uint64_t uh = (uint64_t)u * (uint32_t)hb;
+      const uint32_t bit = (uint32_t)rows[(uint32_t)(uh >> 32)] + (uint32_t)col_lut[__umulhi((uint32_t)uh, (uint32_t)w)];
+      c += (bits[bit >> 5] >> (bit & 31)) & 1u;
     }
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
-    if ((threadIdx.x & 63) == 0) wave_cnt[threadIdx.x >> 6] = c;
+    int n_above = border_above ? -(int)c : (int)c;
+    for (int o = 32; o > 0; o >>= 1) n_above += __shfl_down(n_above, o, 64);
+    if ((threadIdx.x & 63) == 0) wave_cnt[threadIdx.x >> 6] = n_above;
     __syncthreads();
     if (threadIdx.x == 0) {
-      const int tot = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
+      const int tot = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3] + (border_above ? s : 0);
       count[region] = tot;
       samples[region] = s;
       sens[region] = (1000L * tot >= (long)t_permille * s) ? 1 : 0;
@@ -407,7 +449,7 @@ extern "C" int32_t ard_sens_predict(int32_t dtype, int32_t N, int32_t C, int32_t
   if (lut_ok) {
     const FastDiv dw = fast_div((uint32_t)g.y);
     // footprint of a region in LDS when it fits: rows a band can touch x whole width x channels of a block
-    const int ce = dtype == ARD_BF16 ? 8 : 4, taps = kh * kw;
+    const int taps = kh * kw;
     const int nch_max = imin(C, (g.y + taps - 2) / taps + 1);
     // Bands per workgroup.  Consecutive bands touch nearly the same input rows when they are shorter than an
     // output row (98 bands of 8 positions would copy a 28 x 28 image 14 times over), and a band with few draws
@@ -417,37 +459,35 @@ extern "C" int32_t ard_sens_predict(int32_t dtype, int32_t N, int32_t C, int32_t
     // rows of 8 positions 185 -> 138 us (7 bands: two whole rows), of 4 positions 248 -> 139 us (14), of 16
     // positions 149 -> 147 us (3), 8 x 64 blocks 951 -> 285 us (16); regions of 112 x 576 stay alone (113 us,
     // two per workgroup 131 us).
-    int G = 1, nrow_max = 0, chp = 0, rows1 = 0;
+    int G = 1, nrow_max = 0, ch_bits = 0, rows1 = 0;
     size_t stage_bytes = 0;
     const long draws = imax(1, (int)(((long)k_permille * g.x * g.y) / 1000));
     const int g_cap = (int)imin(16, imax(1, (int)(40000 / draws)));
     for (int cand = 1; cand <= g_cap && cand <= imax(1, g.RB); ++cand) {
       // output rows a group can span: groups of whole rows start on a row, any other may start anywhere in one
       const int oh_span = (cand * g.x) % g.Wo == 0 ? cand * g.x / g.Wo : (cand * g.x + g.Wo - 2) / g.Wo + 1;
-      const int nr = imin(H, (oh_span - 1) * stride + kh);
-      const int cp = (int)align_up((size_t)(ce - 1 + nr * Wd), (size_t)ce);
-      const size_t bytes = align_up((size_t)(cp / ce) * nch_max, (size_t)4) + (size_t)(g.y + cand * g.x) * sizeof(int);
+      const int nr = (imin(oh_span, g.Ho) - 1) * stride + kh, bits = nr * (Wd + 2 * pad);
+      const size_t bytes = (((size_t)bits * nch_max + 31) / 32 + 1 + g.y + cand * g.x) * 4;
       if (cand == 1) rows1 = nr;
       if (cand == 1 || (4 * nr <= 3 * cand * rows1 && bytes <= 64 * 1024 && (long)N * ceil_div(g.RB, cand) * g.CB >= 512))
-        G = cand, nrow_max = nr, chp = cp, stage_bytes = bytes;
+        G = cand, nrow_max = nr, ch_bits = bits, stage_bytes = bytes;
     }
     // (pad < filter size: every window then starts inside the image, which the copy's bounds rely on)
-    if (((H * Wd) % ce) == 0 && (((uintptr_t)A) & 15) == 0 && stage_bytes <= 150 * 1024 && (long)chp * nch_max < (1L << 24) &&
-        pad < kh && pad < kw) {
+    if ((((uintptr_t)A) & 15) == 0 && stage_bytes <= 150 * 1024 && (long)ch_bits * nch_max < (1L << 30) && pad < kh && pad < kw) {
       const int RBG = ceil_div(g.RB, G);
-      const SensStage sg{nrow_max, chp, fast_div((uint32_t)taps), fast_div((uint32_t)kw), fast_div((uint32_t)g.Wo), G, RBG};
+      const SensStage sg{nrow_max, ch_bits, fast_div((uint32_t)taps), fast_div((uint32_t)kw), fast_div((uint32_t)g.Wo), fast_div((uint32_t)Wd), G, RBG};
       const unsigned groups = (unsigned)((long)N * RBG * g.CB);
       hipError_t e = hipSuccess;
       if (dtype == ARD_BF16) {
         if (stage_bytes > 65536) e = raise_lds_limit((const void*)sens_predict_staged_kernel<uint16_t>, (int)stage_bytes);
         if (e == hipSuccess)
           ARD_LAUNCH(sens_predict_staged_kernel<uint16_t>, dim3(groups), dim3(256), stage_bytes, (hipStream_t)stream,
-                     (const uint16_t*)A, g, sg, k_permille, t_permille, threshold, prefix, dw, d_count, d_samples, d_sens);
+                     (const uint16_t*)A, g, sg, k_permille, t_permille, threshold, prefix, d_count, d_samples, d_sens);
       } else {
         if (stage_bytes > 65536) e = raise_lds_limit((const void*)sens_predict_staged_kernel<float>, (int)stage_bytes);
         if (e == hipSuccess)
           ARD_LAUNCH(sens_predict_staged_kernel<float>, dim3(groups), dim3(256), stage_bytes, (hipStream_t)stream, (const float*)A, g,
-                     sg, k_permille, t_permille, threshold, prefix, dw, d_count, d_samples, d_sens);
+                     sg, k_permille, t_permille, threshold, prefix, d_count, d_samples, d_sens);
       }
       if (e != hipSuccess) return fail(ARD_EHIP, "raising the LDS limit failed: %s", hipGetErrorString(e));
       ARD_LAUNCH_CHECK("sens_predict_staged_kernel");

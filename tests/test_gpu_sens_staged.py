@@ -1,0 +1,23 @@
+"""Exactness of the prediction that keeps one bit per element of a region's footprint: planes of any size (rows below
+and above a machine word, pieces that start before or end behind a channel's run, the end of the tensor), thresholds on
+both sides of the zero border, and seeds over which the lowest bits of the draw's argument carry and do not carry."""
+import numpy as np
+import pytest
+
+from test_gpu_sensitivity import _predict_both
+from util import from_vals, stored
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("N,C,H,W,k,stride,pad,x,y", [
+    (1, 1, 1, 1, 1, 1, 0, 1, 0), (3, 5, 7, 7, 3, 1, 1, 7, 0), (2, 3, 13, 13, 3, 1, 1, 4, 9), (2, 4, 5, 40, 5, 1, 2, 40, 0),
+    (1, 3, 6, 65, 3, 1, 1, 20, 0), (2, 7, 19, 3, 3, 2, 1, 5, 0), (2, 64, 27, 27, 3, 1, 1, 54, 288)])
+@pytest.mark.parametrize("thr", [-0.2, 0.4])
+def test_odd_planes_and_thresholds(dtype, N, C, H, W, k, stride, pad, x, y, thr):
+    print("prediction", dtype, N, C, H, W, k, stride, pad, x, y, thr, flush=True)
+    rng = np.random.default_rng(H * W + C)
+    Av = stored(rng.standard_normal((N, C, H, W)), dtype)
+    for seed in (1, 123456789, 2 ** 63 + 5):
+        _predict_both(Av, from_vals(Av, dtype), k, stride, pad, x, y, 300, 500, thr, seed, seed % 7)
