@@ -17,7 +17,7 @@
 
 #include <type_traits>
 
-#include "engine.hpp"
+#include "fast.hpp"
 #include "pattern.hpp"
 
 namespace ard {
@@ -185,6 +185,36 @@ __global__ void lstm_scatter_dw_kernel(const T* dwx, const T* dwh, const int* ra
 
 static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
+// What workgroups exchange from step to step is its own flag: every word of the buffer holds kUnwritten when the
+// kernel starts (no pair of bf16 results has these bits: f32_to_bf16_bits makes every NaN 0x7fc0), is written once
+// with a device-scope store, and a reader takes its 16-byte pieces with device-scope loads until none holds the
+// mark.  A step is then one store on its way to memory and one load that comes after it, where separate flags took
+// four trips: the stores' acknowledgement, the flag's store, the poll and the load of the data.
+constexpr unsigned kUnwritten = 0xffffffffu;
+typedef unsigned lp_u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bool lp_unwritten(const lp_u32x4& v) {
+  return v.x == kUnwritten || v.y == kUnwritten || v.z == kUnwritten || v.w == kUnwritten;
+}
+// device-scope 16-byte load at byte `at` of the buffer (SC1: past the XCD's own caches)
+__device__ __forceinline__ lp_u32x4 lp_load(__amdgpu_buffer_rsrc_t r, unsigned at) {
+  return __builtin_bit_cast(lp_u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, 0, 16));
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t lp_buffer(const void* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
+}
+// one more poll failed: true when this wavefront gives up
+__device__ __forceinline__ bool lp_give_up(long& spins, long limit, int* err) {
+  if (++spins <= limit && ((spins & 63) || !__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return false;
+  __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+// before a recurrence: marks the exchange buffer, clears the status word and the flags
+__global__ __launch_bounds__(256) void lstm_mark_kernel(uint4* buf, long n16, int* sync, int n_sync) {
+  const long i0 = (long)blockIdx.x * 256 + threadIdx.x, step = (long)gridDim.x * 256;
+  if (i0 < n_sync) sync[i0] = 0;
+  for (long i = i0; i < n16; i += step) buf[i] = make_uint4(kUnwritten, kUnwritten, kUnwritten, kUnwritten);
+}
+
 // ---- the recurrence in one launch (Section 7.2.3) -----------------------------------------------
 //
 // The per-step products of a batch-128 LSTM are a few hundred MFLOP each: issued as launches, a step
@@ -193,10 +223,12 @@ static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // sequence) and the MB = 32 * TMB batch rows of block bb: per step it multiplies h_{t-1}[rows, :] by its 32
 // gate rows (32x32x16 MFMAs, the contraction dealt over the 4 wavefronts and summed through LDS), adds
 // the input projection, runs the cell for its (row, unit) pairs (c stays in a register) and writes h_t.
-// Steps are separated by one flag per workgroup: after its h_t is written a workgroup posts t + 1; a
-// workgroup starts step t when the S workgroups of its batch block have all posted t.  h_t travels between workgroups on
-// different XCDs through device-scope (write-through) stores and device-scope loads; a workgroup waits for
-// its own stores before it signals.  All workgroups must be resident together (the host launches this
+// h_t travels between workgroups on different XCDs through device-scope (write-through) stores and device-scope
+// loads that wait for the data itself (kUnwritten above).  Large states are read through L2 instead, with one flag per
+// workgroup: after its h_t is written (its own stores waited for) a workgroup posts t + 1; a workgroup starts step t
+// when the S workgroups of its batch block have all posted t.
+// vmcnt counts loads and stores together and in order: what is not wanted by the next step (its outputs to the
+// caller, two trips to memory) is stored, and the next step's projections are fetched, right after a wait has ended.  All workgroups must be resident together (the host launches this
 // kernel only with at most one workgroup per CU); the wait is bounded all the same: a workgroup that gives
 // up sets *err and leaves, and every workgroup that sees *err leaves too.
 struct LstmPersist {
@@ -214,7 +246,8 @@ struct LstmPersist {
 };
 
 // VIA_L2: h_{t-1} is read through the XCD's L2 after an agent-scope acquire (else with device-scope loads)
-template <int TMB, bool VIA_L2>
+// CH: 16-wide slices a wavefront has in flight
+template <int TMB, bool VIA_L2, int CH>
 __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist P) {
   constexpr int MB = 32 * TMB;
   extern __shared__ uint4 lp_lds[];
@@ -224,7 +257,8 @@ __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist
   const int Hp = P.Hp, B = P.B, H = P.H;
   const int pitch = Hp * 2 + 16;  // bytes between the staged weight rows (rows start 16 bytes apart in the banks)
   char* wl = reinterpret_cast<char*>(lp_lds);
-  float* red = reinterpret_cast<float*>(wl + 32 * pitch);  // [4][MB][33]
+  float* const reds = reinterpret_cast<float*>(wl + 32 * pitch);  // [TMB == 1 ? 2 : 1][4][MB][33]
+  if (tid == 0) go_s = 1;
   // this workgroup's 32 gate rows, r = gate * 8 + local unit, staged once
   const int chunks = Hp >> 3;
   for (int i = tid; i < 32 * chunks; i += 256) {
@@ -245,7 +279,44 @@ __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist
   float c_reg[TMB];
 #pragma unroll
   for (int rt = 0; rt < TMB; ++rt) c_reg[rt] = 0.0f;
+  float zx[TMB][4];
+  auto fetch_zx = [&](int t) {
+    const float* Gt = P.Gx + (long)t * B * 4 * Hp;
+#pragma unroll
+    for (int rt = 0; rt < TMB; ++rt) {
+      const int row = bb * MB + rt * 32 + rb;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) zx[rt][g] = (row < B && kept) ? Gt[(long)row * 4 * Hp + g * Hp + j] : 0.0f;
+    }
+  };
+  float gi[TMB], gf[TMB], gg[TMB], go[TMB], hv[TMB];
+  auto store_outputs = [&](int t) {
+#pragma unroll
+    for (int rt = 0; rt < TMB; ++rt) {
+      const int row = bb * MB + rt * 32 + rb;
+      if (row >= B) continue;
+      float* ga = P.gates + ((long)t * B + row) * 4 * H;
+      if (kept) {
+        ga[u] = gi[rt];
+        ga[H + u] = gf[rt];
+        ga[2 * H + u] = gg[rt];
+        ga[3 * H + u] = go[rt];
+        P.c[((long)t * B + row) * H + u] = c_reg[rt];
+        P.h[((long)t * B + row) * H + u] = f32_to_bf16_bits(hv[rt]);
+      }
+      // zeros of the dropped units of this thread's group
+      for (int uz = z_lo; uz < z_hi; ++uz) {
+        if (uz == u) continue;
+        ga[uz] = ga[H + uz] = ga[2 * H + uz] = ga[3 * H + uz] = 0.0f;
+        P.c[((long)t * B + row) * H + uz] = 0.0f;
+        P.h[((long)t * B + row) * H + uz] = 0;
+      }
+    }
+  };
+  if (!VIA_L2) fetch_zx(0);
   for (int t = 0; t < P.T; ++t) {
+    float* const red = reds + (TMB == 1 ? (t & 1) * 4 * MB * 33 : 0);
+    float zn[TMB][4];  // this step's projections
     f32x16_t acc[TMB];
 #pragma unroll
     for (int rt = 0; rt < TMB; ++rt)
@@ -253,16 +324,65 @@ __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist
       for (int v = 0; v < 16; ++v) acc[rt][v] = 0.0f;
     // this step's input projections do not depend on h_{t-1}: fetched before the wait, so that their
     // trip to memory overlaps it
-    float zx[TMB][4];
-    {
-      const float* Gt = P.Gx + (long)t * B * 4 * Hp;
+    if (VIA_L2) fetch_zx(t);
 #pragma unroll
-      for (int rt = 0; rt < TMB; ++rt) {
-        const int row = bb * MB + rt * 32 + rb;
+    for (int rt = 0; rt < TMB; ++rt)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) zx[rt][g] = (row < B && kept) ? Gt[(long)row * 4 * Hp + g * Hp + j] : 0.0f;
+      for (int g = 0; g < 4; ++g) zn[rt][g] = zx[rt][g];
+    if constexpr (!VIA_L2) {
+      if (t > 0) {
+        const auto hp = lp_buffer(P.hc + (long)(t - 1) * B * Hp, (unsigned)(B * Hp * 2));
+        const int khalf = lane >> 5;
+        unsigned rowb[TMB];
+#pragma unroll
+        for (int rt = 0; rt < TMB; ++rt) rowb[rt] = (unsigned)(imin(bb * MB + rt * 32 + (lane & 31), B - 1) * Hp * 2);  // (rows beyond the batch are never stored)
+        bool gone = P.spin_limit < 0;  // (a negative bound is the host's way to force the give-up path)
+        if (gone) __hip_atomic_store(P.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int q0 = wave; q0 < nslice && !gone; q0 += 4 * CH) {
+          lp_u32x4 v[CH][TMB];
+          long spins = 0;
+          for (;;) {
+            bool wait = false;
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+              const int q = q0 + 4 * i, kk = q * 16 + khalf * 8;
+              const int kc = (q < nslice && kk < Hp) ? kk : 0;  // (clamped: the value is discarded below)
+#pragma unroll
+              for (int rt = 0; rt < TMB; ++rt) v[i][rt] = lp_load(hp, rowb[rt] + kc * 2);
+            }
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+#pragma unroll
+              for (int rt = 0; rt < TMB; ++rt) wait |= lp_unwritten(v[i][rt]);
+            if (!__any(wait)) break;
+            if ((gone = lp_give_up(spins, P.spin_limit, P.err))) break;
+          }
+          if (q0 == wave) {
+            store_outputs(t - 1);
+            if (t + 1 < P.T) fetch_zx(t + 1);
+          }
+#pragma unroll
+          for (int i = 0; i < CH; ++i) {
+            const int q = q0 + 4 * i;
+            if (q >= nslice) break;
+            const int kk = q * 16 + khalf * 8;
+            const bool k_ok = kk < Hp;
+            const uint4 bw = *reinterpret_cast<const uint4*>(wl + (lane & 31) * pitch + (k_ok ? kk : 0) * 2);
+            const bf16x8_t bfrag = __builtin_bit_cast(bf16x8_t, k_ok ? bw : make_uint4(0, 0, 0, 0));
+#pragma unroll
+            for (int rt = 0; rt < TMB; ++rt)
+              acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, v[i][rt]), bfrag, acc[rt], 0, 0, 0);
+          }
+        }
+        if (wave >= nslice) {  // (no slice: nothing to wait for)
+          store_outputs(t - 1);
+          if (t + 1 < P.T) fetch_zx(t + 1);
+        }
+        if (gone && lane == 0) go_s = 0;
+      } else if (P.T > 1) {
+        fetch_zx(1);
       }
-    }
+    } else
     if (t > 0) {
       if (wave == 0) {
         // every workgroup of this batch block has posted step t - 1: one flag per workgroup (no contended
@@ -284,16 +404,15 @@ __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist
         }
         if (lane == 0) go_s = ok;
         // (h_{t-1} is complete in memory: drop what this CU's L1 and this XCD's L2 may hold of it)
-        if (VIA_L2) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       }
       __syncthreads();
       if (!go_s) return;  // uniform: every thread of the workgroup leaves
       // recurrent product: this wavefront's 16-wide slices of the contraction
       const unsigned long long* hp = reinterpret_cast<const unsigned long long*>(P.hc + (long)(t - 1) * B * Hp);
       const int khalf = lane >> 5;
-      // the device-scope loads of h_{t-1} travel a long way: a wavefront issues those of CH slices
-      // together and multiplies afterwards (one round trip per CH slices instead of one per slice)
-      constexpr int CH = TMB == 4 ? 4 : 8;
+      // a wavefront issues the loads of CH slices together and multiplies afterwards (one round trip per CH slices
+      // instead of one per slice)
       for (int q0 = wave; q0 < nslice; q0 += 4 * CH) {
         unsigned long long lo[CH][TMB], hi[CH][TMB];
 #pragma unroll
@@ -305,14 +424,8 @@ __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist
           for (int rt = 0; rt < TMB; ++rt) {
             int row = bb * MB + rt * 32 + (lane & 31);
             row = row < B ? row : B - 1;  // rows beyond the batch are never stored
-            const unsigned long long* src = hp + (((long)row * Hp + kc) >> 2);
-            if (VIA_L2) {
-              const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(src);
-              lo[i][rt] = v.x, hi[i][rt] = v.y;
-            } else {
-              lo[i][rt] = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              hi[i][rt] = __hip_atomic_load(src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(hp + (((long)row * Hp + kc) >> 2));
+            lo[i][rt] = v.x, hi[i][rt] = v.y;
           }
         }
 #pragma unroll
@@ -338,10 +451,9 @@ __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist
       for (int v = 0; v < 16; ++v)
         red[(wave * MB + rt * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * 33 + (lane & 31)] = acc[rt][v];
     __syncthreads();
-    // cell.  What the other workgroups wait for is h_t alone: it is stored first (device scope), the
-    // workgroup signals as soon as those stores have completed, and only then writes gates, c and h to
-    // the caller's tensors (their trip to memory is off the critical path of the recurrence).
-    float gi[TMB], gf[TMB], gg[TMB], go[TMB], hv[TMB];
+    if (!go_s) return;  // uniform: every thread of the workgroup leaves
+    // cell.  What the other workgroups wait for is h_t alone: it is stored first (device scope); gates, c and h go
+    // to the caller's tensors off the critical path of the recurrence.
 #pragma unroll
     for (int rt = 0; rt < TMB; ++rt) {
       const int rl = rt * 32 + rb, row = bb * MB + rl;
@@ -351,7 +463,7 @@ __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int col = g * 8 + ul;
-          z[g] = zx[rt][g] + ((red[(0 * MB + rl) * 33 + col] + red[(1 * MB + rl) * 33 + col]) +
+          z[g] = zn[rt][g] + ((red[(0 * MB + rl) * 33 + col] + red[(1 * MB + rl) * 33 + col]) +
                               (red[(2 * MB + rl) * 33 + col] + red[(3 * MB + rl) * 33 + col]));
         }
         gi[rt] = sigmoidf_(z[0]), gf[rt] = sigmoidf_(z[1]), gg[rt] = tanhf(z[2]), go[rt] = sigmoidf_(z[3]);
@@ -368,33 +480,18 @@ __global__ __launch_bounds__(256) void lstm_persist_fwd_kernel(const LstmPersist
                              __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    // every thread's h_t stores have completed before the workgroup signals
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0 && t + 1 < P.T)
-      __hip_atomic_store(&P.counters[(long)bb * P.S + s], t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int rt = 0; rt < TMB; ++rt) {
-      const int row = bb * MB + rt * 32 + rb;
-      if (row >= B) continue;
-      float* ga = P.gates + ((long)t * B + row) * 4 * H;
-      if (kept) {
-        ga[u] = gi[rt];
-        ga[H + u] = gf[rt];
-        ga[2 * H + u] = gg[rt];
-        ga[3 * H + u] = go[rt];
-        P.c[((long)t * B + row) * H + u] = c_reg[rt];
-        P.h[((long)t * B + row) * H + u] = f32_to_bf16_bits(hv[rt]);
-      }
-      // zeros of the dropped units of this thread's group
-      for (int uz = z_lo; uz < z_hi; ++uz) {
-        if (uz == u) continue;
-        ga[uz] = ga[H + uz] = ga[2 * H + uz] = ga[3 * H + uz] = 0.0f;
-        P.c[((long)t * B + row) * H + uz] = 0.0f;
-        P.h[((long)t * B + row) * H + uz] = 0;
-      }
+    if (VIA_L2) {
+      // every thread's h_t stores have completed before the workgroup signals
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0 && t + 1 < P.T)
+        __hip_atomic_store(&P.counters[(long)bb * P.S + s], t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      store_outputs(t);
+    } else if (TMB > 1) {
+      __syncthreads();  // (one buffer of partial tiles: nobody overwrites it before everybody has read it)
     }
   }
+  if (!VIA_L2) store_outputs(P.T - 1);
 }
 
 // ---- the backward recurrence in one launch ------------------------------------------------------
@@ -420,9 +517,10 @@ struct LstmPersistBwd {
   int T, B, H, Hk, Hp, S, UW;
   int off, step;        // kept unit j is physical unit off + j * step
   long spin_limit;
+  char* ex;             // staging wavefronts: [T][batch block][unit slice] blocks the workgroups exchange
 };
 
-template <int TM16, bool VIA_L2>
+template <int TM16, bool VIA_L2, int CH>
 __global__ __launch_bounds__(256) void lstm_persist_bwd_kernel(const LstmPersistBwd P) {
   constexpr int MB = 16 * TM16;
   constexpr int NPMAX = 2 * TM16;  // (row, unit) pairs of a thread when UW = 32
@@ -434,7 +532,8 @@ __global__ __launch_bounds__(256) void lstm_persist_bwd_kernel(const LstmPersist
   const int pitch = K * 2 + 64;  // bytes between the staged columns (64 bytes apart in the banks)
   const int RW = UW + 1;
   char* wl = reinterpret_cast<char*>(lp_lds);
-  float* red = reinterpret_cast<float*>(wl + UW * pitch);  // [4][MB][RW]
+  float* const reds = reinterpret_cast<float*>(wl + UW * pitch);  // [VIA_L2 ? 1 : 2][4][MB][RW]
+  if (tid == 0) go_s = 1;
   // this workgroup's UW columns of Wh', wl[local unit][gate row], staged once
   // (a row of Wh' is read in 16-byte pieces of 8 units: Hp and UW are multiples of 8)
   const int cpr = UW >> 3;
@@ -459,22 +558,31 @@ __global__ __launch_bounds__(256) void lstm_persist_bwd_kernel(const LstmPersist
   float dc_next[NPMAX];
 #pragma unroll
   for (int i = 0; i < NPMAX; ++i) dc_next[i] = 0.0f;
-  for (int tt = 0; tt < P.T; ++tt) {
-    const int t = P.T - 1 - tt;
-    // what the cell needs of the forward pass does not depend on the other workgroups: fetched before the wait
-    float gi[NPMAX], gf[NPMAX], gg[NPMAX], go[NPMAX], ct[NPMAX], cp[NPMAX], dhe[NPMAX];
+  // what the cell of step t needs of the forward pass does not depend on the other workgroups: fetched a step ahead
+  float ni[NPMAX], nf[NPMAX], ng[NPMAX], no[NPMAX], nc[NPMAX], np_c[NPMAX], nd[NPMAX];
+  auto fetch_cell = [&](int t) {
 #pragma unroll
     for (int i = 0; i < NPMAX; ++i) {
-      gi[i] = gf[i] = gg[i] = go[i] = ct[i] = cp[i] = dhe[i] = 0.0f;
+      ni[i] = nf[i] = ng[i] = no[i] = nc[i] = np_c[i] = nd[i] = 0.0f;
       const int row = bb * MB + r0 + i * rstep;
       if (i < np && row < B && kept) {
         const float* ga = P.gates + ((long)t * B + row) * 4 * H;
-        gi[i] = ga[u], gf[i] = ga[H + u], gg[i] = ga[2 * H + u], go[i] = ga[3 * H + u];
-        ct[i] = P.c[((long)t * B + row) * H + u];
-        if (t > 0) cp[i] = P.c[((long)(t - 1) * B + row) * H + u];
-        dhe[i] = bf16_bits_to_f32(P.dh[((long)t * B + row) * H + u]);
+        ni[i] = ga[u], nf[i] = ga[H + u], ng[i] = ga[2 * H + u], no[i] = ga[3 * H + u];
+        nc[i] = P.c[((long)t * B + row) * H + u];
+        if (t > 0) np_c[i] = P.c[((long)(t - 1) * B + row) * H + u];
+        nd[i] = bf16_bits_to_f32(P.dh[((long)t * B + row) * H + u]);
       }
     }
+  };
+  fetch_cell(P.T - 1);
+  for (int tt = 0; tt < P.T; ++tt) {
+    const int t = P.T - 1 - tt;
+    float* const red = reds + (VIA_L2 ? 0 : (tt & 1) * 4 * MB * RW);
+    if (VIA_L2 && tt > 0) fetch_cell(t);
+    float gi[NPMAX], gf[NPMAX], gg[NPMAX], go[NPMAX], ct[NPMAX], cp[NPMAX], dhe[NPMAX];
+#pragma unroll
+    for (int i = 0; i < NPMAX; ++i)
+      gi[i] = ni[i], gf[i] = nf[i], gg[i] = ng[i], go[i] = no[i], ct[i] = nc[i], cp[i] = np_c[i], dhe[i] = nd[i];
     f32x4_t acc[TM16][2];
 #pragma unroll
     for (int rt = 0; rt < TM16; ++rt)
@@ -482,7 +590,55 @@ __global__ __launch_bounds__(256) void lstm_persist_bwd_kernel(const LstmPersist
       for (int cti = 0; cti < 2; ++cti)
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[rt][cti][v] = 0.0f;
-    if (tt > 0) {
+    if constexpr (!VIA_L2) {
+      if (tt > 0) {
+        const auto gsrc = lp_buffer(P.dG + (long)(t + 1) * B * K, (unsigned)(B * K * 2));
+        const int kgrp = lane >> 4, n = lane & 15;
+        unsigned rowb[TM16];
+#pragma unroll
+        for (int rt = 0; rt < TM16; ++rt) rowb[rt] = (unsigned)(imin(bb * MB + rt * 16 + n, B - 1) * K * 2);  // (rows beyond the batch are never stored)
+        bool gone = P.spin_limit < 0;  // (a negative bound is the host's way to force the give-up path)
+        if (gone) __hip_atomic_store(P.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int q0 = wave; q0 < nslice && !gone; q0 += 4 * CH) {
+          lp_u32x4 av[CH][TM16];
+          long spins = 0;
+          for (;;) {
+            bool wait = false;
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+              const int q = q0 + 4 * i, kc = q < nslice ? q * 32 + kgrp * 8 : 0;  // (clamped: the value is discarded below)
+#pragma unroll
+              for (int rt = 0; rt < TM16; ++rt) av[i][rt] = lp_load(gsrc, rowb[rt] + kc * 2);
+            }
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+#pragma unroll
+              for (int rt = 0; rt < TM16; ++rt) wait |= lp_unwritten(av[i][rt]);
+            if (!__any(wait)) break;
+            if ((gone = lp_give_up(spins, P.spin_limit, P.err))) break;
+          }
+          if (q0 == wave && t > 0) fetch_cell(t - 1);
+#pragma unroll
+          for (int i = 0; i < CH; ++i) {
+            const int q = q0 + 4 * i;
+            if (q >= nslice) break;
+            const int kk = q * 32 + kgrp * 8;
+#pragma unroll
+            for (int cti = 0; cti < 2; ++cti) {
+              if (cti >= nct) break;  // (uniform)
+              const bf16x8_t bfrag = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(wl + (cti * 16 + n) * pitch + kk * 2));
+#pragma unroll
+              for (int rt = 0; rt < TM16; ++rt)
+                acc[rt][cti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[i][rt]), bfrag, acc[rt][cti], 0, 0, 0);
+            }
+          }
+        }
+        if (wave >= nslice && t > 0) fetch_cell(t - 1);  // (no slice: nothing to wait for)
+        if (gone && lane == 0) go_s = 0;
+      } else if (t > 0) {
+        fetch_cell(t - 1);
+      }
+    } else if (tt > 0) {
       if (wave == 0) {
         // every workgroup of this batch block has posted dG_{t+1}
         const int* flags = P.counters + (long)bb * P.S;
@@ -499,13 +655,12 @@ __global__ __launch_bounds__(256) void lstm_persist_bwd_kernel(const LstmPersist
           }
         }
         if (lane == 0) go_s = ok;
-        if (VIA_L2) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       }
       __syncthreads();
       if (!go_s) return;  // uniform: every thread of the workgroup leaves
       const uint16_t* gsrc = P.dG + (long)(t + 1) * B * K;
       const int kgrp = lane >> 4, n = lane & 15;
-      constexpr int CH = 16 / TM16;  // slices whose loads a wavefront issues together
       for (int q0 = wave; q0 < nslice; q0 += 4 * CH) {
         uint4 av[CH][TM16];
 #pragma unroll
@@ -516,15 +671,7 @@ __global__ __launch_bounds__(256) void lstm_persist_bwd_kernel(const LstmPersist
           for (int rt = 0; rt < TM16; ++rt) {
             int row = bb * MB + rt * 16 + n;
             row = row < B ? row : B - 1;  // rows beyond the batch are never stored
-            const uint16_t* src = gsrc + (long)row * K + kc;
-            if (VIA_L2) {
-              av[i][rt] = *reinterpret_cast<const uint4*>(src);
-            } else {
-              const unsigned long long* s8 = reinterpret_cast<const unsigned long long*>(src);
-              const unsigned long long lo = __hip_atomic_load(s8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              const unsigned long long hi = __hip_atomic_load(s8 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              av[i][rt] = make_uint4((unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32));
-            }
+            av[i][rt] = *reinterpret_cast<const uint4*>(gsrc + (long)row * K + kc);
           }
         }
 #pragma unroll
@@ -554,6 +701,7 @@ __global__ __launch_bounds__(256) void lstm_persist_bwd_kernel(const LstmPersist
           red[(wave * MB + rt * 16 + 4 * (lane >> 4) + v) * RW + cti * 16 + (lane & 15)] = acc[rt][cti][v];
       }
     __syncthreads();
+    if (!go_s) return;  // uniform: every thread of the workgroup leaves
 #pragma unroll
     for (int i = 0; i < NPMAX; ++i) {
       if (i >= np) break;  // (uniform)
@@ -580,17 +728,352 @@ __global__ __launch_bounds__(256) void lstm_persist_bwd_kernel(const LstmPersist
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    // every thread's stores have completed before the workgroup signals
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0 && tt + 1 < P.T)
-      __hip_atomic_store(&P.counters[(long)bb * P.S + s], tt + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (VIA_L2) {
+      // every thread's stores have completed before the workgroup signals
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0 && tt + 1 < P.T)
+        __hip_atomic_store(&P.counters[(long)bb * P.S + s], tt + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
-__global__ void lstm_zero_ints_kernel(int* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+// ---- both recurrences with staging wavefronts ---------------------------------------------------
+//
+// The recurrences below where a step's operands fit in LDS and the recurrent weights in registers (up to 1024 kept
+// units): a workgroup has four wavefronts that compute and four that do nothing but fetch what the other workgroups
+// write.  Measured in the kernels without them (512 kept units, B = 128): of 10300 clocks a step spent 5000 waiting
+// for one round of device-scope loads that found everything written already, and 2400 between the loads and the
+// product, issuing stores.  The loads took that long because
+//  * a wavefront's MFMA operands are 32 bytes of each row, and a workgroup's results 16: every 128-byte line left
+//    memory in four requests and came there in eight.  Here what a workgroup writes in a step is one contiguous
+//    block in the order the fragments are read in, a store instruction is one whole line, and load instructions take
+//    whole lines into LDS, from where the fragments come without bank conflicts;
+//  * vmcnt counts a wavefront's stores and loads in one order: loads behind stores wait for their acknowledgement.
+//    The fetching wavefronts store nothing.
+// A step: fetch (loads until nothing in them is unwritten) | barrier | product, partial tiles to LDS | barrier | sum,
+// cell, device-scope stores, the caller's outputs; the fetch of the next step starts at the second barrier.
+// A step of 512 kept units, B = 128: forward 12700 -> 7550 clocks (waiting 3300 for the first line after its own cell,
+// fetch 1740, product 710, cell 1300), backward 15600 -> 8230 (fetch 3350: 64 KB a workgroup); 64 steps 339 -> 203 us and
+// 417 -> 225 us.  Starting the workgroups of an XCD at different lines, or more accumulators, changed nothing; 16-byte
+// stores of single lanes instead of whole lines of words made the backward step 40 % longer.
+
+// One wavefront's share of what the workgroups of a batch block wrote in a step: N KB at `at` + i KB of the block's
+// `bytes` bytes, to `dst`.  First one line of every writer is polled past the caches (`peek`: the last it stores); when
+// they have arrived, nearly always everything has, and the share is read through L2, where the workgroups of an XCD
+// find what one of them fetched.  Only if a mark is left in it, a line was read too early and may lie in a cache: the
+// share is then read past the caches until it is complete.  False: gave up.
+template <int N, int NP>
+__device__ __forceinline__ bool lp_fetch(const char* src, unsigned bytes, const unsigned (&at)[N], const unsigned (&peek)[NP], char* dst, int lane,
+                                         long limit, int* err) {
+  if (limit < 0) {  // (a negative bound is the host's way to force the give-up path)
+    __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+  }
+  long spins = 0;
+  const auto buf = lp_buffer(src, bytes);
+  for (;;) {
+    lp_u32x4 v[NP];
+    bool wait = false;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) v[i] = lp_load(buf, peek[i]);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) wait |= lp_unwritten(v[i]);
+    if (!__any(wait)) break;
+    if (lp_give_up(spins, limit, err)) return false;
+  }
+  auto complete = [&] {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bool wait = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) wait |= lp_unwritten(*reinterpret_cast<const lp_u32x4*>(dst + i * 1024 + lane * 16));
+    return !__any(wait);
+  };
+#pragma unroll
+  for (int i = 0; i < N; ++i) __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(src + at[i]), ARD_LDS_PTR(dst + i * 1024), 16, 0, 0);
+  while (!complete()) {
+    if (lp_give_up(spins, limit, err)) return false;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < N; ++i) __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(src + at[i]), ARD_LDS_PTR(dst + i * 1024), 16, 0, 16);
+  }
+  return true;
+}
+// Workgroup -> (unit slice, batch block): XCD x = blockIdx % 8 takes the x-th eighth of the workgroups, batch block by
+// batch block, so that an XCD fetches the rows of few batch blocks.
+__device__ __forceinline__ bool lp_place(int S, int total, int& s, int& bb) {
+  const int x = (int)blockIdx.x & 7, lo = (int)((long)x * total / 8), hi = (int)((long)(x + 1) * total / 8), L = lo + ((int)blockIdx.x >> 3);
+  bb = L / S, s = L - bb * S;
+  return L < hi;
+}
+__device__ __forceinline__ void lp_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  wg_barrier();
+}
+
+// Workgroup (s, bb): 8 * UT kept units, batch rows 32 bb .. 32 bb + 31.  KW: 16-wide slices of the contraction per wavefront.
+template <int UT, int KW>
+__global__ __launch_bounds__(512) void lstm_staged_fwd_kernel(const LstmPersist P) {
+  constexpr int UW = 8 * UT, RP = 32 * UT + 1, BLK = 32 * UW * 2;  // BLK: bytes a workgroup writes in a step, [32 rows][UW units]
+  extern __shared__ uint4 lp_lds[];
+  __shared__ int go_s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int s, bb;
+  if (!lp_place(P.S, P.S * ((P.B + 31) / 32), s, bb)) return;
+  const int Hp = P.Hp, B = P.B, H = P.H;
+  char* const stage = reinterpret_cast<char*>(lp_lds);             // [4 KW] KB: blocks of the unit slices in order
+  float* const red = reinterpret_cast<float*>(stage + 4096 * KW);  // [4][32][RP]
+  char* const ex = reinterpret_cast<char*>(P.hc) + (long)bb * P.S * BLK;  // this batch block's blocks of step 0
+  const long ex_step = (long)((B + 31) / 32) * P.S * BLK;
+  if (tid == 0) go_s = 1;
+  lp_barrier();
+  if (wave >= 4) {
+    const int w = wave - 4;
+    const unsigned total = (unsigned)(P.S * BLK);
+    unsigned at[KW], peek[1];
+#pragma unroll
+    for (int i = 0; i < KW; ++i) {
+      const unsigned o = (unsigned)((w * KW + i) * 1024 + lane * 16);
+      at[i] = o < total ? o : (unsigned)(lane * 16) % BLK;  // (beyond the last slice: multiplied by zero weights)
+    }
+    {
+      // the last line of slice `lane` of the share (a share is at most 32 slices; the rest look at its first one)
+      const unsigned o = (unsigned)(w * KW * 1024 + (lane * BLK < KW * 1024 ? lane : 0) * BLK);
+      peek[0] = (o < total ? o : 0u) + BLK - 128;
+    }
+    for (int t = 0; t < P.T; ++t) {
+      if (t > 0 && !lp_fetch(ex + (t - 1) * ex_step, total, at, peek, stage + w * KW * 1024, lane, P.spin_limit, P.err)) go_s = 0;
+      lp_barrier();
+      if (!go_s) return;  // uniform: every wavefront reads it behind the same barrier
+      lp_barrier();
+    }
+    return;
+  }
+  // this wavefront's part of the gate rows, in registers for the whole sequence: column r = gate * 8 + unit of tile ut
+  const int khalf = lane >> 5, col = lane & 31;
+  bf16x8_t wf[KW][UT];
+#pragma unroll
+  for (int i = 0; i < KW; ++i)
+#pragma unroll
+    for (int ut = 0; ut < UT; ++ut) {
+      const int k = (wave * KW + i) * 16 + khalf * 8, unit = s * UW + ut * 8 + (col & 7);
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (k < Hp && unit < Hp) v = *reinterpret_cast<const uint4*>(P.Wh + ((long)(col >> 3) * Hp + unit) * Hp + k);
+      wf[i][ut] = __builtin_bit_cast(bf16x8_t, v);
+    }
+  // cell: thread = (local unit ul, rows rb + i * 32 / UT)
+  const int ul = tid % UW, rb = tid / UW;
+  const int j = s * UW + ul;  // compact unit
+  const bool kept = j < P.Hk;
+  const int u = P.off + j * P.step;  // physical unit
+  // zeros of the dropped units this thread owns: the rest of its group [j*step, (j+1)*step), the last kept
+  // unit also the tail up to H
+  const int z_lo = j * P.step, z_hi = !kept ? z_lo : (j == P.Hk - 1 ? H : z_lo + P.step);
+  float c_reg[UT], zx[UT][4];
+  auto fetch_zx = [&](int t) {
+    const float* Gt = P.Gx + (long)t * B * 4 * Hp;
+#pragma unroll
+    for (int i = 0; i < UT; ++i) {
+      const int row = imin(bb * 32 + rb + i * (32 / UT), B - 1), jj = imin(j, Hp - 1);  // (clamped: never used)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) zx[i][g] = Gt[(long)row * 4 * Hp + g * Hp + jj];
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < UT; ++i) c_reg[i] = 0.0f;
+  fetch_zx(0);
+  for (int t = 0; t < P.T; ++t) {
+    lp_barrier();
+    if (!go_s) return;
+    f32x16_t acc[UT];
+#pragma unroll
+    for (int ut = 0; ut < UT; ++ut)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[ut][v] = 0.0f;
+    if (t > 0) {
+      const char* mine = stage + wave * KW * 1024;
+      bf16x8_t af[KW];
+#pragma unroll
+      for (int i = 0; i < KW; ++i) af[i] = *reinterpret_cast<const bf16x8_t*>(mine + (UT == 1 ? (2 * i + khalf) * 32 + col : (i * 32 + col) * 2 + khalf) * 16);
+#pragma unroll
+      for (int i = 0; i < KW; ++i)
+#pragma unroll
+        for (int ut = 0; ut < UT; ++ut) acc[ut] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], wf[i][ut], acc[ut], 0, 0, 0);
+    }
+    // partial tiles -> LDS: lane holds column (lane & 31), rows 8*(v/4) + 4*(lane>>5) + v%4
+#pragma unroll
+    for (int ut = 0; ut < UT; ++ut)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[(wave * 32 + 8 * (v >> 2) + 4 * khalf + (v & 3)) * RP + ut * 32 + col] = acc[ut][v];
+    lp_barrier();
+    // cell.  What the other workgroups wait for is h_t alone: it is stored first (device scope).
+    unsigned* const mine = reinterpret_cast<unsigned*>(ex + t * ex_step + s * BLK);
+    float gi[UT], gf[UT], gg[UT], go[UT], hv[UT];
+#pragma unroll
+    for (int i = 0; i < UT; ++i) {
+      const int rl = rb + i * (32 / UT), row = bb * 32 + rl;
+      float z[4];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int cl = (ul >> 3) * 32 + g * 8 + (ul & 7);
+        z[g] = zx[i][g] + ((red[(0 * 32 + rl) * RP + cl] + red[(1 * 32 + rl) * RP + cl]) + (red[(2 * 32 + rl) * RP + cl] + red[(3 * 32 + rl) * RP + cl]));
+      }
+      gi[i] = sigmoidf_(z[0]), gf[i] = sigmoidf_(z[1]), gg[i] = tanhf(z[2]), go[i] = sigmoidf_(z[3]);
+      const float cv = gf[i] * c_reg[i] + gi[i] * gg[i];
+      c_reg[i] = cv;
+      hv[i] = go[i] * tanhf(cv);
+      const unsigned bits = kept ? f32_to_bf16_bits(hv[i]) : 0u;  // (the padding units store their zero)
+      // (a wavefront's store is one whole line of the block; rows beyond the batch are stored like any other)
+      const unsigned other = (unsigned)__shfl_xor((int)bits, 1, 64);
+      if (!(ul & 1)) __hip_atomic_store(mine + (rl * UW + ul) / 2, bits | (other << 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (t + 1 < P.T) fetch_zx(t + 1);
+#pragma unroll
+    for (int i = 0; i < UT; ++i) {
+      const int row = bb * 32 + rb + i * (32 / UT);
+      if (row >= B) continue;
+      float* ga = P.gates + ((long)t * B + row) * 4 * H;
+      if (kept) {
+        ga[u] = gi[i];
+        ga[H + u] = gf[i];
+        ga[2 * H + u] = gg[i];
+        ga[3 * H + u] = go[i];
+        P.c[((long)t * B + row) * H + u] = c_reg[i];
+        P.h[((long)t * B + row) * H + u] = f32_to_bf16_bits(hv[i]);
+      }
+      for (int uz = z_lo; uz < z_hi; ++uz) {
+        if (uz == u) continue;
+        ga[uz] = ga[H + uz] = ga[2 * H + uz] = ga[3 * H + uz] = 0.0f;
+        P.c[((long)t * B + row) * H + uz] = 0.0f;
+        P.h[((long)t * B + row) * H + uz] = 0;
+      }
+    }
+  }
+}
+
+// Workgroup (s, bb): 16 kept units, batch rows 16 bb .. 16 bb + 15.  KW: 32-wide slices of the contraction per wavefront.
+template <int KW>
+__global__ __launch_bounds__(512) void lstm_staged_bwd_kernel(const LstmPersistBwd P) {
+  constexpr int BLK = 4 * 16 * 16 * 2;  // bytes a workgroup writes in a step, [4 gates][16 rows][16 units]
+  extern __shared__ uint4 lp_lds[];
+  __shared__ int go_s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int s, bb;
+  if (!lp_place(P.S, P.S * ((P.B + 15) / 16), s, bb)) return;
+  const int Hp = P.Hp, B = P.B, H = P.H, K = 4 * Hp;
+  char* const stage = reinterpret_cast<char*>(lp_lds);                    // [4 KW] KB: blocks of the unit slices in order
+  float* const red = reinterpret_cast<float*>(stage + 4096 * KW + 1024);  // [4][16][17]
+  char* const ex = P.ex + (long)bb * P.S * BLK;  // this batch block's blocks of step 0
+  const long ex_step = (long)((B + 15) / 16) * P.S * BLK;
+  // This workgroup's 16 columns of Wh', [unit][gate row], pass through LDS once (a row of Wh' is read in 16-byte
+  // pieces of 8 units) and stay in registers.
+  const int pitch = K * 2 + 64;  // (16 of them: at most 4096 KW + 1024 bytes)
+  for (int i = tid; i < K * 2; i += 512) {
+    const int k = i >> 1, x0 = (i & 1) * 8, jj = s * 16 + x0;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (jj < Hp) v = *reinterpret_cast<const uint4*>(P.Wh + (long)k * Hp + jj);
+    const unsigned w4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) *reinterpret_cast<uint16_t*>(stage + (x0 + e) * pitch + k * 2) = (uint16_t)(w4[e >> 1] >> ((e & 1) * 16));
+  }
+  if (tid == 0) go_s = 1;
+  lp_barrier();
+  const int kgrp = lane >> 4, n = lane & 15;
+  // slice q of the contraction: units 16 (q / 2) + 8 (kgrp % 2) ... of gate 2 (q % 2) + kgrp / 2 (the order of the blocks)
+  bf16x8_t wf[KW];
+  if (wave < 4)
+#pragma unroll
+    for (int i = 0; i < KW; ++i) {
+      const int q = wave * KW + i, unit = (q >> 1) * 16 + (kgrp & 1) * 8;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (unit < Hp) v = *reinterpret_cast<const uint4*>(stage + n * pitch + ((2 * (q & 1) + (kgrp >> 1)) * Hp + unit) * 2);
+      wf[i] = __builtin_bit_cast(bf16x8_t, v);
+    }
+  lp_barrier();
+  if (wave >= 4) {
+    const int w = wave - 4;
+    const unsigned total = (unsigned)(P.S * BLK);
+    unsigned at[KW], peek[1];
+#pragma unroll
+    for (int i = 0; i < KW; ++i) {
+      const unsigned o = (unsigned)((w * KW + i) * 1024 + lane * 16);
+      at[i] = o < total ? o : (unsigned)(lane * 16);  // (beyond the last slice: multiplied by zero weights)
+    }
+    {
+      const unsigned o = (unsigned)(w * KW * 1024 + (lane * BLK < KW * 1024 ? lane : 0) * BLK);
+      peek[0] = (o < total ? o : 0u) + BLK - 128;
+    }
+    for (int tt = 0; tt < P.T; ++tt) {
+      if (tt > 0 && !lp_fetch(ex + (tt - 1) * ex_step, total, at, peek, stage + w * KW * 1024, lane, P.spin_limit, P.err)) go_s = 0;
+      lp_barrier();
+      if (!go_s) return;
+      lp_barrier();
+    }
+    return;
+  }
+  // cell: thread = (row tid / 16, local unit tid % 16)
+  const int ul = tid & 15, rl = tid >> 4, row = bb * 16 + rl;
+  const int j = s * 16 + ul;  // compact unit
+  const bool kept = j < P.Hk && row < B, in_store = j < Hp && row < B;
+  const int u = kept ? P.off + j * P.step : 0, rc = imin(row, B - 1);  // physical unit
+  float dc_next = 0.0f;
+  // what the cell of step t needs of the forward pass, fetched a step ahead
+  float ni, nf, ng, no, nc, np, nd;
+  auto fetch_cell = [&](int t) {
+    const long at = (long)t * B + rc;
+    const float* ga = P.gates + at * 4 * H;
+    ni = ga[u], nf = ga[H + u], ng = ga[2 * H + u], no = ga[3 * H + u];
+    nc = P.c[at * H + u];
+    np = P.c[(at - (t > 0 ? B : 0)) * H + u];
+    nd = bf16_bits_to_f32(P.dh[at * H + u]);
+  };
+  fetch_cell(P.T - 1);
+  for (int tt = 0; tt < P.T; ++tt) {
+    const int t = P.T - 1 - tt;
+    lp_barrier();
+    if (!go_s) return;
+    f32x4_t acc[2];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[0][v] = acc[1][v] = 0.0f;
+    if (tt > 0) {
+      const char* mine = stage + wave * KW * 1024 + (kgrp >> 1) * 512 + n * 32 + (kgrp & 1) * 16;
+#pragma unroll
+      for (int i = 0; i < KW; ++i) {
+        const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(mine + i * 1024);
+        acc[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wf[i], acc[i & 1], 0, 0, 0);
+      }
+    }
+    // partial tiles -> LDS: lane holds column (lane & 15), rows 4*(lane>>4) + v
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[(wave * 16 + 4 * kgrp + v) * 17 + n] = acc[0][v] + acc[1][v];
+    lp_barrier();
+    const float gi = ni, gf = nf, gg = ng, go = no, ct = nc, cp = t > 0 ? np : 0.0f;
+    float d[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (kept) {
+      const float dh = nd + ((red[(0 * 16 + rl) * 17 + ul] + red[(1 * 16 + rl) * 17 + ul]) + (red[(2 * 16 + rl) * 17 + ul] + red[(3 * 16 + rl) * 17 + ul]));
+      const float tc = tanhf(ct);
+      const float dc = dh * go * (1.0f - tc * tc) + dc_next;
+      d[0] = dc * gg * gi * (1.0f - gi);
+      d[1] = dc * cp * gf * (1.0f - gf);
+      d[2] = dc * gi * (1.0f - gg * gg);
+      d[3] = dh * tc * go * (1.0f - go);
+      dc_next = dc * gf;
+    }
+    // dG_t to the other workgroups (a wavefront's store is one whole line of the block), then as the pass's result;
+    // padding units and rows store zeros
+    unsigned* const mine = reinterpret_cast<unsigned*>(ex + tt * ex_step + s * BLK);
+    unsigned word[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const unsigned bits = f32_to_bf16_bits(d[g]);
+      word[g] = bits | ((unsigned)__shfl_xor((int)bits, 1, 64) << 16);
+      if (!(ul & 1)) __hip_atomic_store(mine + ((g * 16 + rl) * 16 + ul) / 2, word[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (t > 0) fetch_cell(t - 1);
+    if (!(ul & 1) && in_store)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) *reinterpret_cast<unsigned*>(P.dG + ((long)t * B + row) * K + g * Hp + j) = word[g];
+  }
 }
 
 static int lstm_cu_count() {
@@ -611,6 +1094,7 @@ struct LstmWs {
   char* whc;     // [4Hp x Hp] dtype
   char* hc;      // [T*B x Hp] dtype
   char* big;     // fwd: Gx [T*B x 4Hp] fp32; bwd: dG [T*B x 4Hp] dtype
+  char* ex;      // (second half of big) bwd, bf16: blocks exchanged by the workgroups of the recurrence
   float* dh_next;  // [B x Hp]
   float* dc_next;  // [B x H]
   char* dwx;     // [4Hp x Ip] dtype
@@ -636,8 +1120,11 @@ static LstmWs lstm_ws_layout(char* base, int es, int T, int B, int I, int H, int
   w.xp = (int)Ip != I ? take((size_t)T * B * Ip * es) : nullptr;
   w.dxp = (int)Ip != I ? take((size_t)T * B * Ip * es) : nullptr;
   w.whc = take(4 * Hp * Hp * es);
-  w.hc = take((size_t)T * B * Hp * es);
-  w.big = take((size_t)T * B * 4 * Hp * 4);
+  // (exchange blocks of the recurrences: whole blocks of 32 or 16 rows and 16 units)
+  const size_t B32 = ((size_t)B + 31) / 32 * 32, B16 = ((size_t)B + 15) / 16 * 16, H16 = (Hp + 15) / 16 * 16;
+  w.hc = take((size_t)T * B32 * H16 * es);
+  w.big = take((size_t)T * B16 * 4 * H16 * 4);
+  w.ex = w.big ? w.big + (size_t)T * B16 * 4 * H16 * 2 : nullptr;
   w.dh_next = (float*)take((size_t)B * Hp * 4);
   w.dc_next = (float*)take((size_t)B * H * 4);
   w.dwx = take(4 * Hp * Ip * es);
@@ -741,6 +1228,29 @@ static int32_t lstm_padded_x(const LstmArgs& a, const void* x, const LstmWs& w, 
   return ARD_OK;
 }
 
+static int32_t lstm_mark(void* buf, long bytes, int* sync, int n_sync, hipStream_t stream) {
+  const long n16 = bytes / 16;  // (rows are whole 16-byte pieces)
+  const long blocks = (n16 > n_sync ? n16 : n_sync) / 256 + 1;
+  ARD_LAUNCH(lstm_mark_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, stream, (uint4*)buf, n16, sync, n_sync);
+  ARD_LAUNCH_CHECK("lstm_mark_kernel");
+  return ARD_OK;
+}
+
+// The recurrences with staging wavefronts: kept units per workgroup (0: not taken).  One workgroup per CU, and as many
+// of them as there are: narrow slices first.
+static int lstm_staged_fwd_units(const LstmArgs& a) {
+  const int Hp = pad8(a.Hk);
+  if (a.dtype != ARD_BF16 || a.Hk <= 0 || a.T <= 1 || a.ax.kind != AX_AFFINE || getenv("ARD_NO_PERSIST") || Hp > 1024) return 0;
+  for (int uw : {8, 16})
+    if ((long)ceil_div(Hp, uw) * ceil_div(a.B, 32) <= lstm_cu_count()) return uw;
+  return 0;
+}
+static bool lstm_staged_bwd(const LstmArgs& a) {
+  const int Hp = pad8(a.Hk);
+  return a.dtype == ARD_BF16 && a.Hk > 0 && a.T > 1 && a.ax.kind == AX_AFFINE && !getenv("ARD_NO_PERSIST") && Hp <= 1024 &&
+         (long)ceil_div(Hp, 16) * ceil_div(a.B, 16) <= lstm_cu_count();
+}
+
 // Does the forward pass of this layer run its recurrence in one launch, and how?  (bf16, affine pattern,
 // at most one workgroup per CU, bounded exchange traffic)
 struct PersistPlan {
@@ -758,7 +1268,6 @@ static bool lstm_persist_plan(const LstmArgs& a, PersistPlan& p) {
     if ((long)p.S * ceil_div(a.B, 32 * cand) <= cus) p.tmb = cand;
   if (!p.tmb) return false;
   p.nbb = ceil_div(a.B, 32 * p.tmb);
-  p.lds = (size_t)32 * (Hp * 2 + 16) + (size_t)4 * 32 * p.tmb * 33 * 4;
   // Every unit slice reads the whole h_{t-1} of its batch rows: S * B * Hp * 2 bytes per step over the chip.
   // Device-scope loads fetch each copy from the memory side: best while that volume is small (B = 128,
   // 512 kept units: 8 MB, 6.5 us per step against 12.6 for two launches per step), 15 us per step at 33 MB
@@ -769,6 +1278,7 @@ static bool lstm_persist_plan(const LstmArgs& a, PersistPlan& p) {
   const long traffic = (long)p.S * a.B * Hp * 2;
   p.via_l2 = traffic > (12L << 20);
   const bool traffic_ok = traffic <= (40L << 20);
+  p.lds = (size_t)32 * (Hp * 2 + 16) + (size_t)4 * 32 * p.tmb * 33 * 4 * (p.tmb == 1 ? 2 : 1);
   return traffic_ok && p.lds <= 160 * 1024 - 1024;
 }
 
@@ -787,7 +1297,7 @@ static bool lstm_persist_bwd_plan(const LstmArgs& a, PersistBwdPlan& p) {
   // a launch per step 15.5.
   for (int tm = 1; tm <= 4; tm *= 2)
     for (int uw = 16; uw <= 32; uw *= 2) {
-      const size_t lds = (size_t)uw * (8 * Hp + 64) + (size_t)4 * 16 * tm * (uw + 1) * 4;
+      const size_t lds = (size_t)uw * (8 * Hp + 64) + (size_t)4 * 16 * tm * (uw + 1) * 4 * 2;
       const int S = ceil_div(Hp, uw), nbb = ceil_div(a.B, 16 * tm);
       if (lds > 160 * 1024 - 1024 || (long)S * nbb > cus) continue;
       const long traffic = (long)S * a.B * 4 * Hp * 2;
@@ -817,6 +1327,27 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     if (st) return st;
   }
   // the whole recurrence in one launch when all of its workgroups fit on the chip together
+  const int staged = std::is_same<T, uint16_t>::value ? lstm_staged_fwd_units(a) : 0;
+  if (staged) {
+    const int S = ceil_div(Hp, staged), kw = (int)align_up((size_t)ceil_div(Hp, 64), 4);
+    const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
+    LstmPersist P{Gx, (const uint16_t*)w.whc, (uint16_t*)w.hc, (uint16_t*)h, c, gates, w.sync + 1, w.sync, T_, B, H, Hk, Hp, S,
+                  a.ax.off, a.ax.step, spin_limit};
+    if (int32_t e = lstm_mark(w.hc, (long)(T_ - 1) * ceil_div(B, 32) * S * 64 * staged, w.sync, 1, stream)) return e;
+    const size_t lds = (size_t)4096 * kw + (size_t)4 * 32 * (4 * staged + 1) * 4;
+    auto launch = [&](auto kernel) -> int32_t {
+      if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
+      ARD_LAUNCH_NAMED("lstm_staged_fwd_kernel", kernel, dim3((unsigned)(ceil_div(S * ceil_div(B, 32), 8) * 8)), dim3(512), lds, stream, P);
+      return ARD_OK;
+    };
+    if (staged == 8) st = kw == 4 ? launch(lstm_staged_fwd_kernel<1, 4>) : kw == 8 ? launch(lstm_staged_fwd_kernel<1, 8>)
+                          : kw == 12 ? launch(lstm_staged_fwd_kernel<1, 12>) : launch(lstm_staged_fwd_kernel<1, 16>);
+    else st = kw == 4 ? launch(lstm_staged_fwd_kernel<2, 4>) : kw == 8 ? launch(lstm_staged_fwd_kernel<2, 8>)
+              : kw == 12 ? launch(lstm_staged_fwd_kernel<2, 12>) : launch(lstm_staged_fwd_kernel<2, 16>);
+    if (st) return st;
+    ARD_LAUNCH_CHECK("lstm_staged_fwd_kernel");
+    return ARD_OK;
+  }
   PersistPlan pp;
   if (std::is_same<T, uint16_t>::value && lstm_persist_plan(a, pp)) {
     const int S = pp.S, nbb = pp.nbb, tmb = pp.tmb;
@@ -826,18 +1357,18 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersist P{Gx, (const uint16_t*)w.whc, (uint16_t*)w.hc, (uint16_t*)h, c, gates, w.sync + 1, w.sync, T_, B, H, Hk, Hp, S,
                   a.ax.off, a.ax.step, spin_limit};
-    ARD_LAUNCH(lstm_zero_ints_kernel, dim3(ceil_div(S * nbb + 1, 256)), dim3(256), 0, stream, w.sync, S * nbb + 1);
-    ARD_LAUNCH_CHECK("lstm_zero_ints_kernel");
+    if (int32_t e = lstm_mark(w.hc, pp.via_l2 ? 0 : (long)(T_ - 1) * B * Hp * 2, w.sync, S * nbb + 1, stream)) return e;
     const dim3 grid((unsigned)(S * nbb));
     auto launch = [&](auto kernel) -> int32_t {
       if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
       ARD_LAUNCH_NAMED("lstm_persist_fwd_kernel", kernel, grid, dim3(256), lds, stream, P);
       return ARD_OK;
     };
-    if (pp.via_l2) st = tmb == 1 ? launch(lstm_persist_fwd_kernel<1, true>) : tmb == 2 ? launch(lstm_persist_fwd_kernel<2, true>)
-                                                                                          : launch(lstm_persist_fwd_kernel<4, true>);
-    else st = tmb == 1 ? launch(lstm_persist_fwd_kernel<1, false>) : tmb == 2 ? launch(lstm_persist_fwd_kernel<2, false>)
-                                                                               : launch(lstm_persist_fwd_kernel<4, false>);
+    const bool deep = Hp > 512;  // (slices of a wavefront: one round trip for up to 1024 kept units)
+    if (pp.via_l2) st = tmb == 1 ? launch(lstm_persist_fwd_kernel<1, true, 8>) : tmb == 2 ? launch(lstm_persist_fwd_kernel<2, true, 8>)
+                                                                                             : launch(lstm_persist_fwd_kernel<4, true, 4>);
+    else st = tmb == 1 ? (deep ? launch(lstm_persist_fwd_kernel<1, false, 16>) : launch(lstm_persist_fwd_kernel<1, false, 8>))
+              : tmb == 2 ? launch(lstm_persist_fwd_kernel<2, false, 8>) : launch(lstm_persist_fwd_kernel<4, false, 4>);
     if (st) return st;
     ARD_LAUNCH_CHECK("lstm_persist_fwd_kernel");
     return ARD_OK;
@@ -894,13 +1425,30 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
   const float* dh_src = nullptr;  // dh_t[kept] from the product of step t+1: partial sums or w.dh_next
   int dh_splits = 0;
   PersistBwdPlan bp;
-  const bool one_launch = std::is_same<T, uint16_t>::value && lstm_persist_bwd_plan(a, bp);
-  if (one_launch) {
+  const bool staged = std::is_same<T, uint16_t>::value && lstm_staged_bwd(a);
+  const bool one_launch = staged || (std::is_same<T, uint16_t>::value && lstm_persist_bwd_plan(a, bp));
+  if (staged) {
+    const int S = ceil_div(Hp, 16), need = ceil_div(Hp, 32), kw = need <= 4 ? 4 : (int)align_up((size_t)need, 8);
+    const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
+    LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,
+                     S, 16, a.ax.off, a.ax.step, spin_limit, w.ex};
+    if (int32_t e = lstm_mark(w.ex, (long)(T_ - 1) * ceil_div(B, 16) * S * 2048, w.sync, 1, stream)) return e;
+    const size_t lds = (size_t)4096 * kw + 1024 + (size_t)4 * 16 * 17 * 4;
+    auto launch = [&](auto kernel) -> int32_t {
+      if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
+      ARD_LAUNCH_NAMED("lstm_staged_bwd_kernel", kernel, dim3((unsigned)(ceil_div(S * ceil_div(B, 16), 8) * 8)), dim3(512), lds, stream, P);
+      return ARD_OK;
+    };
+    st = kw == 4 ? launch(lstm_staged_bwd_kernel<4>) : kw == 8 ? launch(lstm_staged_bwd_kernel<8>)
+         : kw == 16 ? launch(lstm_staged_bwd_kernel<16>) : kw == 24 ? launch(lstm_staged_bwd_kernel<24>) : launch(lstm_staged_bwd_kernel<32>);
+    if (st) return st;
+    ARD_LAUNCH_CHECK("lstm_staged_bwd_kernel");
+  } else if (one_launch) {
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,
                      bp.S, bp.UW, a.ax.off, a.ax.step, spin_limit};
-    ARD_LAUNCH(lstm_zero_ints_kernel, dim3(ceil_div(bp.S * bp.nbb + 1, 256)), dim3(256), 0, stream, w.sync, bp.S * bp.nbb + 1);
-    ARD_LAUNCH_CHECK("lstm_zero_ints_kernel");
+    const long first = (long)B * 4 * Hp * 2;  // (the last step's dG is waited for by nobody)
+    if (int32_t e = lstm_mark((char*)dG + first, bp.via_l2 ? 0 : (T_ - 1) * first, w.sync, bp.S * bp.nbb + 1, stream)) return e;
     const dim3 grid((unsigned)(bp.S * bp.nbb));
     const size_t lds = bp.lds;
     auto launch = [&](auto kernel) -> int32_t {
@@ -908,10 +1456,11 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
       ARD_LAUNCH_NAMED("lstm_persist_bwd_kernel", kernel, grid, dim3(256), lds, stream, P);
       return ARD_OK;
     };
-    if (bp.via_l2) st = bp.tm16 == 1 ? launch(lstm_persist_bwd_kernel<1, true>) : bp.tm16 == 2 ? launch(lstm_persist_bwd_kernel<2, true>)
-                                                                                              : launch(lstm_persist_bwd_kernel<4, true>);
-    else st = bp.tm16 == 1 ? launch(lstm_persist_bwd_kernel<1, false>) : bp.tm16 == 2 ? launch(lstm_persist_bwd_kernel<2, false>)
-                                                                                    : launch(lstm_persist_bwd_kernel<4, false>);
+    const bool deep = Hp > 512;  // (slices of a wavefront: one round trip for up to 1024 kept units)
+    if (bp.via_l2) st = bp.tm16 == 1 ? launch(lstm_persist_bwd_kernel<1, true, 16>) : bp.tm16 == 2 ? launch(lstm_persist_bwd_kernel<2, true, 8>)
+                                                                                                 : launch(lstm_persist_bwd_kernel<4, true, 4>);
+    else st = bp.tm16 == 1 ? (deep ? launch(lstm_persist_bwd_kernel<1, false, 32>) : launch(lstm_persist_bwd_kernel<1, false, 16>))
+              : bp.tm16 == 2 ? launch(lstm_persist_bwd_kernel<2, false, 8>) : launch(lstm_persist_bwd_kernel<4, false, 4>);
     if (st) return st;
     ARD_LAUNCH_CHECK("lstm_persist_bwd_kernel");
   }
@@ -989,7 +1538,7 @@ extern "C" size_t ard_lstm_workspace_bytes(int32_t dtype, int32_t T, int32_t B, 
 extern "C" size_t ard_lstm_status_offset(int32_t dtype, int32_t T, int32_t B, int32_t I, int32_t H, const ard_pattern* pat) {
   LstmArgs a{dtype, T, B, I, H, 0, 0, Axis{}, LstmTiles{}};
   PersistPlan pp;
-  if (lstm_check(a, pat) || !lstm_persist_plan(a, pp)) return (size_t)-1;
+  if (lstm_check(a, pat) || (!lstm_staged_fwd_units(a) && !lstm_persist_plan(a, pp))) return (size_t)-1;
   const LstmWs w = lstm_ws_layout((char*)nullptr + 256, a.es, T, B, I, H, a.Hk);
   return (size_t)((char*)w.sync - ((char*)nullptr + 256));
 }
