@@ -22,13 +22,6 @@
 
 namespace ard {
 
-// rank[u] = compact index of unit u or -1
-__global__ __launch_bounds__(1024) void lstm_setup_kernel(Axis ax, int H, int* rank) {
-  for (int u = threadIdx.x; u < H; u += 1024) rank[u] = -1;
-  __syncthreads();
-  for (int j = threadIdx.x; j < ax.n; j += 1024) rank[ax_phys(ax, j)] = j;
-}
-
 // Tile pattern over the fused weight W[4H x (I+H)] (Section 3.2): the synapse at (row, col) lies in tile
 // (row / tr, col / tc), tiles are numbered row-major over a grid of `tcols` tile columns, and tile number
 // t (0-based) is kept iff (t - o) mod dp == 0 (o = b - 1).  dp == 0: no tile pattern.
@@ -41,35 +34,123 @@ __device__ __forceinline__ bool lstm_synapse_kept(const LstmTiles& tp, int row, 
   return t % tp.dp == 0;  // (sign of t is irrelevant for == 0)
 }
 
-// out[g*Hp + j][q] = W[(g*H + unit(j)) * ldw + col(q)] for kept j, 0 at the padding and for synapses of
-// dropped tiles.
-// cols == 0: the input columns, q < ncol identity; cols == 1: the recurrent columns,
-// q < Hp -> I + unit(q) (0 at the padding); out has `ldo` columns.
-template <typename T>
-__global__ void lstm_gather_w_kernel(const T* W, long ldw, Axis ax, int H, int I, int Hp, int recurrent, int ldo,
-                                     LstmTiles tp, T* out) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = blockIdx.y;  // compact gate row
-  if (q >= ldo) return;
-  const int g = r / Hp, j = r - g * Hp;
-  T v = (T)0;
-  if (j < ax.n) {
-    const int prow = g * H + ax_phys(ax, j);
-    const long row = (long)prow * ldw;
-    int col = -1;
-    if (!recurrent) col = q < I ? q : -1;
-    else if (q < ax.n) col = I + ax_phys(ax, q);
-    if (col >= 0 && lstm_synapse_kept(tp, prow, col)) v = W[row + col];
+// Eight consecutive elements from an address of any alignment, and the other way round
+template <typename T> __device__ __forceinline__ void lstm_load8(const T* p, T (&v)[8]) {
+  if ((((uintptr_t)p) & 15) == 0) {
+#pragma unroll
+    for (int i = 0; i < (int)sizeof(T) / 2; ++i) reinterpret_cast<uint4*>(v)[i] = reinterpret_cast<const uint4*>(p)[i];
+  } else if ((((uintptr_t)p) & 3) == 0) {
+#pragma unroll
+    for (int i = 0; i < 2 * (int)sizeof(T); ++i) reinterpret_cast<uint32_t*>(v)[i] = reinterpret_cast<const uint32_t*>(p)[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = p[i];
   }
-  out[(long)r * ldo + q] = v;
+}
+template <typename T> __device__ __forceinline__ void lstm_store8(T* p, const T (&v)[8], int n) {
+  if (n >= 8 && (((uintptr_t)p) & 15) == 0) {
+#pragma unroll
+    for (int i = 0; i < (int)sizeof(T) / 2; ++i) reinterpret_cast<uint4*>(p)[i] = reinterpret_cast<const uint4*>(v)[i];
+  } else if (n >= 8 && (((uintptr_t)p) & 3) == 0) {
+#pragma unroll
+    for (int i = 0; i < 2 * (int)sizeof(T); ++i) reinterpret_cast<uint32_t*>(p)[i] = reinterpret_cast<const uint32_t*>(v)[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (i < n) p[i] = v[i];
+  }
 }
 
-// out[r][j] = j < Hk ? src[r*H + unit(j)] : 0 (compact copy of stored hidden states)
-template <typename T>
-__global__ void lstm_gather_h_kernel(const T* src, int H, Axis ax, int Hp, T* out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const long r = blockIdx.y;
-  if (j < Hp) out[r * Hp + j] = j < ax.n ? src[r * H + ax_phys(ax, j)] : (T)0;
+// Everything a pass needs before its first product, in one launch (as five launches of a few microseconds each they
+// took 33 us of a layer of 1500 units): eight consecutive elements of a row per thread.
+template <typename T> struct LstmPrepare {
+  Axis ax;
+  int H, I, Ip, Hp;
+  LstmTiles tp;
+  // wxc[g*Hp + j][q] = W[(g*H + unit(j))][q], whc[g*Hp + j][q] = W[(g*H + unit(j))][I + unit(q)]; 0 at the padding and
+  // for synapses of dropped tiles
+  const T* W;
+  T *wxc, *whc;
+  const T* h;     // != NULL: hc[r][j] = h[r][unit(j)], `rows` rows
+  T* hc;
+  const T* x;     // != NULL: xp[r][q] = x[r][q], q < I, padded to Ip
+  T* xp;
+  long rows;
+  int* rank;      // rank[u] = compact index of unit u or -1
+  uint4* mark;    // exchange buffer of the recurrence: n16 pieces of kUnwritten
+  long n16;
+  int* sync;      // its status word and flags: zeros
+  int n_sync;
+  FastDiv by_cx, by_ch, by_hp;  // Ip / 8, Hp / 8, Hp
+  int b_w, b_h, b_x, b_mark;    // workgroups of each job (the rank table takes one more)
+};
+constexpr unsigned kUnwritten = 0xffffffffu;
+template <typename T> __global__ __launch_bounds__(256) void lstm_prepare_kernel(const LstmPrepare<T> P) {
+  int b = (int)blockIdx.x;
+  const int tid = threadIdx.x, cx = P.Ip >> 3, ch = P.Hp >> 3;
+  T v[8];
+  if (b < P.b_w) {
+    const uint32_t e = (uint32_t)b * 256 + tid, nx = (uint32_t)(4 * P.Hp * cx);
+    const bool rec = e >= nx;
+    const uint32_t f = rec ? e - nx : e;
+    const int r = (int)fdiv(f, rec ? P.by_ch : P.by_cx), q = ((int)f - r * (rec ? ch : cx)) * 8;
+    if (r >= 4 * P.Hp) return;
+    const int g = (int)fdiv((uint32_t)r, P.by_hp), j = r - g * P.Hp;
+    const int prow = g * P.H + (j < P.ax.n ? ax_phys(P.ax, j) : 0);
+    const T* row = P.W + (long)prow * (P.I + P.H);
+    if (!rec && q + 8 <= P.I && P.tp.dp <= 1) {
+      lstm_load8(row + q, v);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bool ok = rec ? q + i < P.ax.n : q + i < P.I;
+        const int col = ok ? (rec ? P.I + ax_phys(P.ax, q + i) : q + i) : 0;
+        v[i] = row[col];
+        if (!ok || !lstm_synapse_kept(P.tp, prow, col)) v[i] = (T)0;
+      }
+    }
+    if (j >= P.ax.n)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = (T)0;
+    return lstm_store8(rec ? P.whc + (long)r * P.Hp + q : P.wxc + (long)r * P.Ip + q, v, 8);
+  }
+  b -= P.b_w;
+  if (b < P.b_h) {
+    const uint32_t e = (uint32_t)b * 256 + tid;
+    const long r = fdiv(e, P.by_ch);
+    if (r >= P.rows) return;
+    const int j = (int)(e - (uint32_t)r * (uint32_t)ch) * 8;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      v[i] = P.h[r * P.H + (j + i < P.ax.n ? ax_phys(P.ax, j + i) : 0)];
+      if (j + i >= P.ax.n) v[i] = (T)0;
+    }
+    return lstm_store8(P.hc + r * P.Hp + j, v, 8);
+  }
+  b -= P.b_h;
+  if (b < P.b_x) {
+    const uint32_t e = (uint32_t)b * 256 + tid;
+    const long r = fdiv(e, P.by_cx);
+    if (r >= P.rows) return;
+    const int q = (int)(e - (uint32_t)r * (uint32_t)cx) * 8;
+    if (q + 8 <= P.I) {
+      lstm_load8(P.x + r * P.I + q, v);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = q + i < P.I ? P.x[r * P.I + q + i] : (T)0;
+    }
+    return lstm_store8(P.xp + r * P.Ip + q, v, 8);
+  }
+  b -= P.b_x;
+  if (b < P.b_mark) {
+    const long i0 = (long)b * 256 + tid;
+    if (i0 < P.n_sync) P.sync[i0] = 0;
+    for (long i = i0; i < P.n16; i += (long)P.b_mark * 256) P.mark[i] = make_uint4(kUnwritten, kUnwritten, kUnwritten, kUnwritten);
+    return;
+  }
+  for (int u = tid; u < P.H; u += 256) P.rank[u] = -1;
+  __syncthreads();
+  for (int j = tid; j < P.ax.n; j += 256) P.rank[ax_phys(P.ax, j)] = j;
 }
 
 __device__ __forceinline__ float sigmoidf_(float z) { return 1.0f / (1.0f + __expf(-z)); }
@@ -162,25 +243,40 @@ __global__ void lstm_copy_rows_kernel(const T* src, long ld_src, int cols, long 
 
 // dW[(g*H + u)][q] from the compact gradients dwx[4Hp x Ip] and dwh[4Hp x Hp]; +0.0 for every
 // row of a dropped unit, every recurrent column of a dropped unit and every synapse of a dropped tile.
+// Eight neighbouring columns of a row per thread (one at a time: 20 us where the bytes take 6, 512 of 1024 units).
 template <typename T>
-__global__ void lstm_scatter_dw_kernel(const T* dwx, const T* dwh, const int* rank, int H, int I, int Ip, int Hp, LstmTiles tp,
-                                       T* dW) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int p = blockIdx.y;  // physical gate row
-  if (q >= I + H) return;
-  const int g = p / H, u = p - g * H;
-  const int j = rank[u];
-  T v = (T)0;
-  if (j >= 0 && lstm_synapse_kept(tp, p, q)) {
+__global__ __launch_bounds__(256) void lstm_scatter_dw_kernel(const T* dwx, const T* dwh, const int* rank, int H, int I, int Ip, int Hp, LstmTiles tp,
+                                                              FastDiv by_chunks, FastDiv by_h, T* dW) {
+  const uint32_t e = blockIdx.x * 256u + threadIdx.x;
+  const int chunks = (I + H + 7) >> 3, p = (int)fdiv(e, by_chunks), q = (int)(e - (uint32_t)p * (uint32_t)chunks) * 8;  // p: physical gate row
+  if (p >= 4 * H) return;
+  const int g = (int)fdiv((uint32_t)p, by_h), j = rank[p - g * H], n = imin(8, I + H - q);
+  T v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = (T)0;
+  if (j >= 0) {
     const long r = (long)g * Hp + j;
-    if (q < I) {
-      v = dwx[r * Ip + q];
+    if (q + 8 <= I) {
+      lstm_load8(dwx + r * Ip + q, v);
     } else {
-      const int jv = rank[q - I];
-      if (jv >= 0) v = dwh[r * Hp + jv];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int c = q + i;
+        if (c < I) {
+          v[i] = dwx[r * Ip + c];
+        } else if (i < n) {
+          const int jv = rank[c - I];
+          v[i] = dwh[r * Hp + (jv >= 0 ? jv : 0)];
+          if (jv < 0) v[i] = (T)0;
+        }
+      }
     }
+    if (tp.dp > 1)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (!lstm_synapse_kept(tp, p, q + i)) v[i] = (T)0;
   }
-  dW[(long)p * (I + H) + q] = v;
+  lstm_store8(dW + (long)p * (I + H) + q, v, n);
 }
 
 static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -190,7 +286,6 @@ static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // with a device-scope store, and a reader takes its 16-byte pieces with device-scope loads until none holds the
 // mark.  A step is then one store on its way to memory and one load that comes after it, where separate flags took
 // four trips: the stores' acknowledgement, the flag's store, the poll and the load of the data.
-constexpr unsigned kUnwritten = 0xffffffffu;
 typedef unsigned lp_u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ bool lp_unwritten(const lp_u32x4& v) {
   return v.x == kUnwritten || v.y == kUnwritten || v.z == kUnwritten || v.w == kUnwritten;
@@ -208,13 +303,6 @@ __device__ __forceinline__ bool lp_give_up(long& spins, long limit, int* err) {
   __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
 }
-// before a recurrence: marks the exchange buffer, clears the status word and the flags
-__global__ __launch_bounds__(256) void lstm_mark_kernel(uint4* buf, long n16, int* sync, int n_sync) {
-  const long i0 = (long)blockIdx.x * 256 + threadIdx.x, step = (long)gridDim.x * 256;
-  if (i0 < n_sync) sync[i0] = 0;
-  for (long i = i0; i < n16; i += step) buf[i] = make_uint4(kUnwritten, kUnwritten, kUnwritten, kUnwritten);
-}
-
 // ---- the recurrence in one launch (Section 7.2.3) -----------------------------------------------
 //
 // The per-step products of a batch-128 LSTM are a few hundred MFLOP each: issued as launches, a step
@@ -1194,45 +1282,35 @@ static GemmParams plain_gemm(const void* A, long lda, const void* B, long ldb, v
   return P;
 }
 
+// What the recurrence of a pass wants cleared beforehand
+struct LstmMark {
+  void* buf;
+  long bytes;
+  int n_sync;
+};
+// Compact weights, padded x, (backward) compact h, rank table and marks; *xo: x with rows padded to a multiple of 8
+// elements (zeros), so that the products over it can use 16-byte loads whatever the input width.
 template <typename T>
-static int32_t lstm_prepare(const LstmArgs& a, const void* W, const LstmWs& w, hipStream_t stream) {
-  ARD_LAUNCH(lstm_setup_kernel, dim3(1), dim3(1024), 0, stream, a.ax, a.H, w.rank);
-  ARD_LAUNCH_CHECK("lstm_setup_kernel");
-  const int Hp = pad8(a.Hk);
-  if (a.Hk > 0) {
-    ARD_LAUNCH(lstm_gather_w_kernel<T>, dim3(ceil_div(pad8(a.I), 256), 4 * Hp), dim3(256), 0, stream, (const T*)W,
-                       (long)(a.I + a.H), a.ax, a.H, a.I, Hp, 0, pad8(a.I), a.tiles, (T*)w.wxc);
-    ARD_LAUNCH_CHECK("lstm_gather_w_kernel");
-    ARD_LAUNCH(lstm_gather_w_kernel<T>, dim3(ceil_div(Hp, 256), 4 * Hp), dim3(256), 0, stream, (const T*)W,
-                       (long)(a.I + a.H), a.ax, a.H, a.I, Hp, 1, Hp, a.tiles, (T*)w.whc);
-    ARD_LAUNCH_CHECK("lstm_gather_w_kernel");
-  }
-  return ARD_OK;
-}
-
-// x with rows padded to a multiple of 8 elements (zeros), so that the products over it can use 16-byte
-// loads whatever the input width; returns x itself when no padding is needed
-template <typename T>
-static int32_t lstm_padded_x(const LstmArgs& a, const void* x, const LstmWs& w, hipStream_t stream, const void** xo) {
-  const int Ip = pad8(a.I);
-  *xo = x;
-  if (Ip == a.I) return ARD_OK;
-  const long rows_total = (long)a.T * a.B;
-  for (long r0 = 0; r0 < rows_total; r0 += 65535) {
-    const long rows = rows_total - r0 < 65535 ? rows_total - r0 : 65535;
-    ARD_LAUNCH(lstm_gather_h_kernel<T>, dim3(ceil_div(Ip, 256), (unsigned)rows), dim3(256), 0, stream,
-                       (const T*)x + r0 * a.I, a.I, axis_identity(a.I), Ip, (T*)w.xp + r0 * Ip);
-    ARD_LAUNCH_CHECK("lstm_gather_h_kernel");
-  }
-  *xo = w.xp;
-  return ARD_OK;
-}
-
-static int32_t lstm_mark(void* buf, long bytes, int* sync, int n_sync, hipStream_t stream) {
-  const long n16 = bytes / 16;  // (rows are whole 16-byte pieces)
-  const long blocks = (n16 > n_sync ? n16 : n_sync) / 256 + 1;
-  ARD_LAUNCH(lstm_mark_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, stream, (uint4*)buf, n16, sync, n_sync);
-  ARD_LAUNCH_CHECK("lstm_mark_kernel");
+static int32_t lstm_prepare(const LstmArgs& a, const void* W, const void* x, const void* h, const LstmMark& m, const LstmWs& w, hipStream_t stream,
+                            const void** xo) {
+  LstmPrepare<T> P{};
+  P.ax = a.ax, P.H = a.H, P.I = a.I, P.Ip = pad8(a.I), P.Hp = pad8(a.Hk), P.tp = a.tiles;
+  P.W = (const T*)W, P.wxc = (T*)w.wxc, P.whc = (T*)w.whc;
+  P.h = (const T*)h, P.hc = (T*)w.hc;
+  P.rows = (long)a.T * a.B;
+  const bool pad = P.Ip != a.I;
+  P.x = (const T*)x, P.xp = (T*)w.xp;
+  *xo = pad ? (const void*)w.xp : x;
+  P.rank = w.rank;
+  P.mark = (uint4*)m.buf, P.n16 = m.bytes / 16, P.sync = w.sync, P.n_sync = m.n_sync;  // (exchange rows are whole pieces)
+  P.by_cx = fast_div((uint32_t)P.Ip / 8), P.by_ch = fast_div((uint32_t)P.Hp / 8), P.by_hp = fast_div((uint32_t)P.Hp);
+  const long nw = a.Hk > 0 ? 4L * P.Hp * (P.Ip + P.Hp) / 8 : 0, nh = h && a.Hk > 0 ? P.rows * P.Hp / 8 : 0, nx = pad && a.Hk > 0 ? P.rows * P.Ip / 8 : 0;
+  if (nw >= (1L << 31) || nh >= (1L << 31) || nx >= (1L << 31)) return fail(ARD_ESHAPE, "LSTM operands too large");
+  P.b_w = (int)((nw + 255) / 256), P.b_h = (int)((nh + 255) / 256), P.b_x = (int)((nx + 255) / 256);
+  const long blocks = P.n16 || P.n_sync ? (P.n16 > P.n_sync ? P.n16 : P.n_sync) / 256 + 1 : 0;
+  P.b_mark = (int)(blocks < 2048 ? blocks : 2048);
+  ARD_LAUNCH(lstm_prepare_kernel<T>, dim3((unsigned)(P.b_w + P.b_h + P.b_x + P.b_mark + 1)), dim3(256), 0, stream, P);
+  ARD_LAUNCH_CHECK("lstm_prepare_kernel");
   return ARD_OK;
 }
 
@@ -1313,27 +1391,29 @@ template <typename T>
 static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void* h, float* c, float* gates,
                           const LstmWs& w, hipStream_t stream) {
   const int T_ = a.T, B = a.B, I = a.I, H = a.H, Hk = a.Hk, Hp = pad8(Hk), ce = 16 / a.es;
-  int32_t st = lstm_prepare<T>(a, W, w, stream);
+  // the whole recurrence in one launch when all of its workgroups fit on the chip together
+  const int staged = std::is_same<T, uint16_t>::value ? lstm_staged_fwd_units(a) : 0;
+  PersistPlan pp;
+  const bool persist = !staged && std::is_same<T, uint16_t>::value && lstm_persist_plan(a, pp);
+  LstmMark mark{};
+  if (staged) mark = LstmMark{w.hc, (long)(T_ - 1) * ceil_div(B, 32) * ceil_div(Hp, staged) * 64 * staged, 1};
+  else if (persist) mark = LstmMark{w.hc, pp.via_l2 ? 0 : (long)(T_ - 1) * B * Hp * 2, pp.S * pp.nbb + 1};
+  const void* xs;
+  int32_t st = lstm_prepare<T>(a, W, x, nullptr, mark, w, stream, &xs);
   if (st) return st;
   float* Gx = (float*)w.big;
   const int Ip = pad8(I);
   if (Hk > 0) {
     // input projection of every step: Gx[T*B x 4Hp] = x . Wx'^T
-    const void* xs;
-    st = lstm_padded_x<T>(a, x, w, stream, &xs);
-    if (st) return st;
     GemmParams P = plain_gemm(xs, Ip, w.wxc, Ip, Gx, 4 * Hp, T_ * B, 4 * Hp, Ip, true, true, ce, true, 0.0f);
     st = run_gemm(a.dtype, true, true, P, 0, 0, stream, w.part, w.part_bytes);
     if (st) return st;
   }
-  // the whole recurrence in one launch when all of its workgroups fit on the chip together
-  const int staged = std::is_same<T, uint16_t>::value ? lstm_staged_fwd_units(a) : 0;
   if (staged) {
     const int S = ceil_div(Hp, staged), kw = (int)align_up((size_t)ceil_div(Hp, 64), 4);
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersist P{Gx, (const uint16_t*)w.whc, (uint16_t*)w.hc, (uint16_t*)h, c, gates, w.sync + 1, w.sync, T_, B, H, Hk, Hp, S,
                   a.ax.off, a.ax.step, spin_limit};
-    if (int32_t e = lstm_mark(w.hc, (long)(T_ - 1) * ceil_div(B, 32) * S * 64 * staged, w.sync, 1, stream)) return e;
     const size_t lds = (size_t)4096 * kw + (size_t)4 * 32 * (4 * staged + 1) * 4;
     auto launch = [&](auto kernel) -> int32_t {
       if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
@@ -1348,8 +1428,7 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     ARD_LAUNCH_CHECK("lstm_staged_fwd_kernel");
     return ARD_OK;
   }
-  PersistPlan pp;
-  if (std::is_same<T, uint16_t>::value && lstm_persist_plan(a, pp)) {
+  if (persist) {
     const int S = pp.S, nbb = pp.nbb, tmb = pp.tmb;
     const size_t lds = pp.lds;
     // (ARD_LSTM_SPIN_LIMIT: test hook for the give-up path, negative = the first wait fails; a workgroup that
@@ -1357,7 +1436,6 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersist P{Gx, (const uint16_t*)w.whc, (uint16_t*)w.hc, (uint16_t*)h, c, gates, w.sync + 1, w.sync, T_, B, H, Hk, Hp, S,
                   a.ax.off, a.ax.step, spin_limit};
-    if (int32_t e = lstm_mark(w.hc, pp.via_l2 ? 0 : (long)(T_ - 1) * B * Hp * 2, w.sync, S * nbb + 1, stream)) return e;
     const dim3 grid((unsigned)(S * nbb));
     auto launch = [&](auto kernel) -> int32_t {
       if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
@@ -1406,33 +1484,30 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
                           hipStream_t stream) {
   const int T_ = a.T, B = a.B, I = a.I, H = a.H, Hk = a.Hk, Hp = pad8(Hk), ce = 16 / a.es;
   const int Ip = pad8(I);
-  int32_t st = lstm_prepare<T>(a, W, w, stream);
-  if (st) return st;
   if (Hk == 0) {
-    st = fill_matrix(a.dtype, dx, (long)T_ * B * I, 0.0f, stream);
-    if (st) return st;
+    if (int32_t st = fill_matrix(a.dtype, dx, (long)T_ * B * I, 0.0f, stream)) return st;
     return fill_matrix(a.dtype, dW, (long)4 * H * (I + H), 0.0f, stream);
   }
-  // compact copy of the stored hidden states: hc[T*B x Hp] = h[:, kept]
-  for (long r0 = 0; r0 < (long)T_ * B; r0 += 65535) {
-    const long rows = (long)T_ * B - r0 < 65535 ? (long)T_ * B - r0 : 65535;
-    ARD_LAUNCH(lstm_gather_h_kernel<T>, dim3(ceil_div(Hp, 256), (unsigned)rows), dim3(256), 0, stream,
-                       (const T*)h + r0 * H, H, a.ax, Hp, (T*)w.hc + r0 * Hp);
-    ARD_LAUNCH_CHECK("lstm_gather_h_kernel");
-  }
+  PersistBwdPlan bp;
+  const bool staged = std::is_same<T, uint16_t>::value && lstm_staged_bwd(a);
+  const bool one_launch = staged || (std::is_same<T, uint16_t>::value && lstm_persist_bwd_plan(a, bp));
+  const long step_bytes = (long)B * 4 * Hp * 2;
+  LstmMark mark{};  // (dG_0 is waited for by nobody)
+  if (staged) mark = LstmMark{w.ex, (long)(T_ - 1) * ceil_div(B, 16) * ceil_div(Hp, 16) * 2048, 1};
+  else if (one_launch) mark = LstmMark{w.big + step_bytes, bp.via_l2 ? 0 : (T_ - 1) * step_bytes, bp.S * bp.nbb + 1};
+  // (hc: compact copy of the stored hidden states, h[:, kept])
+  const void* xs;
+  int32_t st = lstm_prepare<T>(a, W, x, h, mark, w, stream, &xs);
+  if (st) return st;
   T* dG = (T*)w.big;
   dim3 cgrid(ceil_div(H + (Hp - Hk), 256), B);
   const float* dh_src = nullptr;  // dh_t[kept] from the product of step t+1: partial sums or w.dh_next
   int dh_splits = 0;
-  PersistBwdPlan bp;
-  const bool staged = std::is_same<T, uint16_t>::value && lstm_staged_bwd(a);
-  const bool one_launch = staged || (std::is_same<T, uint16_t>::value && lstm_persist_bwd_plan(a, bp));
   if (staged) {
     const int S = ceil_div(Hp, 16), need = ceil_div(Hp, 32), kw = need <= 4 ? 4 : (int)align_up((size_t)need, 8);
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,
                      S, 16, a.ax.off, a.ax.step, spin_limit, w.ex};
-    if (int32_t e = lstm_mark(w.ex, (long)(T_ - 1) * ceil_div(B, 16) * S * 2048, w.sync, 1, stream)) return e;
     const size_t lds = (size_t)4096 * kw + 1024 + (size_t)4 * 16 * 17 * 4;
     auto launch = [&](auto kernel) -> int32_t {
       if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
@@ -1447,8 +1522,6 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,
                      bp.S, bp.UW, a.ax.off, a.ax.step, spin_limit};
-    const long first = (long)B * 4 * Hp * 2;  // (the last step's dG is waited for by nobody)
-    if (int32_t e = lstm_mark((char*)dG + first, bp.via_l2 ? 0 : (T_ - 1) * first, w.sync, bp.S * bp.nbb + 1, stream)) return e;
     const dim3 grid((unsigned)(bp.S * bp.nbb));
     const size_t lds = bp.lds;
     auto launch = [&](auto kernel) -> int32_t {
@@ -1503,9 +1576,6 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
   }
   {
     // compact weight gradients: dwx[4Hp x I] = dG^T . x, dwh[4Hp x Hp] = dG[1:]^T . h[kept][:-1]
-    const void* xs;
-    st = lstm_padded_x<T>(a, x, w, stream, &xs);
-    if (st) return st;
     GemmParams P = plain_gemm(dG, 4 * Hp, xs, Ip, w.dwx, Ip, 4 * Hp, Ip, T_ * B, false, false, ce, false, 0.0f);
     st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part, w.part_bytes);
     if (st) return st;
@@ -1518,8 +1588,10 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     }
     if (st) return st;
   }
-  ARD_LAUNCH(lstm_scatter_dw_kernel<T>, dim3(ceil_div(I + H, 256), 4 * H), dim3(256), 0, stream, (const T*)w.dwx,
-                     (const T*)w.dwh, (const int*)w.rank, H, I, Ip, Hp, a.tiles, (T*)dW);
+  const int chunks = (I + H + 7) / 8;
+  if (4L * H * chunks >= (1L << 31)) return fail(ARD_ESHAPE, "weight gradient too large for one pass");
+  ARD_LAUNCH(lstm_scatter_dw_kernel<T>, dim3((unsigned)((4L * H * chunks + 255) / 256)), dim3(256), 0, stream, (const T*)w.dwx, (const T*)w.dwh,
+             (const int*)w.rank, H, I, Ip, Hp, a.tiles, fast_div((uint32_t)chunks), fast_div((uint32_t)H), (T*)dW);
   ARD_LAUNCH_CHECK("lstm_scatter_dw_kernel");
   return ARD_OK;
 }
