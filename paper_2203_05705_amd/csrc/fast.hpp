@@ -88,6 +88,12 @@ struct ListMap {
   const int* cnt;
 };
 
+// Dropped tiles of a tile-masked output (MODE 0, weight gradient): zeroed by the last `blocks` workgroups of the launch
+struct ZeroTilesJob {
+  int blocks, rows, cols, TC, dp, o;
+  FastDiv by_tr, by_tc, by_chunks;  // tile rows, tile columns / 8, cols / 8
+};
+
 // (What every launch reads comes first and is fetched in one go, see touch_args; the class tables come last.)
 struct FastParams {
   const uint16_t* A;
@@ -115,7 +121,10 @@ struct FastParams {
   const int* kb_list;
   const int* kb_cnt;
   int kb_stride;
-  ConvMap cv;  // MODE 1 / 2 / 3 of the kernel only
+  union {
+    ConvMap cv;  // MODE 1 / 2 / 3 of the kernel only
+    ZeroTilesJob zt;
+  };
   long a_elems, b_elems;  // elements the caller owns behind A / B: what the loaders may touch (host-side proof)
   union {
     ClassTab tab;
@@ -1171,9 +1180,25 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   }
 }
 
+// 16-byte pieces of the dropped tiles, kZeroTileRows rows of the matrix per workgroup.  In the product's launch because
+// the two write different places: as a launch before it, the zeros of a 4096 x 4096 gradient took 10 us of their own.
+constexpr int kZeroTileRows = 8;
+template <int NT> __device__ __forceinline__ void zero_tiles_body(const ZeroTilesJob& z, uint16_t* C, int ld, int block) {
+  const int chunks = z.cols >> 3, r0 = block * kZeroTileRows, n = imin(kZeroTileRows, z.rows - r0) * chunks;
+  for (int i = threadIdx.x; i < n; i += NT) {
+    const int r = (int)fdiv((uint32_t)i, z.by_chunks), c = i - r * chunks;
+    const int t = (int)fdiv((uint32_t)(r0 + r), z.by_tr) * z.TC + (int)fdiv((uint32_t)c, z.by_tc);
+    if ((t + z.dp - z.o) % z.dp) *reinterpret_cast<uint4*>(C + (long)(r0 + r) * ld + c * 8) = make_uint4(0, 0, 0, 0);
+  }
+}
+
 template <bool A_KC, bool B_KC, int F_BM, int BN, int NW, int MODE = 0>
 __global__ __launch_bounds__(64 * NW) void gemm_direct_kernel(const FastParams P) {
   extern __shared__ uint4 direct_lds[];
+  if constexpr (MODE == 0 && !A_KC && !B_KC) {
+    const int z = (int)blockIdx.x - ((int)gridDim.x - P.zt.blocks);
+    if (z >= 0) return zero_tiles_body<64 * NW>(P.zt, P.C, P.ldc, z);
+  }
   direct_body<A_KC, B_KC, F_BM, BN, NW, MODE>(P, (int)blockIdx.x, direct_lds);
 }
 

@@ -138,7 +138,7 @@ static int32_t launch_direct(bool a_kc, bool b_kc, FastParams& F, int bm, int bn
   if (F.total_tiles <= 0) return ARD_OK;
   if (F.splits < 1) F.splits = 1;
   set_bands(F, direct_group_m(F.total_tiles));
-  const int grid = fast_grid(F);
+  const int grid = fast_grid(F) + (!a_kc && !b_kc ? F.zt.blocks : 0);
   if (bm == 256 && bn == 256) return launch_direct_cfg<256, 256, 8>(a_kc, b_kc, F, grid, stream);
   if (bm == 256 && bn == 128) return launch_direct_cfg<256, 128, 8>(a_kc, b_kc, F, grid, stream);
   if (bm == 128 && bn == 128) return launch_direct_cfg<128, 128, 4>(a_kc, b_kc, F, grid, stream);
@@ -527,7 +527,11 @@ static bool try_fast_tile(int op, const LayerArgs& a, const void* Ap, const void
   F.relu = relu;
   F.relu_src = (const uint16_t*)relu_src;
   F.total_tiles = total;
-  if (op == 2) {
+  // (a kernel that a grouped launch holds is issued later and without the zeros' workgroups)
+  const bool grouped = batch_open() && bn == 64 && bm <= 128;
+  if (op == 2 && !grouped && I % 8 == 0 && y % 8 == 0 && ((uintptr_t)Cp & 15) == 0) {
+    F.zt = ZeroTilesJob{ceil_div(O, kZeroTileRows), O, I, TC, dp, o, fast_div((uint32_t)x), fast_div((uint32_t)y / 8), fast_div((uint32_t)I / 8)};
+  } else if (op == 2) {
     ARD_LAUNCH(zero_dropped_tiles_kernel<uint16_t>, dim3((unsigned)(TR * TC)), dim3(256), 0, stream, (uint16_t*)Cp, I, O, I,
                        x, y, TC, dp, o);
     hipError_t e = ard::launch_status();

@@ -28,7 +28,7 @@ struct SkinnyArgs {
   const uint16_t* relu_src;
   int B, O, Kk;          // batch rows, output neurons, kept input neurons
   int ld_act, ld_dy, ld_w, ld_out;
-  int w_compact;         // W is [pad8(O) x pad8(Kk)]; else dense with columns through `ki`
+  int w_compact;         // rows of W are read as they are (compact, or every input kept); else dense with columns through `ki`
   int w_rows;            // rows of W that exist (O, or pad8(O) when compact)
   int out_cols;          // forward: columns of Y that are stored (O, or pad8(O) when compact)
   int dw_compact, I;     // weight gradient: compact output / physical inputs of the dense one
@@ -304,7 +304,9 @@ static bool try_skinny(int op, int32_t dtype, int B, int I, int O, const void* p
   a.out = (uint16_t*)out;
   if (op == 0 || op == 1) {
     a.w = (const uint16_t*)p1;
-    a.w_compact = w_c;
+    // (without a map on the inputs a dense W is read like a compact one: copied whole into the LDS of every workgroup
+    // first, its 4096 columns made the classifier's three products take 27 us)
+    a.w_compact = w_c || (ident_in && sk_aligned(p1, I));
     a.ld_w = w_c ? pad8(ai.n) : I;
     a.w_rows = w_c ? pad8(O) : O;
     if (w_c && !sk_aligned(p1, a.ld_w)) return false;
@@ -315,8 +317,8 @@ static bool try_skinny(int op, int32_t dtype, int B, int I, int O, const void* p
     a.ld_act = ld_in;
     a.ld_out = ld_o;
     a.out_cols = ld_o;
-    if (!w_c && (I > SK_MAX_COLS || (I % 8) || ((uintptr_t)p1 & 15))) return false;
-    const size_t lds = 4096 + (w_c ? 0 : (size_t)O * (pad8(ai.off + (ai.n - 1) * ai.step + 1) + 8) * 2);
+    if (!a.w_compact && (I > SK_MAX_COLS || (I % 8) || ((uintptr_t)p1 & 15))) return false;
+    const size_t lds = 4096 + (a.w_compact ? 0 : (size_t)O * (pad8(ai.off + (ai.n - 1) * ai.step + 1) + 8) * 2);
     static thread_local bool raised = false;
     if (!raised && lds > 65536) {
       hipError_t e = ard::raise_lds_limit((const void*)skinny_fwd_kernel, 4096 + 16 * (SK_MAX_COLS + 8) * 2);  // the most any qualifying layer asks for
@@ -333,8 +335,8 @@ static bool try_skinny(int op, int32_t dtype, int B, int I, int O, const void* p
     a.ld_out = ld_in;
     a.relu_src = (const uint16_t*)relu_src;
     if (ceil_div(B, SK_BD_ROWS) > 65535) return false;
-    if (!w_c && (I > SK_MAX_COLS || (I % 8) || ((uintptr_t)p1 & 15))) return false;
-    const size_t lds = SK_BD_ROWS * 64 + (w_c ? 0 : (size_t)O * (pad8(I) + 16) * 2);
+    if (!a.w_compact && (I > SK_MAX_COLS || (I % 8) || ((uintptr_t)p1 & 15))) return false;
+    const size_t lds = SK_BD_ROWS * 64 + (a.w_compact ? 0 : (size_t)O * (pad8(I) + 16) * 2);
     static thread_local bool raised_bd = false;
     if (!raised_bd && lds > 65536) {
       hipError_t e = ard::raise_lds_limit((const void*)skinny_bwd_data_kernel, SK_BD_ROWS * 64 + 16 * (SK_MAX_COLS + 16) * 2);
