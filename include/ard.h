@@ -310,6 +310,8 @@ typedef enum {
  * Any other use of the flags (fp32, stride > 1, n_keep = 0, SELECT) is refused.
  */
 enum { ARD_CONV_REUSE_A = 0x100, ARD_CONV_REUSE_DY = 0x200 };
+/* SELECT only: d_keep has room for all C channels, and its entries beyond the kept ones are set to -1 */
+enum { ARD_CONV_PAD_KEEP = 0x400 };
 
 size_t ard_conv_workspace_bytes(int32_t dtype, int32_t N, int32_t C, int32_t H, int32_t Wd,
                                 int32_t Cout, int32_t kh, int32_t kw, int32_t stride, int32_t pad);

@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void channel_score_kernel(const T* A, int N, i
 template <bool IN_LDS>
 __global__ __launch_bounds__(1024) void channel_select_kernel(const unsigned long long* part, int parts,
                                                              unsigned long long* score_out, int C, int n_drop, uint8_t* mask,
-                                                             int* keep, int* count) {
+                                                             int* keep, int* count, int pad_keep) {
   constexpr int STAGED = 4096;
   __shared__ unsigned long long staged[IN_LDS ? STAGED : 1];
   __shared__ int wave_tot[16];
@@ -160,6 +160,8 @@ __global__ __launch_bounds__(1024) void channel_select_kernel(const unsigned lon
     __syncthreads();
   }
   if (tid == 0 && count) *count = running_s;
+  if (pad_keep)  // (the list has room for every channel: what is not kept reads -1)
+    for (int i = running_s + tid; i < C; i += 1024) keep[i] = -1;
 }
 
 // ---- weight repacking ------------------------------------------------------------------------
@@ -1160,6 +1162,7 @@ struct ConvArgs {
   // group of `cpb` channels over its own (0: one group)
   PosListJob lists;
   int32_t cpb;
+  int32_t pad_keep;  // SELECT: ARD_CONV_PAD_KEEP
 };
 
 struct ConvWs {
@@ -1717,10 +1720,10 @@ static int32_t conv_run(const ConvArgs& a, double rate, const void* A, const voi
     const int n_drop = (int)floor(rate * (double)a.C);
     if (a.C <= 4096)
       ARD_LAUNCH(channel_select_kernel<true>, dim3(1), dim3(1024), 0, stream, (const unsigned long long*)w.score_part, parts,
-                         score, a.C, n_drop, d_mask, d_keep, d_count);
+                         score, a.C, n_drop, d_mask, d_keep, d_count, a.pad_keep);
     else
       ARD_LAUNCH(channel_select_kernel<false>, dim3(1), dim3(1024), 0, stream, (const unsigned long long*)w.score_part, parts,
-                         score, a.C, n_drop, d_mask, d_keep, d_count);
+                         score, a.C, n_drop, d_mask, d_keep, d_count, a.pad_keep);
     ARD_LAUNCH_CHECK("channel_select_kernel");
     return ARD_OK;
   }
@@ -2036,8 +2039,11 @@ extern "C" int32_t ard_fmap_drop_conv(int32_t mode, int32_t dtype, int32_t N, in
                                       uint8_t* d_mask, int32_t* d_keep, int32_t* d_count, int64_t* d_score, void* ws,
                                       size_t ws_bytes, void* stream) {
   BatchSuspend not_recorded;  // this entry point's kernels depend on each other: never part of a grouped launch
+  const int32_t pad_keep = (mode & 0xff) == ARD_CONV_SELECT && (mode & ARD_CONV_PAD_KEEP) ? 1 : 0;
+  if (pad_keep) mode &= ~ARD_CONV_PAD_KEEP;
   if (mode < 0 || (mode & ~(0xff | ARD_CONV_REUSE_A | ARD_CONV_REUSE_DY))) return fail(ARD_EINVAL, "unknown conv mode bits 0x%x", mode);
   ConvArgs a{mode & 0xff, dtype, N, C, H, Wd, Cout, kh, kw, stride, pad, n_keep, 0, 0, 0, mode & (ARD_CONV_REUSE_A | ARD_CONV_REUSE_DY)};
+  a.pad_keep = pad_keep;
   if (a.reuse && a.mode == ARD_CONV_SELECT) return fail(ARD_EINVAL, "SELECT builds no grid");
   int32_t st = conv_check(a);
   if (st) return st;

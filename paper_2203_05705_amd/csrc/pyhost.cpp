@@ -600,7 +600,7 @@ PyObject* conv_select(const Args& a) {  // A, rate, Cout, ksize, stride, pad, ws
     mask = dict_tensor(a.v[8], "mask"), keep = dict_tensor(a.v[8], "keep"), count = dict_tensor(a.v[8], "count"), score = dict_tensor(a.v[8], "score");
   } else {
     mask = output({s.C}, at::kByte, A.device());
-    keep = filled({s.C}, -1, A.device());
+    keep = output({s.C}, at::kInt, A.device());
     count = at::empty({1}, keep.options());
     score = output({s.C}, at::kLong, A.device());
   }
@@ -608,7 +608,8 @@ PyObject* conv_select(const Args& a) {  // A, rate, Cout, ksize, stride, pad, ws
   ConvPass p;
   p.rate = a.real(1, 0.0), p.A = ptr(A), p.mask = (uint8_t*)ptr(mask), p.keep = (int32_t*)ptr(keep), p.count = (int32_t*)ptr(count);
   p.score = (int64_t*)ptr(score);
-  p.run(ARD_CONV_SELECT, dt, s, ws, stream_of(a.v[7]));
+  // (a list made here has room for every channel: the kernel fills its end)
+  p.run(ARD_CONV_SELECT | (a.given(8) ? 0 : ARD_CONV_PAD_KEEP), dt, s, ws, stream_of(a.v[7]));
   if (a.given(8)) return give(a.v[8]);
   DictOut d;
   d.put("mask", mask), d.put("keep", keep), d.put("count", count), d.put("score", score);
