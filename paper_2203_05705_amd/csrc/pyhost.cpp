@@ -21,6 +21,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <string>
+#include <type_traits>
 
 #include "../../include/ard.h"
 
@@ -76,12 +77,19 @@ void check(int32_t code) {
   throw PyRaised{};
 }
 
-// an enqueueing call of the C ABI, without the interpreter lock (as ctypes makes it)
-template <class F> void enqueue(F&& f) {
+// An enqueueing call of the C ABI, without the interpreter lock (as ctypes makes it).  Its arguments are values: whatever
+// of them can raise (a tensor without storage has no address) has done so before the lock is given up.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <class... P, class... A> void enqueue(int32_t (*f)(P...), A... args) {
+  static_assert((std::is_scalar_v<A> && ...), "numbers and addresses only: nothing left to evaluate without the lock");
   int32_t rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = f();
-  Py_END_ALLOW_THREADS
+  {
+    Unlocked unlocked;
+    rc = f(args...);
+  }
   check(rc);
 }
 
@@ -408,7 +416,7 @@ PyObject* compact_weight(const Args& a) {  // W, pat_out, pat_in, out, stream
   const at::Tensor Wc = a.given(3) ? tensor_of(a.v[3], "out") : output({pad8(Ok), pad8(Ik)}, W.scalar_type(), W.device());
   const int32_t dt = dtype_code(W);
   void* st = stream_of(a.v[4]);
-  enqueue([&] { return lib().ard_compact_weight(dt, I, O, ptr(W), ptr(Wc), po.p, pi.p, st); });
+  enqueue(lib().ard_compact_weight, dt, I, O, ptr(W), ptr(Wc), po.p, pi.p, st);
   return result(a, 3, Wc);
 }
 
@@ -435,7 +443,7 @@ PyObject* drop_gemm_fwd(const Args& a) {  // X, W, pat_out, pat_in, alpha, relu,
                                   : output({B, flags & ARD_OUT_COMPACT ? pad8(kept(po, O)) : O}, X.scalar_type(), X.device());
   Workspace ws(a, 8, X.device(), [&] { return lib().ard_gemm_workspace_bytes(dt, B, I, O, po.p, pi.p); });
   void* st = stream_of(a.v[9]);
-  enqueue([&] { return lib().ard_drop_gemm_fwd(dt, B, I, O, ptr(X), ptr(W), ptr(Y), po.p, pi.p, alpha, relu, flags, ws.p, ws.bytes, st); });
+  enqueue(lib().ard_drop_gemm_fwd, dt, B, I, O, ptr(X), ptr(W), ptr(Y), po.p, pi.p, alpha, relu, flags, ws.p, ws.bytes, st);
   return result(a, 7, Y);
 }
 
@@ -453,7 +461,7 @@ PyObject* drop_gemm_bwd_data(const Args& a) {  // dY, W, pat_out, pat_in, alpha,
   const void* src = opt_ptr(a, 5, "relu_src");
   Workspace ws(a, 8, dY.device(), [&] { return lib().ard_gemm_workspace_bytes(dt, B, I, O, po.p, pi.p); });
   void* st = stream_of(a.v[9]);
-  enqueue([&] { return lib().ard_drop_gemm_bwd_data(dt, B, I, O, ptr(dY), ptr(W), ptr(dX), po.p, pi.p, alpha, src, flags, ws.p, ws.bytes, st); });
+  enqueue(lib().ard_drop_gemm_bwd_data, dt, B, I, O, ptr(dY), ptr(W), ptr(dX), po.p, pi.p, alpha, src, flags, ws.p, ws.bytes, st);
   return result(a, 7, dX);
 }
 
@@ -472,7 +480,7 @@ PyObject* drop_gemm_bwd_weight(const Args& a) {  // dY, X, pat_out, pat_in, alph
   else dW = output({O, I}, dY.scalar_type(), dY.device());
   Workspace ws(a, 8, dY.device(), [&] { return lib().ard_gemm_workspace_bytes(dt, B, I, O, po.p, pi.p); });
   void* st = stream_of(a.v[9]);
-  enqueue([&] { return lib().ard_drop_gemm_bwd_weight(dt, B, I, O, ptr(dY), ptr(X), ptr(dW), po.p, pi.p, alpha, beta, flags, ws.p, ws.bytes, st); });
+  enqueue(lib().ard_drop_gemm_bwd_weight, dt, B, I, O, ptr(dY), ptr(X), ptr(dW), po.p, pi.p, alpha, beta, flags, ws.p, ws.bytes, st);
   return result(a, 7, dW);
 }
 
@@ -485,7 +493,7 @@ PyObject* drop_gemm_bwd_weight_static(const Args& a) {  // dY, X, pat_out, pat_i
   const float alpha = (float)a.real(5, 1.0), beta = (float)a.real(6, 0.0);
   const int flags = a.integer(7, 0);
   void* st = stream_of(a.v[8]);
-  enqueue([&] { return lib().ard_drop_gemm_bwd_weight_static(dt, B, I, O, ptr(dY), ptr(X), ptr(dW), po.p, pi.p, alpha, beta, flags, st); });
+  enqueue(lib().ard_drop_gemm_bwd_weight_static, dt, B, I, O, ptr(dY), ptr(X), ptr(dW), po.p, pi.p, alpha, beta, flags, st);
   return give(a.v[4]);
 }
 
@@ -527,7 +535,7 @@ PyObject* lstm_fwd(const Args& a) {  // x, W, pat, ws, stream, out
   PatRef p(a.v[2]);
   Workspace ws(a, 3, x.device(), [&] { return lib().ard_lstm_workspace_bytes(dt, T, B, I, H, p.p); });
   void* st = stream_of(a.v[4]);
-  enqueue([&] { return lib().ard_lstm_fwd(dt, T, B, I, H, ptr(x), ptr(W), p.p, ptr(o[0]), (float*)ptr(o[1]), (float*)ptr(o[2]), ws.p, ws.bytes, st); });
+  enqueue(lib().ard_lstm_fwd, dt, T, B, I, H, ptr(x), ptr(W), p.p, ptr(o[0]), (float*)ptr(o[1]), (float*)ptr(o[2]), ws.p, ws.bytes, st);
   return tuple_of(o);
 }
 
@@ -546,10 +554,8 @@ PyObject* lstm_bwd(const Args& a) {  // x, W, pat, h, c, gates, dh, ws, stream, 
   PatRef p(a.v[2]);
   Workspace ws(a, 7, x.device(), [&] { return lib().ard_lstm_workspace_bytes(dt, T, B, I, H, p.p); });
   void* st = stream_of(a.v[8]);
-  enqueue([&] {
-    return lib().ard_lstm_bwd(dt, T, B, I, H, ptr(x), ptr(W), p.p, ptr(h), (const float*)ptr(c), (const float*)ptr(g), ptr(dh), ptr(o[0]), ptr(o[1]),
-                              ws.p, ws.bytes, st);
-  });
+  enqueue(lib().ard_lstm_bwd, dt, T, B, I, H, ptr(x), ptr(W), p.p, ptr(h), (const float*)ptr(c), (const float*)ptr(g), ptr(dh), ptr(o[0]), ptr(o[1]),
+          ws.p, ws.bytes, st);
   return tuple_of(o);
 }
 
@@ -581,10 +587,8 @@ struct ConvPass {
   int32_t *keep = nullptr, *count = nullptr;
   int64_t* score = nullptr;
   void run(int mode, int32_t dt, const ConvShape& s, const Workspace& ws, void* st) const {
-    enqueue([&] {
-      return lib().ard_fmap_drop_conv(mode, dt, s.N, s.C, s.H, s.W, s.Co, s.kh, s.kw, s.stride, s.pad, rate, n_keep, A, Wt, dY, out, mask, keep, count,
-                                      score, ws.p, ws.bytes, st);
-    });
+    enqueue(lib().ard_fmap_drop_conv, mode, dt, s.N, s.C, s.H, s.W, s.Co, s.kh, s.kw, s.stride, s.pad, rate, n_keep, A, Wt, dY, out, mask, keep, count,
+            score, ws.p, ws.bytes, st);
   }
 };
 
@@ -724,10 +728,8 @@ PyObject* conv_fwd_blocks(const Args& a) {  // A, Wt, block_keep, x, y, stride, 
   Workspace ws(a, 7, A.device(), [&] { return s.ws_bytes(dt); });
   const int x = as_int(a.v[3]), y = as_int(a.v[4]);
   void* st = stream_of(a.v[8]);
-  enqueue([&] {
-    return lib().ard_conv_fwd_blocks(dt, s.N, s.C, s.H, s.W, s.Co, s.kh, s.kw, s.stride, s.pad, x, y, ptr(A), ptr(Wt), (const uint8_t*)ptr(keep), ptr(Y),
-                                     ws.p, ws.bytes, st);
-  });
+  enqueue(lib().ard_conv_fwd_blocks, dt, s.N, s.C, s.H, s.W, s.Co, s.kh, s.kw, s.stride, s.pad, x, y, ptr(A), ptr(Wt), (const uint8_t*)ptr(keep), ptr(Y),
+          ws.p, ws.bytes, st);
   return result(a, 9, Y);
 }
 
@@ -746,10 +748,8 @@ PyObject* conv_bwd_blocks(const Args& a) {  // dY, A, Wt, block_keep, x, y, stri
   // (the weight gradient takes what the data gradient just left in the workspace, where it left it)
   const int modes[2] = {ARD_CONV_BWD_DATA, ARD_CONV_BWD_WEIGHT | ARD_CONV_REUSE_DY};
   for (int i = 0; i < 2; ++i)
-    enqueue([&] {
-      return lib().ard_conv_bwd_blocks(modes[i], dt, s.N, s.C, s.H, s.W, s.Co, s.kh, s.kw, s.stride, s.pad, x, y, ptr(A), ptr(Wt), ptr(dY),
-                                       (const uint8_t*)ptr(keep), ptr(o[i]), ws.p, ws.bytes, st);
-    });
+    enqueue(lib().ard_conv_bwd_blocks, modes[i], dt, s.N, s.C, s.H, s.W, s.Co, s.kh, s.kw, s.stride, s.pad, x, y, ptr(A), ptr(Wt), ptr(dY),
+            (const uint8_t*)ptr(keep), ptr(o[i]), ws.p, ws.bytes, st);
   return tuple_of(o);
 }
 
@@ -770,10 +770,8 @@ PyObject* sens_predict(const Args& a) {  // A, ksize, stride, pad, x, y, k_permi
   const at::Tensor count = output({s.N, rb, cb}, at::kInt, A.device()), samples = output({s.N, rb, cb}, at::kInt, A.device()),
                    sens = output({s.N, rb, cb}, at::kByte, A.device());
   void* st = stream_of(a.v[11]);
-  enqueue([&] {
-    return lib().ard_sens_predict(dt, s.N, s.C, s.H, s.W, s.kh, s.kw, s.stride, s.pad, x, y, k, t, thr, seed, it, ptr(A), (int32_t*)ptr(count),
-                                  (int32_t*)ptr(samples), (uint8_t*)ptr(sens), st);
-  });
+  enqueue(lib().ard_sens_predict, dt, s.N, s.C, s.H, s.W, s.kh, s.kw, s.stride, s.pad, x, y, k, t, thr, seed, it, ptr(A), (int32_t*)ptr(count),
+          (int32_t*)ptr(samples), (uint8_t*)ptr(sens), st);
   DictOut d;
   d.put("count", count), d.put("samples", samples), d.put("sens", sens);
   return d.d;
@@ -787,10 +785,8 @@ PyObject* sens_row_pattern(const Args& a) {  // sens, rows, x, m, n, seed, itera
   const int64_t total = (int64_t)N * rows;
   const at::Tensor mask = output({total}, at::kByte, sens.device()), keep = filled({total}, -1, sens.device()), count = at::empty({1}, keep.options());
   void* st = stream_of(a.v[7]);
-  enqueue([&] {
-    return lib().ard_sens_row_pattern(N, rows, x, (const uint8_t*)ptr(sens), m, n, seed, it, (uint8_t*)ptr(mask), (int32_t*)ptr(keep),
-                                      (int32_t*)ptr(count), st);
-  });
+  enqueue(lib().ard_sens_row_pattern, N, rows, x, (const uint8_t*)ptr(sens), m, n, seed, it, (uint8_t*)ptr(mask), (int32_t*)ptr(keep),
+          (int32_t*)ptr(count), st);
   DictOut d;
   d.put("mask", mask), d.put("keep", keep), d.put("count", count);
   return d.d;
@@ -804,10 +800,8 @@ PyObject* sens_block_pattern(const Args& a) {  // pred, balance, m, n, seed, ite
   const uint64_t seed = a.u64(4), it = a.u64(5);
   const at::Tensor sens = output({N, RB, CB}, at::kByte, in.device()), keep = output({N, RB, CB}, at::kByte, in.device());
   void* st = stream_of(a.v[6]);
-  enqueue([&] {
-    return lib().ard_sens_block_pattern(N, RB, CB, (const int32_t*)ptr(cnt), (const int32_t*)ptr(smp), (const uint8_t*)ptr(in), balance, m, n, seed, it,
-                                        (uint8_t*)ptr(sens), (uint8_t*)ptr(keep), st);
-  });
+  enqueue(lib().ard_sens_block_pattern, N, RB, CB, (const int32_t*)ptr(cnt), (const int32_t*)ptr(smp), (const uint8_t*)ptr(in), balance, m, n, seed, it,
+          (uint8_t*)ptr(sens), (uint8_t*)ptr(keep), st);
   DictOut d;
   d.put("sens", sens), d.put("keep", keep);
   return d.d;
@@ -853,7 +847,7 @@ PyObject* batch_exit(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
       lib().ard_batch_abort();
     } else {
       void* st = stream_of(reinterpret_cast<BatchObject*>(self)->stream);
-      enqueue([&] { return lib().ard_batch_launch(st); });
+      enqueue(lib().ard_batch_launch, st);
     }
     return give(Py_False);
   });
