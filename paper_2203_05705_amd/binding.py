@@ -9,6 +9,7 @@ fallback path.
 """
 from __future__ import annotations
 
+import copyreg
 import ctypes as C
 import os
 from typing import Optional
@@ -73,6 +74,16 @@ if _ardcall is not None:
                 p.d_colptr = self.lists["colptr"].data_ptr()
                 p.d_csc_rows = self.lists["csc_rows"].data_ptr()
             return p
+
+        # copies and pickles: the fields (which live in the base's C struct) and whatever else an instance was given
+        _FIELDS = ("kind", "dp", "b", "tile_r", "tile_c", "keep", "count", "lists")
+
+        def __reduce__(self):
+            return copyreg.__newobj__, (type(self),), {**{f: getattr(self, f) for f in self._FIELDS}, **self.__dict__}
+
+        def __setstate__(self, state):
+            for name, value in state.items():
+                setattr(self, name, value)
 
 
 def __getattr__(name):

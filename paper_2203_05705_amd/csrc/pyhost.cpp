@@ -822,6 +822,11 @@ int batch_init(PyObject* self, PyObject* args, PyObject* kw) {
   Py_XSETREF(reinterpret_cast<BatchObject*>(self)->stream, s);
   return 0;
 }
+PyMemberDef batch_members[] = {{"stream", T_OBJECT, offsetof(BatchObject, stream), 0, nullptr}, {nullptr, 0, 0, 0, nullptr}};
+PyObject* batch_reduce(PyObject* self, PyObject*) {  // copies and pickles: type(self)(stream)
+  PyObject* s = reinterpret_cast<BatchObject*>(self)->stream;
+  return Py_BuildValue("O(O)", Py_TYPE(self), s ? s : Py_None);
+}
 void batch_dealloc(PyObject* self) {
   Py_XDECREF(reinterpret_cast<BatchObject*>(self)->stream);
   Py_TYPE(self)->tp_free(self);
@@ -854,6 +859,7 @@ PyObject* batch_exit(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
 }
 PyMethodDef batch_methods[] = {{"__enter__", batch_enter, METH_NOARGS, nullptr},
                                {"__exit__", (PyCFunction)(void (*)(void))batch_exit, METH_FASTCALL, nullptr},
+                               {"__reduce__", batch_reduce, METH_NOARGS, nullptr},
                                {nullptr, nullptr, 0, nullptr}};
 
 // pattern constructors; `cls` is binding.Pattern, its instances are filled directly
@@ -995,6 +1001,7 @@ PyMODINIT_FUNC PyInit__ardcall(void) {
   BatchType.tp_init = batch_init;
   BatchType.tp_dealloc = batch_dealloc;
   BatchType.tp_methods = batch_methods;
+  BatchType.tp_members = batch_members;
   if (PyType_Ready(&PatternType) < 0 || PyType_Ready(&BatchType) < 0) return nullptr;
   s_dtype = PyUnicode_InternFromString("dtype"), s_device = PyUnicode_InternFromString("device");
   s_cuda_stream = PyUnicode_InternFromString("cuda_stream");

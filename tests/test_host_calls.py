@@ -1,6 +1,8 @@
 """The calls of the extension _ardcall on tensors without memory behind them, in dry-run mode: what they accept, what
 they refuse and how, without a GPU."""
+import copy
 import os
+import pickle
 import subprocess
 import sys
 import textwrap
@@ -82,3 +84,25 @@ def test_an_argument_without_storage_raises(name):
     r = subprocess.run([sys.executable, "-c", textwrap.dedent(code)], cwd=os.path.dirname(here), capture_output=True, text=True, timeout=300,
                        env=dict(os.environ, PYTHONPATH=os.pathsep.join((here, os.path.dirname(here)))))
     assert r.returncode == 0 and "raised" in r.stdout, (r.returncode, r.stdout, r.stderr[-2000:])
+
+
+class _Named(ard.Pattern):
+    """A program's own kind of pattern."""
+
+
+@pytest.mark.parametrize("copier", [copy.copy, copy.deepcopy] + [lambda p, v=v: pickle.loads(pickle.dumps(p, v)) for v in range(6)])
+def test_patterns_and_batches_can_be_copied_and_pickled(copier):
+    keep = torch.tensor([1, 4, 6], dtype=torch.int32)
+    named = _Named(ard.PAT_ROW, 4, 2)
+    named.label = "fc1"
+    for p in (ard.Pattern(), ard.Pattern.row(3, 2), ard.Pattern.tile(2, 1, 32, 64, lists=dict(keep=keep)), ard.Pattern(ard.PAT_LIST, keep=keep),
+              ard.Pattern(ard.PAT_LIST, keep=keep, count=2), named):
+        q = copier(p)
+        assert type(q) is type(p) and q is not p
+        for f in ("kind", "dp", "b", "tile_r", "tile_c", "count"):
+            assert getattr(q, f) == getattr(p, f), f
+        assert (q.keep is None) == (p.keep is None) and (p.keep is None or torch.equal(q.keep, p.keep))
+        assert (q.lists is None) == (p.lists is None) and (p.lists is None or torch.equal(q.lists["keep"], keep))
+        assert (q.keep is p.keep) == (copier is copy.copy or p.keep is None)
+    assert copier(named).label == "fc1"
+    assert copier(ard.batch()).stream is None
