@@ -862,9 +862,12 @@ PyMethodDef batch_methods[] = {{"__enter__", batch_enter, METH_NOARGS, nullptr},
                                {"__reduce__", batch_reduce, METH_NOARGS, nullptr},
                                {nullptr, nullptr, 0, nullptr}};
 
-// pattern constructors; `cls` is binding.Pattern, its instances are filled directly
+// Pattern constructors: a binding.Pattern, filled directly, also when called through a class a program derived from it
+// (whose own __new__ and __init__ may want other arguments).
 PyObject* pattern_of(PyObject* cls, int kind, int dp, int b, int tr, int tc, PyObject* lists) {
-  PyObject* o = reinterpret_cast<PyTypeObject*>(cls)->tp_new(reinterpret_cast<PyTypeObject*>(cls), nullptr, nullptr);
+  PyTypeObject* t = reinterpret_cast<PyTypeObject*>(cls);
+  while (t != &PatternType && t->tp_base != &PatternType) t = t->tp_base;
+  PyObject* o = t->tp_new(t, nullptr, nullptr);
   if (!o) throw PyRaised{};
   PatternObject* p = reinterpret_cast<PatternObject*>(o);
   p->kind = kind, p->dp = dp, p->b = b, p->tile_r = tr, p->tile_c = tc;

@@ -106,3 +106,15 @@ def test_patterns_and_batches_can_be_copied_and_pickled(copier):
         assert (q.keep is p.keep) == (copier is copy.copy or p.keep is None)
     assert copier(named).label == "fc1"
     assert copier(ard.batch()).stream is None
+
+
+def test_constructors_called_through_a_derived_class_give_a_plain_pattern():
+    class Layer(ard.Pattern):
+        def __new__(cls, name):
+            return super().__new__(cls)
+
+        def __init__(self, name):
+            super().__init__(ard.PAT_ROW, 2, 1)
+    for p in (Layer.row(3, 2), Layer.tile(3, 2, 8, 8)):
+        assert type(p) is ard.Pattern and (p.dp, p.b) == (3, 2)
+    assert Layer("fc1").dp == 2
