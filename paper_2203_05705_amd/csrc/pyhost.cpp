@@ -158,6 +158,25 @@ int as_int(PyObject* o) {
   if (v < INT32_MIN || v > INT32_MAX) raise(PyExc_OverflowError, "%ld does not fit 32 bits", v);
   return (int)v;
 }
+// int(o) and float(o): counts and rates are taken from whatever converts (a whole-valued float, a 0-d tensor, a string)
+int to_int(PyObject* o) {
+  if (PyLong_CheckExact(o)) return as_int(o);
+  PyObject* n = PyNumber_Long(o);
+  if (!n) throw PyRaised{};
+  int overflow = 0;
+  const long v = PyLong_AsLongAndOverflow(n, &overflow);
+  Py_DECREF(n);
+  if (overflow || v < INT32_MIN || v > INT32_MAX) raise(PyExc_OverflowError, "%R does not fit 32 bits", o);
+  return (int)v;
+}
+double to_float(PyObject* o) {
+  if (PyFloat_CheckExact(o)) return PyFloat_AS_DOUBLE(o);
+  PyObject* f = PyNumber_Float(o);
+  if (!f) throw PyRaised{};
+  const double v = PyFloat_AS_DOUBLE(f);
+  Py_DECREF(f);
+  return v;
+}
 PyMemberDef pattern_members[] = {{"kind", T_INT, offsetof(PatternObject, kind), 0, nullptr},
                                  {"dp", T_INT, offsetof(PatternObject, dp), 0, nullptr},
                                  {"b", T_INT, offsetof(PatternObject, b), 0, nullptr},
@@ -179,7 +198,9 @@ struct PatRef {
     const PatternObject* q = reinterpret_cast<const PatternObject*>(o);
     c.kind = q->kind, c.dp = q->dp, c.b = q->b, c.tile_r = q->tile_r, c.tile_c = q->tile_c, c.count = q->count;
     if (q->kind == ARD_PAT_LIST && q->keep && q->keep != Py_None) c.d_keep = (const int32_t*)tensor_of(q->keep, "keep").data_ptr();
-    if (q->kind == ARD_PAT_TILE && q->lists && PyObject_IsTrue(q->lists) == 1) {
+    const int lists = q->kind == ARD_PAT_TILE && q->lists ? PyObject_IsTrue(q->lists) : 0;
+    if (lists < 0) throw PyRaised{};
+    if (lists) {
       auto get = [&](const char* k) {
         PyObject* v = PyMapping_GetItemString(q->lists, k);
         if (!v) throw PyRaised{};
@@ -235,12 +256,7 @@ struct Args {
   }
   bool given(int i) const { return v[i] && v[i] != Py_None; }
   int integer(int i, int dflt) const { return v[i] ? as_int(v[i]) : dflt; }
-  double real(int i, double dflt) const {
-    if (!v[i]) return dflt;
-    const double d = PyFloat_AsDouble(v[i]);
-    if (d == -1.0 && PyErr_Occurred()) throw PyRaised{};
-    return d;
-  }
+  double real(int i, double dflt) const { return v[i] ? to_float(v[i]) : dflt; }
   uint64_t u64(int i) const {
     const uint64_t d = PyLong_AsUnsignedLongLongMask(v[i]);
     if (d == (uint64_t)-1 && PyErr_Occurred()) throw PyRaised{};
@@ -268,12 +284,13 @@ const at::Tensor& ranked(const at::Tensor& t, int64_t rank, const char* what) {
   if (t.dim() != rank) raise(PyExc_ValueError, "%s: %d dimensions are wanted, got %d", what, (int)rank, (int)t.dim());
   return t;
 }
-int dim(const at::Tensor& t, int i) {
+int dim(const at::Tensor& t, int i) {  // t.shape[i]
+  if (i >= t.dim()) raise(PyExc_IndexError, "tuple index out of range");
   const int64_t n = t.size(i);
   if (n > INT32_MAX) raise(PyExc_OverflowError, "a dimension of %lld elements is too large", (long long)n);
   return (int)n;
 }
-void* ptr(const at::Tensor& t) { return t.data_ptr(); }
+void* ptr(const at::Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; }
 void* opt_ptr(const Args& a, int i, const char* what) { return a.given(i) ? tensor_of(a.v[i], what).data_ptr() : nullptr; }
 
 // torch.cuda.current_stream() of the current device, or the Stream object passed in
@@ -338,12 +355,13 @@ struct DictOut {
     Py_DECREF(o);
   }
 };
-at::Tensor dict_tensor(PyObject* d, const char* k) {
+// d[k]; with `optional` None gives an undefined tensor, whose address is NULL
+at::Tensor dict_tensor(PyObject* d, const char* k, bool optional = false) {
   PyObject* v = PyMapping_GetItemString(d, k);
   if (!v) throw PyRaised{};
   at::Tensor t;
   try {
-    t = tensor_of(v, k);
+    if (!optional || v != Py_None) t = tensor_of(v, k);
   } catch (...) {
     Py_DECREF(v);
     throw;
@@ -351,17 +369,35 @@ at::Tensor dict_tensor(PyObject* d, const char* k) {
   Py_DECREF(v);
   return t;
 }
-void pair_of(PyObject* o, int* a, int* b) {
+// a, b = o
+void unpack_pair(PyObject* o, int* a, int* b) {
   PyObject* f = PySequence_Fast(o, "a pair of integers is wanted");
   if (!f) throw PyRaised{};
-  if (PySequence_Fast_GET_SIZE(f) < 2) {
+  try {
+    const Py_ssize_t n = PySequence_Fast_GET_SIZE(f);
+    if (n != 2) raise(PyExc_ValueError, n < 2 ? "not enough values to unpack (expected 2, got %zd)" : "too many values to unpack (expected 2, got %zd)", n);
+    *a = as_int(PySequence_Fast_GET_ITEM(f, 0)), *b = as_int(PySequence_Fast_GET_ITEM(f, 1));
+  } catch (...) {
     Py_DECREF(f);
-    raise(PyExc_ValueError, "a pair of integers is wanted");
+    throw;
   }
-  const long x = PyLong_AsLong(PySequence_Fast_GET_ITEM(f, 0)), y = PyLong_AsLong(PySequence_Fast_GET_ITEM(f, 1));
   Py_DECREF(f);
-  if (PyErr_Occurred()) throw PyRaised{};
-  *a = (int)x, *b = (int)y;
+}
+// o[i], through `convert`
+int item_of(PyObject* o, int i, int (*convert)(PyObject*)) {
+  PyObject* k = PyLong_FromLong(i);
+  PyObject* v = PyObject_GetItem(o, k);
+  Py_DECREF(k);
+  if (!v) throw PyRaised{};
+  int n;
+  try {
+    n = convert(v);
+  } catch (...) {
+    Py_DECREF(v);
+    throw;
+  }
+  Py_DECREF(v);
+  return n;
 }
 
 struct Workspace {
@@ -388,7 +424,7 @@ int kept(const PatRef& p, int units) {
 }
 int pad8(int n) { return lib().ard_compact_dim(nullptr, n); }
 void check_compact(const at::Tensor& t, int count, const char* what) {
-  if (t.dim() == 2 && t.size(1) == pad8(count) && t.is_contiguous()) return;
+  if (dim(t, 1) == pad8(count) && t.is_contiguous()) return;
   std::string sh = "(";
   for (int64_t i = 0; i < t.dim(); ++i) sh += (i ? ", " : "") + std::to_string(t.size(i));
   raise(PyExc_ValueError, "%s: a compact activation has pad8(kept)=%d contiguous columns, got %s)", what, pad8(count), sh.c_str());
@@ -424,13 +460,12 @@ PyObject* compact_weight(const Args& a) {  // W, pat_out, pat_in, out, stream
 void layer_sizes(const Args& a, int iI, int iO, int flags, const at::Tensor& W, int* I, int* O) {
   const bool own = !(flags & ARD_W_COMPACT);
   if ((!own && !(a.given(iI) && a.given(iO)))) raise(PyExc_AssertionError, "pass I and O with ARD_W_COMPACT");
-  ranked(W, 2, "W");
   *I = a.given(iI) ? as_int(a.v[iI]) : dim(W, 1);
   *O = a.given(iO) ? as_int(a.v[iO]) : dim(W, 0);
 }
 
 PyObject* drop_gemm_fwd(const Args& a) {  // X, W, pat_out, pat_in, alpha, relu, flags, out, ws, stream, I, O
-  const at::Tensor &X = ranked(device_tensor(a.v[0], "X"), 2, "X"), &W = device_tensor(a.v[1], "W");
+  const at::Tensor &X = device_tensor(a.v[0], "X"), &W = device_tensor(a.v[1], "W");
   const int flags = a.integer(6, 0), B = dim(X, 0);
   int I, O;
   layer_sizes(a, 10, 11, flags, W, &I, &O);
@@ -448,7 +483,7 @@ PyObject* drop_gemm_fwd(const Args& a) {  // X, W, pat_out, pat_in, alpha, relu,
 }
 
 PyObject* drop_gemm_bwd_data(const Args& a) {  // dY, W, pat_out, pat_in, alpha, relu_src, flags, out, ws, stream, I, O
-  const at::Tensor &dY = ranked(device_tensor(a.v[0], "dY"), 2, "dY"), &W = device_tensor(a.v[1], "W");
+  const at::Tensor &dY = device_tensor(a.v[0], "dY"), &W = device_tensor(a.v[1], "W");
   const int flags = a.integer(6, 0), B = dim(dY, 0);
   int I, O;
   layer_sizes(a, 10, 11, flags, W, &I, &O);
@@ -466,7 +501,7 @@ PyObject* drop_gemm_bwd_data(const Args& a) {  // dY, W, pat_out, pat_in, alpha,
 }
 
 PyObject* drop_gemm_bwd_weight(const Args& a) {  // dY, X, pat_out, pat_in, alpha, beta, flags, out, ws, stream, I, O
-  const at::Tensor &dY = ranked(device_tensor(a.v[0], "dY"), 2, "dY"), &X = ranked(device_tensor(a.v[1], "X"), 2, "X");
+  const at::Tensor &dY = device_tensor(a.v[0], "dY"), &X = device_tensor(a.v[1], "X");
   const int flags = a.integer(6, 0), B = dim(dY, 0);
   const int I = a.given(10) ? as_int(a.v[10]) : dim(X, 1), O = a.given(11) ? as_int(a.v[11]) : dim(dY, 1);
   const int32_t dt = dtype_code(dY);
@@ -485,7 +520,7 @@ PyObject* drop_gemm_bwd_weight(const Args& a) {  // dY, X, pat_out, pat_in, alph
 }
 
 PyObject* drop_gemm_bwd_weight_static(const Args& a) {  // dY, X, pat_out, pat_in, out, alpha, beta, flags, stream, I, O
-  const at::Tensor &dY = ranked(device_tensor(a.v[0], "dY"), 2, "dY"), &X = ranked(device_tensor(a.v[1], "X"), 2, "X");
+  const at::Tensor &dY = device_tensor(a.v[0], "dY"), &X = device_tensor(a.v[1], "X");
   const at::Tensor& dW = device_tensor(a.v[4], "out");
   const int I = a.given(9) ? as_int(a.v[9]) : dim(X, 1), O = a.given(10) ? as_int(a.v[10]) : dim(dY, 1), B = dim(dY, 0);
   const int32_t dt = dtype_code(dY);
@@ -520,9 +555,9 @@ template <int N> PyObject* tuple_of(const at::Tensor (&t)[N]) {
 }
 
 PyObject* lstm_fwd(const Args& a) {  // x, W, pat, ws, stream, out
-  const at::Tensor &x = ranked(device_tensor(a.v[0], "x"), 3, "x"), &W = ranked(device_tensor(a.v[1], "W"), 2, "W");
+  const at::Tensor &x = ranked(device_tensor(a.v[0], "x"), 3, "x"), &W = device_tensor(a.v[1], "W");
   const int T = dim(x, 0), B = dim(x, 1), I = dim(x, 2), H = dim(W, 0) / 4;
-  if (W.size(0) != 4 * (int64_t)H || W.size(1) != (int64_t)I + H) raise(PyExc_AssertionError, "W is [4H x (I+H)]");
+  if (W.dim() != 2 || W.size(0) != 4 * (int64_t)H || W.size(1) != (int64_t)I + H) raise(PyExc_AssertionError, "W is [4H x (I+H)]");
   const int32_t dt = dtype_code(x);
   at::Tensor o[3];  // h, c, gates
   if (a.given(5)) {
@@ -540,7 +575,7 @@ PyObject* lstm_fwd(const Args& a) {  // x, W, pat, ws, stream, out
 }
 
 PyObject* lstm_bwd(const Args& a) {  // x, W, pat, h, c, gates, dh, ws, stream, out
-  const at::Tensor &x = ranked(device_tensor(a.v[0], "x"), 3, "x"), &W = ranked(device_tensor(a.v[1], "W"), 2, "W"), &h = device_tensor(a.v[3], "h"),
+  const at::Tensor &x = ranked(device_tensor(a.v[0], "x"), 3, "x"), &W = device_tensor(a.v[1], "W"), &h = device_tensor(a.v[3], "h"),
                    &c = device_tensor(a.v[4], "c"), &g = device_tensor(a.v[5], "gates"), &dh = device_tensor(a.v[6], "dh");
   const int T = dim(x, 0), B = dim(x, 1), I = dim(x, 2), H = dim(W, 0) / 4;
   const int32_t dt = dtype_code(x);
@@ -597,11 +632,12 @@ PyObject* conv_select(const Args& a) {  // A, rate, Cout, ksize, stride, pad, ws
   ConvShape s;
   s.in(A);
   s.Co = a.integer(2, 1), s.kh = s.kw = 3, s.stride = a.integer(4, 1), s.pad = a.integer(5, 1);
-  if (a.v[3]) pair_of(a.v[3], &s.kh, &s.kw);
+  if (a.v[3]) unpack_pair(a.v[3], &s.kh, &s.kw);
   const int32_t dt = dtype_code(A);
   at::Tensor mask, keep, count, score;
   if (a.given(8)) {
-    mask = dict_tensor(a.v[8], "mask"), keep = dict_tensor(a.v[8], "keep"), count = dict_tensor(a.v[8], "count"), score = dict_tensor(a.v[8], "score");
+    mask = dict_tensor(a.v[8], "mask", true), keep = dict_tensor(a.v[8], "keep", true), count = dict_tensor(a.v[8], "count", true);
+    score = dict_tensor(a.v[8], "score", true);
   } else {
     mask = output({s.C}, at::kByte, A.device());
     keep = output({s.C}, at::kInt, A.device());
@@ -631,17 +667,17 @@ PyObject* conv_fwd(const Args& a) {  // A, Wt, keep, n_keep, stride, pad, ws, st
   const at::Tensor Y = a.given(8) ? tensor_of(a.v[8], "out") : output({s.N, s.Co, ho, wo}, A.scalar_type(), A.device());
   Workspace ws(a, 6, A.device(), [&] { return s.ws_bytes(dt); });
   ConvPass p;
-  p.n_keep = as_int(a.v[3]), p.A = ptr(A), p.Wt = ptr(Wt), p.out = ptr(Y), p.keep = (int32_t*)opt_ptr(a, 2, "keep");
+  p.n_keep = to_int(a.v[3]), p.A = ptr(A), p.Wt = ptr(Wt), p.out = ptr(Y), p.keep = (int32_t*)opt_ptr(a, 2, "keep");
   p.run(ARD_CONV_FWD | a.integer(9, 0), dt, s, ws, stream_of(a.v[7]));
   return result(a, 8, Y);
 }
 
 PyObject* conv_bwd_data(const Args& a) {  // dY, Wt, keep, n_keep, in_hw, stride, pad, ws, stream, out, reuse
-  const at::Tensor &dY = ranked(device_tensor(a.v[0], "dY"), 4, "dY"), &Wt = device_tensor(a.v[1], "Wt");
+  const at::Tensor &dY = device_tensor(a.v[0], "dY"), &Wt = device_tensor(a.v[1], "Wt");
   ConvShape s;
   s.filter(Wt);
   s.N = dim(dY, 0), s.C = dim(Wt, 1), s.stride = a.integer(5, 1), s.pad = a.integer(6, 1);
-  pair_of(a.v[4], &s.H, &s.W);
+  if (!a.given(9)) s.H = item_of(a.v[4], 0, to_int), s.W = item_of(a.v[4], 1, to_int);
   const int32_t dt = dtype_code(dY);
   const at::Tensor dA = a.given(9) ? tensor_of(a.v[9], "out") : output({s.N, s.C, s.H, s.W}, dY.scalar_type(), dY.device());
   ConvShape o = s;  // (the call takes the activations' sizes from dA)
@@ -649,22 +685,22 @@ PyObject* conv_bwd_data(const Args& a) {  // dY, Wt, keep, n_keep, in_hw, stride
   o.Co = s.Co;
   Workspace ws(a, 7, dY.device(), [&] { return o.ws_bytes(dt); });
   ConvPass p;
-  p.n_keep = as_int(a.v[3]), p.Wt = ptr(Wt), p.dY = ptr(dY), p.out = ptr(dA), p.keep = (int32_t*)opt_ptr(a, 2, "keep");
+  p.n_keep = to_int(a.v[3]), p.Wt = ptr(Wt), p.dY = ptr(dY), p.out = ptr(dA), p.keep = (int32_t*)opt_ptr(a, 2, "keep");
   p.run(ARD_CONV_BWD_DATA | a.integer(10, 0), dt, o, ws, stream_of(a.v[8]));
   return result(a, 9, dA);
 }
 
 PyObject* conv_bwd_weight(const Args& a) {  // dY, A, keep, n_keep, ksize, stride, pad, ws, stream, out, reuse
-  const at::Tensor &dY = ranked(device_tensor(a.v[0], "dY"), 4, "dY"), &A = device_tensor(a.v[1], "A");
+  const at::Tensor &dY = device_tensor(a.v[0], "dY"), &A = device_tensor(a.v[1], "A");
   ConvShape s;
   s.in(A);
   s.Co = dim(dY, 1), s.kh = s.kw = 3, s.stride = a.integer(5, 1), s.pad = a.integer(6, 1);
-  if (a.v[4]) pair_of(a.v[4], &s.kh, &s.kw);
+  if (a.v[4]) unpack_pair(a.v[4], &s.kh, &s.kw);
   const int32_t dt = dtype_code(A);
   const at::Tensor dW = a.given(9) ? tensor_of(a.v[9], "out") : output({s.Co, s.C, s.kh, s.kw}, A.scalar_type(), A.device());
   Workspace ws(a, 7, A.device(), [&] { return s.ws_bytes(dt); });
   ConvPass p;
-  p.n_keep = as_int(a.v[3]), p.A = ptr(A), p.dY = ptr(dY), p.out = ptr(dW), p.keep = (int32_t*)opt_ptr(a, 2, "keep");
+  p.n_keep = to_int(a.v[3]), p.A = ptr(A), p.dY = ptr(dY), p.out = ptr(dW), p.keep = (int32_t*)opt_ptr(a, 2, "keep");
   p.run(ARD_CONV_BWD_WEIGHT | a.integer(10, 0), dt, s, ws, stream_of(a.v[8]));
   return result(a, 9, dW);
 }
@@ -678,10 +714,10 @@ PyObject* conv_fwd_rows(const Args& a) {  // A, Wt, row_pat, n_keep, stride, pad
   s.out_hw(&ho, &wo);
   const int32_t dt = dtype_code(A);
   const at::Tensor Y = a.given(8) ? tensor_of(a.v[8], "out") : output({s.N, s.Co, ho, wo}, A.scalar_type(), A.device());
-  const at::Tensor keep = dict_tensor(a.v[2], "keep"), mask = dict_tensor(a.v[2], "mask");
+  const at::Tensor keep = dict_tensor(a.v[2], "keep", true), mask = dict_tensor(a.v[2], "mask", true);
   Workspace ws(a, 6, A.device(), [&] { return s.ws_bytes(dt); });
   ConvPass p;
-  p.n_keep = as_int(a.v[3]), p.A = ptr(A), p.Wt = ptr(Wt), p.out = ptr(Y), p.keep = (int32_t*)ptr(keep), p.mask = (uint8_t*)ptr(mask);
+  p.n_keep = to_int(a.v[3]), p.A = ptr(A), p.Wt = ptr(Wt), p.out = ptr(Y), p.keep = (int32_t*)ptr(keep), p.mask = (uint8_t*)ptr(mask);
   p.run(ARD_CONV_FWD_ROWS, dt, s, ws, stream_of(a.v[7]));
   return result(a, 8, Y);
 }
@@ -704,7 +740,7 @@ PyObject* conv_bwd_rows(const Args& a) {  // dY, A, Wt, row_pat, stride, pad, ws
   const int32_t dt = dtype_code(A);
   at::Tensor o[2];
   gradient_pair(a, 8, A, Wt, o);
-  const at::Tensor mask = dict_tensor(a.v[3], "mask");
+  const at::Tensor mask = dict_tensor(a.v[3], "mask", true);
   Workspace ws(a, 6, A.device(), [&] { return s.ws_bytes(dt); });
   void* st = stream_of(a.v[7]);
   ConvPass d;
@@ -726,7 +762,7 @@ PyObject* conv_fwd_blocks(const Args& a) {  // A, Wt, block_keep, x, y, stride, 
   const int32_t dt = dtype_code(A);
   const at::Tensor Y = a.given(9) ? tensor_of(a.v[9], "out") : output({s.N, s.Co, ho, wo}, A.scalar_type(), A.device());
   Workspace ws(a, 7, A.device(), [&] { return s.ws_bytes(dt); });
-  const int x = as_int(a.v[3]), y = as_int(a.v[4]);
+  const int x = to_int(a.v[3]), y = to_int(a.v[4]);
   void* st = stream_of(a.v[8]);
   enqueue(lib().ard_conv_fwd_blocks, dt, s.N, s.C, s.H, s.W, s.Co, s.kh, s.kw, s.stride, s.pad, x, y, ptr(A), ptr(Wt), (const uint8_t*)ptr(keep), ptr(Y),
           ws.p, ws.bytes, st);
@@ -743,7 +779,7 @@ PyObject* conv_bwd_blocks(const Args& a) {  // dY, A, Wt, block_keep, x, y, stri
   at::Tensor o[2];
   gradient_pair(a, 10, A, Wt, o);
   Workspace ws(a, 8, A.device(), [&] { return s.ws_bytes(dt); });
-  const int x = as_int(a.v[4]), y = as_int(a.v[5]);
+  const int x = to_int(a.v[4]), y = to_int(a.v[5]);
   void* st = stream_of(a.v[9]);
   // (the weight gradient takes what the data gradient just left in the workspace, where it left it)
   const int modes[2] = {ARD_CONV_BWD_DATA, ARD_CONV_BWD_WEIGHT | ARD_CONV_REUSE_DY};
@@ -759,7 +795,7 @@ PyObject* sens_predict(const Args& a) {  // A, ksize, stride, pad, x, y, k_permi
   const at::Tensor& A = device_tensor(a.v[0], "A");
   ConvShape s;
   s.in(A);
-  pair_of(a.v[1], &s.kh, &s.kw);
+  s.kh = item_of(a.v[1], 0, as_int), s.kw = item_of(a.v[1], 1, as_int);
   s.stride = as_int(a.v[2]), s.pad = as_int(a.v[3]);
   const int x = as_int(a.v[4]), y = as_int(a.v[5]), k = as_int(a.v[6]), t = as_int(a.v[7]);
   const float thr = (float)a.real(8, 0.0);

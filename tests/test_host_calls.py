@@ -118,3 +118,73 @@ def test_constructors_called_through_a_derived_class_give_a_plain_pattern():
     for p in (Layer.row(3, 2), Layer.tile(3, 2, 8, 8)):
         assert type(p) is ard.Pattern and (p.dp, p.b) == (3, 2)
     assert Layer("fc1").dp == 2
+
+
+def test_activations_of_more_than_two_dimensions_are_flattened():
+    """B is the first dimension; the weight (or I and O) says how much follows."""
+    X, W, Y, ws = fake(64, 2, 8, 8), fake(256, 128), fake(64, 256), fake_ws()
+    kw = dict(ws=ws, stream=STREAM)
+    with dry_run():
+        assert ard.drop_gemm_fwd(X, W, out=Y, **kw) is Y
+        assert ard.drop_gemm_bwd_data(fake(64, 16, 16), W, out=X, **kw) is X
+        assert ard.drop_gemm_bwd_weight(fake(64, 16, 16), X, out=W, I=128, O=256, **kw) is W
+        assert ard.drop_gemm_bwd_weight_static(Y, X, None, None, W, I=128, stream=STREAM) is W
+        W4 = fake(256, 2, 8, 8)
+        assert ard.drop_gemm_fwd(X, W4, out=Y, I=128, O=256, **kw) is Y
+        p = ard.Pattern.row(2, 1)
+        ard.drop_gemm_fwd(fake(64, 64, 1), W, None, p, flags=ard.IN_COMPACT, out=Y, **kw)
+        # a convolution's gradient: the first two dimensions count
+        A, dA = fake(2, 8, 6, 6), fake(2, 8, 6, 6)
+        ard.conv_bwd_weight(fake(2, 4, 36), A, None, 8, out=fake(4, 8, 3, 3), **kw)
+        ard.conv_bwd_data(fake(2, 4, 36), fake(4, 8, 3, 3), None, 8, None, out=dA, **kw)   # (sizes come from `out`)
+        x, h, c, g = fake(3, 8, 32), fake(3, 8, 32), fake(3, 8, 32), fake(3, 8, 128)
+        ard.lstm_bwd(x, fake(128, 8, 8), None, h, c, g, h, out=(x, fake(128, 64)), **kw)
+
+
+def test_counts_and_rates_are_taken_from_what_int_and_float_take():
+    A, Wt, Y, ws = fake(2, 8, 6, 6), fake(4, 8, 3, 3), fake(2, 4, 6, 6), fake_ws()
+    keep, u8 = fake(72, dtype=torch.int32), fake(72, dtype=torch.uint8)
+    kw = dict(ws=ws, stream=STREAM)
+    with dry_run():
+        for four in (4, 4.0, "4", torch.tensor(4), torch.tensor(4.0), True + 3):
+            ard.conv_fwd(A, Wt, keep, four, out=Y, **kw)
+            ard.conv_bwd_data(Y, Wt, keep, four, (6, 6), out=A, **kw)
+            ard.conv_bwd_weight(Y, A, keep, four, out=Wt, **kw)
+            ard.conv_fwd_rows(A, Wt, dict(keep=keep, mask=u8), four, out=Y, **kw)
+            ard.conv_fwd_blocks(A, Wt, u8, four, 72.0, out=Y, **kw)
+            ard.conv_bwd_blocks(Y, A, Wt, u8, four, "72", out=(A, Wt), **kw)
+        for half in (0.5, "0.5", torch.tensor(0.5)):
+            ard.conv_select(A, half, out=dict(mask=u8, keep=keep, count=None, score=None), **kw)
+            ard.drop_gemm_fwd(fake(16, 8), fake(8, 8), alpha=half, out=fake(16, 8), **kw)
+        ard.conv_fwd_rows(A, Wt, dict(keep=None, mask=u8), 0, out=Y, **kw)   # (an empty list needs no address)
+        with pytest.raises((TypeError, ValueError)):
+            ard.conv_fwd(A, Wt, keep, "four", out=Y, **kw)
+        with pytest.raises(TypeError):
+            ard.conv_fwd(A, Wt, keep, None, out=Y, **kw)
+
+
+def test_what_was_refused_stays_refused():
+    X, W, Y, ws = fake(64, 128), fake(256, 128), fake(64, 256), fake_ws()
+    A, Wt, keep = fake(2, 8, 6, 6), fake(4, 8, 3, 3), fake(8, dtype=torch.int32)
+    sel = dict(mask=fake(8, dtype=torch.uint8), keep=keep, count=keep, score=fake(8, dtype=torch.int64))
+    kw = dict(ws=ws, stream=STREAM)
+    with dry_run():
+        for error, call in [
+                (ValueError, lambda: ard.compact_weight(fake(4, 4, 4), out=W, stream=STREAM)),
+                (AssertionError, lambda: ard.drop_gemm_fwd(X.t(), W, out=Y, **kw)),
+                (IndexError, lambda: ard.drop_gemm_fwd(X, fake(256), out=Y, **kw)),
+                (IndexError, lambda: ard.drop_gemm_bwd_weight(fake(64), X, out=W, **kw)),
+                (IndexError, lambda: ard.drop_gemm_fwd(fake(64), W, None, None, flags=ard.IN_COMPACT, out=Y, **kw)),
+                (ValueError, lambda: ard.drop_gemm_fwd(X, W, None, ard.Pattern.row(2, 1), flags=ard.IN_COMPACT, out=Y, **kw)),
+                (TypeError, lambda: ard.drop_gemm_fwd(X, W, out=Y, I=128.0, **kw)),
+                (AssertionError, lambda: ard.drop_gemm_fwd(X, W, flags=ard.W_COMPACT, out=Y, **kw)),
+                (ValueError, lambda: ard.lstm_fwd(X, W, out=(X, X, X), **kw)),
+                (AssertionError, lambda: ard.lstm_fwd(fake(3, 8, 32), fake(128, 8, 8), out=(X, X, X), **kw)),
+                (ValueError, lambda: ard.conv_fwd(A, fake(4, 8, 9), keep, 4, out=A, **kw)),
+                (ValueError, lambda: ard.conv_select(A, 0.5, ksize=(3, 3, 3), out=sel, **kw)),
+                (ValueError, lambda: ard.conv_bwd_weight(A, A, keep, 4, ksize=(3,), out=Wt, **kw)),
+                (TypeError, lambda: ard.conv_bwd_weight(A, A, keep, 4, ksize=(3.0, 3.0), out=Wt, **kw)),
+                (TypeError, lambda: ard.conv_fwd(A, Wt, keep, 4, stride=1.0, out=A, **kw)),
+                (ard.ArdError, lambda: ard.conv_fwd_rows(A, Wt, dict(keep=None, mask=None), 4, out=A, **kw))]:
+            with pytest.raises(error):
+                call()
