@@ -18,6 +18,7 @@
 #include <torch/csrc/Device.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/DynamicTypes.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <string>
@@ -436,8 +437,8 @@ PyObject* guarded(Sig& s, PyObject* const* args, Py_ssize_t nargs, PyObject* kwn
     lib();
     return F(Args(s, args, nargs, kwnames));
   } catch (const PyRaised&) {
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {  // (torch's own: IndexError, OutOfMemoryError and the others keep their Python types)
+    torch::translate_exception_to_python(std::current_exception());
   }
   return nullptr;
 }
@@ -871,8 +872,8 @@ template <class F> PyObject* method(F&& f) {
   try {
     return f();
   } catch (const PyRaised&) {
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {  // (torch's own: IndexError, OutOfMemoryError and the others keep their Python types)
+    torch::translate_exception_to_python(std::current_exception());
   }
   return nullptr;
 }

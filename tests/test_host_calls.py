@@ -188,3 +188,14 @@ def test_what_was_refused_stays_refused():
                 (ard.ArdError, lambda: ard.conv_fwd_rows(A, Wt, dict(keep=None, mask=None), 4, out=A, **kw))]:
             with pytest.raises(error):
                 call()
+
+
+def test_errors_of_torch_keep_their_types():
+    """The workspace a call makes itself: where torch refuses it, the error is the one torch.empty raises."""
+    X, W, Y = fake(64, 128, dtype=torch.bfloat16), fake(256, 128, dtype=torch.bfloat16), fake(64, 256, dtype=torch.bfloat16)
+
+    class Refuse(torch.utils._python_dispatch.TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            raise torch.OutOfMemoryError("no room")
+    with dry_run(), Refuse(), pytest.raises(torch.OutOfMemoryError, match="no room"):
+        ard.drop_gemm_fwd(X, W, out=Y, stream=STREAM)
