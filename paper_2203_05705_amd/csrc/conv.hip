@@ -1670,6 +1670,7 @@ static int32_t conv_run_planes(const ConvArgs& a, const void* A, const void* Wt,
   cy = plane_copy(dYin, nullptr, a.Cout, a.Cout, a.Ho, a.Wo, a.N, ph, pw, g.wa, g.plane_a, g.margin, w.plane_y, a.dy_mask);
   if (int32_t st = launch_copies()) return st;
   cv.Wg = g.wa, cv.plane = g.plane_a, cv.Cp = Cp, cv.Co = pad16(a.Cout);
+  cv.Wo = a.Wo, cv.npix = a.Ho * g.wa, cv.per_row = fast_div((uint32_t)g.wa);
   cv.by_cp = fast_div((uint32_t)Cp), cv.steps_inner = fast_div((uint32_t)(g.plane_a / 16));
   int splits = 1;
   const int cap = (int)(w.plane_part_bytes / ((size_t)a.Cout * taps * Cp * 4));

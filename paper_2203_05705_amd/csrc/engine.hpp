@@ -536,8 +536,8 @@ struct F32Conv {
   int Wg, plane, Cp;   // of the B grid
   int Co;              // weight gradient: channels per image of the gradient's grid
   int kw, taps;
-  int npix;            // forward, data gradient: output pixels over the batch
-  FastDiv per_row, per_img, steps_inner;  // Wo, HoWo, 16-deep contraction steps per tap / (weight gradient) per image
+  int npix;            // forward, data gradient: output pixels over the batch; weight gradient: Ho * Wg
+  FastDiv per_row, per_img, steps_inner;  // Wo / (weight gradient) Wg; HoWo; 16-deep contraction steps per tap / per image
   FastDiv by_cp, by_kw;
 };
 int32_t f32_conv_product(const float* W, int rows, const float* grid, const F32Conv& cv, const OutMat& C, hipStream_t stream);
