@@ -1393,6 +1393,9 @@ static int32_t conv_grid_gemm(const uint16_t* Wp, int rows, int K, const uint16_
   return launch_direct_kernel<true, true, 64, 64, 4, 1>(F, grid, stream);
 }
 
+// Whether the weight gradient can take listed pixels: the kernel multiplies their numbers by 24-bit products (a layer
+// beyond contracts over every pixel of dY's masked grid instead).
+static bool pos_lists_fit(const ConvArgs& a) { return (long)a.N * (a.H + 2 * a.pad) * (a.W + 2 * a.pad) < (1L << 24); }
 // The kept positions of the column blocks of a pattern (bands of x positions, CB blocks), listed in the workspace
 static PosListJob pos_list_job(const ConvArgs& a, const uint8_t* blk, int x, int CB, const ConvWs& w) {
   PosListJob j{};
@@ -1763,7 +1766,7 @@ static int32_t conv_run(const ConvArgs& a, double rate, const void* A, const voi
       full.dy_mask = BandMask{(const uint8_t*)d_mask, a.Ho * a.Wo, 1, 0, 1};
       dy_use = dYin;
       // the weight gradient contracts over the kept positions only
-      if (w.grid_a) full.lists = pos_list_job(a, (const uint8_t*)d_mask, 1, 1, w);
+      if (w.grid_a && pos_lists_fit(a)) full.lists = pos_list_job(a, (const uint8_t*)d_mask, 1, 1, w);
     } else {
       ARD_LAUNCH(iota_kernel, dim3(ceil_div(a.C, 256)), dim3(256), 0, stream, w.all_chan, a.C);
       ARD_LAUNCH_CHECK("iota_kernel");
@@ -1984,9 +1987,10 @@ extern "C" int32_t ard_conv_bwd_blocks(int32_t mode, int32_t dtype, int32_t N, i
   const bool by_groups = w.grid_a && !dev_knobs().no_fast && a.by % (8 * taps) == 0 && CB * (a.by / taps) <= pad64(C) && CB <= w.pos_blocks;
   BlockDataParams bd{};
   const bool one_launch = by_groups && block_data_tiles(a, w, bd);
-  if (by_groups) a.lists = pos_list_job(a, d_block_keep, a.bx, CB, w);
+  const bool listed = by_groups && pos_lists_fit(a);
+  if (listed) a.lists = pos_list_job(a, d_block_keep, a.bx, CB, w);
   if (one_launch && mode == ARD_CONV_BWD_DATA) return conv_block_data(a, bd, Wt, dYin, out, w, s);
-  if (by_groups && mode == ARD_CONV_BWD_WEIGHT) {
+  if (listed && mode == ARD_CONV_BWD_WEIGHT) {
     ConvArgs g = a;
     g.blk = nullptr;
     g.cpb = a.by / taps;

@@ -220,3 +220,25 @@ def test_grouped_launch_of_a_dependency_level():
         assert D.launches(lib)[0] >= 1
         lib.ard_batch_abort()
         assert lib.ard_batch_launch(None) == -1
+
+
+@pytest.mark.parametrize("N,listed", [(328, True), (329, False)])
+def test_pattern_gradients_of_layers_too_large_for_position_lists(N, listed):
+    """64 channels of 224 x 224, 3 x 3: from 2^24 grid pixels (328.5 images) on the weight gradients of the row and block
+    patterns leave the kernel that reads listed pixels for the one that reads them all; none is refused."""
+    C, H, k, pad = 64, 224, 3, 1
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        n = lib.ard_conv_workspace_bytes(D.BF16, N, C, H, H, C, k, k, 1, pad)
+        ws, A, dY, Wt, out, keep = heap(n), heap(N * C * H * H * 2), heap(N * C * H * H * 2), heap(C * C * k * k * 2), heap(N * C * H * H * 2), heap(N * H * H)
+        for mode in (6,):
+            _ok(lib, [lib.ard_fmap_drop_conv(mode, D.BF16, N, C, H, H, C, k, k, 1, pad, 0.0, 0, A, Wt, dY, out, keep, None, None, None, ws, n, None)],
+                f"rows {N} mode {mode}")
+        for mode in (2, 3):
+            D.launches(lib)
+            _ok(lib, [lib.ard_conv_bwd_blocks(mode, D.BF16, N, C, H, H, C, k, k, 1, pad, 4 * H, 64 * k * k, A, Wt, dY, keep, out, ws, n, None)],
+                f"blocks {N} mode {mode}")
+            names = D.launches(lib)[1]
+            if mode == 3:
+                assert ("iota_kernel" in names) == (not listed), names   # (column block by column block, each with its own list of channels)
+        D.last_bounds(lib)
