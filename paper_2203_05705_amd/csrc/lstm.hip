@@ -71,11 +71,11 @@ template <typename T> struct LstmPrepare {
   // for synapses of dropped tiles
   const T* W;
   T *wxc, *whc;
-  const T* h;     // != NULL: hc[r][j] = h[r][unit(j)], `rows` rows
+  const T* h;     // != NULL: hc[r][j] = h[r][unit(j)]
   T* hc;
   const T* x;     // != NULL: xp[r][q] = x[r][q], q < I, padded to Ip
   T* xp;
-  long rows;
+  int w0, w1, h0, h1, x0, x1;   // rows of each job that this launch takes
   int* rank;      // rank[u] = compact index of unit u or -1
   uint4* mark;    // exchange buffer of the recurrence: n16 pieces of kUnwritten
   long n16;
@@ -90,11 +90,11 @@ template <typename T> __global__ __launch_bounds__(256) void lstm_prepare_kernel
   const int tid = threadIdx.x, cx = P.Ip >> 3, ch = P.Hp >> 3;
   T v[8];
   if (b < P.b_w) {
-    const uint32_t e = (uint32_t)b * 256 + tid, nx = (uint32_t)(4 * P.Hp * cx);
+    const uint32_t e = (uint32_t)b * 256 + tid, nx = (uint32_t)(P.w1 - P.w0) * (uint32_t)cx;
     const bool rec = e >= nx;
     const uint32_t f = rec ? e - nx : e;
-    const int r = (int)fdiv(f, rec ? P.by_ch : P.by_cx), q = ((int)f - r * (rec ? ch : cx)) * 8;
-    if (r >= 4 * P.Hp) return;
+    const int rw = (int)fdiv(f, rec ? P.by_ch : P.by_cx), q = (int)(f - (uint32_t)rw * (uint32_t)(rec ? ch : cx)) * 8, r = P.w0 + rw;
+    if (r >= P.w1) return;
     const int g = (int)fdiv((uint32_t)r, P.by_hp), j = r - g * P.Hp;
     const int prow = g * P.H + (j < P.ax.n ? ax_phys(P.ax, j) : 0);
     const T* row = P.W + (long)prow * (P.I + P.H);
@@ -117,9 +117,10 @@ template <typename T> __global__ __launch_bounds__(256) void lstm_prepare_kernel
   b -= P.b_w;
   if (b < P.b_h) {
     const uint32_t e = (uint32_t)b * 256 + tid;
-    const long r = fdiv(e, P.by_ch);
-    if (r >= P.rows) return;
-    const int j = (int)(e - (uint32_t)r * (uint32_t)ch) * 8;
+    const uint32_t rh = fdiv(e, P.by_ch);
+    const long r = P.h0 + (long)rh;
+    if (r >= P.h1) return;
+    const int j = (int)(e - rh * (uint32_t)ch) * 8;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       v[i] = P.h[r * P.H + (j + i < P.ax.n ? ax_phys(P.ax, j + i) : 0)];
@@ -130,9 +131,10 @@ template <typename T> __global__ __launch_bounds__(256) void lstm_prepare_kernel
   b -= P.b_h;
   if (b < P.b_x) {
     const uint32_t e = (uint32_t)b * 256 + tid;
-    const long r = fdiv(e, P.by_cx);
-    if (r >= P.rows) return;
-    const int q = (int)(e - (uint32_t)r * (uint32_t)cx) * 8;
+    const uint32_t rx = fdiv(e, P.by_cx);
+    const long r = P.x0 + (long)rx;
+    if (r >= P.x1) return;
+    const int q = (int)(e - rx * (uint32_t)cx) * 8;
     if (q + 8 <= P.I) {
       lstm_load8(P.x + r * P.I + q, v);
     } else {
@@ -242,14 +244,15 @@ __global__ void lstm_copy_rows_kernel(const T* src, long ld_src, int cols, long 
 }
 
 // dW[(g*H + u)][q] from the compact gradients dwx[4Hp x Ip] and dwh[4Hp x Hp]; +0.0 for every
-// row of a dropped unit, every recurrent column of a dropped unit and every synapse of a dropped tile.
+// row of a dropped unit, every recurrent column of a dropped unit and every synapse of a dropped tile; gate rows p0 .. p1-1.
 // Eight neighbouring columns of a row per thread (one at a time: 20 us where the bytes take 6, 512 of 1024 units).
 template <typename T>
 __global__ __launch_bounds__(256) void lstm_scatter_dw_kernel(const T* dwx, const T* dwh, const int* rank, int H, int I, int Ip, int Hp, LstmTiles tp,
-                                                              FastDiv by_chunks, FastDiv by_h, T* dW) {
+                                                              FastDiv by_chunks, FastDiv by_h, int p0, int p1, T* dW) {
   const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-  const int chunks = (I + H + 7) >> 3, p = (int)fdiv(e, by_chunks), q = (int)(e - (uint32_t)p * (uint32_t)chunks) * 8;  // p: physical gate row
-  if (p >= 4 * H) return;
+  const int chunks = (I + H + 7) >> 3, row = (int)fdiv(e, by_chunks), q = (int)(e - (uint32_t)row * (uint32_t)chunks) * 8;
+  const int p = p0 + row;  // physical gate row
+  if (p >= p1) return;
   const int g = (int)fdiv((uint32_t)p, by_h), j = rank[p - g * H], n = imin(8, I + H - q);
   T v[8];
 #pragma unroll
@@ -1282,6 +1285,13 @@ static GemmParams plain_gemm(const void* A, long lda, const void* B, long ldb, v
   return P;
 }
 
+// Rows of `pieces` 8-element pieces that one job of a launch takes: a launch has less than 2^32 threads, one for each
+// piece of its three jobs, and larger operands go in several.  (ARD_LSTM_PIECES: test hook, fewer pieces per job.)
+static int lstm_rows_per_launch(long pieces) {
+  const long most = getenv("ARD_LSTM_PIECES") ? atol(getenv("ARD_LSTM_PIECES")) : 1L << 30;
+  const long rows = most / (pieces > 0 ? pieces : 1);
+  return (int)(rows < 1 ? 1 : rows < 0x7fffffffL ? rows : 0x7fffffffL);
+}
 // What the recurrence of a pass wants cleared beforehand
 struct LstmMark {
   void* buf;
@@ -1297,20 +1307,25 @@ static int32_t lstm_prepare(const LstmArgs& a, const void* W, const void* x, con
   P.ax = a.ax, P.H = a.H, P.I = a.I, P.Ip = pad8(a.I), P.Hp = pad8(a.Hk), P.tp = a.tiles;
   P.W = (const T*)W, P.wxc = (T*)w.wxc, P.whc = (T*)w.whc;
   P.h = (const T*)h, P.hc = (T*)w.hc;
-  P.rows = (long)a.T * a.B;
   const bool pad = P.Ip != a.I;
   P.x = (const T*)x, P.xp = (T*)w.xp;
   *xo = pad ? (const void*)w.xp : x;
   P.rank = w.rank;
   P.mark = (uint4*)m.buf, P.n16 = m.bytes / 16, P.sync = w.sync, P.n_sync = m.n_sync;  // (exchange rows are whole pieces)
-  P.by_cx = fast_div((uint32_t)P.Ip / 8), P.by_ch = fast_div((uint32_t)P.Hp / 8), P.by_hp = fast_div((uint32_t)P.Hp);
-  const long nw = a.Hk > 0 ? 4L * P.Hp * (P.Ip + P.Hp) / 8 : 0, nh = h && a.Hk > 0 ? P.rows * P.Hp / 8 : 0, nx = pad && a.Hk > 0 ? P.rows * P.Ip / 8 : 0;
-  if (nw >= (1L << 31) || nh >= (1L << 31) || nx >= (1L << 31)) return fail(ARD_ESHAPE, "LSTM operands too large");
-  P.b_w = (int)((nw + 255) / 256), P.b_h = (int)((nh + 255) / 256), P.b_x = (int)((nx + 255) / 256);
+  const int cx = P.Ip / 8, ch = P.Hp / 8, rows = a.Hk > 0 ? a.T * a.B : 0;
+  P.by_cx = fast_div((uint32_t)cx), P.by_ch = fast_div((uint32_t)ch), P.by_hp = fast_div((uint32_t)P.Hp);
   const long blocks = P.n16 || P.n_sync ? (P.n16 > P.n_sync ? P.n16 : P.n_sync) / 256 + 1 : 0;
   P.b_mark = (int)(blocks < 2048 ? blocks : 2048);
-  ARD_LAUNCH(lstm_prepare_kernel<T>, dim3((unsigned)(P.b_w + P.b_h + P.b_x + P.b_mark + 1)), dim3(256), 0, stream, P);
-  ARD_LAUNCH_CHECK("lstm_prepare_kernel");
+  const int nw = a.Hk > 0 ? 4 * P.Hp : 0, nh = h ? rows : 0, nx = pad ? rows : 0;
+  const int step_w = lstm_rows_per_launch(cx + ch), step_h = lstm_rows_per_launch(ch), step_x = lstm_rows_per_launch(cx);
+  do {
+    P.w1 = nw - P.w0 < step_w ? nw : P.w0 + step_w, P.h1 = nh - P.h0 < step_h ? nh : P.h0 + step_h, P.x1 = nx - P.x0 < step_x ? nx : P.x0 + step_x;
+    P.b_w = (int)(((long)(P.w1 - P.w0) * (cx + ch) + 255) / 256), P.b_h = (int)(((long)(P.h1 - P.h0) * ch + 255) / 256);
+    P.b_x = (int)(((long)(P.x1 - P.x0) * cx + 255) / 256);
+    ARD_LAUNCH(lstm_prepare_kernel<T>, dim3((unsigned)(P.b_w + P.b_h + P.b_x + P.b_mark + 1)), dim3(256), 0, stream, P);
+    ARD_LAUNCH_CHECK("lstm_prepare_kernel");
+    P.w0 = P.w1, P.h0 = P.h1, P.x0 = P.x1, P.b_mark = 0;
+  } while (P.w0 < nw || P.h0 < nh || P.x0 < nx);
   return ARD_OK;
 }
 
@@ -1588,11 +1603,13 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     }
     if (st) return st;
   }
-  const int chunks = (I + H + 7) / 8;
-  if (4L * H * chunks >= (1L << 31)) return fail(ARD_ESHAPE, "weight gradient too large for one pass");
-  ARD_LAUNCH(lstm_scatter_dw_kernel<T>, dim3((unsigned)((4L * H * chunks + 255) / 256)), dim3(256), 0, stream, (const T*)w.dwx, (const T*)w.dwh,
-             (const int*)w.rank, H, I, Ip, Hp, a.tiles, fast_div((uint32_t)chunks), fast_div((uint32_t)H), (T*)dW);
-  ARD_LAUNCH_CHECK("lstm_scatter_dw_kernel");
+  const int chunks = (I + H + 7) / 8, step = lstm_rows_per_launch(chunks);
+  for (int p0 = 0, p1; p0 < 4 * H; p0 = p1) {
+    p1 = 4 * H - p0 < step ? 4 * H : p0 + step;
+    ARD_LAUNCH(lstm_scatter_dw_kernel<T>, dim3((unsigned)(((long)(p1 - p0) * chunks + 255) / 256)), dim3(256), 0, stream, (const T*)w.dwx,
+               (const T*)w.dwh, (const int*)w.rank, H, I, Ip, Hp, a.tiles, fast_div((uint32_t)chunks), fast_div((uint32_t)H), p0, p1, (T*)dW);
+    ARD_LAUNCH_CHECK("lstm_scatter_dw_kernel");
+  }
   return ARD_OK;
 }
 

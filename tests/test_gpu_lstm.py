@@ -181,3 +181,15 @@ def test_config4_lstm_layer_tile_pattern_full_size(dp, b):
     print(f"config 4 tile dp={dp} b={b}: running oracle (fp64) ...", flush=True)
     errs = _check_tile("bf16", wl.values("x"), wl.values("W"), wl.values("dh"), (64, 64, dp, b), "config4 tile")
     print("config 4 tile max rel err (h, c, gates, dx, dW):", ["%.2e" % e for e in errs], flush=True)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("pieces", [1, 7, 100])
+def test_lstm_operands_in_several_launches(dtype, pieces, monkeypatch):
+    """Gathers and scatter taken a few rows per launch (as operands of more than 2^30 pieces are)."""
+    monkeypatch.setenv("ARD_LSTM_PIECES", str(pieces))
+    T, B, I, H, dp = 3, 5, 21, 20, 2
+    rng = np.random.default_rng(pieces)
+    x, dh = (stored(rng.standard_normal(s), dtype) for s in ((T, B, I), (T, B, H)))
+    W = stored(rng.uniform(-0.2, 0.2, (4 * H, I + H)), dtype)
+    _check(dtype, x, W, dh, P.row_mask(H, dp, 2), ard.Pattern.row(dp, 2), *(from_vals(v, dtype) for v in (x, W, dh)), f"lstm {dtype} {pieces} pieces")

@@ -242,3 +242,19 @@ def test_pattern_gradients_of_layers_too_large_for_position_lists(N, listed):
             if mode == 3:
                 assert ("iota_kernel" in names) == (not listed), names   # (column block by column block, each with its own list of channels)
         D.last_bounds(lib)
+
+
+@pytest.mark.parametrize("dtype", [D.F32, D.BF16])
+def test_lstm_operands_beyond_one_launch(dtype):
+    """A fused weight of 65532 x 316383: gathering it and scattering its gradient take several launches, and neither
+    pass is refused (least of all after its other kernels have been enqueued)."""
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        D.launches(lib)
+        _ok(lib, D.lstm_calls(lib, heap, dtype, 2, 8, 300000, 16383, (2, 1)), "wide lstm")
+        names = D.launches(lib)[1]
+        assert names.count("lstm_prepare_kernel") == 4 and names.count("lstm_scatter_dw_kernel") == 3, names
+        _ok(lib, D.lstm_calls(lib, heap, dtype, 3, 8, 30, 40, (2, 1)), "small lstm")
+        names = D.launches(lib)[1]
+        assert names.count("lstm_prepare_kernel") == 2 and names.count("lstm_scatter_dw_kernel") == 1, names
+        D.last_bounds(lib)
