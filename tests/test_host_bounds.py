@@ -258,3 +258,15 @@ def test_lstm_operands_beyond_one_launch(dtype):
         names = D.launches(lib)[1]
         assert names.count("lstm_prepare_kernel") == 2 and names.count("lstm_scatter_dw_kernel") == 1, names
         D.last_bounds(lib)
+
+
+def test_lstm_shapes_reach_the_recurrences_their_gpu_tests_name():
+    from test_gpu_lstm_staged import BEYOND_BWD, BEYOND_FWD
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        for shapes, kernel in ((BEYOND_FWD, "lstm_persist_fwd_kernel"), (BEYOND_BWD, "lstm_persist_bwd_kernel")):
+            for T, B, H in shapes:
+                D.launches(lib)
+                _ok(lib, D.lstm_calls(lib, heap, D.BF16, T, B, 16, H, (1, 1)), f"lstm {T} {B} {H}")
+                assert kernel in D.launches(lib)[1], (kernel, T, B, H)
+        D.last_bounds(lib)
