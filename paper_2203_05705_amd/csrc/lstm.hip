@@ -1457,10 +1457,10 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
       ARD_LAUNCH_NAMED("lstm_persist_fwd_kernel", kernel, grid, dim3(256), lds, stream, P);
       return ARD_OK;
     };
-    const bool deep = Hp > 512;  // (slices of a wavefront: one round trip for up to 1024 kept units)
+    // (tmb == 1: more than 1024 kept units, the staged kernel takes fewer)
     if (pp.via_l2) st = tmb == 1 ? launch(lstm_persist_fwd_kernel<1, true, 8>) : tmb == 2 ? launch(lstm_persist_fwd_kernel<2, true, 8>)
                                                                                              : launch(lstm_persist_fwd_kernel<4, true, 4>);
-    else st = tmb == 1 ? (deep ? launch(lstm_persist_fwd_kernel<1, false, 16>) : launch(lstm_persist_fwd_kernel<1, false, 8>))
+    else st = tmb == 1 ? launch(lstm_persist_fwd_kernel<1, false, 16>)
               : tmb == 2 ? launch(lstm_persist_fwd_kernel<2, false, 8>) : launch(lstm_persist_fwd_kernel<4, false, 4>);
     if (st) return st;
     ARD_LAUNCH_CHECK("lstm_persist_fwd_kernel");
