@@ -9,6 +9,7 @@ from oracle import patterns as P
 from oracle import rounding as R
 from paper_2203_05705_amd import binding as ard
 from paper_2203_05705_amd import workloads as WL
+from test_gpu_gemm import _run_row_case
 from util import assert_parity, from_vals, stored, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
@@ -332,3 +333,12 @@ def test_weight_gradient_through_the_finishing_pass(B, O, I, po, pi):
     ard.drop_gemm_bwd_weight(compact_in(dYv[:, ko], dtype), compact_in(Xv[:, ki], dtype), ard.Pattern.row(*po),
                              ard.Pattern.row(*pi) if pi else None, flags=ard.IN_COMPACT | ard.OUT_COMPACT, out=dW, I=I, O=O)
     assert_parity(dW, refdW, dtype, zero_mask=(MW == 0), what="dW")
+
+
+@pytest.mark.parametrize("po,pi", [((2, 1), (7, 7)), ((2, 2), (8, 8)), (None, (9, 4)), ((9, 9), None), ((11, 2), (8, 1)), ((3, 1), (16, 5)),
+                                   ((8, 3), (23, 23))])
+def test_outputs_scattered_at_wide_steps(po, pi):
+    """Outputs with dropped columns at the periods where the kernel's own scatter (up to 8) gives way to the pass over
+    partial sums; enough kept tiles for either, extents that are no multiples of the period."""
+    _run_row_case("bf16", 1030, 4001, 1100, po, pi, relu=po is not None, use_relu_src=pi is not None, seed=7)
+    _run_row_case("bf16", 1024, 4000, 1104, po, pi, seed=8)
