@@ -929,9 +929,10 @@ PyObject* pattern_tile(PyObject* cls, PyObject* const* args, Py_ssize_t nargs, P
   });
 }
 PyMethodDef pattern_methods[] = {
-    {"row", (PyCFunction)(void (*)(void))pattern_row, METH_CLASS | METH_FASTCALL | METH_KEYWORDS, "row(dp, b): every dp-th unit from the b-th on is kept"},
+    {"row", (PyCFunction)(void (*)(void))pattern_row, METH_CLASS | METH_FASTCALL | METH_KEYWORDS,
+     "row($type, dp, b)\n--\n\nEvery dp-th unit from the b-th on is kept."},
     {"tile", (PyCFunction)(void (*)(void))pattern_tile, METH_CLASS | METH_FASTCALL | METH_KEYWORDS,
-     "tile(dp, b, tile_r, tile_c, lists=None): every dp-th tile of the weight from the b-th on is kept"},
+     "tile($type, dp, b, tile_r, tile_c, lists=None)\n--\n\nEvery dp-th tile of the weight from the b-th on is kept."},
     {nullptr, nullptr, 0, nullptr}};
 
 // ---- module -----------------------------------------------------------------------------------
@@ -977,42 +978,43 @@ PyObject* py_set_allocator(PyObject*, PyObject* fn) {
   Py_RETURN_NONE;
 }
 
+// (the first line of a documentation, up to --, is what inspect.signature reads)
 #define ENTRY(name, doc) {#name, (PyCFunction)(void (*)(void))py_##name, METH_FASTCALL | METH_KEYWORDS, doc}
 PyMethodDef methods[] = {
-    ENTRY(compact_weight, "compact_weight(W, pat_out=None, pat_in=None, out=None, stream=None)\n"
+    ENTRY(compact_weight, "compact_weight($module, W, pat_out=None, pat_in=None, out=None, stream=None)\n--\n\n"
                           "Wc[pad8(O') x pad8(I')]: W[kept o, kept i] in the top-left corner, zeros elsewhere."),
-    ENTRY(drop_gemm_fwd, "drop_gemm_fwd(X, W, pat_out=None, pat_in=None, alpha=1.0, relu=False, flags=0, out=None, ws=None, stream=None, I=None, O=None)\n"
+    ENTRY(drop_gemm_fwd, "drop_gemm_fwd($module, X, W, pat_out=None, pat_in=None, alpha=1.0, relu=False, flags=0, out=None, ws=None, stream=None, I=None, O=None)\n--\n\n"
                          "Y = X . W^T under the patterns.  With layout flags pass the full sizes I / O explicitly."),
-    ENTRY(drop_gemm_bwd_data, "drop_gemm_bwd_data(dY, W, pat_out=None, pat_in=None, alpha=1.0, relu_src=None, flags=0, out=None, ws=None, stream=None, "
-                              "I=None, O=None)\ndX = dY . W under the patterns."),
-    ENTRY(drop_gemm_bwd_weight, "drop_gemm_bwd_weight(dY, X, pat_out=None, pat_in=None, alpha=1.0, beta=0.0, flags=0, out=None, ws=None, stream=None, "
-                                "I=None, O=None)\ndW = dY^T . X under the patterns."),
-    ENTRY(drop_gemm_bwd_weight_static, "drop_gemm_bwd_weight_static(dY, X, pat_out, pat_in, out, alpha=1.0, beta=0.0, flags=0, stream=None, I=None, O=None)\n"
+    ENTRY(drop_gemm_bwd_data, "drop_gemm_bwd_data($module, dY, W, pat_out=None, pat_in=None, alpha=1.0, relu_src=None, flags=0, out=None, ws=None, stream=None, "
+                              "I=None, O=None)\n--\n\ndX = dY . W under the patterns."),
+    ENTRY(drop_gemm_bwd_weight, "drop_gemm_bwd_weight($module, dY, X, pat_out=None, pat_in=None, alpha=1.0, beta=0.0, flags=0, out=None, ws=None, stream=None, "
+                                "I=None, O=None)\n--\n\ndW = dY^T . X under the patterns."),
+    ENTRY(drop_gemm_bwd_weight_static, "drop_gemm_bwd_weight_static($module, dY, X, pat_out, pat_in, out, alpha=1.0, beta=0.0, flags=0, stream=None, I=None, O=None)\n--\n\n"
                                        "The weight gradient on the library's own scratch: the caller passes every tensor, output included, and nothing is "
                                        "allocated here or in the library."),
-    ENTRY(lstm_fwd, "lstm_fwd(x, W, pat=None, ws=None, stream=None, out=None)\n"
+    ENTRY(lstm_fwd, "lstm_fwd($module, x, W, pat=None, ws=None, stream=None, out=None)\n--\n\n"
                     "x[T,B,I], W[4H, I+H] -> (h[T,B,H] dtype, c[T,B,H] fp32, gates[T,B,4H] fp32); out: reuse such a triple."),
-    ENTRY(lstm_bwd, "lstm_bwd(x, W, pat, h, c, gates, dh, ws=None, stream=None, out=None)\n"
+    ENTRY(lstm_bwd, "lstm_bwd($module, x, W, pat, h, c, gates, dh, ws=None, stream=None, out=None)\n--\n\n"
                     "Returns (dx[T,B,I], dW[4H, I+H]) in the storage dtype; out: reuse such a pair."),
-    ENTRY(conv_select, "conv_select(A, rate, Cout=1, ksize=(3, 3), stride=1, pad=1, ws=None, stream=None, out=None)\n"
+    ENTRY(conv_select, "conv_select($module, A, rate, Cout=1, ksize=(3, 3), stride=1, pad=1, ws=None, stream=None, out=None)\n--\n\n"
                        "Sensitivity scores and channel selection: dict(mask, keep, count, score) (out: reuse such a dict)."),
-    ENTRY(conv_fwd, "conv_fwd(A, Wt, keep, n_keep, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0)"),
-    ENTRY(conv_bwd_data, "conv_bwd_data(dY, Wt, keep, n_keep, in_hw, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0)"),
-    ENTRY(conv_bwd_weight, "conv_bwd_weight(dY, A, keep, n_keep, ksize=(3, 3), stride=1, pad=1, ws=None, stream=None, out=None, reuse=0)"),
-    ENTRY(conv_fwd_rows, "conv_fwd_rows(A, Wt, row_pat, n_keep, stride=1, pad=1, ws=None, stream=None, out=None)\n"
+    ENTRY(conv_fwd, "conv_fwd($module, A, Wt, keep, n_keep, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0)\n--\n\n"),
+    ENTRY(conv_bwd_data, "conv_bwd_data($module, dY, Wt, keep, n_keep, in_hw, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0)\n--\n\n"),
+    ENTRY(conv_bwd_weight, "conv_bwd_weight($module, dY, A, keep, n_keep, ksize=(3, 3), stride=1, pad=1, ws=None, stream=None, out=None, reuse=0)\n--\n\n"),
+    ENTRY(conv_fwd_rows, "conv_fwd_rows($module, A, Wt, row_pat, n_keep, stride=1, pad=1, ws=None, stream=None, out=None)\n--\n\n"
                          "Forward convolution over the kept output positions of a row pattern (dict from sens_row_pattern)."),
-    ENTRY(conv_bwd_rows, "conv_bwd_rows(dY, A, Wt, row_pat, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0)\n"
+    ENTRY(conv_bwd_rows, "conv_bwd_rows($module, dY, A, Wt, row_pat, stride=1, pad=1, ws=None, stream=None, out=None, reuse=0)\n--\n\n"
                          "Gradients (dA, dWt) of conv_fwd_rows: gradient arriving on dropped output positions counts as zero.\n"
                          "reuse: CONV_REUSE_* flags for the weight gradient (grids that conv_fwd_rows and the data gradient left in ws)."),
-    ENTRY(conv_fwd_blocks, "conv_fwd_blocks(A, Wt, block_keep, x, y, stride=1, pad=1, ws=None, stream=None, out=None)\n"
+    ENTRY(conv_fwd_blocks, "conv_fwd_blocks($module, A, Wt, block_keep, x, y, stride=1, pad=1, ws=None, stream=None, out=None)\n--\n\n"
                            "Forward convolution under a block pattern (block_keep from sens_block_pattern, uint8 [N*RB*CB])."),
-    ENTRY(conv_bwd_blocks, "conv_bwd_blocks(dY, A, Wt, block_keep, x, y, stride=1, pad=1, ws=None, stream=None, out=None)\n"
+    ENTRY(conv_bwd_blocks, "conv_bwd_blocks($module, dY, A, Wt, block_keep, x, y, stride=1, pad=1, ws=None, stream=None, out=None)\n--\n\n"
                            "Gradients (dA, dWt) of conv_fwd_blocks."),
-    ENTRY(sens_predict, "sens_predict(A, ksize, stride, pad, x, y, k_permille, t_permille, threshold, seed, iteration, stream=None)\n"
+    ENTRY(sens_predict, "sens_predict($module, A, ksize, stride, pad, x, y, k_permille, t_permille, threshold, seed, iteration, stream=None)\n--\n\n"
                         "Region-level sensitivity prediction: dict(count, samples, sens), each [N, RB, CB] on the device."),
-    ENTRY(sens_row_pattern, "sens_row_pattern(sens, rows, x, m, n, seed, iteration, stream=None)\n"
+    ENTRY(sens_row_pattern, "sens_row_pattern($module, sens, rows, x, m, n, seed, iteration, stream=None)\n--\n\n"
                             "Row-based pattern from the per-band sensitivity sens[N, RB, 1]: dict(mask[N*rows], keep, count)."),
-    ENTRY(sens_block_pattern, "sens_block_pattern(pred, balance, m, n, seed, iteration, stream=None)\n"
+    ENTRY(sens_block_pattern, "sens_block_pattern($module, pred, balance, m, n, seed, iteration, stream=None)\n--\n\n"
                               "Block-based pattern from ard_sens_predict's outputs: dict(sens (balanced), keep), each [N, RB, CB]."),
     {"configure", py_configure, METH_VARARGS, nullptr},
     {"set_allocator", py_set_allocator, METH_O, nullptr},
@@ -1023,6 +1025,7 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_ardcall", "Calls into libard.
 
 PyMODINIT_FUNC PyInit__ardcall(void) {
   PatternType.tp_name = "paper_2203_05705_amd._ardcall.PatternBase";
+  PatternType.tp_doc = "PatternBase(kind=0, dp=1, b=1, tile_r=0, tile_c=0, keep=None, count=None, lists=None)\n--\n\nThe fields of a Pattern.";
   PatternType.tp_basicsize = sizeof(PatternObject);
   PatternType.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_BASETYPE | Py_TPFLAGS_HAVE_GC;
   PatternType.tp_new = pattern_new;
@@ -1033,7 +1036,7 @@ PyMODINIT_FUNC PyInit__ardcall(void) {
   PatternType.tp_members = pattern_members;
   PatternType.tp_methods = pattern_methods;
   BatchType.tp_name = "paper_2203_05705_amd._ardcall.batch";
-  BatchType.tp_doc = "batch(stream=None): context manager; the library calls made inside are recorded and issued as one grouped launch on\n"
+  BatchType.tp_doc = "batch(stream=None)\n--\n\nContext manager: the library calls made inside are recorded and issued as one grouped launch on\n"
                      "leaving it (they must be independent of each other and use separate workspaces).";
   BatchType.tp_basicsize = sizeof(BatchObject);
   BatchType.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_BASETYPE;

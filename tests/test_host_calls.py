@@ -1,6 +1,7 @@
 """The calls of the extension _ardcall on tensors without memory behind them, in dry-run mode: what they accept, what
 they refuse and how, without a GPU."""
 import copy
+import inspect
 import os
 import pickle
 import subprocess
@@ -199,3 +200,26 @@ def test_errors_of_torch_keep_their_types():
             raise torch.OutOfMemoryError("no room")
     with dry_run(), Refuse(), pytest.raises(torch.OutOfMemoryError, match="no room"):
         ard.drop_gemm_fwd(X, W, out=Y, stream=STREAM)
+
+
+def test_signatures_can_be_read():
+    """What help(), editors and wrappers that look at a function's parameters see."""
+    gemm = "pat_out=None, pat_in=None, alpha=1.0, {}flags=0, out=None, ws=None, stream=None, I=None, O=None"
+    conv = "stride=1, pad=1, ws=None, stream=None, out=None"
+    want = dict(
+        compact_weight="W, pat_out=None, pat_in=None, out=None, stream=None", drop_gemm_fwd="X, W, " + gemm.format("relu=False, "),
+        drop_gemm_bwd_data="dY, W, " + gemm.format("relu_src=None, "), drop_gemm_bwd_weight="dY, X, " + gemm.format("beta=0.0, "),
+        drop_gemm_bwd_weight_static="dY, X, pat_out, pat_in, out, alpha=1.0, beta=0.0, flags=0, stream=None, I=None, O=None",
+        lstm_fwd="x, W, pat=None, ws=None, stream=None, out=None", lstm_bwd="x, W, pat, h, c, gates, dh, ws=None, stream=None, out=None",
+        conv_select="A, rate, Cout=1, ksize=(3, 3), " + conv, conv_fwd="A, Wt, keep, n_keep, " + conv + ", reuse=0",
+        conv_bwd_data="dY, Wt, keep, n_keep, in_hw, " + conv + ", reuse=0",
+        conv_bwd_weight="dY, A, keep, n_keep, ksize=(3, 3), " + conv + ", reuse=0", conv_fwd_rows="A, Wt, row_pat, n_keep, " + conv,
+        conv_bwd_rows="dY, A, Wt, row_pat, " + conv + ", reuse=0", conv_fwd_blocks="A, Wt, block_keep, x, y, " + conv,
+        conv_bwd_blocks="dY, A, Wt, block_keep, x, y, " + conv,
+        sens_predict="A, ksize, stride, pad, x, y, k_permille, t_permille, threshold, seed, iteration, stream=None",
+        sens_row_pattern="sens, rows, x, m, n, seed, iteration, stream=None", sens_block_pattern="pred, balance, m, n, seed, iteration, stream=None",
+        batch="stream=None", Pattern="kind=0, dp=1, b=1, tile_r=0, tile_c=0, keep=None, count=None, lists=None")
+    for name, params in want.items():
+        assert str(inspect.signature(getattr(ard, name))) == f"({params})", name
+    assert str(inspect.signature(ard.Pattern.row)) == "(dp, b)"
+    assert str(inspect.signature(ard.Pattern.tile)) == "(dp, b, tile_r, tile_c, lists=None)"
