@@ -43,9 +43,9 @@ REPEATS = 5              # the block of `steps` timed iterations is repeated; me
 # kernel of the call (the product alone or grouped with the pass that zeroes dropped rows, the finishing pass
 # where the pattern needs one), as its time is; the other two: the product kernel, per launch.
 TRAFFIC = {
-    "L2.bwd_weight": (20423402, "profiles/hbm_traffic_L2_bwd_weight.txt"),
-    "C3.fwd.dp2": (151189085, "profiles/hbm_traffic_config3_fwd_dp2.txt"),
-    "C5.fwd": (90894338, "profiles/hbm_traffic_config5_conv_fwd.txt"),
+    "L2.bwd_weight": (20429416, "profiles/hbm_traffic_L2_bwd_weight.txt"),
+    "C3.fwd.dp2": (151214912, "profiles/hbm_traffic_config3_fwd_dp2.txt"),
+    "C5.fwd": (90898275, "profiles/hbm_traffic_config5_conv_fwd.txt"),
 }
 
 
@@ -678,10 +678,10 @@ def extra_conv(ard, torch, rooflines):
                                           fwd_speedup_vs_all_rows=round(dense_fwd / t_fwd, 3),
                                           fwd_speedup_with_prediction=round(dense_fwd / (t_fwd + t_pred + t_pat), 3),
                                           bwd_data_plus_weight_us=round(t_rbwd, 1),
-                                          bwd_passes="the ordinary passes, dY's dropped positions zeroed while it is copied into its grid (no work skipped)")
+                                          bwd_passes="data gradient: the ordinary pass on a dY whose dropped positions are zeroed while it is copied; weight gradient: over the kept positions only")
     # the block-based pattern of Section 5.2.2 on the same layer: blocks of 112 output positions (four rows) by one
-    # 64-channel group over all taps, balanced groups; the forward pass skips the dropped blocks, the gradients run
-    # the ordinary passes once per column block on a dY whose positions in that block's dropped bands are zeroed
+    # 64-channel group over all taps, balanced groups; the forward pass skips the dropped blocks, so do the
+    # gradients (one launch each over all column blocks)
     x, by = 112, 576
     predb = ard.sens_predict(A, (3, 3), 1, 1, x, by, 300, 500, 0.5, 5, 0)
     bp = ard.sens_block_pattern(predb, 1, 0.3, 0.7, 5, 0)
@@ -697,7 +697,7 @@ def extra_conv(ard, torch, rooflines):
                                             fwd_speedup_vs_all_blocks=round(dense_fwd / t_bfwd, 3),
                                             fwd_speedup_with_prediction=round(dense_fwd / (t_bfwd + t_predb + t_bpat), 3),
                                             bwd_data_plus_weight_us=round(t_bbwd, 1), blocks="112 x 576",
-                                            bwd_passes="one ordinary pass per column block, dY masked while it is copied into its grid (no work skipped)")
+                                            bwd_passes="one launch each over all column blocks: filter rows without a kept band are left out, the weight gradient runs over the kept positions only")
     Ag, Wg = A.clone().requires_grad_(True), Wt.clone().requires_grad_(True)
     Y = F.conv2d(Ag, Wg, padding=1)
     res["vendor_dense_us"] = dict(fwd=round(event_us(torch, lambda: F.conv2d(A, Wt, padding=1))["median"], 1),
