@@ -334,6 +334,7 @@ struct LstmPersist {
   int T, B, H, Hk, Hp, S;
   int off, step;       // kept unit j is physical unit off + j * step
   long spin_limit;
+  int spread;          // (a block per XCD) test hook: stores as if its workgroups were on several
 };
 
 // VIA_L2: h_{t-1} is read through the XCD's L2 after an agent-scope acquire (else with device-scope loads)
@@ -608,7 +609,8 @@ struct LstmPersistBwd {
   int T, B, H, Hk, Hp, S, UW;
   int off, step;        // kept unit j is physical unit off + j * step
   long spin_limit;
-  char* ex;             // staging wavefronts: [T][batch block][unit slice] blocks the workgroups exchange
+  char* ex;             // staging wavefronts, a block per XCD: [T][batch block][unit slice] blocks the workgroups exchange
+  int spread;           // as in LstmPersist
 };
 
 template <int TM16, bool VIA_L2, int CH>
@@ -1167,6 +1169,12 @@ __global__ __launch_bounds__(512) void lstm_staged_bwd_kernel(const LstmPersistB
   }
 }
 
+}  // namespace ard
+
+#include "lstm_xcd.hpp"
+
+namespace ard {
+
 static int lstm_cu_count() {
   static int cus = -1;
   if (cus < 0) {
@@ -1211,8 +1219,9 @@ static LstmWs lstm_ws_layout(char* base, int es, int T, int B, int I, int H, int
   w.xp = (int)Ip != I ? take((size_t)T * B * Ip * es) : nullptr;
   w.dxp = (int)Ip != I ? take((size_t)T * B * Ip * es) : nullptr;
   w.whc = take(4 * Hp * Hp * es);
-  // (exchange blocks of the recurrences: whole blocks of 32 or 16 rows and 16 units)
-  const size_t B32 = ((size_t)B + 31) / 32 * 32, B16 = ((size_t)B + 15) / 16 * 16, H16 = (Hp + 15) / 16 * 16;
+  // (exchange blocks of the recurrences: whole blocks of 32 or 16 rows and 16 or 24 units)
+  const size_t B32 = ((size_t)B + 31) / 32 * 32, B16 = ((size_t)B + 15) / 16 * 16, H24 = (Hp + 23) / 24 * 24;
+  const size_t H16 = (Hp + 15) / 16 * 16 > H24 ? (Hp + 15) / 16 * 16 : H24;
   w.hc = take((size_t)T * B32 * H16 * es);
   w.big = take((size_t)T * B16 * 4 * H16 * 4);
   w.ex = w.big ? w.big + (size_t)T * B16 * 4 * H16 * 2 : nullptr;
@@ -1226,7 +1235,7 @@ static LstmWs lstm_ws_layout(char* base, int es, int T, int B, int I, int H, int
   w.part_bytes = big * 4 * 8;
   if (w.part_bytes > ((size_t)256 << 20)) w.part_bytes = (size_t)256 << 20;
   w.part = take(w.part_bytes);
-  w.sync = (int*)take(((size_t)pad8(Hk) / 8 * ((size_t)B / 32 + 1) + 8) * 4);
+  w.sync = (int*)take(((size_t)pad8(Hk) / 8 * ((size_t)B / 32 + 1) + 8 + kLxBlocks * kLxSeats) * 4);
   w.total = off;
   return w;
 }
@@ -1344,6 +1353,18 @@ static bool lstm_staged_bwd(const LstmArgs& a) {
          (long)ceil_div(Hp, 16) * ceil_div(a.B, 16) <= lstm_cu_count();
 }
 
+// The recurrences with a batch block per XCD: kept units per workgroup (0: not taken).  A block has at most the 32 CUs of
+// an XCD, so the recurrent weights of its workgroups, in registers, end the range at 768 kept units, and eight blocks of
+// 16 rows at a batch of 128.
+static int lstm_xcd_units(const LstmArgs& a) {
+  const int Hp = pad8(a.Hk);
+  if (a.dtype != ARD_BF16 || a.Hk <= 0 || a.T <= 1 || a.ax.kind != AX_AFFINE || getenv("ARD_NO_PERSIST")) return 0;
+  if (a.B > 16 * kLxBlocks || Hp > 24 * kLxSeats || lstm_cu_count() < kLxBlocks * kLxSeats) return 0;
+  return Hp <= 16 * kLxSeats ? 16 : 24;
+}
+
+static int lstm_xcd_rows(int B) { return B <= 8 * kLxBlocks ? 8 : 16; }
+
 // Does the forward pass of this layer run its recurrence in one launch, and how?  (bf16, affine pattern,
 // at most one workgroup per CU, bounded exchange traffic)
 struct PersistPlan {
@@ -1407,11 +1428,13 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
                           const LstmWs& w, hipStream_t stream) {
   const int T_ = a.T, B = a.B, I = a.I, H = a.H, Hk = a.Hk, Hp = pad8(Hk), ce = 16 / a.es;
   // the whole recurrence in one launch when all of its workgroups fit on the chip together
-  const int staged = std::is_same<T, uint16_t>::value ? lstm_staged_fwd_units(a) : 0;
+  const int xcd = std::is_same<T, uint16_t>::value ? lstm_xcd_units(a) : 0, rb = lstm_xcd_rows(B);
+  const int staged = !xcd && std::is_same<T, uint16_t>::value ? lstm_staged_fwd_units(a) : 0;
   PersistPlan pp;
-  const bool persist = !staged && std::is_same<T, uint16_t>::value && lstm_persist_plan(a, pp);
+  const bool persist = !xcd && !staged && std::is_same<T, uint16_t>::value && lstm_persist_plan(a, pp);
   LstmMark mark{};
-  if (staged) mark = LstmMark{w.hc, (long)(T_ - 1) * ceil_div(B, 32) * ceil_div(Hp, staged) * 64 * staged, 1};
+  if (xcd) mark = LstmMark{w.hc, (long)(T_ - 1) * ceil_div(B, rb) * ceil_div(Hp, xcd) * rb * xcd * 2, 1 + kLxBlocks * kLxSeats};
+  else if (staged) mark = LstmMark{w.hc, (long)(T_ - 1) * ceil_div(B, 32) * ceil_div(Hp, staged) * 64 * staged, 1};
   else if (persist) mark = LstmMark{w.hc, pp.via_l2 ? 0 : (long)(T_ - 1) * B * Hp * 2, pp.S * pp.nbb + 1};
   const void* xs;
   int32_t st = lstm_prepare<T>(a, W, x, nullptr, mark, w, stream, &xs);
@@ -1423,6 +1446,24 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     GemmParams P = plain_gemm(xs, Ip, w.wxc, Ip, Gx, 4 * Hp, T_ * B, 4 * Hp, Ip, true, true, ce, true, 0.0f);
     st = run_gemm(a.dtype, true, true, P, 0, 0, stream, w.part, w.part_bytes);
     if (st) return st;
+  }
+  if (xcd) {
+    const int S = ceil_div(Hp, xcd);
+    const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
+    LstmPersist P{Gx, (const uint16_t*)w.whc, (uint16_t*)w.hc, (uint16_t*)h, c, gates, w.sync + 1, w.sync, T_, B, H, Hk, Hp, S,
+                  a.ax.off, a.ax.step, spin_limit, getenv("ARD_LSTM_SPREAD") ? 1 : 0};
+    const int waves = lx_fwd_waves(xcd);
+    const size_t lds = (size_t)2 * waves * rb * xcd * 16;
+    auto launch = [&](auto kernel) -> int32_t {
+      if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
+      ARD_LAUNCH_NAMED("lstm_xcd_fwd_kernel", kernel, dim3((unsigned)(kLxBlocks * S)), dim3(64 * (waves + 4)), lds, stream, P);
+      return ARD_OK;
+    };
+    if (rb == 8) st = xcd == 24 ? launch(lstm_xcd_fwd_kernel<8, 24, 3>) : Hp <= 256 ? launch(lstm_xcd_fwd_kernel<8, 16, 2>) : launch(lstm_xcd_fwd_kernel<8, 16, 4>);
+    else st = xcd == 24 ? launch(lstm_xcd_fwd_kernel<16, 24, 3>) : Hp <= 256 ? launch(lstm_xcd_fwd_kernel<16, 16, 2>) : launch(lstm_xcd_fwd_kernel<16, 16, 4>);
+    if (st) return st;
+    ARD_LAUNCH_CHECK("lstm_xcd_fwd_kernel");
+    return ARD_OK;
   }
   if (staged) {
     const int S = ceil_div(Hp, staged), kw = (int)align_up((size_t)ceil_div(Hp, 64), 4);
@@ -1504,11 +1545,13 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     return fill_matrix(a.dtype, dW, (long)4 * H * (I + H), 0.0f, stream);
   }
   PersistBwdPlan bp;
+  const int xcd = std::is_same<T, uint16_t>::value && lstm_staged_bwd(a) ? lstm_xcd_units(a) : 0, rb = lstm_xcd_rows(B);
   const bool staged = std::is_same<T, uint16_t>::value && lstm_staged_bwd(a);
   const bool one_launch = staged || (std::is_same<T, uint16_t>::value && lstm_persist_bwd_plan(a, bp));
   const long step_bytes = (long)B * 4 * Hp * 2;
   LstmMark mark{};  // (dG_0 is waited for by nobody)
-  if (staged) mark = LstmMark{w.ex, (long)(T_ - 1) * ceil_div(B, 16) * ceil_div(Hp, 16) * 2048, 1};
+  if (xcd) mark = LstmMark{w.ex, (long)(T_ - 1) * ceil_div(B, rb) * ceil_div(Hp, xcd) * rb * xcd * 8, 1 + kLxBlocks * kLxSeats};
+  else if (staged) mark = LstmMark{w.ex, (long)(T_ - 1) * ceil_div(B, 16) * ceil_div(Hp, 16) * 2048, 1};
   else if (one_launch) mark = LstmMark{w.big + step_bytes, bp.via_l2 ? 0 : (T_ - 1) * step_bytes, bp.S * bp.nbb + 1};
   // (hc: compact copy of the stored hidden states, h[:, kept])
   const void* xs;
@@ -1518,7 +1561,25 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
   dim3 cgrid(ceil_div(H + (Hp - Hk), 256), B);
   const float* dh_src = nullptr;  // dh_t[kept] from the product of step t+1: partial sums or w.dh_next
   int dh_splits = 0;
-  if (staged) {
+  if (xcd) {
+    const int S = ceil_div(Hp, xcd), kw = xcd == 24 ? 12 : S <= 8 ? 2 : S <= 16 ? 4 : 8;
+    const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
+    LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,
+                     S, xcd, a.ax.off, a.ax.step, spin_limit, w.ex, getenv("ARD_LSTM_SPREAD") ? 1 : 0};
+    const size_t image = (size_t)4 * Hp * xcd * 2 + 64, step = kLxBwdWaves * ((size_t)kw * rb * 64 + (size_t)2 * rb * (xcd + 4) * 4);
+    const size_t lds = image > step ? image : step;
+    auto launch = [&](auto kernel) -> int32_t {
+      if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
+      ARD_LAUNCH_NAMED("lstm_xcd_bwd_kernel", kernel, dim3((unsigned)(kLxBlocks * S)), dim3(64 * (kLxBwdWaves + 4)), lds, stream, P);
+      return ARD_OK;
+    };
+    if (rb == 8) st = kw == 12 ? launch(lstm_xcd_bwd_kernel<8, 24, 12>) : kw == 8 ? launch(lstm_xcd_bwd_kernel<8, 16, 8>)
+                      : kw == 4 ? launch(lstm_xcd_bwd_kernel<8, 16, 4>) : launch(lstm_xcd_bwd_kernel<8, 16, 2>);
+    else st = kw == 12 ? launch(lstm_xcd_bwd_kernel<16, 24, 12>) : kw == 8 ? launch(lstm_xcd_bwd_kernel<16, 16, 8>)
+              : kw == 4 ? launch(lstm_xcd_bwd_kernel<16, 16, 4>) : launch(lstm_xcd_bwd_kernel<16, 16, 2>);
+    if (st) return st;
+    ARD_LAUNCH_CHECK("lstm_xcd_bwd_kernel");
+  } else if (staged) {
     const int S = ceil_div(Hp, 16), need = ceil_div(Hp, 32), kw = need <= 4 ? 4 : (int)align_up((size_t)need, 8);
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,

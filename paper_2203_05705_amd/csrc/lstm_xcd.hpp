@@ -1,0 +1,471 @@
+// Recurrences of the LSTM with a batch block per XCD (included by lstm.hip, after the helpers of the other one-launch forms).
+#pragma once
+
+namespace ard {
+
+// What bounds a recurrence is the exchange from one step to the next.  RB batch rows are one block (8 while eight such
+// blocks hold the batch, else 16), and all workgroups of a block run on one XCD (the dispatcher deals workgroups
+// round-robin, block bb takes XCD bb): what they exchange in a step, h_t forward and dG_t backward, never leaves that XCD's
+// L2.  From a store to the load that sees it 370 ns pass there, 510 if the store is written through to memory, 650 to
+// another XCD.
+//
+// A workgroup owns UW kept units (16 up to 512 kept units, 24 up to 768: 32 workgroups at most, one per CU) and has
+// wavefronts that multiply and four that run the cell; the recurrent weights stay in registers.  The rows arrive at the
+// product wavefronts in the order their MFMAs take them (what a cell wavefront stores is a whole 128-byte line of that
+// image), each leaves its partial tile in LDS, one barrier, the cell wavefronts add the partial tiles, run the cell, store
+// what the others wait for, and then everything else.  A product wavefront stores nothing, so its loads wait for nobody's
+// stores (vmcnt counts both in order).
+//
+// Where the workgroups of a block really run is read from the hardware at the start (lx_meet): on one XCD results are
+// stored into its L2; if they are spread, device-scope stores make the same loads correct at the old price.
+//
+// Recurrences with staging wavefronts -> these, us: 512 kept units, B = 128, 64 steps: forward 204 -> 97, backward
+// 237 -> 155; 750 units, B = 20, 35 steps: 113 -> 67 and 136 -> 87 (with 16 rows per block 95 and 142: half of every
+// operand and of the cells would be padding).  Eight product wavefronts instead of four at 512 units forward, or a higher
+// priority of the cell wavefronts: nothing.
+constexpr int kLxBlocks = 8, kLxSeats = 32;  // most batch blocks, most workgroups of one
+constexpr int kLxBwdWaves = 8;               // wavefronts that multiply, backward and forward
+constexpr int lx_fwd_waves(int uw) { return uw == 16 ? 4 : 8; }
+
+// Byte of (row, unit) in the [RB rows x UW units] image of one workgroup, bf16: groups of 8 units are 16-byte pieces (a
+// lane's MFMA operand); 4 rows x 16 units are one line (a wavefront's cells), the last 8 units of 24 follow in lines of
+// 8 rows.  (The two groups of units change places from row 8 on: the 16 rows an LDS read takes at a time then lie in
+// different banks.)
+template <int RB> __device__ __forceinline__ int lx_at(int row, int unit) {
+  return unit < 16 ? (row >> 2) * 128 + (((unit >> 3) ^ (row >> 3)) & 1) * 64 + (row & 3) * 16 + (unit & 7) * 2 : RB * 32 + row * 16 + (unit & 7) * 2;
+}
+// cell `c` of a workgroup's RB * UW cells, in the order of the image
+template <int RB> __device__ __forceinline__ void lx_cell(int c, int& row, int& unit) {
+  const int d = c - RB * 16;
+  row = d < 0 ? c >> 4 : d >> 3;
+  unit = d < 0 ? c & 15 : 16 + (d & 7);
+}
+// 1 / d for d >= 1: the hardware's reciprocal and one Newton step (which makes a NaN of an infinity's 0)
+__device__ __forceinline__ float lx_rcp(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return d < 3.0e38f ? fmaf(fmaf(-d, r, 1.0f), r, r) : (d != d ? d : r);
+}
+__device__ __forceinline__ float lx_sigmoid(float z) { return lx_rcp(1.0f + __expf(-z)); }
+// tanh without branches: a polynomial fitted to tanh(x) / x on [0, 5/8] (4e-9), 1 - 2 / (1 + e^2x) beyond
+__device__ __forceinline__ float lx_tanh(float x) {
+  const float y = fabsf(x), s = x * x;
+  float p = fmaf(s, -0.005704042501747608f, 0.020637862384319305f);
+  p = fmaf(s, p, -0.05373915657401085f);
+  p = fmaf(s, p, 0.133314311504364f);
+  p = fmaf(s, p, -0.3333328068256378f);
+  const float low = fmaf(x * s, p, x), high = copysignf(fmaf(-2.0f, lx_rcp(1.0f + __expf(2.0f * y)), 1.0f), x);
+  return y < 0.625f ? low : high;
+}
+// All workgroups of a block tell each other which XCD they run on.  -1: gave up, 1: all on one, 0: they are spread.
+__device__ __forceinline__ int lx_meet(int* seat, int S, int s, int lane, long limit, int* err) {
+  unsigned x;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
+  const int mine = (int)(x & 0xffu) + 1;
+  if (lane == 0) __hip_atomic_store(seat + s, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  long spins = 0;
+  for (;;) {
+    const int v = lane < S ? __hip_atomic_load(seat + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : mine;
+    if (limit >= 0 && !__any(v == 0)) return __all(v == mine) ? 1 : 0;
+    if (limit < 0) {  // (the host's way to force the give-up path)
+      __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return -1;
+    }
+    if (lp_give_up(spins, limit, err)) return -1;
+  }
+}
+// a result and its neighbour's (lane ^ 1) as the word that the even one stores; every NaN becomes 0x7fc0 (kUnwritten)
+__device__ __forceinline__ unsigned lx_word(float x) {
+  if (x != x) x = __uint_as_float(0x7fc00000u);
+  const float y = __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0xB1, 0xF, 0xF, true));
+  return pack_bf16x2(x, y);
+}
+__device__ __forceinline__ void lx_store(unsigned* p, unsigned v, bool local) {
+  if (local) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned lx_max3(unsigned a, unsigned b, unsigned c) {
+  const unsigned m = a > b ? a : b;
+  return m > c ? m : c;
+}
+// Loads N pieces per lane until nothing in them is unwritten (kUnwritten is the largest word).  False: gave up.
+template <int N>
+__device__ __forceinline__ bool lx_wait(__amdgpu_buffer_rsrc_t buf, const unsigned (&at)[N], lp_u32x4 (&v)[N], long limit, int* err) {
+  long spins = 0;
+  for (;;) {
+    unsigned most = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = lp_load(buf, at[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) most = lx_max3(lx_max3(most, v[i].x, v[i].y), v[i].z, v[i].w);
+    if (!__any(most == kUnwritten)) return true;
+    if (lp_give_up(spins, limit, err)) return false;
+  }
+}
+
+// KW: 32-wide slices of the contraction per product wavefront.
+template <int RB, int UW, int KW>
+__global__ __launch_bounds__(64 * (lx_fwd_waves(UW) + 4)) void lstm_xcd_fwd_kernel(const LstmPersist P) {
+  constexpr int NM = lx_fwd_waves(UW), BLK = RB * UW * 2, NT = UW / 4, NP = (RB * UW + 255) / 256, RED = RB * UW;
+  extern __shared__ uint4 lp_lds[];
+  __shared__ int go_s[2], local_s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bb = (int)blockIdx.x & 7, s = (int)blockIdx.x >> 3, nbb = (P.B + RB - 1) / RB, S = P.S;
+  if (bb >= nbb) return;
+  const int Hp = P.Hp, B = P.B, H = P.H;
+  float4* const red = reinterpret_cast<float4*>(lp_lds);             // [2][NM][RED] sums of the four gates of a cell
+  char* const ex = reinterpret_cast<char*>(P.hc) + (long)bb * S * BLK;  // this block's images of step 0
+  const long ex_step = (long)nbb * S * BLK;
+  if (tid == 0) go_s[0] = go_s[1] = 1;
+  if (wave == NM) {
+    const int m = lx_meet(P.counters + bb * kLxSeats, S, s, lane, P.spin_limit, P.err);
+    if (lane == 0) local_s = m;
+  }
+  if (wave < NM) {
+    const int n = lane & 15, kg = lane >> 4;
+    // gate columns of this workgroup: tiles 0 .. 3 the gates of its first 16 units; 4 and 5 (24 units) gates 0 | 1 and
+    // 2 | 3 of its last 8
+    bf16x8_t wf[KW][NT];
+#pragma unroll
+    for (int i = 0; i < KW; ++i)
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt) {
+        const int k = ((wave * KW + i) * 4 + kg) * 8;
+        const int gate = tt < 4 ? tt : 2 * (tt - 4) + (n >> 3), unit = s * UW + (tt < 4 ? n : 16 + (n & 7));
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (k < Hp && unit < Hp) v = *reinterpret_cast<const uint4*>(P.Wh + ((long)gate * Hp + unit) * Hp + k);
+        wf[i][tt] = __builtin_bit_cast(bf16x8_t, v);
+      }
+    unsigned at[KW];
+#pragma unroll
+    for (int i = 0; i < KW; ++i) {
+      const int g8 = (wave * KW + i) * 4 + kg, ws = g8 / (UW / 8);  // group of 8 units, its writer (none: zero weights)
+      at[i] = (unsigned)((ws < S ? ws * BLK : 0) + lx_at<RB>(n & (RB - 1), (g8 - ws * (UW / 8)) * 8));
+    }
+    lp_barrier();
+    if (local_s < 0) return;  // uniform
+    for (int t = 0; t < P.T; ++t) {
+      if (t > 0) {
+        lp_u32x4 v[KW];
+        if (!lx_wait<KW>(lp_buffer(ex + (t - 1) * ex_step, (unsigned)(S * BLK)), at, v, P.spin_limit, P.err)) go_s[t & 1] = 0;
+        f32x4_t acc[NT];
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[tt][e] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < KW; ++i)
+#pragma unroll
+          for (int tt = 0; tt < NT; ++tt) acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v[i]), wf[i][tt], acc[tt], 0, 0, 0);
+        // lane holds column n, rows 4 kg + e; the gates of a cell side by side (24 units, the last 8: gates 0 2 | 1 3)
+        float4* const mine = red + ((t & 1) * NM + wave) * RED;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int row = 4 * kg + e;
+          if (RB < 16 && row >= RB) continue;  // (rows beyond the block repeat its rows)
+          mine[row * 16 + n] = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
+          if constexpr (UW == 24)
+            reinterpret_cast<float2*>(mine + RB * 16 + row * 8 + (n & 7))[n >> 3] = make_float2(acc[4][e], acc[5][e]);
+        }
+      }
+      lp_barrier();
+      if (!go_s[t & 1]) return;  // uniform: every wavefront reads it behind the same barrier
+    }
+    return;
+  }
+  const int c0 = tid - 64 * NM;
+  int row[NP], j[NP], u[NP], z_lo[NP], z_hi[NP];
+  bool kept[NP], live[NP], last8[NP];
+  float c_reg[NP], zx[NP][4];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int c = p * 256 + c0;
+    int ul;
+    lx_cell<RB>(c, row[p], ul);
+    live[p] = c < RB * UW;
+    last8[p] = ul >= 16;
+    j[p] = s * UW + ul;  // compact unit
+    kept[p] = live[p] && j[p] < P.Hk;
+    u[p] = P.off + j[p] * P.step;  // physical unit
+    // zeros of the dropped units this thread owns: the rest of its group [j*step, (j+1)*step), the last kept unit also
+    // the tail up to H
+    z_lo[p] = j[p] * P.step, z_hi[p] = !kept[p] ? z_lo[p] : (j[p] == P.Hk - 1 ? H : z_lo[p] + P.step);
+    c_reg[p] = 0.0f;
+  }
+  auto fetch_zx = [&](int t) {
+    const float* Gt = P.Gx + (long)t * B * 4 * Hp;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int r = imin(bb * RB + imin(row[p], RB - 1), B - 1), jj = imin(j[p], Hp - 1);  // (clamped: never used)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) zx[p][g] = Gt[(long)r * 4 * Hp + g * Hp + jj];
+    }
+  };
+  fetch_zx(0);
+  lp_barrier();
+  if (local_s < 0) return;
+  const bool local = local_s != 0 && !P.spread;
+  for (int t = 0; t < P.T; ++t) {
+    lp_barrier();
+    if (!go_s[t & 1]) return;
+    unsigned* const out = reinterpret_cast<unsigned*>(ex + t * ex_step + s * BLK);
+    float gi[NP], gf[NP], gg[NP], go[NP], hv[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (!live[p]) continue;
+      float z[4] = {zx[p][0], zx[p][1], zx[p][2], zx[p][3]};
+      if (t > 0) {
+        const float4* src = red + (t & 1) * NM * RED + p * 256 + c0;
+        float4 a[NM];
+#pragma unroll
+        for (int w = 0; w < NM; ++w) a[w] = src[w * RED];
+#pragma unroll
+        for (int w = NM / 2; w > 0; w >>= 1)
+#pragma unroll
+          for (int i = 0; i < w; ++i) a[i].x += a[i + w].x, a[i].y += a[i + w].y, a[i].z += a[i + w].z, a[i].w += a[i + w].w;
+        z[0] += a[0].x, z[1] += last8[p] ? a[0].z : a[0].y, z[2] += last8[p] ? a[0].y : a[0].z, z[3] += a[0].w;
+      }
+      gi[p] = lx_sigmoid(z[0]), gf[p] = lx_sigmoid(z[1]), gg[p] = lx_tanh(z[2]), go[p] = lx_sigmoid(z[3]);
+      const float cv = gf[p] * c_reg[p] + gi[p] * gg[p];
+      c_reg[p] = cv;
+      hv[p] = go[p] * lx_tanh(cv);
+      // (the padding units store their zero; rows beyond the batch are stored like any other: the image is waited for as
+      // a whole)
+      const unsigned word = lx_word(kept[p] ? hv[p] : 0.0f);
+      if (!(c0 & 1)) lx_store(out + lx_at<RB>(row[p], j[p] - s * UW) / 4, word, local);
+    }
+    if (t + 1 < P.T) fetch_zx(t + 1);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int r = bb * RB + row[p];
+      if (!kept[p] || r >= B) continue;
+      float* ga = P.gates + ((long)t * B + r) * 4 * H;
+      float* const pc = P.c + ((long)t * B + r) * H;
+      uint16_t* const ph = P.h + ((long)t * B + r) * H;
+      ga[u[p]] = gi[p], ga[H + u[p]] = gf[p], ga[2 * H + u[p]] = gg[p], ga[3 * H + u[p]] = go[p];
+      pc[u[p]] = c_reg[p];
+      ph[u[p]] = f32_to_bf16_bits(hv[p]);
+      for (int uz = z_lo[p]; uz < z_hi[p]; ++uz) {
+        if (uz == u[p]) continue;
+        ga[uz] = ga[H + uz] = ga[2 * H + uz] = ga[3 * H + uz] = 0.0f;
+        pc[uz] = 0.0f;
+        ph[uz] = 0;
+      }
+    }
+  }
+}
+
+// KW as above.  The rows of a step, all 4 Hp gate columns of them, come through LDS: 64 KB a workgroup at 512 kept units, which eight
+// wavefronts fetch in 770 clocks past the registers, in 1120 through them, and four in 1720.
+template <int RB, int UW, int KW>
+__global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(const LstmPersistBwd P) {
+  constexpr int NM = kLxBwdWaves, GB = RB * UW * 2, BLK = 4 * GB, NB = UW / 16 + (UW % 16 > 0), NP = (RB * UW + 255) / 256, PITCH = UW + 4;
+  constexpr int SHARE = KW * RB * 64, NL = SHARE / 1024, NOFF = UW == 16 ? 1 : 3;  // bytes of a wavefront's share, its loads
+  constexpr int NA = UW == 16 ? 4 : 2;
+  static_assert(SHARE % 1024 == 0 && SHARE % BLK == 0, "whole loads, whole writers");
+  extern __shared__ uint4 lp_lds[];
+  __shared__ int go_s[2], local_s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bb = (int)blockIdx.x & 7, s = (int)blockIdx.x >> 3, nbb = (P.B + RB - 1) / RB, S = P.S;
+  if (bb >= nbb) return;
+  const int Hp = P.Hp, B = P.B, H = P.H, K = 4 * Hp;
+  char* const stage = reinterpret_cast<char*>(lp_lds);
+  float* const red = reinterpret_cast<float*>(stage + NM * SHARE);  // [2][NM][RB][PITCH]
+  char* const ex = P.ex + (long)bb * S * BLK;                       // this block's images of the last step
+  const long ex_step = (long)nbb * S * BLK;
+  if (tid == 0) go_s[0] = go_s[1] = 1;
+  if (wave == NM) {
+    const int m = lx_meet(P.counters + bb * kLxSeats, S, s, lane, P.spin_limit, P.err);
+    if (lane == 0) local_s = m;
+  }
+  // This workgroup's UW columns of Wh' pass through LDS as they lie in memory, [gate row][unit]; the transposing reads
+  // make the MFMA operands of them, which stay in registers.
+  for (int i = tid; i < K * (UW / 8); i += 64 * (NM + 4)) {
+    const int k = i / (UW / 8), x0 = (i - k * (UW / 8)) * 8, jj = s * UW + x0;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (jj < Hp) v = *reinterpret_cast<const uint4*>(P.Wh + (long)k * Hp + jj);
+    lp_lds[i] = v;
+  }
+  lp_barrier();
+  if (local_s < 0) return;  // uniform
+  if (wave < NM) {
+    const int n = lane & 15, kg = lane >> 4;
+    // slice q of the contraction, lane group kg: group of 8 units ug of gate `gate` of writer ws (the order of the images)
+    Frag wf[KW][NB];
+    const unsigned base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)lp_lds);
+#pragma unroll
+    for (int i = 0; i < KW; ++i) {
+      const int g8 = (wave * KW + i) * 4 + kg, ws = g8 / (UW / 2), r8 = g8 - ws * (UW / 2), gate = r8 / (UW / 8), unit = ws * UW + (r8 - gate * (UW / 8)) * 8;
+      const unsigned w = base + (unsigned)(((unit < Hp ? gate * Hp + unit : 0) + (n >> 2)) * (UW * 2) + (n & 3) * 8);
+#pragma unroll
+      for (int p = 0; p < NB; ++p) {
+        if (p == 0) lds_read_tr16_b64<0>(wf[i][p].lo, w), lds_read_tr16_b64<4 * UW * 2>(wf[i][p].hi, w);
+        else lds_read_tr16_b64<32>(wf[i][p].lo, w), lds_read_tr16_b64<4 * UW * 2 + 32>(wf[i][p].hi, w);
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < KW; ++i) {
+      const int g8 = (wave * KW + i) * 4 + kg, ws = g8 / (UW / 2), unit = ws * UW + ((g8 - ws * (UW / 2)) % (UW / 8)) * 8;
+#pragma unroll
+      for (int p = 0; p < NB; ++p) {
+        frag_wait<false>(wf[i][p]);
+        if (unit >= Hp) wf[i][p].lo = wf[i][p].hi = u32x2_t{0u, 0u};
+      }
+    }
+    // operand of slice i in the share: writer i * 8 / UW of it (4 lane groups a slice, UW / 2 a writer)
+    const char* op[NOFF];
+#pragma unroll
+    for (int o = 0; o < NOFF; ++o) {
+      const int r8 = o * 4 + kg, gate = r8 / (UW / 8), ug = r8 - gate * (UW / 8);
+      op[o] = stage + wave * SHARE + gate * GB + lx_at<RB>(n & (RB - 1), ug * 8);
+    }
+    const unsigned total = (unsigned)(S * BLK), share = (unsigned)(wave * SHARE);
+    unsigned peek[1] = {share + (unsigned)((lane >> 3) * BLK)};
+    peek[0] = (((lane >> 3) + 1) * BLK <= SHARE && peek[0] + BLK <= total ? peek[0] : 0u) + BLK - 128 + (lane & 7) * 16;
+    lp_barrier();
+    for (int tt = 0; tt < P.T; ++tt) {
+      if (tt > 0) {
+        const char* src = ex + (tt - 1) * ex_step;
+        lp_u32x4 last[1];
+        bool ok = lx_wait<1>(lp_buffer(src, total), peek, last, P.spin_limit, P.err);
+        f32x4_t acc[NB][NA];
+        for (long spins = 0; ok;) {
+          // (every writer's last line is there, nearly always everything is: if not, the share is fetched again)
+#pragma unroll
+          for (int i = 0; i < NL; ++i) {
+            const unsigned o = share + i * 1024, at = o + lane * 16;  // (beyond the last writer: multiplied by zero weights)
+            __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(src + (at < total ? at : (unsigned)(lane * 16))), ARD_LDS_PTR(stage + o), 16, 0, 16);
+          }
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+          for (int p = 0; p < NB; ++p)
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[p][a][e] = 0.0f;
+          unsigned most = 0;
+          constexpr int GRP = KW > 8 ? 4 : KW;  // operands in registers at a time (12 and the weights of 24 units spill: 109 instead of 87 us)
+#pragma unroll
+          for (int i0 = 0; i0 < KW; i0 += GRP) {
+            lp_u32x4 v[GRP];
+#pragma unroll
+            for (int k = 0; k < GRP; ++k) {
+              const int i = i0 + k;
+              v[k] = *reinterpret_cast<const lp_u32x4*>(op[i % NOFF] + (UW == 16 ? (i >> 1) * BLK + (i & 1) * 2 * GB : (i / 3) * BLK));
+            }
+#pragma unroll
+            for (int k = 0; k < GRP; ++k) {
+              const int i = i0 + k;
+              most = lx_max3(lx_max3(most, v[k].x, v[k].y), v[k].z, v[k].w);
+#pragma unroll
+              for (int p = 0; p < NB; ++p)
+                acc[p][i % NA] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, v[k]), frag_value<false>(wf[i][p]), acc[p][i % NA], 0, 0, 0);
+            }
+            if (GRP < KW) __builtin_amdgcn_sched_barrier(0);
+          }
+          if (!__any(most == kUnwritten)) break;
+          ok = !lp_give_up(spins, P.spin_limit, P.err);
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+        if (!ok) go_s[tt & 1] = 0;
+        else {
+          // lane holds column n (unit), rows 4 kg + e
+          float* const mine = red + ((tt & 1) * NM + wave) * RB * PITCH;
+#pragma unroll
+          for (int p = 0; p < NB; ++p)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              float x = acc[p][0][e] + acc[p][1][e];
+              if constexpr (NA == 4) x += acc[p][2][e] + acc[p][3][e];
+              if ((p == 0 || n < 8) && 4 * kg + e < RB) mine[(4 * kg + e) * PITCH + p * 16 + n] = x;
+            }
+        }
+      }
+      lp_barrier();
+      if (!go_s[tt & 1]) return;
+    }
+    return;
+  }
+  const bool local = local_s != 0 && !P.spread;
+  const int c0 = tid - 64 * NM;
+  int row[NP], ul[NP], u[NP];
+  bool kept[NP], live[NP], in_store[NP];
+  float dc_next[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    lx_cell<RB>(p * 256 + c0, row[p], ul[p]);
+    live[p] = p * 256 + c0 < RB * UW;
+    const int j = s * UW + ul[p], r = bb * RB + row[p];
+    kept[p] = live[p] && j < P.Hk && r < B, in_store[p] = live[p] && j < Hp && r < B;
+    u[p] = kept[p] ? P.off + j * P.step : 0;
+    dc_next[p] = 0.0f;
+  }
+  // what the cell of step t needs of the forward pass, fetched a step ahead (its c was the c_prev of the step before)
+  float ni[NP], nf[NP], ng[NP], no[NP], nc[NP], np[NP];
+  uint16_t nd[NP];
+  auto fetch_cell = [&](int t) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const long at = (long)t * B + imin(bb * RB + row[p], B - 1);
+      const float* ga = P.gates + at * 4 * H;
+      ni[p] = ga[u[p]], nf[p] = ga[H + u[p]], ng[p] = ga[2 * H + u[p]], no[p] = ga[3 * H + u[p]];
+      nc[p] = np[p];
+      np[p] = P.c[(at - (t > 0 ? B : 0)) * H + u[p]];
+      nd[p] = P.dh[at * H + u[p]];
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < NP; ++p) np[p] = P.c[((long)(P.T - 1) * B + imin(bb * RB + row[p], B - 1)) * H + u[p]];
+  fetch_cell(P.T - 1);
+  lp_barrier();
+  for (int tt = 0; tt < P.T; ++tt) {
+    const int t = P.T - 1 - tt;
+    // all that does not depend on the gradient arriving from the step after, while the others are waited for:
+    // d = (dc ki, dc kf, dc kg, dh ko) with dc = dh kc + dc_next
+    float kc[NP], ki[NP], kf[NP], kg[NP], ko[NP], fg[NP], dh0[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const float gi = ni[p], gf = nf[p], gg = ng[p], go = no[p], cp = t > 0 ? np[p] : 0.0f, tc = lx_tanh(nc[p]);
+      kc[p] = go * (1.0f - tc * tc), ki[p] = gg * gi * (1.0f - gi), kf[p] = cp * gf * (1.0f - gf), kg[p] = gi * (1.0f - gg * gg);
+      ko[p] = tc * go * (1.0f - go), fg[p] = gf, dh0[p] = bf16_bits_to_f32(nd[p]);
+    }
+    lp_barrier();
+    if (!go_s[tt & 1]) return;
+    unsigned* const out = reinterpret_cast<unsigned*>(ex + tt * ex_step + s * BLK);
+    unsigned word[NP][4];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (!live[p]) continue;
+      float dh = dh0[p];
+      if (tt > 0) {
+        const float* src = red + (tt & 1) * NM * RB * PITCH + row[p] * PITCH + ul[p];
+        float a[NM];
+#pragma unroll
+        for (int w = 0; w < NM; ++w) a[w] = src[w * RB * PITCH];
+#pragma unroll
+        for (int w = NM / 2; w > 0; w >>= 1)
+#pragma unroll
+          for (int i = 0; i < w; ++i) a[i] += a[i + w];
+        dh += a[0];
+      }
+      const float dc = dh * kc[p] + dc_next[p];
+      dc_next[p] = dc * fg[p];
+      // dG_t to the other workgroups, then as the pass's result; padding units and rows store zeros
+      const float d[4] = {dc * ki[p], dc * kf[p], dc * kg[p], dh * ko[p]};
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        word[p][g] = lx_word(kept[p] ? d[g] : 0.0f);
+        if (!(c0 & 1)) lx_store(out + (g * GB + lx_at<RB>(row[p], ul[p])) / 4, word[p][g], local);
+      }
+    }
+    if (t > 0) fetch_cell(t - 1);
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      if (!(c0 & 1) && in_store[p])
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<unsigned*>(P.dG + ((long)t * B + bb * RB + row[p]) * K + g * Hp + s * UW + ul[p]) = word[p][g];
+  }
+}
+
+}  // namespace ard

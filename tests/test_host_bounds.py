@@ -270,3 +270,15 @@ def test_lstm_shapes_reach_the_recurrences_their_gpu_tests_name():
                 _ok(lib, D.lstm_calls(lib, heap, D.BF16, T, B, 16, H, (1, 1)), f"lstm {T} {B} {H}")
                 assert kernel in D.launches(lib)[1], (kernel, T, B, H)
         D.last_bounds(lib)
+
+
+def test_lstm_shapes_reach_the_recurrences_with_a_block_per_xcd():
+    from test_gpu_lstm_xcd import SHAPES
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        for T, B, H, dp in SHAPES:
+            D.launches(lib)
+            _ok(lib, D.lstm_calls(lib, heap, D.BF16, T, B, 24, H, (dp, dp)), f"lstm {T} {B} {H}")
+            names = D.launches(lib)[1]
+            assert "lstm_xcd_fwd_kernel" in names and "lstm_xcd_bwd_kernel" in names, (names, T, B, H)
+        D.last_bounds(lib)
