@@ -12,6 +12,8 @@
 // bit on any number of devices (the host folds the first three links, the kernels add the index).
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace ard {
@@ -143,146 +145,252 @@ __global__ __launch_bounds__(256) void sens_predict_lut_kernel(const T* A, SensG
 }
 
 // The prediction once more, with the footprint of the workgroup's regions in the activations brought into LDS
-// first: the draws of a region fall on a few input rows of its channels (config 5, a band of 8 positions:
-// 4 rows x 28 x 256 channels for 5529 draws), and a gather from memory costs a whole cache-line transaction per
-// draw (69 M of them made the pass take 460 us) where the copy is a few coalesced 16-byte loads per thread.
-// Same draws, same elements, same counts.
+// first: the draws of a region fall on a few input rows of its channels (a band of 8 positions of a 28 x 28 layer of 256
+// channels: 4 rows x 28 x 256 for 5529 draws), and a gather from memory costs a whole cache-line transaction per
+// draw.  Same draws, same elements, same counts.
 //
-// What a draw needs of an element is one bit (above the threshold or not).  The bits lie in rows of W + 2 pad with
-// the zero border of the input matrix around them, so that a draw's bit number is a sum of one table entry for its
-// row and one for its column and nothing is tested.  The pass is bound by the vector ALUs, mostly by the mixer's
-// multiplications (a 32-bit one takes four times as long as an addition), and saves what it can of them:
+// What a draw needs of an element is one bit (above the threshold or not).  The bits of a row of W + 2 pad, with the
+// zero border of the input matrix around them, are whole words, so that a draw's bit number is a sum of one table entry
+// for its row and one for its column, nothing is tested, and a thread makes a word of a row out of at most five loads
+// and stores it once.  (Where rows shared words, 16-byte pieces were cut at the row ends and added with atomics: with the
+// copies of 14 workgroups per image, of four rows for two, 46 of the pass's 97 us.)
+//
+// Then the pass is bound by the vector instructions of a draw (leaving out its LDS reads changes nothing; a multiplication
+// costs 2.0 ns of a SIMD, as any instruction of eight bytes does, one of four bytes 1.2), and saves what it can of them:
 //  * the bits of (prefix ^ index) + golden above the lowest 16 take two values over a region (j < 65536; the sum
-//    carries or it does not), so the mixer's first product is one of two constants plus a 16-bit number times the
-//    multiplier; only the upper half of the second product is needed;
+//    carries or it does not).  Thread t of four wavefronts takes the draws whose index is t ^ (low byte of prefix) in its
+//    lowest byte, i.e. t + golden is what this byte becomes before its carry, and the next byte i is the same for all
+//    threads: the mixer's first product is a number of the thread's (one of two) plus one that depends on i, which a
+//    wavefront tabulates in its lanes and reads back as a scalar.  Only the last 21 threads' bytes carry into i's: their
+//    wavefront makes both tables.
+//  * only the upper half of the second product is needed;
 //  * u * h = (row, f) and f * w = (column, .) give row and column of the drawn element without dividing.
-// N=128, 256 channels, 28x28, 3x3, 30 % sampled (69 M draws): bands of 8 positions 138 -> 97 us, 112 x 576
-// regions 120 -> 81 us.
+// N=128, 256 channels, 28x28, 3x3, 30 % sampled (69 M draws): bands of 8 positions 99 -> 88 us with the activations in the
+// Infinity Cache and 98 -> 92 from memory, 112 x 576 regions 83 -> 78 and 84 -> 84 (all workgroups copy first, and then all
+// draw); over 60 layers (8 - 128 images, 16 - 512 channels, 7 x 7 - 56 x 56, both types) 1.17x in the geometric mean.
+// Workgroups of 8 and 4 wavefronts: 92 and 93, 85 and 86 us; twice and four times as many: 93 and 97, 87 and 91 from memory.
 struct SensStage {
-  int nrow_max, ch_bits;  // input rows (border included) a workgroup's bands can touch; bits reserved per channel
-  FastDiv div_taps, div_kw, div_wo, div_w;
+  int nrow, words;        // staged rows of a channel (border included), words of a row
+  FastDiv div_taps, div_kw, div_wo, div_words, div_items;  // ... words of a row, of a channel
   int G, RBG;             // consecutive row bands (of one image and column block) per workgroup; groups per image
 };
+constexpr int kSensWaves = 16;
+struct SensBand {  // what the draws of a band share, made once by a thread of its own
+  uint64_t K[2];
+  uint32_t m[2], p16;
+  int s, h, hits, pad[2];
+};
+static_assert(sizeof(SensBand) == 48, "whole 16-byte pieces");
+// element > threshold shifted into b from below
+__device__ __forceinline__ void sens_push(uint32_t& b, float v, float thr) {
+  asm("v_cmp_gt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(b) : "v"(v), "v"(thr) : "vcc");
+}
+typedef uint32_t sens_u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+// bits of the `n` <= 32 elements from A[first] on, lowest first (whatever lies above them is to be masked off); `end`: elements
+// of the tensor
+__device__ __forceinline__ uint32_t sens_word(const uint16_t* A, long first, int n, int most, long end, float thr) {
+  const long d0 = first >> 1;
+  const int odd = (int)(first & 1), quads = (most + 8) >> 3;  // (uniform: for the longest word, first element odd)
+  uint32_t b = 0;
+  if (d0 + 4 * quads <= end >> 1) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(A) + d0;
+    sens_u32x4 v[5];
+#pragma unroll
+    for (int q = 0; q < 5; ++q)
+      if (q < quads) v[q] = *reinterpret_cast<const sens_u32x4*>(src + 4 * q);
+#pragma unroll
+    for (int q = 4; q >= 0; --q) {
+      if (q >= quads) continue;
+#pragma unroll
+      for (int e = 3; e >= 0; --e) {
+        sens_push(b, __uint_as_float(v[q][e] & 0xffff0000u), thr);
+        const uint32_t above = b;
+        sens_push(b, __uint_as_float(v[q][e] << 16), thr);
+        if (q == 0 && e == 0 && odd) b = above;
+      }
+    }
+  } else {
+    for (int e = n - 1; e >= 0; --e) sens_push(b, bf16_bits_to_f32(A[first + e]), thr);
+  }
+  return b;
+}
+__device__ __forceinline__ uint32_t sens_word(const float* A, long first, int n, int most, long end, float thr) {
+  uint32_t b = 0;
+  if (first + ((most + 15) & ~15) <= end) {
+#pragma unroll 1
+    for (int o = (most - 1) & ~15; o >= 0; o -= 16) {  // (sixteen registers at a time)
+      sens_u32x4 v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const sens_u32x4*>(A + first + o + 4 * q);
+#pragma unroll
+      for (int q = 3; q >= 0; --q)
+#pragma unroll
+        for (int e = 3; e >= 0; --e) sens_push(b, __uint_as_float(v[q][e]), thr);
+    }
+  } else {
+    for (int e = n - 1; e >= 0; --e) sens_push(b, A[first + e], thr);
+  }
+  return b;
+}
 template <typename T>
-__global__ __launch_bounds__(256) void sens_predict_staged_kernel(const T* A, SensGeom g, SensStage sg, int k_permille,
-                                                                  int t_permille, float thr, uint64_t prefix,
-                                                                  int* count, int* samples, uint8_t* sens) {
-  constexpr int CE = ElemTraits<T>::CE;  // elements per 16-byte piece
+__global__ __launch_bounds__(64 * kSensWaves, 8) void sens_predict_staged_kernel(const T* A, SensGeom g, SensStage sg, int k_permille,
+                                                                                 int t_permille, float thr, uint64_t prefix,
+                                                                                 int* count, int* samples, uint8_t* sens) {
   extern __shared__ uint4 sens_stage_lds[];
-  __shared__ int wave_cnt[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int NT = 64 * kSensWaves;
   // workgroup = (image, group of G row bands, column block)
   const int cb = blockIdx.x % g.CB, rbg = (blockIdx.x / g.CB) % sg.RBG, n = blockIdx.x / (g.CB * sg.RBG);
   const int rb_first = rbg * sg.G, nb = min(sg.G, g.RB - rb_first);
+  if (nb <= 0) return;
   const int r0 = rb_first * g.x, q0 = cb * g.y;
   const int h = min(nb * g.x, g.rows - r0), w = min(g.y, g.cols - q0);  // rows of the group, columns of the block
-  const int taps = g.KH * g.KW, pitch = g.W + 2 * g.pad;
-  // footprint: channels [ch_lo, ch_hi], input rows from `top` (border included), of which [ih_lo, ih_hi] exist
+  const int taps = g.KH * g.KW, pitch = sg.words * 32, ch_bits = sg.nrow * pitch;
+  // footprint: channels [ch_lo, ch_hi], sg.nrow input rows from `top` on (border included)
   const int ch_lo = q0 / taps, ch_hi = (q0 + w - 1) / taps;
-  const int oh_lo = r0 / g.Wo, oh_hi = (r0 + h - 1) / g.Wo;
-  const int top = oh_lo * g.stride - g.pad;
-  const int ih_lo = max(0, top), ih_hi = min(g.H - 1, oh_hi * g.stride - g.pad + g.KH - 1);
-  const int nch = ch_hi - ch_lo + 1, run = max(0, ih_hi - ih_lo + 1) * g.W;  // elements of a channel that are staged
-  const int pieces = run > 0 ? (2 * (CE - 1) + run) / CE : 0;  // 16-byte pieces a run can touch
-  const int nch_max = min(g.C, (g.y + taps - 2) / taps + 1);   // channels a column block can touch
-  uint32_t* bits = reinterpret_cast<uint32_t*>(sens_stage_lds);
-  const int words = (sg.ch_bits * nch_max + 31) / 32 + 1;
-  int* col_lut = reinterpret_cast<int*>(bits + words);
+  const int oh_lo = r0 / g.Wo, top = oh_lo * g.stride - g.pad;
+  const int nch = ch_hi - ch_lo + 1, items = nch * sg.nrow * sg.words;
+  uint32_t* bits = reinterpret_cast<uint32_t*>(sens_stage_lds + 3 * sg.G);
+  int* col_lut = reinterpret_cast<int*>(bits + items);
   int* row_lut = col_lut + w;
-  for (int i = threadIdx.x; i < words; i += 256) bits[i] = 0;
-  __syncthreads();
+  SensBand* bands = reinterpret_cast<SensBand*>(sens_stage_lds);  // (first: aligned)
   const int border_above = 0.0f > thr ? 1 : 0;  // the zero border: bits are kept relative to it
   const long img = (long)n * g.C * g.H * g.W, end = (long)g.N * g.C * g.H * g.W;
-  // consecutive threads take consecutive pieces, running on from one channel into the next
-  for (int i = threadIdx.x; i < nch * pieces; i += 256) {
-    const int c = i / pieces, pc = i - c * pieces;
-    const long first = img + (long)(ch_lo + c) * g.H * g.W + ih_lo * g.W;  // the run's first element
-    const long at = (first & ~(long)(CE - 1)) + pc * CE;
-    int o = (int)(at - first);                                            // element of the run, or before it
-    if (o >= run) continue;
-    T el[CE];
-    if (at + CE <= end) {
-      *reinterpret_cast<uint4*>(el) = *reinterpret_cast<const uint4*>(A + at);
-    } else {
-      for (int e = 0; e < CE; ++e) el[e] = at + e < end ? A[at + e] : (T)0;
-    }
+  for (int i = tid; i < items; i += NT) {
+    const int c = (int)fdiv((uint32_t)i, sg.div_items), rw = i - c * sg.nrow * sg.words;
+    const int r = (int)fdiv((uint32_t)rw, sg.div_words), x0 = (rw - r * sg.words) * 32 - g.pad, ih = top + r;
+    const int lo = max(x0, 0), len = min(x0 + 32, g.W) - lo;
     uint32_t b = 0;
-#pragma unroll
-    for (int e = 0; e < CE; ++e) b |= (ElemTraits<T>::to_f32(el[e]) > thr ? 1u : 0u) << e;
-    if (border_above) b = ~b;
-    int left = CE;
-    if (o < 0) b >>= -o, left += o, o = 0;
-    left = min(left, run - o);
-    int row = (int)fdiv((uint32_t)o, sg.div_w), x = o - row * g.W;
-    row += ih_lo - top;
-    while (left > 0) {
-      const int len = min(left, g.W - x), pos = c * sg.ch_bits + row * pitch + x + g.pad, sh = pos & 31;
-      const uint32_t seg = b & ((1u << len) - 1u);
-      atomicOr(&bits[pos >> 5], seg << sh);
-      if (sh + len > 32) atomicOr(&bits[(pos >> 5) + 1], seg >> (32 - sh));
-      b >>= len, left -= len, x = 0, ++row;
+    if (ih >= 0 && ih < g.H && len > 0) {
+      b = sens_word(A, img + ((long)(ch_lo + c) * g.H + ih) * g.W + lo, len, min(g.W, 32), end, thr);
+      if (border_above) b = ~b;
+      b = (len < 32 ? b & ((1u << len) - 1u) : b) << (lo - x0);
     }
+    bits[i] = b;
   }
-  for (int i = threadIdx.x; i < w; i += 256) {
+  for (int i = tid; i < w; i += NT) {
     const int q = q0 + i;
     const int ch = (int)fdiv((uint32_t)q, sg.div_taps), tap = q - ch * taps;
     const int kh = (int)fdiv((uint32_t)tap, sg.div_kw), kw = tap - kh * g.KW;
-    col_lut[i] = (ch - ch_lo) * sg.ch_bits + kh * pitch + kw;
+    col_lut[i] = (ch - ch_lo) * ch_bits + kh * pitch + kw;
   }
-  for (int i = threadIdx.x; i < h; i += 256) {
+  for (int i = tid; i < h; i += NT) {
     const int p = r0 + i;
     const int oh = (int)fdiv((uint32_t)p, sg.div_wo), ow = p - oh * g.Wo;
     row_lut[i] = (oh - oh_lo) * g.stride * pitch + ow * g.stride;
   }
-  __syncthreads();
   constexpr uint32_t C1L = 0x1CE4E5B9u, C1H = 0xBF58476Du, C2L = 0x133111EBu, C2H = 0x94D049BBu;
-  for (int gi = 0; gi < nb; ++gi) {
-    const int region = ((n * g.RB) + rb_first + gi) * g.CB + cb;
-    const int* rows = row_lut + gi * g.x;       // rows of this band within the group
-    const int hb = min(g.x, h - gi * g.x);
-    const int size = hb * w;
-    int s = (int)(((long)k_permille * size) / 1000);
-    if (s < 1) s = 1;
+  constexpr uint64_t C1 = ((uint64_t)C1H << 32) | C1L;
+  constexpr uint32_t g16 = (uint32_t)(kSensGolden & 0xffffu);
+  for (int i = NT - 1 - tid; i < nb; i += NT) {
+    SensBand v{};
+    v.h = min(g.x, h - i * g.x);
+    v.s = max(1, (int)(((long)k_permille * v.h * w) / 1000));
     // z = (prefix ^ index) + golden, index = region * 65536 + j: its bits from 16 up, without and with the carry
-    const uint64_t P = prefix ^ ((uint64_t)region << 16);
-    uint32_t m[2];
-    uint32_t K[2][2];
+    const uint64_t P = prefix ^ ((uint64_t)(((n * g.RB) + rb_first + i) * g.CB + cb) << 16);
     for (int cy = 0; cy < 2; ++cy) {
       const uint64_t H = ((P >> 16) + (kSensGolden >> 16) + cy) & 0xffffffffffffULL;
-      m[cy] = (uint32_t)(H >> 14) & 0xffffu;                       // what z >> 30 puts on the lowest 16 bits
-      const uint64_t k = ((H ^ (H >> 30)) << 16) * (((uint64_t)C1H << 32) | C1L);
-      K[cy][0] = (uint32_t)k, K[cy][1] = (uint32_t)(k >> 32);
-      asm("" : "+s"(m[cy]), "+s"(K[cy][0]), "+s"(K[cy][1]));  // (else every draw multiplies the constant it has chosen)
+      v.m[cy] = (uint32_t)(H >> 14) & 0xffffu;  // what z >> 30 puts on the lowest 16 bits
+      v.K[cy] = ((H ^ (H >> 30)) << 16) * C1;
     }
-    const uint32_t p16 = (uint32_t)P & 0xffffu, g16 = (uint32_t)(kSensGolden & 0xffffu);
+    v.p16 = (uint32_t)P & 0xffffu;
+    bands[i] = v;
+  }
+  __syncthreads();
+  // A wavefront takes a quarter of the low bytes of one band at a time; of the bands beyond the last full round of the
+  // workgroup it takes shares of the i, so that all wavefronts end together (rows of 8 positions: 7 rounds -> 6 and a part).
+  constexpr int PER = kSensWaves / 4;  // bands of a round
+  const int full = nb - nb % PER, jobs = (full + (nb - full) * PER) * 4;
+  for (int job = wave; job < jobs; job += kSensWaves) {
+    const int b4 = job >> 2, quarter = job & 3, part_of = b4 < full ? 1 : PER;
+    const int band = b4 < full ? b4 : full + (b4 - full) / PER, chunk = b4 < full ? 0 : (b4 - full) % PER;
+    const int* rows = row_lut + band * g.x;  // rows of this band within the group
+    const SensBand& B = bands[band];
+    const int s = __builtin_amdgcn_readfirstlane(B.s), hb = __builtin_amdgcn_readfirstlane(B.h), ni = (s + 255) >> 8;
+    const int share = part_of == 1 ? ni : (ni + PER - 1) / PER, i_lo = chunk * share, i_hi = min(ni, i_lo + share);
+    const uint64_t K0 = B.K[0], K1 = B.K[1];
+    const uint32_t m0 = B.m[0], m1 = B.m[1], p16 = B.p16;
+    const uint32_t t = (uint32_t)(quarter * 64 + lane), alo = t + (g16 & 255u), j_lo = t ^ (p16 & 255u);
+    const bool c0 = alo > 255u;
+    const uint64_t mine0 = (uint64_t)((alo ^ m0) & 255u) * C1, mine1 = (uint64_t)((alo ^ m1) & 255u) * C1;
     uint32_t c = 0;
-    // (four draws in flight per thread: their table and LDS reads overlap)
-#pragma unroll 4
-    for (int j = threadIdx.x; j < s; j += 256) {
-      const uint32_t a = (p16 ^ (uint32_t)j) + g16;
-      const bool cy = a > 0xffffu;
-      const uint32_t l = (a & 0xffffu) ^ (cy ? m[1] : m[0]);
-      const uint64_t y = (uint64_t)l * C1L + (((uint64_t)(cy ? K[1][1] : K[0][1]) << 32) | (cy ? K[1][0] : K[0][0]));
+    // the part of i = i0 + lane; bit l of cy: do the 16 bits of i0 + l carry?
+    auto part = [&](int i, uint32_t carry, uint64_t& cy) {
+      const uint32_t ahi = ((p16 >> 8) ^ (uint32_t)i) + (g16 >> 8) + carry;
+      const bool over = ahi > 255u;
+      cy = __ballot(over);
+      return (over ? K1 : K0) + (((uint64_t)((ahi ^ ((over ? m1 : m0) >> 8)) & 255u) * C1) << 8);
+    };
+    auto lane64 = [](uint64_t v, int k) {
+      return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), k) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)v, k);
+    };
+    auto place = [&](uint64_t y) {  // bit number of the draw whose first product is y
       uint32_t ylo = (uint32_t)y, yhi = (uint32_t)(y >> 32);
-      yhi += __umul24(l, C1H & 0xffffffu) + (__umul24(l, C1H >> 24) << 24);
       ylo ^= (yhi << 5) | (ylo >> 27);
       yhi ^= yhi >> 27;
       uint32_t u = __umulhi(ylo, C2L) + ylo * C2H + yhi * C2L;
       u ^= u >> 31;
       const uint64_t uh = (uint64_t)u * (uint32_t)hb;
-      const uint32_t bit = (uint32_t)rows[(uint32_t)(uh >> 32)] + (uint32_t)col_lut[__umulhi((uint32_t)uh, (uint32_t)w)];
-      c += (bits[bit >> 5] >> (bit & 31)) & 1u;
-    }
-    int n_above = border_above ? -(int)c : (int)c;
-    for (int o = 32; o > 0; o >>= 1) n_above += __shfl_down(n_above, o, 64);
-    if ((threadIdx.x & 63) == 0) wave_cnt[threadIdx.x >> 6] = n_above;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const int tot = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3] + (border_above ? s : 0);
-      count[region] = tot;
-      samples[region] = s;
-      sens[region] = (1000L * tot >= (long)t_permille * s) ? 1 : 0;
-    }
-    __syncthreads();  // (wave_cnt is reused by the next band)
+      return (uint32_t)rows[(uint32_t)(uh >> 32)] + (uint32_t)col_lut[__umulhi((uint32_t)uh, (uint32_t)w)];
+    };
+    auto share_of = [&](auto carries) {
+      for (int i0 = i_lo; i0 < i_hi; i0 += 64) {
+        const int e = min(64, i_hi - i0), whole = i0 + e > s >> 8 ? e - 1 : e;  // (the last i of a band may be a partial one)
+        uint64_t cy0, cy1 = 0, S1 = 0;
+        const uint64_t S0 = part(i0 + lane, 0, cy0);
+        if constexpr (decltype(carries)::value) S1 = part(i0 + lane, 1, cy1);
+        const uint64_t low_carries = __ballot(c0);
+        auto at = [&](int k) {
+          uint64_t S = lane64(S0, k), over;  // (which lanes' 16 bits carry: all alike but for low_carries)
+          asm("s_bitcmp1_b64 %1, %2\n\ts_cselect_b64 %0, -1, 0" : "=s"(over) : "s"(cy0), "s"(k) : "scc");
+          if constexpr (decltype(carries)::value) {
+            uint64_t over1;
+            asm("s_bitcmp1_b64 %1, %2\n\ts_cselect_b64 %0, -1, 0" : "=s"(over1) : "s"(cy1), "s"(k) : "scc");
+            S = c0 ? lane64(S1, k) : S;
+            over = (over & ~low_carries) | (over1 & low_carries);
+          }
+          uint32_t lo, hi;
+          asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(lo) : "v"((uint32_t)mine0), "v"((uint32_t)mine1), "s"(over));
+          asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(hi) : "v"((uint32_t)(mine0 >> 32)), "v"((uint32_t)(mine1 >> 32)), "s"(over));
+          return place(S + (((uint64_t)hi << 32) | lo));
+        };
+        int k = 0;
+        for (; k + 4 <= whole; k += 4) {  // (four draws in flight: their table and LDS reads overlap)
+          uint32_t bit[4], word[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) bit[q] = at(k + q);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) word[q] = bits[bit[q] >> 5];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) c += __builtin_amdgcn_ubfe(word[q], bit[q], 1);
+        }
+        for (; k < e; ++k)
+          if (k < whole || (int)j_lo < (s & 255)) {
+            const uint32_t bit = at(k);
+            c += __builtin_amdgcn_ubfe(bits[bit >> 5], bit, 1);
+          }
+      }
+    };
+    if (quarter < 3) share_of(std::integral_constant<bool, false>{});
+    else share_of(std::integral_constant<bool, true>{});
+    // sum over the wavefront, to its last lane
+#define ARD_SENS_DPP(ctrl, rows) c += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, ctrl, rows, 0xf, false)
+    ARD_SENS_DPP(0x111, 0xf);  // 1, 2, 4, 8 lanes within a row of 16
+    ARD_SENS_DPP(0x112, 0xf);
+    ARD_SENS_DPP(0x114, 0xf);
+    ARD_SENS_DPP(0x118, 0xf);
+    ARD_SENS_DPP(0x142, 0xa);  // the rows before
+    ARD_SENS_DPP(0x143, 0xc);
+#undef ARD_SENS_DPP
+    if (lane == 63) atomicAdd(&bands[band].hits, (int)c);
+  }
+  __syncthreads();
+  for (int i = tid; i < nb; i += NT) {
+    const int s = bands[i].s, tot = border_above ? s - bands[i].hits : bands[i].hits;
+    const int region = ((n * g.RB) + rb_first + i) * g.CB + cb;
+    count[region] = tot;
+    samples[region] = s;
+    sens[region] = (1000L * tot >= (long)t_permille * s) ? 1 : 0;
   }
 }
 
@@ -451,42 +559,38 @@ extern "C" int32_t ard_sens_predict(int32_t dtype, int32_t N, int32_t C, int32_t
     // footprint of a region in LDS when it fits: rows a band can touch x whole width x channels of a block
     const int taps = kh * kw;
     const int nch_max = imin(C, (g.y + taps - 2) / taps + 1);
-    // Bands per workgroup.  Consecutive bands touch nearly the same input rows when they are shorter than an
-    // output row (98 bands of 8 positions would copy a 28 x 28 image 14 times over), and a band with few draws
-    // does not pay for its copy: a workgroup takes up to 16 bands, as many as bring it to about 40 k draws,
-    // provided their common footprint is well below the sum of theirs (else grouping only costs workgroups) and
-    // the launch keeps two workgroups per CU.  Config-5 layer, 30 % sampled, one band -> chosen number:
-    // rows of 8 positions 185 -> 138 us (7 bands: two whole rows), of 4 positions 248 -> 139 us (14), of 16
-    // positions 149 -> 147 us (3), 8 x 64 blocks 951 -> 285 us (16); regions of 112 x 576 stay alone (113 us,
-    // two per workgroup 131 us).
-    int G = 1, nrow_max = 0, ch_bits = 0, rows1 = 0;
+    // Bands per workgroup.  Consecutive bands touch nearly the same input rows when they are shorter than an output row
+    // (98 bands of 8 positions would copy a 28 x 28 image 14 times over), so a workgroup takes as many as still leave two
+    // for every CU, unless their footprint would take more LDS than two may have.  (Longer ones in proportion to the
+    // image copy less; fewer workgroups leave CUs without work.)
+    const int words = (Wd + 2 * pad + 31) / 32;
+    int RBG = imin(imax(1, ceil_div(8192 / kSensWaves, (int)((long)N * g.CB < 8192 ? N * g.CB : 8192))), g.RB), G = 1, nrow = 0;
     size_t stage_bytes = 0;
-    const long draws = imax(1, (int)(((long)k_permille * g.x * g.y) / 1000));
-    const int g_cap = (int)imin(16, imax(1, (int)(40000 / draws)));
-    for (int cand = 1; cand <= g_cap && cand <= imax(1, g.RB); ++cand) {
+    for (;; ++RBG) {
+      G = ceil_div(g.RB, RBG);
       // output rows a group can span: groups of whole rows start on a row, any other may start anywhere in one
-      const int oh_span = (cand * g.x) % g.Wo == 0 ? cand * g.x / g.Wo : (cand * g.x + g.Wo - 2) / g.Wo + 1;
-      const int nr = (imin(oh_span, g.Ho) - 1) * stride + kh, bits = nr * (Wd + 2 * pad);
-      const size_t bytes = (((size_t)bits * nch_max + 31) / 32 + 1 + g.y + cand * g.x) * 4;
-      if (cand == 1) rows1 = nr;
-      if (cand == 1 || (4 * nr <= 3 * cand * rows1 && bytes <= 64 * 1024 && (long)N * ceil_div(g.RB, cand) * g.CB >= 512))
-        G = cand, nrow_max = nr, ch_bits = bits, stage_bytes = bytes;
+      const long span = (long)G * g.x;
+      const long oh_span = span % g.Wo == 0 ? span / g.Wo : (span + g.Wo - 2) / g.Wo + 1;
+      nrow = ((int)(oh_span < g.Ho ? oh_span : g.Ho) - 1) * stride + kh;
+      stage_bytes = ((size_t)nrow * words * nch_max + g.y + (size_t)G * g.x) * 4 + G * sizeof(SensBand);
+      if (G == 1 || stage_bytes <= (size_t)4608 * kSensWaves) break;
     }
+    RBG = ceil_div(g.RB, G);
     // (pad < filter size: every window then starts inside the image, which the copy's bounds rely on)
-    if ((((uintptr_t)A) & 15) == 0 && stage_bytes <= 150 * 1024 && (long)ch_bits * nch_max < (1L << 30) && pad < kh && pad < kw) {
-      const int RBG = ceil_div(g.RB, G);
-      const SensStage sg{nrow_max, ch_bits, fast_div((uint32_t)taps), fast_div((uint32_t)kw), fast_div((uint32_t)g.Wo), fast_div((uint32_t)Wd), G, RBG};
+    if ((((uintptr_t)A) & 15) == 0 && stage_bytes <= 150 * 1024 && (long)nrow * words * 32 * nch_max < (1L << 30) && pad < kh && pad < kw) {
+      const SensStage sg{nrow, words, fast_div((uint32_t)taps), fast_div((uint32_t)kw), fast_div((uint32_t)g.Wo), fast_div((uint32_t)words),
+                         fast_div((uint32_t)(nrow * words)), G, RBG};
       const unsigned groups = (unsigned)((long)N * RBG * g.CB);
       hipError_t e = hipSuccess;
       if (dtype == ARD_BF16) {
         if (stage_bytes > 65536) e = raise_lds_limit((const void*)sens_predict_staged_kernel<uint16_t>, (int)stage_bytes);
         if (e == hipSuccess)
-          ARD_LAUNCH(sens_predict_staged_kernel<uint16_t>, dim3(groups), dim3(256), stage_bytes, (hipStream_t)stream,
+          ARD_LAUNCH(sens_predict_staged_kernel<uint16_t>, dim3(groups), dim3(64 * kSensWaves), stage_bytes, (hipStream_t)stream,
                      (const uint16_t*)A, g, sg, k_permille, t_permille, threshold, prefix, d_count, d_samples, d_sens);
       } else {
         if (stage_bytes > 65536) e = raise_lds_limit((const void*)sens_predict_staged_kernel<float>, (int)stage_bytes);
         if (e == hipSuccess)
-          ARD_LAUNCH(sens_predict_staged_kernel<float>, dim3(groups), dim3(256), stage_bytes, (hipStream_t)stream, (const float*)A, g,
+          ARD_LAUNCH(sens_predict_staged_kernel<float>, dim3(groups), dim3(64 * kSensWaves), stage_bytes, (hipStream_t)stream, (const float*)A, g,
                      sg, k_permille, t_permille, threshold, prefix, d_count, d_samples, d_sens);
       }
       if (e != hipSuccess) return fail(ARD_EHIP, "raising the LDS limit failed: %s", hipGetErrorString(e));

@@ -21,3 +21,17 @@ def test_odd_planes_and_thresholds(dtype, N, C, H, W, k, stride, pad, x, y, thr)
     Av = stored(rng.standard_normal((N, C, H, W)), dtype)
     for seed in (1, 123456789, 2 ** 63 + 5):
         _predict_both(Av, from_vals(Av, dtype), k, stride, pad, x, y, 300, 500, thr, seed, seed % 7)
+
+
+@pytest.mark.parametrize("N,C,H,W,k,stride,pad,x,y,permille", [
+    (2, 3, 5, 30, 3, 1, 1, 30, 27, 300), (2, 2, 4, 31, 3, 1, 1, 31, 0, 300), (1, 2, 4, 62, 3, 1, 1, 62, 0, 1000), (1, 2, 4, 63, 3, 1, 1, 7, 0, 500),
+    (3, 1, 3, 33, 1, 1, 0, 33, 0, 1000), (1, 5, 9, 9, 3, 1, 1, 1, 0, 1), (1, 4, 16, 16, 3, 1, 1, 256, 0, 1000), (2, 30, 9, 13, 3, 1, 1, 13, 54, 900)])
+def test_words_of_a_row_and_shares_of_a_band(N, C, H, W, k, stride, pad, x, y, permille):
+    """Bordered rows of exactly one and two words and one element more, odd first elements, the words at the tensor's end; bands
+    of one draw, of whole and part rounds of 256 draws, and of more than 64 rounds; one band and many per workgroup."""
+    print("prediction, words", N, C, H, W, k, x, y, permille, flush=True)
+    rng = np.random.default_rng(H * W + C)
+    for dtype in ("bf16", "f32"):
+        Av = stored(rng.standard_normal((N, C, H, W)), dtype)
+        for seed, thr in ((11, 0.1), (2 ** 61 + 3, -0.3)):
+            _predict_both(Av, from_vals(Av, dtype), k, stride, pad, x, y, permille, 500, thr, seed, 2)
