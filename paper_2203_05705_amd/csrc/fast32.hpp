@@ -215,6 +215,14 @@ __host__ __device__ __forceinline__ void f32_steps(const Axis& k, int& full, int
   rem = n & 15;
 }
 
+// f(std::integral_constant<int, n>) for the n in 1 .. N.
+template <int N, class F>
+__device__ __forceinline__ void f32_pick(int n, const F& f) {
+  if constexpr (N == 1) f(std::integral_constant<int, 1>{});
+  else if (n == N) f(std::integral_constant<int, N>{});
+  else f32_pick<N - 1>(n, f);
+}
+
 // Tile of 16*TM*WM x 16*TN*WN outputs, the contraction dealt over WK groups of wavefronts, D steps in flight.
 // MODE 0: plain product.  MODE 1: convolution (A: packed weights, B: pixels of the bordered grid).
 // MODE 2: its weight gradient, contraction over the pixels of the grid planes.  Between the output positions lie border
@@ -336,7 +344,24 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
     // many younger loads may stay in flight when a step's operands are wanted (with loads behind branches it
     // waited for all of them: a whole memory latency every D steps).
     constexpr int LOADS = F32Loader<AK, TM>::LOADS + F32Loader<BK, TN>::LOADS, MMAS = 4 * TM * TN;
-    if (n_full > 0) {
+    // Small tiles with operands at 4 bytes a load take a contraction of few steps at once, or in two goes, in code of its
+    // own for each number of them, so that this counting still works: the rounds load up to D - 1 steps past the end, which
+    // with loads this narrow cost as much as the contraction did (145 x 448 -> 320, strides 3 and 4: forward and data
+    // gradient 9.7 -> 5.0 us; 64 x 784 -> 1024, stride 2: data gradient 10.4 -> 7.6, weight gradient 7.7 -> 6.5).  With wide
+    // loads it gains nothing (6.0 against 5.8 us) and its code delays the rounds (7.0 -> 7.7 us of 12 steps).
+    auto at_once = [&](auto steps) {
+      constexpr int N = decltype(steps)::value;
+#pragma unroll
+      for (int d = 0; d < N; ++d) load(d);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int d = 0; d < N; ++d) mma(a[d], b[d]);
+    };
+    constexpr bool SCATTERED = AK == F32_KC || BK == F32_KC || AK == F32_MC || BK == F32_MC;
+    if (SCATTERED && BM * BN <= 1024 && n_full > 0 && n_full <= 2 * D - 2) {
+      if (n_full > D) at_once(std::integral_constant<int, D>{});
+      f32_pick<D>(n_full > D ? n_full - D : n_full, at_once);
+    } else if (n_full > 0) {
 #pragma unroll
       for (int d = 0; d < D - 1; ++d) {
         load(d);
@@ -440,6 +465,30 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   const float alpha = raw ? 1.0f : C.alpha, beta = raw ? 0.0f : C.beta;
   const float* const src = raw ? nullptr : (const float*)C.relu_src;
   const bool relu = !raw && C.relu;
+  // 16 x 16 tiles whose results own few positions: an element per thread, stored with the zeros that it owns.  Such a
+  // product is over in a few thousand clocks, of a wavefront or two per SIMD at 7 - 8 clocks an instruction: every
+  // instruction counts (64 x 784 -> 1024, dp = 2: the tables and the general loop below took 3300 of a workgroup's 11400
+  // clocks, this takes 1800; the product 6.4 -> 5.9 us).  Four elements a thread of a 32 x 32 tile are no faster so, and
+  // slower where a row's zeros are wide apart (4.6 -> 5.2 us at 128 x 683, every third column).
+  if (MODE == 0 && BM * BN <= 256 && !classes && beta == 0.0f && rows.kind == AX_AFFINE && cols.kind == AX_AFFINE && (!fill || rows.step * cols.step <= 4)) {
+    const int i_ok = imin(P.M, w.am.n), j_ok = imin(P.N, w.bn.n);
+    const int lr = tid / BN, lc = tid % BN, i = w.m0 + lr, j = w.n0 + lc;
+    if (i >= P.M || j >= P.N) return;
+    float x = alpha * sum(lr, lc);
+    if (relu) x = fmaxf(x, 0.0f);
+    if (i >= i_ok || j >= j_ok) x = 0.0f;  // (beyond the operand: padding of a compact output)
+    const int r = rows.off + i * rows.step, c = cols.off + j * cols.step;
+    if (src) x = src[(long)r * ld + c] > 0.0f ? x : 0.0f;
+    if (!fill) {
+      out[(long)r * ld + c] = x;
+      return;
+    }
+    float* o = out + (long)(i * rows.step) * ld + j * cols.step;
+    const int na = i == P.M - 1 ? rows.nphys - i * rows.step : rows.step, nb = j == P.N - 1 ? cols.nphys - j * cols.step : cols.step;
+    for (int a = 0; a < na; ++a, o += ld)
+      for (int b = 0; b < nb; ++b) o[b] = a == rows.off && b == cols.off ? x : 0.0f;
+    return;
+  }
   const int m_lim = P.c_rows_mapped ? w.am.n : P.M, n_lim = P.c_cols_mapped ? w.bn.n : P.N;
   const int m1 = imin(w.m0 + BM, m_lim), n1 = imin(w.n0 + BN, n_lim);
   // physical row of every row of the tile, -1 beyond the matrix (a class's last block may end beyond it), and
@@ -468,6 +517,116 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   const int sc = walk ? cols.step : 1;
   const int c_end = walk && n1 == P.N ? cols.nphys : n1 * sc;
   const int nr = m1 - w.m0, i_ok = classes ? nr : imin(nr, w.am.n - w.m0);
+  // Large tiles of plain products: runs of four physical columns leave as one store (at any dword).  A thread works out
+  // once which of its four are kept and then goes down the rows, the wavefronts' partial tiles summed in place before (the
+  // loop below sums them again for each position of a strided map).  128 x 2048 -> 2048, dp 2 and 2, weight gradient: 21400
+  // -> 12500 clocks of output, 14.4 -> 12.8 us.  With smaller tiles, tile classes and convolutions the setting up costs
+  // what it saves (10.2 -> 10.8 us at 24 x 1472 -> 448 in tiles, 136.6 -> 138 us in three products of a convolution).
+  const bool runs = MODE == 0 && BM * BN >= 4096 && !classes && beta == 0.0f && cols.kind == AX_AFFINE && (walk || cols.step == 1);
+  if (MODE == 0 && BM * BN >= 4096 && runs) {
+    if constexpr (WK > 1) {  // the partial tiles, summed in place
+      for (int e = tid; e < BM * BN; e += 256) {
+        const int lr = e / BN, lc = e % BN;
+        lds[lr * PITCH + lc] = sum(lr, lc);
+      }
+      __syncthreads();
+    }
+    const int c_lo = w.n0 * sc, pieces = (c_end - c_lo + 3) >> 2;
+    const int pw = pieces > 128 ? 256 : 1 << (32 - __builtin_clz(imax(pieces, 1) * 2 - 1) - 1);  // threads along a row
+    const int pr0 = tid / pw, pc0 = tid % pw, rp = 256 / pw;
+    for (int pc = pc0; pc < pieces; pc += pw) {
+      const int c = c_lo + 4 * pc, nc = imin(4, c_end - c);
+      const int at = walk ? c : cols.off + c;  // of the run within an output row
+      int lc[4];      // its columns in the tile
+      uint32_t m[4];  // kept, and within the operand (beyond it: padding of a compact output, zero)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        int j = c + t;
+        bool ok = t < nc;
+        if (walk) {
+          const int d = j - cols.off, q = d >= 0 ? (int)fdiv((uint32_t)d, P.col_div) : 0;
+          ok = ok && d >= 0 && q * sc == d && q < P.N;
+          j = q;
+        }
+        ok = ok && j < w.bn.n;
+        lc[t] = ok ? j - w.n0 : 0;
+        m[t] = ok ? ~0u : 0u;
+        asm("" : "+v"(m[t]));
+      }
+      auto store = [&](int r, const float (&x)[4]) {
+        float* const o = out + (long)r * ld + at;
+        if (nc == 4) {
+          *reinterpret_cast<F32Run<4>*>(o) = F32Run<4>{{x[0], x[1], x[2], x[3]}};
+        } else {
+#pragma unroll
+          for (int t = 0; t < 3; ++t)
+            if (t < nc) o[t] = x[t];
+        }
+      };
+      constexpr int U = 4;  // rows at a time: everything read before anything is nc
+#pragma unroll 1
+      for (int l0 = pr0; l0 < nr; l0 += U * rp) {
+        float x[U][4];
+        int pr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int lr = imin(l0 + u * rp, nr - 1);
+          pr[u] = l0 + u * rp < nr ? r_p[lr] : -1;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) x[u][t] = lds[lr * PITCH + lc[t]];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          uint32_t row_ok = l0 + u * rp < i_ok ? ~0u : 0u;
+          asm("" : "+v"(row_ok));
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            x[u][t] = __uint_as_float(__float_as_uint(alpha * x[u][t]) & m[t] & row_ok);
+            if (relu) x[u][t] = fmaxf(x[u][t], 0.0f);
+          }
+        }
+        if (src) {
+          float g[U][4];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const float* q = src + (long)imax(pr[u], 0) * ld + at;
+            if (nc == 4) {
+              const F32Run<4> v = *reinterpret_cast<const F32Run<4>*>(q);
+#pragma unroll
+              for (int t = 0; t < 4; ++t) g[u][t] = v.f[t];
+            } else {
+#pragma unroll
+              for (int t = 0; t < 4; ++t) g[u][t] = t < nc ? q[t] : 0.0f;
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x[u][t] = g[u][t] > 0.0f ? x[u][t] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (pr[u] >= 0) store(pr[u], x[u]);
+      }
+      if (!fill || rows.n == rows.nphys) continue;
+      const float zeros[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (list_fill) {
+        for (int lr = pr0; lr < nr; lr += rp)
+          for (int r = r_lo[lr]; r < r_hi[lr]; ++r)
+            if (r != r_p[lr]) store(r, zeros);
+      } else {
+        // row i owns [i*step, (i+1)*step), the last one also the rest
+        for (int lr = pr0; lr < nr; lr += rp)
+          for (int g = 0; g < rows.step; ++g) {
+            const int r = (w.m0 + lr) * rows.step + g;
+            if (g != rows.off && r < rows.nphys) store(r, zeros);
+          }
+        if (m1 == P.M)
+          for (int r = P.M * rows.step + pr0; r < rows.nphys; r += rp) store(r, zeros);
+      }
+    }
+    return;
+  }
   for (int c = w.n0 * sc + tc; c < c_end; c += CL) {
     int j = c, clo, chi, cp;
     if constexpr (MODE == 1) {
