@@ -1357,27 +1357,29 @@ static int32_t conv_grid_gemm(const uint16_t* Wp, int rows, int K, const uint16_
   F.M = rows;
   F.N = cv.npix;
   F.cv = cv;
+  F.cv.set_divisors(K / cv.Cp);
   F.kb_list = kb_list, F.kb_cnt = kb_cnt, F.kb_stride = kb_stride;
   int bm, bn;
   if (force_bn) {
     bm = force_bn == 128 || rows > 128 ? 256 : 128;
     bn = force_bn;
   } else {
-    // A launch runs in rounds: one workgroup of a large shape fills a CU (256 at a time), three of the 64 x 64
-    // shape share one (768 at a time).  Measured on the 3x3 layers, a round of 256 x 128 or 128 x 256 tiles
-    // takes 0.68 and a round of 64 x 64 tiles 0.34 of a round of 256 x 256 tiles: fewest rounds x cost wins
-    // (so a layer with few output positions goes to small tiles on many CUs instead of large ones on a few).
-    const auto rounds = [&](int tm, int tn, long slots) { return ((long)ceil_div(rows, tm) * ceil_div(cv.npix, tn) + slots - 1) / slots; };
-    long best = rounds(64, 64, 768) * 34;
-    bm = bn = 64;
-    if (rows > 64) {
-      const long c = rounds(128, 256, 256) * 68;
-      if (c <= best) best = c, bm = 128, bn = 256;
-    }
-    if (rows > 128) {
-      const long c1 = rounds(256, 128, 256) * 68, c2 = rounds(256, 256, 256) * 100;
-      if (c1 <= best) best = c1, bm = 256, bn = 128;
-      if (c2 <= best) best = c2, bm = 256, bn = 256;
+    // A launch runs in rounds: one workgroup of a large shape fills a CU (256 at a time), three of the 64 x 64 shape share
+    // one (768 at a time).  Costs of a round, a 256 x 256 round being 100, are means of contractions of 1152 and 2304
+    // (27.5, 34.6 and 43.2 us with 256 rows and 128, 192, 256 columns at 1152; 48, 62.5 and 71 us with 128 rows and 256,
+    // 384, 448 columns at 2304): a step of the large tiles takes about the time its operands take to arrive, 25 bytes per
+    // clock and CU.  Fewest rounds x cost wins, so a layer with few output positions goes to small tiles on many CUs
+    // instead of large ones on a few, and one a little above a full round goes to wider tiles (128 rows, 100352 pixels:
+    // two rounds of 256 columns 89 us, one of 448 70 us).  256 rows read their pixels twice in tiles of 128 rows: 82 us in
+    // two rounds of 448 against 77 of 256 x 256, so 448 is dearer.
+    static const struct { int bm, bn, slots, cost; } kTiles[] = {{64, 64, 768, 46}, {128, 256, 256, 66}, {256, 128, 256, 66}, {256, 192, 256, 82},
+                                                                 {128, 384, 256, 88}, {128, 448, 256, 102}, {256, 256, 256, 100}};
+    long best = -1;
+    bm = bn = 0;
+    for (const auto& t : kTiles) {
+      if (t.bm > 64 && rows <= t.bm / 2) continue;
+      const long c = ((long)ceil_div(rows, t.bm) * ceil_div(cv.npix, t.bn) + t.slots - 1) / t.slots * t.cost;
+      if (best < 0 || c <= best) best = c, bm = t.bm, bn = t.bn;
     }
   }
   F.tiles_m = ceil_div(rows, bm);
@@ -1388,6 +1390,9 @@ static int32_t conv_grid_gemm(const uint16_t* Wp, int rows, int K, const uint16_
   set_bands(F, direct_group_m(F.total_tiles));
   const int grid = direct_plain_grid(F.total_tiles);
   if (bm == 256 && bn == 256) return launch_direct_kernel<true, true, 256, 256, 8, 1>(F, grid, stream);
+  if (bm == 256 && bn == 192) return launch_direct_kernel<true, true, 256, 192, 8, 1>(F, grid, stream);
+  if (bm == 128 && bn == 384) return launch_direct_kernel<true, true, 128, 384, 8, 1>(F, grid, stream);
+  if (bm == 128 && bn == 448) return launch_direct_kernel<true, true, 128, 448, 8, 1>(F, grid, stream);
   if (bm == 256) return launch_direct_kernel<true, true, 256, 128, 8, 1>(F, grid, stream);
   if (bm == 128) return launch_direct_kernel<true, true, 128, 256, 8, 1>(F, grid, stream);
   return launch_direct_kernel<true, true, 64, 64, 4, 1>(F, grid, stream);
@@ -1571,6 +1576,7 @@ static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, c
   F.M = a.Cout;
   F.N = Nn;
   F.cv = ConvMap{a.Ho * a.Wo, a.Wo, Hg * Wg, Wg, Cpa, a.kw, 0, 0, nullptr, 0, nullptr, a.N * a.Ho * a.Wo, -1};
+  F.cv.set_divisors(taps);
   if (listed) F.li = ListMap{0, a.lists.stride, a.N * a.Ho * a.Wo, ceil_div(cols, 128), cols, a.cpb, group, a.N * Hg * Wg, a.lists.list, a.lists.cnt};
   set_bands(F, direct_group_m(F.total_tiles));
   if (listed)

@@ -73,7 +73,16 @@ struct ConvMap {
   // pix_fixed >= 0 (host-side bounds proof only): every column reads that pixel instead of the list.
   const int* pix;
   int pix_total, pix_fixed;
-  int pix_pairs;  // list entries 2i, 2i+1 are pixels 2m, 2m+1 of one image (or both padding): stored as one word
+  int pix_pairs;  // list entries 2i, 2i+1 are pixels 2m, 2m+1 of one image (or both padding): the list holds runs, stored in pieces
+  int taps;       // of the filter; it and what follows: set_divisors
+  FastDiv per_img, per_row, by_cp, by_kw, by_taps;  // HoWo, Wo, Cp, kw, taps
+  // Every lane finds its rows' pixels and every step its tap before anything is loaded: by division, a workgroup's first
+  // load came 4000 of a 256 x 256 tile's 70000 clocks after its start.
+  void set_divisors(int n_taps) {
+    taps = n_taps;
+    per_img = fast_div((uint32_t)HoWo), per_row = fast_div((uint32_t)Wo), by_cp = fast_div((uint32_t)Cp);
+    by_kw = fast_div((uint32_t)kw), by_taps = fast_div((uint32_t)n_taps);
+  }
 };
 
 // Weight gradient over listed output positions (MODE 3; row- and block-based sensitivity-aware patterns, Section 5.2):
@@ -156,6 +165,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 #define ARD_LDS_PTR(p) ((void __attribute__((address_space(3)))*)(p))
 #define ARD_GLB_PTR(p) ((const void __attribute__((address_space(1)))*)(p))
 
+// four words at any word address
+struct U4AnyWord {
+  uint32_t x, y, z, w;
+};
+
 // 64 zero bytes: source of the chunks that lie beyond the end of the contraction
 static __device__ uint4 g_zero_chunk[4];
 
@@ -213,8 +227,8 @@ template <int ROWS, int NW> struct DirectLoader<true, ROWS, NW> {
       int row = imin(row0 + (wave * NI + j) * 8 + (lane >> 3), cv.npix - 1);
       if (cv.pix_fixed >= 0) row = cv.pix_fixed;
       else if (cv.pix) row = imax(cv.pix[row], 0);  // (-1: padding entry, reads pixel 0, stores nothing)
-      const int n = row / cv.HoWo, rem = row - n * cv.HoWo;
-      const int ho = rem / cv.Wo, wo = rem - ho * cv.Wo;
+      const int n = (int)fdiv((uint32_t)row, cv.per_img), rem = row - n * cv.HoWo;
+      const int ho = (int)fdiv((uint32_t)rem, cv.per_row), wo = rem - ho * cv.Wo;
       voff[j] = (uint32_t)((n * cv.HgWg + ho * cv.Wg + wo) * cv.Cp + chunk_k(lane, wave, j)) * 2u;
     }
   }
@@ -295,8 +309,8 @@ template <int ROWS, int NW> struct DirectLoader<false, ROWS, NW> {
     for (int j = 0; j < NI; ++j) {
       const int kloc = KPI * (wave * NI + j) + lane / CPR;
       const int col = imin(row0 + lane_chunk(lane, wave, j) * 8, ncols - 8);
-      const int t = col / cv.Cp;
-      voff[j] = (uint32_t)(kloc * ld + ((t / cv.kw) * cv.Wg + t % cv.kw) * cv.Cp + (col - t * cv.Cp)) * 2u;
+      const int t = (int)fdiv((uint32_t)col, cv.by_cp), r = (int)fdiv((uint32_t)t, cv.by_kw);
+      voff[j] = (uint32_t)(kloc * ld + (r * cv.Wg + t - r * cv.kw) * cv.Cp + (col - t * cv.Cp)) * 2u;
     }
   }
   __device__ __forceinline__ void issue(uint4* op_tile, int kslab, int wave) const {
@@ -351,8 +365,8 @@ template <int ROWS, int NW> struct ListLoader {
     init(p, cv.Cp, li.cols, col0, lane, wave);
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
-      const int col = (int)(coff[j] >> 1), t = col / li.cols_per_tap;
-      coff[j] = (uint32_t)(((t / cv.kw) * cv.Wg + t % cv.kw) * cv.Cp + cb * li.chans + col - t * li.cols_per_tap) * 2u;
+      const int col = (int)(coff[j] >> 1), t = col / li.cols_per_tap, r = (int)fdiv((uint32_t)t, cv.by_kw);
+      coff[j] = (uint32_t)((r * cv.Wg + t - r * cv.kw) * cv.Cp + cb * li.chans + col - t * li.cols_per_tap) * 2u;
     }
   }
   __device__ __forceinline__ void look(const int* step_list, uint32_t (&off)[NI]) const {
@@ -419,6 +433,14 @@ __device__ __forceinline__ bf16x8_t frag_value(const Frag& f) {
 #define ARD_NST_SMALL 3
 #endif
 constexpr int direct_stages(int bm, int bn) { return bm + bn <= 128 ? ARD_NST_SMALL : 2; }
+// Wavefronts side by side along the columns, so that each has whole 32 x 32 tiles
+constexpr int direct_wave_columns(int bn, int nw) { return nw == 8 && (bn == 256 || bn == 384) ? 4 : 2; }
+// Dynamic LDS of a product: the operand stages, or in a convolution the output tile and its rows' channels if that is more.
+constexpr size_t direct_lds_bytes(int bm, int bn, int mode) {
+  const size_t stages = (size_t)direct_stages(bm, bn) * (bm + bn) * LDS_ROW_U4 * sizeof(uint4);
+  const size_t tile = (size_t)bm * (bn * 2 + 16) + (size_t)bm * 4;
+  return mode == 1 && tile > stages ? tile : stages;
+}
 
 template <class F, int... I>
 __device__ __forceinline__ void static_for_impl(const F& f, std::integer_sequence<int, I...>) {
@@ -608,9 +630,9 @@ __host__ __device__ __forceinline__ void direct_slab(const FastParams& P, const 
     // The steps run channel group by channel group, all taps of a group in a row: consecutive steps then read
     // the same 128 bytes of pixels that lie a few positions apart, nearly all of them lines the step before
     // left in L2 (tap by tap, a whole pass over the tile's channels lies between two reads of a line).
-    const int taps = kax.nphys / P.cv.Cp, cg = s / taps, t = s - cg * taps;
+    const int cg = (int)fdiv((uint32_t)s, P.cv.by_taps), t = s - cg * P.cv.taps, r = (int)fdiv((uint32_t)t, P.cv.by_kw);
     ks = t * P.cv.Cp + cg * 64;
-    ksb = ((t / P.cv.kw) * P.cv.Wg + t % P.cv.kw) * P.cv.Cp + cg * 64;
+    ksb = (r * P.cv.Wg + t - r * P.cv.kw) * P.cv.Cp + cg * 64;
     return;
   }
   ks = fast_kslab(kax, s * 64);
@@ -628,7 +650,7 @@ __host__ __device__ __forceinline__ void direct_slab(const FastParams& P, const 
 template <bool A_KC, bool B_KC, int F_BM, int BN, int NW, int MODE = 0>
 __device__ __forceinline__ void direct_body(const FastParams& P, const int block_id, uint4* const lds) {
   constexpr int NST = direct_stages(F_BM, BN);
-  constexpr int WGN = (NW == 8 && BN == 256) ? 4 : 2, WGM = NW / WGN;
+  constexpr int WGN = direct_wave_columns(BN, NW), WGM = NW / WGN;
   constexpr int WTM = F_BM / WGM, WTN = BN / WGN;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must hold whole MFMA tiles");
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -675,21 +697,18 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       kbl1 = 64 + lane < cnt ? imin(imax(e1, 0), last) : 0;
     }
   }
-  // the pixels this lane's columns are stored to, looked up before the contraction instead of after it
-  int out_pix[TN];
+  // the channel a row of the tile is stored to, looked up before the contraction instead of after it
+  int out_chan = 0;
   if constexpr (MODE == 1) {
-#pragma unroll
-    for (int in = 0; in < TN; ++in) {
-      const int jc = n0 + wn * WTN + in * 32 + (lane & 31);
-      out_pix[in] = jc < P.cv.npix ? (P.cv.pix ? P.cv.pix[jc] : jc) : -1;
-    }
+    const int i = m0 + tid;
+    if (tid < F_BM) out_chan = P.cv.chan && i < P.cv.n_rows ? P.cv.chan[i] : i;
   }
   auto slab = [&](int s, int& ks, int& ksb) {
     if constexpr (MODE == 1) {
       if (kb_mode) {
         ks = (s < 64 ? __builtin_amdgcn_readlane(kbl0, s) : __builtin_amdgcn_readlane(kbl1, s - 64)) * 64;
-        const int t = ks / P.cv.Cp;
-        ksb = ((t / P.cv.kw) * P.cv.Wg + t % P.cv.kw) * P.cv.Cp + (ks - t * P.cv.Cp);
+        const int t = (int)fdiv((uint32_t)ks, P.cv.by_cp), r = (int)fdiv((uint32_t)t, P.cv.by_kw);
+        ksb = (r * P.cv.Wg + t - r * P.cv.kw) * P.cv.Cp + (ks - t * P.cv.Cp);
         return;
       }
     }
@@ -791,13 +810,17 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
 #pragma unroll
       for (int in = 0; in < TN; ++in) frag_wait<B_KC>(fb[set][in]);
     };
+    // (a convolution's tiles come out transposed: a lane then holds four neighbouring pixels of a channel at a time)
+    auto mfma = [&](f32x16_t& c, const Frag& x, const Frag& y) {
+      if constexpr (MODE == 1) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_value<B_KC>(y), frag_value<A_KC>(x), c, 0, 0, 0);
+      else c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_value<A_KC>(x), frag_value<B_KC>(y), c, 0, 0, 0);
+    };
     auto mma = [&](int set) {
 #pragma unroll
       for (int im = 0; im < TM; ++im)
 #pragma unroll
         for (int in = 0; in < TN; ++in)
-          acc[im][in] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_value<A_KC>(fa[set][im]),
-                                                                frag_value<B_KC>(fb[set][in]), acc[im][in], 0, 0, 0);
+          mfma(acc[im][in], fa[set][im], fb[set][in]);
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
@@ -868,8 +891,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
         for (int im = 0; im < TM; ++im)
 #pragma unroll
           for (int in = 0; in < TN; ++in) {
-            acc[im][in] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_value<A_KC>(fa[1][im]), frag_value<B_KC>(fb[1][in]),
-                                                                  acc[im][in], 0, 0, 0);
+            mfma(acc[im][in], fa[1][im], fb[1][in]);
             ++mi;
 #pragma unroll
             for (int r = 0; r < (LPS + MM - 1) / MM; ++r)
@@ -915,7 +937,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
         __syncthreads();
         for (int i = e0 + tid; i < e1; i += 64 * NW) {
           const int p = imin(imax(src[imin(i, li_cnt - 1)], 0), top);
-          const int n = p / P.cv.HoWo, rem = p - n * P.cv.HoWo, ho = rem / P.cv.Wo;
+          const int n = (int)fdiv((uint32_t)p, P.cv.per_img), rem = p - n * P.cv.HoWo, ho = (int)fdiv((uint32_t)rem, P.cv.per_row);
           list[i - e0] = i < li_cnt ? n * P.cv.HgWg + ho * P.cv.Wg + rem - ho * P.cv.Wo : P.li.pad;
         }
         __syncthreads();
@@ -937,7 +959,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   const int n_valid = (MODE == 0 && P.ncls == 0) ? bn.n : 0x7fffffff;
   // (the 256 x 256 tile has no registers to spare: it only stores plain bf16 results)
   constexpr bool GENERAL_OUT = !(F_BM == 256 && BN == 256);
-  if (GENERAL_OUT && P.part) {
+  if (MODE != 1 && GENERAL_OUT && P.part) {
     // fp32 partial sums of this share of the contraction, compact [M x N]
     float* part = P.part + (long)split * P.M * P.N;
 #pragma unroll
@@ -957,97 +979,114 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     return;
   }
   if constexpr (MODE == 1) {
-    // NCHW output: compact row i -> channel (through the kept-channel list when there is one),
-    // column j -> pixel (n, hw) at n*out_chan*HW + hw.  Pairs of adjacent pixels are packed
-    // into 32-bit stores as below when the plane size is even.
+    // NCHW output: compact row i -> channel (through the kept-channel list when there is one), column j -> pixel (n, hw)
+    // at n*out_chan*HW + hw.  A lane holds row (lane & 31) of each 32 x 32 tile, its pixels 8*(v/4) + 4*(lane>>5) + v%4.
+    // The tile goes through LDS (the operand stages are dead by now) as bf16 [row][BN pixels], eight bytes at a time, and
+    // leaves in 16-byte pieces, a row of the tile one run of 2 BN bytes of its channel's plane.  Rows lie 2 BN + 16 bytes
+    // apart: the 16 rows that a store to LDS touches at a time start four banks apart.
+    // N=128, 28x28, 128 -> 256 channels, 3x3: with pixels in the lanes, exchanged between neighbours to make words of
+    // pairs, and the channel looked up before each store, a 256 x 256 tile's way out took 20000 of its 81000 clocks, now
+    // 9700; the product 82 -> 77 us, the data gradient of 256 channels from 256 (K = 2304) 125 -> 116 us.
     const ConvMap& cv = P.cv;
     const int HW = cv.HoWo;
-    const bool odd = lane & 1;
-    // (listed pixels are not adjacent unless the list says so)
-    const bool pair_ok = ((HW & 1) == 0) && (((uintptr_t)P.C & 3) == 0) && (!cv.pix || cv.pix_pairs);
-    // Consecutive pixels in planes of whole 16-byte pieces: the tile goes through LDS (the operand stages are
-    // dead by now) as bf16 [row][BN pixels] and leaves as 16-byte stores, a row of the tile one contiguous run
-    // of 2 BN bytes of its channel's plane (straight from the registers a store instruction writes runs of 64).
-    // Rows lie 2 BN bytes apart; the 16-byte pieces of a row are exchanged by two bits of its number, so the
-    // four rows one store instruction of a wave touches land on different banks.
-    if (!cv.pix && (HW & 7) == 0 && (((uintptr_t)P.C & 15) == 0)) {
-      constexpr int CH = BN / 8;                               // 16-byte pieces per row
-      constexpr int NT = 64 * NW;
-      static_assert(NT % CH == 0, "whole rows per pass");
-      static_assert(F_BM * BN * 2 <= NST * (F_BM + BN) * LDS_ROW_U4 * 16, "the staged tile fits the operand stages");
-      char* const tile = reinterpret_cast<char*>(lds);
-      auto piece_of = [](int row, int piece) { return piece ^ ((((row & 1) << 2) | (((row >> 2) & 1) << 3)) & (CH - 1)); };
-      __syncthreads();
+    constexpr int NT = 64 * NW, PITCH = BN * 2 + 16;
+    static_assert((size_t)F_BM * (PITCH + 4) <= direct_lds_bytes(F_BM, BN, 1), "the staged tile fits");
+    char* const tile = reinterpret_cast<char*>(lds);
+    int* const chan = reinterpret_cast<int*>(tile + F_BM * PITCH);
+    constexpr int CH = BN / 8;  // 16-byte pieces per row
+    constexpr int CL = CH <= 8 ? 8 : CH <= 16 ? 16 : CH <= 32 ? 32 : 64, RS = NT / CL;  // threads along a row, rows at a time
+    const int piece = tid % CL, jc = n0 + piece * 8;
+    int pix[8];  // of the piece, -1 for padding entries and beyond the last
 #pragma unroll
-      for (int in = 0; in < TN; ++in) {
-        const int lj = wn * WTN + in * 32 + (lane & 31);
+    for (int t = 0; t < 8; ++t) {
+      const bool in = piece < CH && jc + t < cv.npix;
+      pix[t] = in ? (cv.pix ? cv.pix[jc + t] : jc + t) : -1;
+    }
+    __syncthreads();
+    if (tid < F_BM) chan[tid] = out_chan;
 #pragma unroll
-        for (int im = 0; im < TM; ++im) {
-          const int li0 = wm * WTM + im * 32 + 4 * (lane >> 5);
+    for (int im = 0; im < TM; ++im) {
+      char* const row = tile + (wm * WTM + im * 32 + (lane & 31)) * PITCH + (wn * WTN + 4 * (lane >> 5)) * 2;
 #pragma unroll
-          for (int v = 0; v < 16; v += 2) {
-            float x0 = P.alpha * acc[im][in][v], x1 = P.alpha * acc[im][in][v + 1];
-            if (P.relu) {
-              x0 = fmaxf(x0, 0.0f);
-              x1 = fmaxf(x1, 0.0f);
-            }
-            const uint32_t b01 = pack_bf16x2(x0, x1);
-            const uint32_t b0 = b01 & 0xffffu, b1 = b01 >> 16;
-            // the even lane keeps row v of its own and its neighbour's pixel, the odd lane row v + 1
-            const uint32_t send = odd ? b0 : b1;
-            const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0xB1, 0xF, 0xF, true);
-            const uint32_t word = odd ? (got | (b1 << 16)) : (b0 | (got << 16));
-            const int row = li0 + 8 * (v >> 2) + (v & 3) + (odd ? 1 : 0);
-            const int w = lj >> 1;  // word of the row: pixels 2w, 2w + 1
-            *reinterpret_cast<uint32_t*>(tile + row * (BN * 2) + piece_of(row, w >> 2) * 16 + (w & 3) * 4) = word;
+      for (int in = 0; in < TN; ++in)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          float x[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            x[t] = P.alpha * acc[im][in][4 * g + t];
+            if (P.relu) x[t] = fmaxf(x[t], 0.0f);
           }
+          *reinterpret_cast<uint2*>(row + (in * 32 + 8 * g) * 2) = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
         }
-      }
-      __syncthreads();
-      const int piece = tid % CH;
-      const int jc = n0 + piece * 8;
-      if (jc >= cv.npix) return;  // (npix is a multiple of 8 here: a piece is in or out as a whole)
-      const int n = jc / HW;
-      uint16_t* const col = P.C + (long)n * cv.out_chan * HW + (jc - n * HW);
-      for (int r = tid / CH; r < F_BM; r += NT / CH) {
-        const int i = m0 + r;
-        if (i >= cv.n_rows) break;
-        const int ch = cv.chan ? cv.chan[i] : i;
-        *reinterpret_cast<uint4*>(col + (long)ch * HW) = *reinterpret_cast<const uint4*>(tile + r * (BN * 2) + piece_of(r, piece) * 16);
+    }
+    __syncthreads();
+    const int r_end = imin(F_BM, cv.n_rows - m0);
+    constexpr int U = 4;  // rows at a time: everything read before anything is stored
+    if (cv.pix ? !cv.pix_pairs : (HW & 1)) {
+      // scattered pixels, or planes that begin at odd places: a lane per pixel
+      for (int c0 = 0; c0 < BN; c0 += 64) {
+        const int lj = c0 + lane, j = n0 + lj < cv.npix ? (cv.pix ? cv.pix[n0 + lj] : n0 + lj) : -1;
+        if (j < 0) continue;
+        const int n = (int)fdiv((uint32_t)j, cv.per_img);
+        uint16_t* const col = P.C + (long)n * cv.out_chan * HW + (j - n * HW);
+        for (int r0 = wave; r0 < r_end; r0 += U * NW) {
+          uint16_t v[U];
+          int ch[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int r = imin(r0 + u * NW, F_BM - 1);
+            ch[u] = chan[r];
+            v[u] = *reinterpret_cast<const uint16_t*>(tile + r * PITCH + lj * 2);
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (r0 + u * NW < r_end) col[(long)ch[u] * HW] = v[u];
+        }
       }
       return;
     }
+    if (piece >= CH) return;
+    // Eight pixels that are neighbours in one plane leave as a piece (at any word), pairs as words: planes hold whole words,
+    // and listed pixels come in pairs here.
+    const bool words = ((uintptr_t)P.C & 3) == 0;
+    const int n = (int)fdiv((uint32_t)imax(pix[0], 0), cv.per_img), p0 = pix[0] - n * HW;
+    bool whole = pix[0] >= 0 && p0 + 7 < HW && words && (p0 & 1) == 0;
 #pragma unroll
-    for (int in = 0; in < TN; ++in) {
-      const int j = out_pix[in];  // (columns beyond npix hold -1; npix is even whenever pair_ok: a pair is in or out together)
-      if (j < 0) continue;        // padding entry of a tile
-      const int n = j / HW;
-      uint16_t* col = P.C + (long)n * cv.out_chan * HW + (j - n * HW);
+    for (int t = 1; t < 8; ++t) whole = whole && pix[t] == pix[0] + t;
+    uint16_t* const col = P.C + (long)n * cv.out_chan * HW + p0;
+    for (int r0 = tid / CL; r0 < r_end; r0 += U * RS) {
+      uint4 v[U];
+      int ch[U];
 #pragma unroll
-      for (int im = 0; im < TM; ++im) {
-        const int i0 = m0 + wm * WTM + im * 32 + 4 * (lane >> 5);
+      for (int u = 0; u < U; ++u) {
+        const int r = imin(r0 + u * RS, F_BM - 1);
+        ch[u] = chan[r];
+        v[u] = *reinterpret_cast<const uint4*>(tile + r * PITCH + piece * 16);
+      }
+      if (whole) {
 #pragma unroll
-        for (int v = 0; v < 16; v += 2) {
-          const int ia = i0 + 8 * (v >> 2) + (v & 3);  // row of v; v+1 is the next row
-          float x0 = P.alpha * acc[im][in][v], x1 = P.alpha * acc[im][in][v + 1];
-          if (P.relu) {
-            x0 = fmaxf(x0, 0.0f);
-            x1 = fmaxf(x1, 0.0f);
-          }
-          const uint32_t b01 = pack_bf16x2(x0, x1);
-          const uint32_t b0 = b01 & 0xffffu, b1 = b01 >> 16;
-          if (pair_ok) {
-            const uint32_t send = odd ? b0 : b1;
-            const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0xB1, 0xF, 0xF, true);
-            const uint32_t word = odd ? (got | (b1 << 16)) : (b0 | (got << 16));
-            const int i = odd ? ia + 1 : ia;
-            if (i < cv.n_rows) {
-              const int ch = cv.chan ? cv.chan[i] : i;
-              *reinterpret_cast<uint32_t*>(col - (odd ? 1 : 0) + (long)ch * HW) = word;
-            }
+        for (int u = 0; u < U; ++u)
+          if (r0 + u * RS < r_end) *reinterpret_cast<U4AnyWord*>(col + (long)ch[u] * HW) = U4AnyWord{v[u].x, v[u].y, v[u].z, v[u].w};
+        continue;
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int p = pix[2 * t];
+        if (p < 0) continue;
+        const int np = (int)fdiv((uint32_t)p, cv.per_img);
+        uint16_t* const place = P.C + (long)np * cv.out_chan * HW + (p - np * HW);
+        const bool word = words && (p & 1) == 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t w = t == 0 ? v[u].x : t == 1 ? v[u].y : t == 2 ? v[u].z : v[u].w;
+          if (r0 + u * RS >= r_end) continue;
+          uint16_t* const o = place + (long)ch[u] * HW;
+          if (word) {
+            *reinterpret_cast<uint32_t*>(o) = w;
           } else {
-            if (ia < cv.n_rows) col[(long)(cv.chan ? cv.chan[ia] : ia) * HW] = (uint16_t)b0;
-            if (ia + 1 < cv.n_rows) col[(long)(cv.chan ? cv.chan[ia + 1] : ia + 1) * HW] = (uint16_t)b1;
+            o[0] = (uint16_t)w;
+            if (pix[2 * t + 1] >= 0) o[1] = (uint16_t)(w >> 16);
           }
         }
       }
@@ -1706,7 +1745,7 @@ bool batch_push_zero_rows(const ZeroRowsArgs& a, int gx);
 template <bool A_KC, bool B_KC, int BM, int BN, int NW, int MODE>
 static int32_t launch_direct_alone(const FastParams& F, int grid_x, hipStream_t stream) {
   auto kernel = gemm_direct_kernel<A_KC, B_KC, BM, BN, NW, MODE>;
-  const size_t lds_bytes = (size_t)direct_stages(BM, BN) * (BM + BN) * LDS_ROW_U4 * sizeof(uint4) + (MODE == 3 ? direct_list_cap(BM) * 4 : 0);
+  const size_t lds_bytes = direct_lds_bytes(BM, BN, MODE) + (MODE == 3 ? direct_list_cap(BM) * 4 : 0);
   static thread_local bool raised = false;
   if (!raised && lds_bytes >= 65536) {
     ARD_HIP_CHECK(ard::raise_lds_limit((const void*)kernel, (int)lds_bytes));
@@ -1720,7 +1759,7 @@ template <bool A_KC, bool B_KC, int BM, int BN, int NW, int MODE>
 static int32_t launch_direct_kernel(const FastParams& F_in, int grid_x, hipStream_t stream) {
   FastParams F = F_in;
   if (F.splits < 1) F.splits = 1;
-  const size_t lds_bytes = (size_t)direct_stages(BM, BN) * (BM + BN) * LDS_ROW_U4 * sizeof(uint4);
+  const size_t lds_bytes = direct_lds_bytes(BM, BN, MODE);
   // class-free launches: the (split, tile) items are dealt to the XCDs inside the kernel
   if (F.tab.ncls == 0) grid_x = direct_plain_grid(F.total_tiles * (F.splits < 1 ? 1 : F.splits));
   // no lane may leave its operand: cheap envelope always, the exhaustive walk on request
