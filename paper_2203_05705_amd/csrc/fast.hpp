@@ -435,11 +435,15 @@ __device__ __forceinline__ bf16x8_t frag_value(const Frag& f) {
 constexpr int direct_stages(int bm, int bn) { return bm + bn <= 128 ? ARD_NST_SMALL : 2; }
 // Wavefronts side by side along the columns, so that each has whole 32 x 32 tiles
 constexpr int direct_wave_columns(int bn, int nw) { return nw == 8 && (bn == 256 || bn == 384) ? 4 : 2; }
-// Dynamic LDS of a product: the operand stages, or in a convolution the output tile and its rows' channels if that is more.
+// Bytes between the rows of a tile on its way out through LDS, in elements of `size` bytes: the rows that a store to LDS
+// touches at a time start four banks apart.
+constexpr int direct_pitch(int bn, int size) { return bn * size + 16; }
+// Dynamic LDS of a product: the operand stages (MODE 3: and the steps' pixels), or the output tile (as bf16, or
+// half of it as fp32, which is no more) and its rows' places if that is more.
 constexpr size_t direct_lds_bytes(int bm, int bn, int mode) {
-  const size_t stages = (size_t)direct_stages(bm, bn) * (bm + bn) * LDS_ROW_U4 * sizeof(uint4);
-  const size_t tile = (size_t)bm * (bn * 2 + 16) + (size_t)bm * 4;
-  return mode == 1 && tile > stages ? tile : stages;
+  const size_t stages = (size_t)direct_stages(bm, bn) * (bm + bn) * LDS_ROW_U4 * sizeof(uint4) + (mode == 3 ? direct_list_cap(bm) * 4 : 0);
+  const size_t tile = (size_t)bm * direct_pitch(bn, 2) + (size_t)bm * 4;
+  return tile > stages ? tile : stages;
 }
 
 template <class F, int... I>
@@ -810,10 +814,9 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
 #pragma unroll
       for (int in = 0; in < TN; ++in) frag_wait<B_KC>(fb[set][in]);
     };
-    // (a convolution's tiles come out transposed: a lane then holds four neighbouring pixels of a channel at a time)
+    // (tiles come out transposed: a lane then holds four neighbouring columns of a row at a time)
     auto mfma = [&](f32x16_t& c, const Frag& x, const Frag& y) {
-      if constexpr (MODE == 1) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_value<B_KC>(y), frag_value<A_KC>(x), c, 0, 0, 0);
-      else c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_value<A_KC>(x), frag_value<B_KC>(y), c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_value<B_KC>(y), frag_value<A_KC>(x), c, 0, 0, 0);
     };
     auto mma = [&](int set) {
 #pragma unroll
@@ -949,49 +952,52 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     }
   }
 
-  // epilogue: lane holds column (lane & 31) of each 32x32 tile, rows 8*(v/4) + 4*(lane>>5) + v%4.
-  // Mapped rows / columns come in blocks that are multiples of 32, so one index lookup per
-  // 32x32 tile places all of its rows (columns).
-  const int nlim = P.c_cols_mapped ? bn.n : P.N, mlim = P.c_rows_mapped ? am.n : P.M;
-  const int nphys = P.c_cols_mapped ? bn.nphys : P.N, mphys = P.c_rows_mapped ? am.nphys : P.M;
+  // epilogue: lane holds row (lane & 31) of each 32x32 tile, its columns 8*(v/4) + 4*(lane>>5) + v%4.  The tile goes
+  // through LDS (the operand stages are dead once every wave is past its last read) and leaves in 16-byte pieces of its
+  // rows.  Straight from the registers, pairs of columns exchanged between lanes to make words, the way out took 18000 of
+  // 123000 clocks of a 256 x 256 tile (K = 2048) and 37000 of 86000 of a 256 x 128 tile with fp32 results (K = 1024).
+  // 4096^3 in 64 x 64 tiles at dp = 2: 85, 101 and 91 us forward, data and weight gradient, now 79, 94 and 87; projection of
+  // 8192 x 1024 -> 2048 to fp32 67 -> 57 us; 128 x 4096 x 4096 in 32 x 32 tiles at dp = 3, weight gradient 20.8 -> 17.7 us.
+  constexpr int NT = 64 * NW;
+  // (the 256 x 256 tile has no LDS to spare: it only stores plain bf16 results)
+  constexpr bool GENERAL_OUT = !(F_BM == 256 && BN == 256);
   // Columns at or beyond the B operand's extent (padding of a compact output) are stored as zeros:
   // the loaders fed them clamped, i.e. arbitrary, rows.
   const int n_valid = (MODE == 0 && P.ncls == 0) ? bn.n : 0x7fffffff;
-  // (the 256 x 256 tile has no registers to spare: it only stores plain bf16 results)
-  constexpr bool GENERAL_OUT = !(F_BM == 256 && BN == 256);
-  if (MODE != 1 && GENERAL_OUT && P.part) {
-    // fp32 partial sums of this share of the contraction, compact [M x N]
-    float* part = P.part + (long)split * P.M * P.N;
+  char* const tile = reinterpret_cast<char*>(lds);
+  // four results at a time, f(row, column, values): columns of the tile
+  auto each_quad = [&](auto f) {
 #pragma unroll
-    for (int in = 0; in < TN; ++in) {
-      const int jb = jn0 + wn * WTN + in * 32 + (lane & 31), j = jb + li_cb * jlim;
-      if (jb >= jlim) continue;
+    for (int im = 0; im < TM; ++im)
 #pragma unroll
-      for (int im = 0; im < TM; ++im) {
-        const int i0 = m0 + wm * WTM + im * 32 + 4 * (lane >> 5);
+      for (int in = 0; in < TN; ++in)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int i = i0 + 8 * (v >> 2) + (v & 3);
-          if (i < P.M) part[(long)i * P.N + j] = j < n_valid ? acc[im][in][v] : 0.0f;
+        for (int g = 0; g < 4; ++g) {
+          float x[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) x[t] = acc[im][in][4 * g + t];
+          f(wm * WTM + im * 32 + (lane & 31), wn * WTN + in * 32 + 8 * g + 4 * (lane >> 5), x);
         }
+  };
+  auto stage_bf16 = [&] {
+    each_quad([&](int r, int c, float (&x)[4]) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        x[t] *= P.alpha;
+        if (P.relu) x[t] = fmaxf(x[t], 0.0f);
       }
-    }
-    return;
-  }
+      *reinterpret_cast<uint2*>(tile + r * direct_pitch(BN, 2) + c * 2) = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
+    });
+  };
   if constexpr (MODE == 1) {
     // NCHW output: compact row i -> channel (through the kept-channel list when there is one), column j -> pixel (n, hw)
-    // at n*out_chan*HW + hw.  A lane holds row (lane & 31) of each 32 x 32 tile, its pixels 8*(v/4) + 4*(lane>>5) + v%4.
-    // The tile goes through LDS (the operand stages are dead by now) as bf16 [row][BN pixels], eight bytes at a time, and
-    // leaves in 16-byte pieces, a row of the tile one run of 2 BN bytes of its channel's plane.  Rows lie 2 BN + 16 bytes
-    // apart: the 16 rows that a store to LDS touches at a time start four banks apart.
-    // N=128, 28x28, 128 -> 256 channels, 3x3: with pixels in the lanes, exchanged between neighbours to make words of
-    // pairs, and the channel looked up before each store, a 256 x 256 tile's way out took 20000 of its 81000 clocks, now
-    // 9700; the product 82 -> 77 us, the data gradient of 256 channels from 256 (K = 2304) 125 -> 116 us.
+    // at n*out_chan*HW + hw; a row of the tile is one run of 2 BN bytes of its channel's plane.
+    // N=128, 28x28, 128 -> 256 channels, 3x3: with words of pairs straight from the registers and the channel looked up
+    // before each store, a 256 x 256 tile's way out took 20000 of its 81000 clocks, now 9700; the product 82 -> 77 us, the
+    // data gradient of 256 channels from 256 (K = 2304) 125 -> 116 us.
     const ConvMap& cv = P.cv;
     const int HW = cv.HoWo;
-    constexpr int NT = 64 * NW, PITCH = BN * 2 + 16;
-    static_assert((size_t)F_BM * (PITCH + 4) <= direct_lds_bytes(F_BM, BN, 1), "the staged tile fits");
-    char* const tile = reinterpret_cast<char*>(lds);
+    constexpr int PITCH = direct_pitch(BN, 2);
     int* const chan = reinterpret_cast<int*>(tile + F_BM * PITCH);
     constexpr int CH = BN / 8;  // 16-byte pieces per row
     constexpr int CL = CH <= 8 ? 8 : CH <= 16 ? 16 : CH <= 32 ? 32 : 64, RS = NT / CL;  // threads along a row, rows at a time
@@ -1004,22 +1010,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     }
     __syncthreads();
     if (tid < F_BM) chan[tid] = out_chan;
-#pragma unroll
-    for (int im = 0; im < TM; ++im) {
-      char* const row = tile + (wm * WTM + im * 32 + (lane & 31)) * PITCH + (wn * WTN + 4 * (lane >> 5)) * 2;
-#pragma unroll
-      for (int in = 0; in < TN; ++in)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float x[4];
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            x[t] = P.alpha * acc[im][in][4 * g + t];
-            if (P.relu) x[t] = fmaxf(x[t], 0.0f);
-          }
-          *reinterpret_cast<uint2*>(row + (in * 32 + 8 * g) * 2) = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
-        }
-    }
+    stage_bf16();
     __syncthreads();
     const int r_end = imin(F_BM, cv.n_rows - m0);
     constexpr int U = 4;  // rows at a time: everything read before anything is stored
@@ -1094,130 +1085,224 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     return;
   }
   if (GENERAL_OUT && MODE == 0 && P.scatter) {
-    // The physical image of as many rows as fit at a time is made in LDS (the operand stages are dead once every
-    // wave is past its last read): zeros, then the values at their places, then whole pieces to memory.  (Gathering
-    // each piece's elements from a compact tile took 20 thousand clocks of a 64 x 64 tile at dp = 2 x 2, eight
-    // dependent LDS reads and their index arithmetic per piece.)
+    // The physical image of as many rows as fit at a time is made in LDS: zeros, then the values at their places, then
+    // whole pieces to memory.  (Gathering each piece's elements from a compact tile took 20 thousand clocks of a 64 x 64
+    // tile at dp = 2 x 2, eight dependent LDS reads and their index arithmetic per piece.)
     const int sc = P.scn.step, m1 = imin(m0 + F_BM, P.M), n1 = imin(n0 + BN, P.N);
     const int c_lo = n0 * sc, c_hi = n1 == P.N ? P.scn.nphys : n1 * sc;
-    const int pitch = (BN * sc + sc + 15) & ~7;
-    constexpr int LDS_BYTES = NST * (F_BM + BN) * LDS_ROW_U4 * 16;
-    static_assert(LDS_BYTES / (2 * ((BN * kScatterMaxStep + kScatterMaxStep + 15) & ~7)) >= 16, "16 rows of the image fit");
+    // (rows begin an odd number of 16-byte pieces apart: 16 rows at a time start four banks apart)
+    const int pitch = ((BN * sc + sc + 14) & ~15) + 8;
+    constexpr int LDS_BYTES = (int)direct_lds_bytes(F_BM, BN, 0);
+    static_assert(LDS_BYTES / (2 * (((BN * kScatterMaxStep + kScatterMaxStep + 14) & ~15) + 8)) >= 16, "16 rows of the image fit");
     const int rows_fit = imin(F_BM, LDS_BYTES / (pitch * 2) & ~15);
+    uint16_t* const img = reinterpret_cast<uint16_t*>(lds);
     for (int r0 = 0; r0 < F_BM && m0 + r0 < m1; r0 += rows_fit) {
       __syncthreads();
-      for (int i = tid; i < rows_fit * (pitch >> 3); i += 64 * NW) lds[i] = make_uint4(0, 0, 0, 0);
+      for (int i = tid; i < rows_fit * (pitch >> 3); i += NT) lds[i] = make_uint4(0, 0, 0, 0);
       __syncthreads();
-      uint16_t* img = reinterpret_cast<uint16_t*>(lds);
-      int rr = r0, ppitch = pitch;
 #pragma unroll
-      for (int im = 0; im < TM; ++im)
+      for (int im = 0; im < TM; ++im) {
+        const int li = wm * WTM + im * 32 + (lane & 31) - r0, i = m0 + r0 + li;
+        if (li < 0 || li >= rows_fit || i >= m1) continue;
+        int at = li * pitch + scatter_shift(P, i * P.srm.step + P.srm.off, c_lo) + P.scn.off + (wn * WTN + 4 * (lane >> 5)) * sc;
+        // (columns beyond the operand are padding zeros, those beyond the output stay out of the image)
+        int nj = imin(n1, n_valid) - (n0 + wn * WTN + 4 * (lane >> 5));
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          // (opaque: the addresses of all rows computed ahead of the loop would take 100 registers)
-          asm volatile("" : "+s"(rr), "+s"(ppitch));
-          const int lrow = wm * WTM + im * 32 + 16 * half - rr;  // 16 rows of this wave, relative to the image
-          if (lrow < 0 || lrow >= rows_fit) continue;
+        for (int in = 0; in < TN; ++in)
 #pragma unroll
-          for (int v = 8 * half; v < 8 * half + 8; v += 2) {
-            const int li = lrow - 16 * half + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            const int i = m0 + rr + li, r = i * P.srm.step + P.srm.off;
-            const int sh0 = scatter_shift(P, r, c_lo) + P.scn.off, sh1 = scatter_shift(P, r + P.srm.step, c_lo) + P.scn.off;
+          for (int g = 0; g < 4; ++g, at += 8 * sc, nj -= 8) {
+            // (opaque: worked out ahead, the places of all columns would take 100 registers, and whether they exist 70 scalar ones)
+            asm volatile("" : "+v"(at), "+v"(nj));
+            uint16_t* const o = img + at;
 #pragma unroll
-            for (int in = 0; in < TN; ++in) {
-              const int lj = wn * WTN + in * 32 + (lane & 31);
-              float x0 = P.alpha * acc[im][in][v], x1 = P.alpha * acc[im][in][v + 1];
+            for (int t = 0; t < 4; t += 2) {
+              float x0 = P.alpha * acc[im][in][4 * g + t], x1 = P.alpha * acc[im][in][4 * g + t + 1];
               if (P.relu) x0 = fmaxf(x0, 0.0f), x1 = fmaxf(x1, 0.0f);
-              const uint32_t b01 = pack_bf16x2(x0, x1);
-              // (columns beyond the operand are padding zeros, rows and columns beyond the output stay out of the image)
-              if (n0 + lj < n1 && n0 + lj < n_valid) {
-                if (i < m1) img[li * ppitch + sh0 + lj * sc] = (uint16_t)b01;
-                if (i + 1 < m1) img[(li + 1) * ppitch + sh1 + lj * sc] = (uint16_t)(b01 >> 16);
-              }
+              const uint32_t w = pack_bf16x2(x0, x1);
+              if (t < nj) o[t * sc] = (uint16_t)w;
+              if (t + 1 < nj) o[(t + 1) * sc] = (uint16_t)(w >> 16);
             }
           }
-        }
+      }
       __syncthreads();
-      direct_scatter_rows(lds, pitch, P, m0 + r0, imin(m0 + r0 + rows_fit, m1), c_lo, c_hi, tid, 64 * NW);
+      direct_scatter_rows(lds, pitch, P, m0 + r0, imin(m0 + r0 + rows_fit, m1), c_lo, c_hi, tid, NT);
     }
     return;
   }
-  int prow[TM];
+  if (MODE == 0 && F_BM * BN <= 64 * 64 && P.part) {
+    // Partial sums of a small tile go straight from the registers, 32 bytes of a row at a time: such launches are a few
+    // workgroups that are over soon, and the way through LDS took longer (138 x 1152 -> 1664, strides 4 and 8: 6.3 against
+    // 5.3 us each for the forward product and the data gradient).
+    float* const part = P.part + (long)split * P.M * P.N;
+    each_quad([&](int r, int c, float (&x)[4]) {
+      const int i = m0 + r, j = n0 + c;
+      if (i >= P.M) return;
+      float* const o = part + (long)i * P.N + j;
+      if (j + 3 < imin(P.N, n_valid)) {
+        *reinterpret_cast<U4AnyWord*>(o) = U4AnyWord{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+      } else {
 #pragma unroll
-  for (int im = 0; im < TM; ++im) {
-    const int i0 = m0 + wm * WTM + im * 32;
-    prow[im] = i0 < mlim ? (P.c_rows_mapped ? ax_phys(am, i0) : i0) : mphys;
+        for (int t = 0; t < 4; ++t)
+          if (j + t < P.N) o[t] = j + t < n_valid ? x[t] : 0.0f;
+      }
+    });
+    return;
   }
-  const bool plain_bf16 = !GENERAL_OUT || (!P.out_f32 && P.beta == 0.0f);
+  // Mapped rows / columns come in blocks that are multiples of 32, so one index lookup per block places all of its rows
+  // (columns).
+  const bool partial = GENERAL_OUT && P.part;
+  const bool wide = GENERAL_OUT && (P.part || P.out_f32 || P.beta != 0.0f);  // staged, or stored, as fp32
+  constexpr int HALF = F_BM / 2;
+  static_assert(HALF * direct_pitch(BN, 4) <= F_BM * direct_pitch(BN, 2) && (size_t)F_BM * (direct_pitch(BN, 2) + 4) <= direct_lds_bytes(F_BM, BN, MODE),
+                "either tile ends before the rows' places, and these within the LDS of the launch");
+  int* const row_of = reinterpret_cast<int*>(tile + F_BM * direct_pitch(BN, 2));  // physical rows, -1 beyond the output
+  __syncthreads();
+  if (tid < F_BM) {
+    const int i0 = m0 + (tid & ~31), mlim = P.c_rows_mapped ? am.n : P.M, mphys = P.c_rows_mapped ? am.nphys : P.M;
+    const int r = partial ? m0 + tid : i0 < mlim ? (P.c_rows_mapped ? ax_phys(am, i0) : i0) + (tid & 31) : mphys;
+    row_of[tid] = r < (partial ? P.M : mphys) ? r : -1;
+  }
+  const int rows = partial || !P.c_rows_mapped ? imin(F_BM, P.M - m0) : F_BM;  // of the tile, that can exist
+  constexpr int U = 4;  // rows at a time: everything read before anything is stored
+  if (wide) {
+    if constexpr (GENERAL_OUT) {
+      constexpr int PITCH = direct_pitch(BN, 4), CL = BN / 4, RS = NT / CL;
+      const int lj = tid % CL * 4, jb = jn0 + lj, j = jb + li_cb * jlim;  // (MODE 3: column within its block, of the product)
+      const int nlim = partial ? jlim : P.c_cols_mapped ? bn.n : P.N;
+      const int pc = partial ? j : P.c_cols_mapped ? ax_phys(bn, jb & ~31) + (jb & 31) : jb;
+      // columns that exist, and that are not padding of a compact output
+      const int nc = imin(4, partial ? jlim - jb : (P.c_cols_mapped ? bn.nphys : P.N) - pc), nv = n_valid - jb;
+      const long ld = partial ? P.N : P.ldc;
+      const float alpha = partial ? 1.0f : P.alpha;
+      float* const outf = partial ? P.part + (long)split * P.M * P.N : reinterpret_cast<float*>(P.C);
+      const bool relu = !partial && P.relu;
+      const bool to_f32 = partial || P.out_f32, general = !partial && (P.beta != 0.0f || P.relu_src || !to_f32);
+      // (half of the rows at a time: all of a 128 x 128 tile would take the LDS of the CU's second workgroup)
+#pragma unroll 1
+      for (int h = 0; h < 2 && h * HALF < rows; ++h) {
+        if (h) __syncthreads();
+        if (wm / (WGM / 2) == h)
+          each_quad([&](int r, int c, float (&x)[4]) { *reinterpret_cast<float4*>(tile + (r - h * HALF) * PITCH + c * 4) = make_float4(x[0], x[1], x[2], x[3]); });
+        __syncthreads();
+        if (jb >= nlim) continue;
+        const int rows_h = imin(HALF, rows - h * HALF);
+        if (to_f32 && !general && nc == 4 && nv >= 4) {
+          for (int r0 = tid / CL; r0 < rows_h; r0 += U * RS) {
+            float4 x[U];
+            int pr[U];
 #pragma unroll
-  for (int in = 0; in < TN; ++in) {
-    const int j0 = n0 + wn * WTN + in * 32;
-    if (j0 >= nlim) continue;
-    const int pc = (P.c_cols_mapped ? ax_phys(bn, j0) : j0) + (lane & 31);
-    if (pc >= nphys) continue;
-#pragma unroll
-    for (int im = 0; im < TM; ++im) {
-      const int rbase = prow[im] + 4 * (lane >> 5);
-      if (!plain_bf16) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int r = rbase + 8 * (v >> 2) + (v & 3);
-          if (r >= mphys) continue;
-          const long idx = (long)r * P.ldc + pc;
-          float x = (j0 + (lane & 31)) < n_valid ? P.alpha * acc[im][in][v] : 0.0f;
-          if (P.beta != 0.0f) x += P.beta * (P.out_f32 ? reinterpret_cast<const float*>(P.C)[idx] : bf16_bits_to_f32(P.C[idx]));
-          if (P.relu) x = fmaxf(x, 0.0f);
-          if (P.relu_src) x = bf16_bits_to_f32(P.relu_src[idx]) > 0.0f ? x : 0.0f;
-          if (P.out_f32) reinterpret_cast<float*>(P.C)[idx] = x;
-          else P.C[idx] = f32_to_bf16_bits(x);
-        }
-        continue;
-      }
-      // Adjacent lanes hold adjacent columns of the same row.  Rows come in pairs (v, v+1):
-      // the even lane takes the odd lane's value of row v, the odd lane the even lane's value
-      // of row v+1 (one DPP swap), and each stores one packed 32-bit word.
-      const bool odd = lane & 1;
-      uint16_t* dst = P.C + (long)rbase * P.ldc + (pc & ~1);
-      const bool pair_ok = ((pc | 1) < nphys) && ((P.ldc & 1) == 0) && ((nphys & 1) == 0) && (((uintptr_t)P.C & 3) == 0) &&
-                           (((uintptr_t)P.relu_src & 3) == 0);
-#pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        float x0 = P.alpha * acc[im][in][v], x1 = P.alpha * acc[im][in][v + 1];
-        if (P.relu) {
-          x0 = fmaxf(x0, 0.0f);
-          x1 = fmaxf(x1, 0.0f);
-        }
-        if ((j0 + (lane & 31)) >= n_valid) x0 = x1 = 0.0f;
-        const uint32_t b01 = pack_bf16x2(x0, x1);
-        const uint32_t b0 = b01 & 0xffffu, b1 = b01 >> 16;
-        const int dr0 = 8 * (v >> 2) + (v & 3);  // row of v; v+1 is the next row
-        if (pair_ok) {
-          const uint32_t send = odd ? b0 : b1;
-          const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0xB1, 0xF, 0xF, true);  // swap with lane^1
-          const uint32_t word = odd ? (got | (b1 << 16)) : (b0 | (got << 16));
-          const int dr = odd ? dr0 + 1 : dr0;
-          if (rbase + dr < mphys) {
-            uint32_t out = word;
-            if (GENERAL_OUT && P.relu_src) {
-              // ReLU mask of the same two positions (same layout as the output)
-              const uint32_t g = *reinterpret_cast<const uint32_t*>(P.relu_src + (long)(rbase + dr) * P.ldc + (pc & ~1));
-              if (!(bf16_bits_to_f32((uint16_t)(g & 0xffffu)) > 0.0f)) out &= 0xffff0000u;
-              if (!(bf16_bits_to_f32((uint16_t)(g >> 16)) > 0.0f)) out &= 0x0000ffffu;
+            for (int u = 0; u < U; ++u) {
+              const int r = imin(r0 + u * RS, HALF - 1);
+              pr[u] = r0 + u * RS < rows_h ? row_of[h * HALF + r] : -1;
+              x[u] = *reinterpret_cast<const float4*>(tile + r * PITCH + lj * 4);
+              x[u].x *= alpha, x[u].y *= alpha, x[u].z *= alpha, x[u].w *= alpha;
+              if (relu) x[u].x = fmaxf(x[u].x, 0.0f), x[u].y = fmaxf(x[u].y, 0.0f), x[u].z = fmaxf(x[u].z, 0.0f), x[u].w = fmaxf(x[u].w, 0.0f);
             }
-            *reinterpret_cast<uint32_t*>(dst + (long)dr * P.ldc) = out;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (pr[u] >= 0)
+                *reinterpret_cast<U4AnyWord*>(outf + (long)pr[u] * ld + pc) =
+                    U4AnyWord{__float_as_uint(x[u].x), __float_as_uint(x[u].y), __float_as_uint(x[u].z), __float_as_uint(x[u].w)};
           }
-        } else {
-          uint16_t* d1 = P.C + (long)rbase * P.ldc + pc;
-          const uint16_t* g1 = P.relu_src + (long)rbase * P.ldc + pc;
-          uint16_t o0 = (uint16_t)b0, o1 = (uint16_t)b1;
-          if (GENERAL_OUT && P.relu_src) {
-            if (rbase + dr0 < mphys && !(bf16_bits_to_f32(g1[(long)dr0 * P.ldc]) > 0.0f)) o0 = 0;
-            if (rbase + dr0 + 1 < mphys && !(bf16_bits_to_f32(g1[(long)(dr0 + 1) * P.ldc]) > 0.0f)) o1 = 0;
+          continue;
+        }
+#pragma unroll 1
+        for (int r = tid / CL; r < rows_h; r += RS) {
+          const int pr = row_of[h * HALF + r];
+          if (pr < 0) continue;
+          const float* const q = reinterpret_cast<const float*>(tile + r * PITCH + lj * 4);
+          const long at = (long)pr * ld + pc;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            if (t >= nc) break;
+            float x = t < nv ? alpha * q[t] : 0.0f;
+            if (general && P.beta != 0.0f) x += P.beta * (to_f32 ? outf[at + t] : bf16_bits_to_f32(P.C[at + t]));
+            if (relu) x = fmaxf(x, 0.0f);
+            if (general && P.relu_src) x = bf16_bits_to_f32(P.relu_src[at + t]) > 0.0f ? x : 0.0f;
+            if (to_f32) outf[at + t] = x;
+            else P.C[at + t] = f32_to_bf16_bits(x);
           }
-          if (rbase + dr0 < mphys) d1[(long)dr0 * P.ldc] = o0;
-          if (rbase + dr0 + 1 < mphys) d1[(long)(dr0 + 1) * P.ldc] = o1;
         }
       }
+    }
+    return;
+  }
+  if constexpr (MODE == 0) {
+    constexpr int PITCH = direct_pitch(BN, 2), CL = BN / 8, RS = NT / CL;
+    stage_bf16();
+    __syncthreads();
+    const int nlim = P.c_cols_mapped ? bn.n : P.N, nphys = P.c_cols_mapped ? bn.nphys : P.N;
+    const uint16_t* const src = GENERAL_OUT ? P.relu_src : nullptr;
+    if (((P.ldc & 1) | (int)((uintptr_t)P.C & 3) | (int)((uintptr_t)src & 3)) != 0) {
+      // rows that begin at odd places: a lane per column
+      for (int c0 = 0; c0 < BN; c0 += 64) {
+        const int j = n0 + c0 + lane, pc = j < nlim ? (P.c_cols_mapped ? ax_phys(bn, j & ~31) + (j & 31) : j) : nphys;
+        if (pc >= nphys) continue;
+        for (int r0 = wave; r0 < rows; r0 += U * NW) {
+          uint16_t v[U], g[U];
+          int pr[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int r = imin(r0 + u * NW, F_BM - 1);
+            pr[u] = r0 + u * NW < rows ? row_of[r] : -1;
+            v[u] = j < n_valid ? *reinterpret_cast<const uint16_t*>(tile + r * PITCH + (c0 + lane) * 2) : (uint16_t)0;
+          }
+          if (src) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) g[u] = src[(long)imax(pr[u], 0) * P.ldc + pc];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = bf16_bits_to_f32(g[u]) > 0.0f ? v[u] : (uint16_t)0;
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (pr[u] >= 0) P.C[(long)pr[u] * P.ldc + pc] = v[u];
+        }
+      }
+      return;
+    }
+    const int lj = tid % CL * 8, j = n0 + lj;
+    if (j >= nlim) return;
+    const int pc = P.c_cols_mapped ? ax_phys(bn, j & ~31) + (j & 31) : j;
+    const int nc = imin(8, nphys - pc), nv = n_valid - j;  // columns that exist, that are not padding of a compact output
+    if (nc < 8 || nv < 8) {  // the last columns
+#pragma unroll 1
+      for (int r = tid / CL; r < rows; r += RS) {
+        const int pr = row_of[r];
+        if (pr < 0) continue;
+        const uint16_t* const q = reinterpret_cast<const uint16_t*>(tile + r * PITCH + lj * 2);
+        const long at = (long)pr * P.ldc + pc;
+#pragma unroll 1
+        for (int t = 0; t < nc; ++t) P.C[at + t] = t < nv && (!src || bf16_bits_to_f32(src[at + t]) > 0.0f) ? q[t] : (uint16_t)0;
+      }
+      return;
+    }
+    for (int r0 = tid / CL; r0 < rows; r0 += U * RS) {
+      uint32_t v[U][4];
+      int pr[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = imin(r0 + u * RS, F_BM - 1);
+        pr[u] = r0 + u * RS < rows ? row_of[r] : -1;
+        const uint4 q = *reinterpret_cast<const uint4*>(tile + r * PITCH + lj * 2);
+        v[u][0] = q.x, v[u][1] = q.y, v[u][2] = q.z, v[u][3] = q.w;
+      }
+      if (src) {
+        // ReLU mask of the same positions (same layout as the output)
+        uint32_t g[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const U4AnyWord w = *reinterpret_cast<const U4AnyWord*>(src + (long)imax(pr[u], 0) * P.ldc + pc);
+          g[u][0] = w.x, g[u][1] = w.y, g[u][2] = w.z, g[u][3] = w.w;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            v[u][t] &= (bf16_bits_to_f32((uint16_t)g[u][t]) > 0.0f ? 0xffffu : 0u) | (bf16_bits_to_f32((uint16_t)(g[u][t] >> 16)) > 0.0f ? 0xffff0000u : 0u);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (pr[u] >= 0) *reinterpret_cast<U4AnyWord*>(P.C + (long)pr[u] * P.ldc + pc) = U4AnyWord{v[u][0], v[u][1], v[u][2], v[u][3]};
     }
   }
 }
@@ -1234,8 +1319,9 @@ template <int NT> __device__ __forceinline__ void zero_tiles_body(const ZeroTile
   }
 }
 
+// (wavefronts per SIMD: as many workgroups as their LDS lets share a CU)
 template <bool A_KC, bool B_KC, int F_BM, int BN, int NW, int MODE = 0>
-__global__ __launch_bounds__(64 * NW) void gemm_direct_kernel(const FastParams P) {
+__global__ __launch_bounds__(64 * NW, F_BM + BN <= 192 ? 3 : 2) void gemm_direct_kernel(const FastParams P) {
   extern __shared__ uint4 direct_lds[];
   if constexpr (MODE == 0 && !A_KC && !B_KC) {
     const int z = (int)blockIdx.x - ((int)gridDim.x - P.zt.blocks);
@@ -1745,7 +1831,7 @@ bool batch_push_zero_rows(const ZeroRowsArgs& a, int gx);
 template <bool A_KC, bool B_KC, int BM, int BN, int NW, int MODE>
 static int32_t launch_direct_alone(const FastParams& F, int grid_x, hipStream_t stream) {
   auto kernel = gemm_direct_kernel<A_KC, B_KC, BM, BN, NW, MODE>;
-  const size_t lds_bytes = direct_lds_bytes(BM, BN, MODE) + (MODE == 3 ? direct_list_cap(BM) * 4 : 0);
+  const size_t lds_bytes = direct_lds_bytes(BM, BN, MODE);
   static thread_local bool raised = false;
   if (!raised && lds_bytes >= 65536) {
     ARD_HIP_CHECK(ard::raise_lds_limit((const void*)kernel, (int)lds_bytes));

@@ -770,7 +770,7 @@ static_assert(sizeof(GroupTable) <= 4096, "kernel arguments are limited to 4 KiB
 
 // (The table is read through the kernel-argument segment itself: indexing the by-value parameter with a
 // run-time segment number would make the compiler copy all of it into every lane's private memory.)
-__global__ __launch_bounds__(256) void group_kernel(const GroupTable table_in_kernarg) {
+__global__ __launch_bounds__(256, 2) void group_kernel(const GroupTable table_in_kernarg) {
   extern __shared__ uint4 group_lds[];
   const GroupTable& T = *(const GroupTable*)__builtin_amdgcn_kernarg_segment_ptr();
   int s = 0;
