@@ -46,15 +46,21 @@ __device__ __forceinline__ float lx_rcp(float d) {
   return d < 3.0e38f ? fmaf(fmaf(-d, r, 1.0f), r, r) : (d != d ? d : r);
 }
 __device__ __forceinline__ float lx_sigmoid(float z) { return lx_rcp(1.0f + __expf(-z)); }
-// tanh without branches: a polynomial fitted to tanh(x) / x on [0, 5/8] (4e-9), 1 - 2 / (1 + e^2x) beyond
+// tanh without branches: a polynomial fitted to (tanh(x) / x - 1) / x^2 on [0, 1.1] (2e-9), 1 - 2 / (1 + e^2x) beyond.
+// Against 64 bits over 4 M values up to 20: at most 1.11 ulp, 0.215 in the mean (tanhf 1.34 and 0.216, and a training step of
+// 64 time steps of 1024 units at batch 128 531 instead of 526 us).
 __device__ __forceinline__ float lx_tanh(float x) {
   const float y = fabsf(x), s = x * x;
-  float p = fmaf(s, -0.005704042501747608f, 0.020637862384319305f);
-  p = fmaf(s, p, -0.05373915657401085f);
-  p = fmaf(s, p, 0.133314311504364f);
-  p = fmaf(s, p, -0.3333328068256378f);
+  float p = 9.130840044e-05f;
+  p = fmaf(s, p, -0.0007175668143f);
+  p = fmaf(s, p, 0.00287373201f);
+  p = fmaf(s, p, -0.008419346064f);
+  p = fmaf(s, p, 0.02170202322f);
+  p = fmaf(s, p, -0.05393234268f);
+  p = fmaf(s, p, 0.1333295405f);
+  p = fmaf(s, p, -0.3333331943f);
   const float low = fmaf(x * s, p, x), high = copysignf(fmaf(-2.0f, lx_rcp(1.0f + __expf(2.0f * y)), 1.0f), x);
-  return y < 0.625f ? low : high;
+  return y < 1.1f ? low : high;
 }
 // All workgroups of a block tell each other which XCD they run on.  -1: gave up, 1: all on one, 0: they are spread.
 __device__ __forceinline__ int lx_meet(int* seat, int S, int s, int lane, long limit, int* err) {
