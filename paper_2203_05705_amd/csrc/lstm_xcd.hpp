@@ -89,6 +89,7 @@ __device__ __forceinline__ void lx_store(unsigned* p, unsigned v, bool local) {
   if (local) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ unsigned lx_min(unsigned a, unsigned b) { return a < b ? a : b; }
 __device__ __forceinline__ unsigned lx_max3(unsigned a, unsigned b, unsigned c) {
   const unsigned m = a > b ? a : b;
   return m > c ? m : c;
@@ -339,8 +340,12 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
           // (every writer's last line is there, nearly always everything is: if not, the share is fetched again)
 #pragma unroll
           for (int i = 0; i < NL; ++i) {
-            const unsigned o = share + i * 1024, at = o + lane * 16;  // (beyond the last writer: multiplied by zero weights)
-            __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(src + (at < total ? at : (unsigned)(lane * 16))), ARD_LDS_PTR(stage + o), 16, 0, 16);
+            // What lies beyond the last writer is multiplied by zero weights, and 0 times an infinity or a NaN is a NaN: its
+            // place in the operand of a row is filled from the same row, of the writers from the first on (24 units: 22 to
+            // 32 of 32) or of the first writer (16: a load is one or two of its gates whole).
+            const unsigned o = share + i * 1024, at = o + lane * 16;
+            const unsigned from = UW == 24 ? lx_min(at, at - total) : at < total ? at : (unsigned)(lane * 16);
+            __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(src + from), ARD_LDS_PTR(stage + o), 16, 0, 16);
           }
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
