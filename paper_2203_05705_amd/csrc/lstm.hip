@@ -335,6 +335,7 @@ struct LstmPersist {
   int off, step;       // kept unit j is physical unit off + j * step
   long spin_limit;
   int spread;          // (a block per XCD) test hook: stores as if its workgroups were on several
+  int seats;           // (the same) test hook: only so many workgroups of a block are there, 0: all
 };
 
 // VIA_L2: h_{t-1} is read through the XCD's L2 after an agent-scope acquire (else with device-scope loads)
@@ -610,7 +611,8 @@ struct LstmPersistBwd {
   int off, step;        // kept unit j is physical unit off + j * step
   long spin_limit;
   char* ex;             // staging wavefronts, a block per XCD: [T][batch block][unit slice] blocks the workgroups exchange
-  int spread;           // as in LstmPersist
+  int spread, seats;    // as in LstmPersist
+  float* dc;            // (a block per XCD) [B][H]: gradients of c, for workgroups that have several seats
 };
 
 template <int TM16, bool VIA_L2, int CH>
@@ -1366,6 +1368,7 @@ static int lstm_xcd_units(const LstmArgs& a) {
 // Backward: 600 units, B = 128, 64 steps: 680 -> 400 us for the pass, 4 steps 81 -> 70.  Of two or three steps beyond the range
 // of the staging wavefronts most is start-up (72 -> 65): they keep the form that still larger layers take.
 static int lstm_xcd_bwd_units(const LstmArgs& a) { return lstm_staged_bwd(a) || a.T > 3 ? lstm_xcd_units(a) : 0; }
+static int lstm_test_seats() { return getenv("ARD_LSTM_SEATS") ? atoi(getenv("ARD_LSTM_SEATS")) : 0; }
 static int lstm_xcd_rows(int B) { return B <= 8 * kLxBlocks ? 8 : 16; }
 
 // Does the forward pass of this layer run its recurrence in one launch, and how?  (bf16, affine pattern,
@@ -1454,7 +1457,7 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     const int S = ceil_div(Hp, xcd);
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersist P{Gx, (const uint16_t*)w.whc, (uint16_t*)w.hc, (uint16_t*)h, c, gates, w.sync + 1, w.sync, T_, B, H, Hk, Hp, S,
-                  a.ax.off, a.ax.step, spin_limit, getenv("ARD_LSTM_SPREAD") ? 1 : 0};
+                  a.ax.off, a.ax.step, spin_limit, getenv("ARD_LSTM_SPREAD") ? 1 : 0, lstm_test_seats()};
     const int waves = lx_fwd_waves(xcd);
     const size_t lds = (size_t)2 * waves * rb * xcd * 16;
     auto launch = [&](auto kernel) -> int32_t {
@@ -1568,7 +1571,7 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     const int S = ceil_div(Hp, xcd), kw = xcd == 24 ? 12 : S <= 8 ? 2 : S <= 16 ? 4 : 8;
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,
-                     S, xcd, a.ax.off, a.ax.step, spin_limit, w.ex, getenv("ARD_LSTM_SPREAD") ? 1 : 0};
+                     S, xcd, a.ax.off, a.ax.step, spin_limit, w.ex, getenv("ARD_LSTM_SPREAD") ? 1 : 0, lstm_test_seats(), w.dc_next};
     const size_t image = (size_t)4 * Hp * xcd * 2 + 64, step = kLxBwdWaves * ((size_t)kw * rb * 64 + (size_t)2 * rb * (xcd + 4) * 4);
     const size_t lds = image > step ? image : step;
     auto launch = [&](auto kernel) -> int32_t {

@@ -75,3 +75,33 @@ def test_backward_recurrence_give_up_path():
     torch.cuda.synchronize()
     assert status() == 0, "the call after a given-up one left the status word set"
     assert torch.equal(dx1, dx0) and torch.equal(dW1, dW0), "results differ after a given-up call"
+
+
+# (T, B, H, wait bound): a bound of 0 ends the first wait of a later step that is not over at its first look, a negative one
+# the first wait of all; a block per XCD with 8 and 16 rows, 16 and 24 units, and staging wavefronts (a batch above 128)
+@pytest.mark.parametrize("T,B,H,limit", [(12, 20, 300, 0), (12, 128, 500, 0), (12, 20, 750, 0), (12, 128, 760, 0), (12, 20, 750, -1), (12, 200, 200, -1)])
+def test_give_up_paths_of_every_recurrence(T, B, H, limit, monkeypatch):
+    I, pat = 64, ard.Pattern.row(1, 1)
+    off = ard.lstm_status_offset(ard.BF16, T, B, I, H, pat)
+    rng = np.random.default_rng(B + H)
+    x, dh = (from_vals(stored(rng.standard_normal(s), "bf16"), "bf16") for s in ((T, B, I), (T, B, H)))
+    W = from_vals(stored(rng.uniform(-0.05, 0.05, (4 * H, I + H)), "bf16"), "bf16")
+    ws = torch.empty(ard.lstm_workspace_bytes(ard.BF16, T, B, I, H, pat), dtype=torch.uint8, device="cuda")
+    status = lambda: int(ws[off:off + 4].view(torch.int32).item())
+
+    def run():
+        h, c, g = ard.lstm_fwd(x, W, pat, ws=ws)
+        assert status() == 0
+        return (h, c, g) + ard.lstm_bwd(x, W, pat, h, c, g, dh, ws=ws)
+    want = run()
+    assert status() == 0
+    print("giving up", T, B, H, limit, flush=True)
+    monkeypatch.setenv("ARD_LSTM_SPIN_LIMIT", str(limit))
+    ard.lstm_fwd(x, W, pat, ws=ws)
+    assert status() == 1, "forward"
+    ard.lstm_bwd(x, W, pat, *want[:3], dh, ws=ws)
+    assert status() == 1, "backward"
+    monkeypatch.delenv("ARD_LSTM_SPIN_LIMIT")
+    for a, b in zip(run(), want):
+        assert torch.equal(a, b), "results differ after a given-up call"
+    assert status() == 0
