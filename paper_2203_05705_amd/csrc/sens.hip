@@ -566,7 +566,12 @@ extern "C" int32_t ard_sens_predict(int32_t dtype, int32_t N, int32_t C, int32_t
     const int words = (Wd + 2 * pad + 31) / 32;
     int RBG = imin(imax(1, ceil_div(8192 / kSensWaves, (int)((long)N * g.CB < 8192 ? N * g.CB : 8192))), g.RB), G = 1, nrow = 0;
     size_t stage_bytes = 0;
-    for (;; ++RBG) {
+    // No more bands than this fit, counting no row that is touched in part: tried from there on, one number of bands after
+    // another (a 188 x 98 layer of 910 channels in bands of one position: 18 thousand tries from the top).
+    const double row_bytes = 4.0 * words * nch_max * stride, top_rows = 1.0 + (double)g.x / g.Wo;
+    const double room = 4608.0 * kSensWaves - 4.0 * g.y - 4.0 * words * nch_max * kh + row_bytes * top_rows;
+    const int most = (int)fmin(fmax(room / (row_bytes * g.x / g.Wo + 4.0 * g.x + sizeof(SensBand)), 1.0), (double)g.RB);
+    for (;; RBG = imax(ceil_div(g.RB, G - 1), ceil_div(g.RB, most))) {
       G = ceil_div(g.RB, RBG);
       // output rows a group can span: groups of whole rows start on a row, any other may start anywhere in one
       const long span = (long)G * g.x;

@@ -282,3 +282,24 @@ def test_lstm_shapes_reach_the_recurrences_with_a_block_per_xcd():
             names = D.launches(lib)[1]
             assert "lstm_xcd_fwd_kernel" in names and "lstm_xcd_bwd_kernel" in names, (names, T, B, H)
         D.last_bounds(lib)
+
+
+def test_sensitivity_prediction_finds_its_bands_at_once():
+    """How many bands a workgroup takes is worked out on each call: a layer of 18424 bands none of which leaves room for a
+    second costs the host about what one of 98 bands costs (1.4 times; one number of bands after another, 50 times)."""
+    import time
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+
+        def seconds(C, H, W, x):
+            A, out = heap(2 * C * H * W * 4), [heap(1 << 24) for _ in range(3)]
+            best = 1.0
+            for _ in range(20):
+                t = time.perf_counter()
+                for _ in range(10):
+                    _ok(lib, [lib.ard_sens_predict(D.F32, 2, C, H, W, 3, 3, 1, 1, x, 0, 300, 500, 0.5, 1, 0, A, *out, None)], "prediction")
+                best = min(best, time.perf_counter() - t)
+            assert "sens_predict_staged_kernel" in D.launches(lib)[1]
+            return best
+        small, large = seconds(256, 28, 28, 8), seconds(910, 188, 98, 1)
+        assert large < 10 * small, (small, large)
