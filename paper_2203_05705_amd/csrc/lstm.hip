@@ -1553,7 +1553,7 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
   PersistBwdPlan bp;
   const int xcd = std::is_same<T, uint16_t>::value ? lstm_xcd_bwd_units(a) : 0, rb = lstm_xcd_rows(B);
   const bool staged = std::is_same<T, uint16_t>::value && lstm_staged_bwd(a);
-  const bool one_launch = staged || (std::is_same<T, uint16_t>::value && lstm_persist_bwd_plan(a, bp));
+  const bool one_launch = xcd || staged || (std::is_same<T, uint16_t>::value && lstm_persist_bwd_plan(a, bp));
   const long step_bytes = (long)B * 4 * Hp * 2;
   LstmMark mark{};  // (dG_0 is waited for by nobody)
   if (xcd) mark = LstmMark{w.ex, (long)(T_ - 1) * ceil_div(B, rb) * ceil_div(Hp, xcd) * rb * xcd * 8, 1 + kLxBlocks * kLxSeats};
@@ -1694,7 +1694,7 @@ extern "C" size_t ard_lstm_workspace_bytes(int32_t dtype, int32_t T, int32_t B, 
 extern "C" size_t ard_lstm_status_offset(int32_t dtype, int32_t T, int32_t B, int32_t I, int32_t H, const ard_pattern* pat) {
   LstmArgs a{dtype, T, B, I, H, 0, 0, Axis{}, LstmTiles{}};
   PersistPlan pp;
-  if (lstm_check(a, pat) || (!lstm_staged_fwd_units(a) && !lstm_persist_plan(a, pp))) return (size_t)-1;
+  if (lstm_check(a, pat) || (!lstm_xcd_units(a) && !lstm_staged_fwd_units(a) && !lstm_persist_plan(a, pp))) return (size_t)-1;
   const LstmWs w = lstm_ws_layout((char*)nullptr + 256, a.es, T, B, I, H, a.Hk);
   return (size_t)((char*)w.sync - ((char*)nullptr + 256));
 }
