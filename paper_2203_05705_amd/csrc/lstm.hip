@@ -1340,6 +1340,13 @@ static int32_t lstm_prepare(const LstmArgs& a, const void* W, const void* x, con
   return ARD_OK;
 }
 
+// An instance of a kernel in the record of a dry run: units per workgroup / 8, slices per wavefront
+static const char* lstm_instance(const char* kernel, int ut, int kw) {
+  static thread_local char name[64];
+  snprintf(name, sizeof name, "%s %d %d", kernel, ut, kw);
+  return name;
+}
+
 // The recurrences with staging wavefronts: kept units per workgroup (0: not taken).  One workgroup per CU, and as many
 // of them as there are: narrow slices first.
 static int lstm_staged_fwd_units(const LstmArgs& a) {
@@ -1472,18 +1479,18 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     return ARD_OK;
   }
   if (staged) {
-    const int S = ceil_div(Hp, staged), kw = (int)align_up((size_t)ceil_div(Hp, 64), 4);
+    // (12 slices of 8 units: with 256 CUs the recurrences with a block per XCD take all such layers)
+    const int S = ceil_div(Hp, staged), need = (int)align_up((size_t)ceil_div(Hp, 64), 4), kw = staged == 8 && need == 12 ? 16 : need;
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersist P{Gx, (const uint16_t*)w.whc, (uint16_t*)w.hc, (uint16_t*)h, c, gates, w.sync + 1, w.sync, T_, B, H, Hk, Hp, S,
                   a.ax.off, a.ax.step, spin_limit};
     const size_t lds = (size_t)4096 * kw + (size_t)4 * 32 * (4 * staged + 1) * 4;
     auto launch = [&](auto kernel) -> int32_t {
       if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
-      ARD_LAUNCH_NAMED("lstm_staged_fwd_kernel", kernel, dim3((unsigned)(ceil_div(S * ceil_div(B, 32), 8) * 8)), dim3(512), lds, stream, P);
+      ARD_LAUNCH_NAMED(lstm_instance("lstm_staged_fwd_kernel", staged / 8, kw), kernel, dim3((unsigned)(ceil_div(S * ceil_div(B, 32), 8) * 8)), dim3(512), lds, stream, P);
       return ARD_OK;
     };
-    if (staged == 8) st = kw == 4 ? launch(lstm_staged_fwd_kernel<1, 4>) : kw == 8 ? launch(lstm_staged_fwd_kernel<1, 8>)
-                          : kw == 12 ? launch(lstm_staged_fwd_kernel<1, 12>) : launch(lstm_staged_fwd_kernel<1, 16>);
+    if (staged == 8) st = kw == 4 ? launch(lstm_staged_fwd_kernel<1, 4>) : kw == 8 ? launch(lstm_staged_fwd_kernel<1, 8>) : launch(lstm_staged_fwd_kernel<1, 16>);
     else st = kw == 4 ? launch(lstm_staged_fwd_kernel<2, 4>) : kw == 8 ? launch(lstm_staged_fwd_kernel<2, 8>)
               : kw == 12 ? launch(lstm_staged_fwd_kernel<2, 12>) : launch(lstm_staged_fwd_kernel<2, 16>);
     if (st) return st;
@@ -1586,18 +1593,19 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     if (st) return st;
     ARD_LAUNCH_CHECK("lstm_xcd_bwd_kernel");
   } else if (staged) {
-    const int S = ceil_div(Hp, 16), need = ceil_div(Hp, 32), kw = need <= 4 ? 4 : (int)align_up((size_t)need, 8);
+    // (17 to 24 slices: as above)
+    const int S = ceil_div(Hp, 16), need = ceil_div(Hp, 32), kw = need <= 4 ? 4 : need <= 8 ? 8 : need <= 16 ? 16 : 32;
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,
                      S, 16, a.ax.off, a.ax.step, spin_limit, w.ex};
     const size_t lds = (size_t)4096 * kw + 1024 + (size_t)4 * 16 * 17 * 4;
     auto launch = [&](auto kernel) -> int32_t {
       if (lds > 65536) ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));
-      ARD_LAUNCH_NAMED("lstm_staged_bwd_kernel", kernel, dim3((unsigned)(ceil_div(S * ceil_div(B, 16), 8) * 8)), dim3(512), lds, stream, P);
+      ARD_LAUNCH_NAMED(lstm_instance("lstm_staged_bwd_kernel", 2, kw), kernel, dim3((unsigned)(ceil_div(S * ceil_div(B, 16), 8) * 8)), dim3(512), lds, stream, P);
       return ARD_OK;
     };
     st = kw == 4 ? launch(lstm_staged_bwd_kernel<4>) : kw == 8 ? launch(lstm_staged_bwd_kernel<8>)
-         : kw == 16 ? launch(lstm_staged_bwd_kernel<16>) : kw == 24 ? launch(lstm_staged_bwd_kernel<24>) : launch(lstm_staged_bwd_kernel<32>);
+         : kw == 16 ? launch(lstm_staged_bwd_kernel<16>) : launch(lstm_staged_bwd_kernel<32>);
     if (st) return st;
     ARD_LAUNCH_CHECK("lstm_staged_bwd_kernel");
   } else if (one_launch) {

@@ -1,6 +1,7 @@
-"""GPU parity of the bf16 recurrences with staging wavefronts at the edges of their range: 8 and 16 units per workgroup,
-every number of slices per wavefront, slices that end inside a share, one batch row and ragged batch blocks; and beyond it
-(1025 units and more, too many workgroups), where the recurrences without staging wavefronts run."""
+"""GPU parity of the bf16 recurrences with staging wavefronts at the edges of their range (batches above 128, or more than
+768 kept units): 8 and 16 units per workgroup, every number of slices per wavefront, slices that end inside a share and
+ragged batch blocks; and beyond it (1025 units and more, too many workgroups), where the recurrences without staging
+wavefronts run."""
 import numpy as np
 import pytest
 
@@ -17,12 +18,30 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,B,H,dp", [(4, 1, 8, 1), (3, 17, 129, 1), (4, 40, 260, 1), (3, 33, 513, 1), (3, 20, 760, 1), (3, 33, 1020, 1), (3, 128, 600, 1),
                                       (3, 128, 1024, 1), (3, 16, 1100, 1), (4, 100, 1030, 2)])
 def test_staged_recurrences(T, B, H, dp):
+    """Both ends of the recurrences' ranges; those of up to 768 kept units and 128 rows run with a batch block per XCD."""
     print("staged lstm", T, B, H, dp, flush=True)
     rng = np.random.default_rng(T + B + H)
     I = 16
     x, dh = (stored(rng.standard_normal(s), "bf16") for s in ((T, B, I), (T, B, H)))
     W = stored(rng.uniform(-0.06, 0.06, (4 * H, I + H)), "bf16")
     _check("bf16", x, W, dh, P.row_mask(H, dp, 1), ard.Pattern.row(dp, 1), *(from_vals(v, "bf16") for v in (x, W, dh)), f"staged {B} {H}")
+
+
+# (T, B, H) and the slices per wavefront of the kernels with staging wavefronts, forward (units per workgroup / 8, slices)
+# and backward, None where another form takes the pass
+STAGED = [((3, 200, 128), (1, 4), 4), ((3, 200, 200), (1, 4), 8), ((4, 160, 400), (1, 8), 16), ((3, 300, 256), (2, 4), None), ((3, 160, 500), (2, 8), None),
+          ((3, 160, 760), (2, 12), None), ((3, 129, 405), (1, 8), 16), ((3, 128, 1000), (2, 16), None), ((3, 50, 800), (1, 16), 32)]
+
+
+@pytest.mark.parametrize("shape", [s for s, _, _ in STAGED])
+def test_staged_recurrences_of_every_length(shape):
+    T, B, H = shape
+    print("staged lstm, every length", shape, flush=True)
+    rng = np.random.default_rng(T + B + H)
+    I = 16
+    x, dh = (stored(rng.standard_normal(s), "bf16") for s in ((T, B, I), (T, B, H)))
+    W = stored(rng.uniform(-0.06, 0.06, (4 * H, I + H)), "bf16")
+    _check("bf16", x, W, dh, P.row_mask(H, 1, 1), ard.Pattern.row(1, 1), *(from_vals(v, "bf16") for v in (x, W, dh)), f"staged {B} {H}")
 
 
 # (T, B, H): forward, backward without staging wavefronts.  Forward: 32, 64 and 128 batch rows per workgroup, the state read

@@ -272,6 +272,34 @@ def test_lstm_shapes_reach_the_recurrences_their_gpu_tests_name():
         D.last_bounds(lib)
 
 
+def test_lstm_shapes_reach_every_recurrence_with_staging_wavefronts():
+    from test_gpu_lstm_staged import STAGED
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        reached = set()
+        for (T, B, H), fwd, bwd in STAGED:
+            D.launches(lib)
+            _ok(lib, D.lstm_calls(lib, heap, D.BF16, T, B, 16, H, (1, 1)), f"lstm {T} {B} {H}")
+            want = {f"lstm_staged_fwd_kernel {fwd[0]} {fwd[1]}"} | ({f"lstm_staged_bwd_kernel 2 {bwd}"} if bwd else set())
+            got = {n for n in D.launches(lib)[1] if n.startswith("lstm_staged")}
+            assert got == want, (got, T, B, H)
+            reached |= got
+        # every batch and width up to the end of the range: nothing else is launched, and the status word is there exactly
+        # for the layers whose forward pass is one launch
+        for B in (1, 16, 64, 65, 96, 112, 128, 129, 160, 200, 256, 300, 400, 512, 1100, 2100, 9000):
+            for H in (8, 64, 128, 129, 200, 256, 257, 400, 512, 513, 600, 760, 768, 769, 1000, 1024, 1030, 1500):
+                D.launches(lib)
+                _ok(lib, D.lstm_calls(lib, heap, D.BF16, 2, B, 16, H, (1, 1)), f"lstm {B} {H}")
+                names = D.launches(lib)[1]
+                staged = {n for n in names if n.startswith("lstm_staged")}
+                assert staged <= reached, (staged - reached, B, H)
+                s, r = D.cpat((1, 1))
+                one_launch = any(n.startswith(("lstm_xcd_fwd", "lstm_staged_fwd", "lstm_persist_fwd")) for n in names)
+                assert (lib.ard_lstm_status_offset(D.BF16, 2, B, 16, H, r) != 2 ** 64 - 1) == one_launch, (names, B, H)
+                assert any(n.startswith(("lstm_xcd_bwd", "lstm_staged_bwd", "lstm_persist_bwd")) for n in names) != ("lstm_cell_bwd_kernel" in names), (names, B, H)
+        D.last_bounds(lib)
+
+
 def test_lstm_shapes_reach_the_recurrences_with_a_block_per_xcd():
     from test_gpu_lstm_xcd import SHAPES
     with D.dry_run() as lib:
