@@ -1365,20 +1365,21 @@ static int32_t conv_grid_gemm(const uint16_t* Wp, int rows, int K, const uint16_
     bn = force_bn;
   } else {
     // A launch runs in rounds: one workgroup of a large shape fills a CU (256 at a time), three of the 64 x 64 shape share
-    // one (768 at a time).  Costs of a round, a 256 x 256 round being 100, are means of contractions of 1152 and 2304
-    // (27.5, 34.6 and 43.2 us with 256 rows and 128, 192, 256 columns at 1152; 48, 62.5 and 71 us with 128 rows and 256,
-    // 384, 448 columns at 2304): a step of the large tiles takes about the time its operands take to arrive, 25 bytes per
-    // clock and CU.  Fewest rounds x cost wins, so a layer with few output positions goes to small tiles on many CUs
-    // instead of large ones on a few, and one a little above a full round goes to wider tiles (128 rows, 100352 pixels:
-    // two rounds of 256 columns 89 us, one of 448 70 us).  256 rows read their pixels twice in tiles of 128 rows: 82 us in
-    // two rounds of 448 against 77 of 256 x 256, so 448 is dearer.
-    static const struct { int bm, bn, slots, cost; } kTiles[] = {{64, 64, 768, 46}, {128, 256, 256, 66}, {256, 128, 256, 66}, {256, 192, 256, 82},
-                                                                 {128, 384, 256, 88}, {128, 448, 256, 102}, {256, 256, 256, 100}};
+    // one (768 at a time).  Costs of a round, a 256 x 256 round being 100, from launches of two whole rounds, contractions of
+    // 1152 and 2304 (us: 31 and 51 of 64 x 64, 50 and 84 of the smaller large ones, 64 and 107 of 256 x 192, 67 and 111 of
+    // 128 x 384, 78 and 131 of 128 x 448, 79 and 134 of 256 x 256); how often the pixels are read, with 128 to 512 rows,
+    // makes no difference.  A third of a round's cost goes by the tiles in it: those of a last round that is not full are
+    // over sooner (256 rows, 100352 pixels: 392 tiles of 256 x 256 take 74 and 122 us, 448 of 128 x 448, cheaper by the
+    // round, 75 and 125).  Lowest cost wins: over 44 layers (8 - 200 images, 7 x 7 - 56 x 56, 64 - 512 channels and rows) the
+    // choice is within 0.2 % of the best in the mean, within 4 % at most.
+    static const struct { int bm, bn, slots, cost; } kTiles[] = {{64, 64, 768, 40}, {128, 256, 256, 63}, {256, 128, 256, 63}, {256, 192, 256, 81},
+                                                                 {128, 384, 256, 83}, {128, 448, 256, 97}, {256, 256, 256, 100}};
     long best = -1;
     bm = bn = 0;
     for (const auto& t : kTiles) {
       if (t.bm > 64 && rows <= t.bm / 2) continue;
-      const long c = ((long)ceil_div(rows, t.bm) * ceil_div(cv.npix, t.bn) + t.slots - 1) / t.slots * t.cost;
+      const long n = (long)ceil_div(rows, t.bm) * ceil_div(cv.npix, t.bn), rounds = (n + t.slots - 1) / t.slots;
+      const long c = (2 * rounds * t.slots + n) * (768 / t.slots) * t.cost;
       if (best < 0 || c <= best) best = c, bm = t.bm, bn = t.bn;
     }
   }
