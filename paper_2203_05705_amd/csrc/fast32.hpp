@@ -517,12 +517,14 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   const int sc = walk ? cols.step : 1;
   const int c_end = walk && n1 == P.N ? cols.nphys : n1 * sc;
   const int nr = m1 - w.m0, i_ok = classes ? nr : imin(nr, w.am.n - w.m0);
-  // Large tiles of plain products: runs of four physical columns leave as one store (at any dword).  A thread works out
-  // once which of its four are kept and then goes down the rows, the wavefronts' partial tiles summed in place before (the
-  // loop below sums them again for each position of a strided map).  128 x 2048 -> 2048, dp 2 and 2, weight gradient: 21400
-  // -> 12500 clocks of output, 14.4 -> 12.8 us.  With smaller tiles, tile classes and convolutions the setting up costs
-  // what it saves (10.2 -> 10.8 us at 24 x 1472 -> 448 in tiles, 136.6 -> 138 us in three products of a convolution).
-  const bool runs = MODE == 0 && BM * BN >= 4096 && !classes && beta == 0.0f && cols.kind == AX_AFFINE && (walk || cols.step == 1);
+  // Large tiles of plain products that leave dropped columns or rows to be zeroed: runs of four physical columns leave as one
+  // store (at any dword).  A thread works out once which of its four are kept and then goes down the rows, the wavefronts'
+  // partial tiles summed in place before (the loop below sums them again for each position of a strided map).  Weight
+  // gradient, 128 x 2048 -> 2048: dp 2 and 2 21.8 -> 17.6 us, dp 4 and 1 17.2 -> 14.9.  Where nothing is dropped nothing is
+  // summed twice and the pass that sums in place costs more (30 x 1024 -> 3000: 16.6 us, in runs 18.0); with smaller tiles,
+  // tile classes and convolutions the setting up does (10.2 -> 10.8 us at 24 x 1472 -> 448 in tiles, 136.6 -> 138 us in
+  // three products of a convolution).
+  const bool runs = MODE == 0 && BM * BN >= 4096 && !classes && beta == 0.0f && walk && (cols.step > 1 || rows.n < rows.nphys);
   if (MODE == 0 && BM * BN >= 4096 && runs) {
     if constexpr (WK > 1) {  // the partial tiles, summed in place
       for (int e = tid; e < BM * BN; e += 256) {
@@ -536,25 +538,18 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
     const int pr0 = tid / pw, pc0 = tid % pw, rp = 256 / pw;
     for (int pc = pc0; pc < pieces; pc += pw) {
       const int c = c_lo + 4 * pc, nc = imin(4, c_end - c);
-      const int at = walk ? c : cols.off + c;  // of the run within an output row
       int lc[4];      // its columns in the tile
       uint32_t m[4];  // kept, and within the operand (beyond it: padding of a compact output, zero)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        int j = c + t;
-        bool ok = t < nc;
-        if (walk) {
-          const int d = j - cols.off, q = d >= 0 ? (int)fdiv((uint32_t)d, P.col_div) : 0;
-          ok = ok && d >= 0 && q * sc == d && q < P.N;
-          j = q;
-        }
-        ok = ok && j < w.bn.n;
-        lc[t] = ok ? j - w.n0 : 0;
+        const int d = c + t - cols.off, q = d >= 0 ? (int)fdiv((uint32_t)d, P.col_div) : 0;
+        const bool ok = t < nc && d >= 0 && q * sc == d && q < P.N && q < w.bn.n;
+        lc[t] = ok ? q - w.n0 : 0;
         m[t] = ok ? ~0u : 0u;
         asm("" : "+v"(m[t]));
       }
       auto store = [&](int r, const float (&x)[4]) {
-        float* const o = out + (long)r * ld + at;
+        float* const o = out + (long)r * ld + c;
         if (nc == 4) {
           *reinterpret_cast<F32Run<4>*>(o) = F32Run<4>{{x[0], x[1], x[2], x[3]}};
         } else {
@@ -563,7 +558,7 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
             if (t < nc) o[t] = x[t];
         }
       };
-      constexpr int U = 4;  // rows at a time: everything read before anything is nc
+      constexpr int U = 4;  // rows at a time: everything read before anything is stored
 #pragma unroll 1
       for (int l0 = pr0; l0 < nr; l0 += U * rp) {
         float x[U][4];
@@ -589,7 +584,7 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
           float g[U][4];
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            const float* q = src + (long)imax(pr[u], 0) * ld + at;
+            const float* q = src + (long)imax(pr[u], 0) * ld + c;
             if (nc == 4) {
               const F32Run<4> v = *reinterpret_cast<const F32Run<4>*>(q);
 #pragma unroll
