@@ -262,12 +262,13 @@ int32_t ard_lstm_fwd(int32_t dtype, int32_t T, int32_t B, int32_t I, int32_t H,
                      void* ws, size_t ws_bytes, void* stream);
 /*
  * bf16 layers whose kept state is small enough run the whole recurrence of ard_lstm_fwd in ONE launch
- * whose workgroups exchange h_t through memory and wait for each other step by step.  Up to 768 kept
- * units and a batch of 128 (on a GPU with all of its 256 CUs), those that have a CU also do the work of
- * those that have none: recurrences may run on several streams at once, at worst slower.  Beyond that
- * all workgroups, up to one per CU, have to be resident together: let such recurrences, and any other
- * kernel that holds CUs without end, not overlap.  The wait is bounded: workgroups that wait in vain
- * give up, leave normally and set an int32 in the workspace to 1; the outputs are then incomplete.
+ * whose workgroups exchange h_t through memory and wait for each other step by step.  In layers of
+ * up to 768 kept units, a batch of up to 128 and four steps or more (on a GPU with all of its 256 CUs)
+ * those that have a CU also do the work of those that have none: such recurrences may run on several
+ * streams at once, at worst slower.  In any other layer all workgroups, up to one per CU, have to be
+ * resident together: do not let such recurrences overlap with each other or with a kernel that holds
+ * CUs without end.  The wait is bounded: workgroups that wait in vain give up, leave normally and set
+ * an int32 in the workspace to 1; the outputs are then incomplete.
  * ard_lstm_status_offset returns that word's byte offset in the workspace ((size_t)-1 when this layer
  * takes the launch-per-step path, which has no such state); it is 0 after a completed call.
  */

@@ -1372,6 +1372,11 @@ static int lstm_xcd_units(const LstmArgs& a) {
   return Hp <= 16 * kLxSeats ? 16 : 24;
 }
 
+// Forward: two steps of more than 512 units are mostly start-up, which more, narrower workgroups all over the chip are
+// through with sooner: staging wavefronts, 16.2 against 18.9 us (600 units, B = 1), 17.2 against 20.1 (B = 20), 21.8
+// against 24.0 (680 units, B = 96), but 23.3 against 22.1 at B = 128.  Three steps are a draw: 21.5 against
+// 25.0 (680 units, B = 32) to 31.2 against 29.2 (768, B = 96).
+static int lstm_xcd_fwd_units(const LstmArgs& a) { return a.T == 2 && a.Hk > 512 && a.B <= 96 && lstm_staged_fwd_units(a) ? 0 : lstm_xcd_units(a); }
 // Backward: 600 units, B = 128, 64 steps: 680 -> 400 us for the pass, 4 steps 81 -> 70.  Of two or three steps beyond the range
 // of the staging wavefronts most is start-up (72 -> 65): they keep the form that still larger layers take.
 static int lstm_xcd_bwd_units(const LstmArgs& a) { return lstm_staged_bwd(a) || a.T > 3 ? lstm_xcd_units(a) : 0; }
@@ -1441,7 +1446,7 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
                           const LstmWs& w, hipStream_t stream) {
   const int T_ = a.T, B = a.B, I = a.I, H = a.H, Hk = a.Hk, Hp = pad8(Hk), ce = 16 / a.es;
   // the whole recurrence in one launch when all of its workgroups fit on the chip together
-  const int xcd = std::is_same<T, uint16_t>::value ? lstm_xcd_units(a) : 0, rb = lstm_xcd_rows(B);
+  const int xcd = std::is_same<T, uint16_t>::value ? lstm_xcd_fwd_units(a) : 0, rb = lstm_xcd_rows(B);
   const int staged = !xcd && std::is_same<T, uint16_t>::value ? lstm_staged_fwd_units(a) : 0;
   PersistPlan pp;
   const bool persist = !xcd && !staged && std::is_same<T, uint16_t>::value && lstm_persist_plan(a, pp);
@@ -1479,8 +1484,7 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     return ARD_OK;
   }
   if (staged) {
-    // (12 slices of 8 units: with 256 CUs the recurrences with a block per XCD take all such layers)
-    const int S = ceil_div(Hp, staged), need = (int)align_up((size_t)ceil_div(Hp, 64), 4), kw = staged == 8 && need == 12 ? 16 : need;
+    const int S = ceil_div(Hp, staged), kw = (int)align_up((size_t)ceil_div(Hp, 64), 4);
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersist P{Gx, (const uint16_t*)w.whc, (uint16_t*)w.hc, (uint16_t*)h, c, gates, w.sync + 1, w.sync, T_, B, H, Hk, Hp, S,
                   a.ax.off, a.ax.step, spin_limit};
@@ -1490,7 +1494,8 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
       ARD_LAUNCH_NAMED(lstm_instance("lstm_staged_fwd_kernel", staged / 8, kw), kernel, dim3((unsigned)(ceil_div(S * ceil_div(B, 32), 8) * 8)), dim3(512), lds, stream, P);
       return ARD_OK;
     };
-    if (staged == 8) st = kw == 4 ? launch(lstm_staged_fwd_kernel<1, 4>) : kw == 8 ? launch(lstm_staged_fwd_kernel<1, 8>) : launch(lstm_staged_fwd_kernel<1, 16>);
+    if (staged == 8) st = kw == 4 ? launch(lstm_staged_fwd_kernel<1, 4>) : kw == 8 ? launch(lstm_staged_fwd_kernel<1, 8>)
+                          : kw == 12 ? launch(lstm_staged_fwd_kernel<1, 12>) : launch(lstm_staged_fwd_kernel<1, 16>);
     else st = kw == 4 ? launch(lstm_staged_fwd_kernel<2, 4>) : kw == 8 ? launch(lstm_staged_fwd_kernel<2, 8>)
               : kw == 12 ? launch(lstm_staged_fwd_kernel<2, 12>) : launch(lstm_staged_fwd_kernel<2, 16>);
     if (st) return st;
@@ -1593,7 +1598,7 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     if (st) return st;
     ARD_LAUNCH_CHECK("lstm_xcd_bwd_kernel");
   } else if (staged) {
-    // (17 to 24 slices: as above)
+    // (17 to 24 slices: with 256 CUs the recurrences with a block per XCD take all such layers)
     const int S = ceil_div(Hp, 16), need = ceil_div(Hp, 32), kw = need <= 4 ? 4 : need <= 8 ? 8 : need <= 16 ? 16 : 32;
     const long spin_limit = getenv("ARD_LSTM_SPIN_LIMIT") ? atol(getenv("ARD_LSTM_SPIN_LIMIT")) : 4000000L;
     LstmPersistBwd P{gates, c, (const uint16_t*)dh, (const uint16_t*)w.whc, (uint16_t*)dG, w.sync + 1, w.sync, T_, B, H, Hk, Hp,
@@ -1702,7 +1707,7 @@ extern "C" size_t ard_lstm_workspace_bytes(int32_t dtype, int32_t T, int32_t B, 
 extern "C" size_t ard_lstm_status_offset(int32_t dtype, int32_t T, int32_t B, int32_t I, int32_t H, const ard_pattern* pat) {
   LstmArgs a{dtype, T, B, I, H, 0, 0, Axis{}, LstmTiles{}};
   PersistPlan pp;
-  if (lstm_check(a, pat) || (!lstm_xcd_units(a) && !lstm_staged_fwd_units(a) && !lstm_persist_plan(a, pp))) return (size_t)-1;
+  if (lstm_check(a, pat) || (!lstm_xcd_fwd_units(a) && !lstm_staged_fwd_units(a) && !lstm_persist_plan(a, pp))) return (size_t)-1;
   const LstmWs w = lstm_ws_layout((char*)nullptr + 256, a.es, T, B, I, H, a.Hk);
   return (size_t)((char*)w.sync - ((char*)nullptr + 256));
 }

@@ -1,5 +1,5 @@
-"""GPU parity of the bf16 recurrences with staging wavefronts at the edges of their range (batches above 128, or more than
-768 kept units): 8 and 16 units per workgroup, every number of slices per wavefront, slices that end inside a share and
+"""GPU parity of the bf16 recurrences with staging wavefronts at the edges of their range (batches above 128, more than
+768 kept units, or two steps forward of more than 512): 8 and 16 units per workgroup, every number of slices per wavefront, slices that end inside a share and
 ragged batch blocks; and beyond it (1025 units and more, too many workgroups), where the recurrences without staging
 wavefronts run."""
 import numpy as np
@@ -30,7 +30,8 @@ def test_staged_recurrences(T, B, H, dp):
 # (T, B, H) and the slices per wavefront of the kernels with staging wavefronts, forward (units per workgroup / 8, slices)
 # and backward, None where another form takes the pass
 STAGED = [((3, 200, 128), (1, 4), 4), ((3, 200, 200), (1, 4), 8), ((4, 160, 400), (1, 8), 16), ((3, 300, 256), (2, 4), None), ((3, 160, 500), (2, 8), None),
-          ((3, 160, 760), (2, 12), None), ((3, 129, 405), (1, 8), 16), ((3, 128, 1000), (2, 16), None), ((3, 50, 800), (1, 16), 32)]
+          ((3, 160, 760), (2, 12), None), ((3, 129, 405), (1, 8), 16), ((3, 128, 1000), (2, 16), None), ((3, 50, 800), (1, 16), 32),
+          ((2, 20, 600), (1, 12), None), ((2, 96, 513), (1, 12), None), ((2, 65, 768), (2, 12), None)]
 
 
 @pytest.mark.parametrize("shape", [s for s, _, _ in STAGED])
