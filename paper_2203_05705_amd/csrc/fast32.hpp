@@ -348,7 +348,9 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
     // own for each number of them, so that this counting still works: the rounds load up to D - 1 steps past the end, which
     // with loads this narrow cost as much as the contraction did (145 x 448 -> 320, strides 3 and 4: forward and data
     // gradient 9.7 -> 5.0 us; 64 x 784 -> 1024, stride 2: data gradient 10.4 -> 7.6, weight gradient 7.7 -> 6.5).  With wide
-    // loads it gains nothing (6.0 against 5.8 us) and its code delays the rounds (7.0 -> 7.7 us of 12 steps).
+    // loads it gains nothing (6.0 against 5.8 us) and its code delays the rounds (7.0 -> 7.7 us of 12 steps).  So it does in
+    // convolutions, which rarely have so few steps: 9 x 173 channels of 27 x 27 from 384, 3 x 3, data gradient 135 us, with
+    // that code 154; 1 x 1 from 96 channels 7.0, with it 6.0.
     auto at_once = [&](auto steps) {
       constexpr int N = decltype(steps)::value;
 #pragma unroll
@@ -358,7 +360,7 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
       for (int d = 0; d < N; ++d) mma(a[d], b[d]);
     };
     constexpr bool SCATTERED = AK == F32_KC || BK == F32_KC || AK == F32_MC || BK == F32_MC;
-    if (SCATTERED && BM * BN <= 1024 && n_full > 0 && n_full <= 2 * D - 2) {
+    if (MODE == 0 && SCATTERED && BM * BN <= 1024 && n_full > 0 && n_full <= 2 * D - 2) {
       if (n_full > D) at_once(std::integral_constant<int, D>{});
       f32_pick<D>(n_full > D ? n_full - D : n_full, at_once);
     } else if (n_full > 0) {
