@@ -560,25 +560,47 @@ extern "C" int32_t ard_sens_predict(int32_t dtype, int32_t N, int32_t C, int32_t
     const int taps = kh * kw;
     const int nch_max = imin(C, (g.y + taps - 2) / taps + 1);
     // Bands per workgroup.  Consecutive bands touch nearly the same input rows when they are shorter than an output row
-    // (98 bands of 8 positions would copy a 28 x 28 image 14 times over), so a workgroup takes as many as still leave two
-    // for every CU, unless their footprint would take more LDS than two may have.  (Longer ones in proportion to the
-    // image copy less; fewer workgroups leave CUs without work.)
+    // (98 bands of 8 positions would copy a 28 x 28 image 14 times over), so a workgroup takes several.  The pass takes as
+    // long as the CU with the most workgroups, L of them: L (1600 ns + 0.8 ns per staged word, 1.6 in fp32, + 0.24 ns per
+    // draw), 0.30 for one that has the CU to itself; fitted to 29 layers (8 - 128 images, 18 - 408 channels, 7 x 7 - 56 x 56, 1 -
+    // 784 bands) in up to 7 groupings each, 14 % rms.  Tried: the groupings that give every CU up to 1, 2, ... 8.  The choice is
+    // within 0.3 % of the best in the mean; always a little above two for every CU was 9 % slower (35 x 41 channels of
+    // 56 x 56 in bands of 4: 525 workgroups 41 us, 490 30; 59 x 128 of 56 x 56 in blocks of 112 x 576: 590 91, 472 76).
+    // No grouping takes more LDS than two workgroups of a CU may have.
     const int words = (Wd + 2 * pad + 31) / 32;
-    int RBG = imin(imax(1, ceil_div(8192 / kSensWaves, (int)((long)N * g.CB < 8192 ? N * g.CB : 8192))), g.RB), G = 1, nrow = 0;
+    int RBG = 0, G = 1, nrow = 0;
     size_t stage_bytes = 0;
-    // No more bands than this fit, counting no row that is touched in part: tried from there on, one number of bands after
-    // another (a 188 x 98 layer of 910 channels in bands of one position: 18 thousand tries from the top).
-    const double row_bytes = 4.0 * words * nch_max * stride, top_rows = 1.0 + (double)g.x / g.Wo;
-    const double room = 4608.0 * kSensWaves - 4.0 * g.y - 4.0 * words * nch_max * kh + row_bytes * top_rows;
-    const int most = (int)fmin(fmax(room / (row_bytes * g.x / g.Wo + 4.0 * g.x + sizeof(SensBand)), 1.0), (double)g.RB);
-    for (;; RBG = imax(ceil_div(g.RB, G - 1), ceil_div(g.RB, most))) {
-      G = ceil_div(g.RB, RBG);
+    auto group = [&](int groups) {  // sets G, nrow and stage_bytes; do they fit?
+      G = ceil_div(g.RB, groups);
       // output rows a group can span: groups of whole rows start on a row, any other may start anywhere in one
       const long span = (long)G * g.x;
       const long oh_span = span % g.Wo == 0 ? span / g.Wo : (span + g.Wo - 2) / g.Wo + 1;
       nrow = ((int)(oh_span < g.Ho ? oh_span : g.Ho) - 1) * stride + kh;
       stage_bytes = ((size_t)nrow * words * nch_max + g.y + (size_t)G * g.x) * 4 + G * sizeof(SensBand);
-      if (G == 1 || stage_bytes <= (size_t)4608 * kSensWaves) break;
+      return stage_bytes <= (size_t)4608 * kSensWaves;
+    };
+    const long blocks = (long)N * g.CB;  // per group of an image's bands
+    const double draws = (double)k_permille * g.x * g.y / 1000, word_ns = dtype == ARD_BF16 ? 0.8 : 1.6;
+    double least = 0;
+    int tried = 0;
+    for (int r = 1; r <= 8; ++r) {
+      const int groups = (int)imin(g.RB, imax(1, (int)(256L * r / blocks)));
+      if (groups == tried) continue;
+      tried = groups;
+      if (!group(groups)) continue;
+      const long L = (blocks * ceil_div(g.RB, G) + 255) / 256;
+      const double ns = L * (1600 + word_ns * nrow * words * nch_max + (L == 1 ? 0.30 : 0.24) * G * draws);
+      if (!RBG || ns < least) least = ns, RBG = groups;
+    }
+    if (RBG) {
+      group(RBG);
+    } else {
+      // No more bands than this fit, counting no row that is touched in part: tried from there on, one number of bands after
+      // another (a 188 x 98 layer of 910 channels in bands of one position: 18 thousand tries from the top).
+      const double row_bytes = 4.0 * words * nch_max * stride, top_rows = 1.0 + (double)g.x / g.Wo;
+      const double room = 4608.0 * kSensWaves - 4.0 * g.y - 4.0 * words * nch_max * kh + row_bytes * top_rows;
+      const int most = (int)fmin(fmax(room / (row_bytes * g.x / g.Wo + 4.0 * g.x + sizeof(SensBand)), 1.0), (double)g.RB);
+      for (RBG = tried; !group(RBG) && G > 1;) RBG = imax(ceil_div(g.RB, G - 1), ceil_div(g.RB, most));
     }
     RBG = ceil_div(g.RB, G);
     // (pad < filter size: every window then starts inside the image, which the copy's bounds rely on)
