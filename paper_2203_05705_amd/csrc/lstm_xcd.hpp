@@ -91,9 +91,11 @@ __device__ __forceinline__ int lx_meet(int* seat, int S, int s, int lane, long l
     local = __all(v == mine);
     if (!free) return n;
     if (polls < kLxPatience) continue;
-    // the next free one from its own on: those that are there begin at different ones
-    const uint64_t above = free >> s << s;
-    const int k = __builtin_ctzll(above ? above : free);
+    // each its own share of the free ones: in the order of those that are there, and not the next one at once
+    const int rank = __builtin_popcountll(__ballot(lane < s && v != 0)) % __builtin_popcountll(free);
+    const bool wanted = (free >> lane & 1) && __builtin_popcountll(free & ((1ull << lane) - 1)) == rank;
+    const int k = __builtin_ctzll(__ballot(wanted));
+    polls -= 8;
     if (!take(k)) continue;
     if (lane == 0) taken[n] = k;
     ++n;
