@@ -186,10 +186,11 @@ __global__ __launch_bounds__(64 * (lx_fwd_waves(UW) + 4)) void lstm_xcd_fwd_kern
       at[i] = (unsigned)((ws < S ? ws * BLK : 0) + lx_at<RB>(n & (RB - 1), (g8 - ws * (UW / 8)) * 8));
     }
     // (`it` counts the steps of all seats: what go_s and red hold of one stays until the next but one)
+    const char* src = ex;  // images of the step before
     auto product = [&](int t, int it) {
       if (t > 0) {
         lp_u32x4 v[KW];
-        if (!lx_wait<KW>(lp_buffer(ex + (t - 1) * ex_step, (unsigned)(S * BLK)), at, v, P.spin_limit, P.err)) go_s[it & 1] = 0;
+        if (!lx_wait<KW>(lp_buffer(src, (unsigned)(S * BLK)), at, v, P.spin_limit, P.err)) go_s[it & 1] = 0;
         f32x4_t acc[NT];
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt)
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(64 * (lx_fwd_waves(UW) + 4)) void lstm_xcd_fwd_kern
     const int seats = __builtin_amdgcn_readfirstlane(seats_s);  // (0 and -1: nothing to do)
     for (int it = 0, t = 0, i = 0; t < P.T && seats > 0; ++it) {
       if (!product(t, it)) return;
-      if (++i == seats) i = 0, ++t;
+      if (++i == seats) i = 0, src += t > 0 ? ex_step : 0, ++t;
       if (seats > 1) {
         const int l = lx_lane();
         weights(__builtin_amdgcn_readfirstlane(seat_s[i]), l & 15, l >> 4);
@@ -261,10 +262,14 @@ __global__ __launch_bounds__(64 * (lx_fwd_waves(UW) + 4)) void lstm_xcd_fwd_kern
       for (int g = 0; g < 4; ++g) zx[p][g] = Gt[zx_at[p] + (unsigned)(g * Hp)];
   };
   bool local;
+  char* img = ex;  // images of the step
   auto cell = [&](int t, int it, int seat, bool ahead) {
+    char* const out = img + seat * BLK;
+    // (here: the compiler would wait for these loads, and for the stores behind them, behind the barrier)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) asm volatile("" : "+v"(zx[p][0]), "+v"(zx[p][1]), "+v"(zx[p][2]), "+v"(zx[p][3]));
     lp_barrier();
     if (!__builtin_amdgcn_readfirstlane(go_s[it & 1])) return false;
-    char* const out = ex + t * ex_step + seat * BLK;
     float gi[NP], gf[NP], gg[NP], go[NP], hv[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -317,7 +322,7 @@ __global__ __launch_bounds__(64 * (lx_fwd_waves(UW) + 4)) void lstm_xcd_fwd_kern
   const int seats = __builtin_amdgcn_readfirstlane(seats_s);
   for (int it = 0, t = 0, i = 0, seat = s; t < P.T && seats > 0; ++it) {
     if (!cell(t, it, seat, seats == 1)) return;
-    if (++i == seats) i = 0, ++t;
+    if (++i == seats) i = 0, ++t, img += ex_step;
     if (seats > 1 && t < P.T) {
       seat = __builtin_amdgcn_readfirstlane(seat_s[i]);
       cells(seat, (wave - NM) * 64 + lx_lane());
@@ -406,9 +411,9 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
     const unsigned total = (unsigned)(S * BLK), share = (unsigned)(wave * SHARE);
     unsigned peek[1] = {share + (unsigned)((lane >> 3) * BLK)};
     peek[0] = (((lane >> 3) + 1) * BLK <= SHARE && peek[0] + BLK <= total ? peek[0] : 0u) + BLK - 128 + (lane & 7) * 16;
+    const char* src = ex;  // images of the step before
     auto product = [&](int tt, int it) {
       if (tt > 0) {
-        const char* src = ex + (tt - 1) * ex_step;
         lp_u32x4 last[1];
         bool ok = lx_wait<1>(lp_buffer(src, total), peek, last, P.spin_limit, P.err);
         f32x4_t acc[NB][NA];
@@ -476,7 +481,7 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
     weights(n, kg);
     for (int it = 0, tt = 0, i = 0; tt < P.T; ++it) {
       if (!product(tt, it)) return;
-      if (++i == seats) i = 0, ++tt;
+      if (++i == seats) i = 0, src += tt > 0 ? ex_step : 0, ++tt;
       if (seats > 1 && tt < P.T) {
         lp_barrier();  // (what the image overwrites has been read)
         const int l = lx_lane();
@@ -489,7 +494,7 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
   const bool local = local_s != 0 && !P.spread;
   const int c0 = tid - 64 * NM;
   int row[NP], ul[NP], u[NP];
-  unsigned at[NP], red_at[NP];  // byte of the cell's first word in the image, its place in a partial tile
+  unsigned at[NP], red_at[NP], c_at[NP], g_at[NP];  // byte of the cell's first word in the image; its place in a partial tile, in c, in the gates
   bool kept[NP], live[NP], in_store[NP];
   uint32_t mask[NP];  // all ones of a kept cell
   float dc_next[NP];
@@ -502,6 +507,7 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
       const int j = seat * UW + ul[p], r = bb * RB + row[p];
       kept[p] = live[p] && j < P.Hk && r < B, in_store[p] = live[p] && j < Hp && r < B;
       u[p] = kept[p] ? P.off + j * P.step : 0;
+      c_at[p] = (unsigned)(imin(r, B - 1) * H + u[p]), g_at[p] = (unsigned)(imin(r, B - 1) * 4 * H + u[p]);
       mask[p] = kept[p] ? ~0u : 0u;
       asm("" : "+v"(mask[p]));  // (or a branch comes of it)
       dc_next[p] = 0.0f;
@@ -511,23 +517,27 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
   float ni[NP], nf[NP], ng[NP], no[NP], nc[NP], np[NP];
   uint16_t nd[NP];
   auto fetch_cell = [&](int t) {
+    const float* const ga = P.gates + (long)t * B * 4 * H;
+    const float* const before = P.c + (long)(t > 0 ? t - 1 : 0) * B * H;
+    const uint16_t* const dh = P.dh + (long)t * B * H;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      const long at = (long)t * B + imin(bb * RB + row[p], B - 1);
-      const float* ga = P.gates + at * 4 * H;
-      ni[p] = ga[u[p]], nf[p] = ga[H + u[p]], ng[p] = ga[2 * H + u[p]], no[p] = ga[3 * H + u[p]];
-      nc[p] = np[p];
-      np[p] = P.c[(at - (t > 0 ? B : 0)) * H + u[p]];
-      nd[p] = P.dh[at * H + u[p]];
+      ni[p] = ga[g_at[p]], nf[p] = ga[g_at[p] + (unsigned)H], ng[p] = ga[g_at[p] + 2u * H], no[p] = ga[g_at[p] + 3u * H];
+      nd[p] = dh[c_at[p]];
     }
+    // (last: its copy waits for it, and so for all of them before the results are stored)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) nc[p] = np[p], np[p] = before[c_at[p]];
   };
   auto fetch_first = [&](int t) {
 #pragma unroll
-    for (int p = 0; p < NP; ++p) np[p] = P.c[((long)t * B + imin(bb * RB + row[p], B - 1)) * H + u[p]];
+    for (int p = 0; p < NP; ++p) np[p] = P.c[(long)t * B * H + c_at[p]];
     fetch_cell(t);
   };
+  char* img = ex;  // images of the step
   auto cell = [&](int tt, int it, int seat, bool ahead) {
     const int t = P.T - 1 - tt;
+    char* const out = img + seat * BLK;
     // all that does not depend on the gradient arriving from the step after, while the others are waited for:
     // d = (dc ki, dc kf, dc kg, dh ko) with dc = dh kc + dc_next
     float kc[NP], ki[NP], kf[NP], kg[NP], ko[NP], fg[NP], dh0[NP];
@@ -536,10 +546,11 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
       const float gi = ni[p], gf = nf[p], gg = ng[p], go = no[p], cp = t > 0 ? np[p] : 0.0f, tc = lx_tanh(nc[p]);
       kc[p] = go * (1.0f - tc * tc), ki[p] = gg * gi * (1.0f - gi), kf[p] = cp * gf * (1.0f - gf), kg[p] = gi * (1.0f - gg * gg);
       ko[p] = tc * go * (1.0f - go), fg[p] = gf, dh0[p] = bf16_bits_to_f32(nd[p]);
+      // (here: the compiler would do it, and wait for loads and stores, behind the barrier)
+      asm volatile("" : "+v"(kc[p]), "+v"(ki[p]), "+v"(kf[p]), "+v"(kg[p]), "+v"(ko[p]), "+v"(fg[p]), "+v"(dh0[p]));
     }
     lp_barrier();
     if (!__builtin_amdgcn_readfirstlane(go_s[it & 1])) return false;
-    char* const out = ex + tt * ex_step + seat * BLK;
     unsigned word[NP][4];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -580,11 +591,11 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
   lp_barrier();
   for (int it = 0, tt = 0, i = 0, seat = s; tt < P.T; ++it) {
     if (!cell(tt, it, seat, seats == 1)) return;
-    if (++i == seats) i = 0, ++tt;
+    if (++i == seats) i = 0, ++tt, img += ex_step;
     if (seats > 1 && tt < P.T) {
 #pragma unroll
       for (int p = 0; p < NP; ++p)
-        if (kept[p]) P.dc[(long)(bb * RB + row[p]) * H + u[p]] = dc_next[p];
+        if (kept[p]) P.dc[c_at[p]] = dc_next[p];
       seat = __builtin_amdgcn_readfirstlane(seat_s[i]);
       lp_barrier();
       const int l = lx_lane();
@@ -594,7 +605,7 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
       fetch_first(P.T - 1 - tt);
 #pragma unroll
       for (int p = 0; p < NP; ++p)
-        if (tt > 0 && kept[p]) dc_next[p] = P.dc[(long)(bb * RB + row[p]) * H + u[p]];
+        if (tt > 0 && kept[p]) dc_next[p] = P.dc[c_at[p]];
       lx_landed();
     }
   }
