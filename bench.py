@@ -43,9 +43,9 @@ REPEATS = 5              # the block of `steps` timed iterations is repeated; me
 # kernel of the call (the product alone or grouped with the pass that zeroes dropped rows, the finishing pass
 # where the pattern needs one), as its time is; the other two: the product kernel, per launch.
 TRAFFIC = {
-    "L2.bwd_weight": (20429416, "profiles/hbm_traffic_L2_bwd_weight.txt"),
-    "C3.fwd.dp2": (151214912, "profiles/hbm_traffic_config3_fwd_dp2.txt"),
-    "C5.fwd": (90898275, "profiles/hbm_traffic_config5_conv_fwd.txt"),
+    "L2.bwd_weight": (20420318, "profiles/hbm_traffic_L2_bwd_weight.txt"),
+    "C3.fwd.dp2": (134594274, "profiles/hbm_traffic_config3_fwd_dp2.txt"),
+    "C5.fwd": (90848009, "profiles/hbm_traffic_config5_conv_fwd.txt"),
 }
 
 

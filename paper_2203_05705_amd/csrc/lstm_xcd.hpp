@@ -22,10 +22,11 @@ namespace ard {
 // No workgroup waits for one that may not have a CU: two recurrences on two streams may share an XCD's CUs so that neither
 // ever has all of its own.  A workgroup's part of a block is a seat; when some are still free after kLxPatience polls, those
 // that are there take them as well, and do their parts of a step one after the other with weights from memory.  One that
-// comes too late leaves.
+// comes too late leaves.  (750 units, B = 20, 35 steps, with 31, 16 and 1 of 32 workgroups: forward 84 -> 257, 579 and
+// 4800 us, backward 146 -> 557, 1170 and 10200.)
 //
-// Recurrences with staging wavefronts -> these, us: 512 kept units, B = 128, 64 steps: forward 204 -> 97, backward
-// 237 -> 155; 750 units, B = 20, 35 steps: 113 -> 67 and 136 -> 87 (with 16 rows per block 95 and 142: half of every
+// Recurrences with staging wavefronts -> these, us: 512 kept units, B = 128, 64 steps: forward 204 -> 114, backward
+// 237 -> 158; 750 units, B = 20, 35 steps: 113 -> 67 and 136 -> 88 (with 16 rows per block 95 and 142: half of every
 // operand and of the cells would be padding).  Eight product wavefronts instead of four at 512 units forward, or a higher
 // priority of the cell wavefronts: nothing.
 constexpr int kLxBlocks = 8, kLxSeats = 32;  // most batch blocks, most workgroups of one
@@ -438,7 +439,7 @@ __global__ __launch_bounds__(64 * (kLxBwdWaves + 4)) void lstm_xcd_bwd_kernel(co
 #pragma unroll
               for (int e = 0; e < 4; ++e) acc[p][a][e] = 0.0f;
           unsigned most = 0;
-          constexpr int GRP = KW > 8 ? 4 : KW;  // operands in registers at a time (12 and the weights of 24 units spill: 109 instead of 87 us)
+          constexpr int GRP = KW > 8 ? 4 : KW;  // operands in registers at a time (12 and the weights of 24 units spill: 109 instead of 87 us, 8 rows)
 #pragma unroll
           for (int i0 = 0; i0 < KW; i0 += GRP) {
             lp_u32x4 v[GRP];
