@@ -35,3 +35,16 @@ def test_words_of_a_row_and_shares_of_a_band(N, C, H, W, k, stride, pad, x, y, p
         Av = stored(rng.standard_normal((N, C, H, W)), dtype)
         for seed, thr in ((11, 0.1), (2 ** 61 + 3, -0.3)):
             _predict_both(Av, from_vals(Av, dtype), k, stride, pad, x, y, permille, 500, thr, seed, 2)
+
+
+@pytest.mark.parametrize("N,C,H,W,k,stride,pad,x,y,permille", [
+    (300, 2, 13, 13, 3, 1, 1, 4, 0, 300), (70, 4, 14, 14, 3, 1, 1, 14, 0, 300), (40, 6, 13, 13, 3, 1, 1, 5, 27, 400), (120, 3, 9, 40, 3, 2, 1, 7, 0, 500),
+    (257, 1, 8, 8, 1, 1, 0, 3, 0, 1000), (300, 96, 240, 4, 3, 1, 1, 4, 0, 1), (1, 910, 188, 98, 3, 1, 1, 1, 0, 1)])
+def test_several_bands_of_a_workgroup(N, C, H, W, k, stride, pad, x, y, permille):
+    """Images enough that workgroups take several bands, the last one fewer, in rows of one and two words and with two column
+    blocks; an image of which not all bands fit, and one of which a single band takes more LDS than is allotted."""
+    print("prediction, bands", N, C, H, W, k, stride, x, y, permille, flush=True)
+    rng = np.random.default_rng(H * W + C)
+    for dtype in ("bf16", "f32") if N * C * H * W < 1 << 20 else ("bf16",):
+        Av = stored(rng.standard_normal((N, C, H, W), dtype=np.float32), dtype)
+        _predict_both(Av, from_vals(Av, dtype), k, stride, pad, x, y, permille, 500, 0.1, 2 ** 40 + 9, 3)
