@@ -204,7 +204,8 @@ int32_t ard_drop_gemm_bwd_weight(int32_t dtype, int32_t B, int32_t I, int32_t O,
  * of the library (ard_static_scratch_bytes() bytes, 64 MiB, one copy per GPU, held until the
  * process ends).  The call makes no allocation of any kind; the first call on a device looks the
  * array's address up.  A layer for which ard_gemm_workspace_bytes() exceeds the array is refused
- * with ARD_EWORKSPACE before anything is enqueued.  Nothing in the scratch has to start at zero
+ * with ARD_EWORKSPACE before anything is enqueued (under a tile pattern only if its tile lists do not
+ * fit: without room for operand copies it is computed without them).  Nothing in the scratch has to start at zero
  * (every partial sum is written before it is read), so nothing is cleared.  All calls on one GPU
  * share that GPU's array: two calls that overlap in time on the same GPU (different streams or
  * threads) race; calls on one stream are ordered and safe.

@@ -118,7 +118,7 @@ struct FastParams {
   float* part;               // != NULL: write fp32 partial sums part[split][M][N] instead of C
   const uint16_t* relu_src;  // optional, same layout as C
   int relu, out_f32;
-  int c_rows_mapped, c_cols_mapped;  // output rows / columns go through the M / N map (else identity)
+  int c_rows_mapped, c_cols_mapped;  // output rows / columns go through the M / N map (else identity); M x N of them exist
   // Scattering epilogue (row patterns without compact outputs): the tile's results go through
   // LDS and are written, with the dropped positions it owns as +0.0, through these affine maps.
   int scatter;
@@ -1158,7 +1158,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   int* const row_of = reinterpret_cast<int*>(tile + F_BM * direct_pitch(BN, 2));  // physical rows, -1 beyond the output
   __syncthreads();
   if (tid < F_BM) {
-    const int i0 = m0 + (tid & ~31), mlim = P.c_rows_mapped ? am.n : P.M, mphys = P.c_rows_mapped ? am.nphys : P.M;
+    const int i0 = m0 + (tid & ~31), mlim = P.c_rows_mapped ? am.n : P.M, mphys = P.M;
     const int r = partial ? m0 + tid : i0 < mlim ? (P.c_rows_mapped ? ax_phys(am, i0) : i0) + (tid & 31) : mphys;
     row_of[tid] = r < (partial ? P.M : mphys) ? r : -1;
   }
@@ -1171,7 +1171,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       const int nlim = partial ? jlim : P.c_cols_mapped ? bn.n : P.N;
       const int pc = partial ? j : P.c_cols_mapped ? ax_phys(bn, jb & ~31) + (jb & 31) : jb;
       // columns that exist, and that are not padding of a compact output
-      const int nc = imin(4, partial ? jlim - jb : (P.c_cols_mapped ? bn.nphys : P.N) - pc), nv = n_valid - jb;
+      const int nc = imin(4, partial ? jlim - jb : P.N - pc), nv = n_valid - jb;
       const long ld = partial ? P.N : P.ldc;
       const float alpha = partial ? 1.0f : P.alpha;
       float* const outf = partial ? P.part + (long)split * P.M * P.N : reinterpret_cast<float*>(P.C);
@@ -1231,7 +1231,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     constexpr int PITCH = direct_pitch(BN, 2), CL = BN / 8, RS = NT / CL;
     stage_bf16();
     __syncthreads();
-    const int nlim = P.c_cols_mapped ? bn.n : P.N, nphys = P.c_cols_mapped ? bn.nphys : P.N;
+    const int nlim = P.c_cols_mapped ? bn.n : P.N, nphys = P.N;
     const uint16_t* const src = GENERAL_OUT ? P.relu_src : nullptr;
     if (((P.ldc & 1) | (int)((uintptr_t)P.C & 3) | (int)((uintptr_t)src & 3)) != 0) {
       // rows that begin at odd places: a lane per column

@@ -451,100 +451,6 @@ static bool has_tile_lists(const LayerArgs& a, const void* ws, size_t ws_bytes) 
   return (p->d_keep && p->d_mask && p->d_rowptr && p->d_colptr && p->d_csc_rows) || (ws && ws_bytes >= tile_ws_bytes(a.TR, a.TC));
 }
 
-// Tile pattern on the large-tile path: classes of tile rows / columns (see fast.hpp).
-// op 0: Y = X . W^T   1: dX = dY . W   2: dW = dY^T . X
-static bool try_fast_tile(int op, const LayerArgs& a, const void* Ap, const void* Bp, void* Cp, float alpha, int relu,
-                          const void* ws, size_t ws_bytes, hipStream_t stream, int32_t& st, const void* relu_src = nullptr) {
-  // (fp32 calls without room for the tile lists of the general engine are refused there, as documented)
-  if (a.dtype == ARD_F32)
-    return has_tile_lists(a, ws, ws_bytes) && try_f32_tile(op, a.B, a.I, a.O, a.TR, a.TC, *a.po, Ap, Bp, Cp, alpha, relu, relu_src, stream, st);
-  if (a.dtype != ARD_BF16 || dev_knobs().no_fast) return false;
-  const int x = a.po->tile_r, y = a.po->tile_c, dp = a.po->dp, o = a.po->b - 1, TR = a.TR, TC = a.TC;
-  const int B = a.B, I = a.I, O = a.O;
-  if ((I % 8) || (O % 8) || (long)B * O >= (1L << 31) || (long)B * I >= (1L << 31) || (long)O * I >= (1L << 31)) return false;
-  if (((uintptr_t)Ap & 15) || ((uintptr_t)Bp & 15)) return false;
-  FastParams F{};
-  ClassTab& t = F.tab;
-  if (!tile_classes(op, O, I, TR, TC, x, y, dp, o, t)) return false;
-  F.A = (const uint16_t*)Ap, F.B = (const uint16_t*)Bp, F.C = (uint16_t*)Cp;
-  F.ldb = I;
-  F.c_cols_mapped = 1;
-  if (op == 0) {
-    // contraction blocks: whole 64-deep steps, or the 32-wide tiles of Section 3.2 taken two per step
-    if ((256 % x) || ((y % 64) && y != 32)) return false;
-    F.lda = I, F.am = axis_identity(B);
-    F.a_elems = (long)B * I, F.b_elems = (long)O * I;
-    F.ldc = O;
-    F.M = B, F.N = O;
-  } else if (op == 1) {
-    if ((256 % y) || ((x % 64) && x != 32)) return false;
-    F.lda = O, F.am = axis_identity(B);
-    F.a_elems = (long)B * O, F.b_elems = (long)O * I;
-    F.ldc = I;
-    F.M = B, F.N = I;
-  } else {
-    if ((256 % x) || (256 % y) || (x % 8) || (y % 8)) return false;
-    F.lda = O;
-    F.a_elems = (long)B * O, F.b_elems = (long)B * I;
-    F.k = axis_identity(B);
-    F.ldc = I;
-    F.c_rows_mapped = 1;
-    F.M = O, F.N = I;
-  }
-  auto count = [&](int bm, int bn, int& heavy) { return count_classes(op, t, B, bm, bn, heavy); };
-  // Tile choice by estimated time: rounds of workgroups over the chip x contraction steps x the time one
-  // round of one step takes with that tile.  A period that does not divide the tile grid leaves classes of
-  // 21 or 13 tile rows: wide tiles then end in a mostly empty block and the workgroup count lands just above
-  // a multiple of the CU count (288 for dp = 3), which smaller tiles avoid.  Round times (us) measured on
-  // the dense 4096^3 product per tile and operand layout; an 8-wavefront tile has one slot per CU, a
-  // 4-wavefront tile two.
-  static const float kRoundUs[3][5] = {{2.21f, 1.33f, 1.32f, 0.79f, 0.464f},   // forward (both operands contraction-contiguous)
-                                       {2.04f, 1.19f, 1.17f, 0.70f, 0.43f},    // data gradient
-                                       {1.98f, 1.14f, 1.16f, 0.66f, 0.44f}};   // weight gradient
-  int steps = op == 2 ? ceil_div(B, 64) : 0;
-  if (op != 2)
-    for (int c = 0; c < t.ncls; ++c) steps = imax(steps, ceil_div(t.k_cnt[c] * t.k_bs, 64));
-  int heavy = 0, bm = 0, bn = 0, total = 0;
-  float best = 0.0f;
-  for (int ci = 0; ci < 5; ++ci) {
-    const TileCfg& c = kTileCfgs[ci];
-    if ((c.bn % t.n_bs) || (op == 2 && (c.bm % x))) continue;
-    if (dev_knobs().class_tile && ci != dev_knobs().class_tile - 1) continue;
-    if (relu_src && c.bm == 256 && c.bn == 256) continue;  // (that tile only stores plain results)
-    int h = 0;
-    const int tot = count(c.bm, c.bn, h);
-    if (tot == 0) continue;
-    const int slots = c.bm * c.bn >= 256 * 128 ? 256 : 512;
-    const float est = (float)ceil_div(h > 0 ? h : 1, slots) * (float)steps * kRoundUs[op][ci];
-    if (bm == 0 || est < best) best = est, bm = c.bm, bn = c.bn;
-  }
-  if (bm == 0) return false;
-  total = count(bm, bn, heavy);
-  if (total == 0) return false;
-  // (however few tiles there are, this path wins: the general engine's block-list products take 2-3x as
-  // long even on a batch of 128 rows)
-  F.alpha = alpha;
-  F.relu = relu;
-  F.relu_src = (const uint16_t*)relu_src;
-  F.total_tiles = total;
-  // (a kernel that a grouped launch holds is issued later and without the zeros' workgroups)
-  const bool grouped = batch_open() && bn == 64 && bm <= 128;
-  if (op == 2 && !grouped && I % 8 == 0 && y % 8 == 0 && ((uintptr_t)Cp & 15) == 0) {
-    F.zt = ZeroTilesJob{ceil_div(O, kZeroTileRows), O, I, TC, dp, o, fast_div((uint32_t)x), fast_div((uint32_t)y / 8), fast_div((uint32_t)I / 8)};
-  } else if (op == 2) {
-    ARD_LAUNCH(zero_dropped_tiles_kernel<uint16_t>, dim3((unsigned)(TR * TC)), dim3(256), 0, stream, (uint16_t*)Cp, I, O, I,
-                       x, y, TC, dp, o);
-    hipError_t e = ard::launch_status();
-    if (e != hipSuccess) {
-      st = fail(ARD_EHIP, "launch of zero_dropped_tiles_kernel failed: %s", hipGetErrorString(e));
-      return true;
-    }
-  }
-  F.splits = 1;
-  st = launch_direct(op != 2, op == 0, F, bm, bn, stream);
-  return true;
-}
-
 static int pick_bn(int t) { return t % 128 == 0 ? 128 : (t % 64 == 0 ? 64 : 32); }
 
 }  // namespace ard
@@ -606,6 +512,133 @@ __global__ __launch_bounds__(256) void pack_operands_kernel(const PackArgs a) {
   const int second = (int)blockIdx.x >= a.split;
   const int b = (int)blockIdx.x - (second ? a.split : 0), gx = second ? a.gx[1] : a.gx[0];
   compact_weight_body<T>(second ? a.job[1] : a.job[0], b % gx, b / gx);
+}
+
+// Tile pattern on the large-tile path: classes of tile rows / columns (see fast.hpp).
+// op 0: Y = X . W^T   1: dX = dY . W   2: dW = dY^T . X
+static bool try_fast_tile(int op, const LayerArgs& a, const void* Ap, const void* Bp, void* Cp, float alpha, int relu,
+                          void* ws, size_t ws_bytes, hipStream_t stream, int32_t& st, const void* relu_src = nullptr) {
+  // (fp32 calls without room for the tile lists of the general engine are refused there, as documented)
+  if (a.dtype == ARD_F32)
+    return has_tile_lists(a, ws, ws_bytes) && try_f32_tile(op, a.B, a.I, a.O, a.TR, a.TC, *a.po, Ap, Bp, Cp, alpha, relu, relu_src, stream, st);
+  if (a.dtype != ARD_BF16 || dev_knobs().no_fast) return false;
+  const int x = a.po->tile_r, y = a.po->tile_c, dp = a.po->dp, o = a.po->b - 1, TR = a.TR, TC = a.TC;
+  const int B = a.B, I = a.I, O = a.O;
+  // Operands whose rows are no whole 16-byte pieces are copied with rows padded to 8 elements, zeros (they end inside the
+  // last tile, where the pattern's tiles are clipped: its classes are the same), as are those that lie askew; a weight
+  // contracted over its rows also gets the rows that go with a padded dY.  The tile-class product on copies against the
+  // general engine's block lists, us, three products with their copies: 226 x 292 -> 1269, 32 x 32 tiles, dp = 2
+  // 424 -> 47; 21 x 1423 -> 384, 64 x 64 tiles, dp = 1 292 -> 38.
+  const int I8 = pad8(I), O8 = pad8(O);
+  if ((long)pad8(B) * O8 >= (1L << 31) || (long)pad8(B) * I8 >= (1L << 31) || (long)O8 * I8 >= (1L << 31)) return false;
+  const bool askew_a = ((uintptr_t)Ap & 15) != 0, askew_b = ((uintptr_t)Bp & 15) != 0;
+  const bool copy_a = askew_a || (op == 0 ? I != I8 : O != O8), copy_b = askew_b || I != I8 || (op == 1 && O != O8);
+  FastParams F{};
+  ClassTab& t = F.tab;
+  if (!tile_classes(op, op == 0 ? O : O8, I8, TR, TC, x, y, dp, o, t)) return false;
+  F.C = (uint16_t*)Cp;
+  F.ldb = I8;
+  F.c_cols_mapped = 1;
+  if (op == 0) {
+    // contraction blocks: whole 64-deep steps, or the 32-wide tiles of Section 3.2 taken two per step
+    if ((256 % x) || ((y % 64) && y != 32)) return false;
+    F.lda = I8, F.am = axis_identity(B);
+    F.a_elems = (long)B * I8, F.b_elems = (long)O * I8;
+    F.ldc = O;
+    F.M = B, F.N = O;
+  } else if (op == 1) {
+    if ((256 % y) || ((x % 64) && x != 32)) return false;
+    F.lda = O8, F.am = axis_identity(B);
+    F.a_elems = (long)B * O8, F.b_elems = (long)O8 * I8;
+    F.ldc = I;
+    F.M = B, F.N = I;
+  } else {
+    if ((256 % x) || (256 % y) || (x % 8) || (y % 8)) return false;
+    F.lda = O8;
+    F.a_elems = (long)B * O8, F.b_elems = (long)B * I8;
+    F.k = axis_identity(B);
+    F.ldc = I;
+    F.c_rows_mapped = 1;
+    F.M = O, F.N = I;
+  }
+  auto count = [&](int bm, int bn, int& heavy) { return count_classes(op, t, B, bm, bn, heavy); };
+  // Tile choice by estimated time: rounds of workgroups over the chip x contraction steps x the time one
+  // round of one step takes with that tile.  A period that does not divide the tile grid leaves classes of
+  // 21 or 13 tile rows: wide tiles then end in a mostly empty block and the workgroup count lands just above
+  // a multiple of the CU count (288 for dp = 3), which smaller tiles avoid.  Round times (us) measured on
+  // the dense 4096^3 product per tile and operand layout; an 8-wavefront tile has one slot per CU, a
+  // 4-wavefront tile two.
+  static const float kRoundUs[3][5] = {{2.21f, 1.33f, 1.32f, 0.79f, 0.464f},   // forward (both operands contraction-contiguous)
+                                       {2.04f, 1.19f, 1.17f, 0.70f, 0.43f},    // data gradient
+                                       {1.98f, 1.14f, 1.16f, 0.66f, 0.44f}};   // weight gradient
+  int steps = op == 2 ? ceil_div(B, 64) : 0;
+  if (op != 2)
+    for (int c = 0; c < t.ncls; ++c) steps = imax(steps, ceil_div(t.k_cnt[c] * t.k_bs, 64));
+  int heavy = 0, bm = 0, bn = 0, total = 0;
+  float best = 0.0f;
+  for (int ci = 0; ci < 5; ++ci) {
+    const TileCfg& c = kTileCfgs[ci];
+    if ((c.bn % t.n_bs) || (op == 2 && (c.bm % x))) continue;
+    if (dev_knobs().class_tile && ci != dev_knobs().class_tile - 1) continue;
+    if (relu_src && c.bm == 256 && c.bn == 256) continue;  // (that tile only stores plain results)
+    int h = 0;
+    const int tot = count(c.bm, c.bn, h);
+    if (tot == 0) continue;
+    const int slots = c.bm * c.bn >= 256 * 128 ? 256 : 512;
+    const float est = (float)ceil_div(h > 0 ? h : 1, slots) * (float)steps * kRoundUs[op][ci];
+    if (bm == 0 || est < best) best = est, bm = c.bm, bn = c.bn;
+  }
+  if (bm == 0) return false;
+  total = count(bm, bn, heavy);
+  if (total == 0) return false;
+  if (copy_a || copy_b) {
+    PackArgs pa{};
+    int n = 0, blocks = 0;
+    size_t used = 0;
+    auto add = [&](const void* src, int rows, int cols) -> const uint16_t* {
+      void* const dst = (char*)ws + used;
+      used += align_up((size_t)pad8(rows) * pad8(cols) * 2, 256);
+      pa.job[n] = CompactWArgs{src, dst, cols, axis_identity(rows), axis_identity(cols)};
+      pa.gx[n] = ceil_div(pad8(cols), 256);
+      if (n == 0) pa.split = pa.gx[0] * ceil_div(pad8(rows), kCwRows);
+      blocks += pa.gx[n] * ceil_div(pad8(rows), kCwRows);
+      ++n;
+      return (const uint16_t*)dst;
+    };
+    if (copy_a) Ap = add(Ap, B, op == 0 ? I : O);
+    if (copy_b) Bp = add(Bp, op == 2 ? B : O, I);
+    if (!ws || ((uintptr_t)ws & 15) || used > ws_bytes) return false;  // (the general engine copes with the originals)
+    BatchSuspend now;  // the product of this very call reads the copies
+    ARD_LAUNCH(pack_operands_kernel<uint16_t>, dim3((unsigned)blocks), dim3(256), 0, stream, pa);
+    const hipError_t e = ard::launch_status();
+    if (e != hipSuccess) {
+      st = fail(ARD_EHIP, "launch of pack_operands_kernel failed: %s", hipGetErrorString(e));
+      return true;
+    }
+  }
+  F.A = (const uint16_t*)Ap, F.B = (const uint16_t*)Bp;
+  // (however few tiles there are, this path wins: the general engine's block-list products take 2-3x as
+  // long even on a batch of 128 rows)
+  F.alpha = alpha;
+  F.relu = relu;
+  F.relu_src = (const uint16_t*)relu_src;
+  F.total_tiles = total;
+  // (a kernel that a grouped launch holds is issued later and without the zeros' workgroups)
+  const bool grouped = batch_open() && bn == 64 && bm <= 128;
+  if (op == 2 && !grouped && I % 8 == 0 && y % 8 == 0 && ((uintptr_t)Cp & 15) == 0) {
+    F.zt = ZeroTilesJob{ceil_div(O, kZeroTileRows), O, I, TC, dp, o, fast_div((uint32_t)x), fast_div((uint32_t)y / 8), fast_div((uint32_t)I / 8)};
+  } else if (op == 2) {
+    ARD_LAUNCH(zero_dropped_tiles_kernel<uint16_t>, dim3((unsigned)(TR * TC)), dim3(256), 0, stream, (uint16_t*)Cp, I, O, I,
+                       x, y, TC, dp, o);
+    hipError_t e = ard::launch_status();
+    if (e != hipSuccess) {
+      st = fail(ARD_EHIP, "launch of zero_dropped_tiles_kernel failed: %s", hipGetErrorString(e));
+      return true;
+    }
+  }
+  F.splits = 1;
+  st = launch_direct(op != 2, op == 0, F, bm, bn, stream);
+  return true;
 }
 
 static int32_t compact_weight(int32_t dtype, int I, const void* W, void* Wc, const Axis& ao, const Axis& ai,
@@ -974,8 +1007,14 @@ extern "C" size_t ard_gemm_workspace_bytes(int32_t dtype, int32_t B, int32_t I, 
                                            const ard_pattern* pat_in) {
   (void)B;
   if (I <= 0 || O <= 0) return 0;
-  if (pat_out && pat_out->kind == ARD_PAT_TILE && pat_out->tile_r > 0 && pat_out->tile_c > 0)
-    return tile_ws_bytes(ceil_div(O, pat_out->tile_r), ceil_div(I, pat_out->tile_c));
+  if (pat_out && pat_out->kind == ARD_PAT_TILE && pat_out->tile_r > 0 && pat_out->tile_c > 0) {
+    // the tile lists of the general engine, or copies of bf16 operands with padded rows (two of W, X and dY at a time)
+    const size_t lists = tile_ws_bytes(ceil_div(O, pat_out->tile_r), ceil_div(I, pat_out->tile_c));
+    if (dtype != ARD_BF16 || (I % 8 == 0 && O % 8 == 0) || B <= 0) return lists;
+    auto copy = [](int rows, int cols) { return align_up((size_t)pad8(rows) * pad8(cols) * 2, 256); };
+    const size_t w = copy(O, I), x = copy(B, I), dy = copy(B, O), least = w < x ? (w < dy ? w : dy) : (x < dy ? x : dy);
+    return lists > w + x + dy - least ? lists : w + x + dy - least;
+  }
   // compact copies of the operands that may need one (plan_packs), then room for fp32 partial results of up to 8
   // contraction splits
   const size_t Ok = (size_t)kept_count(pat_out, O), Ik = (size_t)kept_count(pat_in, I), Bn = B > 0 ? (size_t)B : 0;
@@ -1246,7 +1285,8 @@ extern "C" int32_t ard_drop_gemm_bwd_weight_static(int32_t dtype, int32_t B, int
   LayerArgs a{dtype, B, I, O, pat_out, pat_in, false, 0, 0};
   int32_t st = check_layer(a, dY, X, dW);
   if (st) return st;
-  const size_t need = ard_gemm_workspace_bytes(dtype, B, I, O, pat_out, pat_in);
+  // (copies of a tile pattern's operands are made where they fit)
+  const size_t need = a.tile ? tile_ws_bytes(a.TR, a.TC) : ard_gemm_workspace_bytes(dtype, B, I, O, pat_out, pat_in);
   if (need > kStaticScratchBytes)
     return fail(ARD_EWORKSPACE,
                 "ard_drop_gemm_bwd_weight_static: this layer asks for %zu bytes of scratch (ard_gemm_workspace_bytes), the "

@@ -72,6 +72,20 @@ def test_random_layers_and_tile_patterns():
         assert D.last_bounds(lib)[0] > 100
 
 
+def test_ragged_tile_patterns():
+    """Copies with padded rows: every remainder of either side modulo 8, extents below, at and beyond whole tiles."""
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        for i in range(48):
+            I, O = 61 + i % 8 + 96 * (i % 5), 57 + i // 3 % 8 + 64 * (i % 7)
+            x, y = ((32, 32), (64, 64), (32, 64), (128, 64))[i % 4]
+            dp = 1 + i % min(8, -(-O // x) * -(-I // y))
+            _ok(lib, D.layer_calls(lib, heap, D.BF16, 1 + 37 * (i % 11), I, O, (dp, 1 + i % dp), None, 0, tile=(x, y)), f"ragged {I} {O} {x}x{y} {dp}")
+            _, names = D.launches(lib)
+            assert "gemm_direct_kernel" in names and "gemm_kernel" not in names, names
+        assert D.last_bounds(lib)[0] > 48
+
+
 def test_the_shape_that_faulted_once():
     """W 2480 x 2760 with 256-row tiles: the last tile row holds 176 rows (block axes are clamped)."""
     with D.dry_run() as lib:
