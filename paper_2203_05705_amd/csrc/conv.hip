@@ -15,6 +15,7 @@
 #include <stdlib.h>
 
 #include "engine.hpp"
+#include "conv_blocks.hpp"
 #include "conv_scatter.hpp"
 #include "pattern.hpp"
 
@@ -1472,6 +1473,14 @@ static PosListJob pos_list_job(const ConvArgs& a, const uint8_t* blk, int x, int
   return j;
 }
 
+// Whether the forward pass under a block pattern can run over tiles that end anywhere in a band (conv_blocks.hpp).  (Bands
+// below 12 positions and layers below 320 stay with the engines that tests/test_host_bounds.py pins them to.)
+static bool block_masked_ok(const ConvArgs& a, const ConvWs& w) {
+  const int taps = a.kh * a.kw, CG = pad64(a.C) / 64;
+  return a.bx >= 12 && a.N * a.Ho * a.Wo >= 320 && w.grid_a && !dev_knobs().no_fast && a.by % (64 * taps) == 0 && CG <= 32 && taps * CG <= 128 && a.kh <= 15 && a.kw <= 15 &&
+         (long)ceil_div(a.N * a.Ho * a.Wo, 128) * ceil_div(a.Cout, 64) < (1L << 24);
+}
+
 // The column tile (128 or 256 positions) that wastes the least padding, or 0 when this path does not apply.
 static int block_fast_tile(const ConvArgs& a, const ConvWs& w) {
   const int taps = a.kh * a.kw;
@@ -1490,8 +1499,36 @@ static int block_fast_tile(const ConvArgs& a, const ConvWs& w) {
   }
   if (!best) return 0;
   const long tiles = (long)a.N * best_len / best;
+  // (fewer workgroups than CUs, each a whole CU's: the smaller tiles of conv_blocks.hpp are faster.  Training steps of drawn
+  // layers, us, these against those: 44 workgroups 126 and 101, 150 73 and 69, 210 211 and 204, 308 257 and 264, 448 178 and
+  // 190, 1344 379 and 426)
+  if (tiles * ceil_div(a.Cout, best == 128 || a.Cout > 128 ? 256 : 128) < 256 && hw * a.N >= 512 && block_masked_ok(a, w)) return 0;
   if ((size_t)(a.N * best_len) > w.blk_ints || (size_t)(tiles * taps * CG) > w.blk_ints || tiles >= (1L << 22)) return 0;
   return best;
+}
+
+// (see block_masked_ok)
+static int32_t conv_block_fwd(const ConvArgs& a, int Cp, int Hg, int Wg, const ConvWs& w, void* out, hipStream_t stream) {
+  BlockFwdParams P{};
+  const int taps = a.kh * a.kw;
+  P.W = w.gwp, P.grid = w.grid_a, P.Y = (uint16_t*)out, P.blk = a.blk;
+  P.ldw = taps * Cp, P.Cp = Cp, P.CG = Cp / 64, P.kh = a.kh, P.kw = a.kw;
+  P.HW = a.Ho * a.Wo, P.W_ = a.Wo, P.Cout = a.Cout, P.npix = a.N * P.HW, P.HgWg = Hg * Wg, P.Wg = Wg;
+  P.RB = ceil_div(P.HW, a.bx), P.CB = ceil_div(a.C * taps, a.by), P.x = a.bx, P.cg_per_blk = imin(a.by / (64 * taps), 32);
+  P.mt = ceil_div(a.Cout, 64), P.total = ceil_div(P.npix, 128) * P.mt;
+  P.width = 2;
+  for (int m = 16; m > 2 && P.width == 2; m /= 2)
+    if (P.HW % (m / 2) == 0 && (uintptr_t)out % m == 0) P.width = m;
+  P.by_mt = fast_div((uint32_t)P.mt), P.by_hw = fast_div((uint32_t)P.HW), P.by_w = fast_div((uint32_t)P.W_), P.by_x = fast_div((uint32_t)a.bx);
+  // (a lane's last read: the last output position's patch, the last tap of it, inside the grid; rows of W: Cout of them)
+  static thread_local bool raised = false;
+  if (!raised) {
+    ARD_HIP_CHECK(raise_lds_limit((const void*)conv_block_fwd_kernel, kBfLds));
+    raised = !dry_run();
+  }
+  ARD_LAUNCH(conv_block_fwd_kernel, dim3((unsigned)(ceil_div(P.total, 8) * 8)), dim3(256), kBfLds, stream, P);
+  ARD_LAUNCH_CHECK("conv_block_fwd_kernel");
+  return ARD_OK;
 }
 
 // Whether the data gradient runs over the kept positions (conv_scatter.hpp): planes whose rows fit in LDS, filters that
@@ -1572,7 +1609,9 @@ static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, c
     int bn = 0;
     if (a.blk) {
       bn = block_fast_tile(a, w);
-      if (!bn) return fail(ARD_EUNSUPPORTED, "block pattern outside the fast path");  // (callers test block_fast_tile first)
+      if (!bn && !block_masked_ok(a, w)) return fail(ARD_EUNSUPPORTED, "block pattern outside the fast path");  // (callers test both first)
+    }
+    if (bn) {
       bj.p = BlockPlan{a.N, a.Ho * a.Wo, a.bx, ceil_div(a.Ho * a.Wo, a.bx), ceil_div(a.C * taps, a.by), ceil_div(a.bx, bn), bn, taps,
                        Cp / 64, a.by / (64 * taps), taps * (Cp / 64)};
       bj.blk = a.blk;
@@ -1593,6 +1632,7 @@ static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, c
       }
     }
     if (st) return st;
+    if (a.blk && !bn) return conv_block_fwd(a, Cp, Hg, Wg, w, out, stream);
     if (a.blk) {
       const BlockPlan& bp = bj.p;
       const int tiles = bj.tiles;
@@ -1876,7 +1916,7 @@ static int32_t conv_run(const ConvArgs& a, double rate, const void* A, const voi
     }
   }
   if (Ck > 0 && w.grid_a && a.mode >= ARD_CONV_FWD && a.mode <= ARD_CONV_BWD_WEIGHT && !dev_knobs().no_fast &&
-      (!a.blk || (a.mode == ARD_CONV_FWD && block_fast_tile(a, w)))) {
+      (!a.blk || (a.mode == ARD_CONV_FWD && (block_fast_tile(a, w) || block_masked_ok(a, w))))) {
     if (a.mode == ARD_CONV_FWD && (!A || !Wt)) return fail(ARD_EINVAL, "FWD needs A and Wt");
     if (a.mode == ARD_CONV_BWD_DATA && (!dYin || !Wt)) return fail(ARD_EINVAL, "BWD_DATA needs dYin and Wt");
     if (a.mode == ARD_CONV_BWD_WEIGHT && (!dYin || !A)) return fail(ARD_EINVAL, "BWD_WEIGHT needs dYin and A");

@@ -1,0 +1,33 @@
+"""GPU parity of the forward pass under the block pattern on tiles of 128 positions that end anywhere in a band (bf16,
+stride 1, blocks of whole 64-channel groups), at the sizes where its kernel changes branch: a tile that is not full, tiles over
+several images, one output channel and several tiles of 64, one and several groups, a last group that is not full, more
+than 64 contraction steps, no kept block at all, planes stored 16, 8, 4 and 2 bytes at a time, paddings that shrink and
+grow the image."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sensitivity as S
+from paper_2203_05705_amd import binding as ard
+from util import assert_parity, from_vals, stored
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,C,Cout,H,W,k,pad,x,groups,p", [
+    (1, 64, 1, 16, 20, 3, 1, 12, 1, 0.5), (7, 64, 16, 7, 7, 3, 1, 12, 1, 0.5), (11, 128, 65, 7, 7, 3, 1, 49, 1, 0.3), (3, 192, 130, 13, 13, 3, 1, 13, 2, 0.4),
+    (2, 448, 40, 14, 14, 3, 1, 28, 1, 0.3), (2, 320, 24, 16, 16, 5, 2, 100, 1, 0.3), (3, 100, 72, 12, 12, 3, 1, 17, 1, 0.5), (7, 128, 200, 9, 10, 3, 0, 16, 1, 0.5),
+    (3, 64, 33, 8, 12, 3, 2, 20, 1, 0.6), (4, 128, 64, 16, 16, 1, 0, 32, 1, 0.5), (2, 128, 64, 16, 16, 3, 1, 32, 1, 0.0), (2, 128, 64, 16, 16, 3, 1, 32, 1, 1.0),
+    (30, 64, 100, 5, 5, 3, 1, 25, 1, 0.4)])
+def test_forward(N, C, Cout, H, W, k, pad, x, groups, p):
+    print("blocks forward", N, C, Cout, H, W, k, pad, x, groups, p, flush=True)
+    rng = np.random.default_rng(C + H + Cout)
+    A, Wt = (stored(rng.standard_normal(s) * 0.5, "bf16") for s in ((N, C, H, W), (Cout, C, k, k)))
+    Ad, Wd = from_vals(A, "bf16"), from_vals(Wt, "bf16")
+    y = 64 * groups * k * k
+    _, RB, CB = ard.sens_regions(A.shape, (k, k), 1, pad, x, y)
+    keep = (rng.uniform(size=(N, RB, CB)) < p).astype(np.uint8)
+    kd = torch.from_numpy(keep.reshape(-1)).cuda()
+    Y = ard.conv_fwd_blocks(Ad, Wd, kd, x, y, 1, pad)
+    assert_parity(Y, S.conv_fwd_blocks(A, Wt, keep, x, y, 1, pad), "bf16", None, "Y")
+    assert torch.equal(Y, ard.conv_fwd_blocks(Ad, Wd, kd, x, y, 1, pad))
