@@ -689,8 +689,9 @@ static PackPlan plan_packs(int op, int32_t dtype, int B, int I, int O, const voi
     auto ragged = [](const void* q, int ld) { return (ld % 8) != 0 || ((uintptr_t)q & 15) != 0; };
     p.x = need_x && (!is_identity(ai) || ragged(X, I));
     p.dy = need_dy && (!is_identity(ao) || ragged(dY, O));
-    // (the data gradient contracts over the output neurons: with a compact dY its weight has to be compact too)
-    p.w = need_w && (!is_identity(ai) || ragged(W, I) || (op == 1 && !is_identity(ao)));
+    // (the data gradient contracts over the output neurons: with a compact dY, or one padded to 8 columns, its weight has to
+    // be compact too, with the rows that go with the padding; 919 x 22 by 22 x 3392 on the general engine 75 us)
+    p.w = need_w && (!is_identity(ai) || ragged(W, I) || (op == 1 && (!is_identity(ao) || ao.n % 8)));
     return p;
   }
   // fp32 kernels take any map themselves: a copy only pays where strided loads would be repeated often enough
@@ -1021,7 +1022,7 @@ extern "C" size_t ard_gemm_workspace_bytes(int32_t dtype, int32_t B, int32_t I, 
   const size_t es = dtype == ARD_BF16 ? 2 : 4;
   const bool bf = dtype == ARD_BF16, po = pat_out && pat_out->kind != ARD_PAT_NONE, pi = pat_in && pat_in->kind != ARD_PAT_NONE;
   size_t bytes = 0;
-  if (pi || (bf && (po || I % 8))) bytes += align_up((size_t)pad8((int)Ok) * pad8((int)Ik) * es, 256);
+  if (pi || (bf && (po || I % 8 || O % 8))) bytes += align_up((size_t)pad8((int)Ok) * pad8((int)Ik) * es, 256);
   if (po || (bf && O % 8)) bytes += align_up((size_t)pad8((int)Bn) * pad8((int)Ok) * es, 256);
   if (pi || (bf && I % 8)) bytes += align_up((size_t)pad8((int)Bn) * pad8((int)Ik) * es, 256);
   const size_t Okp = pad8((int)Ok), Ikp = pad8((int)Ik);

@@ -180,3 +180,15 @@ def test_relu_bwd_kernel():
     dYv, Yv = stored(rng.standard_normal(1000), "bf16"), stored(rng.standard_normal(1000), "bf16")
     out = ard.relu_bwd(from_vals(dYv, "bf16"), from_vals(Yv, "bf16"))
     assert_parity(out, G.relu_bwd(dYv, Yv), "bf16", zero_mask=(Yv <= 0), what="relu_bwd")
+
+
+@pytest.mark.parametrize("B,I,O,pi,out_c", [(919, 3392, 22, None, False), (40, 128, 33, None, True), (130, 72, 129, None, False), (64, 264, 100, (1, 1), True)])
+def test_data_gradient_of_a_dense_layer_with_ragged_outputs(B, I, O, pi, out_c):
+    """No pattern on the outputs and no multiple of 8 of them: dY is padded (here or by the caller) and W gets rows to match."""
+    rng = np.random.default_rng(O)
+    Wv, dYv = stored(rng.standard_normal((O, I)), "bf16"), stored(rng.standard_normal((B, O)), "bf16")
+    W, dY = from_vals(Wv, "bf16"), from_vals(dYv, "bf16")
+    dX = torch.full((B, I), float("nan"), dtype=torch.bfloat16, device="cuda")
+    pat = ard.Pattern.row(*pi) if pi else None
+    ard.drop_gemm_bwd_data(ard.pad_compact(dY) if out_c else dY, W, None, pat, flags=ard.OUT_COMPACT if out_c else 0, I=I, O=O, out=dX)
+    assert_parity(dX, G.drop_gemm_bwd_data(dYv, Wv, np.ones((O, I)), np.ones(O, np.uint8)), "bf16", what="dX")
