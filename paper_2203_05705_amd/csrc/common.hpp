@@ -66,6 +66,16 @@ struct BatchSuspend {
   ~BatchSuspend();
 };
 
+// An entry point that takes no part in its caller's batch, but has a few products of its own that do not depend on
+// each other: what is recorded while one lives is its own, whatever the caller has recorded; launch() issues it.
+struct BatchOwn {
+  BatchOwn();
+  ~BatchOwn();
+  int32_t launch(hipStream_t stream);
+  struct Saved;
+  Saved* saved;
+};
+
 // ---- index maps -------------------------------------------------------------
 // A logical (compact) index j in [0, n) maps to a physical index in [0, nphys):
 //   AFFINE  off + j*step          (row pattern: off = b-1, step = dp; identity: 0, 1)

@@ -870,6 +870,18 @@ BatchSuspend::~BatchSuspend() {
   g_batch.open = was_open;
   --g_batch.suspended;
 }
+struct BatchOwn::Saved {
+  Batch b;
+};
+BatchOwn::BatchOwn() : saved(new Saved) {
+  std::swap(saved->b, g_batch);
+  g_batch.open = true;
+}
+BatchOwn::~BatchOwn() {
+  std::swap(saved->b, g_batch);
+  delete saved;
+}
+int32_t BatchOwn::launch(hipStream_t stream) { return ard_batch_launch(stream); }
 bool batch_self_begin() {
   if (g_batch.open || g_batch.suspended > 0 || !g_batch.items.empty()) return false;
   g_batch.open = true;

@@ -1200,7 +1200,8 @@ struct LstmWs {
   float* dc_next;  // [B x H]
   char* dwx;     // [4Hp x Ip] dtype
   char* dwh;     // [4Hp x Hp] dtype
-  char* part;    // fp32 partial sums of split products
+  char* part;    // fp32 partial sums of split products: three regions of part_bytes (the products at the end of the
+                 // backward pass run together)
   size_t part_bytes;
   int* sync;     // step counters (one per batch block of 32 rows) and the give-up flag of the one-launch recurrence
   size_t total;
@@ -1236,7 +1237,7 @@ static LstmWs lstm_ws_layout(char* base, int es, int T, int B, int I, int H, int
   if ((size_t)B * 4 * Hp > big) big = (size_t)B * 4 * Hp;
   w.part_bytes = big * 4 * 8;
   if (w.part_bytes > ((size_t)256 << 20)) w.part_bytes = (size_t)256 << 20;
-  w.part = take(w.part_bytes);
+  w.part = take(3 * align_up(w.part_bytes, 256));
   w.sync = (int*)take(((size_t)pad8(Hk) / 8 * ((size_t)B / 32 + 1) + 8 + kLxBlocks * kLxSeats) * 4);
   w.total = off;
   return w;
@@ -1654,34 +1655,37 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     }
   }
   {
-    // dx[T*B x I] = dG . Wx'
-    void* dxo = Ip != I ? (void*)w.dxp : dx;
-    GemmParams P = plain_gemm(dG, 4 * Hp, w.wxc, Ip, dxo, Ip, T_ * B, Ip, 4 * Hp, true, false, ce, false, 0.0f);
-    st = run_gemm(a.dtype, true, false, P, 0, 0, stream, w.part, w.part_bytes);
-    if (st) return st;
-    if (Ip != I) {
-      const long rows_total = (long)T_ * B;
-      for (long r0 = 0; r0 < rows_total; r0 += 65535) {
-        const long rows = rows_total - r0 < 65535 ? rows_total - r0 : 65535;
-        ARD_LAUNCH(lstm_copy_rows_kernel<T>, dim3(ceil_div(I, 256), (unsigned)rows), dim3(256), 0, stream,
-                           (const T*)w.dxp + r0 * Ip, (long)Ip, I, (long)I, (T*)dx + r0 * I);
-        ARD_LAUNCH_CHECK("lstm_copy_rows_kernel");
-      }
-    }
-  }
-  {
-    // compact weight gradients: dwx[4Hp x I] = dG^T . x, dwh[4Hp x Hp] = dG[1:]^T . h[kept][:-1]
-    GemmParams P = plain_gemm(dG, 4 * Hp, xs, Ip, w.dwx, Ip, 4 * Hp, Ip, T_ * B, false, false, ce, false, 0.0f);
-    st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part, w.part_bytes);
-    if (st) return st;
+    // dx[T*B x I] = dG . Wx', and the compact weight gradients dwx[4Hp x I] = dG^T . x, dwh[4Hp x Hp] = dG[1:]^T . h[kept][:-1]:
+    // none needs another's result, so the bf16 ones of 64 x 64 tiles share a launch, each with partial sums of its own.
+    // One after the other, each left CUs idle in its last round, or had fewer tiles than there are CUs (T = 64, B = 128,
+    // I = H = 1024, dp = 2: 512 tiles, then 256, of 128 steps each).
+    BatchOwn together;
+    const size_t region = align_up(w.part_bytes, 256);
     if (T_ > 1) {
-      P = plain_gemm(dG + (long)B * 4 * Hp, 4 * Hp, w.hc, Hp, w.dwh, Hp, 4 * Hp, Hp, (T_ - 1) * B, false, false, ce, false,
-                     0.0f);
+      GemmParams P = plain_gemm(dG + (long)B * 4 * Hp, 4 * Hp, w.hc, Hp, w.dwh, Hp, 4 * Hp, Hp, (T_ - 1) * B, false, false, ce, false, 0.0f);
       st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part, w.part_bytes);
     } else {
       st = fill_matrix(a.dtype, w.dwh, (long)4 * Hp * Hp, 0.0f, stream);
     }
     if (st) return st;
+    GemmParams P = plain_gemm(dG, 4 * Hp, xs, Ip, w.dwx, Ip, 4 * Hp, Ip, T_ * B, false, false, ce, false, 0.0f);
+    st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part + region, w.part_bytes);
+    if (st) return st;
+    void* dxo = Ip != I ? (void*)w.dxp : dx;
+    P = plain_gemm(dG, 4 * Hp, w.wxc, Ip, dxo, Ip, T_ * B, Ip, 4 * Hp, true, false, ce, false, 0.0f);
+    st = run_gemm(a.dtype, true, false, P, 0, 0, stream, w.part + 2 * region, w.part_bytes);
+    if (st) return st;
+    st = together.launch(stream);
+    if (st) return st;
+  }
+  if (Ip != I) {
+    const long rows_total = (long)T_ * B;
+    for (long r0 = 0; r0 < rows_total; r0 += 65535) {
+      const long rows = rows_total - r0 < 65535 ? rows_total - r0 : 65535;
+      ARD_LAUNCH(lstm_copy_rows_kernel<T>, dim3(ceil_div(I, 256), (unsigned)rows), dim3(256), 0, stream,
+                         (const T*)w.dxp + r0 * Ip, (long)Ip, I, (long)I, (T*)dx + r0 * I);
+      ARD_LAUNCH_CHECK("lstm_copy_rows_kernel");
+    }
   }
   const int chunks = (I + H + 7) / 8, step = lstm_rows_per_launch(chunks);
   for (int p0 = 0, p1; p0 < 4 * H; p0 = p1) {
