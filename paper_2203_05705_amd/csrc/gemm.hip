@@ -13,6 +13,7 @@
 #include "fast.hpp"
 #include "pattern.hpp"
 #include "skinny.hpp"
+#include "small.hpp"
 
 namespace ard {
 
@@ -705,6 +706,82 @@ static PackPlan plan_packs(int op, int32_t dtype, int B, int I, int O, const voi
   return p;
 }
 
+// Small bf16 products in the caller's layout: one launch of small.hpp in the place of copies, product and finishing pass.
+// op 0: p0 = X, p1 = W; 1: dY, W; 2: dY, X.
+static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0, const void* p1, void* out, float alpha, float beta, int relu,
+                      const void* relu_src, const void* ws, size_t ws_bytes, hipStream_t stream, int32_t& st) {
+  if (a.dtype != ARD_BF16 || dev_knobs().no_fast || flags || beta != 0.0f) return false;
+  const Axis ao = axis_of_pattern(a.po, a.O), ai = axis_of_pattern(a.pi, a.I), b = axis_identity(a.B);
+  auto affine = [](const Axis& x) { return x.kind == AX_AFFINE && x.n >= 1 && x.step >= 1 && x.off >= 0 && x.off < x.step; };
+  if (!affine(ao) || !affine(ai)) return false;
+  const Axis& m = op == 2 ? ao : b;
+  const Axis& n = op == 0 ? ao : ai;
+  const Axis& k = op == 0 ? ai : op == 1 ? ao : b;
+  // only what would not have been one launch without it
+  const PackPlan plan = plan_packs(op, a.dtype, a.B, a.I, a.O, op == 0 ? p0 : p1, p1, p0, ao, ai, flags);
+  if (!plan.x && !plan.w && !plan.dy && is_identity(m) && is_identity(n)) return false;
+  const int tiles_m = ceil_div(m.n, 32), tiles_n = ceil_div(n.n, 32);
+  const long tiles = (long)tiles_m * tiles_n;
+  // (wide loads start at 4-byte boundaries)
+  const bool aligned = ((uintptr_t)p0 & 3) == 0 && (op != 0 || ((uintptr_t)p1 & 3) == 0);
+  const int wide = op != 2 && k.step <= 4 && aligned ? k.step : 0;
+  // What it takes grows with the slices a CU fetches one after the other, 0.15 to 0.25 us each, more where the loads are
+  // narrow or mostly gaps; the other way takes 8 to 10 us with one launch beside the product's, 11 to 16 with two, more
+  // only for long weight gradients.  Measured on 90 drawn layers of 16..4096 in every direction: below these lines 1.1
+  // to 3 times as fast (16 x 66 by 66 x 768, 8 and 4: 11.5 -> 4.2 us; 832 x 282 by 282 x 229: 21.1 -> 15.7), above them
+  // 0.4 to 1.3 times (48 x 3520 by 3520 x 502: 12.6 -> 27.6; 730 x 685 by 1344, two wide: 12.7 -> 44).
+  const int ks = ceil_div(k.n, 32);
+  const double weight = op == 2 ? 0.8 : op == 0 ? (wide == 1 || wide == 2 ? 1.0 : 1.6) : wide == 0 ? 1.8 : wide == 4 ? 1.2 : 1.0;
+  const bool copies = op == 0 ? plan.x || plan.w : op == 2 || !is_identity(ai);
+  if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000) return false;
+  if ((long)a.B * a.I >= (1L << 30) || (long)a.B * a.O >= (1L << 30) || (long)a.O * a.I >= (1L << 30)) return false;
+  // (room for the gathered weight is part of the contract of a call with an input pattern)
+  const size_t need = op != 2 && !is_identity(ai) ? (size_t)pad8(ao.n) * pad8(ai.n) * 2 : 0;
+  if (need && (!ws || ws_bytes < need)) return false;
+  SmallArgs P{};
+  P.A = (const uint16_t*)p0;
+  P.B = (const uint16_t*)p1;
+  P.C = (uint16_t*)out;
+  P.gate = (const uint16_t*)relu_src;
+  P.lda = op == 0 ? a.I : a.O;
+  P.ldb = a.I;
+  P.ldc = op == 0 ? a.O : a.I;
+  P.M = m.n, P.N = n.n, P.K = k.n;
+  P.am_off = m.off, P.am_step = m.step;
+  P.bn_off = n.off, P.bn_step = n.step;
+  P.k_off = k.off, P.k_step = k.step;
+  P.rm_off = m.off, P.rm_step = m.step, P.rows = m.nphys;
+  P.cn_off = n.off, P.cn_step = n.step, P.cols = n.nphys;
+  // (a wide load fetches the gaps behind its last element too: they have to lie in the row)
+  P.full = wide ? (k.nphys - k.off) / (32 * k.step) : k.n / 32;
+  P.alpha = alpha;
+  P.relu = relu;
+  P.vec = P.ldc % 8 == 0 && ((uintptr_t)out & 15) == 0;
+  P.tiles_m = tiles_m, P.tiles_n = tiles_n;
+  // (eight wavefronts halve the chain of a long contraction; with at most one slice a wavefront four leave room for another
+  // workgroup: 540 tiles of three slices 6.6 us against 8.6)
+  const unsigned threads = tiles > 256 && ks <= 4 ? 256 : 512;
+  auto launch = [&](auto kernel) { ARD_LAUNCH_NAMED("gemm_small_kernel", kernel, dim3((unsigned)tiles), dim3(threads), 0, stream, P); };
+  if (op == 0) {
+    if (wide == 1) launch(gemm_small_kernel<true, true, 1, 1>);
+    else if (wide == 2) launch(gemm_small_kernel<true, true, 2, 2>);
+    else if (wide == 3) launch(gemm_small_kernel<true, true, 3, 3>);
+    else if (wide == 4) launch(gemm_small_kernel<true, true, 4, 4>);
+    else launch(gemm_small_kernel<true, true, 0, 0>);
+  } else if (op == 1) {
+    if (wide == 1) launch(gemm_small_kernel<true, false, 1, 0>);
+    else if (wide == 2) launch(gemm_small_kernel<true, false, 2, 0>);
+    else if (wide == 3) launch(gemm_small_kernel<true, false, 3, 0>);
+    else if (wide == 4) launch(gemm_small_kernel<true, false, 4, 0>);
+    else launch(gemm_small_kernel<true, false, 0, 0>);
+  } else {
+    launch(gemm_small_kernel<false, false, 0, 0>);
+  }
+  const hipError_t err = ard::launch_status();
+  if (err != hipSuccess) st = fail(ARD_EHIP, "launch of gemm_small_kernel failed: %s", hipGetErrorString(err));
+  return true;
+}
+
 static int32_t resolve_row_layer(const LayerArgs& a, int op, int32_t flags, const void* X, const void* W, const void* dY, void* ws,
                                  size_t ws_bytes, hipStream_t stream, RowLayer& L) {
   if (flags & ~(ARD_IN_COMPACT | ARD_OUT_COMPACT | ARD_W_COMPACT | ARD_DW_COMPACT))
@@ -1087,6 +1164,7 @@ extern "C" int32_t ard_drop_gemm_fwd(int32_t dtype, int32_t B, int32_t I, int32_
     if (!(flags & ~kLayoutFlags) && try_skinny(0, dtype, B, I, O, X, W, Y, axis_of_pattern(pat_out, O), axis_of_pattern(pat_in, I),
                                                flags, alpha, 0.0f, fuse_relu != 0, nullptr, stream, &st))
       return st;
+    if (try_small(0, a, flags, X, W, Y, alpha, 0.0f, fuse_relu != 0, nullptr, ws, ws_bytes, stream, st)) return st;
     RowLayer L;
     st = resolve_row_layer(a, 0, flags, X, W, nullptr, ws, ws_bytes, stream, L);
     if (st) return st;
@@ -1156,6 +1234,7 @@ extern "C" int32_t ard_drop_gemm_bwd_data(int32_t dtype, int32_t B, int32_t I, i
     if (!(flags & ~kLayoutFlags) && try_skinny(1, dtype, B, I, O, dY, W, dX, axis_of_pattern(pat_out, O), axis_of_pattern(pat_in, I),
                                                flags, alpha, 0.0f, 0, relu_src, stream, &st))
       return st;
+    if (try_small(1, a, flags, dY, W, dX, alpha, 0.0f, 0, relu_src, ws, ws_bytes, stream, st)) return st;
     RowLayer L;
     st = resolve_row_layer(a, 1, flags, nullptr, W, dY, ws, ws_bytes, stream, L);
     if (st) return st;
@@ -1223,6 +1302,7 @@ extern "C" int32_t ard_drop_gemm_bwd_weight(int32_t dtype, int32_t B, int32_t I,
     if (!(flags & ~kLayoutFlags) && try_skinny(2, dtype, B, I, O, dY, X, dW, axis_of_pattern(pat_out, O), axis_of_pattern(pat_in, I),
                                                flags, alpha, beta, 0, nullptr, stream, &st))
       return st;
+    if (try_small(2, a, flags, dY, X, dW, alpha, beta, 0, nullptr, ws, ws_bytes, stream, st)) return st;
     RowLayer L;
     st = resolve_row_layer(a, 2, flags, X, nullptr, dY, ws, ws_bytes, stream, L);
     if (st) return st;

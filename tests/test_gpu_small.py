@@ -1,0 +1,93 @@
+"""GPU parity of the small bf16 products in the caller's own layout: sizes around the 32 x 32 tiles, the slices of 32 and the
+wavefronts' shares of the contraction, every step the wide loads know and one they do not, odd row starts, operands at odd and at
+2-byte aligned addresses, values that are not finite next to the clamped rows and the clamped end of the contraction."""
+import numpy as np
+import pytest
+import torch
+
+from dryrun import FakeHeap, dry_run, launches, layer_calls
+from oracle import gemm as G
+from oracle import patterns as P
+from paper_2203_05705_amd import binding as ard
+from util import assert_parity, from_vals, stored
+
+SIZES = [(1, 1, 1), (31, 33, 65), (32, 64, 96), (33, 66, 131), (64, 255, 100), (17, 379, 317), (130, 77, 290), (257, 130, 67)]
+STEPS = [(1, 1), (2, 1), (1, 2), (3, 3), (4, 2), (2, 4), (5, 3), (8, 8), (9, 5)]
+
+
+def _layer(B, I, O, skew=0):
+    rng = np.random.default_rng(7 * B + 3 * I + O)
+    vals = [stored(rng.standard_normal(s), "bf16") for s in ((B, I), (O, I), (B, O))]
+    dev = [from_vals(v, "bf16") for v in vals]
+    if skew:
+        moved = [torch.empty(t.numel() + skew, dtype=t.dtype, device="cuda") for t in dev]
+        dev = [m[skew:].view(t.shape).copy_(t) for m, t in zip(moved, dev)]
+    return vals, dev
+
+
+def _guarded(shape, skew):
+    """NaN-filled output inside a buffer of sevens, `skew` elements from an aligned address."""
+    n = int(np.prod(shape))
+    buf = torch.full((64 + n + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = buf[64 + skew:64 + skew + n]
+    out.fill_(float("nan"))
+    return buf, out.view(shape), (64 + skew, n)
+
+
+def _intact(buf, at, n):
+    return bool((buf[:at] == 7).all()) and bool((buf[at + n:] == 7).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("skew", [0, 1, 2])
+@pytest.mark.parametrize("dp,dp_in", STEPS)
+@pytest.mark.parametrize("B,I,O", SIZES)
+def test_small_layers(B, I, O, dp, dp_in, skew):
+    print("small layer", B, I, O, dp, dp_in, skew, flush=True)
+    dp, dp_in = min(dp, O), min(dp_in, I)
+    (Xv, Wv, dYv), (X, W, dY) = _layer(B, I, O, skew)
+    for b, b_in in {(1, 1), (dp, dp_in)}:
+        mo, mi = P.row_mask(O, dp, b), P.row_mask(I, dp_in, b_in)
+        MW = G.weight_mask_rows(mo, mi)
+        po, pi = ard.Pattern.row(dp, b), ard.Pattern.row(dp_in, b_in) if dp_in > 1 else None
+        (by, Y, ay), (bx, dX, ax), (bw, dW, aw) = (_guarded(s, skew) for s in ((B, O), (B, I), (O, I)))
+        ard.drop_gemm_fwd(X, W, po, pi, alpha=0.5, relu=True, out=Y)
+        ard.drop_gemm_bwd_data(dY, W, po, pi, relu_src=X, out=dX)
+        ard.drop_gemm_bwd_weight(dY, X, po, pi, out=dW)
+        assert _intact(by, *ay) and _intact(bx, *ax) and _intact(bw, *aw)
+        assert_parity(Y, np.maximum(G.drop_gemm_fwd(Xv, Wv, MW, mo, 0.5), 0), "bf16", (mo == 0)[None, :], "Y")
+        assert_parity(dX, G.drop_gemm_bwd_data(dYv, Wv, MW, mo) * (Xv > 0), "bf16", (mi == 0)[None, :], "dX")
+        assert_parity(dW, G.drop_gemm_bwd_weight(dYv, Xv, MW, mo), "bf16", MW == 0, "dW")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_dropped_and_last_elements_that_are_not_finite(bad):
+    """What is dropped reaches no kept result, and the last row reaches its own results only."""
+    B, I, O, dp, dp_in = 33, 131, 70, 3, 2
+    (Xv, Wv, dYv), (X, W, dY) = _layer(B, I, O)
+    po, pi = ard.Pattern.row(dp, 2), ard.Pattern.row(dp_in, 1)
+    mo, mi = P.row_mask(O, dp, 2), P.row_mask(I, dp_in, 1)
+    MW = G.weight_mask_rows(mo, mi)
+    X[:, torch.from_numpy(mi == 0).cuda()] = bad
+    dY[:, torch.from_numpy(mo == 0).cuda()] = bad
+    W[torch.from_numpy(MW == 0).cuda()] = bad
+    X[B - 1, I - 1], dY[B - 1, 1] = bad, bad
+    Y = ard.drop_gemm_fwd(X, W, po, pi)
+    dX = ard.drop_gemm_bwd_data(dY, W, po, pi)
+    assert_parity(Y[:B - 1], G.drop_gemm_fwd(Xv, Wv, MW, mo)[:B - 1], "bf16", (mo == 0)[None, :], "Y")
+    assert_parity(dX[:B - 1], G.drop_gemm_bwd_data(dYv, Wv, MW, mo)[:B - 1], "bf16", (mi == 0)[None, :], "dX")
+    assert not torch.isfinite(Y[B - 1, torch.from_numpy(mo == 1).cuda()]).any()
+    assert not torch.isfinite(dX[B - 1, torch.from_numpy(mi == 1).cuda()]).any()
+    assert bool((dX[:, torch.from_numpy(mi == 0).cuda()] == 0).all())
+
+
+def test_small_layers_take_one_launch_a_product():
+    with dry_run() as lib:
+        for B, I, O, po, pi in ((64, 100, 130, (2, 1), (3, 2)), (33, 1024, 513, (8, 8), (2, 1))):
+            launches(lib)
+            assert layer_calls(lib, FakeHeap(), ard.BF16, B, I, O, po, pi, 0) == [0, 0, 0]
+            n, names = launches(lib)
+            assert names[-3:] == ["gemm_small_kernel"] * 3, names
+        # without the room that a call with an input pattern asks for it is refused as ever
+        assert layer_calls(lib, FakeHeap(), ard.BF16, 64, 100, 130, (2, 1), (3, 2), 0, ws_bytes=16, ops=(0,)) != [0]
