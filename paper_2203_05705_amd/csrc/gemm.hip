@@ -710,50 +710,62 @@ static PackPlan plan_packs(int op, int32_t dtype, int B, int I, int O, const voi
 // op 0: p0 = X, p1 = W; 1: dY, W; 2: dY, X.
 static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0, const void* p1, void* out, float alpha, float beta, int relu,
                       const void* relu_src, const void* ws, size_t ws_bytes, hipStream_t stream, int32_t& st) {
-  if (a.dtype != ARD_BF16 || dev_knobs().no_fast || flags || beta != 0.0f) return false;
+  if (a.dtype != ARD_BF16 || dev_knobs().no_fast || (flags & ~(ARD_IN_COMPACT | ARD_OUT_COMPACT | ARD_W_COMPACT)) || beta != 0.0f) return false;
   const Axis ao = axis_of_pattern(a.po, a.O), ai = axis_of_pattern(a.pi, a.I), b = axis_identity(a.B);
   auto affine = [](const Axis& x) { return x.kind == AX_AFFINE && x.n >= 1 && x.step >= 1 && x.off >= 0 && x.off < x.step; };
   if (!affine(ao) || !affine(ai)) return false;
-  const Axis& m = op == 2 ? ao : b;
-  const Axis& n = op == 0 ? ao : ai;
-  const Axis& k = op == 0 ? ai : op == 1 ? ao : b;
+  const bool in_c = flags & ARD_IN_COMPACT, out_c = flags & ARD_OUT_COMPACT, w_c = flags & ARD_W_COMPACT;
+  // kept neurons as the activations, the weight and the gradient of the weight hold them
+  auto held = [](const Axis& x, bool compact) { return compact ? axis_affine(0, 1, x.n, pad8(x.n)) : x; };
+  const Axis xi = held(ai, in_c), yo = held(ao, out_c), wi = held(ai, w_c), wo = held(ao, w_c);
+  const Axis &am = op == 2 ? yo : b, &bn = op == 0 ? wo : op == 1 ? wi : xi;    // rows of A, columns of B
+  const Axis &ka = op == 0 ? xi : op == 1 ? yo : b, &kb = op == 0 ? wi : op == 1 ? wo : b;
+  const Axis &m = op == 2 ? ao : b, &n = op == 0 ? yo : op == 1 ? xi : ai;  // rows and columns of C
+  // (a hidden layer between compact activations gives the very bits it gives with its weight compacted beforehand)
+  if (op != 2 && (in_c || out_c) && !is_identity(ao) && !is_identity(ai)) return false;
   // only what would not have been one launch without it
   const PackPlan plan = plan_packs(op, a.dtype, a.B, a.I, a.O, op == 0 ? p0 : p1, p1, p0, ao, ai, flags);
-  if (!plan.x && !plan.w && !plan.dy && is_identity(m) && is_identity(n)) return false;
+  auto dense = [](const Axis& x) { return x.off == 0 && x.step == 1; };
+  if (!plan.x && !plan.w && !plan.dy && dense(m) && dense(n)) return false;
   const int tiles_m = ceil_div(m.n, 32), tiles_n = ceil_div(n.n, 32);
   const long tiles = (long)tiles_m * tiles_n;
   // (wide loads start at 4-byte boundaries)
   const bool aligned = ((uintptr_t)p0 & 3) == 0 && (op != 0 || ((uintptr_t)p1 & 3) == 0);
-  const int wide = op != 2 && k.step <= 4 && aligned ? k.step : 0;
+  const int sa = op != 2 && ka.step <= 4 && aligned ? ka.step : 0, sb = op == 0 && kb.step <= 4 && aligned ? kb.step : 0;
+  const int wide = op == 0 && (sb != sa || sb == 0) && sa != 1 ? 0 : op == 0 ? sb : sa;  // (of the operand with more gaps)
   // What it takes grows with the slices a CU fetches one after the other, 0.15 to 0.25 us each, more where the loads are
   // narrow or mostly gaps; the other way takes 8 to 10 us with one launch beside the product's, 11 to 16 with two, more
   // only for long weight gradients.  Measured on 90 drawn layers of 16..4096 in every direction: below these lines 1.1
   // to 3 times as fast (16 x 66 by 66 x 768, 8 and 4: 11.5 -> 4.2 us; 832 x 282 by 282 x 229: 21.1 -> 15.7), above them
   // 0.4 to 1.3 times (48 x 3520 by 3520 x 502: 12.6 -> 27.6; 730 x 685 by 1344, two wide: 12.7 -> 44).
-  const int ks = ceil_div(k.n, 32);
+  const int ks = ceil_div(ka.n, 32);
   const double weight = op == 2 ? 0.8 : op == 0 ? (wide == 1 || wide == 2 ? 1.0 : 1.6) : wide == 0 ? 1.8 : wide == 4 ? 1.2 : 1.0;
-  const bool copies = op == 0 ? plan.x || plan.w : op == 2 || !is_identity(ai);
+  const bool copies = op == 0 ? plan.x || plan.w : op == 2 || plan.w;
   if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000) return false;
   if ((long)a.B * a.I >= (1L << 30) || (long)a.B * a.O >= (1L << 30) || (long)a.O * a.I >= (1L << 30)) return false;
   // (room for the gathered weight is part of the contract of a call with an input pattern)
-  const size_t need = op != 2 && !is_identity(ai) ? (size_t)pad8(ao.n) * pad8(ai.n) * 2 : 0;
+  const size_t need = op != 2 && !w_c && !is_identity(ai) ? (size_t)pad8(ao.n) * pad8(ai.n) * 2 : 0;
   if (need && (!ws || ws_bytes < need)) return false;
   SmallArgs P{};
   P.A = (const uint16_t*)p0;
   P.B = (const uint16_t*)p1;
   P.C = (uint16_t*)out;
   P.gate = (const uint16_t*)relu_src;
-  P.lda = op == 0 ? a.I : a.O;
-  P.ldb = a.I;
-  P.ldc = op == 0 ? a.O : a.I;
-  P.M = m.n, P.N = n.n, P.K = k.n;
-  P.am_off = m.off, P.am_step = m.step;
-  P.bn_off = n.off, P.bn_step = n.step;
-  P.k_off = k.off, P.k_step = k.step;
+  const int ld_x = in_c ? xi.nphys : a.I, ld_y = out_c ? yo.nphys : a.O, ld_w = w_c ? wi.nphys : a.I;
+  P.lda = op == 0 ? ld_x : ld_y;
+  P.ldb = op == 2 ? ld_x : ld_w;
+  P.ldc = op == 0 ? ld_y : op == 1 ? ld_x : a.I;
+  P.M = m.n, P.N = n.n, P.K = ka.n;
+  P.am_off = am.off, P.am_step = am.step;
+  P.bn_off = bn.off, P.bn_step = bn.step;
+  P.ka_off = ka.off, P.ka_step = ka.step;
+  P.kb_off = kb.off, P.kb_step = kb.step;
   P.rm_off = m.off, P.rm_step = m.step, P.rows = m.nphys;
   P.cn_off = n.off, P.cn_step = n.step, P.cols = n.nphys;
   // (a wide load fetches the gaps behind its last element too: they have to lie in the row)
-  P.full = wide ? (k.nphys - k.off) / (32 * k.step) : k.n / 32;
+  P.full = ka.n / 32;
+  if (sa && wide) P.full = imin(P.full, (ka.nphys - ka.off) / (32 * sa));
+  if (sb && wide) P.full = imin(P.full, (kb.nphys - kb.off) / (32 * sb));
   P.alpha = alpha;
   P.relu = relu;
   P.vec = P.ldc % 8 == 0 && ((uintptr_t)out & 15) == 0;
@@ -761,21 +773,26 @@ static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0,
   // (eight wavefronts halve the chain of a long contraction; with at most one slice a wavefront four leave room for another
   // workgroup: 540 tiles of three slices 6.6 us against 8.6)
   const unsigned threads = tiles > 256 && ks <= 4 ? 256 : 512;
-  auto launch = [&](auto kernel) { ARD_LAUNCH_NAMED("gemm_small_kernel", kernel, dim3((unsigned)tiles), dim3(threads), 0, stream, P); };
-  if (op == 0) {
-    if (wide == 1) launch(gemm_small_kernel<true, true, 1, 1>);
-    else if (wide == 2) launch(gemm_small_kernel<true, true, 2, 2>);
-    else if (wide == 3) launch(gemm_small_kernel<true, true, 3, 3>);
-    else if (wide == 4) launch(gemm_small_kernel<true, true, 4, 4>);
-    else launch(gemm_small_kernel<true, true, 0, 0>);
+  const unsigned t = (unsigned)tiles;
+  if (op == 0 && sa == 1) {
+    if (sb == 1) launch_small<true, true, 1, 1>(P, t, threads, stream);
+    else if (sb == 2) launch_small<true, true, 1, 2>(P, t, threads, stream);
+    else if (sb == 3) launch_small<true, true, 1, 3>(P, t, threads, stream);
+    else if (sb == 4) launch_small<true, true, 1, 4>(P, t, threads, stream);
+    else launch_small<true, true, 1, 0>(P, t, threads, stream);
+  } else if (op == 0) {
+    if (wide == 2) launch_small<true, true, 2, 2>(P, t, threads, stream);
+    else if (wide == 3) launch_small<true, true, 3, 3>(P, t, threads, stream);
+    else if (wide == 4) launch_small<true, true, 4, 4>(P, t, threads, stream);
+    else launch_small<true, true, 0, 0>(P, t, threads, stream);
   } else if (op == 1) {
-    if (wide == 1) launch(gemm_small_kernel<true, false, 1, 0>);
-    else if (wide == 2) launch(gemm_small_kernel<true, false, 2, 0>);
-    else if (wide == 3) launch(gemm_small_kernel<true, false, 3, 0>);
-    else if (wide == 4) launch(gemm_small_kernel<true, false, 4, 0>);
-    else launch(gemm_small_kernel<true, false, 0, 0>);
+    if (sa == 1) launch_small<true, false, 1, 0>(P, t, threads, stream);
+    else if (sa == 2) launch_small<true, false, 2, 0>(P, t, threads, stream);
+    else if (sa == 3) launch_small<true, false, 3, 0>(P, t, threads, stream);
+    else if (sa == 4) launch_small<true, false, 4, 0>(P, t, threads, stream);
+    else launch_small<true, false, 0, 0>(P, t, threads, stream);
   } else {
-    launch(gemm_small_kernel<false, false, 0, 0>);
+    launch_small<false, false, 0, 0>(P, t, threads, stream);
   }
   const hipError_t err = ard::launch_status();
   if (err != hipSuccess) st = fail(ARD_EHIP, "launch of gemm_small_kernel failed: %s", hipGetErrorString(err));
@@ -912,6 +929,27 @@ __global__ __launch_bounds__(256, 2) void group_kernel(const GroupTable table_in
     case GK_SKINNY_BWD_WEIGHT:
       skinny_bwd_weight_body(*reinterpret_cast<const SkinnyArgs*>(arg), local, group_lds);
       break;
+    case GK_SMALL_KK + 0:
+      small_body<true, true, 1, 0, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
+      break;
+    case GK_SMALL_KK + 1:
+      small_body<true, true, 1, 1, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
+      break;
+    case GK_SMALL_KK + 2:
+      small_body<true, true, 1, 2, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
+      break;
+    case GK_SMALL_KK + 3:
+      small_body<true, true, 1, 3, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
+      break;
+    case GK_SMALL_KK + 4:
+      small_body<true, true, 1, 4, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
+      break;
+    case GK_SMALL_KM:
+      small_body<true, false, 1, 0, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
+      break;
+    case GK_SMALL_MM:
+      small_body<false, false, 0, 0, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
+      break;
     case GK_COMPACT_W:
       compact_weight_body<uint16_t>(*reinterpret_cast<const CompactWArgs*>(arg), local % sg.gx, local / sg.gx);
       break;
@@ -990,6 +1028,7 @@ bool batch_push_zero_rows(const ZeroRowsArgs& a, int gx) { return batch_push(GK_
 static bool batch_push_skinny(int kind, const SkinnyArgs& a, int gx, int gy, size_t lds) {
   return batch_push(kind, 0, &a, sizeof(a), gx, gy, lds);
 }
+bool batch_push_small(int kind, const SmallArgs& a, int gx) { return batch_push(kind, 0, &a, sizeof(a), gx, 1, small_lds_bytes(8)); }
 static bool batch_push_compact_w(const CompactWArgs& a, int gx, int gy) { return batch_push(GK_COMPACT_W, 0, &a, sizeof(a), gx, gy, 0); }
 
 // one recorded launch by itself, exactly as it would have been issued without a batch
@@ -1012,6 +1051,27 @@ static int32_t launch_item_alone(const BatchItem& it, hipStream_t stream) {
       break;
     case GK_SKINNY_BWD_WEIGHT:
       ARD_LAUNCH(skinny_bwd_weight_kernel, grid, block, it.lds, stream, *reinterpret_cast<const SkinnyArgs*>(it.args));
+      break;
+    case GK_SMALL_KK + 0:
+      launch_small_alone<true, true, 1, 0>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
+      break;
+    case GK_SMALL_KK + 1:
+      launch_small_alone<true, true, 1, 1>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
+      break;
+    case GK_SMALL_KK + 2:
+      launch_small_alone<true, true, 1, 2>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
+      break;
+    case GK_SMALL_KK + 3:
+      launch_small_alone<true, true, 1, 3>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
+      break;
+    case GK_SMALL_KK + 4:
+      launch_small_alone<true, true, 1, 4>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
+      break;
+    case GK_SMALL_KM:
+      launch_small_alone<true, false, 1, 0>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
+      break;
+    case GK_SMALL_MM:
+      launch_small_alone<false, false, 0, 0>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
       break;
     case GK_COMPACT_W:
       ARD_LAUNCH(compact_weight_kernel<uint16_t>, grid, block, 0, stream, *reinterpret_cast<const CompactWArgs*>(it.args));

@@ -23,7 +23,7 @@ struct SmallArgs {
   int lda, ldb, ldc;
   int M, N, K;
   int am_off, am_step, bn_off, bn_step;  // kept row of C -> row of A, kept column of C -> row of B
-  int k_off, k_step;                     // contraction, of both operands
+  int ka_off, ka_step, kb_off, kb_step;  // contraction -> column (row, where it runs across) of A and of B
   int full;                              // slices of 32 that the wide loads may fetch whole
   int rm_off, rm_step, rows, cn_off, cn_step, cols;  // kept row / column -> C, and C's extents
   float alpha;
@@ -104,35 +104,41 @@ __device__ __forceinline__ bf16x8_t small_tail(const uint16_t* p, long kstride, 
   return small_value<0>(v);
 }
 
-// SA, SB: see SmallRaw.  A_KC, B_KC: the operand runs along the contraction.
-template <bool A_KC, bool B_KC, int SA, int SB>
-__global__ __launch_bounds__(512) void gemm_small_kernel(const SmallArgs P) {
-  __shared__ float red[8][32 * 33];
-  __shared__ uint16_t tile[32 * 34];
+// SA, SB: see SmallRaw.  A_KC, B_KC: the operand runs along the contraction.  Eight sums whatever the number of wavefronts,
+// sum v of slices v, v + 8, ..: a grouped launch, whose four wavefronts make SUMS = 2 of them each, gives the very bits of a
+// launch by itself.  (Four wavefronts with one sum each are right where there are no more than four slices: the
+// others would be zeros.)
+// lds: small_lds_bytes(sums)
+constexpr int kSmallRed = 32 * 33, kSmallTile = 32 * 34;
+constexpr size_t small_lds_bytes(int sums) { return (size_t)sums * kSmallRed * 4 + kSmallTile * 2; }
+template <bool A_KC, bool B_KC, int SA, int SB, int SUMS>
+__device__ __forceinline__ void small_body(const SmallArgs& P, const int block_id, const int threads, void* lds) {
+  uint16_t* const tile = (uint16_t*)lds;
+  float* const red = (float*)(tile + kSmallTile);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4;
-  const int threads = blockDim.x, waves = threads >> 6;  // 4 or 8
-  const int tm = blockIdx.x / P.tiles_n, tn = blockIdx.x - tm * P.tiles_n;
+  const int waves = threads >> 6;  // 4 or 8
+  const int tm = block_id / P.tiles_n, tn = block_id - tm * P.tiles_n;
   const int m0 = tm * 32, n0 = tn * 32;
   const uint16_t *pa[2], *pb[2];
-  const long ka = A_KC ? P.k_step : (long)P.k_step * P.lda, kb = B_KC ? P.k_step : (long)P.k_step * P.ldb;
+  const long ka = A_KC ? P.ka_step : (long)P.ka_step * P.lda, kb = B_KC ? P.kb_step : (long)P.kb_step * P.ldb;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     // (rows beyond the last are copies of it: their results are not stored)
     const long ra = P.am_off + (long)min(m0 + 16 * t + (lane & 15), P.M - 1) * P.am_step;
     const long rb = P.bn_off + (long)min(n0 + 16 * t + (lane & 15), P.N - 1) * P.bn_step;
-    pa[t] = P.A + (A_KC ? ra * P.lda + P.k_off : ra + (long)P.k_off * P.lda);
-    pb[t] = P.B + (B_KC ? rb * P.ldb + P.k_off : rb + (long)P.k_off * P.ldb);
+    pa[t] = P.A + (A_KC ? ra * P.lda + P.ka_off : ra + (long)P.ka_off * P.lda);
+    pb[t] = P.B + (B_KC ? rb * P.ldb + P.kb_off : rb + (long)P.kb_off * P.ldb);
   }
-  f32x4_t acc[2][2] = {};
-  auto multiply = [&](const bf16x8_t (&a)[2], const bf16x8_t (&b)[2]) {
+  f32x4_t acc[SUMS][2][2] = {};
+  auto multiply = [&](f32x4_t (&c)[2][2], const bf16x8_t (&a)[2], const bf16x8_t (&b)[2]) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < 2; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], c[i][j], 0, 0, 0);
   };
   // U slices under way at once, loads unconditional (behind branches every one would be waited for by itself)
-  auto slices = [&](auto count, int s) {
-    constexpr int U = decltype(count)::value;
+  auto slices = [&](auto count, auto first, int s) {
+    constexpr int U = decltype(count)::value, F = decltype(first)::value;
     SmallRaw<SA> va[U][2];
     SmallRaw<SB> vb[U][2];
 #pragma unroll
@@ -146,30 +152,36 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(const SmallArgs P) {
     for (int u = 0; u < U; ++u) {
       const bf16x8_t a[2] = {small_value<SA>(va[u][0]), small_value<SA>(va[u][1])};
       const bf16x8_t b[2] = {small_value<SB>(vb[u][0]), small_value<SB>(vb[u][1])};
-      multiply(a, b);
+      multiply(acc[(F + u) % SUMS], a, b);
     }
   };
   constexpr int U = SA == 1 && SB == 1 ? 4 : 2;
   int s = wave;
-  for (; s + (U - 1) * waves < P.full; s += U * waves) slices(std::integral_constant<int, U>{}, s);
-  for (; s < P.full; s += waves) slices(std::integral_constant<int, 1>{}, s);
+  for (; s + (U - 1) * waves < P.full; s += U * waves) slices(std::integral_constant<int, U>{}, std::integral_constant<int, 0>{}, s);
+  if (s < P.full) slices(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, s);
+  if (U > 2 && s + waves < P.full) slices(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}, s + waves);
+  if (U > 2 && s + 2 * waves < P.full) slices(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{}, s + 2 * waves);
   if (wave == P.full % waves && 32 * P.full < P.K) {
     const int k0 = 32 * P.full + 8 * g;
     const bf16x8_t a[2] = {small_tail(pa[0], ka, k0, P.K), small_tail(pa[1], ka, k0, P.K)};
     const bf16x8_t b[2] = {small_tail(pb[0], kb, k0, P.K), small_tail(pb[1], kb, k0, P.K)};
-    multiply(a, b);
+    if (SUMS == 2 && (P.full / waves) % 2) multiply(acc[SUMS - 1], a, b);
+    else multiply(acc[0], a, b);
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int v = 0; v < SUMS; ++v)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave][(16 * i + 4 * g + r) * 33 + 16 * j + (lane & 15)] = acc[i][j][r];
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[(wave + v * waves) * kSmallRed + (16 * i + 4 * g + r) * 33 + 16 * j + (lane & 15)] = acc[v][i][j][r];
   __syncthreads();
   for (int e = tid; e < 1024; e += threads) {
     const int r = e >> 5, c = e & 31;
-    float x = (red[0][r * 33 + c] + red[1][r * 33 + c]) + (red[2][r * 33 + c] + red[3][r * 33 + c]);
-    if (waves == 8) x += (red[4][r * 33 + c] + red[5][r * 33 + c]) + (red[6][r * 33 + c] + red[7][r * 33 + c]);
+    const float* const p = red + r * 33 + c;
+    float x = (p[0] + p[kSmallRed]) + (p[2 * kSmallRed] + p[3 * kSmallRed]);
+    x += waves * SUMS == 8 ? (p[4 * kSmallRed] + p[5 * kSmallRed]) + (p[6 * kSmallRed] + p[7 * kSmallRed]) : 0.0f;
     x *= P.alpha;
     if (P.relu) x = fmaxf(x, 0.0f);
     tile[r * 34 + c] = f32_to_bf16_bits(x);
@@ -209,6 +221,30 @@ __global__ __launch_bounds__(512) void gemm_small_kernel(const SmallArgs P) {
         if (c + e < c1) P.C[at + e] = (uint16_t)(v.w[e / 2] >> (16 * (e & 1)));
     }
   }
+}
+
+template <bool A_KC, bool B_KC, int SA, int SB>
+__global__ __launch_bounds__(512) void gemm_small_kernel(const SmallArgs P) {
+  __shared__ uint4 lds[small_lds_bytes(8) / 16 + 1];
+  small_body<A_KC, B_KC, SA, SB, 1>(P, (int)blockIdx.x, (int)blockDim.x, lds);
+}
+
+// What a grouped launch holds: products of compact activations with a weight in its own layout (GK_SMALL_KK + SB), with a
+// compact one, and weight gradients.
+enum { GK_SMALL_KK = 110, GK_SMALL_KM = 115, GK_SMALL_MM = 116 };
+bool batch_push_small(int kind, const SmallArgs& a, int gx);
+template <bool A_KC, bool B_KC, int SA, int SB> constexpr int small_group_kind() {
+  return !A_KC ? GK_SMALL_MM : SA != 1 ? -1 : B_KC ? GK_SMALL_KK + SB : GK_SMALL_KM;
+}
+template <bool A_KC, bool B_KC, int SA, int SB>
+static void launch_small_alone(const SmallArgs& P, unsigned tiles, unsigned threads, hipStream_t stream) {
+  ARD_LAUNCH_NAMED("gemm_small_kernel", (gemm_small_kernel<A_KC, B_KC, SA, SB>), dim3(tiles), dim3(threads), 0, stream, P);
+}
+template <bool A_KC, bool B_KC, int SA, int SB>
+static void launch_small(const SmallArgs& P, unsigned tiles, unsigned threads, hipStream_t stream) {
+  constexpr int gk = small_group_kind<A_KC, B_KC, SA, SB>();
+  if (gk >= 0 && batch_open() && batch_push_small(gk, P, (int)tiles)) return;
+  launch_small_alone<A_KC, B_KC, SA, SB>(P, tiles, threads, stream);
 }
 
 }  // namespace ard

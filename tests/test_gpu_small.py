@@ -91,3 +91,41 @@ def test_small_layers_take_one_launch_a_product():
             assert names[-3:] == ["gemm_small_kernel"] * 3, names
         # without the room that a call with an input pattern asks for it is refused as ever
         assert layer_calls(lib, FakeHeap(), ard.BF16, 64, 100, 130, (2, 1), (3, 2), 0, ws_bytes=16, ops=(0,)) != [0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("grouped", [False, True])
+@pytest.mark.parametrize("dp,dp_in", [(1, 1), (1, 3), (2, 2), (3, 1), (5, 4), (8, 6)])
+@pytest.mark.parametrize("B,I,O", [(1, 9, 17), (33, 131, 70), (64, 333, 113), (150, 1030, 40)])
+def test_compact_activations(B, I, O, dp, dp_in, grouped):
+    """Compact activations beside a weight in its own layout, or a compact one: alone and as one grid."""
+    print("small compact", B, I, O, dp, dp_in, grouped, flush=True)
+    (Xv, Wv, dYv), (X, W, dY) = _layer(B, I, O)
+    b, b_in = dp, (dp_in + 1) // 2
+    mo, mi = P.row_mask(O, dp, b), P.row_mask(I, dp_in, b_in)
+    MW = G.weight_mask_rows(mo, mi)
+    ko, ki = np.flatnonzero(mo), np.flatnonzero(mi)
+    po, pi = (ard.Pattern.row(dp, b) if dp > 1 else None), (ard.Pattern.row(dp_in, b_in) if dp_in > 1 else None)
+    Xc, dYc = ard.pad_compact(X[:, ki].contiguous()), ard.pad_compact(dY[:, ko].contiguous())
+    Wc = ard.compact_weight(W, po, pi)
+    ws = [torch.full((ard.gemm_workspace_bytes(ard.BF16, B, I, O, po, pi),), 0xFF, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    both = ard.IN_COMPACT | ard.OUT_COMPACT
+    (bw, dW, aw) = _guarded((O, I), 0)
+
+    def calls():
+        return (ard.drop_gemm_fwd(Xc, W, po, pi, relu=True, flags=both, I=I, O=O, ws=ws[0]),
+                ard.drop_gemm_bwd_data(dYc, W, po, pi, relu_src=Xc, flags=both, I=I, O=O, ws=ws[1]),
+                ard.drop_gemm_fwd(Xc, Wc, po, pi, flags=ard.IN_COMPACT | ard.W_COMPACT, I=I, O=O, ws=ws[2]),
+                ard.drop_gemm_bwd_weight(dYc, Xc, po, pi, flags=both, I=I, O=O, out=dW, ws=ws[3]))
+    if grouped:
+        with ard.batch():
+            Yc, dXc, Y, _ = calls()
+    else:
+        Yc, dXc, Y, _ = calls()
+    assert _intact(bw, *aw)
+    assert_parity(dW, G.drop_gemm_bwd_weight(dYv, Xv, MW, mo), "bf16", MW == 0, "dW")
+    Yr, dXr = G.drop_gemm_fwd(Xv, Wv, MW, mo), G.drop_gemm_bwd_data(dYv, Wv, MW, mo)
+    assert_parity(Yc[:, :len(ko)].contiguous(), np.maximum(Yr, 0)[:, ko], "bf16", None, "Y compact")
+    assert_parity(dXc[:, :len(ki)].contiguous(), (dXr * (Xv > 0))[:, ki], "bf16", None, "dX compact")
+    assert_parity(Y, Yr, "bf16", (mo == 0)[None, :], "Y")
+    assert not Yc[:, len(ko):].any() and not dXc[:, len(ki):].any()
