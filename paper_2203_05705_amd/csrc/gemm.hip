@@ -14,6 +14,7 @@
 #include "pattern.hpp"
 #include "skinny.hpp"
 #include "small.hpp"
+#include "group.hpp"
 
 namespace ard {
 
@@ -460,39 +461,6 @@ using namespace ard;
 
 namespace ard {
 
-// Wc[r][c] = W[out(r)][in(c)]; rows and columns up to the next multiple of 8 are zero
-struct CompactWArgs {
-  const void* W;
-  void* Wc;
-  long ld;
-  Axis ao, ai;
-};
-// a workgroup gathers kCwRows rows x 256 columns: a thread's loads of its rows are independent and in
-// flight together
-constexpr int kCwRows = 16;
-template <typename T>
-__device__ __forceinline__ void compact_weight_body(const CompactWArgs& a, const int bx, const int by) {
-  const int c = bx * 256 + threadIdx.x;
-  const int cols = pad8(a.ai.n), rows = pad8(a.ao.n);
-  if (c >= cols) return;
-  const T* W = reinterpret_cast<const T*>(a.W);
-  T* Wc = reinterpret_cast<T*>(a.Wc);
-  const bool c_ok = c < a.ai.n;
-  const long pc = c_ok ? ax_phys(a.ai, c) : 0;
-  T v[kCwRows];
-#pragma unroll
-  for (int i = 0; i < kCwRows; ++i) {
-    const int r = by * kCwRows + i;
-    const bool ok = c_ok && r < a.ao.n;
-    const T t = W[(long)(ok ? ax_phys(a.ao, r) : 0) * a.ld + pc];  // unconditional (clamped) load
-    v[i] = ok ? t : (T)0;
-  }
-#pragma unroll
-  for (int i = 0; i < kCwRows; ++i) {
-    const int r = by * kCwRows + i;
-    if (r < rows) Wc[(long)r * cols + c] = v[i];
-  }
-}
 template <typename T>
 __global__ __launch_bounds__(256) void compact_weight_kernel(const CompactWArgs a) {
   compact_weight_body<T>(a, (int)blockIdx.x, (int)blockIdx.y);
@@ -773,27 +741,9 @@ static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0,
   // (eight wavefronts halve the chain of a long contraction; with at most one slice a wavefront four leave room for another
   // workgroup: 540 tiles of three slices 6.6 us against 8.6)
   const unsigned threads = tiles > 256 && ks <= 4 ? 256 : 512;
-  const unsigned t = (unsigned)tiles;
-  if (op == 0 && sa == 1) {
-    if (sb == 1) launch_small<true, true, 1, 1>(P, t, threads, stream);
-    else if (sb == 2) launch_small<true, true, 1, 2>(P, t, threads, stream);
-    else if (sb == 3) launch_small<true, true, 1, 3>(P, t, threads, stream);
-    else if (sb == 4) launch_small<true, true, 1, 4>(P, t, threads, stream);
-    else launch_small<true, true, 1, 0>(P, t, threads, stream);
-  } else if (op == 0) {
-    if (wide == 2) launch_small<true, true, 2, 2>(P, t, threads, stream);
-    else if (wide == 3) launch_small<true, true, 3, 3>(P, t, threads, stream);
-    else if (wide == 4) launch_small<true, true, 4, 4>(P, t, threads, stream);
-    else launch_small<true, true, 0, 0>(P, t, threads, stream);
-  } else if (op == 1) {
-    if (sa == 1) launch_small<true, false, 1, 0>(P, t, threads, stream);
-    else if (sa == 2) launch_small<true, false, 2, 0>(P, t, threads, stream);
-    else if (sa == 3) launch_small<true, false, 3, 0>(P, t, threads, stream);
-    else if (sa == 4) launch_small<true, false, 4, 0>(P, t, threads, stream);
-    else launch_small<true, false, 0, 0>(P, t, threads, stream);
-  } else {
-    launch_small<false, false, 0, 0>(P, t, threads, stream);
-  }
+  const int kind = op == 2 ? GK_SMALL_MM : op == 1 ? GK_SMALL_KM + sa : sa == 1 ? GK_SMALL_K1 + sb : GK_SMALL_KK + wide;
+  const bool recorded = small_recorded(kind, [](auto) {}) && batch_open() && batch_push_small(kind, P, (int)tiles);
+  if (!recorded) launch_small_alone(kind, P, (unsigned)tiles, threads, stream);
   const hipError_t err = ard::launch_status();
   if (err != hipSuccess) st = fail(ARD_EHIP, "launch of gemm_small_kernel failed: %s", hipGetErrorString(err));
   return true;
@@ -870,99 +820,7 @@ static int32_t resolve_row_layer(const LayerArgs& a, int op, int32_t flags, cons
 }  // namespace ard
 
 
-// ---- grouped launches ----------------------------------------------------------------------------
-//
-// A training iteration of a small layer chain is a handful of products of a few microseconds each,
-// so what it costs is mostly the fixed part of every launch.  Calls that do not depend on each other
-// (the weight compaction and the first forward product; the three products of the classifier layer;
-// the weight and data gradients of a hidden layer) can be recorded and then issued as one grid of
-// group_kernel, which holds the bodies of every kernel such a chain uses (all run 256 threads per
-// workgroup); each workgroup looks up the segment of the grid it belongs to and runs that body.
 namespace ard {
-
-constexpr int kGroupMaxSeg = 6;
-constexpr int kGroupArgBytes = 3584;
-struct GroupSeg {
-  int kind;      // GK_*
-  int first;     // first workgroup of the segment (a multiple of 8: workgroup ids go round-robin over the XCDs)
-  int nblocks;   // gx * gy
-  int gx, gy;
-  int arg_off;   // byte offset of the body's argument struct in GroupTable::args
-};
-struct GroupTable {
-  int nseg;
-  GroupSeg seg[kGroupMaxSeg];
-  alignas(16) char args[kGroupArgBytes];
-};
-static_assert(sizeof(GroupTable) <= 4096, "kernel arguments are limited to 4 KiB");
-
-// (The table is read through the kernel-argument segment itself: indexing the by-value parameter with a
-// run-time segment number would make the compiler copy all of it into every lane's private memory.)
-__global__ __launch_bounds__(256, 2) void group_kernel(const GroupTable table_in_kernarg) {
-  extern __shared__ uint4 group_lds[];
-  const GroupTable& T = *(const GroupTable*)__builtin_amdgcn_kernarg_segment_ptr();
-  int s = 0;
-  while (s + 1 < T.nseg && (int)blockIdx.x >= T.seg[s + 1].first) ++s;
-  const GroupSeg sg = T.seg[s];
-  const int local = (int)blockIdx.x - sg.first;
-  if (local >= sg.nblocks) return;
-  const char* arg = T.args + sg.arg_off;
-  switch (sg.kind) {
-    case GK_DIRECT_KK_64:
-      direct_body<true, true, 64, 64, 4, 0>(*reinterpret_cast<const FastParams*>(arg), local, group_lds);
-      break;
-    case GK_DIRECT_KM_64:
-      direct_body<true, false, 64, 64, 4, 0>(*reinterpret_cast<const FastParams*>(arg), local, group_lds);
-      break;
-    case GK_DIRECT_MM_64:
-      direct_body<false, false, 64, 64, 4, 0>(*reinterpret_cast<const FastParams*>(arg), local, group_lds);
-      break;
-    case GK_DIRECT_MM_128x64:
-      direct_body<false, false, 128, 64, 4, 0>(*reinterpret_cast<const FastParams*>(arg), local, group_lds);
-      break;
-    case GK_SKINNY_FWD:
-      skinny_fwd_body(*reinterpret_cast<const SkinnyArgs*>(arg), local, group_lds);
-      break;
-    case GK_SKINNY_BWD_DATA:
-      skinny_bwd_data_body(*reinterpret_cast<const SkinnyArgs*>(arg), local % sg.gx, local / sg.gx, group_lds);
-      break;
-    case GK_SKINNY_BWD_WEIGHT:
-      skinny_bwd_weight_body(*reinterpret_cast<const SkinnyArgs*>(arg), local, group_lds);
-      break;
-    case GK_SMALL_KK + 0:
-      small_body<true, true, 1, 0, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
-      break;
-    case GK_SMALL_KK + 1:
-      small_body<true, true, 1, 1, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
-      break;
-    case GK_SMALL_KK + 2:
-      small_body<true, true, 1, 2, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
-      break;
-    case GK_SMALL_KK + 3:
-      small_body<true, true, 1, 3, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
-      break;
-    case GK_SMALL_KK + 4:
-      small_body<true, true, 1, 4, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
-      break;
-    case GK_SMALL_KM:
-      small_body<true, false, 1, 0, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
-      break;
-    case GK_SMALL_MM:
-      small_body<false, false, 0, 0, 2>(*reinterpret_cast<const SmallArgs*>(arg), local, 256, group_lds);
-      break;
-    case GK_COMPACT_W:
-      compact_weight_body<uint16_t>(*reinterpret_cast<const CompactWArgs*>(arg), local % sg.gx, local / sg.gx);
-      break;
-    case GK_FINISH_VEC:
-      finish_vec_body(*reinterpret_cast<const FinishArgs*>(arg), local % sg.gx, local / sg.gx, sg.gy);
-      break;
-    case GK_ZERO_ROWS:
-      zero_rows_body(*reinterpret_cast<const ZeroRowsArgs*>(arg), local, sg.nblocks);
-      break;
-    default:
-      break;
-  }
-}
 
 struct BatchItem {
   int kind, stage, gx, gy;
@@ -1025,7 +883,7 @@ bool batch_push_direct(int kind, const FastParams& F, int grid_x, size_t lds_byt
 }
 bool batch_push_finish(const FinishArgs& a, int gx, int gy) { return batch_push(GK_FINISH_VEC, 1, &a, sizeof(a), gx, gy, 0); }
 bool batch_push_zero_rows(const ZeroRowsArgs& a, int gx) { return batch_push(GK_ZERO_ROWS, 0, &a, sizeof(a), gx, 1, 0); }
-static bool batch_push_skinny(int kind, const SkinnyArgs& a, int gx, int gy, size_t lds) {
+bool batch_push_skinny(int kind, const SkinnyArgs& a, int gx, int gy, size_t lds) {
   return batch_push(kind, 0, &a, sizeof(a), gx, gy, lds);
 }
 bool batch_push_small(int kind, const SmallArgs& a, int gx) { return batch_push(kind, 0, &a, sizeof(a), gx, 1, small_lds_bytes(8)); }
@@ -1052,27 +910,6 @@ static int32_t launch_item_alone(const BatchItem& it, hipStream_t stream) {
     case GK_SKINNY_BWD_WEIGHT:
       ARD_LAUNCH(skinny_bwd_weight_kernel, grid, block, it.lds, stream, *reinterpret_cast<const SkinnyArgs*>(it.args));
       break;
-    case GK_SMALL_KK + 0:
-      launch_small_alone<true, true, 1, 0>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
-      break;
-    case GK_SMALL_KK + 1:
-      launch_small_alone<true, true, 1, 1>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
-      break;
-    case GK_SMALL_KK + 2:
-      launch_small_alone<true, true, 1, 2>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
-      break;
-    case GK_SMALL_KK + 3:
-      launch_small_alone<true, true, 1, 3>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
-      break;
-    case GK_SMALL_KK + 4:
-      launch_small_alone<true, true, 1, 4>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
-      break;
-    case GK_SMALL_KM:
-      launch_small_alone<true, false, 1, 0>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
-      break;
-    case GK_SMALL_MM:
-      launch_small_alone<false, false, 0, 0>(*reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
-      break;
     case GK_COMPACT_W:
       ARD_LAUNCH(compact_weight_kernel<uint16_t>, grid, block, 0, stream, *reinterpret_cast<const CompactWArgs*>(it.args));
       break;
@@ -1083,7 +920,8 @@ static int32_t launch_item_alone(const BatchItem& it, hipStream_t stream) {
       ARD_LAUNCH(zero_rows_kernel, grid, block, 0, stream, *reinterpret_cast<const ZeroRowsArgs*>(it.args));
       break;
     default:
-      return fail(ARD_EINVAL, "unknown recorded kernel kind %d", it.kind);
+      if (!small_kind(it.kind)) return fail(ARD_EINVAL, "unknown recorded kernel kind %d", it.kind);
+      launch_small_alone(it.kind, *reinterpret_cast<const SmallArgs*>(it.args), (unsigned)it.gx, 512, stream);
   }
   ARD_LAUNCH_CHECK("recorded kernel");
   return ARD_OK;
@@ -1096,12 +934,14 @@ static int32_t launch_stage(const std::vector<const BatchItem*>& items, hipStrea
     GroupTable T{};
     size_t lds = 0, arg_used = 0;
     int blocks = 0;
+    bool small = false;
     size_t j = i;
     for (; j < items.size() && T.nseg < kGroupMaxSeg; ++j) {
       const BatchItem& it = *items[j];
       const size_t a16 = align_up(it.arg_bytes, 16);
       if (arg_used + a16 > (size_t)kGroupArgBytes) break;
       GroupSeg& sg = T.seg[T.nseg++];
+      small = small || small_kind(it.kind);
       sg.kind = it.kind, sg.first = blocks, sg.gx = it.gx, sg.gy = it.gy, sg.nblocks = it.gx * it.gy;
       sg.arg_off = (int)arg_used;
       memcpy(T.args + arg_used, it.args, it.arg_bytes);
@@ -1114,11 +954,15 @@ static int32_t launch_stage(const std::vector<const BatchItem*>& items, hipStrea
     } else {
       static thread_local bool raised = false;
       if (!raised) {
-        ARD_HIP_CHECK(raise_lds_limit((const void*)group_kernel, 4096 + 16 * (SK_MAX_COLS + 16) * 2 + 256));
+        ARD_HIP_CHECK(raise_lds_limit((const void*)group_kernel<false>, kGroupMaxLds));
         raised = !dry_run();
       }
-      ARD_LAUNCH(group_kernel, dim3((unsigned)blocks), dim3(256), lds, stream, T);
-      ARD_LAUNCH_CHECK("group_kernel");
+      if (small) {
+        if (int32_t st = launch_group_small(T, blocks, lds, stream)) return st;
+      } else {
+        ARD_LAUNCH_NAMED("group_kernel", group_kernel<false>, dim3((unsigned)blocks), dim3(256), lds, stream, T);
+        ARD_LAUNCH_CHECK("group_kernel");
+      }
     }
     i = j;
   }

@@ -114,7 +114,7 @@ __device__ __forceinline__ void skinny_fwd_body(const SkinnyArgs& a, const int b
   const int orow = bx * 16 + m;
   if (orow < a.B && n < a.out_cols) a.out[(long)orow * a.ld_out + n] = n < a.O ? f32_to_bf16_bits(v) : (uint16_t)0;
 }
-__global__ __launch_bounds__(256) void skinny_fwd_kernel(const SkinnyArgs a) {
+static __global__ __launch_bounds__(256) void skinny_fwd_kernel(const SkinnyArgs a) {
   extern __shared__ uint4 sk_lds_fwd[];
   skinny_fwd_body(a, (int)blockIdx.x, sk_lds_fwd);
 }
@@ -201,7 +201,7 @@ __device__ __forceinline__ void skinny_bwd_data_body(const SkinnyArgs& a, const 
     *reinterpret_cast<uint4*>(a.out + (long)row * a.ld_out + j0) = o;
   }
 }
-__global__ __launch_bounds__(256) void skinny_bwd_data_kernel(const SkinnyArgs a) {
+static __global__ __launch_bounds__(256) void skinny_bwd_data_kernel(const SkinnyArgs a) {
   extern __shared__ uint4 sk_lds_bd[];
   skinny_bwd_data_body(a, (int)blockIdx.x, (int)blockIdx.y, sk_lds_bd);
 }
@@ -263,14 +263,14 @@ __device__ __forceinline__ void skinny_bwd_weight_body(const SkinnyArgs& a, cons
   }
   if (jj < a.Kk) orow[a.ki.off + jj * a.ki.step] = f32_to_bf16_bits(v);
 }
-__global__ __launch_bounds__(256) void skinny_bwd_weight_kernel(const SkinnyArgs a) {
+static __global__ __launch_bounds__(256) void skinny_bwd_weight_kernel(const SkinnyArgs a) {
   extern __shared__ uint4 sk_lds_bw[];
   skinny_bwd_weight_body(a, (int)blockIdx.x, sk_lds_bw);
 }
 
 enum { GK_SKINNY_FWD = 100, GK_SKINNY_BWD_DATA = 101, GK_SKINNY_BWD_WEIGHT = 102 };
 // records the launch in the open batch of this thread (gemm.hip); false: no batch is open, launch now
-static bool batch_push_skinny(int kind, const SkinnyArgs& a, int gx, int gy, size_t lds);
+bool batch_push_skinny(int kind, const SkinnyArgs& a, int gx, int gy, size_t lds);
 
 static bool sk_aligned(const void* p, long ld) { return ((uintptr_t)p & 15) == 0 && (ld % 8) == 0; }
 

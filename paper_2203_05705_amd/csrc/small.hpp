@@ -223,28 +223,29 @@ __device__ __forceinline__ void small_body(const SmallArgs& P, const int block_i
   }
 }
 
-template <bool A_KC, bool B_KC, int SA, int SB>
-__global__ __launch_bounds__(512) void gemm_small_kernel(const SmallArgs P) {
-  __shared__ uint4 lds[small_lds_bytes(8) / 16 + 1];
-  small_body<A_KC, B_KC, SA, SB, 1>(P, (int)blockIdx.x, (int)blockDim.x, lds);
+// The forms there are, by kind.  KK + S: both operands run along the contraction and keep every S-th element, K1 + S: A is
+// compact; KM + S: B runs across it (data gradients); MM: both do (weight gradients).  S = 0: any other step.
+enum { GK_SMALL_KK = 110, GK_SMALL_K1 = 115, GK_SMALL_KM = 120, GK_SMALL_MM = 125 };
+static inline bool small_kind(int kind) { return kind >= GK_SMALL_KK && kind <= GK_SMALL_MM; }
+template <bool A_KC, bool B_KC, int SA, int SB> struct SmallForm {
+  static constexpr bool a_kc = A_KC, b_kc = B_KC;
+  static constexpr int sa = SA, sb = SB;
+};
+// what a grouped launch holds: products of compact activations and weight gradients.  false: not among them
+template <class F> __host__ __device__ __forceinline__ bool small_recorded(int kind, const F& f) {
+  switch (kind) {
+    case GK_SMALL_K1 + 0: f(SmallForm<true, true, 1, 0>{}); return true;
+    case GK_SMALL_K1 + 1: f(SmallForm<true, true, 1, 1>{}); return true;
+    case GK_SMALL_K1 + 2: f(SmallForm<true, true, 1, 2>{}); return true;
+    case GK_SMALL_K1 + 3: f(SmallForm<true, true, 1, 3>{}); return true;
+    case GK_SMALL_K1 + 4: f(SmallForm<true, true, 1, 4>{}); return true;
+    case GK_SMALL_KM + 1: f(SmallForm<true, false, 1, 0>{}); return true;
+    case GK_SMALL_MM: f(SmallForm<false, false, 0, 0>{}); return true;
+    default: return false;
+  }
 }
-
-// What a grouped launch holds: products of compact activations with a weight in its own layout (GK_SMALL_KK + SB), with a
-// compact one, and weight gradients.
-enum { GK_SMALL_KK = 110, GK_SMALL_KM = 115, GK_SMALL_MM = 116 };
 bool batch_push_small(int kind, const SmallArgs& a, int gx);
-template <bool A_KC, bool B_KC, int SA, int SB> constexpr int small_group_kind() {
-  return !A_KC ? GK_SMALL_MM : SA != 1 ? -1 : B_KC ? GK_SMALL_KK + SB : GK_SMALL_KM;
-}
-template <bool A_KC, bool B_KC, int SA, int SB>
-static void launch_small_alone(const SmallArgs& P, unsigned tiles, unsigned threads, hipStream_t stream) {
-  ARD_LAUNCH_NAMED("gemm_small_kernel", (gemm_small_kernel<A_KC, B_KC, SA, SB>), dim3(tiles), dim3(threads), 0, stream, P);
-}
-template <bool A_KC, bool B_KC, int SA, int SB>
-static void launch_small(const SmallArgs& P, unsigned tiles, unsigned threads, hipStream_t stream) {
-  constexpr int gk = small_group_kind<A_KC, B_KC, SA, SB>();
-  if (gk >= 0 && batch_open() && batch_push_small(gk, P, (int)tiles)) return;
-  launch_small_alone<A_KC, B_KC, SA, SB>(P, tiles, threads, stream);
-}
+// (small.hip)
+void launch_small_alone(int kind, const SmallArgs& P, unsigned tiles, unsigned threads, hipStream_t stream);
 
 }  // namespace ard
