@@ -1556,14 +1556,7 @@ static int32_t conv_block_fwd(const ConvArgs& a, int Cp, int Hg, int Wg, const C
     if (P.HW % (m / 2) == 0 && (uintptr_t)out % m == 0) P.width = m;
   P.by_mt = fast_div((uint32_t)P.mt), P.by_hw = fast_div((uint32_t)P.HW), P.by_w = fast_div((uint32_t)P.W_), P.by_x = fast_div((uint32_t)a.bx);
   // (a lane's last read: the last output position's patch, the last tap of it, inside the grid; rows of W: Cout of them)
-  static thread_local bool raised = false;
-  if (!raised) {
-    ARD_HIP_CHECK(raise_lds_limit((const void*)conv_block_fwd_kernel, kBfLds));
-    raised = !dry_run();
-  }
-  ARD_LAUNCH(conv_block_fwd_kernel, dim3((unsigned)(ceil_div(P.total, 8) * 8)), dim3(256), kBfLds, stream, P);
-  ARD_LAUNCH_CHECK("conv_block_fwd_kernel");
-  return ARD_OK;
+  return launch_conv_block_fwd(P, stream);
 }
 
 // Whether the data gradient runs over the kept positions (conv_scatter.hpp): planes whose rows fit in LDS, filters that
@@ -1589,24 +1582,13 @@ static bool scatter_plan(const ConvArgs& a, const ConvWs& w, const BandMask& m, 
   P.by_w = fast_div((uint32_t)P.W_), P.by_x = fast_div((uint32_t)m.x), P.by_gpb = fast_div((uint32_t)(cpb / 16));
   return true;
 }
-template <int KS> static int32_t scatter_launch(const ScatterDataParams& P, hipStream_t stream) {
-  auto kernel = conv_scatter_data_kernel<KS>;
-  static thread_local bool raised = false;
-  if (!raised) {
-    ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, kSdMostLds));
-    raised = !dry_run();
-  }
-  ARD_LAUNCH_NAMED("conv_scatter_data_kernel", kernel, dim3((unsigned)(ceil_div(P.total, 8) * 8)), dim3(256), (size_t)P.lds_bytes, stream, P);
-  ARD_LAUNCH_CHECK("conv_scatter_data_kernel");
-  return ARD_OK;
-}
 static int32_t conv_scatter(ScatterDataParams P, int ks, const ConvWs& w, void* out, hipStream_t stream) {
   P.W = w.gwp, P.dA = (uint16_t*)out;
   const int start = P.bands > 1 ? P.rows * P.W_ : 0;  // (of a band in its plane)
   P.width = 2;
   for (int m = 16; m > 2 && P.width == 2; m /= 2)
     if (P.HW % (m / 2) == 0 && start % (m / 2) == 0 && (uintptr_t)out % m == 0) P.width = m;
-  return ks == 8 ? scatter_launch<8>(P, stream) : ks == 6 ? scatter_launch<6>(P, stream) : ks == 4 ? scatter_launch<4>(P, stream) : scatter_launch<2>(P, stream);
+  return launch_conv_scatter(ks, P, stream);
 }
 
 static int32_t conv_run_grid(const ConvArgs& a, const void* A, const void* Wt, const void* dYin, void* out,

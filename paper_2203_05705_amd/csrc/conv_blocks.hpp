@@ -30,7 +30,7 @@ struct BlockFwdParams {
 
 constexpr int kBfStages = 3, kBfLds = kBfStages * (64 + 128) * 128;
 
-__global__ __launch_bounds__(256, 2) void conv_block_fwd_kernel(const BlockFwdParams P) {
+static __global__ __launch_bounds__(256, 2) void conv_block_fwd_kernel(const BlockFwdParams P) {
   extern __shared__ uint4 bf_lds[];
   __shared__ unsigned any_s[4], all_s[4];
   constexpr int NST = kBfStages, OPA = 64 * LDS_ROW_U4, OPB = 128 * LDS_ROW_U4;
@@ -202,5 +202,8 @@ __global__ __launch_bounds__(256, 2) void conv_block_fwd_kernel(const BlockFwdPa
   else if (P.width == 4) store(uint32_t{});
   else store(uint16_t{});
 }
+
+// (conv_kept.hip)
+int32_t launch_conv_block_fwd(const BlockFwdParams& P, hipStream_t stream);
 
 }  // namespace ard

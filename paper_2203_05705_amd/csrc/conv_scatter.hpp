@@ -407,4 +407,7 @@ __global__ __launch_bounds__(256, 2) void conv_scatter_data_kernel(const Scatter
   else store(uint16_t{});
 }
 
+// (conv_kept.hip)
+int32_t launch_conv_scatter(int ks, const ScatterDataParams& P, hipStream_t stream);
+
 }  // namespace ard
