@@ -694,7 +694,16 @@ static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0,
   // only what would not have been one launch without it
   const PackPlan plan = plan_packs(op, a.dtype, a.B, a.I, a.O, op == 0 ? p0 : p1, p1, p0, ao, ai, flags);
   auto dense = [](const Axis& x) { return x.off == 0 && x.step == 1; };
-  if (!plan.x && !plan.w && !plan.dy && dense(m) && dense(n)) return false;
+  const bool packs = plan.x || plan.w || plan.dy;
+  if (!packs && dense(m) && dense(n)) return false;
+  // A weight gradient between compact activations is stored by its product, beside a pass for the dropped rows in the same
+  // launch, from four tiles of 64 x 64 on, or 64 where columns are dropped; and where a tile owns far more than it computes,
+  // the finishing pass spreads it over more CUs (44 rows, 1720 -> 3856 -> 256, every fifth and every eighth unit kept:
+  // training step 46.6 us, 56.7 with both weight gradients here; 72 rows, 1472 -> 648 -> 2368: 48.6, 52.7).
+  if (op == 2 && !packs) {
+    const int t64 = ceil_div(m.n, 64) * ceil_div(n.n, 64);
+    if (t64 >= (dense(n) ? 4 : 64) || m.step * n.step > 12) return false;
+  }
   const int tiles_m = ceil_div(m.n, 32), tiles_n = ceil_div(n.n, 32);
   const long tiles = (long)tiles_m * tiles_n;
   // (wide loads start at 4-byte boundaries)
@@ -710,6 +719,10 @@ static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0,
   const double weight = op == 2 ? 0.8 : op == 0 ? (wide == 1 || wide == 2 ? 1.0 : 1.6) : wide == 0 ? 1.8 : wide == 4 ? 1.2 : 1.0;
   const bool copies = op == 0 ? plan.x || plan.w : op == 2 || plan.w;
   if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000) return false;
+  // (results whose rows start anywhere leave in pieces that cross lines, which costs more than the copies where they are large:
+  // 44 rows, 1719 -> 3854, weight gradient, in a network's step of 63.5 us 1.5 us more; 45 rows, 3161 -> 1065 less)
+  const bool whole = (op == 0 ? yo.nphys : op == 1 ? xi.nphys : a.I) % 8 == 0 && ((uintptr_t)out & 15) == 0;
+  if (!whole && (long)m.nphys * n.nphys > (5L << 20)) return false;
   if ((long)a.B * a.I >= (1L << 30) || (long)a.B * a.O >= (1L << 30) || (long)a.O * a.I >= (1L << 30)) return false;
   // (room for the gathered weight is part of the contract of a call with an input pattern)
   const size_t need = op != 2 && !w_c && !is_identity(ai) ? (size_t)pad8(ao.n) * pad8(ai.n) * 2 : 0;
