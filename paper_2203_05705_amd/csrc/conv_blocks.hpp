@@ -155,6 +155,7 @@ static __global__ __launch_bounds__(256, 2) void conv_block_fwd_kernel(const Blo
   // Then the tile as bf16 [64 rows][128 positions] in LDS, from where whole runs of a channel plane leave.
   float4* const sum = reinterpret_cast<float4*>(lds);  // [wave][column tile][quarter][lane]
   uint32_t words[2][8];
+  bool nan = false;
 #pragma unroll
   for (int im = 0; im < 2; ++im) {
     __syncthreads();
@@ -173,6 +174,7 @@ static __global__ __launch_bounds__(256, 2) void conv_block_fwd_kernel(const Blo
         x.x += y.x, x.y += y.y, x.z += y.z, x.w += y.w;
       }
       words[im][2 * q] = pack_bf16x2(x.x, x.y), words[im][2 * q + 1] = pack_bf16x2(x.z, x.w);
+      nan |= __builtin_isunordered(x.x, x.y) | __builtin_isunordered(x.z, x.w);
     }
   }
   __syncthreads();
@@ -186,6 +188,34 @@ static __global__ __launch_bounds__(256, 2) void conv_block_fwd_kernel(const Blo
       tile[row * PITCH + col] = (uint16_t)words[im][v >> 1];
       tile[(row + 1) * PITCH + col] = (uint16_t)(words[im][v >> 1] >> 16);
     }
+  // Where a group is kept for some positions only, the others multiplied its weights by zeros, which a weight that is not
+  // finite makes NaN: such a result is summed again over the groups that its own position keeps.  (No finite sum had such a
+  // term: two comparisons for every four results are all that is paid for it.)
+  if (mixed && nan) {
+    const int col = wave * 32 + (lane & 31), q = imin(j0 + col, P.npix - 1);
+    const int n = (int)fdiv((uint32_t)q, P.by_hw), p = q - n * P.HW, h = (int)fdiv((uint32_t)p, P.by_w), w = p - h * P.W_;
+    const uint8_t* const m = P.blk + ((long)n * P.RB + (int)fdiv((uint32_t)p, P.by_x)) * P.CB;
+    const uint16_t* const at = P.grid + ((long)n * P.HgWg + h * P.Wg + w) * P.Cp;
+#pragma unroll 1
+    for (int i = 0; i < 32; ++i) {
+      const int row = (i >> 4) * 32 + 8 * ((i >> 2) & 3) + 4 * (lane >> 5) + (i & 3);
+      if ((tile[row * PITCH + col] & 0x7fff) <= 0x7f80 || row0 + row >= P.Cout) continue;
+      const uint16_t* const wr = P.W + (long)(row0 + row) * P.ldw;
+      float x = 0.0f;
+#pragma unroll 1
+      for (int cg = 0; cg < P.CG && x == x; ++cg) {
+        if (!m[cg / P.cg_per_blk]) continue;
+#pragma unroll 1
+        for (int t = 0; t < taps; ++t) {
+          const int r = t / P.kw, s = t - r * P.kw;
+#pragma unroll 1
+          for (int c = cg * 64; c < cg * 64 + 64; ++c)
+            x += bf16_bits_to_f32(wr[t * P.Cp + c]) * bf16_bits_to_f32(at[(long)(r * P.Wg + s) * P.Cp + c]);
+        }
+      }
+      tile[row * PITCH + col] = f32_to_bf16_bits(x);
+    }
+  }
   __syncthreads();
   // a thread takes E positions of a row: they lie in one plane (host: the planes are whole pieces)
   auto store = [&](auto unit) {

@@ -51,3 +51,32 @@ def test_forward_f32(N, C, Cout, H, W, k, pad, x, cpb, p):
     Ad[0, (CB - 1) * cpb:] = float("nan")
     Y = ard.conv_fwd_blocks(Ad, Wd, torch.from_numpy(keep.reshape(-1)).cuda(), x, y, 1, pad)
     assert_parity(Y, S.conv_fwd_blocks(A, Wt, keep, x, y, 1, pad), "f32", None, "Y")
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("N,C,Cout,H,W,x,groups", [
+    (4, 128, 140, 16, 16, 96, 1), (2, 128, 200, 14, 14, 49, 1), (3, 320, 130, 12, 13, 78, 2), (2, 192, 24, 13, 13, 13, 1), (5, 100, 72, 12, 12, 17, 1)])
+def test_weights_that_are_not_finite_stay_out_of_dropped_blocks(N, C, Cout, H, W, x, groups, bad):
+    """One weight of the second column block that is not finite reaches its output channel where a band keeps that block, and no
+    other; a channel all of whose weights are not finite is +0.0 where a band keeps nothing."""
+    print("blocks not finite", N, C, Cout, H, W, x, groups, bad, flush=True)
+    rng = np.random.default_rng(C + H + Cout)
+    A, Wt = (stored(rng.standard_normal(s) * 0.5, "bf16") for s in ((N, C, H, W), (Cout, C, 3, 3)))
+    y = 64 * groups * 9
+    _, RB, CB = ard.sens_regions(A.shape, (3, 3), 1, 1, x, y)
+    keep = (rng.uniform(size=(N, RB, CB)) < 0.5).astype(np.uint8)
+    keep[0, 0], keep[N - 1, RB - 1, 1] = 0, 1
+    Ad, Wd, kd = from_vals(A, "bf16"), from_vals(Wt, "bf16"), torch.from_numpy(keep.reshape(-1)).cuda()
+    clean = ard.conv_fwd_blocks(Ad, Wd, kd, x, y, 1, 1)
+    Wd[7, 64 * groups + 5, 1, 1] = bad
+    Wd[Cout - 1] = bad
+    Y = ard.conv_fwd_blocks(Ad, Wd, kd, x, y, 1, 1).reshape(N, Cout, H * W)
+    band = torch.arange(H * W, device="cuda") // x
+    kept = torch.from_numpy(keep).cuda().bool()[:, band]   # [N, H * W, CB]
+    clean, other = clean.reshape(N, Cout, H * W), torch.ones(Cout, dtype=torch.bool, device="cuda")
+    other[[7, Cout - 1]] = False
+    assert torch.equal(Y[:, other], clean[:, other])
+    assert_parity(Y[:, 7][~kept[:, :, 1]], clean[:, 7][~kept[:, :, 1]].float().cpu().numpy(), "bf16", None, "one weight, dropped")
+    assert not torch.isfinite(Y[:, 7][kept[:, :, 1]]).any()
+    assert not torch.isfinite(Y[:, Cout - 1][kept.any(-1)]).any()
+    assert not Y[:, Cout - 1][~kept.any(-1)].view(torch.int16).any()
