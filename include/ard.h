@@ -404,10 +404,13 @@ int32_t ard_sens_block_pattern(int32_t N, int32_t row_bands, int32_t col_blocks,
  * image's input matrix takes part iff d_block_keep[(image*RB + p/x)*CB + q/y] != 0 (the array
  * ard_sens_block_pattern writes; y = 0: blocks span the width).  out = Y[N,Cout,Ho,Wo], every element
  * written.  Arguments and workspace as for ard_fmap_drop_conv(ARD_CONV_FWD) with every channel kept.
- * Dropped blocks are skipped (neither loaded nor multiplied) when the blocks are whole 64-channel groups
- * over all filter taps and the bands fill at least half a tile: bf16, stride 1, Cout > 64,
- * y % (64*kh*kw) == 0, kh*kw*ceil(C/64) <= 128, and x such that the bands of an image, each padded to
- * whole tiles of 128 or 256 positions, take at most twice the image's positions.  Any other shape runs on
+ * bf16, stride 1, blocks of whole 64-channel groups over all filter taps (y % (64*kh*kw) == 0, kh*kw*ceil(C/64) <= 128):
+ * what a band drops takes no part in its results, whatever values the weights and activations of dropped blocks have.
+ * Where the bands fill at least half a tile (Cout > 64, the bands of an image, each padded to whole tiles of 128 or 256
+ * positions, take at most twice the image's positions, and there are 256 tiles or more) a dropped block is neither loaded
+ * nor multiplied; with other bands a tile of 128 positions leaves out the groups that none of its positions keeps.
+ * fp32, stride 1, blocks of whole channels (y % (kh*kw) == 0, at most 16 column blocks): one fast pass over the channels
+ * of every column block, of which the positions of kept bands are added (no work skipped).  Any other shape runs on
  * the general convolution engine, which applies the mask while it gathers the patches: correct in both
  * dtypes and for any stride, no time saved.
  */

@@ -1508,11 +1508,13 @@ static PosListJob pos_list_job(const ConvArgs& a, const uint8_t* blk, int x, int
   return j;
 }
 
-// Whether the forward pass under a block pattern can run over tiles that end anywhere in a band (conv_blocks.hpp).  (Bands
-// below 12 positions and layers below 320 stay with the engines that tests/test_host_bounds.py pins them to.)
+// Whether the forward pass under a block pattern can run over tiles that end anywhere in a band (conv_blocks.hpp).  However
+// short the bands and small the layer: against the patch loaders of the general engine, 30 % kept, us, 128 x 256 channels of
+// 28 x 28 -> 256 in bands of 1 and 8 positions 7289 and 6900 -> 208 and 198, 8 x 64 of 14 x 14 -> 32 218 -> 14, one image of
+// 64 of 7 x 7 -> 16 149 -> 14, two of 512 of 7 x 7 -> 256 1512 -> 49.
 static bool block_masked_ok(const ConvArgs& a, const ConvWs& w) {
   const int taps = a.kh * a.kw, CG = pad64(a.C) / 64;
-  return a.bx >= 12 && a.N * a.Ho * a.Wo >= 320 && w.grid_a && !dev_knobs().no_fast && a.by % (64 * taps) == 0 && CG <= 32 && taps * CG <= 128 && a.kh <= 15 && a.kw <= 15 &&
+  return w.grid_a && !dev_knobs().no_fast && a.by % (64 * taps) == 0 && CG <= 32 && taps * CG <= 128 && a.kh <= 15 && a.kw <= 15 &&
          (long)ceil_div(a.N * a.Ho * a.Wo, 128) * ceil_div(a.Cout, 64) < (1L << 24);
 }
 
@@ -1536,8 +1538,9 @@ static int block_fast_tile(const ConvArgs& a, const ConvWs& w) {
   const long tiles = (long)a.N * best_len / best;
   // (fewer workgroups than CUs, each a whole CU's: the smaller tiles of conv_blocks.hpp are faster.  Training steps of drawn
   // layers, us, these against those: 44 workgroups 126 and 101, 150 73 and 69, 210 211 and 204, 308 257 and 264, 448 178 and
-  // 190, 1344 379 and 426)
-  if (tiles * ceil_div(a.Cout, best == 128 || a.Cout > 128 ? 256 : 128) < 256 && hw * a.N >= 512 && block_masked_ok(a, w)) return 0;
+  // 190, 1344 379 and 426; forward passes of a few: 4 workgroups (288 positions) 19.5 and 13.9, 2 (256) 56 and 28, 1 (256) 11.3
+  // and 9.8)
+  if (tiles * ceil_div(a.Cout, best == 128 || a.Cout > 128 ? 256 : 128) < 256 && block_masked_ok(a, w)) return 0;
   if ((size_t)(a.N * best_len) > w.blk_ints || (size_t)(tiles * taps * CG) > w.blk_ints || tiles >= (1L << 22)) return 0;
   return best;
 }

@@ -2,7 +2,7 @@
 stride 1, blocks of whole 64-channel groups), at the sizes where its kernel changes branch: a tile that is not full, tiles over
 several images, one output channel and several tiles of 64, one and several groups, a last group that is not full, more
 than 64 contraction steps, no kept block at all, planes stored 16, 8, 4 and 2 bytes at a time, paddings that shrink and
-grow the image."""
+grow the image, bands of one position, layers of less than a tile."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
     (1, 64, 1, 16, 20, 3, 1, 12, 1, 0.5), (7, 64, 16, 7, 7, 3, 1, 12, 1, 0.5), (11, 128, 65, 7, 7, 3, 1, 49, 1, 0.3), (3, 192, 130, 13, 13, 3, 1, 13, 2, 0.4),
     (2, 448, 40, 14, 14, 3, 1, 28, 1, 0.3), (2, 320, 24, 16, 16, 5, 2, 100, 1, 0.3), (3, 100, 72, 12, 12, 3, 1, 17, 1, 0.5), (7, 128, 200, 9, 10, 3, 0, 16, 1, 0.5),
     (3, 64, 33, 8, 12, 3, 2, 20, 1, 0.6), (4, 128, 64, 16, 16, 1, 0, 32, 1, 0.5), (2, 128, 64, 16, 16, 3, 1, 32, 1, 0.0), (2, 128, 64, 16, 16, 3, 1, 32, 1, 1.0),
-    (30, 64, 100, 5, 5, 3, 1, 25, 1, 0.4)])
+    (30, 64, 100, 5, 5, 3, 1, 25, 1, 0.4), (1, 64, 1, 3, 3, 3, 1, 1, 1, 0.6), (3, 128, 70, 9, 9, 3, 1, 1, 1, 0.5), (2, 192, 24, 13, 13, 3, 1, 5, 2, 0.4),
+    (9, 64, 33, 12, 12, 3, 1, 8, 1, 0.3), (2, 128, 200, 12, 12, 3, 1, 72, 1, 0.4), (3, 100, 140, 12, 13, 3, 1, 78, 1, 0.4), (1, 256, 300, 8, 8, 1, 0, 64, 2, 0.5)])
 def test_forward(N, C, Cout, H, W, k, pad, x, groups, p):
     print("blocks forward", N, C, Cout, H, W, k, pad, x, groups, p, flush=True)
     rng = np.random.default_rng(C + H + Cout)

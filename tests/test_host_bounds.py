@@ -122,20 +122,27 @@ def test_lstm_and_conv_shapes():
 
 def test_block_pattern_dispatch_and_bounds():
     """Forward pass under the block pattern: blocks of whole 64-channel groups over all taps with bands of at
-    least half a tile go to the LDS-direct kernel (tile plan in the copy's launch, per-tile block lists, proof
-    over the whole contraction); any other block shape goes to the general engine."""
+    least half a tile, from 256 tiles on, go to the LDS-direct kernel (tile plan in the copy's launch, per-tile block lists,
+    proof over the whole contraction), those of fewer tiles or shorter bands to the kernel whose tiles end anywhere in a
+    band; any other block shape goes to the general engine."""
+    PLAN, ANYWHERE, GENERAL = "gemm_direct_kernel", "conv_block_fwd_kernel", "conv_gemm_kernel"
     with D.dry_run() as lib:
         heap = D.FakeHeap()
-        for (N, Cc, Cout, H, W, k, pad, x, y), fast in [((128, 256, 256, 28, 28, 3, 1, 112, 576), True),
-                                                         ((128, 256, 256, 28, 28, 3, 1, 196, 1152), True),
-                                                         ((2, 128, 200, 12, 12, 3, 1, 72, 576), True),
-                                                         ((3, 100, 140, 12, 13, 3, 1, 78, 576), True),
-                                                         ((3, 100, 100, 12, 13, 3, 1, 156, 576), True),
-                                                         ((2, 192, 130, 9, 16, 3, 1, 144, 0), True),
-                                                         ((2, 128, 64, 12, 12, 3, 1, 72, 576), False),     # too few output channels
-                                                         ((128, 256, 256, 28, 28, 3, 1, 8, 576), False),   # bands far below a tile
-                                                         ((128, 256, 256, 28, 28, 3, 1, 112, 64), False),  # blocks cut channels
-                                                         ((2, 128, 200, 12, 12, 3, 2, 18, 576), False)]:   # stride 2
+        for (N, Cc, Cout, H, W, k, pad, x, y), engine in [((128, 256, 256, 28, 28, 3, 1, 112, 576), PLAN),
+                                                           ((128, 256, 256, 28, 28, 3, 1, 196, 1152), PLAN),
+                                                           ((128, 128, 200, 12, 12, 3, 1, 72, 576), PLAN),
+                                                           ((128, 100, 140, 12, 13, 3, 1, 78, 576), PLAN),
+                                                           ((256, 100, 100, 12, 13, 3, 1, 156, 576), PLAN),
+                                                           ((256, 192, 130, 9, 16, 3, 1, 144, 0), PLAN),
+                                                           ((2, 128, 200, 12, 12, 3, 1, 72, 576), ANYWHERE),     # few tiles
+                                                           ((3, 100, 140, 12, 13, 3, 1, 78, 576), ANYWHERE),
+                                                           ((3, 100, 100, 12, 13, 3, 1, 156, 576), ANYWHERE),
+                                                           ((2, 192, 130, 9, 16, 3, 1, 144, 0), ANYWHERE),
+                                                           ((2, 128, 64, 12, 12, 3, 1, 72, 576), ANYWHERE),      # few output channels
+                                                           ((128, 256, 256, 28, 28, 3, 1, 8, 576), ANYWHERE),    # bands far below a tile
+                                                           ((1, 64, 16, 7, 7, 3, 1, 1, 576), ANYWHERE),
+                                                           ((128, 256, 256, 28, 28, 3, 1, 112, 64), GENERAL),    # blocks cut channels
+                                                           ((2, 128, 200, 12, 12, 3, 2, 18, 576), GENERAL)]:     # stride 2
             stride = 2 if (pad == 2) else 1
             pad = 1 if stride == 2 else pad
             n = lib.ard_conv_workspace_bytes(D.BF16, N, Cc, H, W, Cout, k, k, stride, pad)
@@ -147,11 +154,10 @@ def test_block_pattern_dispatch_and_bounds():
             rc = lib.ard_conv_fwd_blocks(D.BF16, N, Cc, H, W, Cout, k, k, stride, pad, x, y, A, Wt, keep, out, ws, n, None)
             assert rc == 0, lib.ard_last_error().decode()
             names = D.launches(lib)[1]
-            assert ("gemm_direct_kernel" in names) == fast, (N, Cc, Cout, x, y, names)
-            assert ("conv_gemm_kernel" in names) == (not fast)
-            if fast:   # the plan rides in the copy's launch
+            assert [e for e in (PLAN, ANYWHERE, GENERAL) if e in names] == [engine], (N, Cc, Cout, x, y, names)
+            if engine != GENERAL:   # (the plan rides in the copy's launch)
                 assert "block_plan_kernel" not in names and "to_grid_src_kernel" in names, (H, W, names)
-            if fast:
+            if engine == PLAN:
                 nb, six = D.last_bounds(lib)
                 assert nb == 1 and 0 <= six[0] < six[1] <= six[2] and 0 <= six[3] < six[4] <= six[5]
 
@@ -163,12 +169,14 @@ def test_block_pattern_random_shapes_pass_the_proof():
     rnd = random.Random(52)
     with D.dry_run() as lib:
         heap = D.FakeHeap()
-        fast = 0
-        for _ in range(60):
+        fast = anywhere = 0
+        for i in range(80):
             k = rnd.choice((1, 3, 3, 5))
             pad = rnd.choice((0, k // 2))
             H, W = rnd.randint(k + 4, 30), rnd.randint(k + 4, 30)
             N, Cc, Cout = rnd.randint(1, 6), rnd.choice((8, 40, 64, 100, 128, 192, 256)), rnd.choice((24, 65, 128, 130, 256, 300))
+            if i >= 60:  # (enough images for 256 tiles)
+                N = rnd.randint(100, 200)
             Ho, Wo = H + 2 * pad - k + 1, W + 2 * pad - k + 1
             x = rnd.choice((rnd.randint(1, Ho * Wo), max(1, Ho * Wo // rnd.randint(1, 8))))
             y = rnd.choice((0, 64 * k * k, 128 * k * k, k * k * rnd.randint(1, 70), rnd.randint(1, Cc * k * k)))
@@ -179,11 +187,13 @@ def test_block_pattern_random_shapes_pass_the_proof():
             D.launches(lib)
             rc = lib.ard_conv_fwd_blocks(D.BF16, N, Cc, H, W, Cout, k, k, 1, pad, x, y, A, Wt, keep, out, ws, n, None)
             assert rc == 0, (N, Cc, Cout, H, W, k, pad, x, y, lib.ard_last_error().decode())
-            fast += "gemm_direct_kernel" in D.launches(lib)[1]
+            names = D.launches(lib)[1]
+            fast += "gemm_direct_kernel" in names
+            anywhere += "conv_block_fwd_kernel" in names
             for mode in (2, 3):
                 rc = lib.ard_conv_bwd_blocks(mode, D.BF16, N, Cc, H, W, Cout, k, k, 1, pad, x, y, A, Wt, dY, keep, out, ws, n, None)
                 assert rc == 0, (mode, N, Cc, Cout, H, W, k, pad, x, y, lib.ard_last_error().decode())
-        assert fast >= 3, "the random shapes never reached the path that skips dropped blocks"
+        assert fast >= 3 and anywhere >= 3, "the random shapes never reached the paths that skip dropped blocks"
         assert D.last_bounds(lib)[0] >= fast      # (reading them also resets the count for the next test)
 
 
