@@ -429,8 +429,10 @@ int32_t ard_conv_fwd_blocks(int32_t dtype, int32_t N, int32_t C, int32_t H, int3
  *          pad <= k-1 only, as for ARD_CONV_BWD_DATA of ard_fmap_drop_conv (else ARD_EUNSUPPORTED).
  * Every element of out is written.  d_block_keep, x, y, workspace and dtypes as for ard_conv_fwd_blocks.
  * bf16, stride 1, blocks of whole channels (y % (8*kh*kw) == 0): the weight gradient contracts, for every
- * group of channels, over its kept positions only; with groups of whole 64 channels, bands of whole output rows
- * and a size-preserving filter the data gradient leaves out the filter rows that read dropped bands only.  mode may
+ * group of channels, over its kept positions only; with a size-preserving filter the data gradient is one launch for all
+ * groups, over the kept positions of dY alone (groups of whole 16 channels) or over tiles of pixels that leave out the
+ * filter rows that read dropped bands only (groups of whole 64 channels, bands of whole output rows), whichever is
+ * expected to be faster for these sizes and about half of the blocks kept.  mode may
  * then carry ARD_CONV_REUSE_DY for the weight gradient: the same workspace still holds the copy of dY the data
  * gradient of the same dYin and d_block_keep made (ignored where that pass left none).
  * Other blocks of whole channels (y % (kh*kw) == 0, at most 16 column blocks), without skipping work: per column

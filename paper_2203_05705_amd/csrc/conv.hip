@@ -1432,6 +1432,32 @@ static int32_t to_grid(const void* src, const int* chan, int n_chan, int Cs, int
   return ARD_OK;
 }
 
+// The tile of a product of `rows` rows by `npix` pixels on the grids, and its cost (2304 times the rounds it takes, by their cost).
+struct GridTile {
+  int bm, bn;
+  long cost;
+};
+static GridTile pick_grid_tile(int rows, int npix) {
+  // A launch runs in rounds: one workgroup of a large shape fills a CU (256 at a time), three of the 64 x 64 shape share
+  // one (768 at a time).  Costs of a round, a 256 x 256 round being 100, from launches of two whole rounds, contractions of
+  // 1152 and 2304 (us: 31 and 51 of 64 x 64, 50 and 84 of the smaller large ones, 64 and 107 of 256 x 192, 67 and 111 of
+  // 128 x 384, 78 and 131 of 128 x 448, 79 and 134 of 256 x 256); how often the pixels are read, with 128 to 512 rows,
+  // makes no difference.  A third of a round's cost goes by the tiles in it: those of a last round that is not full are
+  // over sooner (256 rows, 100352 pixels: 392 tiles of 256 x 256 take 74 and 122 us, 448 of 128 x 448, cheaper by the
+  // round, 75 and 125).  Lowest cost wins: over 44 layers (8 - 200 images, 7 x 7 - 56 x 56, 64 - 512 channels and rows) the
+  // choice is within 0.2 % of the best in the mean, within 4 % at most.
+  static const struct { int bm, bn, slots, cost; } kTiles[] = {{64, 64, 768, 40}, {128, 256, 256, 63}, {256, 128, 256, 63}, {256, 192, 256, 81},
+                                                               {128, 384, 256, 83}, {128, 448, 256, 97}, {256, 256, 256, 100}};
+  GridTile best{0, 0, -1};
+  for (const auto& t : kTiles) {
+    if (t.bm > 64 && rows <= t.bm / 2) continue;
+    const long n = (long)ceil_div(rows, t.bm) * ceil_div(npix, t.bn), rounds = (n + t.slots - 1) / t.slots;
+    const long c = (2 * rounds * t.slots + n) * (768 / t.slots) * t.cost;
+    if (best.cost < 0 || c <= best.cost) best = GridTile{t.bm, t.bn, c};
+  }
+  return best;
+}
+
 // Y[row][pixel] = sum_k Wp[row][k] * im2col[pixel][k] on the grid; NCHW output
 // force_bn / kb_*: the block-based pattern's launch (column tile fixed by its plan, per-tile contraction lists)
 static int32_t conv_grid_gemm(const uint16_t* Wp, int rows, int K, const uint16_t* grid_t, long grid_pixels,
@@ -1460,24 +1486,8 @@ static int32_t conv_grid_gemm(const uint16_t* Wp, int rows, int K, const uint16_
     bm = force_bn == 128 || rows > 128 ? 256 : 128;
     bn = force_bn;
   } else {
-    // A launch runs in rounds: one workgroup of a large shape fills a CU (256 at a time), three of the 64 x 64 shape share
-    // one (768 at a time).  Costs of a round, a 256 x 256 round being 100, from launches of two whole rounds, contractions of
-    // 1152 and 2304 (us: 31 and 51 of 64 x 64, 50 and 84 of the smaller large ones, 64 and 107 of 256 x 192, 67 and 111 of
-    // 128 x 384, 78 and 131 of 128 x 448, 79 and 134 of 256 x 256); how often the pixels are read, with 128 to 512 rows,
-    // makes no difference.  A third of a round's cost goes by the tiles in it: those of a last round that is not full are
-    // over sooner (256 rows, 100352 pixels: 392 tiles of 256 x 256 take 74 and 122 us, 448 of 128 x 448, cheaper by the
-    // round, 75 and 125).  Lowest cost wins: over 44 layers (8 - 200 images, 7 x 7 - 56 x 56, 64 - 512 channels and rows) the
-    // choice is within 0.2 % of the best in the mean, within 4 % at most.
-    static const struct { int bm, bn, slots, cost; } kTiles[] = {{64, 64, 768, 40}, {128, 256, 256, 63}, {256, 128, 256, 63}, {256, 192, 256, 81},
-                                                                 {128, 384, 256, 83}, {128, 448, 256, 97}, {256, 256, 256, 100}};
-    long best = -1;
-    bm = bn = 0;
-    for (const auto& t : kTiles) {
-      if (t.bm > 64 && rows <= t.bm / 2) continue;
-      const long n = (long)ceil_div(rows, t.bm) * ceil_div(cv.npix, t.bn), rounds = (n + t.slots - 1) / t.slots;
-      const long c = (2 * rounds * t.slots + n) * (768 / t.slots) * t.cost;
-      if (best < 0 || c <= best) best = c, bm = t.bm, bn = t.bn;
-    }
+    const GridTile t = pick_grid_tile(rows, cv.npix);
+    bm = t.bm, bn = t.bn;
   }
   F.tiles_m = ceil_div(rows, bm);
   F.tiles_n = ceil_div(cv.npix, bn);
@@ -1584,6 +1594,64 @@ static bool scatter_plan(const ConvArgs& a, const ConvWs& w, const BandMask& m, 
   P.by_groups = fast_div((uint32_t)P.G), P.by_bands = fast_div((uint32_t)P.bands), P.by_hw = fast_div((uint32_t)P.HW);
   P.by_w = fast_div((uint32_t)P.W_), P.by_x = fast_div((uint32_t)m.x), P.by_gpb = fast_div((uint32_t)(cpb / 16));
   return true;
+}
+// What the kernels for a data gradient take beside what all of them do (launches, the copy of dY), in us, good enough to compare them:
+// fitted to 168 drawn row-pattern and 247 block-pattern layers (7 x 7 - 56 x 56, 16 - 512 channels, 3 x 3 and 5 x 5), 30 to 100 %
+// kept each, all measured both ways.  Against knowing the faster one, the choice below costs 1 to 3 % in the mean over them up to
+// 70 % kept, 6 to 8 % where everything is kept (there half at worst).  Only the caller may know the share of kept positions;
+// kKeptGuess lies between the 30 % that possibilities of 0.3 and 0.7 leave where nothing is sensitive and the 70 % where all is.
+constexpr double kKeptGuess = 0.45;
+static double launch_rounds(long n, int slots) { return (2.0 * ((n + slots - 1) / slots) + (double)n / slots) / 3.0; }
+// Over the kept positions: a tap of a tile adds its sums in LDS, whatever the channels of dY (5.9: weights double-buffered only).
+// Bands of x positions: the fullest workgroups of a round are what it waits for.
+static double scatter_us(const ScatterDataParams& P, int ks, double kept, int x) {
+  const double rounds = launch_rounds(P.total, P.lds_bytes <= kSdLds ? 512 : 256);
+  const double positions = (double)P.im * imin(P.rows >= P.H ? P.H : P.rows + 2 * P.ph, P.H) * P.W_, bands = positions > x ? positions / x : 1.0;
+  const double full = kept + std::sqrt(kept * (1.0 - kept) / (bands * rounds)), taps = rounds * P.passes * P.taps;
+  return taps * positions * (full < 1.0 ? full : 1.0) / 6400.0 * (ks >= 6 ? 17.2 : 11.3) + taps * ks * 0.0062 + rounds * P.im * P.rows * P.W_ * 0.0042;
+}
+// Over all positions of a masked copy
+static double masked_us(const ConvArgs& a) {
+  const int K = a.kh * a.kw * pad64(a.Cout);
+  return (3.6 * (K / 64) + 34.6) * 1e-6 * pick_grid_tile(a.C, a.N * a.H * a.W).cost - 3.0;
+}
+static double block_tiles_us(const ConvArgs& a, const BlockDataParams& P) {
+  return launch_rounds((long)a.N * P.tiles_img * P.CB * P.mt, 512) * a.kh * a.kw * P.CG * 0.41 + 2.0;
+}
+// Data gradient under the block pattern over tiles of positions (conv_blocks.hpp): tiles of 128 positions are whole bands or
+// parts of a band, and at least half full (else the passes per column block, whose tiles run over all positions).
+static bool block_data_tiles(const ConvArgs& a, const ConvWs& w, BlockDataParams& P) {
+  const int taps = a.kh * a.kw, hw = a.H * a.W;
+  if (!w.grid_a || dev_knobs().no_fast || a.kh - 1 != 2 * a.pad || a.kw - 1 != 2 * a.pad || a.kh > 15 || a.kw > 15) return false;
+  if (a.by % (64 * taps) || (long)a.C * taps % a.by || a.bx % a.W) return false;
+  P.RB = ceil_div(hw, a.bx), P.CB = a.C * taps / a.by;
+  P.CG = pad64(a.Cout) / 64;
+  if (P.RB > 64 || taps * P.CG > 128) return false;
+  P.x = a.bx, P.rows_per_band = a.bx / a.W;
+  P.bands_per_tile = imax(1, 128 / a.bx), P.parts = ceil_div(a.bx, 128);
+  P.tiles_img = P.parts == 1 ? ceil_div(P.RB, P.bands_per_tile) : P.RB * P.parts;
+  P.cpb = a.by / taps, P.mt = P.cpb / 64;
+  return hw * 2 >= P.tiles_img * 128 && (long)a.N * P.tiles_img * P.CB * P.mt < (1L << 24);
+}
+static int32_t conv_block_data(const ConvArgs& a, BlockDataParams P, const void* Wt, const void* dYin, void* out, const ConvWs& w,
+                               hipStream_t stream) {
+  const int taps = a.kh * a.kw, ph = a.kh - 1 - a.pad, pw = a.kw - 1 - a.pad, Cp = pad64(a.Cout), Hg = a.Ho + 2 * ph, Wg = a.Wo + 2 * pw;
+  int hgm, wgm;
+  (void)conv_grid_pixels(a, &hgm, &wgm);
+  const long margin = (long)a.kh * wgm + a.kw + 128;
+  // (the kept positions of every group, which the weight gradient of the same workspace contracts over, ride along)
+  if (int32_t st = to_grid(dYin, nullptr, a.Cout, a.Cout, a.Ho, a.Wo, a.N, Hg, Wg, ph, pw, Cp, margin, w.grid_y, stream, BandMask{},
+                           pack_job(Wt, nullptr, a.C, taps, a.C, a.Cout, Cp, 1, w.gwp), ZeroPlanesJob{}, ZeroPixelsJob{}, BlockPlanJob{}, a.lists))
+    return st;
+  P.W = w.gwp, P.grid = w.grid_y, P.dA = (uint16_t*)out, P.blk = a.blk;
+  P.ldw = taps * Cp, P.Cp = Cp, P.kh = a.kh, P.kw = a.kw, P.ph = ph, P.pw = pw;
+  P.H = a.H, P.W_ = a.W, P.C = a.C, P.HgWg = Hg * Wg, P.Wg = Wg;
+  P.total = a.N * P.tiles_img * P.CB * P.mt;
+  const int hw = a.H * a.W;
+  P.width = hw % 8 == 0 && a.bx % 8 == 0 && al16c(out) ? 16 : hw % 2 == 0 && a.bx % 2 == 0 && ((uintptr_t)out & 3) == 0 ? 4 : 2;
+  P.by_groups = fast_div((uint32_t)(P.CB * P.mt)), P.by_tiles = fast_div((uint32_t)P.tiles_img), P.by_w = fast_div((uint32_t)a.W);
+  // (a lane's last read: the last pixel of the last image through the last tap, inside the grid; rows of W: C of them)
+  return launch_conv_block_data(P, stream);
 }
 static int32_t conv_scatter(ScatterDataParams P, int ks, const ConvWs& w, void* out, hipStream_t stream) {
   P.W = w.gwp, P.dA = (uint16_t*)out;
@@ -2144,16 +2212,24 @@ extern "C" int32_t ard_conv_bwd_blocks(int32_t mode, int32_t dtype, int32_t N, i
   hipStream_t s = (hipStream_t)stream;
   const int taps = kh * kw;
   const int CB = ceil_div(C * taps, a.by), RB = ceil_div(a.Ho * a.Wo, a.bx);
-  // Groups of whole channels on the channels-last grids: each contracts over its kept positions only, all of them in
-  // one launch; the data gradient likewise where its tiles fit the bands.
+  // Groups of whole channels on the channels-last grids: the weight gradient contracts over the kept positions of each, all of
+  // them in one launch; the data gradient is one launch over tiles of positions, or over the kept positions alone, whichever
+  // is expected to be faster (22 images of 64 channels of 56 x 56 -> 24, 5 x 5, 30 % kept: 33 against 74 us; 56 of 64 of 56 x 56 -> 48,
+  // 3 x 3: 39 and 50; 64 of 512 of 14 x 14 -> 512: 120 and 59).
   const bool by_groups = w.grid_a && !dev_knobs().no_fast && a.by % (8 * taps) == 0 && CB * (a.by / taps) <= pad64(C) && CB <= w.pos_blocks;
   ScatterDataParams sd;
+  BlockDataParams bd{};
   int ks;
   const BandMask bands{d_block_keep, RB, CB, 0, a.bx};
-  const bool one_launch = a.by % (16 * taps) == 0 && scatter_plan(a, w, bands, a.by / taps, sd, ks);
+  const bool tiles = by_groups && block_data_tiles(a, w, bd);
+  const bool over_kept = a.by % (16 * taps) == 0 && scatter_plan(a, w, bands, a.by / taps, sd, ks) &&
+                         (tiles ? scatter_us(sd, ks, kKeptGuess, a.bx) <= block_tiles_us(a, bd)
+                                : CB > 1 || scatter_us(sd, ks, kKeptGuess, a.bx) <= masked_us(a) + 6.0);  // (masked passes: a launch more)
+  const bool one_launch = over_kept || tiles;
   const bool listed = by_groups && pos_lists_fit(a);
   if (listed) a.lists = pos_list_job(a, d_block_keep, a.bx, CB, w);
   if (one_launch && mode == ARD_CONV_BWD_DATA) {
+    if (!over_kept) return conv_block_data(a, bd, Wt, dYin, out, w, s);
     ConvArgs g = a;
     g.blk = nullptr;
     g.scatter = bands, g.scatter_cpb = a.by / taps;
@@ -2163,9 +2239,10 @@ extern "C" int32_t ard_conv_bwd_blocks(int32_t mode, int32_t dtype, int32_t N, i
     ConvArgs g = a;
     g.blk = nullptr;
     g.cpb = a.by / taps;
-    g.reuse = one_launch ? reuse : 0;  // (else the data gradient left dY masked for its last column block)
+    g.reuse = one_launch || CB == 1 ? reuse : 0;  // (else the data gradient left dY masked for its last column block)
     return conv_run<uint16_t>(g, 0.0, A, Wt, dYin, out, nullptr, nullptr, nullptr, nullptr, w, s);
   }
+  const PosListJob lists = a.lists;
   a.lists = PosListJob{};
   // every channel is kept: the passes take the identity list
   ARD_LAUNCH(iota_kernel, dim3(ceil_div(C, 256)), dim3(256), 0, s, w.all_chan, C);
@@ -2187,6 +2264,7 @@ extern "C" int32_t ard_conv_bwd_blocks(int32_t mode, int32_t dtype, int32_t N, i
         // the pass copies dY into its grid anyway: that copy applies the mask
         g.dy_mask = BandMask{d_block_keep, RB, CB, cb, a.bx};
         dy_use = dYin;
+        if (CB == 1) g.lists = lists;  // (for the weight gradient of the same workspace)
       } else {
         if (dtype == ARD_BF16)
           ARD_LAUNCH(mask_bands_kernel<uint16_t>, dim3(Cout, N), dim3(256), 0, s, (const uint16_t*)dYin, d_block_keep, RB, CB, cb,

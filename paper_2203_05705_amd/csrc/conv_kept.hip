@@ -5,15 +5,22 @@
 
 namespace ard {
 
-int32_t launch_conv_block_fwd(const BlockFwdParams& P, hipStream_t stream) {
-  static thread_local bool raised = false;
+template <class P> static int32_t block_launch(void (*kernel)(P), const char* name, const P& p, hipStream_t stream, bool& raised) {
   if (!raised) {
-    ARD_HIP_CHECK(raise_lds_limit((const void*)conv_block_fwd_kernel, kBfLds));
+    ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, kBlockLds));
     raised = !dry_run();
   }
-  ARD_LAUNCH(conv_block_fwd_kernel, dim3((unsigned)(ceil_div(P.total, 8) * 8)), dim3(256), kBfLds, stream, P);
-  ARD_LAUNCH_CHECK("conv_block_fwd_kernel");
+  ARD_LAUNCH_NAMED(name, kernel, dim3((unsigned)(ceil_div(p.total, 8) * 8)), dim3(256), kBlockLds, stream, p);
+  ARD_LAUNCH_CHECK(name);
   return ARD_OK;
+}
+int32_t launch_conv_block_fwd(const BlockFwdParams& P, hipStream_t stream) {
+  static thread_local bool raised = false;
+  return block_launch(conv_block_fwd_kernel, "conv_block_fwd_kernel", P, stream, raised);
+}
+int32_t launch_conv_block_data(const BlockDataParams& P, hipStream_t stream) {
+  static thread_local bool raised = false;
+  return block_launch(conv_block_data_kernel, "conv_block_data_kernel", P, stream, raised);
 }
 
 template <int KS> static int32_t scatter_launch(const ScatterDataParams& P, hipStream_t stream) {
