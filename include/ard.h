@@ -339,7 +339,9 @@ size_t ard_conv_workspace_bytes(int32_t dtype, int32_t N, int32_t C, int32_t H, 
  *   part in the product, so gradient arriving on a dropped position counts as zero: d_mask[N*Ho*Wo] is the
  *   row mask; BWD_DATA / BWD_WEIGHT run with every channel kept on a dY whose dropped positions are zero
  *   (zeroed while dY is copied into its grid; a masked copy for fp32 and strided layers).  The bf16 stride-1
- *   weight gradient contracts over the kept positions only; n_keep, d_keep are ignored.  Needs dYin, d_mask and Wt (data) or A (weight).
+ *   weight gradient contracts over the kept positions only, the data gradient where that is expected to be faster: n_keep,
+ *   if given (1 .. N*Ho*Wo), is taken for the number of kept rows in this choice, else 40 % of them are; results depend
+ *   on it in the order of their sums only.  d_keep is ignored.  Needs dYin, d_mask and Wt (data) or A (weight).
  *   The reuse flags apply as for BWD_DATA / BWD_WEIGHT: ARD_CONV_REUSE_A takes the grid FWD_ROWS left,
  *   ARD_CONV_REUSE_DY the masked grid an earlier *_ROWS gradient of the same mask left.
  * FWD / BWD_DATA / BWD_WEIGHT read the kept channels from d_keep (n_keep entries,
@@ -432,7 +434,7 @@ int32_t ard_conv_fwd_blocks(int32_t dtype, int32_t N, int32_t C, int32_t H, int3
  * group of channels, over its kept positions only; with a size-preserving filter the data gradient is one launch for all
  * groups, over the kept positions of dY alone (groups of whole 16 channels) or over tiles of pixels that leave out the
  * filter rows that read dropped bands only (groups of whole 64 channels, bands of whole output rows), whichever is
- * expected to be faster for these sizes and about half of the blocks kept.  mode may
+ * expected to be faster for these sizes with 40 % of the blocks kept.  mode may
  * then carry ARD_CONV_REUSE_DY for the weight gradient: the same workspace still holds the copy of dY the data
  * gradient of the same dYin and d_block_keep made (ignored where that pass left none).
  * Other blocks of whole channels (y % (kh*kw) == 0, at most 16 column blocks), without skipping work: per column

@@ -1598,9 +1598,10 @@ static bool scatter_plan(const ConvArgs& a, const ConvWs& w, const BandMask& m, 
 // What the kernels for a data gradient take beside what all of them do (launches, the copy of dY), in us, good enough to compare them:
 // fitted to 168 drawn row-pattern and 247 block-pattern layers (7 x 7 - 56 x 56, 16 - 512 channels, 3 x 3 and 5 x 5), 30 to 100 %
 // kept each, all measured both ways.  Against knowing the faster one, the choice below costs 1 to 3 % in the mean over them up to
-// 70 % kept, 6 to 8 % where everything is kept (there half at worst).  Only the caller may know the share of kept positions;
-// kKeptGuess lies between the 30 % that possibilities of 0.3 and 0.7 leave where nothing is sensitive and the 70 % where all is.
-constexpr double kKeptGuess = 0.45;
+// 70 % kept, 6 to 8 % where everything is kept (there nearly half at worst).  The share of kept positions: the 30 % that possibilities of
+// 0.3 and 0.7 leave where nothing is sensitive, and some more.  (Both kernels launched, the one to run found by the count on
+// the GPU, was 7 % slower with 30 % kept and 12 % faster with all, over the 49 layers whose line lies between: taken back.)
+constexpr double kKeptGuess = 0.4;
 static double launch_rounds(long n, int slots) { return (2.0 * ((n + slots - 1) / slots) + (double)n / slots) / 3.0; }
 // Over the kept positions: a tap of a tile adds its sums in LDS, whatever the channels of dY (5.9: weights double-buffered only).
 // Bands of x positions: the fullest workgroups of a round are what it waits for.
@@ -1970,10 +1971,17 @@ static int32_t conv_run(const ConvArgs& a, double rate, const void* A, const voi
       // the pass copies dY into its grid anyway: that copy drops the positions (bands of one row)
       full.dy_mask = BandMask{(const uint8_t*)d_mask, a.Ho * a.Wo, 1, 0, 1};
       dy_use = dYin;
-      // the gradients run over the kept positions only
-      // (the data gradient from 65 channels of dY on: below, adding up costs more than the product; training steps of 40
-      // drawn layers, 30 % kept: 1.21 to 1.00 of the speed over all positions above, 1.03 to 0.89 below)
-      if (a.Cout > 64) full.scatter = full.dy_mask, full.scatter_cpb = pad16(a.C);
+      // The weight gradient runs over the kept positions only, the data gradient where that is expected to be faster and dY has more
+      // than 64 channels (30 % kept, us, all positions and the kept ones: 128 x 256 channels of 28 x 28 -> 256 151 and 102, 64 x 512
+      // of 14 x 14 -> 512 98 and 56, 112 x 248 of 56 x 56 -> 96 251 and 296; up to 64 channels 0.54 to 1.2 of the speed, in the mean
+      // of 51 layers of more than 20 us none).  n_keep, where a caller gives it, says how many rows are kept (128 x 256 of 28 x 28 ->
+      // 256, all kept: 151 and 211).
+      ScatterDataParams sd;
+      int ks;
+      const long rows = (long)a.N * a.Ho * a.Wo;
+      const double kept = a.n_keep > 0 && a.n_keep <= rows ? (double)a.n_keep / (double)rows : kKeptGuess;
+      if (a.mode == ARD_CONV_BWD_DATA_ROWS && a.Cout > 64 && scatter_plan(a, w, full.dy_mask, pad16(a.C), sd, ks) && scatter_us(sd, ks, kept, 1) <= masked_us(a))
+        full.scatter = full.dy_mask, full.scatter_cpb = pad16(a.C);
       if (w.grid_a && pos_lists_fit(a)) full.lists = pos_list_job(a, (const uint8_t*)d_mask, 1, 1, w);
     } else {
       ARD_LAUNCH(iota_kernel, dim3(ceil_div(a.C, 256)), dim3(256), 0, stream, w.all_chan, a.C);

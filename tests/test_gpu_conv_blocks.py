@@ -93,8 +93,8 @@ def _data_gradient_kernels(N, C, Cout, H, W, k, x, y):
 
 
 @pytest.mark.parametrize("N,C,Cout,H,W,k,x,groups,p", [
-    (2, 64, 64, 8, 36, 7, 144, 1, 0.5), (1, 192, 64, 28, 29, 7, 29, 1, 0.4), (2, 128, 8, 21, 24, 7, 72, 1, 0.5), (6, 256, 64, 31, 27, 3, 81, 2, 0.3),
-    (3, 128, 24, 20, 17, 7, 340, 2, 0.5), (2, 192, 24, 20, 21, 7, 147, 1, 0.6), (4, 384, 8, 10, 40, 5, 40, 2, 0.5), (2, 128, 100, 29, 39, 7, 273, 1, 0.4),
+    (4, 64, 48, 16, 36, 7, 144, 1, 0.5), (1, 192, 64, 28, 29, 7, 29, 1, 0.4), (2, 128, 8, 21, 24, 7, 72, 1, 0.5), (9, 512, 40, 31, 27, 3, 81, 2, 0.3),
+    (3, 128, 24, 20, 17, 7, 340, 2, 0.5), (2, 192, 24, 20, 21, 7, 147, 1, 0.6), (6, 128, 8, 16, 40, 7, 40, 2, 0.5), (5, 64, 8, 27, 35, 5, 140, 1, 0.5), (2, 128, 100, 29, 39, 7, 273, 1, 0.4),
     (4, 128, 24, 24, 40, 5, 80, 2, 0.0), (4, 128, 24, 24, 40, 5, 80, 2, 1.0)])
 def test_data_gradient_over_tiles(N, C, Cout, H, W, k, x, groups, p):
     """Tiles of several bands, one and part of one, one and two groups of 64 channels per block, one and more than 64 steps, planes
@@ -123,7 +123,7 @@ def test_data_gradient_over_tiles(N, C, Cout, H, W, k, x, groups, p):
 
 
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
-@pytest.mark.parametrize("N,C,Cout,H,W,k,x,groups", [(2, 128, 64, 38, 31, 5, 93, 1), (3, 64, 40, 13, 28, 5, 196, 1), (2, 64, 80, 13, 28, 3, 56, 1)])
+@pytest.mark.parametrize("N,C,Cout,H,W,k,x,groups", [(2, 128, 64, 38, 31, 5, 93, 1), (3, 64, 40, 26, 28, 5, 196, 1), (2, 64, 80, 13, 28, 3, 56, 1)])
 def test_data_gradient_with_a_weight_that_is_not_finite(N, C, Cout, H, W, k, x, groups, bad):
     """It reaches the pixels that a kept entry was cut from through its tap, and no other."""
     print("blocks data gradient not finite", N, C, Cout, H, W, k, x, groups, bad, flush=True)

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from dryrun import FakeHeap, dry_run, launches
 from oracle import sensitivity as S
 from paper_2203_05705_amd import binding as ard
 from util import assert_parity, from_vals, stored
@@ -39,9 +40,10 @@ def test_row_pattern(N, C, Cout, H, W, k, p):
 
 
 @pytest.mark.parametrize("N,C,Cout,H,W,k,x,group", [
-    (2, 64, 16, 13, 13, 3, 5, 16), (3, 96, 130, 16, 16, 3, 100, 32), (2, 80, 24, 28, 28, 3, 56, 48), (40, 48, 256, 7, 7, 3, 49, 16), (2, 130, 40, 20, 12, 5, 7, 64)])
+    (2, 64, 16, 13, 13, 3, 5, 16), (3, 96, 130, 16, 16, 3, 100, 32), (2, 80, 24, 28, 28, 3, 56, 48), (40, 48, 256, 7, 7, 3, 49, 16), (2, 130, 40, 20, 12, 5, 7, 64), (2, 64, 8, 39, 40, 5, 100, 64)])
 def test_block_pattern(N, C, Cout, H, W, k, x, group):
-    """Column blocks of 16 and more channels, the last one smaller; bands that end anywhere in a row."""
+    """Column blocks of 16 and more channels, the last one smaller; bands that end anywhere in a row.  (The last layer's one column
+    block takes a pass over all positions of a masked copy, which the weight gradient shares.)"""
     print("blocks", N, C, Cout, H, W, k, x, group, flush=True)
     rng, (A, Wt, dY), (Ad, Wd, dYd) = _layer(N, C, Cout, H, W, k, C + x)
     y = group * k * k
@@ -66,3 +68,25 @@ def test_an_infinity_stays_where_it_belongs():
     assert bad[0, :, 3:6, 3:6].all()
     bad[0, :, 3:6, 3:6] = False
     assert not bad.any()
+
+
+@pytest.mark.parametrize("N,C,Cout,S_,share", [(16, 448, 127, 16, 0.3), (16, 448, 127, 16, 1.0), (40, 256, 200, 28, 0.3), (40, 256, 200, 28, 1.0)])
+def test_the_number_of_kept_rows_only_chooses(N, C, Cout, S_, share):
+    """The gradient of FWD_ROWS with its number of kept rows, without it and with a number that cannot be: the same sums."""
+    print("rows hint", N, C, Cout, S_, share, flush=True)
+    rng, (_, Wt, dY), (_, Wd, dYd) = _layer(N, C, Cout, S_, S_, 3, C)
+    mask = (rng.uniform(size=(N, S_ * S_)) < share).astype(np.uint8)
+    md = torch.from_numpy(mask.reshape(-1)).cuda()
+    used = []
+    for n_keep in (int(mask.sum()), 0, -5, N * S_ * S_ + 1):
+        with dry_run() as lib:
+            n, p = lib.ard_conv_workspace_bytes(ard.BF16, N, C, S_, S_, Cout, 3, 3, 1, 1), FakeHeap()(1 << 20)
+            launches(lib)
+            assert lib.ard_fmap_drop_conv(5, ard.BF16, N, C, S_, S_, Cout, 3, 3, 1, 1, 0.0, n_keep, None, p, p, p, p, None, None, None, p, n, None) == 0
+            used.append("conv_scatter_data_kernel" in launches(lib)[1])
+        dA = torch.full((N, C, S_, S_), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ard.fmap_drop_conv(5, (N, C, S_, S_), ard.BF16, Cout, (3, 3), 1, 1, n_keep=n_keep, Wt=Wd, dY=dYd, out=dA, mask=md)
+        idx = [0, N - 1]
+        ref, _ = S.conv_bwd_rows(dY[idx], np.zeros((2, C, S_, S_)), Wt, mask[idx], 1, 1)
+        assert_parity(dA[idx], ref, "bf16", None, "dA")
+    assert used[1] == used[2] == used[3] and used[0] == (share < 0.5)
