@@ -526,6 +526,12 @@ __global__ void scale_fill_kernel(T* p, long n, float beta) {
 // max_bn: the widest column tile the contraction lists allow (tile pattern), or 0.
 int32_t run_gemm(int32_t dtype, bool a_kc, bool b_kc, GemmParams P, int max_bn, int max_bm, hipStream_t stream,
                  void* ws = nullptr, size_t ws_bytes = 0);
+// The most fp32 partial sums that run_gemm makes of a plain bf16 product: it splits no contraction from 160 tiles of 64 x 64 on,
+// below that into at most 8 parts and 320 tiles altogether.
+static inline size_t split_part_bytes(long M, long N) {
+  const long tiles = ((M + 63) / 64) * ((N + 63) / 64);
+  return tiles < 1 || tiles >= 160 ? 0 : (size_t)(320 / tiles > 8 ? 8 : 320 / tiles) * (size_t)(M * N) * 4;
+}
 bool run_gemm_partials(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P, hipStream_t stream, void* part,
                        size_t part_bytes, int* splits, int32_t* status);
 

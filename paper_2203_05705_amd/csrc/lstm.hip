@@ -1201,9 +1201,10 @@ struct LstmWs {
   float* dc_next;  // [B x H]
   char* dwx;     // [4Hp x Ip] dtype
   char* dwh;     // [4Hp x Hp] dtype
-  char* part;    // fp32 partial sums of split products: three regions of part_bytes (the products at the end of the
-                 // backward pass run together)
+  char* part;    // fp32 partial sums of split products
   size_t part_bytes;
+  char *part_dwx, *part_dx;  // bf16: those of two products that run together with one whose sums are in `part` (fp32: `part`)
+  size_t part_dwx_bytes, part_dx_bytes;
   int* sync;     // step counters (one per batch block of 32 rows) and the give-up flag of the one-launch recurrence
   size_t total;
 };
@@ -1238,7 +1239,12 @@ static LstmWs lstm_ws_layout(char* base, int es, int T, int B, int I, int H, int
   if ((size_t)B * 4 * Hp > big) big = (size_t)B * 4 * Hp;
   w.part_bytes = big * 4 * 8;
   if (w.part_bytes > ((size_t)256 << 20)) w.part_bytes = (size_t)256 << 20;
-  w.part = take(3 * align_up(w.part_bytes, 256));
+  w.part = take(w.part_bytes);
+  w.part_dwx = w.part_dx = w.part, w.part_dwx_bytes = w.part_dx_bytes = w.part_bytes;
+  if (es == 2) {  // (fp32 products run one after the other)
+    w.part_dwx_bytes = split_part_bytes(4 * (long)Hp, (long)Ip), w.part_dx_bytes = split_part_bytes((long)T * B, (long)Ip);
+    w.part_dwx = take(w.part_dwx_bytes), w.part_dx = take(w.part_dx_bytes);
+  }
   w.sync = (int*)take(((size_t)pad8(Hk) / 8 * ((size_t)B / 32 + 1) + 8 + kLxBlocks * kLxSeats) * 4);
   w.total = off;
   return w;
@@ -1694,7 +1700,6 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     // One after the other, each left CUs idle in its last round, or had fewer tiles than there are CUs (T = 64, B = 128,
     // I = H = 1024, dp = 2: 512 tiles, then 256, of 128 steps each).
     BatchOwn together;
-    const size_t region = align_up(w.part_bytes, 256);
     if (T_ > 1) {
       GemmParams P = plain_gemm(dG + (long)B * 4 * Hp, 4 * Hp, w.hc, Hp, w.dwh, Hp, 4 * Hp, Hp, (T_ - 1) * B, false, false, ce, false, 0.0f);
       st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part, w.part_bytes);
@@ -1703,11 +1708,11 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     }
     if (st) return st;
     GemmParams P = plain_gemm(dG, 4 * Hp, xs, Ip, w.dwx, Ip, 4 * Hp, Ip, T_ * B, false, false, ce, false, 0.0f);
-    st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part + region, w.part_bytes);
+    st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part_dwx, w.part_dwx_bytes);
     if (st) return st;
     void* dxo = Ip != I ? (void*)w.dxp : dx;
     P = plain_gemm(dG, 4 * Hp, w.wxc, Ip, dxo, Ip, T_ * B, Ip, 4 * Hp, true, false, ce, false, 0.0f);
-    st = run_gemm(a.dtype, true, false, P, 0, 0, stream, w.part + 2 * region, w.part_bytes);
+    st = run_gemm(a.dtype, true, false, P, 0, 0, stream, w.part_dx, w.part_dx_bytes);
     if (st) return st;
     st = together.launch(stream);
     if (st) return st;

@@ -284,6 +284,19 @@ def test_lstm_operands_beyond_one_launch(dtype):
         D.last_bounds(lib)
 
 
+@pytest.mark.parametrize("dtype", [D.F32, D.BF16])
+def test_lstm_workspace_holds_the_partial_sums_of_one_product(dtype):
+    """Beside its operands a workspace has room for the largest product split 8 ways (at most 256 MiB) and, bf16, for what two
+    more products can split into: 320 tiles of 64 x 64 each."""
+    with D.dry_run() as lib:
+        for T, B, I, H in ((64, 128, 1024, 1024), (35, 20, 1500, 1500), (8, 45, 56, 56), (64, 8, 4096, 2048), (100, 128, 64, 64)):
+            es, Hp, Ip = 2 if dtype == D.BF16 else 4, -(-H // 8) * 8, -(-I // 8) * 8
+            part = min(8 * 4 * 4 * Hp * max(Ip, Hp, B), 256 << 20)
+            operands = es * (8 * Hp * (Ip + Hp) + 2 * T * B * Ip + T * (B + 31) * (Hp + 23)) + 16 * T * (B + 15) * (Hp + 23) + 4 * B * (Hp + H)
+            more = 2 * 320 * 64 * 64 * 4 if dtype == D.BF16 else 0
+            assert lib.ard_lstm_workspace_bytes(dtype, T, B, I, H, None) <= operands + part + more + (1 << 18), (T, B, I, H)
+
+
 def test_lstm_shapes_reach_the_recurrences_their_gpu_tests_name():
     from test_gpu_lstm_staged import BEYOND_BWD, BEYOND_FWD
     with D.dry_run() as lib:
