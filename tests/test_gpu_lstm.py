@@ -193,3 +193,33 @@ def test_lstm_operands_in_several_launches(dtype, pieces, monkeypatch):
     x, dh = (stored(rng.standard_normal(s), dtype) for s in ((T, B, I), (T, B, H)))
     W = stored(rng.uniform(-0.2, 0.2, (4 * H, I + H)), dtype)
     _check(dtype, x, W, dh, P.row_mask(H, dp, 2), ard.Pattern.row(dp, 2), *(from_vals(v, dtype) for v in (x, W, dh)), f"lstm {dtype} {pieces} pieces")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,B,I,H,dp", [(4, 16, 40, 64, 1), (100, 128, 64, 64, 1), (12, 64, 512, 512, 2), (1, 8, 24, 40, 2)])
+def test_lstm_between_the_calls_of_a_batch(dtype, T, B, I, H, dp):
+    """Both passes inside an open batch run at once, whatever the batch has recorded, and leave that as it was: their results and
+    those of the batch are what the calls give one by one.  (The second layer's weight gradients are split, bf16: partial
+    sums of their own in the launch that they share.)"""
+    print("lstm in a batch", dtype, T, B, I, H, dp, flush=True)
+    rng = np.random.default_rng(T + H)
+    x, dh = (from_vals(stored(rng.standard_normal(s), dtype), dtype) for s in ((T, B, I), (T, B, H)))
+    W = from_vals(stored(rng.uniform(-0.1, 0.1, (4 * H, I + H)), dtype), dtype)
+    X, V, dY = (from_vals(stored(rng.standard_normal(s), "bf16"), "bf16") for s in ((64, 256), (128, 256), (64, 128)))
+    pat, po = ard.Pattern.row(dp, 1), ard.Pattern.row(2, 1)
+    ws = [torch.empty(ard.gemm_workspace_bytes(ard.BF16, 64, 256, 128, po, None), dtype=torch.uint8, device="cuda") for _ in range(2)]
+
+    def calls():
+        Y = ard.drop_gemm_fwd(X, V, po, flags=ard.OUT_COMPACT, ws=ws[0])
+        h, c, gates = ard.lstm_fwd(x, W, pat)
+        dx, dW = ard.lstm_bwd(x, W, pat, h, c, gates, dh)
+        dV = ard.drop_gemm_bwd_weight(dY, X, po, ws=ws[1])
+        return h, c, gates, dx, dW, Y, dV
+    alone = calls()
+    with ard.batch():
+        grouped = calls()
+        torch.cuda.synchronize()
+        for a, g in zip(alone[:5], grouped[:5]):   # (the LSTM's do not wait for the batch)
+            assert torch.equal(a, g)
+    for name, a, g in zip(("h", "c", "gates", "dx", "dW", "Y", "dV"), alone, grouped):
+        assert torch.equal(a, g), name
