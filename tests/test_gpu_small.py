@@ -129,3 +129,36 @@ def test_compact_activations(B, I, O, dp, dp_in, grouped):
     assert_parity(dXc[:, :len(ki)].contiguous(), (dXr * (Xv > 0))[:, ki], "bf16", None, "dX compact")
     assert_parity(Y, Yr, "bf16", (mo == 0)[None, :], "Y")
     assert not Yc[:, len(ko):].any() and not dXc[:, len(ki):].any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dp,dp_in", [(1, 1), (1, 2), (1, 3), (1, 4), (3, 1), (1, 6)])
+def test_grouped_results_are_those_of_the_calls_alone(dp, dp_in):
+    """Four wavefronts with two sums each (grouped) and eight with one (alone; four, where there are more than 256 tiles and at
+    most four slices): contractions that end in each of the eight sums, with whole slices of 32 and with a part of one."""
+    for B, k, N in [(40, 32 * s + t, 70) for s in (1, 2, 3, 5, 7, 8, 9, 12, 16, 17, 21, 31) for t in (0, 9)] + [(600, 100, 520), (520, 128, 600)]:
+        print("small grouped", B, k, N, dp, dp_in, flush=True)
+        I, O = k * dp_in, N * dp   # (k kept inputs in the forward pass, N kept outputs)
+        _, (X, W, dY) = _layer(B, I, O)
+        po, pi = (ard.Pattern.row(dp, dp) if dp > 1 else None), (ard.Pattern.row(dp_in, 1) if dp_in > 1 else None)
+        with dry_run() as lib:
+            launches(lib)
+            layer_calls(lib, FakeHeap(), ard.BF16, B, I, O, (dp, dp) if dp > 1 else None, (dp_in, 1) if dp_in > 1 else None, ard.IN_COMPACT | ard.OUT_COMPACT)
+            assert launches(lib)[1].count("gemm_small_kernel") >= (3 if dp_in > 1 and k <= 544 else 0)
+        kept = lambda M, d, b: ard.pad_compact(M[:, b - 1::d].contiguous())
+        Xc, dYc = kept(X, dp_in, 1), kept(dY, dp, dp)
+        Wc = ard.compact_weight(W, po, pi)
+        ws = [torch.full((ard.gemm_workspace_bytes(ard.BF16, B, I, O, po, pi),), 0xFF, dtype=torch.uint8, device="cuda") for _ in range(4)]
+        both = ard.IN_COMPACT | ard.OUT_COMPACT
+        dW = [torch.full((O, I), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+
+        def calls(i):
+            return (ard.drop_gemm_fwd(Xc, W, po, pi, relu=True, flags=both, I=I, O=O, ws=ws[0]),
+                    ard.drop_gemm_bwd_data(dYc, W, po, pi, relu_src=Xc, flags=both, I=I, O=O, ws=ws[1]),
+                    ard.drop_gemm_fwd(Xc, Wc, po, pi, flags=ard.IN_COMPACT | ard.W_COMPACT, I=I, O=O, ws=ws[2]),
+                    ard.drop_gemm_bwd_weight(dYc, Xc, po, pi, flags=both, I=I, O=O, out=dW[i], ws=ws[3]))
+        alone = calls(0)
+        with ard.batch():
+            grouped = calls(1)
+        for name, a, g in zip(("Y compact", "dX compact", "Y", "dW"), alone, grouped):
+            assert torch.equal(a, g), (name, B, I, O)
