@@ -719,6 +719,18 @@ static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0,
   const double weight = op == 2 ? 0.8 : op == 0 ? (wide == 1 || wide == 2 ? 1.0 : 1.6) : wide == 0 ? 1.8 : wide == 4 ? 1.2 : 1.0;
   const bool copies = op == 0 ? plan.x || plan.w : op == 2 || plan.w;
   if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000) return false;
+  // Where kept neurons lie far apart, a workgroup is bound by the lines its operands' elements touch (50 GB/s a CU) and by the zeros
+  // of what it owns (0.4 us for 512 pieces of 16 bytes, 0.85 where it spreads rows only); the copies and the finishing
+  // pass spread both over all CUs.  4365 products of up to 20000 neurons, 1 to 64 apart, against the other way: below these lines
+  // 1.4 to 1.8 times as fast in the mean, above them 0.5 (8 x 1192 by 8 x 1544, 64 and 48: 11 against 117 us; 98 x 14361 by 14361 x 926,
+  // 24: 13 against 42).
+  {
+    auto touched = [](int n, int step) { return (double)imin(32, n) * imin(2 * step, 128); };
+    const double rounds = tiles > 256 ? (double)tiles / 256.0 : 1.0;
+    const double fetched = ka.n * (touched(m.n, op == 2 ? am.step : ka.step) + touched(n.n, op == 0 ? kb.step : bn.step));
+    const double pieces = (double)imin(32, m.n) * m.step * ((imin(32, n.n) * n.step + 7) / 8);
+    if (rounds * (fetched / 50e3 + pieces / 512.0 * (op == 2 ? 0.42 : 0.85)) > (op == 2 ? 8.0 : 10.0)) return false;
+  }
   // (results whose rows start anywhere leave in pieces that cross lines, which costs more than the copies where they are large:
   // 44 rows, 1719 -> 3854, weight gradient, in a network's step of 63.5 us 1.5 us more; 45 rows, 3161 -> 1065 less)
   const bool whole = (op == 0 ? yo.nphys : op == 1 ? xi.nphys : a.I) % 8 == 0 && ((uintptr_t)out & 15) == 0;

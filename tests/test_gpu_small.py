@@ -162,3 +162,32 @@ def test_grouped_results_are_those_of_the_calls_alone(dp, dp_in):
             grouped = calls(1)
         for name, a, g in zip(("Y compact", "dX compact", "Y", "dW"), alone, grouped):
             assert torch.equal(a, g), (name, B, I, O)
+
+
+FAR = [(8, 1192, 1544, 48, 64), (33, 776, 1030, 64, 3), (40, 2304, 96, 1, 24), (17, 130, 3001, 32, 2), (600, 640, 1280, 16, 16)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,I,O,dp,dp_in", FAR)
+def test_neurons_far_apart(B, I, O, dp, dp_in):
+    """Steps of up to 64, on either side of the line behind which copies and a finishing pass are faster."""
+    print("small far apart", B, I, O, dp, dp_in, flush=True)
+    (Xv, Wv, dYv), (X, W, dY) = _layer(B, I, O)
+    for b, b_in in ((1, 1), (dp, dp_in)):
+        mo, mi = P.row_mask(O, dp, b), P.row_mask(I, dp_in, b_in)
+        MW = G.weight_mask_rows(mo, mi)
+        po, pi = (ard.Pattern.row(dp, b) if dp > 1 else None), (ard.Pattern.row(dp_in, b_in) if dp_in > 1 else None)
+        assert_parity(ard.drop_gemm_fwd(X, W, po, pi), G.drop_gemm_fwd(Xv, Wv, MW, mo), "bf16", (mo == 0)[None, :], "Y")
+        assert_parity(ard.drop_gemm_bwd_data(dY, W, po, pi), G.drop_gemm_bwd_data(dYv, Wv, MW, mo), "bf16", (mi == 0)[None, :], "dX")
+        assert_parity(ard.drop_gemm_bwd_weight(dY, X, po, pi), G.drop_gemm_bwd_weight(dYv, Xv, MW, mo), "bf16", MW == 0, "dW")
+
+
+def test_which_products_of_neurons_far_apart_are_one_launch():
+    with dry_run() as lib:
+        got = []
+        for B, I, O, dp, dp_in in FAR:
+            for op in range(3):
+                launches(lib)
+                assert layer_calls(lib, FakeHeap(), ard.BF16, B, I, O, (dp, dp) if dp > 1 else None, (dp_in, 1) if dp_in > 1 else None, 0, ops=(op,)) == [0]
+                got.append(launches(lib)[1] == ["gemm_small_kernel"])
+        assert got == [True, True, False, True, True, False, True, True, True, True, True, True, True, True, False], got
