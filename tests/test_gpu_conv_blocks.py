@@ -38,10 +38,10 @@ def test_forward(N, C, Cout, H, W, k, pad, x, groups, p):
 @pytest.mark.parametrize("N,C,Cout,H,W,k,pad,x,cpb,p", [
     (1, 16, 1, 7, 7, 3, 1, 12, 16, 0.5), (3, 64, 24, 13, 13, 3, 1, 52, 64, 0.4), (2, 100, 33, 9, 10, 3, 0, 17, 37, 0.5), (2, 48, 40, 14, 14, 5, 2, 28, 3, 0.3),
     (3, 64, 65, 12, 8, 3, 2, 20, 64, 0.6), (4, 32, 16, 16, 16, 1, 0, 256, 7, 0.5), (2, 128, 64, 16, 16, 3, 1, 32, 64, 0.0), (2, 128, 64, 16, 16, 3, 1, 32, 64, 1.0),
-    (2, 40, 16, 10, 10, 3, 1, 30, 2, 0.5)])
+    (2, 40, 16, 10, 10, 3, 1, 30, 2, 0.5), (2, 160, 16, 10, 10, 5, 2, 30, 10, 0.5), (6, 16, 2, 19, 19, 1, 0, 19, 1, 0.5)])
 def test_forward_f32(N, C, Cout, H, W, k, pad, x, cpb, p):
-    """fp32: one pass per column block, up to 16 of them and the first number beyond, the last with fewer channels; what no
-    kept block reads does not have to be finite."""
+    """fp32: one pass per column block, up to 16 of them and the first number beyond, the last with fewer channels, or one over the
+    patches of all where blocks are many and small; what no kept block reads does not have to be finite."""
     print("blocks forward f32", N, C, Cout, H, W, k, pad, x, cpb, p, flush=True)
     rng = np.random.default_rng(C + H + Cout)
     A, Wt = (stored(rng.standard_normal(s) * 0.5, "f32") for s in ((N, C, H, W), (Cout, C, k, k)))

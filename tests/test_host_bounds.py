@@ -284,6 +284,21 @@ def test_lstm_operands_beyond_one_launch(dtype):
         D.last_bounds(lib)
 
 
+def test_fp32_block_patterns_of_many_small_blocks_stay_in_one_pass():
+    """A pass per column block where it is expected to be faster, else one over the patches of all."""
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        for (N, Cc, Cout, S, k, cpb), passes in [((8, 64, 16, 16, 3, 64), 1), ((75, 64, 330, 16, 3, 32), 2), ((2, 48, 40, 14, 5, 3), 16),
+                                                 ((2, 160, 16, 10, 5, 10), 16), ((2, 170, 16, 10, 5, 10), 0), ((36, 16, 2, 19, 1, 1), 0),
+                                                 ((14, 32, 96, 28, 1, 2), 0), ((23, 8, 8, 13, 1, 1), 0)]:
+            n = lib.ard_conv_workspace_bytes(D.F32, N, Cc, S, S, Cout, k, k, 1, k // 2)
+            ws, p = heap(n), heap(1 << 20)
+            D.launches(lib)
+            _ok(lib, [lib.ard_conv_fwd_blocks(D.F32, N, Cc, S, S, Cout, k, k, 1, k // 2, S, cpb * k * k, p, p, p, p, ws, n, None)], "fp32 blocks")
+            names = D.launches(lib)[1]
+            assert names.count("add_bands_kernel") == passes and ("conv_gemm_kernel" in names) == (passes == 0), (N, Cc, Cout, S, k, cpb, names)
+
+
 @pytest.mark.parametrize("dtype", [D.F32, D.BF16])
 def test_lstm_workspace_holds_the_partial_sums_of_one_product(dtype):
     """Beside its operands a workspace has room for the largest product split 8 ways (at most 256 MiB) and, bf16, for what two
