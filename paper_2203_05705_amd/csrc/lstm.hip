@@ -1456,6 +1456,13 @@ static bool lstm_step32(const LstmArgs& a) {
   return a.dtype == ARD_F32 && a.Hk > 0 && (long)ceil_div(a.B, 16) * a.Hk * a.Hk <= (1L << 21) && a.ax.kind == AX_AFFINE && a.ax.off < a.ax.step;
 }
 
+// (The forward kernel's threads write the zeros of their unit's dropped neighbours one after the other, which eats it where full tiles
+// own units far apart: every eighth unit, 38 rows, 894 units, 8 steps 59 us with two launches a step and 77 with one, 8 rows, 626
+// units 56 and 52.  One step alone has no product.)
+static bool lstm_step32_fwd(const LstmArgs& a) {
+  return lstm_step32(a) && a.T > 1 && (long)imin(a.B, 16) * imin(a.Hk, 16) * a.ax.step <= 1024;
+}
+
 template <typename T>
 static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void* h, float* c, float* gates,
                           const LstmWs& w, hipStream_t stream) {
@@ -1540,7 +1547,7 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
     ARD_LAUNCH_CHECK("lstm_persist_fwd_kernel");
     return ARD_OK;
   }
-  if (lstm_step32(a)) {
+  if (lstm_step32_fwd(a)) {
     for (int t = 0; t < T_; ++t) {
       LstmStep32 P{};
       P.whc = (const float*)w.whc;
