@@ -718,7 +718,8 @@ static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0,
   const int ks = ceil_div(ka.n, 32);
   const double weight = op == 2 ? 0.8 : op == 0 ? (wide == 1 || wide == 2 ? 1.0 : 1.6) : wide == 0 ? 1.8 : wide == 4 ? 1.2 : 1.0;
   const bool copies = op == 0 ? plan.x || plan.w : op == 2 || plan.w;
-  if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000) return false;
+  // (more tiles than six a CU: 3951 x 10 by 10 x 968 11 -> 19, 7 rows, 1064 -> 3614, weight gradient, 10 -> 16)
+  if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000 || tiles > 1500) return false;
   // Where kept neurons lie far apart, a workgroup is bound by the lines its operands' elements touch (50 GB/s a CU) and by the zeros
   // of what it owns (0.4 us for 512 pieces of 16 bytes, 0.85 where it spreads rows only); the copies and the finishing
   // pass spread both over all CUs.  4365 products of up to 20000 neurons, 1 to 64 apart, against the other way: below these lines
