@@ -14,7 +14,7 @@ from util import assert_parity, from_vals, stored
 pytestmark = pytest.mark.gpu
 
 CASES = [(1, 1, 1, 32, 32, 1, 1), (37, 33, 65, 32, 32, 2, 1), (64, 90, 128, 64, 64, 3, 2), (130, 128, 95, 32, 32, 2, 2), (226, 292, 1269, 32, 32, 2, 1),
-         (21, 1423, 384, 64, 64, 1, 1), (1000, 503, 337, 64, 64, 5, 3), (513, 1030, 1001, 32, 64, 8, 8), (96, 2049, 777, 128, 64, 6, 4)]
+         (21, 1423, 384, 64, 64, 1, 1), (1000, 503, 337, 64, 64, 5, 3), (513, 1030, 1001, 32, 64, 8, 8), (96, 2049, 777, 128, 64, 6, 4), (23, 803, 399, 128, 256, 2, 1), (64, 555, 1030, 256, 256, 3, 2)]
 
 
 def _operands(B, I, O, skew=0):

@@ -86,6 +86,16 @@ def test_ragged_tile_patterns():
         assert D.last_bounds(lib)[0] > 48
 
 
+def test_ragged_tile_weight_gradients_of_few_rows_in_few_large_tiles():
+    """Rows that start at odd elements, tiles of 256 columns: up to 63 rows and 32 tiles on the general engine."""
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        for (B, I, O, x, dp), general in (((23, 803, 399, 128, 2), True), ((64, 803, 399, 128, 2), False), ((23, 804, 399, 128, 2), False), ((23, 8003, 3999, 256, 2), False)):
+            D.launches(lib)
+            _ok(lib, D.layer_calls(lib, heap, D.BF16, B, I, O, (dp, 1), None, 0, tile=(x, 256), ops=(2,)), f"ragged {B} {I} {O}")
+            assert ("gemm_kernel" in D.launches(lib)[1]) == general, (B, I, O)
+
+
 def test_the_shape_that_faulted_once():
     """W 2480 x 2760 with 256-row tiles: the last tile row holds 176 rows (block axes are clamped)."""
     with D.dry_run() as lib:
