@@ -2252,7 +2252,8 @@ extern "C" int32_t ard_conv_bwd_blocks(int32_t mode, int32_t dtype, int32_t N, i
     ConvArgs g = a;
     g.blk = nullptr;
     g.cpb = a.by / taps;
-    g.reuse = one_launch || CB == 1 ? reuse : 0;  // (else the data gradient left dY masked for its last column block)
+    // (else the data gradient left dY masked for its last column block, or on a grid of another shape)
+    g.reuse = one_launch || (CB == 1 && kh - 1 == 2 * pad && kw - 1 == 2 * pad) ? reuse : 0;
     return conv_run<uint16_t>(g, 0.0, A, Wt, dYin, out, nullptr, nullptr, nullptr, nullptr, w, s);
   }
   const PosListJob lists = a.lists;

@@ -294,6 +294,21 @@ def test_lstm_operands_beyond_one_launch(dtype):
         D.last_bounds(lib)
 
 
+def test_block_gradients_share_the_copy_of_dY_where_one_is_left():
+    """The weight gradient takes the flag for any filter, and the copy itself where the data gradient left one that it can read: one
+    column block or several, filters that keep the image's size and others."""
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        for C, k, pad, x, y, shared in ((64, 3, 1, 50, 576, True), (64, 5, 2, 100, 0, True), (128, 3, 1, 40, 576, True), (64, 3, 0, 50, 576, False),
+                                        (64, 3, 2, 50, 0, False), (128, 5, 0, 50, 1600, False), (24, 3, 1, 50, 72, False)):
+            n = lib.ard_conv_workspace_bytes(D.BF16, 2, C, 40, 40, 8, k, k, 1, pad)
+            ws, p = heap(n), heap(1 << 24)
+            for mode in (2, 3 | 0x200):
+                D.launches(lib)
+                _ok(lib, [lib.ard_conv_bwd_blocks(mode, D.BF16, 2, C, 40, 40, 8, k, k, 1, pad, x, y, p, p, p, p, p, ws, n, None)], f"{C} {k} {pad} {mode}")
+            assert (D.launches(lib)[1].count("to_grid_src_kernel") == 1) == shared, (C, k, pad, x, y)
+
+
 def test_fp32_block_patterns_of_many_small_blocks_stay_in_one_pass():
     """A pass per column block where it is expected to be faster, else one over the patches of all."""
     with D.dry_run() as lib:
