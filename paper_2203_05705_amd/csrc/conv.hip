@@ -99,11 +99,13 @@ __global__ __launch_bounds__(256) void channel_score_kernel(const T* A, int N, i
 
 // Adds the `parts` partial scores of every map (score_out gets the totals), then drops the n_drop maps that
 // come first in ascending (score, index) order; writes the mask (1 = kept) and the ascending kept list
-// (ballot + mbcnt compaction, one workgroup).  The rank of a map is counted by four threads, a quarter
-// of the other maps each, first over the scores rounded to 32-bit floats (a map is dropped if fewer than n_drop are
-// smaller): one comparison a map from 16-byte LDS reads, where 64-bit scores and indices took four and more (384 maps: 20.6 -> 7.3 us,
-// 389 maps 15.1 -> 7.7; 64 maps 5 us either way, so up to there it is not done).  Only if maps with the same rounded score make that more than n_drop is the whole count done again
-// over scores and indices (all scores alike: 1.15 to 1.25 times as long as that count alone).  IN_LDS: the scores fit the staging array (else they are re-read from memory).
+// (ballot + mbcnt compaction, one workgroup).  The rank of a map is counted by four threads, a quarter of the
+// other maps each.  From 64 maps on they first count over the scores rounded to 32-bit floats (a map is dropped
+// if fewer than n_drop are smaller): one comparison a map from 16-byte LDS reads, where 64-bit scores and
+// indices take four and more (384 maps 20.6 -> 7.3 us, 389 15.1 -> 7.7, 64 to 127 maps 1.07 times as fast;
+// fewer gain nothing).  Only if maps with the same rounded score make that more than n_drop is the whole count
+// done again over scores and indices (all scores alike: 1.06 to 1.25 times as long as that count alone).
+// IN_LDS: the scores fit the staging array (else they are re-read from memory).
 // The code is kept short on purpose: a single workgroup that runs once pays every instruction-cache line it
 // touches with a fetch from memory (3 KB of straight-line code took 10 us for 256 maps).
 template <bool IN_LDS>
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(1024) void channel_select_kernel(const unsigned lon
   const int n_kept = min(max(C - n_drop, 0), C);
   const bool count_all = n_kept > 0 && n_kept < C;
 #pragma unroll 1
-  for (int exact = IN_LDS && C > 64 ? 0 : 1; exact < 2; ++exact) {
+  for (int exact = IN_LDS && C >= 64 ? 0 : 1; exact < 2; ++exact) {
     for (int base = 0; base < C; base += 256) {
       const int c = base + (tid >> 2), part_id = tid & 3;
       int rank = 0;
