@@ -1458,9 +1458,9 @@ static bool lstm_step32(const LstmArgs& a) {
 
 // (The forward kernel's threads write the zeros of their unit's dropped neighbours one after the other, which eats it where full tiles
 // own units far apart: every eighth unit, 38 rows, 894 units, 8 steps 59 us with two launches a step and 77 with one, 8 rows, 626
-// units 56 and 52.  One step alone has no product.)
+// units 56 and 52.  Every sixth, 25 rows, 160 units 58 and 43, 17 rows, 1216 units 63 and 55.  One step alone has no product.)
 static bool lstm_step32_fwd(const LstmArgs& a) {
-  return lstm_step32(a) && a.T > 1 && (long)imin(a.B, 16) * imin(a.Hk, 16) * a.ax.step <= 1024;
+  return lstm_step32(a) && a.T > 1 && (long)imin(a.B, 16) * imin(a.Hk, 16) * a.ax.step <= 1536;
 }
 
 template <typename T>
