@@ -724,17 +724,21 @@ static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0,
   const bool copies = op == 0 ? plan.x || plan.w : op == 2 || plan.w;
   // (more tiles than six a CU: 3951 x 10 by 10 x 968 11 -> 19, 7 rows, 1064 -> 3614, weight gradient, 10 -> 16)
   if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000 || tiles > 1500) return false;
-  // Where kept neurons lie far apart, a workgroup is bound by the lines its operands' elements touch (50 GB/s a CU) and by the zeros
-  // of what it owns (0.4 us for 512 pieces of 16 bytes, 0.85 where it spreads rows only); the copies and the finishing
-  // pass spread both over all CUs.  4365 products of up to 20000 neurons, 1 to 64 apart, against the other way: below these lines
-  // 1.4 to 1.8 times as fast in the mean, above them 0.5 (8 x 1192 by 8 x 1544, 64 and 48: 11 against 117 us; 98 x 14361 by 14361 x 926,
-  // 24: 13 against 42).
+  // Where kept neurons lie far apart, a workgroup is bound by the lines its operands' elements touch and by the zeros of what it owns;
+  // the copies and the finishing pass spread both over all CUs (8 x 1192 by 8 x 1544, 64 and 48 apart: 11 against 117 us; 98 x
+  // 14361 by 14361 x 926, 24: 13 against 42).  Times of both in us, fitted to 5351 products of up to 8192 neurons, 1 to 64 apart: within
+  // 0.5, 0.3 and 1 % (forward, data, weight gradient) of the faster one in the mean.
   {
     auto touched = [](int n, int step) { return (double)imin(32, n) * imin(2 * step, 128); };
-    const double rounds = tiles > 256 ? (double)tiles / 256.0 : 1.0;
-    const double fetched = ka.n * (touched(m.n, op == 2 ? am.step : ka.step) + touched(n.n, op == 0 ? kb.step : bn.step));
-    const double pieces = (double)imin(32, m.n) * m.step * ((imin(32, n.n) * n.step + 7) / 8);
-    if (rounds * (fetched / 50e3 + pieces / 512.0 * (op == 2 ? 0.42 : 0.85)) > (op == 2 ? 8.0 : 10.0)) return false;
+    const double rounds = tiles > 256 ? (double)tiles / 256.0 : 1.0, slices = ks / 8.0;
+    const double fetched = 1e-5 * ka.n * (touched(m.n, op == 2 ? am.step : ka.step) + touched(n.n, op == 0 ? kb.step : bn.step));
+    const double pieces = (double)imin(32, m.n) * m.step * ((imin(32, n.n) * n.step + 7) / 8) / 512.0;
+    const double written = 1e-6 * m.nphys * n.nphys, spread = dense(m) && dense(n) ? 0.0 : 1.0;
+    const double copied = 1e-6 * ((double)pad8(a.B) * pad8(op == 1 ? ao.n : ai.n) + (double)pad8(ao.n) * pad8(ai.n));
+    const double small_us = op == 2 ? 3.5 + rounds * (0.65 * slices + 0.73 * fetched + 0.54 * pieces) : 3.9 + rounds * (0.69 * slices + 0.5 * fetched + 0.72 * pieces);
+    const double copies_us = op == 2 ? 5.3 + 1.8 * spread + (packs ? 3.7 : 0.0) + 0.65 * written + 1.05 * slices
+                                     : 4.8 + 2.7 * spread + (packs ? 3.0 : 0.0) + written + 1.8 * copied + 0.8 * slices;
+    if (small_us > copies_us) return false;
   }
   // (results whose rows start anywhere leave in pieces that cross lines, which costs more than the copies where they are large:
   // 44 rows, 1719 -> 3854, weight gradient, in a network's step of 63.5 us 1.5 us more; 45 rows, 3161 -> 1065 less)

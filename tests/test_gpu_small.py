@@ -190,4 +190,4 @@ def test_which_products_of_neurons_far_apart_are_one_launch():
                 launches(lib)
                 assert layer_calls(lib, FakeHeap(), ard.BF16, B, I, O, (dp, dp) if dp > 1 else None, (dp_in, 1) if dp_in > 1 else None, 0, ops=(op,)) == [0]
                 got.append(launches(lib)[1] == ["gemm_small_kernel"])
-        assert got == [True, True, False, True, True, False, True, True, True, True, True, True, True, True, False], got
+        assert got == [True, True, False, True, True, False, True, True, True, True, True, False, True, True, False], got
