@@ -1976,13 +1976,14 @@ static int32_t conv_run(const ConvArgs& a, double rate, const void* A, const voi
       // The weight gradient runs over the kept positions only, the data gradient where that is expected to be faster and dY has more
       // than 64 channels (30 % kept, us, all positions and the kept ones: 128 x 256 channels of 28 x 28 -> 256 151 and 102, 64 x 512
       // of 14 x 14 -> 512 98 and 56, 112 x 248 of 56 x 56 -> 96 251 and 296; up to 64 channels 0.54 to 1.2 of the speed, in the mean
-      // of 51 layers of more than 20 us none).  n_keep, where a caller gives it, says how many rows are kept (128 x 256 of 28 x 28 ->
+      // of 51 layers of more than 20 us none; 1 x 1 filters have one tap to gain what writing the tiles costs: 63 x 256 of 56 x 56 -> 80
+      // 176 and 192, 78 layers 0.94 to 1.05 of the speed at 30 % kept, in the mean 0.98).  n_keep, where a caller gives it, says how many rows are kept (128 x 256 of 28 x 28 ->
       // 256, all kept: 151 and 211).
       ScatterDataParams sd;
       int ks;
       const long rows = (long)a.N * a.Ho * a.Wo;
       const double kept = a.n_keep > 0 && a.n_keep <= rows ? (double)a.n_keep / (double)rows : kKeptGuess;
-      if (a.mode == ARD_CONV_BWD_DATA_ROWS && a.Cout > 64 && scatter_plan(a, w, full.dy_mask, pad16(a.C), sd, ks) && scatter_us(sd, ks, kept, 1) <= masked_us(a))
+      if (a.mode == ARD_CONV_BWD_DATA_ROWS && a.Cout > 64 && a.kh * a.kw > 1 && scatter_plan(a, w, full.dy_mask, pad16(a.C), sd, ks) && scatter_us(sd, ks, kept, 1) <= masked_us(a))
         full.scatter = full.dy_mask, full.scatter_cpb = pad16(a.C);
       if (w.grid_a && pos_lists_fit(a)) full.lists = pos_list_job(a, (const uint8_t*)d_mask, 1, 1, w);
     } else {

@@ -309,6 +309,18 @@ def test_block_gradients_share_the_copy_of_dY_where_one_is_left():
             assert (D.launches(lib)[1].count("to_grid_src_kernel") == 1) == shared, (C, k, pad, x, y)
 
 
+def test_row_pattern_data_gradients_over_the_kept_positions():
+    """Filters of several taps and more than 64 channels of dY; one tap has nothing to gain."""
+    with D.dry_run() as lib:
+        heap = D.FakeHeap()
+        for (N, Cc, Cout, S, k), kept in [((128, 256, 256, 28, 3), True), ((128, 256, 256, 28, 1), False), ((63, 256, 80, 56, 1), False), ((128, 256, 64, 28, 3), False)]:
+            n = lib.ard_conv_workspace_bytes(D.BF16, N, Cc, S, S, Cout, k, k, 1, k // 2)
+            ws, p = heap(n), heap(1 << 20)
+            D.launches(lib)
+            _ok(lib, [lib.ard_fmap_drop_conv(5, D.BF16, N, Cc, S, S, Cout, k, k, 1, k // 2, 0.0, 0, None, p, p, p, p, None, None, None, ws, n, None)], "rows")
+            assert ("conv_scatter_data_kernel" in D.launches(lib)[1]) == kept, (N, Cc, Cout, S, k)
+
+
 def test_fp32_block_patterns_of_many_small_blocks_stay_in_one_pass():
     """A pass per column block where it is expected to be faster, else one over the patches of all."""
     with D.dry_run() as lib:
