@@ -2177,12 +2177,14 @@ extern "C" int32_t ard_conv_fwd_blocks(int32_t dtype, int32_t N, int32_t C, int3
   // smallest layers; 24 drawn ones of 1 to 4 column blocks 1.6 to 13 times as fast (8 x 64 channels of 16 x 16 -> 16
   // 165 -> 12 us, 96 x 256 of 27 x 27 -> 32 1401 -> 273, 75 x 64 of 16 x 16 -> 330 232 -> 148).
   // Many blocks of few channels are the general engine's: a block is three launches, reads and writes the result once more and fills up
-  // to 16 channels (36 x 16 of 19 x 19 -> 2, 1 x 1, a channel each: 17 against 182 us).  Times of both in us, fitted to 720
-  // layers of 1 to 16 blocks: within 1 % of the faster one in the mean.
+  // to 16 channels (36 x 16 of 19 x 19 -> 2, 1 x 1, a channel each: 17 against 182 us).  Times of both in us, fitted to 1500
+  // layers of 1 to 16 blocks: within 0.3 % of the faster one in the mean over 400 others.
   const int taps = kh * kw, CB = ceil_div(C * taps, a.by), RB = ceil_div(a.Ho * a.Wo, x), cpb = a.by / taps;
   const double npix = (double)N * a.Ho * a.Wo, held = (double)CB * pad16(cpb), tiles = (double)ceil_div(Cout, 128) * ((npix + 127.0) / 128.0);
-  const double passes_us = 3.0 + 7.9 * CB + 6.2e-6 * CB * npix * Cout + 2.7e-6 * held * npix + 2.4e-8 * held * taps * npix * imax(Cout, 32) + 1.8e-3 * held * taps;
-  const double patches_us = 5.3 + (tiles > 256.0 ? tiles / 256.0 : 1.0) * (8.4 * ceil_div(C * taps, 32) + 9.5);
+  const double passes_us = 1.7 + 10.0 * CB + 4.7e-6 * (CB - 0.25) * npix * Cout + 2.5e-6 * held * npix + 2.67e-8 * held * taps * npix * imax(Cout, 32) +
+                           2.2e-3 * held * taps;
+  const int steps = ceil_div(C * taps, 32);
+  const double patches_us = 4.6 + (tiles > 256.0 ? tiles / 256.0 : 1.0) * (8.34 * steps + 8.25) + imin(Cout, 128) / 128.0 * (0.41 * steps + 20.0);
   if (w.plane_a && !dev_knobs().no_fast && a.by % taps == 0 && CB <= 16 && N <= 65535 && passes_us <= patches_us) {
     hipStream_t s = (hipStream_t)stream;
     ARD_LAUNCH(iota_kernel, dim3(ceil_div(C, 256)), dim3(256), 0, s, w.all_chan, C);

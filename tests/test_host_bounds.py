@@ -327,7 +327,7 @@ def test_fp32_block_patterns_of_many_small_blocks_stay_in_one_pass():
         heap = D.FakeHeap()
         for (N, Cc, Cout, S, k, cpb), passes in [((8, 64, 16, 16, 3, 64), 1), ((75, 64, 330, 16, 3, 32), 2), ((2, 48, 40, 14, 5, 3), 16),
                                                  ((2, 160, 16, 10, 5, 10), 16), ((2, 170, 16, 10, 5, 10), 0), ((36, 16, 2, 19, 1, 1), 0),
-                                                 ((14, 32, 96, 28, 1, 2), 0), ((23, 8, 8, 13, 1, 1), 0)]:
+                                                 ((14, 32, 96, 28, 1, 2), 0), ((23, 8, 8, 13, 1, 1), 0), ((24, 128, 232, 28, 1, 128), 1)]:
             n = lib.ard_conv_workspace_bytes(D.F32, N, Cc, S, S, Cout, k, k, 1, k // 2)
             ws, p = heap(n), heap(1 << 20)
             D.launches(lib)
