@@ -722,22 +722,26 @@ static bool try_small(int op, const LayerArgs& a, int32_t flags, const void* p0,
   const int ks = ceil_div(ka.n, 32);
   const double weight = op == 2 ? 0.8 : op == 0 ? (wide == 1 || wide == 2 ? 1.0 : 1.6) : wide == 0 ? 1.8 : wide == 4 ? 1.2 : 1.0;
   const bool copies = op == 0 ? plan.x || plan.w : op == 2 || plan.w;
-  // (more tiles than six a CU: 3951 x 10 by 10 x 968 11 -> 19, 7 rows, 1064 -> 3614, weight gradient, 10 -> 16)
-  if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000 || tiles > 1500) return false;
-  // Where kept neurons lie far apart, a workgroup is bound by the lines its operands' elements touch and by the zeros of what it owns;
-  // the copies and the finishing pass spread both over all CUs (8 x 1192 by 8 x 1544, 64 and 48 apart: 11 against 117 us; 98 x
-  // 14361 by 14361 x 926, 24: 13 against 42).  Times of both in us, fitted to 5351 products of up to 8192 neurons, 1 to 64 apart: within
-  // 0.5, 0.3 and 1 % (forward, data, weight gradient) of the faster one in the mean.
+  // (with many tiles a CU the copies are faster again, forward, data and weight gradient from 1500, 2500 and 2000 on: there 1.2, 1.2 and
+  // 1.05 of their time in the mean of 15, 17 and 12 products of one and two slices; data and weight gradients from 1000 on below 0.88 and
+  // 0.84 of it; 3951 x 10 by 10 x 968 11 -> 19, 7 rows, 1064 -> 3614, weight gradient, 10 -> 16)
+  if (weight * (double)((tiles + 255) / 256) * ks > (copies ? 32 : 16) || (op == 0 ? weight : 1.0) * (double)tiles * ks > 4000) return false;
+  if (tiles >= (op == 0 ? 1500 : op == 1 ? 2500 : 2000)) return false;
+  // Where kept neurons lie far apart, a workgroup is bound by the lines its operands' elements touch and by the zeros of what it owns, by
+  // itself and the more so the more of them there are; the copies and the finishing pass spread both over all CUs (8 x 1192 by 8 x
+  // 1544, 64 and 48 apart: 11 against 117 us; 98 x 14361 by 14361 x 926, 24: 13 against 42).  Times of both in us, fitted to 5351 products
+  // of up to 8192 neurons, 1 to 64 apart: within 0.3, 0.2 and 1 % (forward, data, weight gradient) of the faster one in the mean.
   {
     auto touched = [](int n, int step) { return (double)imin(32, n) * imin(2 * step, 128); };
-    const double rounds = tiles > 256 ? (double)tiles / 256.0 : 1.0, slices = ks / 8.0;
+    const double share = (double)tiles / 256.0, rounds = share > 1.0 ? share : 1.0, slices = ks / 8.0;
     const double fetched = 1e-5 * ka.n * (touched(m.n, op == 2 ? am.step : ka.step) + touched(n.n, op == 0 ? kb.step : bn.step));
     const double pieces = (double)imin(32, m.n) * m.step * ((imin(32, n.n) * n.step + 7) / 8) / 512.0;
     const double written = 1e-6 * m.nphys * n.nphys, spread = dense(m) && dense(n) ? 0.0 : 1.0;
     const double copied = 1e-6 * ((double)pad8(a.B) * pad8(op == 1 ? ao.n : ai.n) + (double)pad8(ao.n) * pad8(ai.n));
-    const double small_us = op == 2 ? 3.5 + rounds * (0.65 * slices + 0.73 * fetched + 0.54 * pieces) : 3.9 + rounds * (0.69 * slices + 0.5 * fetched + 0.72 * pieces);
-    const double copies_us = op == 2 ? 5.3 + 1.8 * spread + (packs ? 3.7 : 0.0) + 0.65 * written + 1.05 * slices
-                                     : 4.8 + 2.7 * spread + (packs ? 3.0 : 0.0) + written + 1.8 * copied + 0.8 * slices;
+    const double small_us = op == 2 ? 3.4 + 0.67 * rounds * slices + (0.67 + 0.39 * share) * fetched + (0.45 + 0.73 * share) * pieces
+                                    : 3.9 + 0.70 * rounds * slices + (0.32 + 0.94 * share) * fetched + (0.61 + 0.92 * share) * pieces;
+    const double copies_us = op == 2 ? 5.1 + 2.1 * spread + (packs ? 3.7 : 0.0) + 0.67 * written + 1.04 * slices
+                                     : 4.2 + 2.7 * spread + (packs ? 3.55 : 0.0) + 1.1 * written + 1.7 * copied + 0.8 * slices;
     if (small_us > copies_us) return false;
   }
   // (results whose rows start anywhere leave in pieces that cross lines, which costs more than the copies where they are large:
