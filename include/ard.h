@@ -341,7 +341,7 @@ size_t ard_conv_workspace_bytes(int32_t dtype, int32_t N, int32_t C, int32_t H, 
  *   (zeroed while dY is copied into its grid; a masked copy for fp32 and strided layers).  The bf16 stride-1
  *   weight gradient contracts over the kept positions only, the data gradient where that is expected to be faster: n_keep,
  *   if given (1 .. N*Ho*Wo), is taken for the number of kept rows in this choice, else 40 % of them are; results depend
- *   on it in the order of their sums only.  d_keep is ignored.  Needs dYin, d_mask and Wt (data) or A (weight).
+ *   on it in the order of their sums only (and on a weight that is not finite beside dropped positions).  d_keep is ignored.  Needs dYin, d_mask and Wt (data) or A (weight).
  *   The reuse flags apply as for BWD_DATA / BWD_WEIGHT: ARD_CONV_REUSE_A takes the grid FWD_ROWS left,
  *   ARD_CONV_REUSE_DY the masked grid an earlier *_ROWS gradient of the same mask left.
  * FWD / BWD_DATA / BWD_WEIGHT read the kept channels from d_keep (n_keep entries,
