@@ -341,7 +341,8 @@ size_t ard_conv_workspace_bytes(int32_t dtype, int32_t N, int32_t C, int32_t H, 
  *   (zeroed while dY is copied into its grid; a masked copy for fp32 and strided layers).  The bf16 stride-1
  *   weight gradient contracts over the kept positions only, the data gradient where that is expected to be faster: n_keep,
  *   if given (1 .. N*Ho*Wo), is taken for the number of kept rows in this choice, else 40 % of them are; results depend
- *   on it in the order of their sums only (and on a weight that is not finite beside dropped positions).  d_keep is ignored.  Needs dYin, d_mask and Wt (data) or A (weight).
+ *   on it in the order of their sums only (and on a weight that is not finite beside dropped positions).  d_keep is
+ *   ignored.  Needs dYin, d_mask and Wt (data) or A (weight).
  *   The reuse flags apply as for BWD_DATA / BWD_WEIGHT: ARD_CONV_REUSE_A takes the grid FWD_ROWS left,
  *   ARD_CONV_REUSE_DY the masked grid an earlier *_ROWS gradient of the same mask left.
  * FWD / BWD_DATA / BWD_WEIGHT read the kept channels from d_keep (n_keep entries,
@@ -406,14 +407,14 @@ int32_t ard_sens_block_pattern(int32_t N, int32_t row_bands, int32_t col_blocks,
  * image's input matrix takes part iff d_block_keep[(image*RB + p/x)*CB + q/y] != 0 (the array
  * ard_sens_block_pattern writes; y = 0: blocks span the width).  out = Y[N,Cout,Ho,Wo], every element
  * written.  Arguments and workspace as for ard_fmap_drop_conv(ARD_CONV_FWD) with every channel kept.
- * bf16, stride 1, blocks of whole 64-channel groups over all filter taps (y % (64*kh*kw) == 0, kh*kw*ceil(C/64) <= 128):
- * what a band drops takes no part in its results, whatever values the weights and activations of dropped blocks have.
+ * bf16, stride 1, blocks of whole 64-channel groups over all filter taps (y % (64*kh*kw) == 0, kh*kw*ceil(C/64) <= 128,
+ * C <= 2048, filters of up to 15 x 15): what a band drops takes no part in its results, whatever values the weights and activations of dropped blocks have.
  * Where the bands fill at least half a tile (Cout > 64, the bands of an image, each padded to whole tiles of 128 or 256
  * positions, take at most twice the image's positions, and there are 256 tiles or more) a dropped block is neither loaded
  * nor multiplied; with other bands a tile of 128 positions leaves out the groups that none of its positions keeps.
  * fp32, stride 1, blocks of whole channels (y % (kh*kw) == 0, at most 16 column blocks): one fast pass over the channels
- * of every column block, of which the positions of kept bands are added (no work skipped).  Any other shape runs on
- * the general convolution engine, which applies the mask while it gathers the patches: correct in both
+ * of every column block, of which the positions of kept bands are added (no work skipped), where that is expected to be
+ * faster than the general engine.  Any other shape runs on the general convolution engine, which applies the mask while it gathers the patches: correct in both
  * dtypes and for any stride, no time saved.
  */
 int32_t ard_conv_fwd_blocks(int32_t dtype, int32_t N, int32_t C, int32_t H, int32_t Wd, int32_t Cout,
