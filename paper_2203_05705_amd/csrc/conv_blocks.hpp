@@ -45,7 +45,7 @@ __device__ __forceinline__ void block_product(uint4* const lds, const int S, con
   unsigned aaddr[2], baddr[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = i * 32 + (lane & 31), xr = (row & 7) ^ ((row >> 3) & 7);
+    const int row = i * 32 + (lane & 31), xr = kc_swz<true>(row);
     const unsigned at = (unsigned)(row * 8 + ((2 * wave + (lane >> 5)) ^ xr)) * 16u;
     if (i < 2) aaddr[i & 1] = lds_base + at;
     baddr[i] = lds_base + (unsigned)(NST * OPA) * 16u + at;
@@ -58,7 +58,7 @@ __device__ __forceinline__ void block_product(uint4* const lds, const int S, con
 #pragma unroll
     for (int i = 0; i < 4; ++i) lds_read_b128<BUF * OPB * 16>(fb[set][i].v, baddr[i]);
   };
-  constexpr int LPS = 2 + DirectLoader<true, 128, 4>::NI;
+  constexpr int LPS = 2 + DirectLoader<true, 128, 4, true>::NI;
   auto step = [&](auto bufc, auto setc, int it) {
     constexpr int BUF = decltype(bufc)::value, SET = decltype(setc)::value;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -175,14 +175,14 @@ static __global__ __launch_bounds__(256, 2) void conv_block_fwd_kernel(const Blo
   if (L >= hi) return;
   const int T = (int)fdiv((uint32_t)L, P.by_mt), row0 = (L - T * P.mt) * 64, j0 = T * 128;
   // the positions this lane fetches, and their kept channel groups (one bit each)
-  constexpr int NB = DirectLoader<true, 128, 4>::NI;
+  constexpr int NB = DirectLoader<true, 128, 4, true>::NI;
   uint32_t voff[NB];
   unsigned kept[NB], any = 0, all = ~0u;
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int q = imin(j0 + (wave * NB + j) * 8 + (lane >> 3), P.npix - 1);
     const int n = (int)fdiv((uint32_t)q, P.by_hw), p = q - n * P.HW, h = (int)fdiv((uint32_t)p, P.by_w), w = p - h * P.W_;
-    voff[j] = (uint32_t)((n * P.HgWg + h * P.Wg + w) * P.Cp + DirectLoader<true, 128, 4>::chunk_k(lane, wave, j)) * 2u;
+    voff[j] = (uint32_t)((n * P.HgWg + h * P.Wg + w) * P.Cp + DirectLoader<true, 128, 4, true>::chunk_k(lane, wave, j)) * 2u;
     const uint8_t* const m = P.blk + ((long)n * P.RB + (int)fdiv((uint32_t)p, P.by_x)) * P.CB;
     kept[j] = 0;
     for (int cb = 0; cb < P.CB; ++cb)
@@ -205,7 +205,7 @@ static __global__ __launch_bounds__(256, 2) void conv_block_fwd_kernel(const Blo
     return r | ((t - r * P.kw) << 4) | (__builtin_ctz(m | 0x80000000u) << 8);
   };
   const int e0 = entry(imin(lane, S - 1)), e1 = entry(imin(64 + lane, S - 1));
-  DirectLoader<true, 64, 4> la;
+  DirectLoader<true, 64, 4, true> la;
   la.init(P.W, P.ldw, axis_identity(P.Cout), row0, lane, wave);
   const char* const gridb = reinterpret_cast<const char*>(P.grid);
   auto load_stage = [&](int s, int buf) {
@@ -323,16 +323,16 @@ static __global__ __launch_bounds__(256, 2) void conv_block_data_kernel(const Bl
     return (__builtin_ctz(m | 0x80000000u) & 15) | (col << 4) | (cg << 8);
   };
   const int e0 = entry(imin(lane, S - 1)), e1 = entry(imin(64 + lane, S - 1));
-  DirectLoader<true, 64, 4> la;
+  DirectLoader<true, 64, 4, true> la;
   la.init(P.W, P.ldw, axis_identity(P.C), row0, lane, wave);
-  constexpr int NB = DirectLoader<true, 128, 4>::NI;
+  constexpr int NB = DirectLoader<true, 128, 4, true>::NI;
   uint32_t voff[NB];
   unsigned kept[NB];  // filter rows whose source pixel counts, per chunk of this lane
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int p = imin(p0 + (wave * NB + j) * 8 + (lane >> 3), p1 - 1);
     const int h = (int)fdiv((uint32_t)p, P.by_w), w = p - h * P.W_;
-    voff[j] = (uint32_t)((n * P.HgWg + h * P.Wg + w) * P.Cp + DirectLoader<true, 128, 4>::chunk_k(lane, wave, j)) * 2u;
+    voff[j] = (uint32_t)((n * P.HgWg + h * P.Wg + w) * P.Cp + DirectLoader<true, 128, 4, true>::chunk_k(lane, wave, j)) * 2u;
     kept[j] = 0;
     for (int r = 0; r < P.kh; ++r) {
       const int hs = imin(imax(h + r - P.ph, 0), P.H - 1);  // (rows outside the image are zeros in the grid already)

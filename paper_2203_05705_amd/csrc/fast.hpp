@@ -1,6 +1,6 @@
 // LDS-direct bf16 path of the gathered GEMM for gfx950.
 //
-// Workgroup tiles BM x BN x 64 of 32x32x16 bf16 MFMA tiles: 256x256, 256x128, 128x256 with 8
+// Workgroup tiles BM x BN x 64 of 16x16x32 bf16 MFMA tiles: 256x256, 256x128, 128x256 with 8
 // wavefronts (two per SIMD), 128x128, 128x64 and 64x64 with 4 wavefronts for products too small
 // to fill 256 CUs with large tiles; optional split of the contraction over blockIdx.y with
 // fp32 partial sums that a finishing kernel reduces (fixed split: deterministic).
@@ -14,10 +14,18 @@
 //     instruction fills 8 rows; lane = (row, slot) fetches logical chunk slot ^ xr(row).
 //     Fragments: ds_read_b128.
 //   MC operand (contraction-strided in memory): LDS tile [64 k][rows] exactly as in memory; lane
-//     = (k, pos) fetches chunk pos ^ 4*(k & 3).  Fragments: two ds_read_b64_tr_b16 (the
+//     = (k, pos) fetches chunk pos ^ mc_swz(k).  Fragments: two ds_read_b64_tr_b16 (the
 //     transposing LDS read of gfx950) per MFMA operand, no register transpose anywhere.
-// LDS: [A stages | B stages] (2 stages, 3 for the 64x64 tile); the stage is an immediate offset
+// LDS: [A stages | B stages] (2 stages, 3 for tiles of 64x64, 256x128 and 128x256); the stage is an immediate offset
 // of the fragment reads, so every read address is a loop invariant.
+//
+// What bounds the large tiles is power and the way of the loads.  16x16x32 MFMAs take less power than 32x32x16 ones (random
+// operands from registers, 300 launches in a row: 67 against 79 us for the FLOPs of a 4096^3 product, with the LDS reads of a
+// 256 x 256 tile beside them 84 against 90).  Three stages of 48 KB give the loads two steps to arrive (a step of a 256 x 128
+// tile is 1024 MFMA clocks, about what a load from the Infinity Cache takes), and issued as a burst the loads of a stage
+// hold up the MFMAs behind them.  Before and now, us: 4096^3, 64 x 64 tiles at dp = 2, forward 81 -> 72, data gradient 93 ->
+// 85, weight gradient 88 -> 78; 8192 x 2048 x 1024 43 -> 36; convolution products of 128 images of 28 x 28, 3 x 3: 128 -> 256
+// channels 76 -> 72 (256 x 256 tiles), its data gradient 71 -> 62, weight gradient 73 -> 66; listed pixels 60 -> 50, 62 -> 51.
 //
 // Tile patterns (Section 3.2) are period patterns over the linear tile index, so the tile
 // rows (or columns) fall into a few CLASSES that share one kept-column (kept-row) set:
@@ -189,21 +197,29 @@ __host__ __device__ __forceinline__ int direct_kbump(const Axis& k) {
   return (k.kind == AX_BAFF && k.bs == 32) ? (k.step - 1) * 32 : 0;
 }
 
-template <bool KC, int ROWS, int NW> struct DirectLoader;
+// KC tile: chunk c of row r sits at position c ^ kc_swz(r).  A 16-byte LDS read serves 16 lanes at a time, lanes 0-3, 12-15,
+// 20-23 and 24-27 first: for MFMA tiles of 16 rows (lane l: row l % 16, chunk l / 16) these are eight rows of one chunk and eight
+// of its neighbour, for tiles of 32 rows (T32) sixteen rows of one chunk.
+template <bool T32>
+__host__ __device__ __forceinline__ int kc_swz(int row) {
+  return T32 ? (row & 7) ^ ((row >> 3) & 7) : row & 6;
+}
+
+template <bool KC, int ROWS, int NW, bool T32 = false> struct DirectLoader;
 
 // Both loaders keep, per lane and instruction, a loop-invariant 32-bit BYTE offset from a base that
 // is uniform over the workgroup; a contraction step only moves the uniform base, so a load costs
 // no vector ALU work.  A lane whose tile row lies beyond the operand reads some valid row instead
 // (clamped at set-up): such rows only feed outputs that are never stored, or that the epilogue
 // overwrites with zeros.  Only the last, partial step of a contraction redirects lanes to a zero chunk.
-template <int ROWS, int NW> struct DirectLoader<true, ROWS, NW> {
+template <int ROWS, int NW, bool T32> struct DirectLoader<true, ROWS, NW, T32> {
   static constexpr int NI = ROWS / 8 / NW;  // instructions per wavefront and stage (8 rows each)
   static_assert(NI >= 1, "tile too small for the workgroup");
   const char* base;
   uint32_t voff[NI];
   __host__ __device__ static __forceinline__ int chunk_k(int lane, int wave, int j) {
     const int row = (wave * NI + j) * 8 + (lane >> 3);
-    return ((lane & 7) ^ (row & 7) ^ ((row >> 3) & 7)) * 8;
+    return ((lane & 7) ^ kc_swz<T32>(row)) * 8;
   }
   // (host-callable: the host-side bounds proof runs this very arithmetic for every lane)
   __host__ __device__ __forceinline__ void init(const uint16_t* p, int ld, const Axis& r, int row0, int lane, int wave,
@@ -240,8 +256,9 @@ template <int ROWS, int NW> struct DirectLoader<true, ROWS, NW> {
       __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(sb + voff[j]), ARD_LDS_PTR(op_tile + (wave * NI + j) * 64), 16, 0, 0);
   }
   // one of the NI loads of a full step (for callers that spread them between other instructions)
-  __device__ __forceinline__ void issue_one(uint4* op_tile, int kslab, int wave, int j) const {
+  __device__ __forceinline__ void issue_one(uint4* op_tile, int kslab, int wave, int j) {
     const char* sb = base + (long)kslab * 2;
+    asm volatile("" : "+v"(voff[j]));  // (widened ahead of the loop, it would be added to the base by the vector unit instead of the load)
     __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(sb + voff[j]), ARD_LDS_PTR(op_tile + (wave * NI + j) * 64), 16, 0, 0);
   }
   // last, partial step of a contraction: chunks beyond its end come from the zero chunk
@@ -266,14 +283,14 @@ template <int ROWS, int NW> struct DirectLoader<true, ROWS, NW> {
 };
 
 // swizzle of an MC tile: chunk c of contraction row k sits at position c ^ mc_swz(k).  Rows are
-// ROWS*2 bytes apart; the XOR makes the four rows a transposing read touches land in different
-// banks (rows of 256+ bytes all start at the same bank, rows of 128 bytes alternate).
+// ROWS*2 bytes apart; the XOR makes the eight rows that 32 lanes of a transposing read touch (k .. k + 3 and k + 8 .. k + 11,
+// 32 bytes of each) land in different banks (rows of 256+ bytes all start at the same bank, rows of 128 bytes alternate).
 template <int ROWS>
 __host__ __device__ __forceinline__ int mc_swz(int k) {
-  return ROWS >= 128 ? 4 * (k & 3) : 4 * ((k >> 1) & 1);
+  return (ROWS >= 128 ? 4 * (k & 3) : 4 * ((k >> 1) & 1)) + 2 * ((k >> 3) & 1);
 }
 
-template <int ROWS, int NW> struct DirectLoader<false, ROWS, NW> {
+template <int ROWS, int NW, bool T32> struct DirectLoader<false, ROWS, NW, T32> {
   static constexpr int CPR = ROWS / 8;         // 16-byte chunks per contraction row
   static constexpr int KPI = 64 / CPR;         // contraction rows per instruction
   static constexpr int NI = 64 / KPI / NW;     // instructions per wavefront and stage
@@ -319,8 +336,9 @@ template <int ROWS, int NW> struct DirectLoader<false, ROWS, NW> {
     for (int j = 0; j < NI; ++j)
       __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(sb + voff[j]), ARD_LDS_PTR(op_tile + (wave * NI + j) * 64), 16, 0, 0);
   }
-  __device__ __forceinline__ void issue_one(uint4* op_tile, int kslab, int wave, int j) const {
+  __device__ __forceinline__ void issue_one(uint4* op_tile, int kslab, int wave, int j) {
     const char* sb = base + (long)kslab * ld * 2;
+    asm volatile("" : "+v"(voff[j]));
     __builtin_amdgcn_global_load_lds(ARD_GLB_PTR(sb + voff[j]), ARD_LDS_PTR(op_tile + (wave * NI + j) * 64), 16, 0, 0);
   }
   __host__ __device__ static __forceinline__ bool tail_live(int lane, int wave, int j, int kslab, int krem, int kphys_end,
@@ -378,21 +396,19 @@ template <int ROWS, int NW> struct ListLoader {
   }
 };
 // list entries a workgroup of the 256-row / 128-row tile holds in LDS at a time
-constexpr int direct_list_cap(int bm) { return bm == 256 ? 8192 : 3072; }
+constexpr int direct_list_cap(int bm) { return bm == 256 ? 4096 : 3072; }
 
 // Byte offset, inside an MC operand tile of `ROWS` rows, of this lane's source position for the
-// transposing reads of the 32-wide MFMA tile that starts at tile row `tile_col0`.  The reads
-// of slice q, half h add the immediate (q*16 + h*4) * ROWS*2.
+// transposing reads of the 16-wide MFMA tile that starts at tile row `tile_col0`.  The reads
+// of slice q, half h add the immediate (q*32 + h*4) * ROWS*2.
 // ds_read_b64_tr_b16 works on groups of 16 lanes: result lane i, element e comes from source
 // lane 4e + i/4, element i%4.  With source lane s at (k = s/4, column 4*(s%4)) of a 4 x 16
 // block, result lane i holds column i for k = 0..3: the MFMA operand order.
 template <int ROWS>
 __device__ __forceinline__ int mc_frag_base(int tile_col0, int lane) {
-  const int s = lane & 15, G = lane >> 4;
-  const int g = G >> 1, jhalf = G & 1;
-  const int c = (tile_col0 >> 3) + 2 * jhalf + ((s & 3) >> 1);
-  const int pc = c ^ mc_swz<ROWS>(s >> 2);
-  return (g * 8 + (s >> 2)) * (ROWS * 2) + pc * 16 + 8 * (s & 1);
+  const int s = lane & 15, k = (lane >> 4) * 8 + (s >> 2);
+  const int pc = ((tile_col0 >> 3) + ((s & 3) >> 1)) ^ mc_swz<ROWS>(k);
+  return k * (ROWS * 2) + pc * 16 + 8 * (s & 1);
 }
 
 // LDS fragment reads are issued as volatile asm with ONE explicit wait per 16-wide slice: the
@@ -428,11 +444,20 @@ __device__ __forceinline__ bf16x8_t frag_value(const Frag& f) {
 // LDS stages of a tile configuration: the loads of NST - 1 contraction steps are in flight
 // while one step is multiplied.  A 4-wavefront workgroup wants a second workgroup on its CU
 // (8 wavefronts hide the LDS and MFMA latencies), so its stages must fit twice into the 160 KiB
-// LDS; only the smallest tile has room for a third stage.
+// LDS; only the smallest of these tiles has room for a third stage.  Of the 8-wavefront tiles, one workgroup a CU, those of 384
+// rows and columns together have it (two stages: 8192 x 2048 x 1024 42 us, three 37).
 #ifndef ARD_NST_SMALL
 #define ARD_NST_SMALL 3
 #endif
-constexpr int direct_stages(int bm, int bn) { return bm + bn <= 128 ? ARD_NST_SMALL : 2; }
+constexpr int direct_stages(int bm, int bn) { return bm + bn <= 128 || bm + bn == 384 ? ARD_NST_SMALL : 2; }
+// MFMAs of a wavefront, from the hand-over of a stage on, over which the loads of a stage are spread (`step`: of a step, `unit`: of a
+// unit; the last unit of a step but one is left out).  Over all of a step where a stage has two steps to arrive; where it has one,
+// what a spread gains at the issue it loses at the end: over five eighths of a step, 4096^3 at dp = 2 took 134 instead of 120
+// thousand clocks on 256 x 256 tiles, and a unit is best for 128 x 128.  128 x 448, whose units are four MFMAs: half a step 62 us, one
+// unit 66 (above).  Small tiles: a whole step made five dependent launches of 64 x 64 tiles 56.3 us instead of 55.
+constexpr int direct_load_window(int bm, int bn, int step, int unit) {
+  return bm + bn == 384 ? step - unit : bn == 448 ? step / 2 : bm + bn >= 512 ? 2 * unit : unit;
+}
 // Wavefronts side by side along the columns, so that each has whole 32 x 32 tiles
 constexpr int direct_wave_columns(int bn, int nw) { return nw == 8 && (bn == 256 || bn == 384) ? 4 : 2; }
 // Bytes between the rows of a tile on its way out through LDS, in elements of `size` bytes: the rows that a store to LDS
@@ -459,6 +484,10 @@ __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+
+// Stages of `bytes` bytes whose fragments, up to `reach` bytes behind a place in the first, are within the 16 bits of an LDS
+// read's offset
+constexpr int frag_stages(int bytes, int reach) { return reach + 2 * bytes <= 65535 ? 3 : reach + bytes <= 65535 ? 2 : 1; }
 
 // Plain barrier.  The LDS stages are filled by LDS-direct loads (each wave waits for its own
 // with wait_vmcnt before the barrier) and read by volatile asm, so no fence is wanted: a fence
@@ -657,7 +686,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   constexpr int WGN = direct_wave_columns(BN, NW), WGM = NW / WGN;
   constexpr int WTM = F_BM / WGM, WTN = BN / WGN;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must hold whole MFMA tiles");
-  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int TM = WTM / 16, TN = WTN / 16;
   constexpr int OPA = F_BM * LDS_ROW_U4, OPB = BN * LDS_ROW_U4;  // u4 entries of one operand stage
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -671,13 +700,13 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   const int m0 = wk.m0, n0 = wk.n0, split = wk.split;
   const int Kn = kax.n;
 
-  f32x16_t acc[TM][TN];
+  f32x4_t acc[TM][TN];
 #pragma unroll
   for (int im = 0; im < TM; ++im)
 #pragma unroll
     for (int in = 0; in < TN; ++in)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[im][in][v] = 0.0f;
+      for (int v = 0; v < 4; ++v) acc[im][in][v] = 0.0f;
 
   int li_cb = 0, li_cnt = 0, jn0 = n0, jlim = P.N;  // jn0, jlim: this tile's columns within its block
   if constexpr (MODE == 3) {
@@ -730,30 +759,26 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     else if constexpr (MODE == 2) lb.init_tap_columns(P.B, P.cv, P.N, n0, lane, wave);
     else lb.init(P.B, P.ldb, bn, n0, lane, wave, kbump);
     const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)lds);
-    unsigned aaddr[TM][A_KC ? 4 : 1], baddr[TN][B_KC ? 4 : 1];
+    // KC: one place per slice, tile i's rows lie 16 i rows further; MC: one per tile, slice q lies 32 q contraction rows further.
+    // (an offset has 16 bits: so many stages share their places)
+    constexpr int QA = 32 * F_BM * 2, QB = 32 * BN * 2;  // bytes per 32-wide slice of an MC tile
+    constexpr int SHARE_A = frag_stages(OPA * 16, A_KC ? (TM - 1) * 2048 : QA + QA / 8), SHARE_B = frag_stages(OPB * 16, B_KC ? (TN - 1) * 2048 : QB + QB / 8);
+    constexpr int PA = A_KC ? 2 : TM, PB = B_KC ? 2 : TN;
+    unsigned aaddr[(NST + SHARE_A - 1) / SHARE_A][PA], baddr[(NST + SHARE_B - 1) / SHARE_B][PB];
+    auto frag_place = [&](int row0, int q) {
+      const int row = row0 + (lane & 15);
+      return (unsigned)(row * 8 + (((lane >> 4) + 4 * q) ^ kc_swz<false>(row))) * 16u;
+    };
 #pragma unroll
-    for (int im = 0; im < TM; ++im) {
-      if (A_KC) {
-        const int row = wm * WTM + im * 32 + (lane & 31);
-        const int xr = (row & 7) ^ ((row >> 3) & 7);
+    for (int i = 0; i * SHARE_A < NST; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) aaddr[im][q] = lds_base + (unsigned)(row * 8 + ((2 * q + (lane >> 5)) ^ xr)) * 16u;
-      } else {
-        aaddr[im][0] = lds_base + (unsigned)mc_frag_base<F_BM>(wm * WTM + im * 32, lane);
-      }
-    }
+      for (int p = 0; p < PA; ++p)
+        aaddr[i][p] = lds_base + (unsigned)(i * SHARE_A * OPA) * 16u + (A_KC ? frag_place(wm * WTM, p) : (unsigned)mc_frag_base<F_BM>(wm * WTM + p * 16, lane));
 #pragma unroll
-    for (int in = 0; in < TN; ++in) {
-      if (B_KC) {
-        const int row = wn * WTN + in * 32 + (lane & 31);
-        const int xr = (row & 7) ^ ((row >> 3) & 7);
+    for (int i = 0; i * SHARE_B < NST; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          baddr[in][q] = lds_base + (unsigned)(NST * OPA + row * 8 + ((2 * q + (lane >> 5)) ^ xr)) * 16u;
-      } else {
-        baddr[in][0] = lds_base + (unsigned)(NST * OPA) * 16u + (unsigned)mc_frag_base<BN>(wn * WTN + in * 32, lane);
-      }
-    }
+      for (int p = 0; p < PB; ++p)
+        baddr[i][p] = lds_base + (unsigned)(NST * OPA + i * SHARE_B * OPB) * 16u + (B_KC ? frag_place(wn * WTN, p) : (unsigned)mc_frag_base<BN>(wn * WTN + p * 16, lane));
     // contraction steps of this workgroup (a share of them when the contraction is split)
     const int S_all = ((MODE == 3 ? li_cnt : Kn) + 63) >> 6;
     const int s_lo = (int)((long)split * S_all / P.splits), s_hi = (int)((long)(split + 1) * S_all / P.splits);
@@ -782,84 +807,173 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       }
       }
     };
-    constexpr int QA = 16 * F_BM * 2, QB = 16 * BN * 2;  // bytes per 16-wide slice of an MC tile
-    Frag fa[2][TM], fb[2][TN];
-    // issue the fragment reads of slice Q of stage BUF (both compile-time: immediates) into `set`
-    auto issue = [&](auto bufc, auto qc, int set) {
-      constexpr int BUF = decltype(bufc)::value, Q = decltype(qc)::value;
-      constexpr int SA = BUF * OPA * 16, SB = BUF * OPB * 16;  // byte offsets of the stage
-#pragma unroll
-      for (int im = 0; im < TM; ++im) {
-        if (A_KC) {
-          lds_read_b128<SA>(fa[set][im].v, aaddr[im][A_KC ? Q : 0]);
-        } else {
-          lds_read_tr16_b64<SA + Q * QA>(fa[set][im].lo, aaddr[im][0]);
-          lds_read_tr16_b64<SA + Q * QA + QA / 4>(fa[set][im].hi, aaddr[im][0]);
-        }
+    // A step is 2 PARTS units: slice Q of 32 by part H of the wavefront's rows or columns, whichever are more.  The parts share
+    // the other operand, so that what two units hold fits beside the accumulators.
+    constexpr bool SPLIT_N = TN > TM;
+    constexpr int PARTS = TM * TN <= 4 ? 1 : SPLIT_N ? (TN % 7 == 0 ? 7 : 2) : TM * TN >= 32 && TM % 4 == 0 ? 4 : 2;
+    constexpr int AF = SPLIT_N ? TM : TM / PARTS, BF = SPLIT_N ? TN / PARTS : TN;
+    static_assert((SPLIT_N ? TN : TM) % PARTS == 0, "whole tiles");
+    Frag fa[2][AF], fb[2][BF];
+    // issue the fragment reads of unit U of stage BUF (compile-time: immediates): the parted operand into set U % 2, the
+    // shared one, with a slice's first part, into the slice's set
+    auto issue = [&](auto bufc, auto uc) {
+      constexpr int BUF = decltype(bufc)::value, U = decltype(uc)::value, Q = U / PARTS, H = U % PARTS;
+      constexpr int SA = BUF % SHARE_A * OPA * 16, SB = BUF % SHARE_B * OPB * 16;  // byte offsets of the stage
+      if constexpr (SPLIT_N || H == 0) {
+        static_for<BF>([&](auto ic) {
+          constexpr int I = (SPLIT_N ? H * BF : 0) + decltype(ic)::value;
+          Frag& f = fb[SPLIT_N ? U & 1 : Q][decltype(ic)::value];
+          if constexpr (B_KC) {
+            lds_read_b128<SB + I * 2048>(f.v, baddr[BUF / SHARE_B][Q]);
+          } else {
+            lds_read_tr16_b64<SB + Q * QB>(f.lo, baddr[BUF / SHARE_B][I]);
+            lds_read_tr16_b64<SB + Q * QB + QB / 8>(f.hi, baddr[BUF / SHARE_B][I]);
+          }
+        });
       }
-#pragma unroll
-      for (int in = 0; in < TN; ++in) {
-        if (B_KC) {
-          lds_read_b128<SB>(fb[set][in].v, baddr[in][B_KC ? Q : 0]);
-        } else {
-          lds_read_tr16_b64<SB + Q * QB>(fb[set][in].lo, baddr[in][0]);
-          lds_read_tr16_b64<SB + Q * QB + QB / 4>(fb[set][in].hi, baddr[in][0]);
-        }
+      if constexpr (!SPLIT_N || H == 0) {
+        static_for<AF>([&](auto ic) {
+          constexpr int I = (SPLIT_N ? 0 : H * AF) + decltype(ic)::value;
+          Frag& f = fa[SPLIT_N ? Q : U & 1][decltype(ic)::value];
+          if constexpr (A_KC) {
+            lds_read_b128<SA + I * 2048>(f.v, aaddr[BUF / SHARE_A][Q]);
+          } else {
+            lds_read_tr16_b64<SA + Q * QA>(f.lo, aaddr[BUF / SHARE_A][I]);
+            lds_read_tr16_b64<SA + Q * QA + QA / 8>(f.hi, aaddr[BUF / SHARE_A][I]);
+          }
+        });
       }
     };
-    auto wait = [&](int set) {
+    auto wait = [&](int u) {
+      const int q = u / PARTS, h = u % PARTS;
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (!SPLIT_N || h == 0) {
 #pragma unroll
-      for (int im = 0; im < TM; ++im) frag_wait<A_KC>(fa[set][im]);
+        for (int im = 0; im < AF; ++im) frag_wait<A_KC>(fa[SPLIT_N ? q : u & 1][im]);
+      }
+      if (SPLIT_N || h == 0) {
 #pragma unroll
-      for (int in = 0; in < TN; ++in) frag_wait<B_KC>(fb[set][in]);
+        for (int in = 0; in < BF; ++in) frag_wait<B_KC>(fb[SPLIT_N ? u & 1 : q][in]);
+      }
     };
     // (tiles come out transposed: a lane then holds four neighbouring columns of a row at a time)
-    auto mfma = [&](f32x16_t& c, const Frag& x, const Frag& y) {
-      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_value<B_KC>(y), frag_value<A_KC>(x), c, 0, 0, 0);
+    auto mfma = [&](f32x4_t& c, const Frag& x, const Frag& y) {
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_value<B_KC>(y), frag_value<A_KC>(x), c, 0, 0, 0);
     };
-    auto mma = [&](int set) {
-#pragma unroll
-      for (int im = 0; im < TM; ++im)
-#pragma unroll
-        for (int in = 0; in < TN; ++in)
-          mfma(acc[im][in], fa[set][im], fb[set][in]);
+    auto mfma_of = [&](int u, int im, int in) {
+      const int q = u / PARTS, h = u % PARTS;
+      if (SPLIT_N) mfma(acc[im][h * BF + in], fa[q][im], fb[u & 1][in]);
+      else mfma(acc[h * AF + im][in], fa[u & 1][im], fb[q][in]);
+    };
+    // unit U's MFMAs; each(m) runs behind MFMA m of the step, the last unit's being the first (left to itself the scheduler
+    // gathers the MFMAs of several units behind their waits)
+    constexpr int UNITS = 2 * PARTS, MM = AF * BF;
+    auto mma_each = [&](auto uc, auto each) {
+      constexpr int U = decltype(uc)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<MM>([&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        mfma_of(U, I / BF, I % BF);
+        each(std::integral_constant<int, (U + 1) % UNITS * MM + I>{});
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // all units of a stage but the last one's MFMAs; `late` runs behind the others' reads
+    auto first_units = [&](auto bufc, auto each, auto late) {
+      static_for<UNITS - 1>([&](auto uc) {
+        constexpr int U = decltype(uc)::value;
+        wait(U);
+        issue(bufc, std::integral_constant<int, U + 1>{});
+        if constexpr (U == UNITS - 2) late();
+        mma_each(uc, each);
+      });
+      wait(UNITS - 1);
     };
     using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
-    // One contraction step from stage BUF.  Slice q+1's reads are in flight behind slice q's
-    // MFMAs; the stage hand-over (wait for the next stage's loads, barrier, start the loads of
-    // stage it+NST into the buffer just released, read the next stage's first slice) sits in
-    // front of the LAST slice's MFMAs, so neither the barrier nor the first LDS latency of a
-    // stage leaves the matrix cores idle.  Loads complete in order: with NST - 2 younger
-    // stages allowed in flight, stage it+1 has landed.
-    constexpr int LPS = decltype(la)::NI + decltype(lb)::NI;  // loads of one thread per stage
-    auto step = [&](auto bufc, int it) {
+    // Slabs one after the other, without the divisions that finding one takes; in scalar registers, so that the loads take their
+    // base from there.
+    int next_ks = 0, next_ksb = 0, in_run = 0, run = 0, jump = 0, in_row = 0;
+    auto begin_slabs = [&](int s) {
+      if constexpr (MODE == 1) {
+        int ks, ksb;
+        direct_slab<MODE>(P, kax, s, ks, ksb);
+        next_ks = __builtin_amdgcn_readfirstlane(ks), next_ksb = __builtin_amdgcn_readfirstlane(ksb);
+        in_run = s - (int)fdiv((uint32_t)s, P.cv.by_taps) * P.cv.taps, in_row = in_run - (int)fdiv((uint32_t)in_run, P.cv.by_kw) * P.cv.kw;
+      } else if constexpr (MODE != 3) {
+        next_ks = __builtin_amdgcn_readfirstlane(fast_kslab(kax, s * 64));
+        run = kax.kind == AX_BAFF ? imax(kax.bs, 64) : 0x40000000, jump = kax.kind == AX_BAFF ? (kax.step - 1) * run : 0;
+        in_run = kax.kind == AX_BAFF ? s * 64 % run : 0;
+      }
+    };
+    auto next_slab = [&](int s, int& ks, int& ksb) {
+      if constexpr (MODE == 1) {
+        if (kb_mode) return slab(s, ks, ksb);
+        ks = next_ks, ksb = next_ksb;
+        next_ks += P.cv.Cp, next_ksb += P.cv.Cp;
+        if (++in_row == P.cv.kw) in_row = 0, next_ksb += (P.cv.Wg - P.cv.kw) * P.cv.Cp;
+        if (++in_run == P.cv.taps) {  // the next 64 channels
+          next_ks += 64 - P.cv.taps * P.cv.Cp;
+          next_ksb = next_ks;
+          in_run = 0;
+        }
+      } else {
+        ks = ksb = next_ks;
+        next_ks += 64, in_run += 64;
+        if (in_run == run) next_ks += jump, in_run = 0;
+      }
+    };
+    // One contraction step from stage BUF.  A unit's reads are in flight behind the MFMAs of the one before; the stage
+    // hand-over (wait for the next stage's loads, barrier, read the next stage's first unit, start the loads of stage it+NST
+    // into the buffer just released) sits in front of the LAST unit's MFMAs, so neither the barrier nor the first LDS latency
+    // of a stage leaves the matrix cores idle.  Loads complete in order: with NST - 2 younger stages allowed in flight,
+    // stage it+1 has landed.
+    constexpr int LPS = decltype(la)::NI + decltype(lb)::NI, NA = decltype(la)::NI;  // loads of one thread per stage
+    using LastUnit = std::integral_constant<int, UNITS - 1>;
+    // Loads go out spread over the MFMAs, from the hand-over on: the memory pipe of a CU takes one in 16 clocks, and a wavefront
+    // that finds it full issues no MFMAs either.  Over a step where a stage has two steps to arrive, sooner where it has one.
+    constexpr int WINDOW = direct_load_window(F_BM, BN, UNITS * MM, MM);
+    int ks = 0, ksb = 0;  // slabs of the stage whose loads are going out
+    // loads [LO, HI) of that stage into buffer BUF
+    auto loads = [&](auto bufc, auto lo, auto hi) {
+      constexpr int BUF = decltype(bufc)::value, LO = decltype(lo)::value;
+      static_for<decltype(hi)::value - LO>([&](auto jc) {
+        constexpr int L = LO + decltype(jc)::value;
+        if constexpr (MODE == 3) {
+          if constexpr (L < NA) la.issue_one(lds + BUF * OPA, ao[L], wave, L);
+          else lb.issue_one(lds + NST * OPA + BUF * OPB, bo[L - NA], wave, L - NA);
+        } else {
+          if constexpr (L < NA) la.issue_one(lds + BUF * OPA, ks, wave, L);
+          else lb.issue_one(lds + NST * OPA + BUF * OPB, ksb, wave, L - NA);
+        }
+      });
+    };
+    constexpr auto loads_before = [](int m) { return (m * LPS + WINDOW - 1) / WINDOW < LPS ? (m * LPS + WINDOW - 1) / WINDOW : LPS; };  // of the window's MFMA m
+    auto loads_at = [&](auto bufc, auto mc) {
+      constexpr int M = decltype(mc)::value, L0 = loads_before(M), L1 = loads_before(M + 1);
+      loads(bufc, std::integral_constant<int, L0>{}, std::integral_constant<int, L1>{});
+      if constexpr (L1 > L0) __builtin_amdgcn_sched_barrier(0);
+    };
+    using LeftOver = std::integral_constant<int, loads_before(MM)>;  // first load that goes out in the step behind the hand-over
+    auto step = [&](auto bufc, int it, bool begin_window) {
       constexpr int BUF = decltype(bufc)::value;
       using B = std::integral_constant<int, BUF>;
       using NB = std::integral_constant<int, (BUF + 1) % NST>;
-      wait(0);
-      issue(B{}, I1{}, 1);
-      mma(0);
-      wait(1);
-      issue(B{}, I2{}, 0);
-      mma(1);
-      wait(0);
-      issue(B{}, I3{}, 1);
-      mma(0);
-      wait(1);
+      first_units(B{}, [](auto) {}, [] {});
       if (it + 1 < S) {
         if (it + NST - 1 < S) wait_vmcnt<(NST - 2) * LPS>();
         else wait_vmcnt<0>();
         wg_barrier();  // stage it+1 is complete and visible; nobody reads stage it any more
-        issue(NB{}, I0{}, 0);
+        issue(NB{}, I0{});
       }
-      mma(1);
-      // the loads of stage it+NST go into the buffer just released; issued behind the MFMAs so
-      // that nothing but the barrier and one fragment read sits between two slices' MFMAs
-      if (it + NST < S) load_stage(it + NST, BUF);
+      mma_each(LastUnit{}, [](auto) {});
+      // (behind the MFMAs so that nothing but the barrier and one fragment read sits between two units' MFMAs)
+      if (begin_window) {
+        if constexpr (MODE == 3) la.look(list + (it + NST) * 64, ao), lb.look(list + (it + NST) * 64, bo);
+        else next_slab(s_lo + it + NST, ks, ksb);
+        loads(B{}, I0{}, LeftOver{});
+      } else if (it + NST < S) {
+        load_stage(it + NST, BUF);
+      }
     };
     // The same step where every question is settled: a successor stage exists, the stage to load
     // exists and is a full one (the axis is affine, or made of whole blocks that hold whole steps:
@@ -868,66 +982,41 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       constexpr int BUF = decltype(bufc)::value;
       using B = std::integral_constant<int, BUF>;
       using NB = std::integral_constant<int, (BUF + 1) % NST>;
-      wait(0);
-      issue(B{}, I1{}, 1);
-      mma(0);
-      wait(1);
-      issue(B{}, I2{}, 0);
-      // (looked up here, the rows of the next loads are known long before the loads are issued)
-      if constexpr (MODE == 3) la.look(list + (it + NST) * 64, ao), lb.look(list + (it + NST) * 64, bo);
-      mma(1);
-      wait(0);
-      issue(B{}, I3{}, 1);
-      mma(0);
-      wait(1);
+      using PB = std::integral_constant<int, (BUF + NST - 1) % NST>;
+      first_units(B{}, [&](auto mc) { loads_at(PB{}, mc); }, [&] {
+        // (looked up here, the rows of the next loads are known before the loads are issued)
+        if constexpr (MODE == 3) la.look(list + (it + NST) * 64, ao), lb.look(list + (it + NST) * 64, bo);
+        else next_slab(s_lo + it + NST, ks, ksb);
+      });
       wait_vmcnt<(NST - 2) * LPS>();
       wg_barrier();
-      issue(NB{}, I0{}, 0);
-      int ks, ksb;
-      if constexpr (MODE != 3) slab(s_lo + it + NST, ks, ksb);
-      // the loads of stage it+NST spread between the last slice's MFMAs (a burst of LPS load instructions
-      // keeps this wavefront from issuing MFMAs for as long as it takes to issue them)
-      {
-        constexpr int NA = decltype(la)::NI, MM = TM * TN;
-        int li = 0, mi = 0;
-#pragma unroll
-        for (int im = 0; im < TM; ++im)
-#pragma unroll
-          for (int in = 0; in < TN; ++in) {
-            mfma(acc[im][in], fa[1][im], fb[1][in]);
-            ++mi;
-#pragma unroll
-            for (int r = 0; r < (LPS + MM - 1) / MM; ++r)
-              if (li < LPS && li * MM < mi * LPS) {
-                if constexpr (MODE == 3) {
-                  if (li < NA) la.issue_one(lds + BUF * OPA, ao[li < NA ? li : 0], wave, li);
-                  else lb.issue_one(lds + NST * OPA + BUF * OPB, bo[li < NA ? 0 : li - NA], wave, li - NA);
-                } else {
-                  if (li < NA) la.issue_one(lds + BUF * OPA, ks, wave, li);
-                  else lb.issue_one(lds + NST * OPA + BUF * OPB, ksb, wave, li - NA);
-                }
-                ++li;
-              }
-            __builtin_amdgcn_sched_barrier(0);
-          }
-      }
+      issue(NB{}, I0{});
+      mma_each(LastUnit{}, [&](auto mc) { loads_at(B{}, mc); });
     };
     auto contract = [&] {
 #pragma unroll
       for (int st = 0; st < NST; ++st)
         if (st < S) load_stage(st, st);
       if (S >= NST) wait_vmcnt<(NST - 1) * LPS>();
+      else if (NST > 2 && S == 2) wait_vmcnt<LPS>();
       else wait_vmcnt<0>();
       wg_barrier();
-      issue(I0{}, I0{}, 0);
-      int it0 = 0;
-      if (MODE == 3 || kax.kind == AX_AFFINE || (kax.kind == AX_BAFF && (kax.bs % 64 == 0 || kax.bs == 32) && kax.nphys % kax.bs == 0)) {
-        // steps whose stage it+NST is not the last one (only the last can be partial)
-        for (; it0 + 2 * NST < S; it0 += NST) static_for<NST>([&](auto b) { steady_step(b, it0 + decltype(b)::value); });
+      issue(I0{}, I0{});
+      // steps it whose stage it+NST is not the last one (only the last can be partial); a window longer than a unit begins in the
+      // step before them
+      constexpr int LEAD = LeftOver::value < LPS ? 1 : 0;
+      const bool steady = (MODE == 3 || kax.kind == AX_AFFINE || (kax.kind == AX_BAFF && (kax.bs % 64 == 0 || kax.bs == 32) && kax.nphys % kax.bs == 0)) && LEAD + 2 * NST < S;
+      int it0 = LEAD;
+      if (steady) begin_slabs(s_lo + NST);
+      if constexpr (LEAD) step(I0{}, 0, steady);
+      if (steady) {
+        for (; it0 + 2 * NST < S; it0 += NST)
+          static_for<NST>([&](auto b) { steady_step(std::integral_constant<int, (decltype(b)::value + LEAD) % NST>{}, it0 + decltype(b)::value); });
+        if constexpr (LEAD) loads(I0{}, LeftOver{}, std::integral_constant<int, LPS>{});
       }
       for (int it = it0; it < S; it += NST)
         static_for<NST>([&](auto b) {
-          if (it + decltype(b)::value < S) step(b, it + decltype(b)::value);
+          if (it + decltype(b)::value < S) step(std::integral_constant<int, (decltype(b)::value + LEAD) % NST>{}, it + decltype(b)::value, false);
         });
     };
     if constexpr (MODE == 3) {
@@ -952,7 +1041,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     }
   }
 
-  // epilogue: lane holds row (lane & 31) of each 32x32 tile, its columns 8*(v/4) + 4*(lane>>5) + v%4.  The tile goes
+  // epilogue: lane holds row (lane & 15) of each 16x16 tile, its columns 4*(lane>>4) + v.  The tile goes
   // through LDS (the operand stages are dead once every wave is past its last read) and leaves in 16-byte pieces of its
   // rows.  Straight from the registers, pairs of columns exchanged between lanes to make words, the way out took 18000 of
   // 123000 clocks of a 256 x 256 tile (K = 2048) and 37000 of 86000 of a 256 x 128 tile with fp32 results (K = 1024).
@@ -971,13 +1060,12 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
     for (int im = 0; im < TM; ++im)
 #pragma unroll
       for (int in = 0; in < TN; ++in)
+      {
+        float x[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float x[4];
-#pragma unroll
-          for (int t = 0; t < 4; ++t) x[t] = acc[im][in][4 * g + t];
-          f(wm * WTM + im * 32 + (lane & 31), wn * WTN + in * 32 + 8 * g + 4 * (lane >> 5), x);
-        }
+        for (int t = 0; t < 4; ++t) x[t] = acc[im][in][t];
+        f(wm * WTM + im * 16 + (lane & 15), wn * WTN + in * 16 + 4 * (lane >> 4), x);
+      }
   };
   auto stage_bf16 = [&] {
     each_quad([&](int r, int c, float (&x)[4]) {
@@ -1102,21 +1190,19 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       __syncthreads();
 #pragma unroll
       for (int im = 0; im < TM; ++im) {
-        const int li = wm * WTM + im * 32 + (lane & 31) - r0, i = m0 + r0 + li;
+        const int li = wm * WTM + im * 16 + (lane & 15) - r0, i = m0 + r0 + li;
         if (li < 0 || li >= rows_fit || i >= m1) continue;
-        int at = li * pitch + scatter_shift(P, i * P.srm.step + P.srm.off, c_lo) + P.scn.off + (wn * WTN + 4 * (lane >> 5)) * sc;
+        int at = li * pitch + scatter_shift(P, i * P.srm.step + P.srm.off, c_lo) + P.scn.off + (wn * WTN + 4 * (lane >> 4)) * sc;
         // (columns beyond the operand are padding zeros, those beyond the output stay out of the image)
-        int nj = imin(n1, n_valid) - (n0 + wn * WTN + 4 * (lane >> 5));
+        int nj = imin(n1, n_valid) - (n0 + wn * WTN + 4 * (lane >> 4));
 #pragma unroll
-        for (int in = 0; in < TN; ++in)
-#pragma unroll
-          for (int g = 0; g < 4; ++g, at += 8 * sc, nj -= 8) {
+        for (int in = 0; in < TN; ++in, at += 16 * sc, nj -= 16) {
             // (opaque: worked out ahead, the places of all columns would take 100 registers, and whether they exist 70 scalar ones)
             asm volatile("" : "+v"(at), "+v"(nj));
             uint16_t* const o = img + at;
 #pragma unroll
             for (int t = 0; t < 4; t += 2) {
-              float x0 = P.alpha * acc[im][in][4 * g + t], x1 = P.alpha * acc[im][in][4 * g + t + 1];
+              float x0 = P.alpha * acc[im][in][t], x1 = P.alpha * acc[im][in][t + 1];
               if (P.relu) x0 = fmaxf(x0, 0.0f), x1 = fmaxf(x1, 0.0f);
               const uint32_t w = pack_bf16x2(x0, x1);
               if (t < nj) o[t * sc] = (uint16_t)w;
