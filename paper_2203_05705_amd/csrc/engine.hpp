@@ -64,6 +64,7 @@ struct GemmParams {
   // applied) that a finishing pass reduces; NULL: the kernel stores the result itself
   float* part;
   int splits;
+  int sum_splits;  // run_gemm_partials: tiles of 256 x 128 and so many partial sums (0: its own choice)
 };
 
 // Host: may this operand be fetched with 16-byte loads?  KC operands need contiguous,

@@ -1048,8 +1048,8 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   // 4096^3 in 64 x 64 tiles at dp = 2: 85, 101 and 91 us forward, data and weight gradient, now 79, 94 and 87; projection of
   // 8192 x 1024 -> 2048 to fp32 67 -> 57 us; 128 x 4096 x 4096 in 32 x 32 tiles at dp = 3, weight gradient 20.8 -> 17.7 us.
   constexpr int NT = 64 * NW;
-  // (the 256 x 256 tile has no LDS to spare: it only stores plain bf16 results)
-  constexpr bool GENERAL_OUT = !(F_BM == 256 && BN == 256);
+  // (the 256 x 256 tile only stores plain results: bf16, and of operands along the contraction fp32)
+  constexpr bool GENERAL_OUT = !(F_BM == 256 && BN == 256), WIDE_OUT = GENERAL_OUT || (A_KC && B_KC && MODE == 0);
   // Columns at or beyond the B operand's extent (padding of a compact output) are stored as zeros:
   // the loaders fed them clamped, i.e. arbitrary, rows.
   const int n_valid = (MODE == 0 && P.ncls == 0) ? bn.n : 0x7fffffff;
@@ -1237,7 +1237,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   // Mapped rows / columns come in blocks that are multiples of 32, so one index lookup per block places all of its rows
   // (columns).
   const bool partial = GENERAL_OUT && P.part;
-  const bool wide = GENERAL_OUT && (P.part || P.out_f32 || P.beta != 0.0f);  // staged, or stored, as fp32
+  const bool wide = WIDE_OUT && (P.part || P.out_f32 || P.beta != 0.0f);  // staged, or stored, as fp32
   constexpr int HALF = F_BM / 2;
   static_assert(HALF * direct_pitch(BN, 4) <= F_BM * direct_pitch(BN, 2) && (size_t)F_BM * (direct_pitch(BN, 2) + 4) <= direct_lds_bytes(F_BM, BN, MODE),
                 "either tile ends before the rows' places, and these within the LDS of the launch");
@@ -1251,7 +1251,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   const int rows = partial || !P.c_rows_mapped ? imin(F_BM, P.M - m0) : F_BM;  // of the tile, that can exist
   constexpr int U = 4;  // rows at a time: everything read before anything is stored
   if (wide) {
-    if constexpr (GENERAL_OUT) {
+    if constexpr (WIDE_OUT) {
       constexpr int PITCH = direct_pitch(BN, 4), CL = BN / 4, RS = NT / CL;
       const int lj = tid % CL * 4, jb = jn0 + lj, j = jb + li_cb * jlim;  // (MODE 3: column within its block, of the product)
       const int nlim = partial ? jlim : P.c_cols_mapped ? bn.n : P.N;

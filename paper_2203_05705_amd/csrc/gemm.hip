@@ -196,7 +196,7 @@ static bool try_direct(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P,
   const int steps = ceil_div(k.n, 64);
   int bm = 64, bn = 64;
   long tiles = 0;
-  const bool plain_out = !raw_splits && direct_out && !C.out_f32 && C.beta == 0.0f && !C.relu_src;
+  const bool plain_out = !raw_splits && direct_out && (!C.out_f32 || (a_kc && b_kc)) && C.beta == 0.0f && !C.relu_src;
   for (const TileCfg& c : kTileCfgs) {
     if (c.bm == 256 && c.bn == 256 && !plain_out) continue;  // that tile only stores plain bf16
     tiles = (long)ceil_div(P.M, c.bm) * ceil_div(P.N, c.bn);
@@ -263,6 +263,10 @@ static bool try_direct(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P,
         if (gain > best) best = gain, splits = sp;
       }
     }
+  }
+  if (raw_splits && P.sum_splits > 0) {
+    bm = 256, bn = 128, splits = imin(P.sum_splits, steps);
+    tiles = (long)ceil_div(P.M, bm) * ceil_div(P.N, bn);
   }
   if (bm == 256 && bn == 256) splits = 1;
   size_t need = (splits > 1 || raw_splits || (!direct_out && !scatter)) ? (size_t)splits * P.M * P.N * 4 : 0;

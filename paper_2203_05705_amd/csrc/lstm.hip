@@ -19,6 +19,7 @@
 
 #include "fast.hpp"
 #include "pattern.hpp"
+#include "small.hpp"
 
 namespace ard {
 
@@ -61,6 +62,32 @@ template <typename T> __device__ __forceinline__ void lstm_store8(T* p, const T 
   }
 }
 
+// Kept units j .. j + 7 of the n of a row of them: every ax.step-th element of 8 ax.step, by 16-byte loads where the step is at most 4
+// and another kept unit follows (the loads end before it), else one by one (n > j; those beyond n are not read, and zero).
+template <typename T> __device__ __forceinline__ void lstm_gather8(const T* units, const Axis& ax, int j, T (&v)[8]) {
+  if (ax.kind == AX_AFFINE && ax.step == 1 && j + 8 <= ax.n) return lstm_load8(units + ax.off + j, v);
+  if constexpr (std::is_same<T, uint16_t>::value) {
+    if (ax.kind == AX_AFFINE && ax.step <= 4 && j + 8 < ax.n) {
+      auto wide = [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        SmallRaw<S> raw;
+        small_load<S>(raw, units + ax.off + j * S, 0, 0);
+        const bf16x8_t b = small_value<S>(raw);
+        __builtin_memcpy(v, &b, 16);
+      };
+      if (ax.step == 2) wide(std::integral_constant<int, 2>{});
+      else if (ax.step == 3) wide(std::integral_constant<int, 3>{});
+      else wide(std::integral_constant<int, 4>{});
+      return;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = units[ax_phys(ax, imin(j + i, ax.n - 1))];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (j + i >= ax.n) v[i] = (T)0;
+}
+
 // Everything a pass needs before its first product, in one launch (as five launches of a few microseconds each they
 // took 33 us of a layer of 1500 units): eight consecutive elements of a row per thread.
 template <typename T> struct LstmPrepare {
@@ -100,6 +127,8 @@ template <typename T> __global__ __launch_bounds__(256) void lstm_prepare_kernel
     const T* row = P.W + (long)prow * (P.I + P.H);
     if (!rec && q + 8 <= P.I && P.tp.dp <= 1) {
       lstm_load8(row + q, v);
+    } else if (rec && q < P.ax.n && P.tp.dp <= 1) {
+      lstm_gather8(row + P.I, P.ax, q, v);
     } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -121,11 +150,7 @@ template <typename T> __global__ __launch_bounds__(256) void lstm_prepare_kernel
     const long r = P.h0 + (long)rh;
     if (r >= P.h1) return;
     const int j = (int)(e - rh * (uint32_t)ch) * 8;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      v[i] = P.h[r * P.H + (j + i < P.ax.n ? ax_phys(P.ax, j + i) : 0)];
-      if (j + i >= P.ax.n) v[i] = (T)0;
-    }
+    lstm_gather8(P.h + r * P.H, P.ax, j, v);
     return lstm_store8(P.hc + r * P.Hp + j, v, 8);
   }
   b -= P.b_h;
@@ -245,41 +270,103 @@ __global__ void lstm_copy_rows_kernel(const T* src, long ld_src, int cols, long 
 
 // dW[(g*H + u)][q] from the compact gradients dwx[4Hp x Ip] and dwh[4Hp x Hp]; +0.0 for every
 // row of a dropped unit, every recurrent column of a dropped unit and every synapse of a dropped tile; gate rows p0 .. p1-1.
-// Eight neighbouring columns of a row per thread (one at a time: 20 us where the bytes take 6, 512 of 1024 units).
-template <typename T>
-__global__ __launch_bounds__(256) void lstm_scatter_dw_kernel(const T* dwx, const T* dwh, const int* rank, int H, int I, int Ip, int Hp, LstmTiles tp,
-                                                              FastDiv by_chunks, FastDiv by_h, int p0, int p1, T* dW) {
+// The gradients come in the storage type, or (SUMS) as nx and nh fp32 partial sums of each, added in order and rounded once.
+// Eight neighbouring columns of a row per thread (one at a time: 20 us where the bytes take 6, 512 of 1024 units); kept units in
+// arithmetic progression are worked out, not looked up (LISTED), so that one load stands before the store, and those among
+// eight recurrent columns are neighbours in the compact gradient: every second of 1500 units 19 -> 12 us.  (Four rows per thread
+// took a fifth longer.)
+struct LstmScatter {
+  const void *x, *h;
+  int nx, nh;
+  Axis ax;  // kept units
+  const int* rank;
+  int H, I, Ip, Hp;
+  LstmTiles tp;
+  FastDiv by_chunks, by_h, by_step;
+  int p0, p1;
+  void* dW;
+};
+template <typename T, bool SUMS, bool LISTED>
+__global__ __launch_bounds__(256) void lstm_scatter_dw_kernel(const LstmScatter P) {
+  static_assert(!(SUMS && LISTED), "partial sums come from affine patterns");
   const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-  const int chunks = (I + H + 7) >> 3, row = (int)fdiv(e, by_chunks), q = (int)(e - (uint32_t)row * (uint32_t)chunks) * 8;
-  const int p = p0 + row;  // physical gate row
-  if (p >= p1) return;
-  const int g = (int)fdiv((uint32_t)p, by_h), j = rank[p - g * H], n = imin(8, I + H - q);
+  const int H = P.H, I = P.I, chunks = (I + H + 7) >> 3, row = (int)fdiv(e, P.by_chunks), q = (int)(e - (uint32_t)row * (uint32_t)chunks) * 8;
+  const int p = P.p0 + row;  // physical gate row
+  if (p >= P.p1) return;
+  const int g = (int)fdiv((uint32_t)p, P.by_h), n = imin(8, I + H - q), u = p - g * H - P.ax.off, step = P.ax.step;
+  const int j = LISTED ? P.rank[p - g * H] : u < 0 ? 0 : (int)fdiv((uint32_t)u, P.by_step);
   T v[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) v[i] = (T)0;
-  if (j >= 0) {
-    const long r = (long)g * Hp + j;
-    if (q + 8 <= I) {
-      lstm_load8(dwx + r * Ip + q, v);
-    } else {
+  if (LISTED ? j >= 0 : u >= 0 && j * step == u && j < P.ax.n) {
+    const long r = (long)g * P.Hp + j;
+    if (q < I) {
+      // (rows are padded to eight: beyond the input's last column lie zeros)
+      if constexpr (SUMS) {
+        const float* src = (const float*)P.x + r * P.Ip + q;
+        const long plane = 4L * P.Hp * P.Ip;
+        float s[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k = 0; k < P.nx; k += 2) {
+          float4 t[4];
+          const float4 *s0 = reinterpret_cast<const float4*>(src + k * plane), *s1 = reinterpret_cast<const float4*>(src + imin(k + 1, P.nx - 1) * plane);
+          t[0] = s0[0], t[1] = s0[1], t[2] = s1[0], t[3] = s1[1];
+          const float* f = reinterpret_cast<const float*>(t);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int c = q + i;
-        if (c < I) {
-          v[i] = dwx[r * Ip + c];
-        } else if (i < n) {
-          const int jv = rank[c - I];
-          v[i] = dwh[r * Hp + (jv >= 0 ? jv : 0)];
-          if (jv < 0) v[i] = (T)0;
+          for (int i = 0; i < 8; ++i) s[i] += f[i];
+          if (k + 1 < P.nx)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s[i] += f[8 + i];
         }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = ElemTraits<T>::from_f32(s[i]);
+      } else {
+        lstm_load8((const T*)P.x + r * P.Ip + q, v);
       }
     }
-    if (tp.dp > 1)
+    if (LISTED && q + 8 > I) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int c = q + i - I, jv = c >= 0 && i < n ? P.rank[c] : -1;
+        const T b = ((const T*)P.h)[r * P.Hp + (jv >= 0 ? jv : 0)];
+        if (c >= 0) v[i] = jv >= 0 ? b : (T)0;
+      }
+    } else if (q + 8 > I) {
+      // recurrent columns: kept unit j0 + t at column `at` of the eight
+      const int c0 = q - I - P.ax.off, j0 = c0 <= 0 ? 0 : (int)fdiv((uint32_t)(c0 + step - 1), P.by_step);
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        if (!lstm_synapse_kept(tp, p, q + i)) v[i] = (T)0;
+        if (q + i >= I) v[i] = (T)0;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        if (t * step >= 8) break;
+        const int jc = j0 + t, at = jc < P.ax.n ? jc * step - c0 : 8;
+        const long from = r * P.Hp + imin(jc, P.Hp - 1);
+        T b;
+        if constexpr (SUMS) {
+          const long plane = 4L * P.Hp * P.Hp;
+          float s = 0.0f;
+          for (int k = 0; k < P.nh; k += 4) {
+            float f[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f[i] = ((const float*)P.h)[imin(k + i, P.nh - 1) * plane + from];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (k + i < P.nh) s += f[i];
+          }
+          b = ElemTraits<T>::from_f32(s);
+        } else {
+          b = ((const T*)P.h)[from];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = i == at ? b : v[i];
+      }
+    }
+    if (P.tp.dp > 1)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (!lstm_synapse_kept(P.tp, p, q + i)) v[i] = (T)0;
   }
-  lstm_store8(dW + (long)p * (I + H) + q, v, n);
+  lstm_store8((T*)P.dW + (long)p * (I + H) + q, v, n);
 }
 
 static bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -1587,6 +1674,33 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
   return ARD_OK;
 }
 
+// Weight gradients over many steps: tiles of 256 x 128 take less than half of the time per product that tiles of 64 x 64 take, but
+// there are too few of them for the chip; split into partial sums, h and x of them, which the pass that spreads the gradients adds.
+// Fitted times in us (256 CUs): a step of the large tiles 1, their start and end 5.5, 0.24 for each of a CU's steps of small ones;
+// partial sums are written at 5 and read back at 4 MB per us.  T = 64, B = 128, I = H = 1024, dp = 2: products 110 -> 66 us, the
+// spreading pass 15 -> 28 us.
+static bool lstm_sum_splits(const LstmArgs& a, int Ip, int Hp, size_t room, int& h, int& x) {
+  h = x = 0;
+  if (a.dtype != ARD_BF16 || a.T < 2 || a.ax.kind != AX_AFFINE || dev_knobs().no_fast) return false;
+  auto cost = [&](int N, int rows, int sp) {  // sp = 0: as it is without partial sums
+    const int steps = ceil_div(rows, 64), tiles = ceil_div(4 * Hp, 256) * ceil_div(N, 128);
+    const double mb = 16e-6 * Hp * (double)N;
+    if (sp == 0 && tiles < 220) return 4.0 + 0.24 / 256 * ceil_div(4 * Hp, 64) * ceil_div(N, 64) * (double)steps;
+    return ceil_div(tiles * (sp ? sp : 1), 256) * (ceil_div(steps, sp ? sp : 1) + 5.5) + sp * mb / 5 + sp * mb / 4;
+  };
+  auto best = [&](int N, int rows, size_t planes) {
+    int b = 0;
+    for (int sp = 1; sp <= 8 && (size_t)sp <= planes && sp * 4 <= ceil_div(rows, 64); ++sp)
+      if (!b || cost(N, rows, sp) < cost(N, rows, b)) b = sp;
+    return b;
+  };
+  const int rows = a.T * a.B;
+  const size_t plane_x = (size_t)16 * Hp * Ip, plane_h = (size_t)16 * Hp * Hp;
+  x = best(Ip, rows, room / plane_x);
+  if (x) h = best(Hp, rows - a.B, (room - x * plane_x) / plane_h);
+  return h && cost(Ip, rows, x) + cost(Hp, rows - a.B, h) + 8 < cost(Ip, rows, 0) + cost(Hp, rows - a.B, 0);
+}
+
 template <typename T>
 static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const void* h, const float* c,
                           const float* gates, const void* dh, void* dx, void* dW, const LstmWs& w,
@@ -1701,30 +1815,39 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
       }
     }
   }
+  LstmScatter S{};
+  void* dxo = Ip != I ? (void*)w.dxp : dx;
   {
     // dx[T*B x I] = dG . Wx', and the compact weight gradients dwx[4Hp x I] = dG^T . x, dwh[4Hp x Hp] = dG[1:]^T . h[kept][:-1]:
     // none needs another's result, so the bf16 ones of 64 x 64 tiles share a launch, each with partial sums of its own.
     // One after the other, each left CUs idle in its last round, or had fewer tiles than there are CUs (T = 64, B = 128,
     // I = H = 1024, dp = 2: 512 tiles, then 256, of 128 steps each).
     BatchOwn together;
-    if (T_ > 1) {
-      GemmParams P = plain_gemm(dG + (long)B * 4 * Hp, 4 * Hp, w.hc, Hp, w.dwh, Hp, 4 * Hp, Hp, (T_ - 1) * B, false, false, ce, false, 0.0f);
-      st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part, w.part_bytes);
-    } else {
-      st = fill_matrix(a.dtype, w.dwh, (long)4 * Hp * Hp, 0.0f, stream);
+    GemmParams Ph = plain_gemm(dG + (long)B * 4 * Hp, 4 * Hp, w.hc, Hp, w.dwh, Hp, 4 * Hp, Hp, (T_ - 1) * B, false, false, ce, false, 0.0f);
+    GemmParams Px = plain_gemm(dG, 4 * Hp, xs, Ip, w.dwx, Ip, 4 * Hp, Ip, T_ * B, false, false, ce, false, 0.0f);
+    if (lstm_sum_splits(a, Ip, Hp, w.part_bytes, Ph.sum_splits, Px.sum_splits)) {
+      const size_t room_x = (size_t)Px.sum_splits * 16 * Hp * Ip;
+      S.x = w.part, S.h = w.part + room_x;
+      if (!run_gemm_partials(a.dtype, false, false, Px, stream, w.part, room_x, &S.nx, &st)) S.nx = 0;
+      else if (!st && !run_gemm_partials(a.dtype, false, false, Ph, stream, w.part + room_x, w.part_bytes - room_x, &S.nh, &st)) S.nx = 0;
+      if (st) return st;
     }
-    if (st) return st;
-    GemmParams P = plain_gemm(dG, 4 * Hp, xs, Ip, w.dwx, Ip, 4 * Hp, Ip, T_ * B, false, false, ce, false, 0.0f);
-    st = run_gemm(a.dtype, false, false, P, 0, 0, stream, w.part_dwx, w.part_dwx_bytes);
-    if (st) return st;
-    void* dxo = Ip != I ? (void*)w.dxp : dx;
-    P = plain_gemm(dG, 4 * Hp, w.wxc, Ip, dxo, Ip, T_ * B, Ip, 4 * Hp, true, false, ce, false, 0.0f);
+    if (!S.nx) {
+      st = T_ > 1 ? run_gemm(a.dtype, false, false, Ph, 0, 0, stream, w.part, w.part_bytes) : fill_matrix(a.dtype, w.dwh, (long)4 * Hp * Hp, 0.0f, stream);
+      if (st) return st;
+      st = run_gemm(a.dtype, false, false, Px, 0, 0, stream, w.part_dwx, w.part_dwx_bytes);
+      if (st) return st;
+    }
+    // (bf16 rows of whole words leave without their padding)
+    if (Ip != I && a.es == 2 && I % 2 == 0 && ((uintptr_t)dx & 3) == 0 && !dev_knobs().no_fast && 4L * Hp * (T_ * (long)B > Ip ? T_ * (long)B : Ip) < (1L << 31) && (long)T_ * B * Ip < (1L << 31)) dxo = dx;
+    GemmParams P = plain_gemm(dG, 4 * Hp, w.wxc, Ip, dxo, dxo == dx ? I : Ip, T_ * B, dxo == dx ? I : Ip, 4 * Hp, true, false, ce, false, 0.0f);
+    if (a.es == 2) P.B.rpad = 1, P.B.vec = 1;  // (16-byte runs of the weights end in their padding)
     st = run_gemm(a.dtype, true, false, P, 0, 0, stream, w.part_dx, w.part_dx_bytes);
     if (st) return st;
     st = together.launch(stream);
     if (st) return st;
   }
-  if (Ip != I) {
+  if (dxo != dx) {
     const long rows_total = (long)T_ * B;
     for (long r0 = 0; r0 < rows_total; r0 += 65535) {
       const long rows = rows_total - r0 < 65535 ? rows_total - r0 : 65535;
@@ -1734,10 +1857,15 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
     }
   }
   const int chunks = (I + H + 7) / 8, step = lstm_rows_per_launch(chunks);
-  for (int p0 = 0, p1; p0 < 4 * H; p0 = p1) {
-    p1 = 4 * H - p0 < step ? 4 * H : p0 + step;
-    ARD_LAUNCH(lstm_scatter_dw_kernel<T>, dim3((unsigned)(((long)(p1 - p0) * chunks + 255) / 256)), dim3(256), 0, stream, (const T*)w.dwx,
-               (const T*)w.dwh, (const int*)w.rank, H, I, Ip, Hp, a.tiles, fast_div((uint32_t)chunks), fast_div((uint32_t)H), p0, p1, (T*)dW);
+  if (!S.nx) S.x = w.dwx, S.h = w.dwh;
+  S.ax = a.ax, S.H = H, S.I = I, S.Ip = Ip, S.Hp = Hp, S.tp = a.tiles, S.dW = dW, S.rank = w.rank;
+  S.by_chunks = fast_div((uint32_t)chunks), S.by_h = fast_div((uint32_t)H), S.by_step = fast_div((uint32_t)imax(a.ax.step, 1));
+  for (S.p0 = 0; S.p0 < 4 * H; S.p0 = S.p1) {
+    S.p1 = 4 * H - S.p0 < step ? 4 * H : S.p0 + step;
+    const dim3 grid((unsigned)(((long)(S.p1 - S.p0) * chunks + 255) / 256));
+    if (S.nx) ARD_LAUNCH_NAMED("lstm_scatter_dw_kernel", (lstm_scatter_dw_kernel<T, true, false>), grid, dim3(256), 0, stream, S);
+    else if (a.ax.kind == AX_AFFINE) ARD_LAUNCH_NAMED("lstm_scatter_dw_kernel", (lstm_scatter_dw_kernel<T, false, false>), grid, dim3(256), 0, stream, S);
+    else ARD_LAUNCH_NAMED("lstm_scatter_dw_kernel", (lstm_scatter_dw_kernel<T, false, true>), grid, dim3(256), 0, stream, S);
     ARD_LAUNCH_CHECK("lstm_scatter_dw_kernel");
   }
   return ARD_OK;
