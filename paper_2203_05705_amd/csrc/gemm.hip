@@ -541,9 +541,9 @@ static bool try_fast_tile(int op, const LayerArgs& a, const void* Ap, const void
   // a multiple of the CU count (288 for dp = 3), which smaller tiles avoid.  Round times (us) measured on
   // the dense 4096^3 product per tile and operand layout; an 8-wavefront tile has one slot per CU, a
   // 4-wavefront tile two.
-  static const float kRoundUs[3][5] = {{2.21f, 1.33f, 1.32f, 0.79f, 0.464f},   // forward (both operands contraction-contiguous)
-                                       {2.04f, 1.19f, 1.17f, 0.70f, 0.43f},    // data gradient
-                                       {1.98f, 1.14f, 1.16f, 0.66f, 0.44f}};   // weight gradient
+  static const float kRoundUs[3][5] = {{1.65f, 0.93f, 0.98f, 0.60f, 0.366f},   // forward (both operands contraction-contiguous)
+                                       {1.61f, 0.905f, 0.98f, 0.59f, 0.375f},  // data gradient
+                                       {1.70f, 0.95f, 1.01f, 0.66f, 0.433f}};  // weight gradient
   int steps = op == 2 ? ceil_div(B, 64) : 0;
   if (op != 2)
     for (int c = 0; c < t.ncls; ++c) steps = imax(steps, ceil_div(t.k_cnt[c] * t.k_bs, 64));
