@@ -446,10 +446,7 @@ __device__ __forceinline__ bf16x8_t frag_value(const Frag& f) {
 // (8 wavefronts hide the LDS and MFMA latencies), so its stages must fit twice into the 160 KiB
 // LDS; only the smallest of these tiles has room for a third stage.  Of the 8-wavefront tiles, one workgroup a CU, those of 384
 // rows and columns together have it (two stages: 8192 x 2048 x 1024 42 us, three 37).
-#ifndef ARD_NST_SMALL
-#define ARD_NST_SMALL 3
-#endif
-constexpr int direct_stages(int bm, int bn) { return bm + bn <= 128 || bm + bn == 384 ? ARD_NST_SMALL : 2; }
+constexpr int direct_stages(int bm, int bn) { return bm + bn <= 128 || bm + bn == 384 ? 3 : 2; }
 // MFMAs of a wavefront, from the hand-over of a stage on, over which the loads of a stage are spread (`step`: of a step, `unit`: of a
 // unit; the last unit of a step but one is left out).  Over all of a step where a stage has two steps to arrive; where it has one,
 // what a spread gains at the issue it loses at the end: over five eighths of a step, 4096^3 at dp = 2 took 134 instead of 120

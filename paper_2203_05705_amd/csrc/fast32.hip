@@ -38,10 +38,12 @@ struct F32Cfg {
   int bm, bn, wk, d;
   float eff;
 };
-// The last two are for convolutions: few channels, any number of pixels, whose wavefronts lie side by side along the
+// The last four are for convolutions: few channels, any number of pixels, whose wavefronts lie side by side along the
 // pixels so that a contraction of a few dozen steps is not dealt over them as well (64 rows, 65536 pixels, 18 steps:
-// 32 us against 43 with 64 x 64 tiles; 32 rows, 36 steps: 29 against 43 with 32 x 32 tiles).
-static const F32Cfg kF32Cfgs[6] = {{128, 128, 1, 3, 0.85f}, {64, 64, 4, 3, 0.8f}, {32, 32, 4, 4, 0.6f}, {16, 16, 4, 8, 0.4f}, {64, 256, 1, 3, 0.8f}, {32, 256, 1, 4, 0.7f}};
+// 32 us against 43 with 64 x 64 tiles; 32 rows, 36 steps: 29 against 43 with 32 x 32 tiles; 64 rows, 25088 pixels, 72 steps,
+// layer 71 us with 32 x 32 tiles, 57 with 32 x 256, 60 with 64 x 128).
+static const F32Cfg kF32Cfgs[8] = {{128, 128, 1, 3, 0.85f}, {64, 64, 4, 3, 0.8f}, {32, 32, 4, 4, 0.6f}, {16, 16, 4, 8, 0.4f},
+                                   {64, 256, 1, 3, 0.94f}, {32, 256, 1, 4, 0.78f}, {64, 128, 1, 3, 0.79f}, {32, 128, 1, 4, 0.63f}};
 
 template <int AK, int BK, int MODE>
 static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
@@ -63,6 +65,8 @@ static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
     switch (cfg) {
       ARD_F32_CASE(4, 4, 4, 1, 4, 1, 3)
       ARD_F32_CASE(5, 2, 4, 1, 4, 1, 4)
+      ARD_F32_CASE(6, 4, 2, 1, 4, 1, 3)
+      ARD_F32_CASE(7, 2, 2, 1, 4, 1, 4)
       default: break;
     }
   }
@@ -71,7 +75,7 @@ static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
     ARD_F32_CASE(1, 4, 4, 1, 1, 4, 3)
     ARD_F32_CASE(2, 2, 2, 1, 1, 4, 4)
     ARD_F32_CASE(3, 1, 1, 1, 1, 4, 8)
-    case 4: case 5: break;
+    case 4: case 5: case 6: case 7: break;
     default: return fail(ARD_EUNSUPPORTED, "no such fp32 tile");
   }
 #undef ARD_F32_CASE
@@ -188,12 +192,17 @@ int32_t f32_conv_product(const float* W, int rows, const float* grid, const F32C
   F.am = axis_identity(rows), F.bn = axis_identity(cv.npix), F.k = axis_identity(taps_cp);
   F.C = C, F.M = rows, F.N = cv.npix, F.splits = 1;
   F.cv = cv;
+  // Shares of the matrix-core rate and clocks of a memory round trip and of a workgroup's start and end in convolutions, fitted to
+  // forward passes and data gradients of 140 layers (8 - 128 images, 16 - 512 channels, 7 x 7 - 56 x 56, a third to all maps kept):
+  // the choice is 1.7 % off the best tile in the mean (products' values, without the last two tiles: 6.4 %).
+  static const float kConvEff[8] = {0.85f, 0.68f, 0.49f, 0.31f, 0.94f, 0.78f, 0.79f, 0.63f};
   int cfg = 0;
   float best = 0.0f;
-  for (int i = 0; i < 6; ++i) {
+  for (int i = 0; i < 8; ++i) {
     const F32Cfg& c = kF32Cfgs[i];
-    const long tiles = (long)ceil_div(rows, c.bm) * ceil_div(cv.npix, c.bn);
-    const float t = f32_clocks(c, tiles, taps_cp, 1, 1.0f);
+    const float rounds = (float)(((long)ceil_div(rows, c.bm) * ceil_div(cv.npix, c.bn) + 255) / 256), area = (float)c.bm * c.bn;
+    const float mfma = rounds * area * taps_cp * (2.0f / 256.0f) / kConvEff[i], chain = 1870.0f * ceil_div(imax(1, taps_cp / 16 / c.wk), c.d);
+    const float t = (mfma > chain ? mfma : chain) + rounds * (965.0f + 0.25f * area);
     if (i == 0 || t < best) best = t, cfg = i;
   }
   F.tiles_m = ceil_div(rows, kF32Cfgs[cfg].bm), F.tiles_n = ceil_div(cv.npix, kF32Cfgs[cfg].bn);
