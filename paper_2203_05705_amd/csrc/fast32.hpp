@@ -549,11 +549,15 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   // store (at any dword).  A thread works out once which of its four are kept and then goes down the rows, the wavefronts'
   // partial tiles summed in place before (the loop below sums them again for each position of a strided map).  Weight
   // gradient, 128 x 2048 -> 2048: dp 2 and 2 21.8 -> 17.6 us, dp 4 and 1 17.2 -> 14.9.  Where nothing is dropped nothing is
-  // summed twice and the pass that sums in place costs more (30 x 1024 -> 3000: 16.6 us, in runs 18.0); with smaller tiles,
-  // tile classes and convolutions the setting up does (10.2 -> 10.8 us at 24 x 1472 -> 448 in tiles, 136.6 -> 138 us in
+  // summed twice and the pass that sums in place costs more (30 x 1024 -> 3000: 16.6 us, in runs 18.0); with tile classes,
+  // convolutions and tiles that own no wider rows the setting up does (10.2 -> 10.8 us at 24 x 1472 -> 448 in tiles, 136.6 -> 138 us in
   // three products of a convolution).
-  const bool runs = MODE == 0 && BM * BN >= 4096 && !classes && beta == 0.0f && walk && (cols.step > 1 || rows.n < rows.nphys);
-  if (MODE == 0 && BM * BN >= 4096 && runs) {
+  // Tiles of 32 x 32 only where columns are dropped too: 128 x 2048 -> 2048, dp 3 and 3 12.8 -> 11.1 us, 5 and 5 16.6 -> 12.7,
+  // 2 and 1 19.5 -> 20.0.  (Strided rows of A beside whole columns of B: a weight gradient whose columns are all kept, which the
+  // code alone makes longer, 64 x 784 -> 1024 18.66 -> 18.82 us for three products.)
+  constexpr bool RUNS = MODE == 0 && (BM * BN >= 4096 || (BM * BN >= 1024 && !(AK == F32_MC && BK == F32_MC_VEC)));
+  const bool runs = RUNS && !classes && beta == 0.0f && walk && (cols.step > 1 || (BM * BN >= 4096 && rows.n < rows.nphys));
+  if constexpr (RUNS) if (runs) {
     if constexpr (WK > 1) {  // the partial tiles, summed in place
       for (int e = tid; e < BM * BN; e += 256) {
         const int lr = e / BN, lc = e % BN;
