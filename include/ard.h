@@ -496,6 +496,9 @@ int32_t ard_debug_dry_launches(char* names, size_t cap);
 /* Bounds proofs run on this thread since the last call; six[0..5] = first byte, end byte and size of
  * operand A, then of operand B, of the most recent one (offsets relative to the operand's pointer). */
 int32_t ard_debug_last_bounds(int64_t* six);
+/* Contraction steps, since the last call on this thread, at which those proofs stepped the iterator of a kernel's steady
+ * loop beside the arithmetic that they walk (a step where the two differ refuses the launch). */
+int64_t ard_debug_compared_slabs(void);
 /* The proofs treat every operand as `elems` elements shorter than stated (0 = normal).  Lets a test
  * show that a proof rejects a launch whose loads would end past a (pretended) operand end. */
 void ard_debug_set_extent_slack(int64_t elems);

@@ -132,6 +132,7 @@ _SIGS = {
     "ard_debug_set_dry_run": (None, [C.c_int32]),
     "ard_debug_dry_launches": (C.c_int32, [C.c_char_p, C.c_size_t]),
     "ard_debug_last_bounds": (C.c_int32, [C.c_void_p]),
+    "ard_debug_compared_slabs": (C.c_int64, []),
     "ard_debug_set_extent_slack": (None, [C.c_int64]),
     "ard_last_error": (C.c_char_p, []),
     "ard_version": (C.c_int32, []),

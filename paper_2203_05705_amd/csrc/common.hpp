@@ -44,6 +44,7 @@ hipError_t raise_lds_limit(const void* kernel, int bytes);  // hipFuncSetAttribu
 // byte ranges [lo, hi) the loaders of one LDS-direct launch touch behind A and B (host-side proof)
 struct DirectBounds {
   long a_lo, a_hi, b_lo, b_hi;
+  long slabs;  // contraction steps at which the steady loop's iterator was compared with the arithmetic proved
 };
 void note_direct_bounds(const DirectBounds& b, long a_bytes, long b_bytes);
 long extent_slack();  // elements the proofs pretend each operand is shorter by (ard_debug_set_extent_slack; 0 in normal use)

@@ -669,6 +669,52 @@ __host__ __device__ __forceinline__ void direct_slab(const FastParams& P, const 
   ksb = ks;
 }
 
+// May only the last step of this contraction be a partial one?  (The axis is affine, or made of whole blocks that hold whole steps.)
+__host__ __device__ __forceinline__ bool direct_full_steps(const Axis& k) {
+  return k.kind == AX_AFFINE || (k.kind == AX_BAFF && (k.bs % 64 == 0 || k.bs == 32) && k.nphys % k.bs == 0);
+}
+
+// The slabs of direct_slab one after the other from step `s` on, without the divisions that finding one takes; in scalar
+// registers, so that the loads take their base from there.  (Host-callable: the bounds proof steps it beside direct_slab.)
+template <int MODE> struct DirectSlabs {
+  int at = 0, atb = 0, in_run = 0, run = 0, jump = 0, in_row = 0;
+  __host__ __device__ static __forceinline__ int uniform(int x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_readfirstlane(x);
+#else
+    return x;
+#endif
+  }
+  __host__ __device__ __forceinline__ void begin(const FastParams& P, const Axis& kax, int s) {
+    if constexpr (MODE == 1) {
+      int ks, ksb;
+      direct_slab<MODE>(P, kax, s, ks, ksb);
+      at = uniform(ks), atb = uniform(ksb);
+      in_run = s - (int)fdiv((uint32_t)s, P.cv.by_taps) * P.cv.taps, in_row = in_run - (int)fdiv((uint32_t)in_run, P.cv.by_kw) * P.cv.kw;
+    } else {
+      at = uniform(fast_kslab(kax, s * 64));
+      run = kax.kind == AX_BAFF ? imax(kax.bs, 64) : 0x40000000, jump = kax.kind == AX_BAFF ? (kax.step - 1) * run : 0;
+      in_run = kax.kind == AX_BAFF ? s * 64 % run : 0;
+    }
+  }
+  __host__ __device__ __forceinline__ void next(const FastParams& P, int& ks, int& ksb) {
+    if constexpr (MODE == 1) {
+      ks = at, ksb = atb;
+      at += P.cv.Cp, atb += P.cv.Cp;
+      if (++in_row == P.cv.kw) in_row = 0, atb += (P.cv.Wg - P.cv.kw) * P.cv.Cp;
+      if (++in_run == P.cv.taps) {  // the next 64 channels
+        at += 64 - P.cv.taps * P.cv.Cp;
+        atb = at;
+        in_run = 0;
+      }
+    } else {
+      ks = ksb = at;
+      at += 64, in_run += 64;
+      if (in_run == run) at += jump, in_run = 0;
+    }
+  }
+};
+
 // MODE 0: plain product.  MODE 1: convolution, B rows are output pixels gathered from the
 // bordered channels-last grid (contraction = (tap, channel)), output NCHW.  MODE 2: weight
 // gradient of the convolution, contraction over the grid's pixels, B columns = (tap, channel).
@@ -887,37 +933,13 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       wait(UNITS - 1);
     };
     using I0 = std::integral_constant<int, 0>;
-    // Slabs one after the other, without the divisions that finding one takes; in scalar registers, so that the loads take their
-    // base from there.
-    int next_ks = 0, next_ksb = 0, in_run = 0, run = 0, jump = 0, in_row = 0;
-    auto begin_slabs = [&](int s) {
-      if constexpr (MODE == 1) {
-        int ks, ksb;
-        direct_slab<MODE>(P, kax, s, ks, ksb);
-        next_ks = __builtin_amdgcn_readfirstlane(ks), next_ksb = __builtin_amdgcn_readfirstlane(ksb);
-        in_run = s - (int)fdiv((uint32_t)s, P.cv.by_taps) * P.cv.taps, in_row = in_run - (int)fdiv((uint32_t)in_run, P.cv.by_kw) * P.cv.kw;
-      } else if constexpr (MODE != 3) {
-        next_ks = __builtin_amdgcn_readfirstlane(fast_kslab(kax, s * 64));
-        run = kax.kind == AX_BAFF ? imax(kax.bs, 64) : 0x40000000, jump = kax.kind == AX_BAFF ? (kax.step - 1) * run : 0;
-        in_run = kax.kind == AX_BAFF ? s * 64 % run : 0;
-      }
-    };
+    // The steady loop's slabs come from the iterator (DirectSlabs).
+    DirectSlabs<MODE> slabs;
     auto next_slab = [&](int s, int& ks, int& ksb) {
       if constexpr (MODE == 1) {
         if (kb_mode) return slab(s, ks, ksb);
-        ks = next_ks, ksb = next_ksb;
-        next_ks += P.cv.Cp, next_ksb += P.cv.Cp;
-        if (++in_row == P.cv.kw) in_row = 0, next_ksb += (P.cv.Wg - P.cv.kw) * P.cv.Cp;
-        if (++in_run == P.cv.taps) {  // the next 64 channels
-          next_ks += 64 - P.cv.taps * P.cv.Cp;
-          next_ksb = next_ks;
-          in_run = 0;
-        }
-      } else {
-        ks = ksb = next_ks;
-        next_ks += 64, in_run += 64;
-        if (in_run == run) next_ks += jump, in_run = 0;
       }
+      slabs.next(P, ks, ksb);
     };
     // One contraction step from stage BUF.  A unit's reads are in flight behind the MFMAs of the one before; the stage
     // hand-over (wait for the next stage's loads, barrier, read the next stage's first unit, start the loads of stage it+NST
@@ -1002,9 +1024,9 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
       // steps it whose stage it+NST is not the last one (only the last can be partial); a window longer than a unit begins in the
       // step before them
       constexpr int LEAD = LeftOver::value < LPS ? 1 : 0;
-      const bool steady = (MODE == 3 || kax.kind == AX_AFFINE || (kax.kind == AX_BAFF && (kax.bs % 64 == 0 || kax.bs == 32) && kax.nphys % kax.bs == 0)) && LEAD + 2 * NST < S;
+      const bool steady = (MODE == 3 || direct_full_steps(kax)) && LEAD + 2 * NST < S;
       int it0 = LEAD;
-      if (steady) begin_slabs(s_lo + NST);
+      if (MODE != 3 && steady) slabs.begin(P, kax, s_lo + NST);
       if constexpr (LEAD) step(I0{}, 0, steady);
       if (steady) {
         for (; it0 + 2 * NST < S; it0 += NST)
@@ -1721,7 +1743,8 @@ static inline int class_grid(const ClassTab& t) {
 //    indices the clamps in DirectLoader::init* and the tail rules allow, as inequalities.
 //  * direct_prove (dry-run mode and ARD_PROVE_BOUNDS=1, every workgroup x wave x lane x step): runs
 //    the kernel's own assignment and address arithmetic (direct_assign, DirectLoader::init*,
-//    direct_slab, tail_live are host-callable) and records the smallest and largest byte touched.
+//    direct_slab, tail_live are host-callable) and records the smallest and largest byte touched;
+//    the steady loop's iterator (DirectSlabs) is stepped beside direct_slab and has to give the same slabs.
 static inline bool axis_rows_ok(const Axis& r, bool has_list) {
   // rows of a KC operand after the clamp of init(): min(row, n-1), block axes also clamped to nphys-1
   if (r.n < 1 || r.nphys < 1) return false;
@@ -1836,7 +1859,7 @@ static inline Axis axis_list_surrogate(const Axis& r, bool last) {
 template <bool A_KC, bool B_KC, int BM, int BN, int NW, int MODE>
 static int32_t direct_prove(const FastParams& P_in, int grid_x, DirectBounds& out) {
   constexpr long NONE_LO = 0x7fffffffffffffffL;
-  out = DirectBounds{NONE_LO, -1, NONE_LO, -1};
+  out = DirectBounds{NONE_LO, -1, NONE_LO, -1, 0};
   using LA = DirectLoader<A_KC, BM, NW>;
   using LB = DirectLoader<B_KC, BN, NW>;
   FastParams P = P_in;
@@ -1849,6 +1872,18 @@ static int32_t direct_prove(const FastParams& P_in, int grid_x, DirectBounds& ou
     if (Kn <= 0) continue;
     const int S_all = (Kn + 63) >> 6;
     const int s_lo = (int)((long)wk.split * S_all / P.splits), s_hi = (int)((long)(wk.split + 1) * S_all / P.splits);
+    if (direct_full_steps(wk.kax)) {
+      DirectSlabs<MODE> it;
+      const int s0 = s_lo + direct_stages(BM, BN);
+      if (s0 < s_hi) it.begin(P, wk.kax, s0);
+      for (int s = s0; s < s_hi; ++s) {
+        int ks, ksb, is, isb;
+        direct_slab<MODE>(P, wk.kax, s, ks, ksb);
+        it.next(P, is, isb);
+        if (is != ks || isb != ksb) return fail(ARD_ESHAPE, "bounds proof: step %d at %d, %d and not at %d, %d", s, is, isb, ks, ksb);
+      }
+      if (s0 < s_hi) out.slabs += s_hi - s0;
+    }
     for (int pass = 0; pass < 2; ++pass) {  // (second pass only differs for LIST axes and pixel lists)
       if (pass == 1 && wk.am.kind != AX_LIST && wk.bn.kind != AX_LIST && !P.cv.pix) break;
       const Axis am = axis_list_surrogate(wk.am, pass == 1), bn = axis_list_surrogate(wk.bn, pass == 1);

@@ -42,10 +42,11 @@ void note_dry_launch(const char* kernel) {
 // the number of proofs since the last query
 static thread_local long g_last_bounds[6] = {0, 0, 0, 0, 0, 0};
 static thread_local int g_n_proofs = 0;
+static thread_local long g_slabs = 0;  // steps compared in these proofs
 void note_direct_bounds(const DirectBounds& b, long a_bytes, long b_bytes) {
   g_last_bounds[0] = b.a_lo, g_last_bounds[1] = b.a_hi, g_last_bounds[2] = a_bytes;
   g_last_bounds[3] = b.b_lo, g_last_bounds[4] = b.b_hi, g_last_bounds[5] = b_bytes;
-  ++g_n_proofs;
+  ++g_n_proofs, g_slabs += b.slabs;
 }
 static long g_extent_slack = 0;
 long extent_slack() { return g_extent_slack; }
@@ -217,6 +218,12 @@ extern "C" int32_t ard_debug_last_bounds(int64_t* six) {
     for (int i = 0; i < 6; ++i) six[i] = g_last_bounds[i];
   const int n = g_n_proofs;
   g_n_proofs = 0;
+  return n;
+}
+
+extern "C" int64_t ard_debug_compared_slabs(void) {
+  const long n = g_slabs;
+  g_slabs = 0;
   return n;
 }
 
