@@ -493,6 +493,9 @@ void ard_debug_set_dry_run(int32_t on);
 /* Launches skipped on this thread since the last call (or mode switch); if names != NULL their kernel
  * names, comma separated and truncated to cap-1 characters, are copied there. */
 int32_t ard_debug_dry_launches(char* names, size_t cap);
+/* The same launches, left to be read again, their names separated by semicolons and with what says which instance of a
+ * kernel was taken, for instance the workgroup tile: "gemm_direct_kernel<256, 128, 0>" (rows, columns, mode). */
+int32_t ard_debug_dry_instances(char* names, size_t cap);
 /* Bounds proofs run on this thread since the last call; six[0..5] = first byte, end byte and size of
  * operand A, then of operand B, of the most recent one (offsets relative to the operand's pointer). */
 int32_t ard_debug_last_bounds(int64_t* six);

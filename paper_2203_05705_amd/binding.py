@@ -131,6 +131,7 @@ _SIGS = {
     "ard_conv_out_size": (C.c_int32, [C.c_int32] * 4),
     "ard_debug_set_dry_run": (None, [C.c_int32]),
     "ard_debug_dry_launches": (C.c_int32, [C.c_char_p, C.c_size_t]),
+    "ard_debug_dry_instances": (C.c_int32, [C.c_char_p, C.c_size_t]),
     "ard_debug_last_bounds": (C.c_int32, [C.c_void_p]),
     "ard_debug_compared_slabs": (C.c_int64, []),
     "ard_debug_set_extent_slack": (None, [C.c_int64]),

@@ -20,6 +20,7 @@ int32_t fail(int32_t code, const char* fmt, ...);
 // would have issued.  The mode exists so that host logic can be tested on a machine without a GPU.
 bool dry_run();
 void note_dry_launch(const char* kernel);
+const char* launch_instance(const char* kernel, int a, int b, int c);  // "kernel<a, b, c>" until this thread's next call
 hipError_t launch_status();  // hipGetLastError(), or hipSuccess in dry-run mode
 hipError_t raise_lds_limit(const void* kernel, int bytes);  // hipFuncSetAttribute(max dynamic LDS); no-op in dry-run mode
 #define ARD_LAUNCH_NAMED(name, kernel, ...)                      \

@@ -1955,7 +1955,7 @@ static int32_t launch_direct_alone(const FastParams& F, int grid_x, hipStream_t 
     ARD_HIP_CHECK(ard::raise_lds_limit((const void*)kernel, (int)lds_bytes));
     raised = !dry_run();
   }
-  ARD_LAUNCH_NAMED("gemm_direct_kernel", kernel, dim3((unsigned)grid_x), dim3(64 * NW), lds_bytes, stream, F);
+  ARD_LAUNCH_NAMED(launch_instance("gemm_direct_kernel", BM, BN, MODE), kernel, dim3((unsigned)grid_x), dim3(64 * NW), lds_bytes, stream, F);
   ARD_LAUNCH_CHECK("gemm_direct_kernel");
   return ARD_OK;
 }

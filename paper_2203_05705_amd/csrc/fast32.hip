@@ -58,7 +58,7 @@ static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
       ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));                                     \
       raised = !dry_run();                                                                               \
     }                                                                                                    \
-    ARD_LAUNCH_NAMED("gemm_f32_kernel", kernel, g, b, lds, stream, F);                                   \
+    ARD_LAUNCH_NAMED(launch_instance("gemm_f32_kernel", c.bm, c.bn, MODE), kernel, g, b, lds, stream, F); \
     break;                                                                                               \
   }
   if constexpr (MODE == 1) {

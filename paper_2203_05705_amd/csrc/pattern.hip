@@ -25,9 +25,12 @@ static thread_local char g_err[512] = "";
 static int g_dry_run = 0;                       // process-wide switch
 static thread_local int g_dry_count = 0;        // launches skipped on this thread since the last reset
 static thread_local char g_dry_log[2048] = "";  // their kernel names, comma separated (truncated when full)
+static thread_local char g_dry_instances[8192] = "";  // the same with what says which instance, separated by semicolons
 bool dry_run() { return g_dry_run != 0; }
 void note_dry_launch(const char* kernel) {
   ++g_dry_count;
+  const size_t at = strlen(g_dry_instances);
+  if (at + strlen(kernel) + 2 < sizeof(g_dry_instances)) snprintf(g_dry_instances + at, sizeof(g_dry_instances) - at, at ? ";%s" : "%s", kernel);
   // keep the template name without its argument list
   size_t len = strlen(g_dry_log), n = 0;
   while (*kernel == '(') ++kernel;
@@ -37,6 +40,11 @@ void note_dry_launch(const char* kernel) {
     memcpy(g_dry_log + len, kernel, n);
     g_dry_log[len + n] = 0;
   }
+}
+const char* launch_instance(const char* kernel, int a, int b, int c) {
+  static thread_local char name[96];
+  snprintf(name, sizeof name, "%s<%d, %d, %d>", kernel, a, b, c);
+  return name;
 }
 // [a_lo, a_hi, a_bytes, b_lo, b_hi, b_bytes] of this thread's most recent exhaustive bounds proof, and
 // the number of proofs since the last query
@@ -198,7 +206,7 @@ extern "C" int32_t ard_version(void) { return 200; }
 extern "C" void ard_debug_set_dry_run(int32_t on) {
   g_dry_run = on ? 1 : 0;
   g_dry_count = 0;
-  g_dry_log[0] = 0;
+  g_dry_log[0] = g_dry_instances[0] = 0;
 }
 extern "C" int32_t ard_debug_dry_launches(char* names, size_t cap) {
   if (names && cap) {
@@ -207,8 +215,15 @@ extern "C" int32_t ard_debug_dry_launches(char* names, size_t cap) {
   }
   const int n = g_dry_count;
   g_dry_count = 0;
-  g_dry_log[0] = 0;
+  g_dry_log[0] = g_dry_instances[0] = 0;
   return n;
+}
+extern "C" int32_t ard_debug_dry_instances(char* names, size_t cap) {
+  if (names && cap) {
+    strncpy(names, g_dry_instances, cap - 1);
+    names[cap - 1] = 0;
+  }
+  return g_dry_count;
 }
 
 extern "C" void ard_debug_set_extent_slack(int64_t elems) { g_extent_slack = elems; }

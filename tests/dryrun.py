@@ -37,6 +37,14 @@ def launches(lib):
     return n, buf.value.decode().split(",") if buf.value else []
 
 
+def instances(lib):
+    """Names of the launches since the last launches(), with what says which instance of a kernel was taken; resets both."""
+    buf = C.create_string_buffer(8192)
+    lib.ard_debug_dry_instances(buf, 8192)
+    launches(lib)
+    return buf.value.decode().split(";") if buf.value else []
+
+
 def last_bounds(lib):
     six = (C.c_int64 * 6)()
     n = lib.ard_debug_last_bounds(six)
