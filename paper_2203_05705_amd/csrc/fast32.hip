@@ -32,18 +32,31 @@ static __global__ void gemm_finish_f32_kernel(const float* part, int splits, int
   }
 }
 
-// Workgroup tiles: how the four wavefronts share it, contraction steps in flight, and the share of the
-// matrix-core rate a full chip of them reaches (128 x 128 on 2048^3, the small ones on products they fill).
+// What a workgroup of a convolution costs: times its products at the matrix cores' rate, if it has a CU to itself and if two share
+// it, and us to begin and to store its results.
+struct F32ConvCost {
+  float alone, pair, begin;
+};
+// Workgroup tiles: how the four wavefronts share it, contraction steps in flight, the share of the
+// matrix-core rate a full chip of them reaches in products (128 x 128 on 2048^3, the small ones on products they fill), and
+// costs in convolutions whose output rows are whole groups of four pixels (`fours`) or not (`ones`: pixels are fetched one by one).
 struct F32Cfg {
   int bm, bn, wk, d;
   float eff;
+  F32ConvCost fours, ones;
 };
-// The last four are for convolutions: few channels, any number of pixels, whose wavefronts lie side by side along the
+// The last four are for convolutions alone: few channels, any number of pixels, whose wavefronts lie side by side along the
 // pixels so that a contraction of a few dozen steps is not dealt over them as well (64 rows, 65536 pixels, 18 steps:
 // 32 us against 43 with 64 x 64 tiles; 32 rows, 36 steps: 29 against 43 with 32 x 32 tiles; 64 rows, 25088 pixels, 72 steps,
 // layer 71 us with 32 x 32 tiles, 57 with 32 x 256, 60 with 64 x 128).
-static const F32Cfg kF32Cfgs[8] = {{128, 128, 1, 3, 0.85f}, {64, 64, 4, 3, 0.8f}, {32, 32, 4, 4, 0.6f}, {16, 16, 4, 8, 0.4f},
-                                   {64, 256, 1, 3, 0.94f}, {32, 256, 1, 4, 0.78f}, {64, 128, 1, 3, 0.79f}, {32, 128, 1, 4, 0.63f}};
+static const F32Cfg kF32Cfgs[8] = {{128, 128, 1, 3, 0.85f, {1.16f, 1.85f, 4.01f}, {1.15f, 2.49f, 8.81f}},
+                                   {64, 64, 4, 3, 0.8f, {1.07f, 1.59f, 4.25f}, {1.05f, 1.83f, 7.26f}},
+                                   {32, 32, 4, 4, 0.6f, {1.35f, 1.94f, 1.7f}, {2.41f, 2.2f, 1.59f}},
+                                   {16, 16, 4, 8, 0.4f, {2.96f, 3.14f, 0.93f}, {4.25f, 3.82f, 1.07f}},
+                                   {64, 256, 1, 3, 0.0f, {0.93f, 1.65f, 5.37f}, {1.06f, 2.75f, 10.79f}},
+                                   {32, 256, 1, 4, 0.0f, {1.21f, 1.84f, 1.72f}, {1.66f, 2.94f, 4.9f}},
+                                   {64, 128, 1, 3, 0.0f, {1.36f, 2.1f, 3.06f}, {1.2f, 2.7f, 3.34f}},
+                                   {32, 128, 1, 4, 0.0f, {1.49f, 1.83f, 1.75f}, {2.01f, 2.28f, 1.67f}}};
 
 template <int AK, int BK, int MODE>
 static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
@@ -192,17 +205,20 @@ int32_t f32_conv_product(const float* W, int rows, const float* grid, const F32C
   F.am = axis_identity(rows), F.bn = axis_identity(cv.npix), F.k = axis_identity(taps_cp);
   F.C = C, F.M = rows, F.N = cv.npix, F.splits = 1;
   F.cv = cv;
-  // Shares of the matrix-core rate and clocks of a memory round trip and of a workgroup's start and end in convolutions, fitted to
-  // forward passes and data gradients of 140 layers (8 - 128 images, 16 - 512 channels, 7 x 7 - 56 x 56, a third to all maps kept):
-  // the choice is 1.7 % off the best tile in the mean (products' values, without the last two tiles: 6.4 %).
-  static const float kConvEff[8] = {0.85f, 0.68f, 0.49f, 0.31f, 0.94f, 0.78f, 0.79f, 0.63f};
+  // Tile of the least estimated time.  Workgroups come two to a CU; up to four a CU the last pair, or single one, counts in full, beyond
+  // it starts here and there as others end.  Costs fitted to the products of 610 layers, forward and data gradient (8 - 128 images,
+  // 16 - 512 channels, 7 x 7 - 56 x 56, filters of 1, 3 and 5, a third to all maps kept); in 305 others the choice is 1.3 % off the
+  // best tile in the mean, 9 % at the 95th percentile (one share of the matrix-core rate per tile and whole rounds: 4.1 and 23 %),
+  // 1.1 and 1.5 % below and above 2.2 GFLOP.  21 images, 48 -> 192 channels of 56 x 56: 64 x 64 tiles 147 us, 64 x 256 170.
+  const bool fours = cv.Wo % 4 == 0;
   int cfg = 0;
   float best = 0.0f;
   for (int i = 0; i < 8; ++i) {
     const F32Cfg& c = kF32Cfgs[i];
-    const float rounds = (float)(((long)ceil_div(rows, c.bm) * ceil_div(cv.npix, c.bn) + 255) / 256), area = (float)c.bm * c.bn;
-    const float mfma = rounds * area * taps_cp * (2.0f / 256.0f) / kConvEff[i], chain = 1870.0f * ceil_div(imax(1, taps_cp / 16 / c.wk), c.d);
-    const float t = (mfma > chain ? mfma : chain) + rounds * (965.0f + 0.25f * area);
+    const F32ConvCost& w = fours ? c.fours : c.ones;
+    const long tiles = (long)ceil_div(rows, c.bm) * ceil_div(cv.npix, c.bn), whole = (tiles + 255) / 256;  // on the fullest CU
+    const float product = (float)c.bm * c.bn * taps_cp * (2.0f / (256.0f * 2400.0f)), two = 2.0f * w.pair * product + w.begin;  // us at 2.4 GHz
+    const float t = whole > 4 ? two * 0.25f * (tiles / 256.0f + whole) : two * (whole / 2) + (whole % 2 ? w.alone * product + w.begin : 0.0f);
     if (i == 0 || t < best) best = t, cfg = i;
   }
   F.tiles_m = ceil_div(rows, kF32Cfgs[cfg].bm), F.tiles_n = ceil_div(cv.npix, kF32Cfgs[cfg].bn);
@@ -211,7 +227,7 @@ int32_t f32_conv_product(const float* W, int rows, const float* grid, const F32C
   set_bands(F, direct_group_m(F.total_tiles));
   const int grid_x = direct_plain_grid(F.total_tiles);
   // (groups of four pixels are contiguous where output rows are whole numbers of them)
-  return cv.Wo % 4 == 0 ? launch_f32<F32_KC_VEC, F32_MC_VEC, 1>(F, cfg, grid_x, stream) : launch_f32<F32_KC_VEC, F32_MC, 1>(F, cfg, grid_x, stream);
+  return fours ? launch_f32<F32_KC_VEC, F32_MC_VEC, 1>(F, cfg, grid_x, stream) : launch_f32<F32_KC_VEC, F32_MC, 1>(F, cfg, grid_x, stream);
 }
 
 // Its weight gradient: part[split][co][tap*Cp + channel] = sum over the pixels of the grid planes of dY * A, both
