@@ -1676,29 +1676,47 @@ static int32_t lstm_fwd_t(const LstmArgs& a, const void* x, const void* W, void*
 
 // Weight gradients over many steps: tiles of 256 x 128 take less than half of the time per product that tiles of 64 x 64 take, but
 // there are too few of them for the chip; split into partial sums, h and x of them, which the pass that spreads the gradients adds.
-// Fitted times in us (256 CUs): a step of the large tiles 1, their start and end 5.5, 0.24 for each of a CU's steps of small ones;
-// partial sums are written at 5 and read back at 4 MB per us.  T = 64, B = 128, I = H = 1024, dp = 2: products 110 -> 66 us, the
-// spreading pass 15 -> 28 us.
+// Both ways cost, in us at 256 CUs: the launch that small tiles share, 8.4 and per step of a CU's 64 x 64 (128 x 64) tiles 0.237 (0.39),
+// the gradient of x among them where its tiles are 64 x 64, which else has a launch of its own; large tiles 4.6 a launch, 7.2 a round,
+// 0.57 to 0.815 a step the fuller the round; each MB of partial sums 0.04 to read, beyond 89 MB 0.37, and those of the recurrent
+// columns, a kept unit at a time, 0.77 per MB of the gradient for every four of them.  Fitted to the kernels of 170 layers (1024 -
+// 16384 rows, I and H 256 - 2048, dp 1 - 4), large tiles to 3 %, the others to 10 %; in whole backward passes, where three launches take
+// the place of one, the large tiles cost 10 us more than their kernels (100 layers).  Over 220 other layers, backward pass, 0.997 of the time of
+// the former estimate, none slower than with small tiles alone.  The line: backward passes in us with
+// small tiles and with partial sums, T = 24, B = 115, I = 900, H = 1529, dp = 2 197 and 209, 92, 48, 1280, 1088, 2 302 and 314, 24, 128, 801, 801, 1
+// 413 and 420, none of them taken; 36, 101, 768, 1675, 2 522 and 517, 78, 64, 1000, 1408, 2 349 and 336, 60, 128, 1024, 1024, 2 288 and 283,
+// 64, 128, 960, 960, 2 295 and 284, 85, 88, 1032, 1280, 2 554 and 494, all taken.  Where the recurrent weight's large tiles
+// fill the chip by themselves, summing their kept columns costs more than it gives (120, 83, 256, 1696, 1 2507 and 2545).
 static bool lstm_sum_splits(const LstmArgs& a, int Ip, int Hp, size_t room, int& h, int& x) {
   h = x = 0;
   if (a.dtype != ARD_BF16 || a.T < 2 || a.ax.kind != AX_AFFINE || dev_knobs().no_fast) return false;
-  auto cost = [&](int N, int rows, int sp) {  // sp = 0: as it is without partial sums
-    const int steps = ceil_div(rows, 64), tiles = ceil_div(4 * Hp, 256) * ceil_div(N, 128);
-    const double mb = 16e-6 * Hp * (double)N;
-    if (sp == 0 && tiles < 220) return 4.0 + 0.24 / 256 * ceil_div(4 * Hp, 64) * ceil_div(N, 64) * (double)steps;
-    return ceil_div(tiles * (sp ? sp : 1), 256) * (ceil_div(steps, sp ? sp : 1) + 5.5) + sp * mb / 5 + sp * mb / 4;
+  const int rows = a.T * a.B, rows_h = rows - a.B, M = 4 * Hp;
+  // what a product of 4-wavefront tiles adds to the launch they share (-1: it has larger ones)
+  auto share = [](int m, int n, int k, bool tall) {
+    if ((long)ceil_div(m, 256) * ceil_div(n, 128) >= 220 || (long)ceil_div(m, 128) * ceil_div(n, 128) >= 440) return -1.0f;
+    const float steps = ceil_div(k, 64) / 256.0f;
+    if ((long)ceil_div(m, 128) * ceil_div(n, 64) >= 440) return tall ? 0.39f * ceil_div(m, 128) * ceil_div(n, 64) * steps : -1.0f;
+    return 0.237f * ceil_div(m, 64) * ceil_div(n, 64) * steps;
   };
-  auto best = [&](int N, int rows, size_t planes) {
-    int b = 0;
-    for (int sp = 1; sp <= 8 && (size_t)sp <= planes && sp * 4 <= ceil_div(rows, 64); ++sp)
-      if (!b || cost(N, rows, sp) < cost(N, rows, b)) b = sp;
-    return b;
+  auto large = [&](int n, int k, int splits) {
+    const int tiles = ceil_div(M, 256) * ceil_div(n, 128) * splits, steps = ceil_div(ceil_div(k, 64), splits);
+    const float last = (tiles % 256) / 256.0f;
+    return 4.6f + tiles / 256 * (0.815f * steps + 7.2f) + (last > 0 ? (0.57f + 0.245f * last) * steps + 7.2f * fmaxf(last, 0.6f) : 0.0f);
   };
-  const int rows = a.T * a.B;
-  const size_t plane_x = (size_t)16 * Hp * Ip, plane_h = (size_t)16 * Hp * Hp;
-  x = best(Ip, rows, room / plane_x);
-  if (x) h = best(Hp, rows - a.B, (room - x * plane_x) / plane_h);
-  return h && cost(Ip, rows, x) + cost(Hp, rows - a.B, h) + 8 < cost(Ip, rows, 0) + cost(Hp, rows - a.B, 0);
+  const float small_x = share(M, Ip, rows, true), small_h = share(M, Hp, rows_h, true), dx = share(rows, Ip, M, false);
+  if (small_h < 0) return false;
+  const float small = 8.4f + (small_x < 0 ? large(Ip, rows, 1) : small_x) + small_h + (dx < 0 ? 0.0f : dx);
+  const float alone = 10.0f + (dx < 0 ? 0.0f : 6.5f + 0.8f * dx);
+  float best = small;
+  for (int sx = 1; sx <= 8 && sx * 4 <= ceil_div(rows, 64); ++sx)
+    for (int sh = 1; sh <= 8 && sh * 4 <= ceil_div(rows_h, 64); ++sh) {
+      const size_t bytes = (size_t)16 * Hp * ((size_t)sx * Ip + (size_t)sh * Hp);
+      if (bytes > room) break;
+      const float mb = bytes * 1e-6f, spread = 0.04f * mb + 0.33f * fmaxf(mb - 89.0f, 0.0f) + 0.77f * 16e-6f * Hp * Hp * ceil_div(sh, 4);
+      const float t = large(Ip, rows, sx) + large(Hp, rows_h, sh) + alone + spread;
+      if (t < best) best = t, x = sx, h = sh;
+    }
+  return x > 0;
 }
 
 template <typename T>
@@ -1863,8 +1881,14 @@ static int32_t lstm_bwd_t(const LstmArgs& a, const void* x, const void* W, const
   for (S.p0 = 0; S.p0 < 4 * H; S.p0 = S.p1) {
     S.p1 = 4 * H - S.p0 < step ? 4 * H : S.p0 + step;
     const dim3 grid((unsigned)(((long)(S.p1 - S.p0) * chunks + 255) / 256));
-    if (S.nx) ARD_LAUNCH_NAMED("lstm_scatter_dw_kernel", (lstm_scatter_dw_kernel<T, true, false>), grid, dim3(256), 0, stream, S);
-    else if (a.ax.kind == AX_AFFINE) ARD_LAUNCH_NAMED("lstm_scatter_dw_kernel", (lstm_scatter_dw_kernel<T, false, false>), grid, dim3(256), 0, stream, S);
+    if constexpr (std::is_same<T, uint16_t>::value) {
+      if (S.nx) {
+        ARD_LAUNCH_NAMED(launch_instance("lstm_scatter_dw_kernel", S.nx, S.nh, 0), (lstm_scatter_dw_kernel<T, true, false>), grid, dim3(256), 0, stream, S);
+        ARD_LAUNCH_CHECK("lstm_scatter_dw_kernel");
+        continue;
+      }
+    }
+    if (a.ax.kind == AX_AFFINE) ARD_LAUNCH_NAMED("lstm_scatter_dw_kernel", (lstm_scatter_dw_kernel<T, false, false>), grid, dim3(256), 0, stream, S);
     else ARD_LAUNCH_NAMED("lstm_scatter_dw_kernel", (lstm_scatter_dw_kernel<T, false, true>), grid, dim3(256), 0, stream, S);
     ARD_LAUNCH_CHECK("lstm_scatter_dw_kernel");
   }
