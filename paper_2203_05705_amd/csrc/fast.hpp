@@ -23,9 +23,10 @@
 // operands from registers, 300 launches in a row: 67 against 79 us for the FLOPs of a 4096^3 product, with the LDS reads of a
 // 256 x 256 tile beside them 84 against 90).  Three stages of 48 KB give the loads two steps to arrive (a step of a 256 x 128
 // tile is 1024 MFMA clocks, about what a load from the Infinity Cache takes), and issued as a burst the loads of a stage
-// hold up the MFMAs behind them.  Before and now, us: 4096^3, 64 x 64 tiles at dp = 2, forward 81 -> 72, data gradient 93 ->
-// 85, weight gradient 88 -> 78; 8192 x 2048 x 1024 43 -> 36; convolution products of 128 images of 28 x 28, 3 x 3: 128 -> 256
-// channels 76 -> 72 (256 x 256 tiles), its data gradient 71 -> 62, weight gradient 73 -> 66; listed pixels 60 -> 50, 62 -> 51.
+// hold up the MFMAs behind them.  Medians of the kernels in whole training steps, with two stages of 32x32x16 MFMAs and so, traced in
+// turn on one card, us: 4096^3, 64 x 64 tiles at dp = 2, forward 79 and 73, data gradient 93 and 80, weight gradient 88 and 83;
+// 8192 x 2048 x 1024 to fp32 55 and 42, 8192 x 1024 x 2048 43 and 37; convolution products of 128 images of 28 x 28, 3 x 3: 128 -> 256
+// channels 78 and 72 (256 x 256 tiles), its data gradient 72 and 62, weight gradient 73 and 66; listed pixels 60 and 51, 50 and 44.
 //
 // Tile patterns (Section 3.2) are period patterns over the linear tile index, so the tile
 // rows (or columns) fall into a few CLASSES that share one kept-column (kept-row) set:
@@ -411,9 +412,9 @@ __device__ __forceinline__ int mc_frag_base(int tile_col0, int lane) {
   return k * (ROWS * 2) + pc * 16 + 8 * (s & 1);
 }
 
-// LDS fragment reads are issued as volatile asm with ONE explicit wait per 16-wide slice: the
-// compiler cannot sink a read next to its consumer, so a slice's reads are in flight while
-// the previous slice's MFMAs run (left to itself the scheduler waits right after each read).
+// LDS fragment reads are issued as volatile asm with ONE explicit wait per unit (a 32-wide slice of a step by a part of the
+// wavefront's rows or columns): the compiler cannot sink a read next to its consumer, so a unit's reads are in flight while
+// the MFMAs of the one before run (left to itself the scheduler waits right after each read).
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 struct Frag {  // one MFMA operand: a full 16-byte read (KC) or two transposing 8-byte reads (MC)
@@ -835,19 +836,18 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
         for (int j = 0; j < decltype(la)::NI; ++j) la.issue_one(lds + buf * OPA, ao[j], wave, j);
 #pragma unroll
         for (int j = 0; j < decltype(lb)::NI; ++j) lb.issue_one(lds + NST * OPA + buf * OPB, bo[j], wave, j);
-        return;
       } else {
-      const int krem = Kn - (s_lo + it) * 64;
-      int ks, ksb;
-      slab(s_lo + it, ks, ksb);
-      const bool tail = krem < 64 || ks + 64 + kbump > kax.nphys;
-      if (__builtin_expect(tail, 0)) {
-        la.issue_tail(lds + buf * OPA, ks, krem, kax.nphys, lane, wave, kbump);
-        lb.issue_tail(lds + NST * OPA + buf * OPB, ksb, krem, MODE == 1 ? 0x7fffffff : kax.nphys, lane, wave, kbump);
-      } else {
-        la.issue(lds + buf * OPA, ks, wave);
-        lb.issue(lds + NST * OPA + buf * OPB, ksb, wave);
-      }
+        const int krem = Kn - (s_lo + it) * 64;
+        int ks, ksb;
+        slab(s_lo + it, ks, ksb);
+        const bool tail = krem < 64 || ks + 64 + kbump > kax.nphys;
+        if (__builtin_expect(tail, 0)) {
+          la.issue_tail(lds + buf * OPA, ks, krem, kax.nphys, lane, wave, kbump);
+          lb.issue_tail(lds + NST * OPA + buf * OPB, ksb, krem, MODE == 1 ? 0x7fffffff : kax.nphys, lane, wave, kbump);
+        } else {
+          la.issue(lds + buf * OPA, ks, wave);
+          lb.issue(lds + NST * OPA + buf * OPB, ksb, wave);
+        }
       }
     };
     // A step is 2 PARTS units: slice Q of 32 by part H of the wavefront's rows or columns, whichever are more.  The parts share
@@ -1068,8 +1068,9 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
   // through LDS (the operand stages are dead once every wave is past its last read) and leaves in 16-byte pieces of its
   // rows.  Straight from the registers, pairs of columns exchanged between lanes to make words, the way out took 18000 of
   // 123000 clocks of a 256 x 256 tile (K = 2048) and 37000 of 86000 of a 256 x 128 tile with fp32 results (K = 1024).
-  // 4096^3 in 64 x 64 tiles at dp = 2: 85, 101 and 91 us forward, data and weight gradient, now 79, 94 and 87; projection of
-  // 8192 x 1024 -> 2048 to fp32 67 -> 57 us; 128 x 4096 x 4096 in 32 x 32 tiles at dp = 3, weight gradient 20.8 -> 17.7 us.
+  // With the core of 32 x 32 x 16 MFMAs, before and after: 4096^3 in 64 x 64 tiles at dp = 2 85, 101 and 91 us forward, data and
+  // weight gradient, then 79, 94 and 87; projection of 8192 x 1024 -> 2048 to fp32 67, 57 us; 128 x 4096 x 4096 in 32 x 32 tiles at
+  // dp = 3, weight gradient 20.8, 17.7 us.
   constexpr int NT = 64 * NW;
   // (the 256 x 256 tile only stores plain results: bf16, and of operands along the contraction fp32)
   constexpr bool GENERAL_OUT = !(F_BM == 256 && BN == 256), WIDE_OUT = GENERAL_OUT || (A_KC && B_KC && MODE == 0);
@@ -1082,8 +1083,7 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
 #pragma unroll
     for (int im = 0; im < TM; ++im)
 #pragma unroll
-      for (int in = 0; in < TN; ++in)
-      {
+      for (int in = 0; in < TN; ++in) {
         float x[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) x[t] = acc[im][in][t];
@@ -1220,18 +1220,18 @@ __device__ __forceinline__ void direct_body(const FastParams& P, const int block
         int nj = imin(n1, n_valid) - (n0 + wn * WTN + 4 * (lane >> 4));
 #pragma unroll
         for (int in = 0; in < TN; ++in, at += 16 * sc, nj -= 16) {
-            // (opaque: worked out ahead, the places of all columns would take 100 registers, and whether they exist 70 scalar ones)
-            asm volatile("" : "+v"(at), "+v"(nj));
-            uint16_t* const o = img + at;
+          // (opaque: worked out ahead, the places of all columns would take 100 registers, and whether they exist 70 scalar ones)
+          asm volatile("" : "+v"(at), "+v"(nj));
+          uint16_t* const o = img + at;
 #pragma unroll
-            for (int t = 0; t < 4; t += 2) {
-              float x0 = P.alpha * acc[im][in][t], x1 = P.alpha * acc[im][in][t + 1];
-              if (P.relu) x0 = fmaxf(x0, 0.0f), x1 = fmaxf(x1, 0.0f);
-              const uint32_t w = pack_bf16x2(x0, x1);
-              if (t < nj) o[t * sc] = (uint16_t)w;
-              if (t + 1 < nj) o[(t + 1) * sc] = (uint16_t)(w >> 16);
-            }
+          for (int t = 0; t < 4; t += 2) {
+            float x0 = P.alpha * acc[im][in][t], x1 = P.alpha * acc[im][in][t + 1];
+            if (P.relu) x0 = fmaxf(x0, 0.0f), x1 = fmaxf(x1, 0.0f);
+            const uint32_t w = pack_bf16x2(x0, x1);
+            if (t < nj) o[t * sc] = (uint16_t)w;
+            if (t + 1 < nj) o[(t + 1) * sc] = (uint16_t)(w >> 16);
           }
+        }
       }
       __syncthreads();
       direct_scatter_rows(lds, pitch, P, m0 + r0, imin(m0 + r0 + rows_fit, m1), c_lo, c_hi, tid, NT);

@@ -553,8 +553,9 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   // convolutions and tiles that own no wider rows the setting up does (10.2 -> 10.8 us at 24 x 1472 -> 448 in tiles, 136.6 -> 138 us in
   // three products of a convolution).
   // Tiles of 32 x 32 only where columns are dropped too: 128 x 2048 -> 2048, dp 3 and 3 12.8 -> 11.1 us, 5 and 5 16.6 -> 12.7,
-  // 2 and 1 19.5 -> 20.0.  (Strided rows of A beside whole columns of B: a weight gradient whose columns are all kept, which the
-  // code alone makes longer, 64 x 784 -> 1024 18.66 -> 18.82 us for three products.)
+  // 2 and 1 19.5 -> 20.0.  (Not for strided rows of A beside neighbouring columns of B, where the loaders' kinds tell that columns are
+  // all kept but for one combination, a compact X with a dY that is not: the code alone, never run, makes such weight gradients
+  // longer, three products of 64 x 784 -> 1024 18.66 -> 18.85 us.)
   constexpr bool RUNS = MODE == 0 && (BM * BN >= 4096 || (BM * BN >= 1024 && !(AK == F32_MC && BK == F32_MC_VEC)));
   const bool runs = RUNS && !classes && beta == 0.0f && walk && (cols.step > 1 || (BM * BN >= 4096 && rows.n < rows.nphys));
   if constexpr (RUNS) if (runs) {

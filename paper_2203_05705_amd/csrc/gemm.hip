@@ -198,7 +198,7 @@ static bool try_direct(int32_t dtype, bool a_kc, bool b_kc, const GemmParams& P,
   long tiles = 0;
   const bool plain_out = !raw_splits && direct_out && (!C.out_f32 || (a_kc && b_kc)) && C.beta == 0.0f && !C.relu_src;
   for (const TileCfg& c : kTileCfgs) {
-    if (c.bm == 256 && c.bn == 256 && !plain_out) continue;  // that tile only stores plain bf16
+    if (c.bm == 256 && c.bn == 256 && !plain_out) continue;  // that tile only stores plain results: bf16, and of operands along the contraction fp32
     tiles = (long)ceil_div(P.M, c.bm) * ceil_div(P.N, c.bn);
     bm = c.bm, bn = c.bn;
     // An 8-wavefront tile wants a workgroup per CU; a 4-wavefront tile runs one wavefront per SIMD
