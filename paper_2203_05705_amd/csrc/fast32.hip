@@ -49,14 +49,14 @@ struct F32Cfg {
 // pixels so that a contraction of a few dozen steps is not dealt over them as well (64 rows, 65536 pixels, 18 steps:
 // 32 us against 43 with 64 x 64 tiles; 32 rows, 36 steps: 29 against 43 with 32 x 32 tiles; 64 rows, 25088 pixels, 72 steps,
 // layer 71 us with 32 x 32 tiles, 57 with 32 x 256, 60 with 64 x 128).
-static const F32Cfg kF32Cfgs[8] = {{128, 128, 1, 3, 0.85f, {1.16f, 1.85f, 4.01f}, {1.15f, 2.49f, 8.81f}},
-                                   {64, 64, 4, 3, 0.8f, {1.07f, 1.59f, 4.25f}, {1.05f, 1.83f, 7.26f}},
-                                   {32, 32, 4, 4, 0.6f, {1.35f, 1.94f, 1.7f}, {2.41f, 2.2f, 1.59f}},
-                                   {16, 16, 4, 8, 0.4f, {2.96f, 3.14f, 0.93f}, {4.25f, 3.82f, 1.07f}},
-                                   {64, 256, 1, 3, 0.0f, {0.93f, 1.65f, 5.37f}, {1.06f, 2.75f, 10.79f}},
-                                   {32, 256, 1, 4, 0.0f, {1.21f, 1.84f, 1.72f}, {1.66f, 2.94f, 4.9f}},
-                                   {64, 128, 1, 3, 0.0f, {1.36f, 2.1f, 3.06f}, {1.2f, 2.7f, 3.34f}},
-                                   {32, 128, 1, 4, 0.0f, {1.49f, 1.83f, 1.75f}, {2.01f, 2.28f, 1.67f}}};
+static const F32Cfg kF32Cfgs[8] = {{128, 128, 1, 3, 0.85f, {1.15f, 1.82f, 4.39f}, {1.17f, 2.51f, 8.88f}},
+                                   {64, 64, 4, 3, 0.8f, {1.08f, 1.57f, 4.31f}, {1.1f, 1.9f, 6.69f}},
+                                   {32, 32, 4, 4, 0.6f, {1.7f, 1.9f, 1.58f}, {2.23f, 2.25f, 1.62f}},
+                                   {16, 16, 4, 8, 0.4f, {3.03f, 3.08f, 0.99f}, {4.24f, 3.83f, 1.11f}},
+                                   {64, 256, 1, 3, 0.0f, {0.96f, 1.65f, 4.63f}, {1.1f, 2.77f, 10.48f}},
+                                   {32, 256, 1, 4, 0.0f, {1.13f, 1.83f, 1.9f}, {1.7f, 2.95f, 4.81f}},
+                                   {64, 128, 1, 3, 0.0f, {1.3f, 2.09f, 3.16f}, {1.22f, 2.71f, 3.38f}},
+                                   {32, 128, 1, 4, 0.0f, {1.48f, 1.82f, 1.77f}, {2.03f, 2.31f, 1.69f}}};
 
 template <int AK, int BK, int MODE>
 static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
@@ -206,10 +206,12 @@ int32_t f32_conv_product(const float* W, int rows, const float* grid, const F32C
   F.C = C, F.M = rows, F.N = cv.npix, F.splits = 1;
   F.cv = cv;
   // Tile of the least estimated time.  Workgroups come two to a CU; up to four a CU the last pair, or single one, counts in full, beyond
-  // it starts here and there as others end.  Costs fitted to the products of 610 layers, forward and data gradient (8 - 128 images,
-  // 16 - 512 channels, 7 x 7 - 56 x 56, filters of 1, 3 and 5, a third to all maps kept); in 305 others the choice is 1.3 % off the
-  // best tile in the mean, 9 % at the 95th percentile (one share of the matrix-core rate per tile and whole rounds: 4.1 and 23 %),
-  // 1.1 and 1.5 % below and above 2.2 GFLOP.  21 images, 48 -> 192 channels of 56 x 56: 64 x 64 tiles 147 us, 64 x 256 170.
+  // it starts here and there as others end.  Costs fitted to the products of 870 layers, forward and data gradient (610 of 8 - 128
+  // images, 16 - 512 channels, 7 x 7 - 56 x 56, filters of 1, 3 and 5, a third to all maps kept; 260 of up to 40 images and 12000
+  // pixels, contractions of up to 12800).  In 305 and 260 others the choice is 1.3 and 0.7 % off the best tile in the mean, 9 and 5 %
+  // at the 95th percentile (one share of the matrix-core rate per tile and whole rounds: 4.1 and 1.5, 23 and 11 %).  21 images, 48 ->
+  // 192 channels of 56 x 56: 64 x 64 tiles 147 us, 64 x 256 170; 8 images of 16 x 16, 33 of 110 channels <- 248, 5 x 5, data
+  // gradient: 16 x 16 tiles 5 us less than 32 x 32.
   const bool fours = cv.Wo % 4 == 0;
   int cfg = 0;
   float best = 0.0f;
