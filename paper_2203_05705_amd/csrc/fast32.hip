@@ -58,20 +58,31 @@ static const F32Cfg kF32Cfgs[8] = {{128, 128, 1, 3, 0.85f, {1.15f, 1.82f, 4.39f}
                                    {64, 128, 1, 3, 0.0f, {1.3f, 2.09f, 3.16f}, {1.22f, 2.71f, 3.38f}},
                                    {32, 128, 1, 4, 0.0f, {1.48f, 1.82f, 1.77f}, {2.03f, 2.31f, 1.69f}}};
 
+// Do the results of a 32 x 32 tile leave in runs of four physical columns (one store each, zeros of the dropped ones included)?  Where
+// columns lie three and more apart, or two and rows are dropped as well: 260 weight gradients of up to 1024 rows, 3072 x 4096 neurons, 0.97
+// of the time in the mean, 0.57 at best (128 x 2048 -> 2048, dp 3 and 3 12.8 -> 11.1 us, 5 and 5 16.6 -> 12.7); 220 forward products and data
+// gradients without compact layouts 0.99, 0.72 at best.  Every second column of whole rows: 1.01 and 1.00 in the mean (55 x 254 -> 2688, dp 1
+// and 2 6.95 -> 7.18 us), every column 19.5 -> 20.0 (128 x 2048 -> 2048, dp 2 and 1).
+static bool f32_leaves_in_runs(const F32Params& F) {
+  const OutMat& C = F.C;
+  return !F.part && F.tab.ncls == 0 && C.fill && C.beta == 0.0f && C.cn.kind == AX_AFFINE && (C.cn.step > 2 || (C.cn.step == 2 && C.rm.kind == AX_AFFINE && C.rm.step > 1));
+}
+
 template <int AK, int BK, int MODE>
 static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
   const F32Cfg& c = kF32Cfgs[cfg];
   const size_t lds = (size_t)c.wk * c.bm * (c.bn + 1) * 4 + (size_t)(c.bm * 3 > c.bm + c.bn ? c.bm * 3 : c.bm + c.bn) * 4;  // accumulators, tables
   const dim3 g((unsigned)grid), b(256);
-#define ARD_F32_CASE(I, ...)                                                                             \
+#define ARD_F32_CASE(I, ...) ARD_F32_INSTANCE(I, false, __VA_ARGS__)
+#define ARD_F32_INSTANCE(I, IN_RUNS, ...)                                                                \
   case I: {                                                                                              \
-    auto kernel = gemm_f32_kernel<AK, BK, __VA_ARGS__, MODE>;                                            \
+    auto kernel = gemm_f32_kernel<AK, BK, __VA_ARGS__, MODE, IN_RUNS>;                                   \
     static thread_local bool raised = false;                                                             \
     if (!raised && lds >= 65536) {                                                                       \
       ARD_HIP_CHECK(raise_lds_limit((const void*)kernel, (int)lds));                                     \
       raised = !dry_run();                                                                               \
     }                                                                                                    \
-    ARD_LAUNCH_NAMED(launch_instance("gemm_f32_kernel", c.bm, c.bn, MODE), kernel, g, b, lds, stream, F); \
+    ARD_LAUNCH_NAMED(launch_instance(IN_RUNS ? "gemm_f32_kernel<runs>" : "gemm_f32_kernel", c.bm, c.bn, MODE), kernel, g, b, lds, stream, F); \
     break;                                                                                               \
   }
   if constexpr (MODE == 1) {
@@ -83,7 +94,13 @@ static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
       default: break;
     }
   }
-  switch (cfg) {
+  const bool in_runs = MODE == 0 && cfg == 2 && f32_leaves_in_runs(F);
+  if constexpr (MODE == 0) {
+    if (in_runs) switch (cfg) {
+      ARD_F32_INSTANCE(2, true, 2, 2, 1, 1, 4, 4)
+    }
+  }
+  if (!in_runs) switch (cfg) {
     ARD_F32_CASE(0, 4, 4, 2, 2, 1, 3)
     ARD_F32_CASE(1, 4, 4, 1, 1, 4, 3)
     ARD_F32_CASE(2, 2, 2, 1, 1, 4, 4)
@@ -92,6 +109,7 @@ static int32_t launch_f32(F32Params& F, int cfg, int grid, hipStream_t stream) {
     default: return fail(ARD_EUNSUPPORTED, "no such fp32 tile");
   }
 #undef ARD_F32_CASE
+#undef ARD_F32_INSTANCE
   ARD_LAUNCH_CHECK("gemm_f32_kernel");
   return ARD_OK;
 }

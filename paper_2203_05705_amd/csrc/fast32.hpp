@@ -231,7 +231,7 @@ __device__ __forceinline__ void f32_pick(int n, const F& f) {
 // sum that ends finite had none; a wavefront with any other sum contracts again with the border's elements masked.  (Masks
 // in the one loop, 16 v_and for 64 MFMAs, took the gradient of the 32 x 32 layer in conv.hip from 33.6 to 36.5 - 39 us
 // wherever they were placed.)
-template <int AK, int BK, int TM, int TN, int WM, int WN, int WK, int D, int MODE>
+template <int AK, int BK, int TM, int TN, int WM, int WN, int WK, int D, int MODE, bool IN_RUNS>
 __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id, float* const lds) {
   constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, PITCH = BN + 1;
   static_assert(WM * WN * WK == 4, "four wavefronts");
@@ -552,12 +552,10 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   // summed twice and the pass that sums in place costs more (30 x 1024 -> 3000: 16.6 us, in runs 18.0); with tile classes,
   // convolutions and tiles that own no wider rows the setting up does (10.2 -> 10.8 us at 24 x 1472 -> 448 in tiles, 136.6 -> 138 us in
   // three products of a convolution).
-  // Tiles of 32 x 32 only where columns are dropped too: 128 x 2048 -> 2048, dp 3 and 3 12.8 -> 11.1 us, 5 and 5 16.6 -> 12.7,
-  // 2 and 1 19.5 -> 20.0.  (Not for strided rows of A beside neighbouring columns of B, where the loaders' kinds tell that columns are
-  // all kept but for one combination, a compact X with a dY that is not: the code alone, never run, makes such weight gradients
-  // longer, three products of 64 x 784 -> 1024 18.66 -> 18.85 us.)
-  constexpr bool RUNS = MODE == 0 && (BM * BN >= 4096 || (BM * BN >= 1024 && !(AK == F32_MC && BK == F32_MC_VEC)));
-  const bool runs = RUNS && !classes && beta == 0.0f && walk && (cols.step > 1 || (BM * BN >= 4096 && rows.n < rows.nphys));
+  // Tiles of 32 x 32 in an instance of their own (IN_RUNS, f32_leaves_in_runs): the code alone, not run, made other products longer
+  // (forward products 0.2 of 5.3 us, three products of 64 x 784 -> 1024 18.66 -> 18.85 us).
+  constexpr bool RUNS = MODE == 0 && (BM * BN >= 4096 || IN_RUNS);
+  const bool runs = IN_RUNS || (RUNS && !classes && beta == 0.0f && walk && (cols.step > 1 || rows.n < rows.nphys));
   if constexpr (RUNS) if (runs) {
     if constexpr (WK > 1) {  // the partial tiles, summed in place
       for (int e = tid; e < BM * BN; e += 256) {
@@ -742,10 +740,10 @@ __device__ __forceinline__ void f32_body(const F32Params& P, const int block_id,
   }
 }
 
-template <int AK, int BK, int TM, int TN, int WM, int WN, int WK, int D, int MODE>
+template <int AK, int BK, int TM, int TN, int WM, int WN, int WK, int D, int MODE, bool IN_RUNS = false>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const F32Params P) {
   extern __shared__ float f32_lds[];
-  f32_body<AK, BK, TM, TN, WM, WN, WK, D, MODE>(P, (int)blockIdx.x, f32_lds);
+  f32_body<AK, BK, TM, TN, WM, WN, WK, D, MODE, IN_RUNS>(P, (int)blockIdx.x, f32_lds);
 }
 
 }  // namespace ard
